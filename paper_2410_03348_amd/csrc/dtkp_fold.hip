@@ -1,14 +1,16 @@
 // Fused left fold of Apply under DTKP-AM (the loop of Fig. 2 with the top-k proofs provenance of Sec. 3.2 /
 // App. A) over naturally initialised inputs: symbol i of input t carries the single proof {fact_of_sym[t][i]}.
-// One wavefront owns a sample: the fact probabilities and the running Distribution's proofs (two buffers of
-// S x k masks and probabilities) live in LDS, a lane owns an output symbol, streams the candidates of its tuples
-// through a k-entry sorted list in registers and writes the list back to LDS for the next stage.  HBM sees the
-// fact probabilities once and the final Distribution once.  Optionally the gradient of the final tag
-// probabilities w.r.t. the fact probabilities follows in the same launch (lane f owns fact f).
+// One wavefront owns a sample: the fact probabilities and the running Distribution's proofs (S x k masks and
+// probabilities) live in LDS, a lane owns an output symbol, streams the candidates of its tuples through a k-entry
+// sorted list in registers and writes the list back to LDS for the next stage.  Up to four wavefronts form a
+// workgroup and share one copy of the symbol side.  HBM sees the fact probabilities once and the final Distribution
+// once.  Optionally the gradient of the final tag probabilities w.r.t. the fact probabilities follows in the same
+// launch (lane f owns fact f).
 // Candidate order, proof probabilities, exclusion test and list order are those of dol_apply2, so the result is the
 // same bit for bit.  The sorted list of a column carries probabilities and the origin of each proof; masks are built
 // for the k winners only, and a stage whose input brings only new, higher facts (fresh_t below) never reads one.
 #include "dtkp_util.h"
+#include "plan_cache.h"
 #include "wave_util.h"
 
 #include <cfloat>
@@ -17,19 +19,20 @@
 namespace dol {
 
 constexpr int kDfMax = 32;              // most inputs of one fold
+constexpr int kDfWaves = 4;             // most wavefronts (samples) of one workgroup
 
 // The symbol side of the whole fold as one array of words, copied into LDS at the start of the kernel:
 //   [0] number of inputs n, then for t = 0 .. n-1 four words: S_t, p_t, r_t, fresh_t
 //   t = 0:  S_0 words at p_0: the facts of the first input's symbols
 //   t >= 1: S_t + 1 words at p_t: where each output column's tuples start and end inside the stage's records;
 //           the records at r_t, one per tuple in column order: first operand's symbol | second operand's FACT << 16
-//           (one spare record at the end so that the read-ahead stays inside)
+//           (two spare records at the end so that the read-ahead stays inside)
 //   fresh_t = 1: every fact of input t lies above every fact of the inputs before it and shares no exclusion group
 //           with any of them.  A proof of the running Distribution then never holds the new fact or a rival of it, and
 //           the product over ascending facts is the proof's stored probability times the new fact's: the stage needs
 //           no mask at all until its k winners are known.
 struct DtkpFoldArgs {
-    int32_t n, batch, n_facts, max_s, n_words;
+    int32_t n, batch, n_facts, max_s, n_words, wave_bytes;
     const int32_t *words;
     const uint64_t *rival;              // device [n_facts]: the other facts of each fact's exclusion group
     const float *fact_prob;
@@ -42,28 +45,63 @@ struct DtkpFoldArgs {
     float *gfact;
 };
 
+// Sorts p[0 .. N-1] (with the ids beside them) in descending order when p falls and then rises, as the elementwise maxima
+// of a descending and an ascending list do: the bitonic network of the next power of two with its tail taken as +infinity,
+// of which only the exchanges between real entries remain (2 for N = 3, 5 for N = 5, 9 for N = 7).
+template <int N, int K>
+__device__ __forceinline__ void sort_valley(float (&p)[K], int (&id)[K], int at)
+{
+    if constexpr (N > 1) {
+        constexpr int M = N > 4 ? 4 : N > 2 ? 2 : 1;     // half of the next power of two: N <= 8
+        constexpr int H = N - M;
+        float hp[H], lp[M];
+        int hi[H], li[M];
+#pragma unroll
+        for (int x = 0; x < M; ++x) {
+            if (x < H) {
+                const int xh = x < H ? x : 0;
+                const bool keep = p[at + x] > p[at + x + M];
+                hp[xh] = keep ? p[at + x] : p[at + x + M], lp[x] = keep ? p[at + x + M] : p[at + x];
+                hi[xh] = keep ? id[at + x] : id[at + x + M], li[x] = keep ? id[at + x + M] : id[at + x];
+            } else {
+                lp[x] = p[at + x], li[x] = id[at + x];
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < H; ++x) p[at + x] = hp[x], id[at + x] = hi[x];
+#pragma unroll
+        for (int x = 0; x < M; ++x) p[at + H + x] = lp[x], id[at + H + x] = li[x];
+        sort_valley<H, K>(p, id, at);
+        sort_valley<M, K>(p, id, at + H);
+    }
+}
+
 // One stage of the fold for this wavefront's sample: the columns of the stage's table, a lane each.  KA: slots of the
 // first operand's lists that can hold a proof (1 right after the natural initialisation); FRESH: see fresh_t above.
-// Absent slots carry the probability -1 in LDS (0 in the result tensors).
+// Absent slots carry the probability -1 in LDS (0 in the result tensors); in the registers slot x is -1 - x, so that
+// absent slots never tie.
 // The list keeps, per rank, the probability and where the proof came from (record, slot of the first operand's list);
-// the masks are put together for the k winners only.  A candidate whose probability differs from every kept one
-// finds its rank by comparing probabilities alone; one that ties (duplicates of a kept proof always do) takes the
-// full comparison of the list's contract.
+// the masks are put together for the k winners only.  In a FRESH stage a tuple's k candidates are the first operand's
+// list times one factor, i.e. in descending order already: the k best of both lists are the elementwise maxima of one and
+// the other reversed, sorted again by a short network.  Equal probabilities among the kept ones, or on either side of the
+// cut, are the only cases in which masks matter: such a tuple is redone candidate by candidate from the list before it.
+// (Compare/select code bound by the vector ALUs: k = 5 costs about 65 instructions a tuple, against 5 x 33 when every
+// candidate was inserted by itself.  Sum-5, k = 3, B = 1024: 16.2 -> 10.5 us a pass; Sum-6, k = 5 with a target's
+// gradient, B = 12 000: 870 -> 132 us, of which the gradient, which walked every proof of every column, was most.)
 template <int K, int KA, bool FRESH>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,
                                                 float *np, const uint64_t *rival, const float *fp, float *gh)
 {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & (kWave - 1);
     for (int c = lane; c < S; c += kWave) {
         float tp[K];
         int tid_[K];
 #pragma unroll
-        for (int x = 0; x < K; ++x) { tp[x] = -1.0f; tid_[x] = -1; }
-        auto mask_of = [&](int id) -> uint64_t {
-            const int q = id / K, x = id - q * K;
-            const uint32_t r = l_rec[q];
-            return cm[static_cast<int>(r & 0xffffu) * K + x] | (uint64_t(1) << (r >> 16));
+        for (int x = 0; x < K; ++x) { tp[x] = -1.0f - x; tid_[x] = -1; }
+        auto mask_of = [&](int id) -> uint64_t {            // id = record << 3 | slot (at most DOL_MAX_K = 8 slots)
+            const uint32_t r = l_rec[id >> 3];
+            return cm[static_cast<int>(r & 0xffffu) * K + (id & 7)] | (uint64_t(1) << (r >> 16));
         };
         // the full comparison: equal masks are one proof, order by probability, then by mask
         auto insert_tied = [&](uint64_t mask, float pr, int id) {
@@ -83,9 +121,10 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                 else if (here) { tp[y] = pr; tid_[y] = id; }
             }
         };
-        // offer < 0: nothing to offer (below every slot, absent ones included)
+        // offer = kNone: nothing to offer (below every slot, absent ones included)
         // (the kept probabilities are in descending order and the offer equals none of them: the new list is the larger
         // of the first and the offer, then the median of each neighbouring pair and the offer)
+        constexpr float kNone = -32.0f;
         auto insert_untied = [&](float offer, int id) {
             bool gt[K];
 #pragma unroll
@@ -98,26 +137,70 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
             }
         };
         const uint32_t q0 = l_ptr[c], q1 = l_ptr[c + 1];
-        uint32_t rec = l_rec[q0];
-        for (uint32_t q = q0; q < q1; ++q) {
-            const int i = static_cast<int>(rec & 0xffffu), fb = static_cast<int>(rec >> 16);
-            rec = l_rec[q + 1];                 // the next tuple's record is on its way while this one is worked on
-            const float pb = 1.0f * fp[fb];
-            if constexpr (FRESH) {
-                float pa[KA];
+        if constexpr (FRESH) {
+            // a tuple's record is read two tuples ahead and its operands one ahead; records past the last one are the
+            // spare ones behind every array, which name operands that exist
+            float pa[KA], pb;
+            auto fetch = [&](uint32_t r) {
+                pb = fp[r >> 16];
 #pragma unroll
-                for (int x = 0; x < KA; ++x) pa[x] = cp[i * K + x];
+                for (int x = 0; x < KA; ++x) pa[x] = cp[static_cast<int>(r & 0xffffu) * K + x];
+            };
+            uint32_t rec = l_rec[q0], rec_next = l_rec[q0 + 1];
+            fetch(rec);
+            for (uint32_t q = q0; q < q1; ++q) {
+                const uint32_t cur = rec;
+                float offer[KA];
 #pragma unroll
-                for (int x = 0; x < KA; ++x) {
-                    const float offer = pa[x] >= 0.0f ? pa[x] * pb : -2.0f;
-                    const int id = static_cast<int>(q) * K + x;
-                    bool tie = false;
+                for (int x = 0; x < KA; ++x) offer[x] = pa[x] >= 0.0f ? pa[x] * pb : kNone;
+                rec = rec_next;
+                rec_next = l_rec[q + 2];
+                fetch(rec);
+                const int id0 = static_cast<int>(q) << 3;
+                bool tie = false;
+                if constexpr (KA == K && K > 1) {
+                    float mp[K];
+                    int mi[K];
+                    float cut = 2.0f * kNone;           // the best of the candidates and kept ones that drop out
 #pragma unroll
-                    for (int y = 0; y < K; ++y) tie |= offer == tp[y];
-                    if (tie) insert_tied(cm[i * K + x] | (uint64_t(1) << fb), offer, id);
-                    else insert_untied(offer, id);
+                    for (int x = 0; x < K; ++x) {
+                        const float o = offer[K - 1 - x];
+                        const bool keep = tp[x] > o;
+                        mp[x] = keep ? tp[x] : o;
+                        mi[x] = keep ? tid_[x] : id0 + (K - 1 - x);
+                        cut = fmaxf(cut, keep ? o : tp[x]);
+                    }
+                    sort_valley<K, K>(mp, mi, 0);
+#pragma unroll
+                    for (int x = 0; x + 1 < K; ++x) tie |= mp[x] == mp[x + 1];
+                    tie |= mp[K - 1] == cut;
+                    if (!tie) {
+#pragma unroll
+                        for (int x = 0; x < K; ++x) { tp[x] = mp[x]; tid_[x] = mi[x]; }
+                    }
+                } else {
+#pragma unroll
+                    for (int y = 0; y < K; ++y) tie |= offer[0] == tp[y];
+                    insert_untied(tie ? kNone : offer[0], id0);
                 }
-            } else {
+                if (__builtin_expect(tie, 0)) {
+#pragma unroll
+                    for (int x = 0; x < KA; ++x) {
+                        if (offer[x] < 0.0f) continue;
+                        bool t2 = false;
+#pragma unroll
+                        for (int y = 0; y < K; ++y) t2 |= offer[x] == tp[y];
+                        if (t2) insert_tied(cm[static_cast<int>(cur & 0xffffu) * K + x] | (uint64_t(1) << (cur >> 16)), offer[x], id0 | x);
+                        else insert_untied(offer[x], id0 | x);
+                    }
+                }
+            }
+        } else {
+            uint32_t rec = l_rec[q0];
+            for (uint32_t q = q0; q < q1; ++q) {
+                const int i = static_cast<int>(rec & 0xffffu), fb = static_cast<int>(rec >> 16);
+                rec = l_rec[q + 1];                 // the next tuple's record is on its way while this one is worked on
+                const float pb = fp[fb];
                 uint64_t ma[KA];
                 float pa[KA];
 #pragma unroll
@@ -133,31 +216,32 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                     const bool plain = (ma[x] & mb) || ma[x] < mb;
                     float pr = (ma[x] & mb) ? pa[x] : pa[x] * pb;
                     if (ok && !plain) pr = proof_prob(ma[x] | mb, fp);
-                    const int id = static_cast<int>(q) * K + x;
+                    const int id = static_cast<int>(q) << 3 | x;
                     bool tie = false;
 #pragma unroll
                     for (int y = 0; y < K; ++y) tie |= pr == tp[y];
                     if (ok && tie) insert_tied(ma[x] | mb, pr, id);
-                    else insert_untied(ok ? pr : -2.0f, id);
+                    else insert_untied(ok ? pr : kNone, id);
                 }
             }
         }
         float sum = 0.0f;
         uint64_t wm[K];
-        float wp[K];
 #pragma unroll
         for (int x = 0; x < K; ++x) {
             const bool present = tid_[x] >= 0;
-            wm[x] = present ? mask_of(tid_[x]) : kAbsent;
-            wp[x] = present ? tp[x] : 0.0f;
+            const uint64_t m = mask_of(max(tid_[x], 0));
+            wm[x] = present ? m : kAbsent;
+            sum = present ? sum + tp[x] : sum;
+        }
+        // a Distribution of at most 64 symbols is replaced in place: every lane has read what it needs by now
+        wave_lds_fence();
+#pragma unroll
+        for (int x = 0; x < K; ++x) {
             nm[c * K + x] = wm[x];
-            np[c * K + x] = present ? tp[x] : -1.0f;
-            if (present) sum = sum + tp[x];
+            np[c * K + x] = tid_[x] >= 0 ? tp[x] : -1.0f;
         }
         if (last) {
-            const int64_t o = (s * S + c) * K;
-#pragma unroll
-            for (int x = 0; x < K; ++x) { A.om[o + x] = wm[x]; A.op[o + x] = wp[x]; }
             const float pr = fminf(sum, 1.0f);
             A.oprob[s * A.ldo + c] = pr;
             if (A.gfact) {                      // upstream gradient, gated by the clamp (passes on sum <= 1)
@@ -171,40 +255,40 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
 }
 
 template <int K>
-__global__ void __launch_bounds__(kWave)
+__global__ void __launch_bounds__(kDfWaves * kWave)
 dtkp_fold_kernel(const DtkpFoldArgs A)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    // masks of both buffers, rivals, probabilities of both buffers, fact probabilities, gated gradients, symbol side
-    uint64_t *bufm = reinterpret_cast<uint64_t *>(lds_raw);
-    uint64_t *rival = bufm + 2 * A.max_s * K;
-    float *bufp = reinterpret_cast<float *>(rival + 64);
-    float *fp = bufp + 2 * A.max_s * K;
+    // shared by the workgroup: rivals, symbol side; then per wavefront: masks and probabilities (two buffers where a
+    // Distribution has more than 64 symbols, else one), fact probabilities, gated gradients
+    uint64_t *rival = reinterpret_cast<uint64_t *>(lds_raw);
+    uint32_t *const wl = reinterpret_cast<uint32_t *>(rival + 64);
+    const uint32_t *w = wl;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    const int bufs = A.max_s > kWave ? 2 : 1, flip = (bufs - 1) * A.max_s * K;
+    unsigned char *mine_lds = lds_raw + 64 * sizeof(uint64_t) + sizeof(uint32_t) * A.n_words + static_cast<size_t>(wave) * A.wave_bytes;
+    uint64_t *bufm = reinterpret_cast<uint64_t *>(mine_lds);
+    float *bufp = reinterpret_cast<float *>(bufm + bufs * A.max_s * K);
+    float *fp = bufp + bufs * A.max_s * K;
     float *gh = fp + 64;
-    // the symbol side starts at the next multiple of 16 bytes
-    const uint32_t w_off = (static_cast<uint32_t>(reinterpret_cast<unsigned char *>(gh + A.max_s) - lds_raw) + 15u) & ~15u;
-    const uint32_t *w = reinterpret_cast<const uint32_t *>(lds_raw + w_off);
-    const int lane = threadIdx.x;
-    const int64_t s = blockIdx.x;
-    const float my_fp = lane < A.n_facts ? A.fact_prob[s * A.n_facts + lane] : 1.0f;
-    const uint64_t my_rival = lane < A.n_facts ? A.rival[lane] : 0;
-    {   // 16 bytes per lane and four loads in flight: the words are the same for every sample and sit in L2, so what
+    const int64_t s = static_cast<int64_t>(blockIdx.x) * (blockDim.x / kWave) + wave;
+    const bool live = s < A.batch;
+    const float my_fp = live && lane < A.n_facts ? A.fact_prob[s * A.n_facts + lane] : 1.0f;
+    {   // 16 bytes per lane and two loads in flight: the words are the same for every sample and sit in L2, so what
         // this costs is round trips
-        uint4 *wl = reinterpret_cast<uint4 *>(lds_raw + w_off);
+        uint4 *dst = reinterpret_cast<uint4 *>(wl);
         const uint4 *src = reinterpret_cast<const uint4 *>(A.words);
-        const int n4 = A.n_words / 4;           // the host pads the array to whole 16-byte pieces
-        for (int base = 0; base < n4; base += 4 * kWave) {
-            uint4 v[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = src[min(base + k * kWave + lane, n4 - 1)];
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (base + k * kWave + lane < n4) wl[base + k * kWave + lane] = v[k];
+        const int n4 = A.n_words / 4, step = blockDim.x;      // the host pads the array to whole 16-byte pieces
+        for (int base = threadIdx.x; base < n4; base += 2 * step) {
+            const uint4 v0 = src[base], v1 = src[min(base + step, n4 - 1)];
+            dst[base] = v0;
+            if (base + step < n4) dst[base + step] = v1;
         }
+        if (threadIdx.x < 64) rival[threadIdx.x] = static_cast<int>(threadIdx.x) < A.n_facts ? A.rival[threadIdx.x] : 0;
     }
     fp[lane] = my_fp;
-    rival[lane] = my_rival;
-    wave_lds_fence();
+    __syncthreads();
+    if (!live) return;                          // no barrier of the workgroup follows
     {   // natural initialisation (App. A.1)
         const int S0 = static_cast<int>(w[1]);
         const uint32_t *fact0 = w + w[2];
@@ -219,13 +303,13 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
     wave_lds_fence();
     int S = 0;
     for (int t = 1; t < A.n; ++t) {
-        const uint64_t *cm = bufm + ((t - 1) & 1) * A.max_s * K;
-        const float *cp = bufp + ((t - 1) & 1) * A.max_s * K;
-        uint64_t *nm = bufm + (t & 1) * A.max_s * K;
-        float *np = bufp + (t & 1) * A.max_s * K;
-        S = static_cast<int>(w[1 + 4 * t]);
+        const uint64_t *cm = bufm + ((t - 1) & 1) * flip;
+        const float *cp = bufp + ((t - 1) & 1) * flip;
+        uint64_t *nm = bufm + (t & 1) * flip;
+        float *np = bufp + (t & 1) * flip;
+        S = __builtin_amdgcn_readfirstlane(static_cast<int>(w[1 + 4 * t]));
         const uint32_t *l_ptr = w + w[2 + 4 * t], *l_rec = w + w[3 + 4 * t];
-        const bool last = t == A.n - 1, fresh = w[4 + 4 * t] != 0;
+        const bool last = t == A.n - 1, fresh = __builtin_amdgcn_readfirstlane(static_cast<int>(w[4 + 4 * t])) != 0;
         if (t == 1) {                       // the first operand is naturally initialised: one proof per symbol
             if (fresh) dtkp_fold_stage<K, 1, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh);
             else dtkp_fold_stage<K, 1, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh);
@@ -235,24 +319,43 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         }
         wave_lds_fence();
     }
+    // the proofs leave as one contiguous run per sample, in the order they have in LDS
+    const uint64_t *fm = bufm + ((A.n - 1) & 1) * flip;
+    {
+        const float *fq = bufp + ((A.n - 1) & 1) * flip;
+        const int64_t o = s * S * K;
+        for (int e = lane; e < S * K; e += kWave) {
+            A.om[o + e] = fm[e];
+            A.op[o + e] = fmaxf(fq[e], 0.0f);
+        }
+    }
     if (!A.gfact) return;
-    // d Pr / d p_f = sum over the kept proofs holding f of the product of their other facts (ascending symbol, rank)
-    const int n1 = A.n - 1;
-    const uint64_t *fm = bufm + (n1 & 1) * A.max_s * K;
+    // d Pr / d p_f = sum over the kept proofs holding f of the product of their other facts (ascending symbol, rank).
+    // Lane f owns fact f and holds its probability; a proof is the same for all lanes, so its facts are walked with
+    // scalar instructions and their probabilities read from the lanes that own them.  Columns without a gradient
+    // (all but one under a target) are passed over.
     const uint64_t mine = uint64_t(1) << lane;
     float acc = 0.0f;
-    for (int c = 0; c < S; ++c) {
-        const float g = gh[c];
+    for (int base = 0; base < S; base += kWave) {
+        const int c = base + lane;
+        const float g_l = c < S ? gh[c] : 0.0f;
+        for (uint64_t todo = __ballot(g_l != 0.0f); todo; todo &= todo - 1) {
+            const int cl = __builtin_ctzll(todo);
+            const float g = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(g_l), cl));
 #pragma unroll
-        for (int x = 0; x < K; ++x) {
-            const uint64_t mm = fm[c * K + x];
-            if (mm == kAbsent) continue;
-            float others = 1.0f;
-            for (uint64_t r = mm; r; r &= r - 1) {
-                const int j = __builtin_ctzll(r);
-                others = others * (j == lane ? 1.0f : fp[j]);
+            for (int x = 0; x < K; ++x) {
+                const uint64_t raw = fm[(base + cl) * K + x];
+                const uint64_t mm = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(raw))) |
+                                    (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(raw >> 32)))) << 32);
+                if (mm == kAbsent) continue;
+                float others = 1.0f;
+                for (uint64_t r = mm; r; r &= r - 1) {
+                    const int j = __builtin_ctzll(r);
+                    const float pj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_fp), j));
+                    others = others * (j == lane ? 1.0f : pj);
+                }
+                if (mm & mine) acc = __builtin_fmaf(g, others, acc);
             }
-            if (mm & mine) acc = __builtin_fmaf(g, others, acc);
         }
     }
     if (lane < A.n_facts) A.gfact[s * A.n_facts + lane] = acc;
@@ -262,31 +365,29 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
 
 using namespace dol;
 
-extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_prov *prov, void *hip_stream)
+namespace {
+
+// The symbol side of a fold: a function of the tables, the facts of the inputs' symbols and the exclusion groups, kept by
+// content (building it takes as long as the launch itself).
+struct DtkpFoldPlan {
+    DevArray<int32_t> words;
+    DevArray<uint64_t> rival;
+    int32_t n_words = 0, max_s = 0, s_last = 0;
+};
+
+Cache<DtkpFoldPlan> &g_fold_plans = *new Cache<DtkpFoldPlan>;      // never destroyed, as the other plan caches
+
+dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldPlan *p)
 {
-    if (!fold || !prov) return fail(DOL_EINVAL, "NULL argument");
-    if (prov->kind != DOL_DTKP) return fail(DOL_EINVAL, "dol_dtkp_fold_apply2 needs a DTKP provenance");
-    const int n = fold->n_inputs, K = prov->k;
-    if (n < 2 || n > kDfMax) return fail(n < 2 ? DOL_EINVAL : DOL_EUNSUPPORTED, "n_inputs = %d outside 2..%d", n, kDfMax);
-    if (K < 1 || K > DOL_MAX_K) return fail(DOL_EINVAL, "k = %d outside 1..%d", K, DOL_MAX_K);
-    if (prov->n_facts < 1 || prov->n_facts > 63) return fail(DOL_EINVAL, "n_facts = %d outside 1..63", prov->n_facts);
-    if (!fold->inputs || !fold->tables || !fold->fact_of_sym || !fold->out) return fail(DOL_EINVAL, "inputs, tables, fact_of_sym or out is NULL");
-    DtkpFoldArgs A{};
-    A.n = n;
-    A.n_facts = prov->n_facts;
+    const int n = fold->n_inputs;
     std::vector<int32_t> words(1 + 4 * static_cast<size_t>(n), 0);
     words[0] = n;
-    int32_t s_prev = 0, s_last = 0;
+    int32_t s_prev = 0;
     int32_t fact_hi = -1;                   // highest fact of the inputs so far
     uint64_t facts_seen = 0;
     for (int t = 0; t < n; ++t) {
         const dol_dist *d = fold->inputs[t];
-        if (!d) return fail(DOL_EINVAL, "inputs[%d] is NULL", t);
-        if (d->batch < 0 || d->n_sym < 1) return fail(DOL_ESHAPE, "inputs[%d] has a bad shape", t);
-        if (t == 0) A.batch = d->batch;
-        if (d->batch != A.batch) return fail(DOL_ESHAPE, "inputs[%d].batch = %d, inputs[0].batch = %d", t, d->batch, A.batch);
         const int32_t *fos = fold->fact_of_sym[t];
-        if (!fos) return fail(DOL_EINVAL, "fact_of_sym[%d] is NULL", t);
         for (int32_t i = 0; i < d->n_sym; ++i)
             if (fos[i] < 0 || fos[i] >= prov->n_facts)
                 return fail(DOL_EINVAL, "fact_of_sym[%d][%d] = %d outside 0..%d", t, i, fos[i], prov->n_facts - 1);
@@ -308,15 +409,14 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
             words[1] = d->n_sym;
             words[2] = static_cast<int32_t>(words.size());
             words.insert(words.end(), fos, fos + d->n_sym);
-            s_prev = s_last = A.max_s = d->n_sym;
+            s_prev = p->s_last = p->max_s = d->n_sym;
             continue;
         }
         const dol_fn_table *f = fold->tables[t - 1];
-        if (!f) return fail(DOL_EINVAL, "tables[%d] is NULL", t - 1);
         if (f->na != s_prev || f->nb != d->n_sym)
             return fail(DOL_ESHAPE, "tables[%d] is %d x %d, its operands have %d and %d symbols", t - 1, f->na, f->nb, s_prev, d->n_sym);
         if (f->n_out < 1) return fail(DOL_EUNSUPPORTED, "tables[%d] produces no symbol", t - 1);
-        if (words.size() + static_cast<size_t>(f->n_out) + static_cast<size_t>(f->n_tuples) + 2 > 16000)
+        if (words.size() + static_cast<size_t>(f->n_out) + static_cast<size_t>(f->n_tuples) + 3 > 16000)
             return fail(DOL_EUNSUPPORTED, "the tables of the fold do not fit in LDS");
         words[1 + 4 * t] = f->n_out;
         words[2 + 4 * t] = static_cast<int32_t>(words.size());
@@ -326,35 +426,92 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
             const uint32_t ij = f->h_col_ij[static_cast<size_t>(q)];
             words.push_back(static_cast<int32_t>((ij & 0xffffu) | (static_cast<uint32_t>(fos[ij >> 16]) << 16)));
         }
-        words.push_back(0);
-        s_prev = s_last = f->n_out;
-        A.max_s = f->n_out > A.max_s ? f->n_out : A.max_s;
+        words.insert(words.end(), 2, 0);
+        s_prev = p->s_last = f->n_out;
+        p->max_s = std::max(p->max_s, f->n_out);
     }
     while (words.size() % 4) words.push_back(0);
-    A.n_words = static_cast<int32_t>(words.size());
+    p->n_words = static_cast<int32_t>(words.size());
+    std::vector<uint64_t> rival(static_cast<size_t>(prov->n_facts), 0);      // the other facts of each fact's exclusion group
+    for (int f = 0; f < prov->n_facts && prov->fact_group; ++f)
+        for (int h = 0; h < prov->n_facts; ++h)
+            if (h != f && prov->fact_group[h] == prov->fact_group[f]) rival[f] |= uint64_t(1) << h;
+    hipError_t e;
+    if ((e = p->words.upload(words)) != hipSuccess || (e = p->rival.upload(rival)) != hipSuccess)
+        return hip_fail(e, "uploading the fold's tables");
+    return DOL_OK;
+}
+
+dol_status get_plan(const dol_dtkp_fold *fold, const dol_prov *prov, const DtkpFoldPlan **plan)
+{
+    int device = 0;
+    (void)hipGetDevice(&device);
+    const int n = fold->n_inputs;
+    std::vector<int32_t> desc{n, prov->n_facts, prov->fact_group ? 1 : 0};
+    desc.reserve(3 + static_cast<size_t>(prov->n_facts) + 24 * static_cast<size_t>(n));
+    if (prov->fact_group) desc.insert(desc.end(), prov->fact_group, prov->fact_group + prov->n_facts);
+    for (int t = 0; t < n; ++t) {
+        const uint64_t uid = t ? fold->tables[t - 1]->uid : 0;
+        desc.insert(desc.end(), {static_cast<int32_t>(uid), static_cast<int32_t>(uid >> 32), fold->inputs[t]->n_sym});
+        desc.insert(desc.end(), fold->fact_of_sym[t], fold->fact_of_sym[t] + fold->inputs[t]->n_sym);
+    }
+    std::vector<unsigned char> key = make_key(device, {{desc.data(), sizeof(int32_t) * desc.size()}});
+    const uint64_t h = hash_bytes(key.data(), key.size());
+    std::lock_guard<std::mutex> lock(g_fold_plans.mu);
+    if ((*plan = g_fold_plans.find(h, key)) != nullptr) return DOL_OK;
+    std::unique_ptr<DtkpFoldPlan> p(new (std::nothrow) DtkpFoldPlan);
+    if (!p) return fail(DOL_ENOMEM, "out of host memory");
+    if (dol_status st = build_plan(fold, prov, p.get())) return st;
+    *plan = g_fold_plans.insert(h, std::move(key), std::move(p));
+    return DOL_OK;
+}
+
+}  // namespace
+
+extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_prov *prov, void *hip_stream)
+{
+    if (!fold || !prov) return fail(DOL_EINVAL, "NULL argument");
+    if (prov->kind != DOL_DTKP) return fail(DOL_EINVAL, "dol_dtkp_fold_apply2 needs a DTKP provenance");
+    const int n = fold->n_inputs, K = prov->k;
+    if (n < 2 || n > kDfMax) return fail(n < 2 ? DOL_EINVAL : DOL_EUNSUPPORTED, "n_inputs = %d outside 2..%d", n, kDfMax);
+    if (K < 1 || K > DOL_MAX_K) return fail(DOL_EINVAL, "k = %d outside 1..%d", K, DOL_MAX_K);
+    if (prov->n_facts < 1 || prov->n_facts > 63) return fail(DOL_EINVAL, "n_facts = %d outside 1..63", prov->n_facts);
+    if (!fold->inputs || !fold->tables || !fold->fact_of_sym || !fold->out) return fail(DOL_EINVAL, "inputs, tables, fact_of_sym or out is NULL");
+    DtkpFoldArgs A{};
+    A.n = n;
+    A.n_facts = prov->n_facts;
+    for (int t = 0; t < n; ++t) {
+        const dol_dist *d = fold->inputs[t];
+        if (!d) return fail(DOL_EINVAL, "inputs[%d] is NULL", t);
+        if (d->batch < 0 || d->n_sym < 1) return fail(DOL_ESHAPE, "inputs[%d] has a bad shape", t);
+        if (t == 0) A.batch = d->batch;
+        if (d->batch != A.batch) return fail(DOL_ESHAPE, "inputs[%d].batch = %d, inputs[0].batch = %d", t, d->batch, A.batch);
+        if (!fold->fact_of_sym[t]) return fail(DOL_EINVAL, "fact_of_sym[%d] is NULL", t);
+        if (t && !fold->tables[t - 1]) return fail(DOL_EINVAL, "tables[%d] is NULL", t - 1);
+    }
+    const DtkpFoldPlan *plan = nullptr;
+    if (dol_status st = get_plan(fold, prov, &plan)) return st;
+    const int32_t s_last = plan->s_last;
+    A.max_s = plan->max_s;
+    A.n_words = plan->n_words;
+    A.words = plan->words.ptr;
+    A.rival = plan->rival.ptr;
     const dol_dist *o = fold->out;
     if (o->batch != A.batch || o->n_sym != s_last || o->ld < o->n_sym)
         return fail(DOL_ESHAPE, "out has %d x %d, the fold produces %d x %d", o->batch, o->n_sym, A.batch, s_last);
-    const size_t lds = static_cast<size_t>(2) * A.max_s * K * (sizeof(uint64_t) + sizeof(float)) + 64 * sizeof(uint64_t) +
-                       sizeof(float) * (64 + A.max_s) + 16 + sizeof(uint32_t) * words.size();
+    const size_t bufs = A.max_s > kWave ? 2 : 1;
+    const size_t wave_bytes = (bufs * A.max_s * K * (sizeof(uint64_t) + sizeof(float)) + sizeof(float) * (64 + A.max_s) + 15) & ~size_t(15);
+    const size_t shared_bytes = 64 * sizeof(uint64_t) + sizeof(uint32_t) * static_cast<size_t>(A.n_words);
+    // wavefronts to a workgroup: as many as fit 64 KB (the symbol side is a third of a lone wavefront's LDS for Sum-6 at
+    // k = 5, so four of them together fit a compute unit 28 times over instead of 11)
+    int waves = kDfWaves;
+    while (waves > 1 && shared_bytes + waves * wave_bytes > 64 * 1024) waves /= 2;
+    const size_t lds = shared_bytes + waves * wave_bytes;
     if (lds > 64 * 1024) return fail(DOL_EUNSUPPORTED, "the fold needs %zu bytes of LDS per sample, more than 65536", lds);
+    A.wave_bytes = static_cast<int32_t>(wave_bytes);
     if (A.batch == 0) return DOL_OK;
     if (!o->proof_mask || !o->proof_prob || !o->prob) return fail(DOL_EINVAL, "out.proof_mask, out.proof_prob or out.prob is NULL");
     if (!prov->fact_prob) return fail(DOL_EINVAL, "prov.fact_prob is NULL");
-    {   // rival[f]: the other facts of f's exclusion group (a device array cached by content)
-        std::vector<int32_t> words(2 * static_cast<size_t>(prov->n_facts), 0);
-        for (int f = 0; f < prov->n_facts && prov->fact_group; ++f) {
-            uint64_t r = 0;
-            for (int h = 0; h < prov->n_facts; ++h)
-                if (h != f && prov->fact_group[h] == prov->fact_group[f]) r |= uint64_t(1) << h;
-            words[2 * f] = static_cast<int32_t>(static_cast<uint32_t>(r));
-            words[2 * f + 1] = static_cast<int32_t>(static_cast<uint32_t>(r >> 32));
-        }
-        const int32_t *dptr = nullptr;
-        if (dol_status st = get_i32_array(2 * prov->n_facts, words.data(), &dptr)) return st;
-        A.rival = reinterpret_cast<const uint64_t *>(dptr);
-    }
-    if (dol_status st = get_i32_array(A.n_words, words.data(), &A.words)) return st;
     A.fact_prob = prov->fact_prob;
     A.om = o->proof_mask;
     A.op = o->proof_prob;
@@ -369,7 +526,7 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
         if (A.ldg < s_last) return fail(DOL_ESHAPE, "grad_out_ld = %lld is smaller than %d", static_cast<long long>(A.ldg), s_last);
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const dim3 grid(static_cast<unsigned>(A.batch)), block(kWave);
+    const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(A.batch) + waves - 1) / waves)), block(static_cast<unsigned>(waves * kWave));
 #define DOL_DF(KK) hipLaunchKernelGGL(dtkp_fold_kernel<KK>, grid, block, lds, st, A)
     switch (K) {
     case 1: DOL_DF(1); break;

@@ -90,6 +90,7 @@ __host__ __device__ static inline uint32_t pack16(uint32_t lo, uint32_t hi) { re
 // Eq. 1-2: admitted tuples grouped by the output column they land in (the "shuffle" stage),
 // plus the two transposed groupings the vector-Jacobian products walk.
 struct dol_fn_table {
+    uint64_t uid = 0;                    // never given to another table of this process (keys of plans over tables)
     int32_t na = 0, nb = 0, n_out = 0;
     int64_t n_tuples = 0;
     int32_t max_col_len = 0;             // most tuples landing in one column

@@ -1,8 +1,10 @@
 // Symbol side of the operators (Sec. 3.1.2): everything that depends only on the symbols and the
 // user function, computed once on the host for the whole batch and uploaded as index arrays.
 #include "internal.h"
+#include "plan_cache.h"
 
 #include <algorithm>
+#include <atomic>
 #include <cstring>
 #include <memory>
 #include <mutex>
@@ -73,6 +75,8 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
 
     std::unique_ptr<dol_fn_table> tb(new (std::nothrow) dol_fn_table);
     if (!tb) return fail(DOL_ENOMEM, "out of host memory");
+    static std::atomic<uint64_t> tables_made{0};
+    tb->uid = ++tables_made;
     tb->na = na;
     tb->nb = nb;
     tb->n_tuples = static_cast<int64_t>(tup.size());
@@ -245,63 +249,6 @@ static dol_status check_table_dims(int32_t na, int32_t nb, dol_fn_table **table)
 
 // ---------------------------------------------------------------- content-addressed plan caches
 
-static uint64_t fnv1a(const void *data, size_t n, uint64_t h = 1469598103934665603ull)
-{
-    const unsigned char *p = static_cast<const unsigned char *>(data);
-    for (size_t x = 0; x < n; ++x) h = (h ^ p[x]) * 1099511628211ull;
-    return h;
-}
-
-// At most kCacheMax plans per cache: a program whose predicates or symbol lists keep changing would otherwise grow the
-// caches without bound.  Beyond that the plan that has gone unused longest is released (hipFree waits for launches
-// that may still read its arrays; plans handed out earlier must not be used after kCacheMax newer ones were made).
-constexpr size_t kCacheMax = 4096;
-
-template <typename Plan>
-struct Cache {
-    struct Entry {
-        std::vector<unsigned char> key;
-        std::unique_ptr<Plan> plan;
-        uint64_t used = 0;
-    };
-    std::mutex mu;
-    std::unordered_multimap<uint64_t, Entry> map;
-    uint64_t clock = 0;
-
-    const Plan *find(uint64_t h, const std::vector<unsigned char> &key)
-    {
-        auto range = map.equal_range(h);
-        for (auto it = range.first; it != range.second; ++it)
-            if (it->second.key == key) { it->second.used = ++clock; return it->second.plan.get(); }
-        return nullptr;
-    }
-    const Plan *insert(uint64_t h, std::vector<unsigned char> &&key, std::unique_ptr<Plan> &&plan)
-    {
-        if (map.size() >= kCacheMax) {
-            auto oldest = map.begin();
-            for (auto it = map.begin(); it != map.end(); ++it)
-                if (it->second.used < oldest->second.used) oldest = it;
-            map.erase(oldest);
-        }
-        auto it = map.emplace(h, Entry{std::move(key), std::move(plan), ++clock});
-        return it->second.plan.get();
-    }
-};
-
-static std::vector<unsigned char> make_key(int device, std::initializer_list<std::pair<const void *, size_t>> parts)
-{
-    std::vector<unsigned char> key(sizeof(int));
-    std::memcpy(key.data(), &device, sizeof(int));
-    for (const auto &p : parts) {
-        const uint64_t n = p.second;
-        const unsigned char *nb = reinterpret_cast<const unsigned char *>(&n);
-        key.insert(key.end(), nb, nb + sizeof n);
-        const unsigned char *d = static_cast<const unsigned char *>(p.first);
-        if (n) key.insert(key.end(), d, d + n);
-    }
-    return key;
-}
-
 // (on the heap and never destroyed: no hipFree during static destruction, when the HIP runtime may already be down)
 static Cache<FilterPlan> &g_filter_cache = *new Cache<FilterPlan>;
 static Cache<UnionPlan> &g_union_cache = *new Cache<UnionPlan>;
@@ -313,7 +260,7 @@ dol_status get_filter_plan(int32_t n, const uint8_t *pred, const FilterPlan **pl
     std::vector<uint8_t> norm(static_cast<size_t>(n));
     for (int32_t i = 0; i < n; ++i) norm[i] = pred[i] ? 1 : 0;
     std::vector<unsigned char> key = make_key(device, {{norm.data(), norm.size()}});
-    const uint64_t h = fnv1a(key.data(), key.size());
+    const uint64_t h = hash_bytes(key.data(), key.size());
     std::lock_guard<std::mutex> lock(g_filter_cache.mu);
     if ((*plan = g_filter_cache.find(h, key)) != nullptr) return DOL_OK;
 
@@ -340,7 +287,7 @@ dol_status get_union_plan(int32_t na, const int32_t *sa, int32_t nb, const int32
     (void)hipGetDevice(&device);
     std::vector<unsigned char> key =
         make_key(device, {{sa, sizeof(int32_t) * static_cast<size_t>(na)}, {sb, sizeof(int32_t) * static_cast<size_t>(nb)}});
-    const uint64_t h = fnv1a(key.data(), key.size());
+    const uint64_t h = hash_bytes(key.data(), key.size());
     std::lock_guard<std::mutex> lock(g_union_cache.mu);
     if ((*plan = g_union_cache.find(h, key)) != nullptr) return DOL_OK;
 
@@ -383,7 +330,7 @@ dol_status get_filter_union_plan(int32_t n, const int32_t *sd, const uint8_t *pr
     std::vector<unsigned char> key = make_key(device, {{norm.data(), norm.size()},
                                                        {sd, sizeof(int32_t) * static_cast<size_t>(n)},
                                                        {sc, sizeof(int32_t) * static_cast<size_t>(nc)}});
-    const uint64_t h = fnv1a(key.data(), key.size());
+    const uint64_t h = hash_bytes(key.data(), key.size());
     std::lock_guard<std::mutex> lock(g_filter_union_cache.mu);
     if ((*plan = g_filter_union_cache.find(h, key)) != nullptr) return DOL_OK;
 
@@ -427,7 +374,7 @@ dol_status get_i32_array(int32_t n, const int32_t *data, const int32_t **dptr)
     int device = 0;
     (void)hipGetDevice(&device);
     std::vector<unsigned char> key = make_key(device, {{data, sizeof(int32_t) * static_cast<size_t>(n)}});
-    const uint64_t h = fnv1a(key.data(), key.size());
+    const uint64_t h = hash_bytes(key.data(), key.size());
     std::lock_guard<std::mutex> lock(g_i32_cache.mu);
     const I32Array *hit = g_i32_cache.find(h, key);
     if (!hit) {

@@ -435,6 +435,37 @@ def test_fused_dtkp_fold_when_a_stage_brings_no_new_facts(dol, k):
     assert_close(host(gf), oracle.dtkp_prob_bwd(m, fp, g), "fold gradient")
 
 
+@pytest.mark.parametrize("batch", [1, 6])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8])
+def test_fused_dtkp_fold_list_merge_with_ties(dol, k, batch):
+    """The fused fold where every input brings new facts, for every list length: probabilities from four values only (equal
+    probabilities inside a list, between lists and on either side of the k-th place, zeros among them), Distributions of
+    10, 100 and 109 symbols (in place up to 64, two buffers above), a last workgroup that is not full."""
+    sym = np.arange(10, dtype=np.int32)
+    fp = (W.splitmix64(k, np.arange(batch * 40)) % np.uint64(4)).astype(np.float32).reshape(batch, 40) / 4
+    grp = (np.arange(40) // 10).astype(np.int32)
+    for tabs in ([sym[:, None] * 10 + sym[None, :]] + [None, None], [None, None, None]):
+        m, pp, pr = oracle.dtkp_init(sym, fp, k)
+        syms, tables = sym, []
+        for t, tab in enumerate(tabs):
+            tab = W.sum_table(syms, sym) if tab is None else tab.astype(np.int32)
+            dm, _, _ = oracle.dtkp_init(10 * (t + 1) + sym, fp, k)
+            syms, m, pp, pr = oracle.dtkp_apply2(oracle.dense_to_triples(tab), syms.size, 10, k, grp, fp, m, dm)
+            tables.append(dol.FnTable.create_dense(tab))
+        digits = [dol.Dist(sym, torch.empty((batch, 10), device="cuda")) for _ in range(4)]
+        out = dol.Dist.empty(syms, batch, k=k)
+        gf = torch.empty((batch, 40), device="cuda")
+        target = (np.arange(batch) * 5 % syms.size).astype(np.int32)
+        dol.dtkp_fold_apply2(dol.DtkpFold(digits, [10 * t + sym for t in range(4)], tables, out, target_col=dev(target),
+                                          grad_fact_prob=gf), dol.Prov(dol.DTKP, k, dev(fp), grp))
+        np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), m)
+        np.testing.assert_array_equal(host(out.proof_prob), pp)
+        assert_close(host(out.prob), pr, "fold tag prob")
+        g = np.zeros((batch, syms.size), np.float32)
+        g[np.arange(batch), target] = -1.0 / np.maximum(pr[np.arange(batch), target], np.float32(1.17549435e-38))
+        assert_close(host(gf), oracle.dtkp_prob_bwd(m, fp, g), "fold gradient")
+
+
 # ---------------------------------------------------------------- config 5
 
 @pytest.mark.parametrize("batch,side,rounds", [(256, 32, 64), (33, 7, 20), (2, 3, 5)])
