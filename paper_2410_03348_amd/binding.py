@@ -120,8 +120,8 @@ def _ptr(a: Optional[np.ndarray], ct):
 
 def _stream(stream) -> C.c_void_p:
     """A torch stream, a raw handle, or None = torch's current stream."""
-    if stream is None:
-        stream = torch.cuda.current_stream()
+    if stream is None:                   # the handle alone: 0.2 us against 2.9 for a stream object, of 7 for a whole call
+        return C.c_void_p(torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()))
     if isinstance(stream, torch.cuda.Stream):
         return C.c_void_p(stream.cuda_stream)
     return C.c_void_p(int(stream))
