@@ -85,65 +85,6 @@ damp_apply2_fwd_kernel(Rows R, const uint32_t *__restrict__ col_ptr, const uint3
     });
 }
 
-// The same for wide operand rows, staged in LDS (element_map.h): both rows of the sample are copied in, then every
-// thread walks columns as above with its gathers served by LDS.
-__global__ void __launch_bounds__(kStageThreads)
-damp_apply2_fwd_staged_kernel(int32_t na, int32_t nb, int32_t S, int32_t parts, const uint32_t *__restrict__ order,
-                              const uint32_t *__restrict__ col_ptr, const uint32_t *__restrict__ col_ij,
-                              const uint4 *__restrict__ col_head,
-                              const float *__restrict__ a, int64_t lda, const float *__restrict__ b, int64_t ldb,
-                              float *__restrict__ out, int64_t ldo)
-{
-    extern __shared__ __align__(16) float lds_rows[];
-    float *ar = lds_rows, *br = lds_rows + ((na + 3) & ~3);
-    const int64_t s = blockIdx.x / static_cast<unsigned>(parts);
-    int c0, c1;
-    stage_part(S, parts, static_cast<int>(blockIdx.x - s * parts), c0, c1);
-    stage_row(ar, a + s * lda, na);
-    stage_row(br, b + s * ldb, nb);
-    __syncthreads();
-    // kStageUnroll columns per thread and pass, so that their index and head loads are in flight together
-    for (int r0 = c0 + threadIdx.x; r0 < c1; r0 += kStageUnroll * kStageThreads) {
-        uint32_t c[kStageUnroll];
-        uint4 h[kStageUnroll];
-#pragma unroll
-        for (int v = 0; v < kStageUnroll; ++v) {
-            const int r = min(r0 + v * kStageThreads, c1 - 1);
-            c[v] = order[r];                                               // lanes of a wavefront: columns of like length
-            h[v] = col_head[r];                                            // (the head table in that order: a coalesced load)
-        }
-#pragma unroll
-        for (int v = 0; v < kStageUnroll; ++v) {
-            if (r0 + v * kStageThreads >= c1) continue;
-            const uint32_t t[4] = {h[v].x, h[v].y, h[v].z, h[v].w};
-            float x[4], y[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {                                  // all eight reads at once (tuple (0, 0) for "none")
-                const uint32_t ij = t[u] != 0xFFFFFFFFu ? t[u] : 0u;
-                x[u] = ar[ij & 0xffffu];
-                y[u] = br[ij >> 16];
-            }
-            float acc = 0.0f;
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-                if (t[u] != 0xFFFFFFFFu) acc = __builtin_fmaf(x[u], y[u], acc);
-            if (t[3] != 0xFFFFFFFFu) {                                     // four or more tuples: the rest of the list
-                const uint32_t q0 = col_ptr[c[v]], q1 = col_ptr[c[v] + 1];
-                if (q1 - q0 > static_cast<uint32_t>(kLongTableCol)) continue;   // left to the wavefront-per-column kernel
-                for (uint32_t q = q0 + 4; q < q1; q += kGather) {
-                    uint32_t ij[kGather];
-#pragma unroll
-                    for (int u = 0; u < kGather; ++u) ij[u] = col_ij[min(q + u, q1 - 1)];
-#pragma unroll
-                    for (int u = 0; u < kGather; ++u)
-                        if (q + u < q1) acc = __builtin_fmaf(ar[ij[u] & 0xffffu], br[ij[u] >> 16], acc);
-                }
-            }
-            out[s * ldo + c[v]] = fminf(acc, 1.0f);
-        }
-    }
-}
-
 // One workgroup of 1, 4 or 16 wavefronts (by the table's longest column) per (sample, long column).  The lanes stride
 // over the column's tuples and their partial sums meet by shuffles and, between wavefronts, through LDS; this is not the order the clamp decision is defined in, so alongside the sum the lanes add up the
 // terms' magnitudes, which bounds how far the two orders can lie apart (n roundings of relative size 2^-24 each
@@ -197,106 +138,6 @@ damp_apply2_fwd_long_kernel(int32_t n_long, const uint32_t *__restrict__ long_co
     if (threadIdx.x == 0) out[s * ldo + c] = fminf(pre, 1.0f);
 }
 
-// Tables with a short second operand: one thread per (sample, column) walks the dense map one j at a time (index
-// loads coalesced, the gathers of neighbouring lanes adjacent wherever the function is monotone in i).  That is
-// not the order the clamp decision is defined in; the terms' magnitudes bound how far the two sums can lie apart,
-// and only a sum within that distance of 1 is taken again in the defining order.
-// (The maps have NBP >= nb rows, the extra ones empty.)
-template <int NBP>
-__global__ void __launch_bounds__(kThreads)
-damp_byj_fwd_kernel(Rows R, int32_t nb, const uint16_t *__restrict__ src, const uint32_t *__restrict__ col_ptr,
-                    const uint32_t *__restrict__ col_ij, const float *__restrict__ a, int64_t lda,
-                    const float *__restrict__ b, int64_t ldb, float *__restrict__ out, int64_t ldo)
-{
-    float y[NBP];                                   // the short operand's row of the sample at hand
-    int64_t s_held = -1;
-    for_each_element(R, [&](int64_t s, int c) {
-        const float *ar = a + s * lda, *br = b + s * ldb;
-        if (s != s_held) {
-#pragma unroll
-            for (int j = 0; j < NBP; ++j) y[j] = br[j < nb ? j : 0];
-            s_held = s;
-        }
-        uint16_t i[NBP];
-        float x[NBP];
-#pragma unroll
-        for (int j = 0; j < NBP; ++j) i[j] = src[static_cast<size_t>(j) * R.n + c];
-        if (i[0] == kByJWave) return;                                     // left to the wavefront-per-column kernel
-        if (i[0] == kByJList) {                                           // some j twice: the tuple list itself
-            out[s * ldo + c] = fminf(column_sum(ar, br, col_ij, col_ptr[c], col_ptr[c + 1]), 1.0f);
-            return;
-        }
-#pragma unroll
-        for (int j = 0; j < NBP; ++j) x[j] = i[j] != kByJNone ? ar[i[j]] : 0.0f;
-        float acc = 0.0f, mag = 0.0f;
-#pragma unroll
-        for (int j = 0; j < NBP; ++j) {
-            acc = __builtin_fmaf(x[j], y[j], acc);
-            mag = __builtin_fmaf(fabsf(x[j]), fabsf(y[j]), mag);
-        }
-        float pre = acc;
-        if (fabsf(acc - 1.0f) <= mag * (static_cast<float>(NBP + 2) * 1.1920929e-7f))
-            pre = column_sum(ar, br, col_ij, col_ptr[c], col_ptr[c + 1]);
-        out[s * ldo + c] = fminf(pre, 1.0f);
-    });
-}
-
-// The same with the first operand's row staged in LDS (element_map.h), for rows of thousands of tags: one workgroup
-// per (sample, part of the output row); the map is still read coalesced and the gathers become LDS reads (an empty
-// entry reads element 0 and counts as 0).
-template <int NBP>
-__global__ void __launch_bounds__(kStageThreads)
-damp_byj_fwd_staged_kernel(int32_t na, int32_t nb, int32_t S, int32_t parts, const uint16_t *__restrict__ src,
-                           const uint32_t *__restrict__ col_ptr, const uint32_t *__restrict__ col_ij,
-                           const float *__restrict__ a, int64_t lda, const float *__restrict__ b, int64_t ldb,
-                           float *__restrict__ out, int64_t ldo)
-{
-    extern __shared__ __align__(16) float a_row[];
-    const int64_t s = blockIdx.x / static_cast<unsigned>(parts);
-    int c0, c1;
-    stage_part(S, parts, static_cast<int>(blockIdx.x - s * parts), c0, c1);
-    const float *ar = a + s * lda, *br = b + s * ldb;
-    stage_row(a_row, ar, na);
-    float y[NBP];
-#pragma unroll
-    for (int j = 0; j < NBP; ++j) y[j] = br[j < nb ? j : 0];
-    __syncthreads();
-    for (int c = c0 + threadIdx.x; c < c1; c += kStageThreads) {
-        uint16_t i[NBP];
-        float x[NBP];
-#pragma unroll
-        for (int j = 0; j < NBP; ++j) i[j] = src[static_cast<size_t>(j) * S + c];
-        if (i[0] == kByJWave) continue;                                   // left to the wavefront-per-column kernel
-        if (i[0] == kByJList) {                                           // some j twice: the tuple list itself
-            out[s * ldo + c] = fminf(column_sum(ar, br, col_ij, col_ptr[c], col_ptr[c + 1]), 1.0f);
-            continue;
-        }
-#pragma unroll
-        for (int j = 0; j < NBP; ++j) {
-            const float v = a_row[i[j] != kByJNone ? i[j] : 0];
-            x[j] = i[j] != kByJNone ? v : 0.0f;
-        }
-        float acc = 0.0f, mag = 0.0f;
-#pragma unroll
-        for (int j = 0; j < NBP; ++j) {
-            acc = __builtin_fmaf(x[j], y[j], acc);
-            mag = __builtin_fmaf(fabsf(x[j]), fabsf(y[j]), mag);
-        }
-        float pre = acc;
-        if (fabsf(acc - 1.0f) <= mag * (static_cast<float>(NBP + 2) * 1.1920929e-7f))
-            pre = column_sum(ar, br, col_ij, col_ptr[c], col_ptr[c + 1]);
-        out[s * ldo + c] = fminf(pre, 1.0f);
-    }
-}
-
-#define DOL_DISPATCH_NBP(nbp, CALL) \
-    switch (nbp) {                  \
-    case 4: CALL(4); break;         \
-    case 8: CALL(8); break;         \
-    case 10: CALL(10); break;       \
-    default: CALL(16); break;       \
-    }
-
 static dol_status launch_fwd_waves(const dol_fn_table *f, const DevArray<uint32_t> &cols, int32_t n_huge, int32_t batch,
                                    const float *a, int64_t lda, const float *b, int64_t ldb, float *out, int64_t ldo,
                                    hipStream_t st)
@@ -321,7 +162,7 @@ dol_status launch_damp_apply2_fwd(const dol_fn_table *f, int32_t batch, const fl
 {
     if (batch == 0 || f->n_out == 0) return DOL_OK;
     {   // shape limits before anything is launched (a failing call leaves the outputs untouched)
-        const int64_t most = static_cast<int64_t>(std::max(f->long_cols.n, f->byj_wave_cols.n));
+        const int64_t most = static_cast<int64_t>(f->long_cols.n);
         if (batch * most > 0x7fffffffLL)
             return fail(DOL_EUNSUPPORTED, "batch x long table columns = %lld exceeds 2^31", static_cast<long long>(batch * most));
     }
@@ -331,39 +172,11 @@ dol_status launch_damp_apply2_fwd(const dol_fn_table *f, int32_t batch, const fl
     if (done) return DOL_OK;
     if (dol_status s2 = launch_damp_lds_fwd(f, batch, a, lda, b, ldb, out, ldo, st, &done)) return s2;
     if (done) return DOL_OK;
+    if (dol_status s2 = launch_sample_fwd(f, batch, a, lda, b, ldb, out, ldo, st, &done)) return s2;
+    if (done) return DOL_OK;
     const Rows R = rows_of(batch, f->n_out);
-    if (f->byj_fwd && byj_fwd_staged_ok(f)) {
-        const int32_t parts = stage_parts(batch, f->n_out);
-#define CALL(N)                                                                                                           \
-    {                                                                                                                     \
-        DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_byj_fwd_staged_kernel<N>), kStageMaxBytes));                    \
-        hipLaunchKernelGGL(damp_byj_fwd_staged_kernel<N>, dim3(static_cast<unsigned>(batch) * parts), dim3(kStageThreads), \
-                           sizeof(float) * f->na, st, f->na, f->nb, f->n_out, parts, f->byj_src.ptr, f->col_ptr.ptr,      \
-                           f->col_ij.ptr, a, lda, b, ldb, out, ldo);                                                      \
-    }
-        DOL_DISPATCH_NBP(f->byj_nbp, CALL)
-#undef CALL
-        DOL_HIP(hipGetLastError());
-        return launch_fwd_waves(f, f->byj_wave_cols, f->n_huge_byj_cols, batch, a, lda, b, ldb, out, ldo, st);
-    }
-    if (f->byj_fwd) {
-#define CALL(N) hipLaunchKernelGGL(damp_byj_fwd_kernel<N>, dim3(R.grid), dim3(kThreads), 0, st, R, f->nb, f->byj_src.ptr, \
-                                   f->col_ptr.ptr, f->col_ij.ptr, a, lda, b, ldb, out, ldo)
-        DOL_DISPATCH_NBP(f->byj_nbp, CALL)
-#undef CALL
-        DOL_HIP(hipGetLastError());
-        return launch_fwd_waves(f, f->byj_wave_cols, f->n_huge_byj_cols, batch, a, lda, b, ldb, out, ldo, st);
-    }
-    if (staged_fwd_ok(f)) {
-        const int32_t parts = stage_parts(batch, f->n_out);
-        DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_fwd_staged_kernel), kStageMaxBytes));
-        hipLaunchKernelGGL(damp_apply2_fwd_staged_kernel, dim3(static_cast<unsigned>(batch) * parts), dim3(kStageThreads),
-                           sizeof(float) * (((f->na + 3) & ~3) + f->nb), st, f->na, f->nb, f->n_out, parts, f->col_order.ptr,
-                           f->col_ptr.ptr, f->col_ij.ptr, reinterpret_cast<const uint4 *>(f->col_head_ord.ptr), a, lda, b, ldb, out, ldo);
-    } else {
-        hipLaunchKernelGGL(damp_apply2_fwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, f->col_ptr.ptr, f->col_ij.ptr,
-                           reinterpret_cast<const uint4 *>(f->col_head.ptr), a, lda, b, ldb, out, ldo);
-    }
+    hipLaunchKernelGGL(damp_apply2_fwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, f->col_ptr.ptr, f->col_ij.ptr,
+                       reinterpret_cast<const uint4 *>(f->col_head.ptr), a, lda, b, ldb, out, ldo);
     DOL_HIP(hipGetLastError());
     return launch_fwd_waves(f, f->long_cols, f->n_huge_cols, batch, a, lda, b, ldb, out, ldo, st);
 }
@@ -439,209 +252,6 @@ damp_apply2_bwd_kernel(Rows R, BwdTable T, const float *__restrict__ a, int64_t 
     });
 }
 
-// The same with the gated gradient row in LDS: one workgroup per sample first works out gh[c] = g[c] * [pre(c) <= 1] for
-// every column ONCE (a column's sum is re-derived only where out == 1), then every symbol of a and b adds up its tuples
-// from that row, in the order of its list.  The kernel above re-derives a column's decision for every tuple that reads
-// it: with many results at the clamp (the later rounds of a reachability sweep) that is most of its time.  Rows of more
-// than kLongTableRow tuples are summed by the whole workgroup: strided partial sums in list order, then the
-// wavefronts' totals in a fixed order.
-constexpr int kBwdStagedThreads = 1024;
-
-__global__ void __launch_bounds__(kBwdStagedThreads)
-damp_apply2_bwd_staged_kernel(BwdTable T, int32_t S, int32_t n_long, const uint32_t *__restrict__ long_rows,
-                              const float *__restrict__ a, int64_t lda, const float *__restrict__ b, int64_t ldb,
-                              const float *__restrict__ out, int64_t ldo, const float *__restrict__ g, int64_t ldg,
-                              float *__restrict__ ga, float *__restrict__ gb, int32_t accumulate)
-{
-    extern __shared__ float gh[];           // [S], then one float per wavefront
-    float *red = gh + S;
-    const int tid = threadIdx.x;
-    const int64_t s = blockIdx.x;
-    const float *ar = a + s * lda, *br = b + s * ldb, *outr = out + s * ldo, *gr = g + s * ldg;
-    for (int c = tid; c < S; c += kBwdStagedThreads)
-        gh[c] = gated_grad(gr[c], outr[c], ar, br, T.col_ptr, T.col_ij, static_cast<uint32_t>(c));
-    __syncthreads();
-    for (int x = tid; x < T.na + T.nb; x += kBwdStagedThreads) {
-        const bool is_a = x < T.na;
-        if (is_a ? !ga : !gb) continue;
-        const int r = is_a ? x : x - T.na;
-        const uint32_t *ent = is_a ? T.rowa_jc : T.rowb_ic;
-        const float *other = is_a ? br : ar;
-        const uint32_t q0 = (is_a ? T.rowa_ptr : T.rowb_ptr)[r], q1 = (is_a ? T.rowa_ptr : T.rowb_ptr)[r + 1];
-        if (q1 - q0 > static_cast<uint32_t>(kLongTableRow)) continue;
-        float acc = 0.0f;
-        for (uint32_t q = q0; q < q1; ++q) {
-            const uint32_t e = ent[q];
-            acc = __builtin_fmaf(gh[e >> 16], other[e & 0xffffu], acc);
-        }
-        float *dst = is_a ? ga + s * lda + r : gb + s * ldb + r;
-        *dst = (is_a ? (accumulate & 1) : (accumulate & 2)) ? *dst + acc : acc;
-    }
-    for (int l = 0; l < n_long; ++l) {
-        const int x = static_cast<int>(long_rows[l]);
-        const bool is_a = x < T.na;
-        if (is_a ? !ga : !gb) continue;     // (the same for every thread)
-        const int r = is_a ? x : x - T.na;
-        const uint32_t *ent = is_a ? T.rowa_jc : T.rowb_ic;
-        const float *other = is_a ? br : ar;
-        const uint32_t q0 = (is_a ? T.rowa_ptr : T.rowb_ptr)[r], q1 = (is_a ? T.rowa_ptr : T.rowb_ptr)[r + 1];
-        float acc = 0.0f;
-        for (uint32_t q = q0 + tid; q < q1; q += kBwdStagedThreads) {
-            const uint32_t e = ent[q];
-            acc = __builtin_fmaf(gh[e >> 16], other[e & 0xffffu], acc);
-        }
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) acc += __shfl_xor(acc, d, kWave);
-        __syncthreads();                    // (the last row's totals have been read)
-        if ((tid & (kWave - 1)) == 0) red[tid / kWave] = acc;
-        __syncthreads();
-        if (tid == 0) {
-            float tot = 0.0f;
-            for (int w = 0; w < kBwdStagedThreads / kWave; ++w) tot += red[w];
-            float *dst = is_a ? ga + s * lda + r : gb + s * ldb + r;
-            *dst = (is_a ? (accumulate & 1) : (accumulate & 2)) ? *dst + tot : tot;
-        }
-    }
-}
-
-// Tables the staged kernel takes: enough symbols to give a workgroup per sample its work, a result row that fits LDS.
-bool apply2_bwd_staged(const dol_fn_table *f)
-{
-    return f->n_out >= 256 && f->na + f->nb >= 1024 && sizeof(float) * (f->n_out + kBwdStagedThreads / kWave) <= kStageMaxBytes;
-}
-
-// Gradient of row i of a from the dense map, one j at a time (ascending j, the order of the row's tuple list), and
-// the row's shares gh * a[i] of the gradient of b (added to pb where SHARES).  `clamped`: some column of the sample may
-// sit at the clamp, so `out` has to be looked at.  Empty map entries read element 0 and count as 0.
-template <int NBP, bool SHARES>
-__device__ __forceinline__ float byj_row(const uint16_t *__restrict__ col_of, int32_t na, int i, bool clamped,
-                                         const float *__restrict__ gr, const float *__restrict__ outr,
-                                         const float *__restrict__ ar, const float *__restrict__ br,
-                                         const float (&bj)[NBP], const BwdTable &T, float (&pb)[NBP])
-{
-    uint16_t c[NBP];
-    float gv[NBP];
-#pragma unroll
-    for (int j = 0; j < NBP; ++j) c[j] = col_of[static_cast<size_t>(j) * na + i];
-#pragma unroll
-    for (int j = 0; j < NBP; ++j) gv[j] = gr[c[j] == kByJNone ? 0 : c[j]];
-    if (clamped) {
-#pragma unroll
-        for (int j = 0; j < NBP; ++j)
-            if (c[j] != kByJNone) gv[j] = gated_grad(gv[j], outr[c[j]], ar, br, T.col_ptr, T.col_ij, c[j]);
-    }
-    const float ai = SHARES ? ar[i] : 0.0f;
-    float acc = 0.0f;
-#pragma unroll
-    for (int j = 0; j < NBP; ++j) {
-        const float gh = c[j] == kByJNone ? 0.0f : gv[j];
-        acc = __builtin_fmaf(gh, bj[j], acc);
-        if (SHARES) pb[j] = __builtin_fmaf(gh, ai, pb[j]);
-    }
-    return acc;
-}
-
-// Backward for tables with a short second operand: a row i of a reads its columns from the dense map; rows of b walk
-// their lists as above.
-template <int NBP>
-__global__ void __launch_bounds__(kThreads)
-damp_byj_bwd_kernel(Rows R, BwdTable T, const uint16_t *__restrict__ col_of, const float *__restrict__ a, int64_t lda,
-                    const float *__restrict__ b, int64_t ldb, const float *__restrict__ out, int64_t ldo,
-                    const float *__restrict__ g, int64_t ldg, float *__restrict__ ga, float *__restrict__ gb,
-                    int32_t accumulate)
-{
-    float bj[NBP];                                  // the short operand's row of the sample at hand
-    int64_t s_held = -1;
-    for_each_element(R, [&](int64_t s, int x) {
-        const float *ar = a + s * lda, *br = b + s * ldb, *outr = out + s * ldo, *gr = g + s * ldg;
-        if (x < T.na) {
-            if (!ga) return;
-            float none[NBP];
-            if (s != s_held) {
-#pragma unroll
-                for (int j = 0; j < NBP; ++j) bj[j] = j < T.nb ? br[j] : 0.0f;
-                s_held = s;
-            }
-            const float acc = byj_row<NBP, false>(col_of, T.na, x, true, gr, outr, ar, br, bj, T, none);
-            float *dst = ga + s * lda + x;
-            *dst = (accumulate & 1) ? *dst + acc : acc;
-            return;
-        }
-        if (!gb) return;
-        const int r = x - T.na;
-        const uint32_t q0 = T.rowb_ptr[r], q1 = T.rowb_ptr[r + 1];
-        if (q1 - q0 > kLongTableRow) return;
-        const float acc = row_sum(0.0f, T.rowb_ic, q0, q1, 1, gr, outr, ar, ar, br, T.col_ptr, T.col_ij);
-        float *dst = gb + s * ldb + r;
-        *dst = (accumulate & 2) ? *dst + acc : acc;
-    });
-}
-
-// The same for wide operands (na + nb > 1024): one workgroup of 1024 threads owns a whole sample.  STAGED (the result
-// row fits LDS): a first pass copies the sample's gradient row into LDS, gated by the clamp (a column with out == 1 has
-// its sum taken again), and the rows then gather from LDS alone.  Otherwise a first pass over the sample's result row
-// tells whether any column sits at the clamp; if none does, the gate is open everywhere and `out` is not gathered
-// again.  Each thread also adds its rows' shares g^[col(i, j)] * a[i] of the gradient w.r.t. b[j] into registers; the
-// workgroup sums them, so the long rows of b need no launch of their own.
-constexpr int kByJRowThreads = 1024;
-
-template <int NBP, bool STAGED>
-__global__ void __launch_bounds__(kByJRowThreads)
-damp_byj_bwd_row_kernel(BwdTable T, int32_t S, const uint16_t *__restrict__ col_of, const float *__restrict__ a,
-                        int64_t lda, const float *__restrict__ b, int64_t ldb, const float *__restrict__ out, int64_t ldo,
-                        const float *__restrict__ g, int64_t ldg, float *__restrict__ ga, float *__restrict__ gb,
-                        int32_t accumulate)
-{
-    extern __shared__ __align__(16) float gh_row[];                 // STAGED: [S] gated gradient
-    __shared__ float red[NBP][kByJRowThreads / kWave];
-    const int64_t s = blockIdx.x;
-    const float *ar = a + s * lda, *br = b + s * ldb, *outr = out + s * ldo, *gr = g + s * ldg;
-    bool clamped = false;
-    if (STAGED) {
-        for (int c = threadIdx.x; c < S; c += kByJRowThreads) {
-            const float o = outr[c];
-            float v = gr[c];
-            if (o >= 1.0f) v = gated_grad(v, o, ar, br, T.col_ptr, T.col_ij, c);
-            gh_row[c] = v;
-        }
-        __syncthreads();
-    } else {
-        int hit = 0;
-        for (int c = threadIdx.x; c < S; c += kByJRowThreads) hit |= outr[c] >= 1.0f;
-        clamped = __syncthreads_or(hit) != 0;
-    }
-    float bj[NBP], pb[NBP];
-#pragma unroll
-    for (int j = 0; j < NBP; ++j) {
-        bj[j] = j < T.nb ? br[j] : 0.0f;
-        pb[j] = 0.0f;
-    }
-    for (int i = threadIdx.x; i < T.na; i += kByJRowThreads) {
-        const float acc = STAGED ? byj_row<NBP, true>(col_of, T.na, i, false, gh_row, outr, ar, br, bj, T, pb)
-                                 : byj_row<NBP, true>(col_of, T.na, i, clamped, gr, outr, ar, br, bj, T, pb);
-        if (ga) {
-            float *dst = ga + s * lda + i;
-            *dst = (accumulate & 1) ? *dst + acc : acc;
-        }
-    }
-    if (!gb) return;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
-#pragma unroll
-    for (int j = 0; j < NBP; ++j) {
-        float v = pb[j];
-#pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, kWave);
-        if (lane == 0) red[j][wave] = v;
-    }
-    __syncthreads();
-    if (threadIdx.x < static_cast<unsigned>(T.nb)) {
-        float tot = 0.0f;
-        for (int w = 0; w < kByJRowThreads / kWave; ++w) tot = tot + red[threadIdx.x][w];
-        float *dst = gb + s * ldb + threadIdx.x;
-        *dst = (accumulate & 2) ? *dst + tot : tot;
-    }
-}
-
 // One wavefront per (sample, long row): lanes stride over the row's tuples, the partial sums meet by shuffles.
 __global__ void __launch_bounds__(kWave)
 damp_apply2_bwd_long_kernel(int32_t n_long, const uint32_t *__restrict__ long_rows, BwdTable T,
@@ -668,9 +278,6 @@ damp_apply2_bwd_long_kernel(int32_t n_long, const uint32_t *__restrict__ long_ro
     }
 }
 
-// The workgroup-per-sample backward stages the gated gradient row in LDS when it fits beside the reduction scratch.
-static bool byj_bwd_staged(const dol_fn_table *f) { return sizeof(float) * f->n_out + 2048 <= kStageMaxBytes; }
-
 dol_status launch_damp_apply2_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b,
                                   int64_t ldb, const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga,
                                   float *gb, int32_t accumulate, hipStream_t st)
@@ -685,47 +292,13 @@ dol_status launch_damp_apply2_bwd(const dol_fn_table *f, int32_t batch, const fl
     if (done) return DOL_OK;
     if (dol_status s2 = launch_damp_lds_bwd(f, batch, a, lda, b, ldb, out, ldo, g, ldg, ga, gb, accumulate, st, &done)) return s2;
     if (done) return DOL_OK;
+    if (dol_status s2 = launch_sample_bwd(f, batch, a, lda, b, ldb, out, ldo, g, ldg, ga, gb, accumulate, st, &done)) return s2;
+    if (done) return DOL_OK;
     const BwdTable T{f->col_ptr.ptr, f->col_ij.ptr, f->rowa_ptr.ptr, f->rowa_jc.ptr, f->rowb_ptr.ptr, f->rowb_ic.ptr,
                      f->na, f->nb};
     const Rows R = rows_of(batch, f->na + f->nb);
-    if (f->byj_ok && R.rpb == 1) {
-        if (byj_bwd_staged(f)) {
-#define CALL(N)                                                                                                           \
-    {                                                                                                                     \
-        DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_byj_bwd_row_kernel<N, true>), kStageMaxBytes));                    \
-        hipLaunchKernelGGL((damp_byj_bwd_row_kernel<N, true>), dim3(static_cast<unsigned>(batch)), dim3(kByJRowThreads),  \
-                           sizeof(float) * f->n_out, st, T, f->n_out, f->byj_col.ptr, a, lda, b, ldb, out, ldo, g, ldg,   \
-                           ga, gb, accumulate);                                                                           \
-    }
-            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
-#undef CALL
-        } else {
-#define CALL(N) hipLaunchKernelGGL((damp_byj_bwd_row_kernel<N, false>), dim3(static_cast<unsigned>(batch)), dim3(kByJRowThreads), 0, \
-                                   st, T, f->n_out, f->byj_col.ptr, a, lda, b, ldb, out, ldo, g, ldg, ga, gb, accumulate)
-            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
-#undef CALL
-        }
-        DOL_HIP(hipGetLastError());
-        return DOL_OK;
-    }
-    if (f->byj_ok) {
-#define CALL(N) hipLaunchKernelGGL(damp_byj_bwd_kernel<N>, dim3(R.grid), dim3(kThreads), 0, st, R, T, f->byj_col.ptr, a, lda, \
-                                   b, ldb, out, ldo, g, ldg, ga, gb, accumulate)
-        DOL_DISPATCH_NBP(f->byj_nbp, CALL)
-#undef CALL
-    }
-    else if (apply2_bwd_staged(f)) {
-        const size_t lds = sizeof(float) * (f->n_out + kBwdStagedThreads / kWave);
-        if (lds > 64 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_bwd_staged_kernel), kStageMaxBytes));
-        hipLaunchKernelGGL(damp_apply2_bwd_staged_kernel, dim3(static_cast<unsigned>(batch)), dim3(kBwdStagedThreads), lds, st, T,
-                           f->n_out, static_cast<int32_t>(f->long_rows.n), f->long_rows.ptr, a, lda, b, ldb, out, ldo, g, ldg, ga, gb,
-                           accumulate);
-        DOL_HIP(hipGetLastError());
-        return DOL_OK;
-    }
-    else
-        hipLaunchKernelGGL(damp_apply2_bwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, T, a, lda, b, ldb, out, ldo, g,
-                           ldg, ga, gb, accumulate);
+    hipLaunchKernelGGL(damp_apply2_bwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, T, a, lda, b, ldb, out, ldo, g, ldg, ga, gb,
+                       accumulate);
     DOL_HIP(hipGetLastError());
     const int64_t n_long = static_cast<int64_t>(f->long_rows.n);
     if (n_long > 0) {
@@ -878,6 +451,30 @@ nll_grad_kernel(Rows R, const float *__restrict__ p, int64_t ld, const int32_t *
     });
 }
 
+// The same for wide rows, any row stride: a workgroup owns kThreads * kNllWide neighbouring columns of one row, whose
+// target and value are the same for all its threads (23 410 columns at B=256: 42 us with whole rows to a workgroup).
+constexpr int kNllWide = 8;
+
+__global__ void __launch_bounds__(kThreads)
+nll_grad_wide_kernel(int32_t n, int32_t cpr, const float *__restrict__ p, int64_t ld, const int32_t *__restrict__ target,
+                     float *__restrict__ grad)
+{
+    const int64_t s = blockIdx.x / static_cast<unsigned>(cpr);
+    const int32_t c0 = static_cast<int32_t>(blockIdx.x - s * cpr) * (kThreads * kNllWide);
+    const int32_t t = target[s];
+    const float val = t >= 0 && t < n ? -1.0f / fmaxf(p[s * ld + t], 1.17549435e-38f) : 0.0f;
+    float *gr = grad + s * ld;
+#pragma unroll
+    for (int x = 0; x < kNllWide / 4; ++x) {
+        const int32_t c = c0 + 4 * (static_cast<int32_t>(threadIdx.x) + x * kThreads);
+        f32x4_u v;
+        v.x = c == t ? val : 0.0f, v.y = c + 1 == t ? val : 0.0f, v.z = c + 2 == t ? val : 0.0f, v.w = c + 3 == t ? val : 0.0f;
+        if (c + 3 < n) *reinterpret_cast<f32x4_u *>(gr + c) = v;
+        else
+            for (int k = 0; c + k < n; ++k) gr[c + k] = c + k == t ? val : 0.0f;
+    }
+}
+
 // The same over a contiguous [batch, n] gradient, 16 bytes per store: a workgroup owns `rows` whole rows (a multiple of
 // four, so its piece starts on a 16-byte boundary; at most kNllRows), first puts every row's target and value in LDS
 // and then walks its piece without a division and without a load between the stores (a load's wait would also wait for
@@ -926,6 +523,14 @@ dol_status launch_nll_grad(int32_t batch, int32_t n, const float *p, int64_t ld,
                            hipStream_t st)
 {
     if (batch == 0 || n == 0) return DOL_OK;
+    if (n >= kThreads * kNllWide / 2) {             // at least half a workgroup's columns
+        const int32_t cpr = (n + kThreads * kNllWide - 1) / (kThreads * kNllWide);
+        if (static_cast<int64_t>(batch) * cpr <= 0x7fffffffLL) {
+            hipLaunchKernelGGL(nll_grad_wide_kernel, dim3(static_cast<unsigned>(batch) * cpr), dim3(kThreads), 0, st, n, cpr, p, ld, target, grad);
+            DOL_HIP(hipGetLastError());
+            return DOL_OK;
+        }
+    }
     if (ld == n && reinterpret_cast<uintptr_t>(grad) % 16 == 0) {
         const int32_t rows = std::min(kNllRows, std::max(4, (8192 / n + 3) / 4 * 4));
         if (static_cast<int64_t>(rows) * n < (int64_t{1} << 30)) {

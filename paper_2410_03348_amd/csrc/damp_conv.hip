@@ -32,21 +32,6 @@ static int padded_nb(int nb) { return nb <= 4 ? 4 : nb <= 8 ? 8 : nb <= 10 ? 10 
 // Smallest row stride >= n with stride % 64 == 32: the two samples of a wavefront then use disjoint banks.
 static int pad_row(int n) { return ((n + 31) / 64) * 64 + 32; }
 
-// Tables served by the thread-per-column forward kernel whose operand rows are wide enough to be worth staging in
-// LDS and narrow enough to fit.
-bool staged_fwd_ok(const dol_fn_table *f)
-{
-    // (rows of a thousand tags already: one round of reachability over a 32 x 32 grid, 1 024 x 1 985 symbols, at B=256
-    // takes 7.6 us through LDS against 9.7 us with cached gathers)
-    return std::max(f->na, f->nb) >= kStageMinRow / 2 && sizeof(float) * (static_cast<size_t>(f->na) + f->nb + 4) <= kStageMaxBytes;
-}
-
-// Tables walked through their per-j map whose first operand's row is worth staging in LDS, and fits.
-bool byj_fwd_staged_ok(const dol_fn_table *f)
-{
-    return f->na >= kStageMinRow && sizeof(float) * static_cast<size_t>(f->na) <= kStageMaxBytes;
-}
-
 bool conv_path_ok(const dol_fn_table *f)
 {
     return f->conv_like && f->nb <= kConvMaxNb && f->na + 3 * kConvMaxNb <= kConvMaxRow;
@@ -56,9 +41,14 @@ std::string damp_kernel_name(const dol_fn_table *f, bool backward, int64_t batch
 {
     if (!conv_path_ok(f)) {
         if (table_code_ok(f)) return backward ? "damp_table_bwd_kernel" : "damp_table_fwd_kernel";
-        if (backward) return f->lds_bwd_ok ? "damp_lds_bwd_kernel" : !f->byj_ok ? (apply2_bwd_staged(f) ? "damp_apply2_bwd_staged_kernel" : "damp_apply2_bwd_kernel") : f->na + f->nb > 1024 ? "damp_byj_bwd_row_kernel" : "damp_byj_bwd_kernel";
-        return f->lds_fwd_ok ? "damp_lds_fwd_kernel" : f->byj_fwd ? (byj_fwd_staged_ok(f) ? "damp_byj_fwd_staged_kernel" : "damp_byj_fwd_kernel") :
-               staged_fwd_ok(f) ? "damp_apply2_fwd_staged_kernel" : "damp_apply2_fwd_kernel";
+        if (backward) {
+            if (f->lds_bwd_ok && !lds_small_batch(f, batch, true)) return "damp_lds_bwd_kernel";
+            if (byj_bwd_sample_ok(f)) return byj_bwd_wide(f) ? "damp_byj_bwd_row_kernel" : "damp_byj_bwd_kernel";
+            return list_bwd_sample_ok(f) ? "damp_apply2_bwd_staged_kernel" : "damp_apply2_bwd_kernel";
+        }
+        if (f->lds_fwd_ok && !lds_small_batch(f, batch, false)) return "damp_lds_fwd_kernel";
+        if (byj_fwd_sample_ok(f)) return byj_fwd_wide(f) ? "damp_byj_fwd_staged_kernel" : "damp_byj_fwd_kernel";
+        return list_fwd_sample_ok(f) ? "damp_apply2_fwd_staged_kernel" : "damp_apply2_fwd_kernel";
     }
     char buf[96];
     snprintf(buf, sizeof buf, "damp_conv_%s_%s_kernel<%d", backward ? "bwd" : "fwd",

@@ -399,12 +399,23 @@ static unsigned lds_grid(int n_tiles, size_t lds_bytes)
     return static_cast<unsigned>(n_tiles < cap ? n_tiles : cap);
 }
 
+// Up to 4 096 samples (8 192 where the per-sample kernel walks a dense map) a workgroup per sample is faster than one per
+// tile of 64: 64 tiles leave most of the chip idle, and a tile's time does not depend on how many there are until each compute
+// unit has one.  Forward / backward in us, per sample against tiles, table 50 x 37 -> 201: B=64 4.3 / 5.1 against 10.4 / 14.4,
+// B=4096 10.5 / 10.0 against 11.1 / 15.1, B=8192 17.9 / 16.7 against 11.5 / 15.3; 442 x 10 -> 785 forward (dense map): B=256
+// 4.8 against 29.6, B=8192 22.8 against 32.7, B=16384 41.6 against 37.9.
+bool lds_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
+{
+    const bool map = backward ? byj_bwd_sample_ok(f) : byj_fwd_sample_ok(f), lists = backward ? list_bwd_sample_ok(f) : list_fwd_sample_ok(f);
+    return batch > 0 && (map || lists) && batch <= (map ? 8192 : 4096);
+}
+
 // *done = the call was taken (otherwise the caller uses the direct kernels).
 dol_status launch_damp_lds_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b,
                                int64_t ldb, float *out, int64_t ldo, hipStream_t st, bool *done)
 {
     *done = false;
-    if (!f->lds_fwd_ok || batch < 1) return DOL_OK;
+    if (!f->lds_fwd_ok || batch < 1 || lds_small_batch(f, batch, false)) return DOL_OK;
     const int n_tiles = (batch + kLdsTile - 1) / kLdsTile;
     DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_lds_fwd_kernel<true>), kLdsBytesMax));
     DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_lds_fwd_kernel<false>), kLdsBytesMax));
@@ -429,7 +440,7 @@ dol_status launch_damp_lds_bwd(const dol_fn_table *f, int32_t batch, const float
                                float *gb, int32_t accumulate, hipStream_t st, bool *done)
 {
     *done = false;
-    if (!f->lds_bwd_ok || batch < 1 || (ga && ga == gb)) return DOL_OK;
+    if (!f->lds_bwd_ok || batch < 1 || (ga && ga == gb) || lds_small_batch(f, batch, true)) return DOL_OK;
     const int n_tiles = (batch + kLdsTile - 1) / kLdsTile;
     DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_lds_bwd_kernel<true>), kLdsBytesMax));
     DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_lds_bwd_kernel<false>), kLdsBytesMax));

@@ -1,0 +1,717 @@
+// DAMP apply2 with a workgroup per sample (or per sample and part of its output row), for any function table whose rows
+// fit in LDS: Apply forward and its vector-Jacobian products.
+//
+//     out[s, c] = min(1, sum over the tuples (i, j) of column c, ascending (i, j), of a[s, i] * b[s, j])
+//     ga[s, i]  = sum_j gh[s, col(i, j)] * b[s, j],    gb[s, j] = sum_i gh[s, col(i, j)] * a[s, i]
+//
+// The rows a sample's tuples gather from are copied into LDS first (a cached gather from a row of thousands of tags touches
+// another cache line on every lane, and a compute unit looks up about one line a clock); everything else is read and
+// written coalesced:
+//   * second operands of at most 16 symbols: dense maps, one j at a time, four neighbouring columns (rows) a thread, so
+//     that a map entry costs two bytes of an 8-byte load and results leave as 16-byte stores;
+//   * other tables: tuple lists of columns (rows) sorted by length inside blocks of 4 096 and interleaved in chunks of 64
+//     (struct ListPlan), so that a wavefront's tuples are one 256-byte load and its lanes end together; the forward results of a block meet in LDS and leave in column order.
+// Lists longer than 64 tuples are summed by a wavefront (rows: by 16 lanes), those above 512 by the workgroup, in the same launch.
+// Empty map entries and the words past a list's end name one slot past the row, which holds 0.
+#include "element_map.h"
+#include "internal.h"
+#include "wave_util.h"
+
+namespace dol {
+
+constexpr int kSmallThreads = 256;      // workgroups of the kernels over rows of fewer than kStageMinRow tags
+constexpr int kSampleThreads = 1024;
+
+constexpr int kLateMax = 64;            // long columns at the clamp that a workgroup re-derives a wavefront each
+
+struct Lists {                          // struct ListPlan (internal.h) on the device
+    const uint32_t *order, *ptr, *words, *longer;
+    int32_t n_huge, n_wave, n_mid;
+};
+
+struct SampleFwd {
+    int32_t na, nb, S, parts;
+    int32_t map_ld, long_weight;        // dense maps
+    const uint16_t *map;
+    Lists lists;                        // of the columns
+    const uint32_t *col_ptr, *col_ij;   // a column's tuples in their order
+    const float *a, *b;
+    int64_t lda, ldb, ldo;
+    float *out;
+};
+
+struct SampleBwd {
+    int32_t na, nb, S, accumulate;
+    int32_t map_ld;                     // dense maps
+    const uint16_t *map;
+    Lists lists;                        // of the symbols of a, then of b
+    const uint32_t *rowa_ptr, *rowa_jc, *rowb_ptr, *rowb_ic;
+    const uint32_t *col_ptr, *col_ij;
+    const float *a, *b, *out, *g;
+    int64_t lda, ldb, ldo, ldg;
+    float *ga, *gb;
+};
+
+// ---------------------------------------------------------------- device helpers
+
+// Copies n floats into LDS (16-byte aligned there) with every thread of the workgroup, and puts a 0 behind them.
+__device__ __forceinline__ void copy_row(float *__restrict__ dst, const float *__restrict__ src, int n)
+{
+    const int n4 = n >> 2, step = blockDim.x;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < n4; e += step) {
+        const f32x4_u v = reinterpret_cast<const f32x4_u *>(src)[e];
+        reinterpret_cast<float4 *>(dst)[e] = make_float4(v.x, v.y, v.z, v.w);
+    }
+    for (int e = (n4 << 2) + threadIdx.x; e < n; e += step) dst[e] = src[e];
+    if (threadIdx.x == 0) dst[n] = 0.0f;
+}
+
+// The sum of x * y over the tuples [q0, q1) in list order, one fused multiply-add each, worked out by a whole wavefront
+// (every lane gets it).  The order is serial by definition, but a term t changes nothing once s + t rounds to s, and for
+// terms >= 0 the sum only grows, so a term whose DOUBLE rounds away against the sum so far (then t is at most a quarter of
+// the sum's last place) is out whatever the sum becomes: 64 terms are tested at a time and only the others are added.
+// A column of tens of thousands of small probabilities behind a few large ones costs a test per 64 terms; one lane adding
+// them up took 0.77 ms for 18 506 terms.
+__device__ __forceinline__ float serial_sum(const float *ar, const float *br, const uint32_t *__restrict__ ij_of, uint32_t q0, uint32_t q1)
+{
+    constexpr int kAhead = 8;
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    float s = 0.0f;
+    for (uint32_t q = q0; q < q1; q += kAhead * kWave) {
+        uint32_t ij[kAhead];
+        float x[kAhead], y[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) ij[u] = ij_of[min(q + u * kWave + lane, q1 - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            x[u] = q + u * kWave + lane < q1 ? ar[ij[u] & 0xffffu] : 0.0f;
+            y[u] = br[ij[u] >> 16];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            const bool quiet = x[u] * y[u] >= 0.0f && s >= 0.0f && __builtin_fmaf(x[u] + x[u], y[u], s) == s;
+            uint64_t todo = __ballot(!quiet);
+            if (__ballot(!(x[u] * y[u] >= 0.0f))) todo = ~uint64_t(0);      // a negative term (or none): every term counts
+            for (; todo; todo &= todo - 1) {
+                const int k = __builtin_ctzll(todo);
+                const float xk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[u]), k));
+                const float yk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y[u]), k));
+                s = __builtin_fmaf(xk, yk, s);
+            }
+        }
+    }
+    return s;
+}
+
+__device__ __forceinline__ float wave_sum(float x)
+{
+    x = reduce32<AddOp>(x);
+    return x + __shfl_xor(x, 32, kWave);
+}
+
+// A long column's sum: the lanes of a wavefront (WG: of the workgroup) stride over its tuples; whole wavefronts call this.
+// That is not the order the clamp decision is defined in.  How far the two can lie apart: a step of the serial sum errs by at
+// most half a unit in the last place of a partial sum, and by at most the term itself (s is one of the two neighbours of
+// s + t), so by the sum of min(|t|, 2^-23) while the terms' magnitudes sum to at most 2; the sum over lanes errs by a rounding
+// per step.  Only a sum within that distance of 1 is taken again in the defining order.
+template <bool WG>
+__device__ __forceinline__ float long_sum(const float *ar, const float *br, const uint32_t *__restrict__ ij_of, uint32_t q0, uint32_t q1,
+                                          float *scratch)
+{
+    constexpr int kAhead = 4;
+    const uint32_t step = WG ? blockDim.x : kWave, me = WG ? threadIdx.x : threadIdx.x & (kWave - 1);
+    float acc = 0.0f, mag = 0.0f, err = 0.0f;
+    for (uint32_t q = q0 + me; q < q1; q += kAhead * step) {
+        uint32_t ij[kAhead];
+        float x[kAhead], y[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) ij[u] = ij_of[min(q + u * step, q1 - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            x[u] = q + u * step < q1 ? ar[ij[u] & 0xffffu] : 0.0f;
+            y[u] = br[ij[u] >> 16];
+        }
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            acc = __builtin_fmaf(x[u], y[u], acc);
+            mag = __builtin_fmaf(fabsf(x[u]), fabsf(y[u]), mag);
+            err += fminf(fabsf(x[u] * y[u]), 1.1920929e-7f);
+        }
+    }
+    acc = wave_sum(acc), mag = wave_sum(mag), err = wave_sum(err);
+    if (WG && step > kWave) {
+        const int wave = threadIdx.x / kWave, n_waves = step / kWave;
+        __syncthreads();                            // the scratch of an earlier column has been read
+        if ((threadIdx.x & (kWave - 1)) == 0) { scratch[wave] = acc; scratch[16 + wave] = mag; scratch[32 + wave] = err; }
+        __syncthreads();
+        acc = mag = err = 0.0f;
+        for (int w = 0; w < n_waves; ++w) { acc += scratch[w]; mag += scratch[16 + w]; err += scratch[32 + w]; }
+    }
+    if (WG && threadIdx.x >= kWave) return acc;     // (the first wavefront's answer is the one that counts)
+    const float parallel = mag * (static_cast<float>((q1 - q0) / step + 40) * 1.1920929e-7f);
+    const float serial = mag <= 2.0f ? 1.01f * err : mag * (static_cast<float>(q1 - q0) * 1.1920929e-7f);
+    if (!(fabsf(acc - 1.0f) > parallel + serial)) acc = serial_sum(ar, br, ij_of, q0, q1);
+    return acc;
+}
+
+// The same over one thread's own list, in the defining order.
+__device__ __forceinline__ float column_sum(const float *ar, const float *br, const uint32_t *__restrict__ ij_of, uint32_t q0, uint32_t q1)
+{
+    float acc = 0.0f;
+    for (uint32_t q = q0; q < q1; ++q) {
+        const uint32_t ij = ij_of[q];
+        acc = __builtin_fmaf(ar[ij & 0xffffu], br[ij >> 16], acc);
+    }
+    return acc;
+}
+
+// The columns among [c0, c1) of more than kLaneList tuples: put(c, sum) is called by one lane.
+template <typename F>
+__device__ __forceinline__ void long_columns(const SampleFwd &A, const float *ar, const float *br, int c0, int c1, float *scratch, F put)
+{
+    const Lists &L = A.lists;
+    for (int l = 0; l < L.n_huge; ++l) {
+        const int c = static_cast<int>(L.longer[l]);
+        if (c < c0 || c >= c1) continue;
+        const float v = long_sum<true>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], scratch);
+        if (threadIdx.x == 0) put(c, v);
+    }
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
+    for (int l = L.n_huge + wave; l < L.n_huge + L.n_wave; l += n_waves) {
+        const int c = __builtin_amdgcn_readfirstlane(static_cast<int>(L.longer[l]));
+        if (c < c0 || c >= c1) continue;
+        const float v = long_sum<false>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], scratch);
+        if (lane == 0) put(c, v);
+    }
+}
+
+// Four neighbouring floats at a 4-byte aligned address, of which the first n exist.
+__device__ __forceinline__ float4 load4(const float *__restrict__ p, int n)
+{
+    if (n >= 4) {
+        const f32x4_u v = *reinterpret_cast<const f32x4_u *>(p);
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+    return make_float4(p[0], n > 1 ? p[1] : 0.0f, n > 2 ? p[2] : 0.0f, 0.0f);
+}
+
+__device__ __forceinline__ void store4(float *__restrict__ p, const float (&v)[4], int n, uint32_t skip = 0)
+{
+    if (n >= 4 && skip == 0) {
+        f32x4_u w;
+        w.x = v[0], w.y = v[1], w.z = v[2], w.w = v[3];
+        *reinterpret_cast<f32x4_u *>(p) = w;
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (k < n && !((skip >> k) & 1u)) p[k] = v[k];
+}
+
+// ---------------------------------------------------------------- forward, dense maps
+
+// One j at a time is not the order the clamp decision is defined in; the terms' magnitudes bound how far the two sums can
+// lie apart, and only a sum within that distance of 1 is taken again in the defining order.
+template <int NBP>
+__device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
+{
+    __shared__ float scratch[48];
+    const int64_t s = blockIdx.x / static_cast<unsigned>(A.parts);
+    const int part = static_cast<int>(blockIdx.x - s * A.parts);
+    // the last part also sums the long columns: they weigh as much as `long_weight` columns
+    const int per = ((A.S + A.long_weight + A.parts - 1) / A.parts + 3) & ~3;
+    const int c0 = min(A.S, part * per), c1 = part == A.parts - 1 ? A.S : min(A.S, c0 + per);
+    const float *br = A.b + s * A.ldb;
+    float *out = A.out + s * A.ldo;
+    copy_row(ar, A.a + s * A.lda, A.na);
+    float y[NBP];
+#pragma unroll
+    for (int j = 0; j < NBP; ++j) y[j] = br[j < A.nb ? j : 0];      // (the maps' extra rows are empty)
+    __syncthreads();
+    for (int c = c0 + 4 * static_cast<int>(threadIdx.x); c < c1; c += 4 * static_cast<int>(blockDim.x)) {
+        ushort4 m[NBP];
+#pragma unroll
+        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + c);
+        uint16_t mark[4] = {m[0].x, m[0].y, m[0].z, m[0].w};
+        const uint16_t none = static_cast<uint16_t>(A.na);
+        m[0].x = min(m[0].x, none), m[0].y = min(m[0].y, none), m[0].z = min(m[0].z, none), m[0].w = min(m[0].w, none);
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, mag[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j = 0; j < NBP; ++j) {
+            const float x[4] = {ar[m[j].x], ar[m[j].y], ar[m[j].z], ar[m[j].w]};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                acc[k] = __builtin_fmaf(x[k], y[j], acc[k]);
+                mag[k] = __builtin_fmaf(fabsf(x[k]), fabsf(y[j]), mag[k]);
+            }
+        }
+        uint32_t skip = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool near = !(fabsf(acc[k] - 1.0f) > mag[k] * (static_cast<float>(NBP + 2) * 1.1920929e-7f));
+            if (mark[k] == kByJWave) skip |= 1u << k;               // summed below
+            else if ((near || mark[k] == kByJList) && c + k < c1)   // some j occurs twice: the tuple list itself
+                acc[k] = column_sum(ar, br, A.col_ij, A.col_ptr[c + k], A.col_ptr[c + k + 1]);
+            acc[k] = fminf(acc[k], 1.0f);
+        }
+        store4(out + c, acc, c1 - c, skip);
+    }
+    if (part == A.parts - 1)
+        long_columns(A, ar, br, 0, A.S, scratch, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
+}
+
+template <int NBP>
+__global__ void __launch_bounds__(kSmallThreads)
+damp_byj_fwd_kernel(const SampleFwd A)
+{
+    extern __shared__ __align__(16) float lds[];
+    byj_fwd<NBP>(A, lds);
+}
+
+template <int NBP>
+__global__ void __launch_bounds__(kSampleThreads)
+damp_byj_fwd_staged_kernel(const SampleFwd A)
+{
+    extern __shared__ __align__(16) float lds[];
+    byj_fwd<NBP>(A, lds);
+}
+
+// ---------------------------------------------------------------- forward, tuple lists
+
+// A wavefront walks one chunk of 64 lists at a time, four words of each per step; a step's words, and the first ones of the
+// next chunk, are read while the step before is worked on (they come from L2, whose latency is what this would cost).
+struct Chunk {
+    uint32_t e, w0, len, t[4];
+};
+
+__device__ __forceinline__ void read_words(uint32_t (&t)[4], const Lists &L, uint32_t w)
+{
+    const uint32_t *__restrict__ p = L.words + static_cast<size_t>(w) * kWave + (threadIdx.x & (kWave - 1));
+#pragma unroll
+    for (int u = 0; u < 4; ++u) t[u] = p[u * kWave];
+}
+
+__device__ __forceinline__ Chunk read_chunk(const Lists &L, int ch)
+{
+    Chunk c;
+    c.w0 = L.ptr[ch], c.len = L.ptr[ch + 1] - c.w0;
+    c.e = L.order[ch * kWave + (threadIdx.x & (kWave - 1))];
+    read_words(c.t, L, c.w0);
+    return c;
+}
+
+__device__ __forceinline__ int wave_number() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave); }
+
+// Walks the chunks [ch0, ch1), a wavefront every blockDim.x / 64th: term(word, sum) takes a tuple into a list's sum, in list
+// order, and done(list, sum) is called for every list that is walked here.  `now`: this wavefront's first chunk.
+template <typename T, typename D>
+__device__ __forceinline__ void walk_lists(const Lists &L, int ch0, int ch1, Chunk now, T term, D done)
+{
+    const int n_waves = blockDim.x / kWave;
+    for (int ch = ch0 + wave_number(); ch < ch1; ch += n_waves) {
+        const Chunk next = read_chunk(L, min(ch + n_waves, ch1 - 1));
+        float acc = 0.0f;
+        for (uint32_t w = 0; w < now.len; w += 4) {
+            uint32_t t[4] = {now.t[0], now.t[1], now.t[2], now.t[3]};
+            if (w + 4 < now.len) read_words(now.t, L, now.w0 + w + 4);
+            const uint32_t left = now.len - w;              // (the same for all lanes)
+            if (left >= 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc = term(t[u], acc);
+            } else {
+                acc = term(t[0], acc);
+                if (left > 1) acc = term(t[1], acc);
+                if (left > 2) acc = term(t[2], acc);
+            }
+        }
+        if (!(now.e & kListElsewhere)) done(static_cast<int>(now.e), acc);
+        now = next;
+    }
+}
+
+__global__ void __launch_bounds__(kSampleThreads)
+damp_apply2_fwd_staged_kernel(const SampleFwd A)
+{
+    extern __shared__ __align__(16) float lds[];            // a's row and a 0, b's and a 0, a block of results
+    __shared__ float scratch[48];
+    float *ar = lds, *br = lds + ((A.na + 4) & ~3), *res = br + ((A.nb + 4) & ~3);
+    const int64_t s = blockIdx.x / static_cast<unsigned>(A.parts);
+    const int part = static_cast<int>(blockIdx.x - s * A.parts);
+    constexpr int kBlockChunks = kOrderBlock / kWave;
+    const int n_chunks = (A.S + kWave - 1) / kWave;
+    Chunk now = read_chunk(A.lists, min(part * kBlockChunks + wave_number(), n_chunks - 1));
+    copy_row(ar, A.a + s * A.lda, A.na);
+    copy_row(br, A.b + s * A.ldb, A.nb);
+    __syncthreads();
+    float *out = A.out + s * A.ldo;
+    for (int b0 = part * kOrderBlock; b0 < A.S; b0 += A.parts * kOrderBlock) {
+        const int b1 = min(A.S, b0 + kOrderBlock);
+        walk_lists(A.lists, b0 / kWave, (b1 + kWave - 1) / kWave, now,
+                   [&](uint32_t t, float acc) { return __builtin_fmaf(ar[t & 0xffffu], br[t >> 16], acc); },
+                   [&](int c, float v) { res[c - b0] = v; });
+        const int next = b0 + A.parts * kOrderBlock;
+        if (next < A.S) now = read_chunk(A.lists, min(next / kWave + wave_number(), n_chunks - 1));
+        long_columns(A, ar, br, b0, b1, scratch, [&](int c, float v) { res[c - b0] = v; });
+        __syncthreads();
+        for (int c = 4 * static_cast<int>(threadIdx.x); c < b1 - b0; c += 4 * static_cast<int>(blockDim.x)) {
+            const float4 v = *reinterpret_cast<const float4 *>(res + c);
+            const float r[4] = {fminf(v.x, 1.0f), fminf(v.y, 1.0f), fminf(v.z, 1.0f), fminf(v.w, 1.0f)};
+            store4(out + b0 + c, r, b1 - b0 - c);
+        }
+        __syncthreads();
+    }
+}
+
+// ---------------------------------------------------------------- backward
+
+// gh[c] = g[c] where the clamp did not act, else 0, for the whole row, and a 0 behind it.  out < 1: it did not act;
+// out == 1 leaves pre == 1 (passes) and pre > 1 (blocks) apart only by pre itself, taken again in its defining order
+// (long columns: by a wavefront each, after the others).
+__device__ __forceinline__ void gated_row(const SampleBwd &A, int64_t s, float *gh, int *n_late, int *late)
+{
+    const float *ar = A.a + s * A.lda, *br = A.b + s * A.ldb, *outr = A.out + s * A.ldo, *gr = A.g + s * A.ldg;
+    if (threadIdx.x == 0) { *n_late = 0; gh[A.S] = 0.0f; }
+    __syncthreads();
+    for (int c = 4 * static_cast<int>(threadIdx.x); c < A.S; c += 4 * static_cast<int>(blockDim.x)) {
+        const int n = A.S - c;
+        const float4 o4 = load4(outr + c, n), g4 = load4(gr + c, n);
+        const float o[4] = {o4.x, o4.y, o4.z, o4.w};
+        float g[4] = {g4.x, g4.y, g4.z, g4.w};
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (o[k] >= 1.0f && k < n) {
+                const uint32_t q0 = A.col_ptr[c + k], q1 = A.col_ptr[c + k + 1];
+                const int slot = q1 - q0 > static_cast<uint32_t>(kLongTableCol) ? atomicAdd(n_late, 1) : kLateMax;
+                if (slot < kLateMax) late[slot] = c + k;
+                else if (!(column_sum(ar, br, A.col_ij, q0, q1) <= 1.0f)) g[k] = 0.0f;
+            }
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (k < n) gh[c + k] = g[k];
+    }
+    __syncthreads();
+    const int wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave, n = min(*n_late, kLateMax);
+    for (int l = wave; l < n; l += n_waves) {
+        const int c = __builtin_amdgcn_readfirstlane(late[l]);
+        const float pre = serial_sum(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1]);
+        if (!(pre <= 1.0f) && (threadIdx.x & (kWave - 1)) == 0) gh[c] = 0.0f;
+    }
+    if (n) __syncthreads();
+}
+
+// Dense maps: a thread owns four neighbouring rows of a and adds their shares of gb up in registers; the workgroup's
+// shares meet at the end (so the long rows of b need no launch of their own).
+template <int NBP, int T>
+__device__ __forceinline__ void byj_bwd(const SampleBwd &A, float *gh)
+{
+    __shared__ float red[NBP][T / kWave];
+    __shared__ int n_late, late[kLateMax];
+    const int64_t s = blockIdx.x;
+    const float *ar = A.a + s * A.lda, *br = A.b + s * A.ldb;
+    gated_row(A, s, gh, &n_late, late);
+    float bj[NBP], pb[NBP];
+#pragma unroll
+    for (int j = 0; j < NBP; ++j) {
+        bj[j] = j < A.nb ? br[j] : 0.0f;
+        pb[j] = 0.0f;
+    }
+    for (int i = 4 * static_cast<int>(threadIdx.x); i < A.na; i += 4 * static_cast<int>(blockDim.x)) {
+        ushort4 m[NBP];
+#pragma unroll
+        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + i);
+        const int n = A.na - i;
+        const float4 a4 = load4(ar + i, n);
+        const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j = 0; j < NBP; ++j) {
+            const float v[4] = {gh[m[j].x], gh[m[j].y], gh[m[j].z], gh[m[j].w]};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                acc[k] = __builtin_fmaf(v[k], bj[j], acc[k]);
+                pb[j] = __builtin_fmaf(v[k], av[k], pb[j]);
+            }
+        }
+        if (A.ga) {
+            float *dst = A.ga + s * A.lda + i;
+            if (A.accumulate & 1) {
+                const float4 old = load4(dst, n);
+                acc[0] += old.x, acc[1] += old.y, acc[2] += old.z, acc[3] += old.w;
+            }
+            store4(dst, acc, n);
+        }
+    }
+    if (!A.gb) return;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
+#pragma unroll
+    for (int j = 0; j < NBP; ++j) {
+        const float v = wave_sum(pb[j]);
+        if (lane == 0) red[j][wave] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < static_cast<unsigned>(A.nb)) {
+        float tot = 0.0f;
+        for (int w = 0; w < n_waves; ++w) tot = tot + red[threadIdx.x][w];
+        float *dst = A.gb + s * A.ldb + threadIdx.x;
+        *dst = (A.accumulate & 2) ? *dst + tot : tot;
+    }
+}
+
+template <int NBP>
+__global__ void __launch_bounds__(kSmallThreads)
+damp_byj_bwd_kernel(const SampleBwd A)
+{
+    extern __shared__ __align__(16) float lds[];
+    byj_bwd<NBP, kSmallThreads>(A, lds);
+}
+
+template <int NBP>
+__global__ void __launch_bounds__(kSampleThreads)
+damp_byj_bwd_row_kernel(const SampleBwd A)
+{
+    extern __shared__ __align__(16) float lds[];
+    byj_bwd<NBP, kSampleThreads>(A, lds);
+}
+
+// Tuple lists: a lane owns a symbol of a or b (element x: symbol x of a, or x - na of b) and adds up its tuples from the
+// gated gradient row, in list order; longer lists are summed by 16 lanes, a wavefront or the workgroup, strided partial sums
+// in list order that meet in a fixed order.  ROWS: the operand rows fit in LDS as well.
+template <bool ROWS>
+__global__ void __launch_bounds__(kSampleThreads)
+damp_apply2_bwd_staged_kernel(const SampleBwd A)
+{
+    extern __shared__ __align__(16) float lds[];            // gated gradient row and a 0 [a and b behind each other, a 0]
+    __shared__ float scratch[kSampleThreads / kWave];
+    __shared__ int n_late, late[kLateMax];
+    const int64_t s = blockIdx.x;
+    float *gh = lds, *rows = lds + ((A.S + 4) & ~3);
+    const float *ar = A.a + s * A.lda, *br = A.b + s * A.ldb;
+    const int n = A.na + A.nb;
+    const int n_chunks = (n + kWave - 1) / kWave;
+    const Chunk now = read_chunk(A.lists, min(wave_number(), n_chunks - 1));
+    if (ROWS) {
+        for (int e = threadIdx.x; e < A.na; e += blockDim.x) rows[e] = ar[e];
+        for (int e = threadIdx.x; e < A.nb; e += blockDim.x) rows[A.na + e] = br[e];
+        if (threadIdx.x == 0) rows[n] = 0.0f;
+    }
+    gated_row(A, s, gh, &n_late, late);                     // (ends after a barrier)
+    // a list's word: the other operand's symbol, counted from a's first one (b's from na on; na + nb: none), and the column
+    auto other = [&](uint32_t x) {
+        if (ROWS) return rows[x];
+        const uint32_t na = A.na, end = A.na + A.nb;
+        return x < na ? ar[x] : x < end ? br[x - na] : 0.0f;
+    };
+    auto term = [&](uint32_t t, float acc) { return __builtin_fmaf(gh[t >> 16], other(t & 0xffffu), acc); };
+    auto put = [&](int x, float v) {
+        const bool is_a = x < A.na;
+        if (is_a ? !A.ga : !A.gb) return;
+        float *dst = is_a ? A.ga + s * A.lda + x : A.gb + s * A.ldb + (x - A.na);
+        *dst = (A.accumulate & (is_a ? 1 : 2)) ? *dst + v : v;
+    };
+    walk_lists(A.lists, 0, n_chunks, now, term, put);
+    const Lists &L = A.lists;
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
+    // the partial sum of this lane, one of `step` lanes, over the list of element x
+    auto partial = [&](int x, uint32_t me, uint32_t step) {
+        const bool is_a = x < A.na;
+        const uint32_t *__restrict__ ent = is_a ? A.rowa_jc : A.rowb_ic;
+        const uint32_t q0 = is_a ? A.rowa_ptr[x] : A.rowb_ptr[x - A.na], q1 = is_a ? A.rowa_ptr[x + 1] : A.rowb_ptr[x - A.na + 1];
+        const uint32_t base = is_a ? A.na : 0;
+        float acc = 0.0f;
+        for (uint32_t q = q0 + me; q < q1; q += 4 * step) {
+            uint32_t t[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t[u] = ent[min(q + u * step, q1 - 1)];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float x4 = other(base + (t[u] & 0xffffu)), g4 = gh[t[u] >> 16];
+                acc = __builtin_fmaf(q + u * step < q1 ? g4 : 0.0f, x4, acc);
+            }
+        }
+        return acc;
+    };
+    for (int l0 = 4 * wave; l0 < L.n_mid; l0 += 4 * n_waves) {
+        const int l = l0 + lane / 16;
+        const int x = static_cast<int>(L.longer[L.n_huge + L.n_wave + min(l, L.n_mid - 1)]);
+        const float v = reduce16<AddOp>(partial(x, lane & 15, 16));
+        if (l < L.n_mid && (lane & 15) == 0) put(x, v);
+    }
+    for (int l = L.n_huge + wave; l < L.n_huge + L.n_wave; l += n_waves) {
+        const int x = __builtin_amdgcn_readfirstlane(static_cast<int>(L.longer[l]));
+        const float v = wave_sum(partial(x, lane, kWave));
+        if (lane == 0) put(x, v);
+    }
+    for (int l = 0; l < L.n_huge; ++l) {
+        const int x = static_cast<int>(L.longer[l]);
+        const float v = wave_sum(partial(x, threadIdx.x, blockDim.x));
+        __syncthreads();                                    // (the last list's totals have been read)
+        if (lane == 0) scratch[wave] = v;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            float tot = 0.0f;
+            for (int w = 0; w < n_waves; ++w) tot += scratch[w];
+            put(x, tot);
+        }
+    }
+}
+
+// ---------------------------------------------------------------- which tables, which launch
+
+static unsigned threads_for(int64_t work, int most)
+{
+    const int64_t t = (work + kWave - 1) / kWave * kWave;
+    return static_cast<unsigned>(std::max<int64_t>(kWave, std::min<int64_t>(most, t)));
+}
+
+static Lists lists_of(const ListPlan &p)
+{
+    return Lists{p.order.ptr, p.ptr.ptr, p.words.ptr, p.longer.ptr, p.n_huge, p.n_wave, p.n_mid};
+}
+
+// Threads for n lists (a lane each, eight for one that 16 lanes sum) beside the copying of a row.
+static unsigned list_threads(const ListPlan &p, int32_t n, int32_t row)
+{
+    return threads_for(std::max<int64_t>(n + 8 * static_cast<int64_t>(p.n_mid), row / 4), kSampleThreads);
+}
+
+// Parts of a sample's output row, at most `most`: a workgroup copies `row` floats and then does `work` floats' worth of
+// gathers, shared by the parts; the grid runs in rounds of what the chip holds at once (256 compute units, 2 048 threads and
+// 160 KB of LDS each), and a round that is nearly empty costs as much as a full one.
+static int32_t best_parts(int64_t batch, int most, double row, double work, unsigned threads, size_t lds)
+{
+    const int64_t held = 256 * std::max<int64_t>(1, std::min<int64_t>(2048 / threads, static_cast<int64_t>(160 * 1024 / (lds + 1024))));
+    int32_t best = 1;
+    double best_cost = 0.0;
+    for (int p = 1; p <= most && batch * p <= 0x7fffffffLL; ++p) {
+        const double cost = static_cast<double>((batch * p + held - 1) / held) * (row + 1500.0 + work / p);
+        if (p == 1 || cost < 0.97 * best_cost) { best = p; best_cost = cost; }
+    }
+    return best;
+}
+
+static size_t list_fwd_bytes(const dol_fn_table *f)
+{
+    return sizeof(float) * (static_cast<size_t>((f->na + 4) & ~3) + ((f->nb + 4) & ~3) + std::min(f->n_out + 3, kOrderBlock));
+}
+
+static size_t gated_bytes(const dol_fn_table *f) { return sizeof(float) * static_cast<size_t>((f->n_out + 4) & ~3); }
+
+bool byj_fwd_sample_ok(const dol_fn_table *f) { return f->byj_fwd && sizeof(float) * static_cast<size_t>(f->na + 4) <= kStageMaxBytes; }
+
+bool list_fwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && list_fwd_bytes(f) <= kStageMaxBytes; }
+
+bool byj_bwd_sample_ok(const dol_fn_table *f) { return f->byj_ok && gated_bytes(f) <= kStageMaxBytes; }
+
+bool list_bwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && gated_bytes(f) <= kStageMaxBytes; }
+
+#define DOL_DISPATCH_NBP(nbp, CALL) \
+    switch (nbp) {                  \
+    case 4: CALL(4); break;         \
+    case 8: CALL(8); break;         \
+    case 10: CALL(10); break;       \
+    default: CALL(16); break;       \
+    }
+
+// The launch of the dense-map kernels over rows of at least kStageMinRow tags takes up to 1 024 threads, over shorter
+// rows up to 256 (two or more workgroups share a compute unit then).
+bool byj_fwd_wide(const dol_fn_table *f) { return f->na >= kStageMinRow; }
+bool byj_bwd_wide(const dol_fn_table *f) { return f->na + f->nb > 1024; }
+
+dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb, float *out,
+                             int64_t ldo, hipStream_t st, bool *done)
+{
+    *done = false;
+    const bool byj = byj_fwd_sample_ok(f);
+    if (!byj && !list_fwd_sample_ok(f)) return DOL_OK;
+    SampleFwd A{};
+    A.na = f->na, A.nb = f->nb, A.S = f->n_out;
+    A.a = a, A.lda = lda, A.b = b, A.ldb = ldb, A.out = out, A.ldo = ldo;
+    A.col_ptr = f->col_ptr.ptr, A.col_ij = f->col_ij.ptr;
+    A.lists = lists_of(f->col_lists);
+    if (byj) {
+        A.map = f->byj_src.ptr, A.map_ld = f->byj_src_ld;
+        A.long_weight = static_cast<int32_t>(std::min<int64_t>(f->col_lists.long_words / f->byj_nbp, f->n_out));
+        const size_t lds = sizeof(float) * static_cast<size_t>(f->na + 4);
+        A.parts = best_parts(batch, std::min(16, (f->n_out + 4 * kSmallThreads - 1) / (4 * kSmallThreads)), f->na,
+                             static_cast<double>(f->n_out + A.long_weight) * f->byj_nbp, byj_fwd_wide(f) ? kSampleThreads : kSmallThreads, lds);
+        const unsigned grid = static_cast<unsigned>(batch) * A.parts;
+        const int64_t work = std::max<int64_t>(f->n_out / A.parts + 3, f->na) / 4;
+        if (byj_fwd_wide(f)) {
+#define CALL(N)                                                                                                                \
+    {                                                                                                                          \
+        if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_byj_fwd_staged_kernel<N>), kStageMaxBytes));   \
+        hipLaunchKernelGGL(damp_byj_fwd_staged_kernel<N>, dim3(grid), dim3(threads_for(work, kSampleThreads)), lds, st, A);    \
+    }
+            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
+#undef CALL
+        } else {
+#define CALL(N) hipLaunchKernelGGL(damp_byj_fwd_kernel<N>, dim3(grid), dim3(threads_for(work, kSmallThreads)), lds, st, A)
+            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
+#undef CALL
+        }
+    } else {
+        const size_t lds = list_fwd_bytes(f);
+        A.parts = best_parts(batch, (f->n_out + kOrderBlock - 1) / kOrderBlock, f->na + f->nb, 2.0 * f->n_tuples + f->n_out, kSampleThreads, lds);
+        if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_fwd_staged_kernel), kStageMaxBytes));
+        hipLaunchKernelGGL(damp_apply2_fwd_staged_kernel, dim3(static_cast<unsigned>(batch) * A.parts),
+                           dim3(list_threads(f->col_lists, f->n_out, f->na)), lds, st, A);
+    }
+    DOL_HIP(hipGetLastError());
+    *done = true;
+    return DOL_OK;
+}
+
+dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
+                             const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
+                             hipStream_t st, bool *done)
+{
+    *done = false;
+    const bool byj = byj_bwd_sample_ok(f);
+    if (!byj && !list_bwd_sample_ok(f)) return DOL_OK;
+    SampleBwd A{};
+    A.na = f->na, A.nb = f->nb, A.S = f->n_out;
+    A.a = a, A.lda = lda, A.b = b, A.ldb = ldb, A.out = out, A.ldo = ldo, A.g = g, A.ldg = ldg, A.ga = ga, A.gb = gb;
+    A.accumulate = accumulate;
+    A.col_ptr = f->col_ptr.ptr, A.col_ij = f->col_ij.ptr;
+    A.lists = lists_of(f->row_lists);
+    size_t lds = gated_bytes(f);
+    const dim3 grid(static_cast<unsigned>(batch));
+    if (byj) {
+        A.map = f->byj_col.ptr, A.map_ld = f->byj_col_ld;
+        const int64_t work = std::max(f->na, f->n_out) / 4 + 1;
+        if (byj_bwd_wide(f)) {
+#define CALL(N)                                                                                                                \
+    {                                                                                                                          \
+        if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_byj_bwd_row_kernel<N>), kStageMaxBytes));   \
+        hipLaunchKernelGGL(damp_byj_bwd_row_kernel<N>, grid, dim3(threads_for(work, kSampleThreads)), lds, st, A);             \
+    }
+            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
+#undef CALL
+        } else {
+#define CALL(N)                                                                                                                \
+    {                                                                                                                          \
+        if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_byj_bwd_kernel<N>), kStageMaxBytes));   \
+        hipLaunchKernelGGL(damp_byj_bwd_kernel<N>, grid, dim3(threads_for(work, kSmallThreads)), lds, st, A);                  \
+    }
+            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
+#undef CALL
+        }
+    } else {
+        A.rowa_ptr = f->rowa_ptr.ptr, A.rowa_jc = f->rowa_jc.ptr, A.rowb_ptr = f->rowb_ptr.ptr, A.rowb_ic = f->rowb_ic.ptr;
+        const size_t with_rows = lds + sizeof(float) * static_cast<size_t>(f->na + f->nb + 1);
+        const dim3 block(list_threads(f->row_lists, f->na + f->nb, f->n_out));
+        if (with_rows <= kStageMaxBytes) {
+            if (with_rows > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_bwd_staged_kernel<true>), kStageMaxBytes));
+            hipLaunchKernelGGL(damp_apply2_bwd_staged_kernel<true>, grid, block, with_rows, st, A);
+        } else {
+            if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_bwd_staged_kernel<false>), kStageMaxBytes));
+            hipLaunchKernelGGL(damp_apply2_bwd_staged_kernel<false>, grid, block, lds, st, A);
+        }
+    }
+    DOL_HIP(hipGetLastError());
+    *done = true;
+    return DOL_OK;
+}
+
+}  // namespace dol

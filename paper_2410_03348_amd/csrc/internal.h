@@ -74,12 +74,29 @@ constexpr int32_t kStageMinRow = 2048;       // operand rows of at least this ma
 constexpr size_t kStageMaxBytes = 158 * 1024;   // narrower ones stay with the cached gathers; of the 160 KB of a compute unit
 constexpr int kByJMax = 16;         // tables whose second operand has at most this many symbols get dense per-j maps
 constexpr int kByJMaxNa = 65000;    // ... and whose first operand leaves room for the three marks below
-constexpr uint16_t kByJNone = 0xFFFF, kByJWave = 0xFFFE, kByJList = 0xFFFD;
+constexpr uint16_t kByJWave = 0xFFFE, kByJList = 0xFFFD;
+constexpr uint32_t kListElsewhere = 0x80000000u;   // struct ListPlan: this list is summed elsewhere
 
 // Code compiled for one function table on its first use (damp_table.hip)
 struct JitState;
 struct JitDeleter {
     void operator()(JitState *p) const;
+};
+
+// Tuple lists for the workgroup-per-sample kernels.  Lists of at most kLaneList words are laid out for a lane each: inside
+// blocks of kOrderBlock consecutive lists the longest come first (longer lists than that last, as empty ones), and the lists
+// are taken 64 at a time: word k of the 64 lists of chunk ch stands at words[(ptr[ch] + k) * 64 + lane], filled up to the
+// longest of the 64 with a word whose product is 0.  order[r] is the list that lane r % 64 of chunk r / 64 walks, with
+// kListElsewhere set for the longer ones, which are named by `longer`: first those above kHugeList words (summed by a
+// workgroup each), then those summed by a wavefront each, then those summed by 16 lanes (rows only).
+constexpr int kLaneList = 64;
+constexpr int kHugeList = 512;
+constexpr int kMidRow = 512;            // rows of up to this many tuples are summed by 16 lanes
+struct ListPlan {
+    DevArray<uint32_t> order, ptr, words, longer;
+    int32_t n_huge = 0, n_wave = 0, n_mid = 0;
+    int64_t long_words = 0;             // words of the huge and the wavefront lists
+    size_t n_words = 0;                 // words laid out for lanes, filling included
 };
 
 // A tuple of the function table packed for the kernels: low 16 bits = first index, high 16 = second.
@@ -108,7 +125,6 @@ struct dol_fn_table {
     // the first four tuples of every column again, 16 bytes per column (0xFFFFFFFF = no tuple): the forward kernel
     // for irregular tables gets a short column with one load
     dol::DevArray<uint32_t> col_head;
-    dol::DevArray<uint32_t> col_head_ord;   // the same, entry r being that of column col_order[r] (read coalesced there)
     // backward w.r.t. a: row i owns rowa_ptr[i] .. rowa_ptr[i+1] of rowa_jc = pack16(j, column), ascending j
     dol::DevArray<uint32_t> rowa_ptr, rowa_jc;
     // backward w.r.t. b: row j owns rowb_ptr[j] .. rowb_ptr[j+1] of rowb_ic = pack16(i, column), ascending i
@@ -127,24 +143,28 @@ struct dol_fn_table {
     // neighbouring r read neighbouring words
     dol::DevArray<uint32_t> ord_tuples, ord_len;
     // each list starts with its huge columns (more than dol::kHugeTableCol / dol::kHugeDtkpCol tuples)
-    int32_t n_huge_cols = 0, n_huge_dtkp_cols = 0, n_huge_byj_cols = 0;
+    int32_t n_huge_cols = 0, n_huge_dtkp_cols = 0;
     int32_t n_wave_dtkp_cols = 0;        // dtkp_long_cols: huge, then this many one-wavefront columns, then the shorter ones
     // LDS gather kernels (damp_lds.hip): per output column (forward), row of a, row of b (backward) a list of
     // 16-byte packets of four tuples; *_ptr[x] .. *_ptr[x+1] are the packets of x
     bool lds_fwd_ok = false, lds_bwd_ok = false;
     size_t lds_fwd_bytes = 0, lds_bwd_bytes = 0;
     dol::DevArray<uint32_t> lds_pk, lds_pk_ptr, lds_pka, lds_pka_ptr, lds_pkb, lds_pkb_ptr;
-    // Tables with a short second operand (nb <= dol::kByJMax, na <= dol::kByJMaxNa) that take neither path above:
-    // dense 16-bit maps walked one j at a time, so that lane-adjacent elements read the operand through one map each
-    // (adjacent addresses for monotone functions).  byj_src[j * n_out + c] = the i with f(i, j) = column c, or
-    // dol::kByJNone; a long column has dol::kByJWave at j = 0 and is listed in byj_wave_cols (summed by a wavefront); a
-    // short column where some j occurs twice has dol::kByJList there and is summed from its tuple list.
-    // byj_col[j * na + i] = column of (i, j) or dol::kByJNone.
+    // Workgroup-per-sample kernels (damp_sample.hip).  Any table of fewer than 65 535 symbols in all: the columns' tuples
+    // (i | j << 16; filling (na, nb)), and for every symbol x of a, then of b, (other symbol counted from a's first one |
+    // column << 16; filling (na + nb, n_out)).
+    bool lists_ok = false;
+    dol::ListPlan col_lists, row_lists;
+    // Tables with a short second operand (nb <= dol::kByJMax, na <= dol::kByJMaxNa): dense 16-bit maps walked one j at a
+    // time, so that lane-adjacent elements read the operand through one map each (adjacent addresses for monotone
+    // functions).  byj_src[j * byj_src_ld + c] = the i with f(i, j) = column c, or na; a long column has dol::kByJWave
+    // at j = 0 (it is among col_lists.longer); a short column where some j occurs twice has dol::kByJList there and is summed from
+    // its tuple list.  byj_col[j * byj_col_ld + i] = column of (i, j) or n_out.  Rows are padded to multiples of four.
     bool byj_ok = false;
-    int32_t byj_nbp = 0;               // rows of the two maps: nb padded to 4, 8, 10 or 16 (the extra rows hold kByJNone)
+    int32_t byj_nbp = 0;               // rows of the two maps: nb padded to 4, 8, 10 or 16 (the extra rows name nothing)
+    int32_t byj_src_ld = 0, byj_col_ld = 0;
     bool byj_fwd = false;              // forward uses the map only where it is at least half full (else the tuple lists)
     dol::DevArray<uint16_t> byj_src, byj_col;
-    dol::DevArray<uint32_t> byj_wave_cols;
     // tables whose operand rows fit in registers: straight-line kernels written for the table (built on first use)
     mutable std::unique_ptr<dol::JitState, dol::JitDeleter> jit;
     int device = 0;
@@ -227,12 +247,9 @@ dol_status launch_nll_grad(int32_t batch, int32_t n, const float *p, int64_t ld,
                            hipStream_t st);
 // Convolution-shaped tables with a short second operand (damp_conv.hip)
 bool conv_path_ok(const dol_fn_table *f);
-bool byj_fwd_staged_ok(const dol_fn_table *f);   // forward through the per-j map with the first operand's row in LDS
-bool staged_fwd_ok(const dol_fn_table *f);   // forward through the kernel that stages both operand rows in LDS
 std::string damp_kernel_name(const dol_fn_table *f, bool backward, int64_t batch = 0);
 // Large batches of contiguous, 16-byte aligned tensors (damp_conv_rows.hip); false: the call was not taken.
 bool conv_rows_ok(const dol_fn_table *f, int64_t batch, bool backward);
-bool apply2_bwd_staged(const dol_fn_table *f);       // the tuple-list backward stages the gated gradient row in LDS
 bool launch_damp_conv_rows_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
                                float *out, int64_t ldo, hipStream_t st, dol_status *status);
 bool launch_damp_conv_rows_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
@@ -247,6 +264,7 @@ dol_status launch_damp_conv_bwd(const dol_fn_table *f, int32_t batch, const floa
 dol_status lds_plan_build(dol_fn_table *tb, const std::vector<uint32_t> &col_ptr, const std::vector<uint32_t> &col_ij,
                           const std::vector<uint32_t> &rowa_ptr, const std::vector<uint32_t> &rowa_jc,
                           const std::vector<uint32_t> &rowb_ptr, const std::vector<uint32_t> &rowb_ic);
+bool lds_small_batch(const dol_fn_table *f, int64_t batch, bool backward);   // a workgroup per sample is faster (batch > 0)
 dol_status launch_damp_lds_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b,
                                int64_t ldb, float *out, int64_t ldo, hipStream_t st, bool *done);
 dol_status launch_damp_lds_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b,
@@ -261,6 +279,18 @@ bool fold_chain_ok(int n, const int32_t *m, const int32_t *nb, const int64_t *ld
 dol_status launch_fold_chain(int n, const int32_t *m, const int32_t *nb, int32_t batch, const float *const *in, const int64_t *ld,
                              float *const *gin, float *out, int64_t ldo, const int32_t *target, const float *gout, int64_t ldg,
                              int32_t backward, hipStream_t st);
+// A workgroup per sample, rows staged in LDS (damp_sample.hip); *done = false: the rows do not fit
+bool byj_fwd_sample_ok(const dol_fn_table *f);       // forward through the dense map
+bool list_fwd_sample_ok(const dol_fn_table *f);      // forward through the tuple lists
+bool byj_bwd_sample_ok(const dol_fn_table *f);
+bool list_bwd_sample_ok(const dol_fn_table *f);
+bool byj_fwd_wide(const dol_fn_table *f);
+bool byj_bwd_wide(const dol_fn_table *f);
+dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb, float *out,
+                             int64_t ldo, hipStream_t st, bool *done);
+dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
+                             const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
+                             hipStream_t st, bool *done);
 // Small arbitrary tables as code written for the table (damp_table.hip); *done = false: the call was not taken
 bool table_code_ok(const dol_fn_table *f);
 dol_status launch_damp_table_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b,

@@ -65,6 +65,41 @@ struct Tuple {
     int32_t i, j, id;
 };
 
+// struct ListPlan from lists ptr[x] .. ptr[x + 1] of word(q); lists above `wave_above` words get a wavefront.
+template <typename F>
+static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, uint32_t wave_above, F word, uint32_t filling, ListPlan *plan)
+{
+    std::vector<uint32_t> order = columns_by_length(ptr, n, kLaneList), start{0}, words, huge, wave, mid;
+    auto length = [&](uint32_t x) { const uint32_t l = ptr[x + 1] - ptr[x]; return l > static_cast<uint32_t>(kLaneList) ? 0u : l; };
+    for (int32_t r0 = 0; r0 < n; r0 += 64) {
+        uint32_t most = 0;
+        for (int32_t r = r0; r < std::min(n, r0 + 64); ++r) most = std::max(most, length(order[r]));
+        const size_t at = words.size();
+        words.resize(at + static_cast<size_t>(most) * 64, filling);
+        for (int32_t r = r0; r < std::min(n, r0 + 64); ++r)
+            for (uint32_t k = 0; k < length(order[r]); ++k) words[at + static_cast<size_t>(k) * 64 + (r - r0)] = word(ptr[order[r]] + k);
+        start.push_back(start.back() + most);
+    }
+    plan->n_words = words.size();
+    words.resize(words.size() + 4 * 64, filling);           // four words are read at a time
+    for (uint32_t &x : order)
+        if (ptr[x + 1] - ptr[x] > static_cast<uint32_t>(kLaneList)) x |= kListElsewhere;
+    while (order.size() % 64) order.push_back(kListElsewhere);
+    for (int32_t x = 0; x < n; ++x) {
+        const uint32_t l = ptr[x + 1] - ptr[x];
+        if (l <= static_cast<uint32_t>(kLaneList)) continue;
+        if (l > wave_above) plan->long_words += l;
+        (l > static_cast<uint32_t>(kHugeList) ? huge : l > wave_above ? wave : mid).push_back(static_cast<uint32_t>(x));
+    }
+    plan->n_huge = static_cast<int32_t>(huge.size()), plan->n_wave = static_cast<int32_t>(wave.size()), plan->n_mid = static_cast<int32_t>(mid.size());
+    huge.insert(huge.end(), wave.begin(), wave.end());
+    huge.insert(huge.end(), mid.begin(), mid.end());
+    hipError_t e;
+    if ((e = plan->order.upload(order)) != hipSuccess || (e = plan->ptr.upload(start)) != hipSuccess ||
+        (e = plan->longer.upload(huge)) != hipSuccess) return e;
+    return plan->words.upload(words);
+}
+
 static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, dol_fn_table **out)
 {
     // ascending (i, j); a function has one value per argument tuple
@@ -187,12 +222,6 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
         if ((e = tb->ord_len.upload(ord_len)) != hipSuccess || (e = tb->ord_tuples.upload(ord_tuples)) != hipSuccess)
             return hip_fail(e, "uploading the function table");
     }
-    {
-        std::vector<uint32_t> ord(col_head.size());
-        for (int32_t r = 0; r < S; ++r)
-            for (int u = 0; u < 4; ++u) ord[static_cast<size_t>(r) * 4 + u] = col_head[static_cast<size_t>(col_order[r]) * 4 + u];
-        if ((e = tb->col_head_ord.upload(ord)) != hipSuccess) return hip_fail(e, "uploading the function table");
-    }
     if ((e = tb->col_ptr.upload(col_ptr)) != hipSuccess || (e = tb->col_ij.upload(col_ij)) != hipSuccess ||
         (e = tb->rowa_ptr.upload(rowa_ptr)) != hipSuccess || (e = tb->rowa_jc.upload(rowa_jc)) != hipSuccess ||
         (e = tb->rowb_ptr.upload(rowb_ptr)) != hipSuccess || (e = tb->rowb_ic.upload(rowb_ic)) != hipSuccess ||
@@ -200,32 +229,42 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
         return hip_fail(e, "uploading the function table");
     if (!conv_path_ok(tb.get()))
         if (dol_status s2 = lds_plan_build(tb.get(), col_ptr, col_ij, rowa_ptr, rowa_jc, rowb_ptr, rowb_ic)) return s2;
-    if (!conv_path_ok(tb.get()) && !tb->lds_fwd_ok && !tb->lds_bwd_ok && nb >= 1 && nb <= kByJMax && na >= 1 &&
-        na <= kByJMaxNa && S >= 1 && S <= kByJMaxNa) {
+    if (!conv_path_ok(tb.get()) && na >= 1 && nb >= 1 && S >= 1 && na + nb < 0xFFFF && S < 0xFFFF) {
+        if ((e = upload_lists(col_ptr, S, kLaneList, [&](uint32_t q) { return col_ij[q]; }, pack16(na, nb), &tb->col_lists)) != hipSuccess)
+            return hip_fail(e, "uploading the function table");
+        std::vector<uint32_t> row_ptr(rowa_ptr);
+        for (int32_t j = 0; j < nb; ++j) row_ptr.push_back(rowa_ptr[na] + rowb_ptr[j + 1]);
+        const uint32_t n_a = rowa_ptr[na];
+        auto word = [&](uint32_t q) {
+            if (q < n_a) return pack16(na + (rowa_jc[q] & 0xffffu), rowa_jc[q] >> 16);
+            return rowb_ic[q - n_a];
+        };
+        if ((e = upload_lists(row_ptr, na + nb, kMidRow, word, pack16(na + nb, S), &tb->row_lists)) != hipSuccess)
+            return hip_fail(e, "uploading the function table");
+        tb->lists_ok = true;
+    }
+    if (!conv_path_ok(tb.get()) && nb >= 1 && nb <= kByJMax && na >= 1 && na <= kByJMaxNa && S >= 1 && S <= kByJMaxNa &&
+        tb->lists_ok) {
         const int32_t nbp = nb <= 4 ? 4 : nb <= 8 ? 8 : nb <= 10 ? 10 : 16;
-        tb->byj_nbp = nbp;
-        std::vector<uint16_t> src(static_cast<size_t>(nbp) * S, kByJNone), colof(static_cast<size_t>(nbp) * na, kByJNone);
-        std::vector<uint32_t> wave_cols, huge_cols;
+        const int32_t src_ld = (S + 3) & ~3, col_ld = (na + 3) & ~3;
+        tb->byj_nbp = nbp, tb->byj_src_ld = src_ld, tb->byj_col_ld = col_ld;
+        const uint16_t no_i = static_cast<uint16_t>(na), no_c = static_cast<uint16_t>(S);
+        std::vector<uint16_t> src(static_cast<size_t>(nbp) * src_ld, no_i), colof(static_cast<size_t>(nbp) * col_ld, no_c);
         for (int32_t c = 0; c < S; ++c) {
-            bool regular = col_ptr[c + 1] - col_ptr[c] <= static_cast<uint32_t>(kLongTableCol);
+            const bool is_long = col_ptr[c + 1] - col_ptr[c] > static_cast<uint32_t>(kLaneList);
+            bool regular = !is_long;
             for (uint32_t q = col_ptr[c]; q < col_ptr[c + 1] && regular; ++q) {
-                uint16_t &slot = src[static_cast<size_t>(col_ij[q] >> 16) * S + c];
-                if (slot != kByJNone) regular = false;
+                uint16_t &slot = src[static_cast<size_t>(col_ij[q] >> 16) * src_ld + c];
+                if (slot != no_i) regular = false;
                 slot = static_cast<uint16_t>(col_ij[q] & 0xffffu);
             }
             if (!regular) {
-                const bool is_long = col_ptr[c + 1] - col_ptr[c] > static_cast<uint32_t>(kLongTableCol);
-                for (int32_t j = 0; j < nb; ++j) src[static_cast<size_t>(j) * S + c] = kByJNone;
+                for (int32_t j = 0; j < nb; ++j) src[static_cast<size_t>(j) * src_ld + c] = no_i;
                 src[c] = is_long ? kByJWave : kByJList;
-                if (is_long) (col_ptr[c + 1] - col_ptr[c] > static_cast<uint32_t>(kHugeTableCol) ? huge_cols : wave_cols).push_back(static_cast<uint32_t>(c));
             }
         }
-        tb->n_huge_byj_cols = static_cast<int32_t>(huge_cols.size());
-        huge_cols.insert(huge_cols.end(), wave_cols.begin(), wave_cols.end());
-        wave_cols.swap(huge_cols);
-        for (size_t t = 0; t < tup.size(); ++t) colof[static_cast<size_t>(tup[t].j) * na + tup[t].i] = static_cast<uint16_t>(col[t]);
-        if ((e = tb->byj_src.upload(src)) != hipSuccess || (e = tb->byj_col.upload(colof)) != hipSuccess ||
-            (e = tb->byj_wave_cols.upload(wave_cols)) != hipSuccess)
+        for (size_t t = 0; t < tup.size(); ++t) colof[static_cast<size_t>(tup[t].j) * col_ld + tup[t].i] = static_cast<uint16_t>(col[t]);
+        if ((e = tb->byj_src.upload(src)) != hipSuccess || (e = tb->byj_col.upload(colof)) != hipSuccess)
             return hip_fail(e, "uploading the function table");
         tb->byj_ok = true;
         tb->byj_fwd = 2 * tup.size() >= static_cast<size_t>(nb) * static_cast<size_t>(S);

@@ -1644,6 +1644,72 @@ def test_short_second_operand_tables_near_the_clamp(dol):
     assert_close(host(gb), wb, "per-j grad b")
 
 
+@pytest.mark.parametrize("nb", [4, 16, 40])
+@pytest.mark.parametrize("extra,batch", [(0, 3), (57, 1), (4096, 2), (4097, 300)])
+def test_workgroup_per_sample_kernels(dol, nb, extra, batch):
+    """The kernels that give a sample a workgroup: columns of every kind of length (a lane each up to 64 tuples, a wavefront,
+    the workgroup above 512), result rows on either side of a block of 4 096 columns and of a part per workgroup, rows that
+    are not multiples of four.  A column's tags sum to within a few roundings of 1, so its clamp decision, seen through the
+    backward pass, must be the sequential float sum's; one long column hides its tail behind a large first term."""
+    lengths = [1, 2, 3, 4, 5, 16, 17, 63, 64, 65, 130, 511, 512, 513, 1500] + [4 if nb <= 16 else 1 + c % 3 for c in range(extra)]
+    total = sum(lengths)
+    col = np.repeat(np.arange(len(lengths)), lengths).astype(np.int32)
+    first = np.repeat(np.cumsum([0] + lengths[:-1]), lengths)
+    i = np.arange(total, dtype=np.int32)
+    j = ((i - first) % nb).astype(np.int32)
+    w = W.uniform01(900 + nb, batch * total).reshape(batch, total) ** 3 + 1e-9
+    w[:, first[col == 14][0]] *= 1e4
+    sums = np.add.reduceat(w, np.unique(first), axis=1)
+    a = (w / sums[:, col] * (1.0 + 1e-7 * ((np.arange(len(lengths)) * 7 + np.arange(batch)[:, None] * 3) % 5 - 2))[:, col]).astype(np.float32)
+    b = np.ones((batch, nb), np.float32)
+    tri = (i, j, col)
+    syms, want, pre32, pre64 = oracle.damp_apply2_fwd(tri, total, nb, a, b, want_pre=True)
+    assert (pre32 > 1).any() and (pre32 <= 1).any() and np.abs(pre64 - 1).max() < 1e-5
+    f = dol.FnTable.create_sparse(total, nb, *tri)
+    da, db = dol.Dist(np.arange(total), dev(a)), dol.Dist(np.arange(nb), dev(b))
+    out = dol.Dist.empty(f.out_syms, batch)
+    dol.apply2(da, db, f, None, out)
+    assert_close(host(out.prob), want, "forward")
+    np.testing.assert_array_equal(host(out.prob) == 1.0, pre32 >= 1.0)
+    g = (np.abs(W.normal(901, batch * syms.size)) + 0.5).astype(np.float32).reshape(batch, -1)
+    wa, wb = oracle.damp_apply2_bwd(tri, total, nb, a, b, g)
+    ga, gb = torch.empty_like(da.prob), torch.empty_like(db.prob)
+    rec = dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f)
+    dol.backward(rec, dev(g), ga, gb)
+    assert_close(host(ga), wa, "backward a")
+    assert_close(host(gb), wb, "backward b")
+    rec3 = dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f, accumulate=3)
+    dol.backward(rec3, dev(g), ga, gb)
+    assert_close(host(ga), 2.0 * wa.astype(np.float64), "backward a accumulated")
+    assert_close(host(gb), 2.0 * wb.astype(np.float64), "backward b accumulated")
+
+
+@pytest.mark.parametrize("na,nb,n_ids,batch", [(50, 37, 201, 4097), (13, 12, 30, 8200), (101, 10, 226, 8193)])
+def test_tiles_of_64_samples_at_large_batches(dol, na, nb, n_ids, batch):
+    """The kernels over tiles of 64 samples, which serve tables of this size above 4 096 (8 192) samples: ragged symbol counts
+    and a last tile that is not full, columns on either side of the clamp."""
+    tab = W.hashed_table(61, na, nb, n_ids)
+    tab[0, :] = -1
+    a = (W.uniform01(62, batch * na) * 0.5).astype(np.float32).reshape(batch, na)
+    b = (W.uniform01(63, batch * nb) * 0.8).astype(np.float32).reshape(batch, nb)
+    tri = oracle.dense_to_triples(tab)
+    syms, want, pre32, _ = oracle.damp_apply2_fwd(tri, na, nb, a, b, want_pre=True)
+    f = dol.FnTable.create_dense(tab)
+    assert f.kernel_at(False, batch) == "damp_lds_fwd_kernel" and f.kernel_at(True, batch) == "damp_lds_bwd_kernel"
+    assert f.kernel_at(False, 64) != f.kernel_at(False, batch)
+    da, db = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b))
+    out = dol.Dist.empty(syms, batch)
+    dol.apply2(da, db, f, None, out)
+    assert_close(host(out.prob), want, "tiles forward")
+    np.testing.assert_array_equal(host(out.prob) == 1.0, pre32 >= 1.0)
+    g = np.abs(W.normal(64, batch * syms.size)).astype(np.float32).reshape(batch, -1)
+    wa, wb = oracle.damp_apply2_bwd(tri, na, nb, a, b, g)
+    ga, gb = torch.empty_like(da.prob), torch.empty_like(db.prob)
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), dev(g), ga, gb)
+    assert_close(host(ga), wa, "tiles backward a")
+    assert_close(host(gb), wb, "tiles backward b")
+
+
 # ---------------------------------------------------------------- seeded random tables over every kernel choice
 
 @pytest.mark.parametrize("seed", range(24))
