@@ -60,9 +60,12 @@ __device__ __forceinline__ void sort_valley(float (&p)[K], int (&id)[K], int at)
         for (int x = 0; x < M; ++x) {
             if (x < H) {
                 const int xh = x < H ? x : 0;
-                const bool keep = p[at + x] > p[at + x + M];
-                hp[xh] = keep ? p[at + x] : p[at + x + M], lp[x] = keep ? p[at + x + M] : p[at + x];
-                hi[xh] = keep ? id[at + x] : id[at + x + M], li[x] = keep ? id[at + x + M] : id[at + x];
+                // (values first: a choice between array elements becomes a chain of selects over the whole array)
+                const float pa = p[at + x], pb = p[at + x + M];
+                const int ia = id[at + x], ib = id[at + x + M];
+                const bool keep = pa > pb;
+                hp[xh] = keep ? pa : pb, lp[x] = keep ? pb : pa;
+                hi[xh] = keep ? ia : ib, li[x] = keep ? ib : ia;
             } else {
                 lp[x] = p[at + x], li[x] = id[at + x];
             }
@@ -164,11 +167,12 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                     float cut = 2.0f * kNone;           // the best of the candidates and kept ones that drop out
 #pragma unroll
                     for (int x = 0; x < K; ++x) {
-                        const float o = offer[K - 1 - x];
-                        const bool keep = tp[x] > o;
-                        mp[x] = keep ? tp[x] : o;
-                        mi[x] = keep ? tid_[x] : id0 + (K - 1 - x);
-                        cut = fmaxf(cut, keep ? o : tp[x]);
+                        const float o = offer[K - 1 - x], t = tp[x];
+                        const int i_o = id0 + (K - 1 - x), i_t = tid_[x];
+                        const bool keep = t > o;
+                        mp[x] = keep ? t : o;
+                        mi[x] = keep ? i_t : i_o;
+                        cut = fmaxf(cut, keep ? o : t);
                     }
                     sort_valley<K, K>(mp, mi, 0);
 #pragma unroll
