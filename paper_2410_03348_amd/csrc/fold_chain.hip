@@ -67,6 +67,29 @@ struct Layout {
 
 int ceil_div(int a, int b) { return (a + b - 1) / b; }
 
+// Columns of an m-symbol row per lane.  Lanes read and write their blocks word by word, a block's width apart: a width of 8
+// puts the 16 lanes of a sample on four of the 32 LDS banks.  A column more costs 30 multiply-adds per lane and stage (half
+// of Sum-15's stages of that width would be idle columns otherwise) and takes a quarter of the bank conflicts away; widths
+// of 4, two to a bank, are not worth theirs.  Only the form for large grids is bound by that.
+int block_width(int m, int kL, bool regs)
+{
+    const int w = ceil_div(m, kL);
+    return regs && w % 8 == 0 ? w + 1 : w;
+}
+
+// Extra LDS cycles of a 64-lane word access whose lanes are `w` words apart inside a sample and whose samples are `stride`
+// words apart: 32 lanes are served at a time, by 32 banks.
+int conflict_cycles(int stride, int w, int kL)
+{
+    int extra = 0;
+    for (int first = 0; first < 64; first += 32) {
+        int hits[32] = {}, most = 0;
+        for (int lane = first; lane < first + 32; ++lane) most = std::max(most, ++hits[(lane / kL * stride + lane % kL * w) & 31]);
+        extra += most - 1;
+    }
+    return extra;
+}
+
 // regs: the reverse sweep's operands stay in the registers of the lanes that computed them and LDS holds two row buffers;
 // otherwise every running Distribution keeps a row of its own in LDS.
 Layout lay_out(const std::vector<int> &shape, int kL, bool regs)
@@ -77,9 +100,9 @@ Layout lay_out(const std::vector<int> &shape, int kL, bool regs)
     for (int t = 1; t < Y.n; ++t) {
         Y.nb[t] = shape[1 + t];
         Y.m[t] = Y.m[t - 1] + Y.nb[t] - 1;
-        Y.w[t] = ceil_div(Y.m[t], kL);
+        Y.w[t] = block_width(Y.m[t], kL, regs);
     }
-    Y.w[0] = ceil_div(Y.m[0], kL);
+    Y.w[0] = block_width(Y.m[0], kL, regs);
     int pos = 0;
     if (regs) {
         // Two row buffers: acc_t lives in buffer t & 1 while the next stage reads it.  A buffer holds a zero halo in front
@@ -109,12 +132,21 @@ Layout lay_out(const std::vector<int> &shape, int kL, bool regs)
     Y.off_d = pos;
     pos += Y.n * kNBR;
     int g_len = Y.m[Y.n - 1];
-    for (int t = 1; t < Y.n; ++t) g_len = std::max(g_len, kL * ceil_div(Y.m[t - 1], kL) + Y.nb[t] - 1);
+    for (int t = 1; t < Y.n; ++t) g_len = std::max(g_len, kL * Y.w[t - 1] + Y.nb[t] - 1);
     Y.g_len = g_len;
     Y.off_g0 = pos;
     Y.off_g1 = pos + g_len;
     pos += 2 * g_len;
-    Y.stride = pos | 1;                 // odd: the samples of a wavefront start in different banks
+    // the distance between a wavefront's samples: of the 32 that differ in their banks, the one with the fewest conflicts
+    // over the sweeps' accesses (Sum-15 at B=524288: 393 M of 395 M LDS cycles were in use, 164 M of them conflicts)
+    long best = 0;
+    for (int stride = pos + 1; stride <= pos + 32; ++stride) {
+        long cost = 0;
+        for (int t = 1; t < Y.n; ++t)
+            cost += static_cast<long>(2 * Y.w[t] + Y.nb[t]) * conflict_cycles(stride, Y.w[t], kL) +
+                    static_cast<long>(2 * Y.w[t - 1] + Y.nb[t]) * conflict_cycles(stride, Y.w[t - 1], kL);
+        if (stride == pos + 1 || cost < best) { best = cost; Y.stride = stride; }
+    }
     return Y;
 }
 
@@ -203,7 +235,7 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
     {
         bool used[64] = {};
         used[0] = true;
-        for (int t = 1; t < n; ++t) { used[Y.w[t]] = true; used[ceil_div(Y.m[t - 1], kL)] = true; }
+        for (int t = 1; t < n; ++t) { used[Y.w[t]] = true; used[Y.w[t - 1]] = true; }
         for (int x = 0; x < 64; ++x)
             if (used[x]) o("  const int lw%d = l * %d;\n", x, 4 * x);
         if (kL == 16) {     // which of a short operand's gradient sums a lane ends up with (see emit_scattered_sums)
@@ -247,6 +279,31 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
         }
     }
     o("  fence();\n");
+    // ---- can any sum of this wavefront's samples exceed 1?  max(acc_t) <= max(acc_0) * product of the sums of the short rows
+    // so far, and what rounding adds is far below the distance to 1 that is asked for.  Where none can, and no tag is
+    // negative, the sweeps below run without a clamp, a sign or a gate: 280 of the 2 900 vector instructions of Sum-15.
+    o("  bool calm;\n  { float top = 0.0f, prod = 1.0f; int bad = 0;\n");
+    for (int x = 0; x < Y.m[0]; x += kL)
+        o("    if (l + %d < %d) { const float v = base[%d + l]; top = fmaxf(top, v); bad |= !(v >= 0.0f); }\n", x, Y.m[0], Y.off[0] + x);
+    for (int t0 = 1; t0 < n; t0 += kL) {
+        o("    if (l + %d < %d) { const float *row = base + %d + l * %d; float sum = 0.0f;\n", t0, n, Y.off_d + t0 * kNBR, kNBR);
+        // (rows of different lengths: entries past a row's end were never written and count as 0)
+        int nb_max = 0;
+        bool same = true;
+        for (int t = t0; t < std::min(n, t0 + kL); ++t) { nb_max = std::max(nb_max, Y.nb[t]); same = same && Y.nb[t] == Y.nb[t0]; }
+        if (!same) {
+            o("      int len = 0;\n");
+            for (int t = t0; t < std::min(n, t0 + kL); ++t) o("      len = l == %d ? %d : len;\n", t - t0, Y.nb[t]);
+        }
+        for (int j = 0; j < nb_max; ++j)
+            o("      { const float v = row[%d]; %s{ sum += v; bad |= !(v >= 0.0f); } }\n", j, same ? "" : (std::string("if (") + std::to_string(j) + " < len) ").c_str());
+        o("      prod *= sum; }\n");
+    }
+    for (int st = 0; st < 4; ++st) o("    top = fmaxf(top, dppx(top, %d)); prod *= dppx(prod, %d);\n", st, st);
+    if (kL == 32) o("    top = fmaxf(top, __shfl_xor(top, 16)); prod *= __shfl_xor(prod, 16);\n");
+    o("    calm = __ballot(bad || !(top * fmaxf(prod, 1.0f) <= 0.999f)) == 0; }\n");
+    auto sweeps = [&](bool calm) {
+    auto tag = [&](const std::string &x) { return calm ? x : "__builtin_fabsf(" + x + ")"; };
     // ---- a lane's own block of every running Distribution stays in registers for the reverse sweep (sign = clamp decision)
     if (regs) {
         for (int k = 0; k < Y.w[0]; ++k) o("  const float h0_%d = base[%d + l * %d + %d];\n", k, Y.off[0], Y.w[0], k);
@@ -258,7 +315,7 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
         const int nb = Y.nb[t], w = Y.w[t], win = w + nb - 1;
         o("  {\n    DOL_ROW(rp, %d, %d); DOL_ROW(dp, %d, 0);\n", Y.off[t - 1] - (nb - 1), w, Y.off_d + t * kNBR);
         for (int j = 0; j < nb; ++j) o("    const float d%d = dp[%d];\n", j, j);
-        for (int k = 0; k < win; ++k) o("    const float r%d = __builtin_fabsf(rp[%d]);\n", k, k);
+        for (int k = 0; k < win; ++k) o("    const float r%d = %s;\n", k, tag("rp[" + std::to_string(k) + "]").c_str());
         for (int k = 0; k < w; ++k) {
             // column c = l * w + k: ascending i = c - j, one fma per tuple
             o("    float p%d = 0.0f;\n", k);
@@ -266,8 +323,9 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
         }
         o("    DOL_ROW(wp, %d, %d);\n", Y.off[t], w);
         for (int k = 0; k < w; ++k) {
-            if (regs) o("    h%d_%d = p%d <= 1.0f ? p%d : -1.0f; wp[%d] = h%d_%d;\n", t, k, k, k, k, t, k);
-            else o("    wp[%d] = p%d <= 1.0f ? p%d : -1.0f;\n", k, k, k);
+            const std::string kept = calm ? "p" + std::to_string(k) : "p" + std::to_string(k) + " <= 1.0f ? p" + std::to_string(k) + " : -1.0f";
+            if (regs) o("    h%d_%d = %s; wp[%d] = h%d_%d;\n", t, k, kept.c_str(), k, t, k);
+            else o("    wp[%d] = %s;\n", k, kept.c_str());
         }
         o("  }\n  fence();\n");
     }
@@ -277,15 +335,24 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
         o("    %s os[%d + l] = __builtin_fabsf(base[%d + l]);\n", Y.m[n1] - x >= kL ? "" : (std::string("if (l < ") + std::to_string(Y.m[n1] - x) + ")").c_str(),
           x, Y.off[n1] + x);
     o("  }\n  if (!A.backward) return;\n");
-    // ---- upstream gradient into the first gradient row, gated by the last stage's clamp.  With a target the row is
-    // zero but for one entry, which one lane works out (one division per sample instead of one per column)
-    o("  if (A.target) {\n");
-    for (int x = 0; x < Y.g_len; x += kL)
-        o("    %sbase[%d + l] = 0.0f;\n", Y.g_len - x >= kL ? "" : (std::string("if (l < ") + std::to_string(Y.g_len - x) + ") ").c_str(), Y.off_g0 + x);
-    o("    const int tgt = A.target[s];\n");
-    o("    if (l == 0 && tgt >= 0 && tgt < %d) { const float xv = base[%d + tgt];\n", Y.m[n1], Y.off[n1]);
-    o("      base[%d + tgt] = xv < 0.0f ? 0.0f : -1.0f / fmaxf(xv, 1.17549435e-38f); }\n", Y.off_g0);
-    o("  } else { const float *gs = A.gout + (long long)s * A.ldg;\n");
+    // ---- the last stage under a target: its gradient row is zero but for one entry G, so the first operand's gradient is
+    // G * d[target - i] (nb entries) and the short operand's G * a[target - j]; a lane per entry (one division per lane,
+    // where the general stage below takes w * 2 nb multiply-adds and a reduction)
+    {
+        const int t = n1, nb = Y.nb[t], m = Y.m[t - 1];
+        o("  if (A.target) {\n");
+        for (int x = 0; x < Y.g_len; x += kL)
+            o("    %sbase[%d + l] = 0.0f;\n", Y.g_len - x >= kL ? "" : (std::string("if (l < ") + std::to_string(Y.g_len - x) + ") ").c_str(), Y.off_g1 + x);
+        o("    fence();\n    const int tgt = A.target[s];\n    float gv = 0.0f;\n");
+        o("    if (tgt >= 0 && tgt < %d) { const float xv = base[%d + tgt]; gv = xv < 0.0f ? 0.0f : -1.0f / fmaxf(xv, 1.17549435e-38f); }\n", Y.m[n1], Y.off[n1]);
+        o("    if (l < %d) { const int i = tgt - l; float sv = 0.0f;\n", nb);
+        o("      if (i >= 0 && i < %d) { const float x = base[%d + i];\n", m, Y.off[t - 1]);
+        o("        base[%d + i] = %sgv * base[%d + l]; sv = gv * __builtin_fabsf(x); }\n", Y.off_g1, t > 1 ? "x < 0.0f ? 0.0f : " : "", Y.off_d + t * kNBR);
+        o("      base[%d + l] = sv; }\n", Y.off_d + t * kNBR);
+        o("    fence();\n  } else {\n");
+    }
+    // ---- upstream gradient into the first gradient row, gated by the last stage's clamp
+    o("  { const float *gs = A.gout + (long long)s * A.ldg;\n");
     for (int x = 0; x < Y.g_len; x += kL) {
         const bool whole = Y.g_len - x >= kL;
         o("    %s{ const int c = %d + l; float gv = 0.0f;\n", whole ? "" : (std::string("if (l < ") + std::to_string(Y.g_len - x) + ") ").c_str(), x);
@@ -298,7 +365,7 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
     o("  }\n  fence();\n");
     // ---- reverse sweep
     for (int t = n1; t >= 1; --t) {
-        const int nb = Y.nb[t], m = Y.m[t - 1], v = ceil_div(m, kL), win = v + nb - 1;
+        const int nb = Y.nb[t], m = Y.m[t - 1], v = Y.w[t - 1], win = v + nb - 1;
         const int g_cur = (n1 - t) & 1 ? Y.off_g1 : Y.off_g0, g_nxt = (n1 - t) & 1 ? Y.off_g0 : Y.off_g1;
         o("  {\n    DOL_ROW(gp, %d, %d); DOL_ROW(dp, %d, 0);\n", g_cur, v, Y.off_d + t * kNBR);
         if (!regs) o("    DOL_ROW(ap, %d, %d);\n", Y.off[t - 1], v);
@@ -315,17 +382,17 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
             for (int j = 0; j < nb; ++j) o("      acc = __builtin_fmaf(g%d, d%d, acc);\n", k + j, j);
             // rows past the operand's last symbol hold 0; a row whose own sum was clamped (sign) passes no gradient on
             // (only the last lanes' last rows can lie past the end: the test is written where that can happen)
-            const bool past = (kL - 1) * v + k >= m;
-            if (t > 1 && past) o("      wp[%d] = (l * %d + %d < %d && !(x%d < 0.0f)) ? acc : 0.0f;\n", k, v, k, m, k);
-            else if (t > 1) o("      wp[%d] = !(x%d < 0.0f) ? acc : 0.0f;\n", k, k);
+            const bool past = (kL - 1) * v + k >= m, gate = t > 1 && !calm;
+            if (gate && past) o("      wp[%d] = (l * %d + %d < %d && !(x%d < 0.0f)) ? acc : 0.0f;\n", k, v, k, m, k);
+            else if (gate) o("      wp[%d] = !(x%d < 0.0f) ? acc : 0.0f;\n", k, k);
             else if (past) o("      wp[%d] = l * %d + %d < %d ? acc : 0.0f;\n", k, v, k, m);
             else o("      wp[%d] = acc;\n", k);
-            for (int j = 0; j < nb; ++j) o("      s%d = __builtin_fmaf(g%d, __builtin_fabsf(x%d), s%d);\n", j, k + j, k, j);
+            for (int j = 0; j < nb; ++j) o("      s%d = __builtin_fmaf(g%d, %s, s%d);\n", j, k + j, tag("x" + std::to_string(k)).c_str(), j);
             o("    }\n");
         }
         // the next stage's windows reach past the rows just written: zeros there
         if (t > 1) {
-            const int need = kL * ceil_div(Y.m[t - 2], kL) + Y.nb[t - 1] - 1, have = kL * v;
+            const int need = kL * Y.w[t - 2] + Y.nb[t - 1] - 1, have = kL * v;
             for (int x = have; x < need; x += kL)
                 o("    %s base[%d + l] = 0.0f;\n", need - x >= kL ? "" : (std::string("if (l < ") + std::to_string(need - x) + ")").c_str(), g_nxt + x);
         }
@@ -341,7 +408,14 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
             emit_scattered_sums(o, nb);
             o("    dp[jl%d] = s0;\n  }\n  fence();\n", nb);
         }
+        if (t == n1) o("  }\n");                                    // (end of the branch without a target)
     }
+    };
+    o("  if (calm) {\n");
+    sweeps(true);
+    o("  } else {\n");
+    sweeps(false);
+    o("  }\n");
     // ---- gradients out
     o("  if (!live) return;\n");
     {
@@ -390,8 +464,16 @@ bool fold_chain_ok(int n, const int32_t *m, const int32_t *nb, const int64_t *ld
         shape.push_back(nb[t]);
     }
     if (m[0] < 1 || m[0] > 256) return false;
-    const Layout Y = lay_out(shape, kLanes, false);
-    return sizeof(float) * (64 / kLanes) * static_cast<size_t>(Y.stride) <= kChainLdsMax;
+    static std::mutex mu;
+    static std::map<std::vector<int>, bool> known;          // (laying a chain out takes 70 us)
+    std::lock_guard<std::mutex> lock(mu);
+    auto it = known.find(shape);
+    if (it == known.end()) {
+        const Layout Y = lay_out(shape, kLanes, false);
+        if (known.size() >= 4096) known.clear();
+        it = known.emplace(std::move(shape), sizeof(float) * (64 / kLanes) * static_cast<size_t>(Y.stride) <= kChainLdsMax).first;
+    }
+    return it->second;
 }
 
 dol_status launch_fold_chain(int n, const int32_t *m, const int32_t *nb, int32_t batch, const float *const *in, const int64_t *ld,
