@@ -17,12 +17,15 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libdolphin_hip.so")
 
-if not os.path.exists(LIB_PATH):
+_NATIVE_PATH = os.path.join(_HERE, "_native.so")
+
+if not (os.path.exists(LIB_PATH) and os.path.exists(_NATIVE_PATH)):
     raise ImportError(
-        "libdolphin_hip.so is not built (%s). Run `python -c 'import __graft_entry__ as g; g.build()'` "
+        "libdolphin_hip.so or _native.so is not built (%s). Run `python -c 'import __graft_entry__ as g; g.build()'` "
         "or `python paper_2410_03348_amd/build.py`; there is no CPU fallback." % LIB_PATH)
 
 _lib = C.CDLL(LIB_PATH)
+from . import _native  # noqa: E402 (the calls issued once per operator; the others go through ctypes)
 
 DAMP, DTKP = 0, 1
 OP_APPLY2, OP_FILTER, OP_UNION, OP_FILTER_UNION = 0, 1, 2, 3
@@ -110,12 +113,24 @@ def _check(status: int):
         raise DolError(status, last_error())
 
 
+def _fail(status: int):
+    raise DolError(status, last_error())
+
+
+_native.setup(_fail, torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+
+
 def _np_i32(x) -> np.ndarray:
     return np.ascontiguousarray(x, dtype=np.int32)
 
 
 def _ptr(a: Optional[np.ndarray], ct):
     return None if a is None else a.ctypes.data_as(C.POINTER(ct))
+
+
+def _handle(stream):
+    """The same as the native calls take it: an integer, or None = torch's current stream."""
+    return stream.cuda_stream if isinstance(stream, torch.cuda.Stream) else stream if stream is None else int(stream)
 
 
 def _stream(stream) -> C.c_void_p:
@@ -142,6 +157,7 @@ class Prov:
             assert self._grp.size == n_facts
         self.c = _Prov(kind, k, n_facts, _ptr(self._grp, C.c_int32),
                        C.c_void_p(fact_prob.data_ptr()) if fact_prob is not None else None)
+        self._p = C.addressof(self.c)
 
     def ref(self):
         return C.byref(self.c)
@@ -171,6 +187,7 @@ class Dist:
                        C.c_void_p(prob.data_ptr()) if prob is not None else None,
                        C.c_void_p(proof_mask.data_ptr()) if proof_mask is not None else None,
                        C.c_void_p(proof_prob.data_ptr()) if proof_prob is not None else None)
+        self._p = C.addressof(self.c)
 
     def ref(self):
         return C.byref(self.c)
@@ -193,7 +210,7 @@ class FnTable:
     """dol_fn_table handle."""
 
     def __init__(self, handle: C.c_void_p, na: int, nb: int):
-        self._h, self.na, self.nb = handle, na, nb
+        self._h, self._p, self.na, self.nb = handle, handle.value, na, nb
         self.n_out = int(_lib.dol_fn_table_n_out(handle))
         p = _lib.dol_fn_table_out_syms(handle)
         self.out_syms = np.ctypeslib.as_array(p, shape=(self.n_out,)).copy() if self.n_out else np.empty(0, np.int32)
@@ -234,7 +251,7 @@ class FnTable:
     def destroy(self):
         if self._h is not None:
             _lib.dol_fn_table_destroy(self._h)
-            self._h = None
+            self._h = self._p = None
 
     def __del__(self):
         # The collector may run this at any moment, also while a stream is being captured into a HIP graph, where
@@ -244,7 +261,7 @@ class FnTable:
                 return
             if torch.cuda.is_available() and torch.cuda.is_current_stream_capturing():
                 _deferred_tables.append(self._h)
-                self._h = None
+                self._h = self._p = None
                 return
             self.destroy()
             while _deferred_tables:
@@ -257,7 +274,7 @@ _deferred_tables = []
 
 
 def apply2(a: Dist, b: Dist, f: FnTable, prov: Optional[Prov], out: Dist, stream=None):
-    _check(_lib.dol_apply2(a.ref(), b.ref(), f._h, prov.ref() if prov else None, out.ref(), _stream(stream)))
+    _native.apply2(a._p, b._p, f._p, prov._p if prov else None, out._p, None if stream is None else _handle(stream))
 
 
 class FnkTable:
@@ -319,7 +336,7 @@ def dtkp_apply2_input(a: Dist, fact_of_sym_b, f: FnTable, prov: Prov, out: Dist,
     """dol_apply2 whose second operand is an input Distribution: symbol j of it is fact fact_of_sym_b[j]."""
     fb = _np_i32(fact_of_sym_b)
     assert fb.size == f.nb
-    _check(_lib.dol_dtkp_apply2_input(a.ref(), _ptr(fb, C.c_int32), f._h, prov.ref(), out.ref(), _stream(stream)))
+    _native.dtkp_apply2_input(a._p, fb, f._p, prov._p, out._p, _handle(stream))
 
 
 def filter_plan(d: Dist, pred_mask):
@@ -332,7 +349,7 @@ def filter_plan(d: Dist, pred_mask):
 
 def filter(d: Dist, pred_mask, prov: Optional[Prov], out: Dist, stream=None):  # noqa: A001 (the operator's name)
     pm = np.ascontiguousarray(pred_mask, dtype=np.uint8)
-    _check(_lib.dol_filter(d.ref(), _ptr(pm, C.c_uint8), prov.ref() if prov else None, out.ref(), _stream(stream)))
+    _native.filter(d._p, pm, prov._p if prov else None, out._p, _handle(stream))
 
 
 def union_plan(a: Dist, b: Dist):
@@ -343,7 +360,7 @@ def union_plan(a: Dist, b: Dist):
 
 
 def union(a: Dist, b: Dist, prov: Optional[Prov], out: Dist, stream=None):
-    _check(_lib.dol_union(a.ref(), b.ref(), prov.ref() if prov else None, out.ref(), _stream(stream)))
+    _native.union(a._p, b._p, prov._p if prov else None, out._p, _handle(stream))
 
 
 def filter_union_plan(d: Dist, pred_mask, c: Dist):
@@ -406,7 +423,7 @@ def apply2_filter_union_forward_backward(m: ApplyMerge, grad_out: torch.Tensor, 
 
 def dtkp_init(d: Dist, fact_of_sym, prov: Prov, stream=None):
     fos = _np_i32(fact_of_sym)
-    _check(_lib.dol_dtkp_init(d.ref(), _ptr(fos, C.c_int32), prov.ref(), _stream(stream)))
+    _native.dtkp_init(d._p, fos, prov._p, _handle(stream))
 
 
 class OpRecord:
@@ -419,6 +436,7 @@ class OpRecord:
         self.c = _OpRecord(op, C.pointer(a.c), C.pointer(b.c) if b is not None else None, C.pointer(out.c),
                            f._h if f is not None else None, _ptr(self.pred, C.c_uint8),
                            C.pointer(prov.c) if prov is not None else None, accumulate)
+        self._p = C.addressof(self.c)
 
 
 def _dptr(t: Optional[torch.Tensor]):
@@ -428,15 +446,16 @@ def _dptr(t: Optional[torch.Tensor]):
 def backward(rec: OpRecord, grad_out: torch.Tensor, grad_a: Optional[torch.Tensor], grad_b: Optional[torch.Tensor],
              stream=None):
     """grad_out rows have stride rec.out.ld, grad_a rows rec.a.ld, grad_b rows rec.b.ld."""
-    _check(_lib.dol_backward(C.byref(rec.c), _dptr(grad_out), _dptr(grad_a), _dptr(grad_b), _stream(stream)))
+    _native.backward(rec._p, None if grad_out is None else grad_out.data_ptr(), None if grad_a is None else grad_a.data_ptr(),
+                     None if grad_b is None else grad_b.data_ptr(), None if stream is None else _handle(stream))
 
 
 def dtkp_backward(d: Dist, prov: Prov, grad_prob: torch.Tensor, grad_fact_prob: torch.Tensor, stream=None):
     """grad_prob [batch, >= n_sym] (row stride = its stride(0)); grad_fact_prob [batch, n_facts] contiguous, overwritten."""
     assert grad_prob.dtype == torch.float32 and grad_prob.dim() == 2 and grad_prob.stride(1) == 1
     assert grad_fact_prob.dtype == torch.float32 and grad_fact_prob.is_contiguous()
-    _check(_lib.dol_dtkp_backward(d.ref(), prov.ref(), _dptr(grad_prob), max(int(grad_prob.stride(0)), grad_prob.shape[1]),
-                                  _dptr(grad_fact_prob), _stream(stream)))
+    _native.dtkp_backward(d._p, prov._p, grad_prob.data_ptr(), max(int(grad_prob.stride(0)), grad_prob.shape[1]),
+                          grad_fact_prob.data_ptr(), _handle(stream))
 
 
 class _Fold(C.Structure):
@@ -473,10 +492,11 @@ class Fold:
         self.c = _Fold(n, self._in, self._tb, C.pointer(out.c) if out is not None else None,
                        _dptr(target_col), _dptr(grad_out), ldg,
                        C.cast(self._gi, C.POINTER(C.c_void_p)) if self._gi is not None else None)
+        self._p = C.addressof(self.c)
 
 
 def fold_apply2(fold: Fold, stream=None):
-    _check(_lib.dol_fold_apply2(C.byref(fold.c), _stream(stream)))
+    _native.fold_apply2(fold._p, None if stream is None else _handle(stream))
 
 
 def fold_kernel(fold: Fold) -> str:
@@ -514,10 +534,11 @@ class DtkpFold:
             assert grad_fact_prob.dtype == torch.float32 and grad_fact_prob.is_contiguous()
         self.c = _DtkpFold(n, self._in, self._fo, self._tb, C.pointer(out.c), _dptr(target_col), _dptr(grad_out), ldg,
                            _dptr(grad_fact_prob))
+        self._p = C.addressof(self.c)
 
 
 def dtkp_fold_apply2(fold: DtkpFold, prov: Prov, stream=None):
-    _check(_lib.dol_dtkp_fold_apply2(C.byref(fold.c), prov.ref(), _stream(stream)))
+    _native.dtkp_fold_apply2(fold._p, prov._p, None if stream is None else _handle(stream))
 
 
 _lib.dol_iterate_apply2.argtypes = [C.POINTER(_Dist), C.POINTER(_Dist), C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]
@@ -618,4 +639,4 @@ def iterate_backward_noalloc(r0: Dist, e: Dist, f: FnTable, rounds: int, grad_ou
 def nll_grad(d: Dist, target_col: torch.Tensor, grad: torch.Tensor, stream=None):
     """target_col: int32 device tensor [batch]; grad rows have stride d.ld."""
     assert target_col.dtype == torch.int32 and target_col.is_contiguous()
-    _check(_lib.dol_nll_grad(d.ref(), _dptr(target_col), _dptr(grad), _stream(stream)))
+    _native.nll_grad(d._p, target_col.data_ptr(), grad.data_ptr(), None if stream is None else _handle(stream))

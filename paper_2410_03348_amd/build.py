@@ -6,12 +6,14 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libdolphin_hip.so")
+NATIVE = os.path.join(HERE, "_native.so")       # CPython front of the per-operator calls (csrc/native.cpp)
 
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
@@ -61,6 +63,14 @@ def build(verbose: bool = False, incremental: bool = False) -> str:
     rc, err = _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs + ["-L/opt/rocm/lib", "-lhiprtc"])
     if rc != 0:
         raise RuntimeError("linking libdolphin_hip.so failed:\n" + err)
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-I", os.path.join(ROOT, "include"),
+           "-I", sysconfig.get_paths()["include"], os.path.join(CSRC, "native.cpp"), "-o", NATIVE, "-L", HERE, "-ldolphin_hip",
+           "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    rc, err = _run(cmd)
+    if rc != 0:
+        raise RuntimeError("building _native.so failed:\n" + err)
     return LIB
 
 
