@@ -279,22 +279,26 @@ damp_byj_fwd_staged_kernel(const SampleFwd A)
 
 // ---------------------------------------------------------------- forward, tuple lists
 
-// A wavefront walks one chunk of 64 lists at a time, four words of each per step; a step's words, and the first ones of the
+// A wavefront walks one chunk of 64 lists at a time, N words of each per step; a step's words, and the first ones of the
 // next chunk, are read while the step before is worked on (they come from L2, whose latency is what this would cost).
+// Columns: N = 4 (most are short); rows, of as many tuples as the other operand has symbols: N = 8.
+template <int N>
 struct Chunk {
-    uint32_t e, w0, len, t[4];
+    uint32_t e, w0, len, t[N];
 };
 
-__device__ __forceinline__ void read_words(uint32_t (&t)[4], const Lists &L, uint32_t w)
+template <int N>
+__device__ __forceinline__ void read_words(uint32_t (&t)[N], const Lists &L, uint32_t w)
 {
     const uint32_t *__restrict__ p = L.words + static_cast<size_t>(w) * kWave + (threadIdx.x & (kWave - 1));
 #pragma unroll
-    for (int u = 0; u < 4; ++u) t[u] = p[u * kWave];
+    for (int u = 0; u < N; ++u) t[u] = p[u * kWave];
 }
 
-__device__ __forceinline__ Chunk read_chunk(const Lists &L, int ch)
+template <int N>
+__device__ __forceinline__ Chunk<N> read_chunk(const Lists &L, int ch)
 {
-    Chunk c;
+    Chunk<N> c;
     c.w0 = L.ptr[ch], c.len = L.ptr[ch + 1] - c.w0;
     c.e = L.order[ch * kWave + (threadIdx.x & (kWave - 1))];
     read_words(c.t, L, c.w0);
@@ -305,24 +309,26 @@ __device__ __forceinline__ int wave_number() { return __builtin_amdgcn_readfirst
 
 // Walks the chunks [ch0, ch1), a wavefront every blockDim.x / 64th: term(word, sum) takes a tuple into a list's sum, in list
 // order, and done(list, sum) is called for every list that is walked here.  `now`: this wavefront's first chunk.
-template <typename T, typename D>
-__device__ __forceinline__ void walk_lists(const Lists &L, int ch0, int ch1, Chunk now, T term, D done)
+template <int N, typename T, typename D>
+__device__ __forceinline__ void walk_lists(const Lists &L, int ch0, int ch1, Chunk<N> now, T term, D done)
 {
     const int n_waves = blockDim.x / kWave;
     for (int ch = ch0 + wave_number(); ch < ch1; ch += n_waves) {
-        const Chunk next = read_chunk(L, min(ch + n_waves, ch1 - 1));
+        const Chunk<N> next = read_chunk<N>(L, min(ch + n_waves, ch1 - 1));
         float acc = 0.0f;
-        for (uint32_t w = 0; w < now.len; w += 4) {
-            uint32_t t[4] = {now.t[0], now.t[1], now.t[2], now.t[3]};
-            if (w + 4 < now.len) read_words(now.t, L, now.w0 + w + 4);
-            const uint32_t left = now.len - w;              // (the same for all lanes)
-            if (left >= 4) {
+        for (uint32_t w = 0; w < now.len; w += N) {
+            uint32_t t[N];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) acc = term(t[u], acc);
+            for (int u = 0; u < N; ++u) t[u] = now.t[u];
+            if (w + N < now.len) read_words<N>(now.t, L, now.w0 + w + N);
+            const uint32_t left = now.len - w;              // (the same for all lanes)
+            if (left >= static_cast<uint32_t>(N)) {
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc = term(t[u], acc);
             } else {
-                acc = term(t[0], acc);
-                if (left > 1) acc = term(t[1], acc);
-                if (left > 2) acc = term(t[2], acc);
+#pragma unroll
+                for (int u = 0; u < N - 1; ++u)
+                    if (static_cast<uint32_t>(u) < left) acc = term(t[u], acc);
             }
         }
         if (!(now.e & kListElsewhere)) done(static_cast<int>(now.e), acc);
@@ -340,18 +346,18 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
     const int part = static_cast<int>(blockIdx.x - s * A.parts);
     constexpr int kBlockChunks = kOrderBlock / kWave;
     const int n_chunks = (A.S + kWave - 1) / kWave;
-    Chunk now = read_chunk(A.lists, min(part * kBlockChunks + wave_number(), n_chunks - 1));
+    Chunk<4> now = read_chunk<4>(A.lists, min(part * kBlockChunks + wave_number(), n_chunks - 1));
     copy_row(ar, A.a + s * A.lda, A.na);
     copy_row(br, A.b + s * A.ldb, A.nb);
     __syncthreads();
     float *out = A.out + s * A.ldo;
     for (int b0 = part * kOrderBlock; b0 < A.S; b0 += A.parts * kOrderBlock) {
         const int b1 = min(A.S, b0 + kOrderBlock);
-        walk_lists(A.lists, b0 / kWave, (b1 + kWave - 1) / kWave, now,
+        walk_lists<4>(A.lists, b0 / kWave, (b1 + kWave - 1) / kWave, now,
                    [&](uint32_t t, float acc) { return __builtin_fmaf(ar[t & 0xffffu], br[t >> 16], acc); },
                    [&](int c, float v) { res[c - b0] = v; });
         const int next = b0 + A.parts * kOrderBlock;
-        if (next < A.S) now = read_chunk(A.lists, min(next / kWave + wave_number(), n_chunks - 1));
+        if (next < A.S) now = read_chunk<4>(A.lists, min(next / kWave + wave_number(), n_chunks - 1));
         long_columns(A, ar, br, b0, b1, scratch, [&](int c, float v) { res[c - b0] = v; });
         __syncthreads();
         for (int c = 4 * static_cast<int>(threadIdx.x); c < b1 - b0; c += 4 * static_cast<int>(blockDim.x)) {
@@ -489,7 +495,7 @@ damp_apply2_bwd_staged_kernel(const SampleBwd A)
     const float *ar = A.a + s * A.lda, *br = A.b + s * A.ldb;
     const int n = A.na + A.nb;
     const int n_chunks = (n + kWave - 1) / kWave;
-    const Chunk now = read_chunk(A.lists, min(wave_number(), n_chunks - 1));
+    const Chunk<8> now = read_chunk<8>(A.lists, min(wave_number(), n_chunks - 1));
     if (ROWS) {
         for (int e = threadIdx.x; e < A.na; e += blockDim.x) rows[e] = ar[e];
         for (int e = threadIdx.x; e < A.nb; e += blockDim.x) rows[A.na + e] = br[e];
@@ -509,7 +515,7 @@ damp_apply2_bwd_staged_kernel(const SampleBwd A)
         float *dst = is_a ? A.ga + s * A.lda + x : A.gb + s * A.ldb + (x - A.na);
         *dst = (A.accumulate & (is_a ? 1 : 2)) ? *dst + v : v;
     };
-    walk_lists(A.lists, 0, n_chunks, now, term, put);
+    walk_lists<8>(A.lists, 0, n_chunks, now, term, put);
     const Lists &L = A.lists;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
     // the partial sum of this lane, one of `step` lanes, over the list of element x
@@ -556,6 +562,93 @@ damp_apply2_bwd_staged_kernel(const SampleBwd A)
     }
 }
 
+// ---------------------------------------------------------------- Apply + Filter + Union, forward, backward or both
+
+struct SampleMerge {
+    int32_t na, nb, S, nc, n3, accumulate;
+    Lists cols, rows;
+    const int32_t *ia, *ib, *ca, *cb;   // struct UnionPlan
+    const float *a, *b, *c, *g;
+    float *out, *ga, *gb, *gc;
+    int32_t *saved;
+};
+
+// The merged calls (api.hip) for small batches and tables of columns and rows of at most 64 tuples: contiguous tensors, all
+// of a sample's rows in LDS, nothing intermediate anywhere else.  What counts is the chain of latencies: the rows and the
+// first words of both sweeps' lists are requested together, and the only other memory the kernel waits for are the lists'
+// further words.
+template <bool FWD, bool BWD>
+__global__ void __launch_bounds__(512)
+damp_merge_sample_kernel(const SampleMerge A)
+{
+    extern __shared__ __align__(16) float lds[];            // [a][b][0], sums of the Apply, c's row, gated gradient and 0
+    const int n = A.na + A.nb;
+    float *rows = lds, *pre = rows + ((n + 4) & ~3), *cr = pre + A.S, *gh = cr + A.nc;
+    const int64_t s = blockIdx.x;
+    const int T = blockDim.x, tid = threadIdx.x, wave = wave_number();
+    const int col_chunks = (A.S + kWave - 1) / kWave, row_chunks = (n + kWave - 1) / kWave;
+    Chunk<4> first_cols = read_chunk<4>(A.cols, min(wave, col_chunks - 1));
+    Chunk<8> first_rows{};
+    if (BWD) first_rows = read_chunk<8>(A.rows, min(wave, row_chunks - 1));
+    int acted = BWD && !FWD && A.saved ? A.saved[s] : 1;
+    for (int e = tid; e < n; e += T) rows[e] = e < A.na ? A.a[s * A.na + e] : A.b[s * A.nb + (e - A.na)];
+    for (int e = tid; e < A.nc; e += T) cr[e] = A.c[s * A.nc + e];
+    if (tid == 0) { rows[n] = 0.0f; if (BWD) gh[A.S] = 0.0f; }
+    __syncthreads();
+    if (FWD || acted) {                     // (the same for the whole workgroup)
+        int over = 0;
+        walk_lists<4>(A.cols, 0, col_chunks, first_cols,
+                      [&](uint32_t t, float acc) { return __builtin_fmaf(rows[t & 0xffffu], rows[A.na + (t >> 16)], acc); },
+                      [&](int c, float v) { pre[c] = v; over |= v > 1.0f; });
+        __syncthreads();
+        if (FWD) {
+            for (int u = tid; u < A.n3; u += T) {
+                const int i = A.ia[u], j = A.ib[u];
+                const float x = i >= 0 ? fminf(pre[i], 1.0f) : 0.0f, y = j >= 0 ? cr[j] : 0.0f;
+                float v = i >= 0 ? x : y;
+                if (i >= 0 && j >= 0) {
+                    v = x + y;
+                    over |= !(v <= 1.0f);
+                    v = fminf(v, 1.0f);
+                }
+                A.out[s * A.n3 + u] = v;
+            }
+            acted = __syncthreads_or(over);
+            if (A.saved && tid == 0) A.saved[s] = acted ? 1 : 0;
+        }
+    }
+    if (!BWD) return;
+    const float *gr = A.g + s * A.n3;
+    for (int x = tid; x < A.S; x += T) {    // the gradient that reaches each of the Apply's sums
+        const int oc = A.ca[x];
+        float v = oc >= 0 ? gr[oc] : 0.0f;
+        if (acted && oc >= 0) {
+            const int j = A.ib[oc];
+            if (!(pre[x] <= 1.0f) || (j >= 0 && !(fminf(pre[x], 1.0f) + cr[j] <= 1.0f))) v = 0.0f;
+        }
+        gh[x] = v;
+    }
+    if (A.gc)
+        for (int j = tid; j < A.nc; j += T) {
+            const int oc = A.cb[j];
+            float v = oc >= 0 ? gr[oc] : 0.0f;
+            if (acted && oc >= 0) {
+                const int i = A.ia[oc];
+                if (i >= 0 && !(fminf(pre[i], 1.0f) + cr[j] <= 1.0f)) v = 0.0f;
+            }
+            float *dst = A.gc + s * A.nc + j;
+            *dst = (A.accumulate & 4) ? *dst + v : v;
+        }
+    __syncthreads();
+    walk_lists<8>(A.rows, 0, row_chunks, first_rows, [&](uint32_t t, float acc) { return __builtin_fmaf(gh[t >> 16], rows[t & 0xffffu], acc); },
+                  [&](int x, float v) {
+                      const bool is_a = x < A.na;
+                      if (is_a ? !A.ga : !A.gb) return;
+                      float *dst = is_a ? A.ga + s * A.na + x : A.gb + s * A.nb + (x - A.na);
+                      *dst = (A.accumulate & (is_a ? 1 : 2)) ? *dst + v : v;
+                  });
+}
+
 // ---------------------------------------------------------------- which tables, which launch
 
 static unsigned threads_for(int64_t work, int most)
@@ -597,7 +690,11 @@ static size_t list_fwd_bytes(const dol_fn_table *f)
 
 static size_t gated_bytes(const dol_fn_table *f) { return sizeof(float) * static_cast<size_t>((f->n_out + 4) & ~3); }
 
-bool byj_fwd_sample_ok(const dol_fn_table *f) { return f->byj_fwd && sizeof(float) * static_cast<size_t>(f->na + 4) <= kStageMaxBytes; }
+// (tables that have generated code add their columns up in the defining order at every batch: the lists do, the map does not)
+bool byj_fwd_sample_ok(const dol_fn_table *f)
+{
+    return f->byj_fwd && !table_code_ok(f) && sizeof(float) * static_cast<size_t>(f->na + 4) <= kStageMaxBytes;
+}
 
 bool list_fwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && list_fwd_bytes(f) <= kStageMaxBytes; }
 
@@ -711,6 +808,32 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
     }
     DOL_HIP(hipGetLastError());
     *done = true;
+    return DOL_OK;
+}
+
+// Batches that the generated tile kernels (damp_table.hip) leave most of the chip idle with: a tile's time does not depend on
+// how many there are until each compute unit has one.  Apply + Filter + Union both ways, tiles against a workgroup per
+// sample: 64 x 64 -> 256 at B=256 20.0 against 8.0 us, 2048 20.7 / 15.5, 4096 20.9 / 23.4; 32 x 40 -> 128 at B=256 11.8 / 6.3,
+// 2048 12.0 / 8.0, 4096 12.5 / 13.2.  Only tables of which a lane walks every list: their sums are then the tiles' bit for bit.
+bool table_small_batch(const dol_fn_table *f, int64_t batch)
+{
+    return batch <= 3072 && f->lists_ok && f->col_lists.longer.n == 0 && f->row_lists.longer.n == 0;
+}
+
+dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b, const float *c,
+                               float *out, int32_t *saved, const float *g, float *ga, float *gb, float *gc, int32_t accumulate, hipStream_t st)
+{
+    SampleMerge A{};
+    A.na = f->na, A.nb = f->nb, A.S = f->n_out, A.nc = p->nb, A.n3 = p->n_out, A.accumulate = accumulate;
+    A.cols = lists_of(f->col_lists), A.rows = lists_of(f->row_lists);
+    A.ia = p->d_ia.ptr, A.ib = p->d_ib.ptr, A.ca = p->d_ca.ptr, A.cb = p->d_cb.ptr;
+    A.a = a, A.b = b, A.c = c, A.g = g, A.out = out, A.ga = ga, A.gb = gb, A.gc = gc, A.saved = saved;
+    const size_t lds = sizeof(float) * (static_cast<size_t>((f->na + f->nb + 4) & ~3) + f->n_out + p->nb + f->n_out + 1);
+    const dim3 grid(static_cast<unsigned>(batch)), block(threads_for(std::max(std::max(f->n_out, f->na + f->nb), p->n_out / 2), 512));
+    if (out && g) hipLaunchKernelGGL((damp_merge_sample_kernel<true, true>), grid, block, lds, st, A);
+    else if (out) hipLaunchKernelGGL((damp_merge_sample_kernel<true, false>), grid, block, lds, st, A);
+    else hipLaunchKernelGGL((damp_merge_sample_kernel<false, true>), grid, block, lds, st, A);
+    DOL_HIP(hipGetLastError());
     return DOL_OK;
 }
 

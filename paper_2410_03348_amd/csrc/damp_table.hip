@@ -615,7 +615,7 @@ dol_status launch_damp_table_fwd(const dol_fn_table *f, int32_t batch, const flo
                                  int64_t ldb, float *out, int64_t ldo, hipStream_t st, bool *done)
 {
     *done = false;
-    if (!table_code_ok(f) || batch < 1) return DOL_OK;
+    if (!table_code_ok(f) || batch < 1 || table_small_batch(f, batch)) return DOL_OK;
     if (lda != f->na || ldb != f->nb || ldo != f->n_out || !aligned16(a) || !aligned16(b) || !aligned16(out)) return DOL_OK;
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, kSlotFwd, build_for(batch), &fn)) return s;
@@ -632,7 +632,7 @@ dol_status launch_damp_table_bwd(const dol_fn_table *f, int32_t batch, const flo
                                  hipStream_t st, bool *done)
 {
     *done = false;
-    if (!table_code_ok(f) || batch < 1 || (ga && ga == gb)) return DOL_OK;
+    if (!table_code_ok(f) || batch < 1 || (ga && ga == gb) || table_small_batch(f, batch)) return DOL_OK;
     if (lda != f->na || ldb != f->nb || ldg != f->n_out || !aligned16(a) || !aligned16(b) || !aligned16(g) || !aligned16(ga) ||
         !aligned16(gb))
         return DOL_OK;
@@ -651,6 +651,7 @@ bool table_merge_ok(const dol_fn_table *f) { return table_code_ok(f) && f->n_out
 dol_status launch_damp_table_merge_fwd(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b,
                                        const float *c, float *out, int32_t *saved, hipStream_t st)
 {
+    if (table_small_batch(f, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, nullptr, nullptr, nullptr, nullptr, 0, st);
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeFwdAligned : kSlotMergeFwd, build_for(batch), &fn)) return s;
     const JitBuild bd = build_for(batch);
@@ -665,6 +666,7 @@ dol_status launch_damp_table_merge_bwd(const dol_fn_table *f, const UnionPlan *p
                                        const float *c, const float *g, float *ga, float *gb, float *gc, const int32_t *saved,
                                        int32_t accumulate, hipStream_t st)
 {
+    if (table_small_batch(f, batch)) return launch_sample_merge(f, p, batch, a, b, c, nullptr, const_cast<int32_t *>(saved), g, ga, gb, gc, accumulate, st);
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBwdAligned : kSlotMergeBwd, build_for(batch), &fn)) return s;
     const JitBuild bd = build_for(batch);
@@ -679,6 +681,7 @@ dol_status launch_damp_table_merge_both(const dol_fn_table *f, const UnionPlan *
                                         const float *c, float *out, int32_t *saved, const float *g, float *ga, float *gb, float *gc,
                                         int32_t accumulate, hipStream_t st)
 {
+    if (table_small_batch(f, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, g, ga, gb, gc, accumulate, st);
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBothAligned : kSlotMergeBoth, build_for(batch), &fn)) return s;
     const JitBuild bd = build_for(batch);

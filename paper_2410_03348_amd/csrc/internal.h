@@ -291,6 +291,11 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
 dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
                              const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
                              hipStream_t st, bool *done);
+// The same for tables that damp_table.hip generates code for, at batches too small for its tiles; the merged calls take
+// out == nullptr (backward only) or g == nullptr (forward only).
+bool table_small_batch(const dol_fn_table *f, int64_t batch);
+dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b, const float *c,
+                               float *out, int32_t *saved, const float *g, float *ga, float *gb, float *gc, int32_t accumulate, hipStream_t st);
 // Small arbitrary tables as code written for the table (damp_table.hip); *done = false: the call was not taken
 bool table_code_ok(const dol_fn_table *f);
 dol_status launch_damp_table_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b,

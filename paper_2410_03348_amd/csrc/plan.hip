@@ -81,7 +81,7 @@ static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, uint
         start.push_back(start.back() + most);
     }
     plan->n_words = words.size();
-    words.resize(words.size() + 4 * 64, filling);           // four words are read at a time
+    words.resize(words.size() + 8 * 64, filling);           // up to eight words are read at a time
     for (uint32_t &x : order)
         if (ptr[x + 1] - ptr[x] > static_cast<uint32_t>(kLaneList)) x |= kListElsewhere;
     while (order.size() % 64) order.push_back(kListElsewhere);

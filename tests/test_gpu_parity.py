@@ -252,6 +252,24 @@ def test_config3_apply_filter_union_in_one_launch(gp, dol, batch, na, nb, n_out,
     np.testing.assert_array_equal(host(gb), host(prog.gb))
 
 
+@pytest.mark.parametrize("batch,na,nb,n_out", [(3072, 32, 16, 64), (3073, 32, 16, 64), (7, 12, 20, 36), (3, 64, 64, 512)])
+def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, na, nb, n_out):
+    """dol_apply2_filter_union both ways, in two calls and in one, at the batch up to which a sample gets a workgroup and above
+    it (tiles of 32 samples), for the smallest and widest symbol sets: against the oracle, clamps acting in many samples."""
+    w = W.config3(batch=batch, na=na, nb=nb, n_out=n_out, seed=31)
+    for key in ("pa", "pb", "p2"):
+        w.arrays[key] = np.minimum(w[key] * np.float32(6.0), np.float32(1.0))
+    w.arrays["g"] = np.abs(w["g"])
+    ref = OP.hashed_pipeline_fwd_bwd(w)
+    for one in (False, True):
+        prog = gp.HashedPipelineMerged(w, one_launch=one)
+        prog.step()
+        np.testing.assert_array_equal(host(prog.o3.prob) == 1.0, ref["o3"] == 1.0)
+        for got, want in ((prog.o3.prob, ref["o3"]), (prog.ga, ref["ga"]), (prog.gb, ref["gb"]), (prog.gp2, ref["gp2"])):
+            assert_close(host(got), want, "merged, one launch %s" % one)
+        assert n_out == 512 or host(prog.saved).any()
+
+
 @pytest.mark.parametrize("batch,scale", [(16384, 1.0), (16421, 6.0), (12301, 6.0), (333, 12.0), (64, 1.0), (1, 1.0)])
 def test_config3_forward_and_backward_in_one_launch(gp, dol, batch, scale):
     """dol_apply2_filter_union_forward_backward: the results of the two separate calls, bit for bit (clamp words included),
