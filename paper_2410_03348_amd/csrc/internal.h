@@ -99,6 +99,20 @@ struct ListPlan {
     size_t n_words = 0;                 // words laid out for lanes, filling included
 };
 
+// Square tables that are a grid (iterate_grid.hip): column c has one tuple (i, j) for each i among c and its neighbours in a
+// grid `width` wide (c - w, c - 1, c + 1, c + w as far as they exist), and no others.
+struct GridPlan {
+    int32_t width = 0;                  // 0: not such a table
+    // second operand's symbols of node x's tuples in the slots c - w, c - 1, c, c + 1, c + w: first as a column (the operand in
+    // the slot is i), then as a row (the result in the slot is c); nb where there is none
+    DevArray<uint32_t> slots;           // [2][5][na]
+    // where the tuples of symbol j's row lie in [5][na] (slot, node i), the slot being that of c: up to four as 16-bit
+    // numbers, 5 na for none; rows of more: 5 na in all four and an entry (j, first, end) of `longer` into `pos`
+    DevArray<uint32_t> brief;           // [nb][2]
+    DevArray<uint32_t> longer, pos;
+    int32_t n_longer = 0;
+};
+
 // A tuple of the function table packed for the kernels: low 16 bits = first index, high 16 = second.
 __host__ __device__ static inline uint32_t pack16(uint32_t lo, uint32_t hi) { return lo | (hi << 16); }
 
@@ -113,6 +127,7 @@ struct dol_fn_table {
     int32_t max_col_len = 0;             // most tuples landing in one column
     int32_t max_rowa_len = 0;            // most tuples of one symbol of the first operand
     int32_t n_long_rowa = 0;               // first-operand rows among long_rows
+    dol::GridPlan grid;
     bool sum_like = false;               // every column's tuples have i ascending by 1 and j descending by 1
     bool conv_like = false;              // all na*nb tuples admitted and tuple (i, j) lands in column i + j:
                                          // the operator is a discrete convolution of the two tag rows
@@ -261,6 +276,8 @@ dol_status launch_damp_conv_bwd(const dol_fn_table *f, int32_t batch, const floa
                                 int64_t ldb, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
                                 hipStream_t st);
 // Arbitrary tables whose operand rows fit in LDS (damp_lds.hip); *done = false: the call was not taken.
+dol_status grid_plan_build(dol_fn_table *tb, const std::vector<uint32_t> &col_ptr, const std::vector<uint32_t> &col_ij,
+                           const std::vector<uint32_t> &rowb_ptr, const std::vector<uint32_t> &rowb_ic);
 dol_status lds_plan_build(dol_fn_table *tb, const std::vector<uint32_t> &col_ptr, const std::vector<uint32_t> &col_ij,
                           const std::vector<uint32_t> &rowa_ptr, const std::vector<uint32_t> &rowa_jc,
                           const std::vector<uint32_t> &rowb_ptr, const std::vector<uint32_t> &rowb_ic);

@@ -26,15 +26,13 @@
 // and is summed over the rounds in a register (or in the tuple's own LDS word); at the end the shares of every symbol
 // of e are added in ascending order of the first operand's symbol by one thread (rows of more than 64 tuples: by one
 // wavefront, strided, then a fixed exchange tree).  No atomics: the result is the same bit for bit on every run.
-#include "internal.h"
-#include "wave_util.h"
+#include "iterate.h"
 
 #include <mutex>
 
 namespace dol {
 
 constexpr int kItMaxRow = 4096;         // most symbols of either operand
-constexpr size_t kItLdsMax = 160 * 1024;
 
 // The tuples [q0, q1) of one column or row: the first N in registers (with the tag of e each names), the rest
 // behind `list`.  Register slots past the end of a short list point at the zero entry kept behind the operand
@@ -83,22 +81,6 @@ __device__ __forceinline__ float col_pre(const Cached<N> &c, const uint32_t *__r
     return acc;
 }
 
-__device__ __forceinline__ float signed_tag(float pre) { return pre <= 1.0f ? pre : -1.0f; }
-
-struct ItFwdArgs {
-    int32_t batch, na, nb, rounds;
-    const uint32_t *col_ptr, *col_ij;
-    const float *r0;
-    int64_t ldr;
-    const float *e;
-    int64_t lde;
-    float *hist;                        // [rounds + 1, batch, na] or nullptr
-    float *ckpt;                        // [n_ckpt, batch, na] or nullptr: r_every, r_2*every, ... (those before r_rounds)
-    int32_t every;
-    float *out;                         // [batch, ldo] or nullptr: r_rounds
-    int64_t ldo;
-};
-
 // ---------------------------------------------------------------- rows in LDS
 
 // Rows of tags lie T * K + 1 floats apart whatever the width of the operand: the shape's threads cover T * K symbols, so
@@ -110,25 +92,6 @@ __device__ __forceinline__ void zero_row_ends(float *rows, int n_rows, int rs, i
 {
     const int w = rs - na;
     for (int q = threadIdx.x; q < n_rows * w; q += T) rows[(q / w) * rs + na + q % w] = 0.0f;
-}
-
-// LDS addresses as 32-bit numbers: what a thread keeps in a register is the address of its element in the first row.
-typedef __attribute__((address_space(3))) float lds_float;
-
-__device__ __forceinline__ uint32_t lds_address(const float *p)
-{
-    return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((const lds_float *)p));
-}
-
-__device__ __forceinline__ float lds_at(uint32_t address) { return *reinterpret_cast<const lds_float *>(static_cast<uintptr_t>(address)); }
-
-__device__ __forceinline__ void lds_put(uint32_t address, float v) { *reinterpret_cast<lds_float *>(static_cast<uintptr_t>(address)) = v; }
-
-// (an address the compiler must take as it is: what is added to it afterwards stays a constant on the instruction)
-__device__ __forceinline__ uint32_t fixed_offset(uint32_t x)
-{
-    asm volatile("" : "+v"(x));
-    return x;
 }
 
 // `len` rounds inside LDS: row x + 1 (of `rows`, whose LDS address is rows_at) from row x, for x = 0 .. len - 1, a barrier
@@ -280,28 +243,6 @@ damp_iterate_fwd_kernel(const ItFwdArgs A)
 }
 
 // ---------------------------------------------------------------- backward
-
-struct ItBwdArgs {
-    int32_t batch, na, nb, rounds, every;   // every: rounds per segment (the checkpoint interval)
-    int32_t n_tuples, n_long;
-    int32_t shares_in_seg;                  // every tuple's share lives in a register during the sweep: the LDS words they
-                                            // are gathered through at the end take the place of the (then spent) segment
-    const uint32_t *col_ptr, *col_ij, *rowa_ptr, *rowa_jc, *rowb_ptr, *rowb_pos, *long_rows;
-    const float *e;
-    int64_t lde;
-    const float *hist;                      // full history, or nullptr: then r0 and ckpt
-    const float *r0;
-    int64_t ldr;
-    const float *ckpt;
-    const float *gout;                      // upstream gradient w.r.t. r_rounds, or
-    int64_t ldg;
-    const int32_t *target;                  // [batch]: the loss is -log r_rounds[target], read from `out`
-    const float *out;
-    int64_t ldo;
-    float *grad_r0;                         // [batch, na] or nullptr
-    float *grad_e;                          // [batch, ldge] or nullptr
-    int64_t ldge;
-};
 
 // Sum of x over the workgroup (every thread gets the total); `red` holds one float per wavefront.  Successive
 // calls must alternate between two such arrays: a wavefront may still be reading the last call's partial sums.
@@ -591,6 +532,7 @@ dol_status check_r0(const dol_dist *r0, const dol_dist *e, const dol_fn_table *f
 struct ItShape {
     int T, K, CA;
     bool tails;
+    int32_t batch;
     size_t row() const { return static_cast<size_t>(T) * K + 1; }     // floats between two rows in LDS
 };
 
@@ -598,15 +540,16 @@ static ItShape pick_shape(const dol_fn_table *f, int32_t batch, bool reverse)
 {
     const int longest = static_cast<int>(std::max(f->max_col_len, f->max_rowa_len));
     ItShape s;
-    if (f->na <= 512) s = {512, 1, 6, false};
+    if (f->na <= 512) s = {512, 1, 6, false, 0};
     // (the reverse sweep of a table of five tuples fits 64 registers with one symbol per thread: two workgroups of
     // sixteen wavefronts then fill a unit, and that is its fastest shape at any batch)
-    else if (f->na <= 1024 && (batch <= 512 || (reverse && longest <= 5))) s = {1024, 1, 6, false};
-    else if (f->na <= 1024) s = {512, 2, 6, false};
-    else if (f->na <= 2048) s = {512, 4, 3, false};
-    else s = {1024, 4, 3, false};
+    else if (f->na <= 1024 && (batch <= 512 || (reverse && longest <= 5))) s = {1024, 1, 6, false, 0};
+    else if (f->na <= 1024) s = {512, 2, 6, false, 0};
+    else if (f->na <= 2048) s = {512, 4, 3, false, 0};
+    else s = {1024, 4, 3, false, 0};
     if (s.CA == 6 && longest <= 5) s.CA = 5;
     s.tails = longest > s.CA;
+    s.batch = batch;
     return s;
 }
 
@@ -654,8 +597,13 @@ static bool shares_in_seg(const dol_fn_table *f, const ItShape &sh, int32_t ever
            static_cast<size_t>(f->n_tuples) <= (static_cast<size_t>(every) + 1) * sh.row();
 }
 
+// The reverse sweep runs in the kernels for grids: segments of `every` rounds of such a table, where they fit LDS (with
+// nodes past the grid their rows can be longer than the general kernels').
+static bool grid_sweep(const dol_fn_table *f, int32_t batch, int32_t every) { return grid_table(f) && grid_bwd_lds(f, batch, every) <= kItLdsMax; }
+
 static size_t bwd_lds(const dol_fn_table *f, const ItShape &sh, int32_t every)
 {
+    if (grid_sweep(f, sh.batch, every)) return grid_bwd_lds(f, sh.batch, every);
     const size_t shares = shares_in_seg(f, sh, every) ? 0 : static_cast<size_t>(f->n_tuples);
     return sizeof(float) * ((static_cast<size_t>(every) + 3) * sh.row() + f->nb + 1 + shares + 2 * 16);
 }
@@ -677,7 +625,7 @@ static ItBwdArgs bwd_args(const dol_dist *e, const dol_fn_table *f, const ItShap
     ItBwdArgs A{};
     A.batch = e->batch, A.na = f->na, A.nb = f->nb, A.rounds = rounds, A.every = every;
     A.n_tuples = static_cast<int32_t>(f->n_tuples), A.n_long = static_cast<int32_t>(f->long_rows.n);
-    A.shares_in_seg = shares_in_seg(f, sh, every) ? 1 : 0;
+    A.shares_in_seg = (grid_sweep(f, e->batch, every) ? grid_shares_in_seg(f, e->batch, every) : shares_in_seg(f, sh, every)) ? 1 : 0;
     A.col_ptr = f->col_ptr.ptr, A.col_ij = f->col_ij.ptr, A.rowa_ptr = f->rowa_ptr.ptr, A.rowa_jc = f->rowa_jc.ptr;
     A.rowb_ptr = f->rowb_ptr.ptr, A.rowb_pos = f->rowb_pos.ptr, A.long_rows = f->long_rows.ptr;
     A.e = e->prob, A.lde = e->ld, A.hist = hist, A.r0 = r0, A.ldr = ldr, A.ckpt = ckpt;
@@ -688,10 +636,11 @@ static ItBwdArgs bwd_args(const dol_dist *e, const dol_fn_table *f, const ItShap
 dol_status launch_iterate_fwd(const dol_dist *r0, const dol_dist *e, const dol_fn_table *f, int32_t rounds,
                                      float *hist, float *ckpt, int32_t every, float *out, int64_t ldo, hipStream_t st)
 {
+    const ItFwdArgs A = fwd_args(r0, e, f, rounds, hist, ckpt, every, out, ldo);
+    if (grid_table(f)) return launch_grid_fwd(f, A, st);
     const ItShape sh = pick_shape(f, r0->batch, false);
     const size_t lds = fwd_lds(f, sh);
     if (lds > 64 * 1024) return fail(DOL_EUNSUPPORTED, "the rows need %zu bytes of LDS, more than 65536", lds);
-    const ItFwdArgs A = fwd_args(r0, e, f, rounds, hist, ckpt, every, out, ldo);
     return launch_shape<FwdKernels>(sh, r0->batch, lds, st, A);
 }
 
@@ -707,6 +656,7 @@ static dol_status launch_reverse(const dol_dist *e, const dol_fn_table *f, int32
         return fail(DOL_EUNSUPPORTED, "segments of %d rounds need %zu bytes of LDS, more than %zu", every, lds, kItLdsMax);
     ItBwdArgs A = bwd_args(e, f, sh, rounds, hist, r0, ldr, ckpt, every, grad_out, ldg, grad_r0, grad_e);
     A.target = target, A.out = out, A.ldo = ldo;
+    if (grid_sweep(f, e->batch, every)) return launch_grid_bwd(f, A, lds, st);
     return launch_shape<BwdKernels>(sh, e->batch, lds, st, A);
 }
 
@@ -721,6 +671,8 @@ dol_status launch_iterate_bwd(const dol_dist *e, const dol_fn_table *f, int32_t 
 // the tables are fetched once, the last segment is not replayed); a larger batch in two launches back to back, each in
 // the shape and with the LDS of its own sweep: the forward sweep then runs four workgroups to a unit instead of the
 // reverse sweep's two, which is worth more than the replayed segment (B = 8192, 32 x 32 grid: 0.26 + 0.77 ms against 1.09).
+// The kernels for grids need little LDS in either sweep: one launch at any batch (B = 1024: 16 x 16 29 us against 37,
+// 32 x 32 82 against 91).
 constexpr int32_t kOneLaunchBatch = 512;
 
 static dol_status launch_iterate_fwd_bwd(const dol_dist *r0, const dol_dist *e, const dol_fn_table *f, int32_t rounds, int32_t every,
@@ -728,7 +680,7 @@ static dol_status launch_iterate_fwd_bwd(const dol_dist *r0, const dol_dist *e, 
                                          int64_t ldg, float *grad_r0, float *grad_e, hipStream_t st)
 {
     if (!f->rowb_pos.ptr && f->n_tuples > 0) return fail(DOL_EINVAL, "the table lacks the row cross-index of square tables");
-    if (e->batch > kOneLaunchBatch) {
+    if (e->batch > kOneLaunchBatch && !grid_sweep(f, e->batch, every)) {
         if (dol_status s = launch_iterate_fwd(r0, e, f, rounds, nullptr, ckpt, every, out, ldo, st)) return s;
         return launch_reverse(e, f, rounds, nullptr, r0->prob, r0->ld, ckpt, every, target, out, ldo, grad_out, ldg, grad_r0, grad_e, st);
     }
@@ -739,6 +691,7 @@ static dol_status launch_iterate_fwd_bwd(const dol_dist *r0, const dol_dist *e, 
     const ItFwdArgs F = fwd_args(r0, e, f, rounds, nullptr, ckpt, every, out, ldo);
     ItBwdArgs B = bwd_args(e, f, sh, rounds, nullptr, r0->prob, r0->ld, ckpt, every, grad_out, ldg, grad_r0, grad_e);
     B.target = target, B.out = out, B.ldo = ldo;
+    if (grid_sweep(f, e->batch, every)) return launch_grid_fwd_bwd(f, F, B, lds, st);
     return launch_shape<FwdBwdKernels>(sh, e->batch, lds, st, F, B);
 }
 
@@ -784,9 +737,13 @@ int32_t dol_iterate_ckpt_every(const dol_fn_table *f, int32_t batch, int32_t rou
     if (!f || rounds <= 1 || f->na <= 0) return 1;
     const ItShape sh = pick_shape(f, batch, true);
     // a batch that leaves units idle: one workgroup has a unit's LDS to itself; else as many workgroups as fill a
-    // unit's 32 wavefronts share it
-    const size_t sharers = batch <= kOneLaunchBatch ? 1 : std::max(1, 32 / (sh.T / kWave));
-    const size_t budget = batch <= kOneLaunchBatch ? kItLdsMax - 4096 : kItLdsMax / sharers - 1024;
+    // unit's 32 wavefronts share it (grids: as many as the batch has per unit, of sixteen wavefronts and eight workgroups in
+    // all: with more, segments get so short that the checkpoints' traffic bounds the sweeps - B = 8192, 32 x 32 grid,
+    // 64 rounds: 0.56 ms with four workgroups, 0.62 with three, 1.24 with six)
+    const bool grid = grid_sweep(f, batch, 1);
+    size_t sharers = batch <= kOneLaunchBatch ? 1 : std::max(1, 32 / (sh.T / kWave));
+    if (grid) sharers = std::min((std::max(batch, 1) + 255) / 256, std::min(8, std::max(1, 16 / grid_waves(f, batch))));
+    const size_t budget = sharers == 1 ? kItLdsMax - 4096 : kItLdsMax / sharers - 1024;
     for (int32_t n_seg = 1; n_seg <= rounds; ++n_seg) {
         const int32_t every = (rounds + n_seg - 1) / n_seg;
         if (bwd_lds(f, sh, every) <= budget) return every;

@@ -227,6 +227,7 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
         (e = tb->rowb_ptr.upload(rowb_ptr)) != hipSuccess || (e = tb->rowb_ic.upload(rowb_ic)) != hipSuccess ||
         (e = tb->rowb_pos.upload(rowb_pos)) != hipSuccess)
         return hip_fail(e, "uploading the function table");
+    if (dol_status s2 = grid_plan_build(tb.get(), col_ptr, col_ij, rowb_ptr, rowb_ic)) return s2;
     if (!conv_path_ok(tb.get()))
         if (dol_status s2 = lds_plan_build(tb.get(), col_ptr, col_ij, rowa_ptr, rowa_jc, rowb_ptr, rowb_ic)) return s2;
     if (!conv_path_ok(tb.get()) && na >= 1 && nb >= 1 && S >= 1 && na + nb < 0xFFFF && S < 0xFFFF) {

@@ -433,16 +433,16 @@ class GridReachFused(Program):
             fwd = lambda: dol.iterate_apply2(self.r0, self.edges, self.table, R, self.hist)
             bwd = lambda: dol.iterate_backward(self.edges, self.table, R, self.hist, self.g_out, None, self.g_e)
         self.launches = [
-            Launch("damp_iterate_fwd_kernel", fwd, 4 * B * (n + E + 1 + n), B * R * n_tup, "fwd"),     # r_0 and e in, r_R out
-            Launch("damp_iterate_bwd_kernel", bwd, 4 * B * (n + 2 * (E + 1)), 2 * B * R * n_tup, "bwd"),  # gradient and e in, gradient of e out
+            Launch("damp_iterate_grid_fwd_kernel", fwd, 4 * B * (n + E + 1 + n), B * R * n_tup, "fwd"),     # r_0 and e in, r_R out
+            Launch("damp_iterate_grid_bwd_kernel", bwd, 4 * B * (n + 2 * (E + 1)), 2 * B * R * n_tup, "bwd"),  # gradient and e in, gradient of e out
         ]                                    # (what the sweeps keep of the rounds in between is not algorithmic)
-        # dol_iterate_apply2_backward: both sweeps in one launch.  (For a batch above 512 that call issues the same two
-        # kernels as the two calls above, back to back: the program then keeps the two calls, so each is timed by itself.)
+        # dol_iterate_apply2_backward: both sweeps in one launch.  (For a batch above 512 the program keeps the two calls,
+        # so each is timed by itself.)
         if one_launch and B <= 512:
             assert ckpt_every, "the one-launch form keeps checkpoints"
             both = lambda: dol.iterate_apply2_backward(self.r0, self.edges, self.table, R, ckpt_every, self.out, self.ckpt,
                                                        None, self.g_out, None, self.g_e)
-            self.launches = [Launch("damp_iterate_fwd_bwd_kernel", both, 4 * B * (3 * n + 3 * (E + 1)), 3 * B * R * n_tup, "fwd+bwd")]
+            self.launches = [Launch("damp_iterate_grid_fwd_bwd_kernel", both, 4 * B * (3 * n + 3 * (E + 1)), 3 * B * R * n_tup, "fwd+bwd")]
         self.sample_ops = 2 * R * B
         self.min_bytes = 4 * B * (2 * E + 2 * n)
         self.flops = 2 * 3 * B * R * n_tup

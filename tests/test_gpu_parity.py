@@ -739,6 +739,61 @@ def test_fused_iteration_with_six_tuples_per_symbol(dol, B, na):
         np.testing.assert_array_equal(host(a), host(b))
 
 
+@pytest.mark.parametrize("B,w,h", [(3, 2, 2), (3, 64, 2), (2, 33, 31), (5, 5, 40), (2, 2, 512), (300, 7, 9), (800, 22, 22), (600, 32, 3),
+                                   (1030, 9, 17), (2, 64, 32), (2, 65, 3)])
+def test_fused_iteration_over_a_grid(dol, B, w, h):
+    """Tables of a full w x h grid with a "stay" tuple per node: strips of one, two and four nodes, bands that fill a wavefront
+    and bands that do not, last strips of one node, samples beside each other on a unit; symbols of e with one tuple, a few,
+    more than four and more than a wavefront."""
+    na, rounds, every = w * h, 9, 4
+    x, y = np.arange(na) % w, np.arange(na) // w
+    ti, tj, to, nb = [np.arange(na)], [np.zeros(na, np.int64)], [np.arange(na)], 1
+    for dx, dy, share in ((1, 0, na), (-1, 0, 7), (0, 1, 3), (0, -1, 1)):       # so many nodes share a symbol of e
+        ok = (x + dx >= 0) & (x + dx < w) & (y + dy >= 0) & (y + dy < h)
+        ti.append(np.arange(na)[ok])
+        to.append(np.arange(na)[ok] + dx + w * dy)
+        tj.append(nb + (np.arange(na)[ok] * 5) // share % (na // share + 1))
+        nb = int(tj[-1].max()) + 2
+    ti, tj, to = (np.concatenate(v) for v in (ti, tj, to))
+    order = np.lexsort((tj, ti))
+    tri = tuple(np.asarray(v, np.int32)[order] for v in (ti, tj, to))
+    r0 = (W.uniform01(1, B * na) * 0.9).astype(np.float32).reshape(B, na)
+    r0[:, 1] = 1.0
+    e = (W.uniform01(2, B * nb) * 0.45).astype(np.float32).reshape(B, nb)
+    n_ref = min(B, 4)
+    hist = [r0[-n_ref:]]
+    for t in range(rounds):
+        hist.append(oracle.damp_apply2_fwd(tri, na, nb, hist[-1], e[-n_ref:])[1])
+    g = np.abs(W.normal(3, B * na)).astype(np.float32).reshape(B, na)
+    want_ge, gr = np.zeros((n_ref, nb), np.float64), g[-n_ref:]
+    for t in reversed(range(rounds)):
+        gr, ge = oracle.damp_apply2_bwd(tri, na, nb, hist[t], e[-n_ref:], gr)
+        want_ge += ge
+    f = dol.FnTable.create_sparse(na, nb, *tri)
+    d0, de = dol.Dist(np.arange(na), dev(r0)), dol.Dist(np.arange(nb), dev(e))
+    dh = torch.empty((rounds + 1, B, na), device="cuda")
+    dol.iterate_apply2(d0, de, f, rounds, dh)
+    step = dol.Dist(np.arange(na), dev(r0))
+    for t in range(rounds):                            # the rounds are those of as many calls, bit for bit
+        nxt = dol.Dist.empty(np.arange(na), B)
+        dol.apply2(step, de, f, None, nxt)
+        torch.testing.assert_close(dh[t + 1], nxt.prob, rtol=0, atol=0)
+        step = nxt
+    g0, ge = torch.empty((B, na), device="cuda"), torch.empty((B, nb), device="cuda")
+    dol.iterate_backward(de, f, rounds, dh, dev(g), g0, ge)
+    assert_close(host(g0)[-n_ref:], gr, "grid: gradient of r0")
+    assert_close(host(ge)[-n_ref:], want_ge, "grid: gradient of e")
+    n_ck = dol.iterate_ckpt_count(rounds, every)
+    out, ck = dol.Dist.empty(np.arange(na), B), torch.empty((n_ck, B, na), device="cuda")
+    g0b, geb = torch.empty_like(g0), torch.empty_like(ge)
+    dol.iterate_apply2_ckpt(d0, de, f, rounds, every, out, ck)
+    dol.iterate_backward_ckpt(d0, de, f, rounds, every, ck, dev(g), g0b, geb)
+    out2, ck2, g0c, gec = dol.Dist.empty(np.arange(na), B), torch.empty_like(ck), torch.empty_like(g0), torch.empty_like(ge)
+    dol.iterate_apply2_backward(d0, de, f, rounds, every, out2, ck2, None, dev(g), g0c, gec)
+    for a, b in ((out.prob, dh[-1]), (ck[0], dh[every]), (g0b, g0), (geb, ge), (out2.prob, out.prob), (ck2, ck), (g0c, g0), (gec, ge)):
+        torch.testing.assert_close(a, b, rtol=0, atol=0)
+
+
 def test_fused_iteration_with_more_than_1024_symbols(dol):
     """Four symbols of the first operand per thread (the widest build of the fused sweeps)."""
     na, nb, B, rounds = 1100, 40, 3, 4
