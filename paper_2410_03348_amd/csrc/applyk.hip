@@ -6,7 +6,7 @@
 // operand row lists the tuples it takes part in.  One thread owns one (sample, output symbol) in the forward kernels
 // and one (sample, operand symbol) in the backward kernel; lanes run along a row, so stores are coalesced and the
 // gathers of neighbouring lanes fall into the same few cache lines of the sample's tag rows.
-#include "dtkp_util.h"
+#include "dtkp_columns.h"
 #include "element_map.h"
 #include "internal.h"
 #include "wave_util.h"
@@ -30,8 +30,12 @@ struct dol_fnk_table {
     dol::DevArray<uint32_t> row_ptr;     // [sum n_sym + 1]
     dol::DevArray<uint32_t> row_tup;     // [n_tuples*K] grouped-tuple numbers of each operand row, ascending
     dol::DevArray<uint32_t> long_cols;   // columns with more than dol::kLongTableCol tuples
-    dol::DevArray<uint32_t> dtkp_long_cols;   // ... more than dol::kLongDtkpCol: first those above dol::kWaveDtkpCol
-    int32_t n_wave_dtkp_cols = 0;             // (one wavefront each), then the shorter ones (four to a wavefront)
+    // ... more than dol::kLongDtkpCol: first those above dol::kHugeDtkpCol (a workgroup each), then those above
+    // dol::kWaveDtkpCol (a wavefront each), then the shorter ones (16 lanes each)
+    dol::DevArray<uint32_t> dtkp_long_cols;
+    int32_t n_huge_dtkp_cols = 0, n_wave_dtkp_cols = 0;
+    dol::DevArray<uint32_t> dtkp_order, dtkp_len;   // the others (by length; length 0: a longer one)
+    dol::DevArray<uint16_t> dtkp_tuples;            // ... of a unary function: symbol k of the r-th column at [k * n_out + r]
     dol::DevArray<uint32_t> col_order;   // all columns in the order of dol::columns_by_length (limit: kLongDtkpCol)
     // unary functions (K = 1): the first eight symbols of every image again, 16 bytes per column (0xFFFF = none), and
     // the column of every symbol (-1: rejected)
@@ -384,8 +388,6 @@ static void launch_bwd_k(const Rows &R, const KOperands &in, const KGrads &gin, 
 
 // ---------------------------------------------------------------- DTKP-AM
 
-constexpr int kThreadsP = 128;
-
 // Offers the proofs of one tuple's tag to the list: the binary conjunction of Table 1 folded over the operands left
 // to right, each intermediate pruned to k proofs.
 template <int KP>
@@ -429,101 +431,75 @@ __device__ __forceinline__ void offer_tuple_k(TopK<KP> &top, const uint16_t *__r
         if (cur.m[x] != kAbsent) top.insert(cur.m[x], cur.p[x]);
 }
 
-// One thread per (sample, output symbol): the proofs of the column's tuples meet in one k-entry list.
-template <int KP>
-__global__ void __launch_bounds__(kThreadsP)
-dtkp_applyk_kernel(int64_t total, int32_t S, int32_t arity, KProofs in, const uint32_t *__restrict__ order,
-                   const uint32_t *__restrict__ col_ptr,
-                   const uint16_t *__restrict__ tup, GroupMasks gm, int32_t n_facts, const float *__restrict__ fact_prob,
-                   uint64_t *__restrict__ om, float *__restrict__ op, float *__restrict__ oprob, int64_t ldo)
-{
-    // (each XCD takes a contiguous range of samples: a sample's operand lists then fill one L2 and not all eight)
-    const int64_t idx = static_cast<int64_t>(xcd_contiguous(blockIdx.x, gridDim.x)) * kThreadsP + threadIdx.x;
-    if (idx >= total) return;
-    const int64_t s = idx / S;
-    const int32_t r = static_cast<int32_t>(idx - s * S);
-    // lanes of a wavefront: columns of like length (not for a unary function under DTKP-AM, whose lists are one
-    // gather each: there the neighbouring columns' neighbouring symbols matter more)
-    const int32_t c = order ? static_cast<int32_t>(order[r]) : r;
-    const float *fp = fact_prob + s * n_facts;
-    const uint32_t q0 = col_ptr[c], q1 = col_ptr[c + 1];
-    if (q1 - q0 > static_cast<uint32_t>(kLongDtkpCol)) return;             // left to the wavefront-per-column kernel
-    TopK<KP> top;
-    top.clear();
-    for (uint32_t q = q0; q < q1; ++q) {
-        offer_tuple_k<KP>(top, tup + static_cast<size_t>(q) * arity, s, arity, in, gm, fp);
-    }
-    const int64_t o = s * S + c;
-    oprob[s * ldo + c] = top.store(om + o * KP, op + o * KP);
-}
+struct TupleArgs {
+    int32_t S, arity, n_facts;
+    const uint32_t *col_ptr;
+    const uint16_t *tup;
+    const uint16_t *ord_tuples;         // unary functions: symbol k of the r-th short column at [k * S + r]
+    const float *fact_prob;
+    KProofs in;
+};
 
-// One wavefront per (sample, long column): every lane streams a share of the tuples through a list of its own; the
-// lists meet by exchange rounds (the list order is total on distinct proofs, so the split does not matter).
 template <int KP>
-__global__ void __launch_bounds__(kWave)
-dtkp_applyk_long_kernel(int32_t n_long, const uint32_t *__restrict__ long_cols, int32_t S, int32_t arity, KProofs in,
-                        const uint32_t *__restrict__ col_ptr, const uint16_t *__restrict__ tup, GroupMasks gm,
-                        int32_t n_facts, const float *__restrict__ fact_prob, uint64_t *__restrict__ om,
-                        float *__restrict__ op, float *__restrict__ oprob, int64_t ldo)
-{
-    const int64_t wg = xcd_contiguous(blockIdx.x, gridDim.x);       // a sample's columns on one XCD: its lists fill one L2
-    const int64_t s = wg / n_long;
-    const uint32_t c = long_cols[wg - s * n_long];
-    const float *fp = fact_prob + s * n_facts;
-    TopK<KP> top;
-    top.clear();
-    for (uint32_t q = col_ptr[c] + threadIdx.x, q1 = col_ptr[c + 1]; q < q1; q += kWave)
-        offer_tuple_k<KP>(top, tup + static_cast<size_t>(q) * arity, s, arity, in, gm, fp);
-    merge_lists<KP>(top);
-    if (threadIdx.x == 0) {
-        const int64_t idx = s * S + c;
-        oprob[s * ldo + c] = top.store(om + idx * KP, op + idx * KP);
-    }
-}
+struct TupleOffer {
+    static constexpr int kAhead = KP <= 3 ? 4 : 2;
+    const TupleArgs &A;
+    const GroupMasks &gm;
+    const float *fp;
+    int64_t s;
 
-// Columns of a few dozen tuples: four to a wavefront, 16 lanes each.
-template <int KP>
-__global__ void __launch_bounds__(kWave)
-dtkp_applyk_mid_kernel(int32_t n_mid, const uint32_t *__restrict__ cols, int32_t S, int32_t arity, KProofs in,
-                       const uint32_t *__restrict__ col_ptr, const uint16_t *__restrict__ tup, GroupMasks gm,
-                       int32_t n_facts, const float *__restrict__ fact_prob, uint64_t *__restrict__ om,
-                       float *__restrict__ op, float *__restrict__ oprob, int64_t ldo)
-{
-    const int32_t quads = (n_mid + 3) / 4;
-    const int64_t wg = xcd_contiguous(blockIdx.x, gridDim.x);       // a sample's columns on one XCD: its lists fill one L2
-    const int64_t s = wg / quads;
-    const int32_t ci = static_cast<int32_t>(wg - s * quads) * 4 + static_cast<int32_t>(threadIdx.x / 16);
-    if (ci >= n_mid) return;                        // a whole group of 16 lanes at once
-    const uint32_t c = cols[ci];
-    const float *fp = fact_prob + s * n_facts;
-    TopK<KP> top;
-    top.clear();
-    for (uint32_t q = col_ptr[c] + (threadIdx.x & 15), q1 = col_ptr[c + 1]; q < q1; q += 16)
-        offer_tuple_k<KP>(top, tup + static_cast<size_t>(q) * arity, s, arity, in, gm, fp);
-    merge_lists<KP, 16>(top);
-    if ((threadIdx.x & 15) == 0) {
-        const int64_t idx = s * S + c;
-        oprob[s * ldo + c] = top.store(om + idx * KP, op + idx * KP);
+    __device__ __forceinline__ void begin(int64_t sample) { s = sample, fp = A.fact_prob + sample * A.n_facts; }
+    // a unary function's symbols are one list each: several on their way at a time
+    template <class Symbol>
+    __device__ __forceinline__ void unary(TopK<KP> &top, uint32_t q, uint32_t q1, uint32_t step, Symbol symbol) const
+    {
+        for (; q < q1; q += step * kAhead) {
+            uint64_t m[kAhead][KP];
+            float p[kAhead][KP];
+            uint32_t i[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) i[u] = symbol(q + u * step < q1 ? q + u * step : q);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (u > 0 && q + u * step >= q1) continue;
+                const int64_t o = (s * A.in.n[0] + i[u]) * KP;
+                load_masks<KP>(A.in.m[0] + o, m[u]);
+                if (A.in.p[0]) load_probs<KP>(A.in.p[0] + o, p[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (u > 0 && q + u * step >= q1) continue;
+#pragma unroll
+                for (int x = 0; x < KP; ++x)
+                    if (m[u][x] != kAbsent) top.insert(m[u][x], A.in.p[0] ? p[u][x] : proof_prob(m[u][x], fp));
+            }
+        }
     }
+    __device__ __forceinline__ void listed(TopK<KP> &top, uint32_t q, uint32_t q1, uint32_t step) const
+    {
+        if (A.arity == 1) unary(top, q, q1, step, [&](uint32_t x) { return A.tup[x]; });
+        else
+            for (; q < q1; q += step) offer_tuple_k<KP>(top, A.tup + static_cast<size_t>(q) * A.arity, s, A.arity, A.in, gm, fp);
+    }
+    __device__ __forceinline__ void laned(TopK<KP> &top, uint32_t len, int32_t r, uint32_t c) const
+    {
+        if (A.arity == 1) unary(top, 0, len, 1, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; });
+        else if (len > 0) listed(top, A.col_ptr[c], A.col_ptr[c] + len, 1);
+    }
+};
+
+template <int KP>
+__global__ void __launch_bounds__(kHugeThreads)
+dtkp_applyk_kernel(ColumnArgs C, TupleArgs A, GroupMasks gm)
+{
+    dtkp_columns<KP>(C, TupleOffer<KP>{A, gm, nullptr, 0});
 }
 
 template <int KP>
-static void launch_dtkp_k(int64_t total, const dol_fnk_table *f, const KProofs &in, const GroupMasks &gm, int32_t n_facts,
-                          const float *fact_prob, uint64_t *om, float *op, float *oprob, int64_t ldo, hipStream_t st)
+static void launch_dtkp_k(ColumnArgs C, const TupleArgs &A, const GroupMasks &gm, hipStream_t st)
 {
-    hipLaunchKernelGGL(dtkp_applyk_kernel<KP>, dim3(static_cast<unsigned>((total + kThreadsP - 1) / kThreadsP)),
-                       dim3(kThreadsP), 0, st, total, f->n_out, f->K, in, f->K >= 2 ? f->col_order.ptr : nullptr, f->col_ptr.ptr, f->tup.ptr, gm,
-                       n_facts, fact_prob, om, op, oprob, ldo);
-    const int64_t n_wave = f->n_wave_dtkp_cols, n_mid = static_cast<int64_t>(f->dtkp_long_cols.n) - n_wave;
-    const int64_t batch = total / f->n_out;
-    if (n_wave > 0)
-        hipLaunchKernelGGL(dtkp_applyk_long_kernel<KP>, dim3(static_cast<unsigned>(batch * n_wave)), dim3(kWave), 0, st,
-                           static_cast<int32_t>(n_wave), f->dtkp_long_cols.ptr, f->n_out, f->K, in, f->col_ptr.ptr, f->tup.ptr,
-                           gm, n_facts, fact_prob, om, op, oprob, ldo);
-    if (n_mid > 0)
-        hipLaunchKernelGGL(dtkp_applyk_mid_kernel<KP>, dim3(static_cast<unsigned>(batch * ((n_mid + 3) / 4))), dim3(kWave), 0, st,
-                           static_cast<int32_t>(n_mid), f->dtkp_long_cols.ptr + n_wave, f->n_out, f->K, in, f->col_ptr.ptr,
-                           f->tup.ptr, gm, n_facts, fact_prob, om, op, oprob, ldo);
+    const unsigned grid = column_launch(C);
+    hipLaunchKernelGGL(dtkp_applyk_kernel<KP>, dim3(grid), dim3(column_threads(C)), 0, st, C, A, gm);
 }
 
 // ---------------------------------------------------------------- plan
@@ -594,17 +570,38 @@ static dol_status build_k(int32_t K, const int32_t *n_sym, int64_t n, const int3
             for (int l = 0; l < K; ++l) row_tup[fill[tb->row_base[l] + tup[t * K + l]]++] = static_cast<uint32_t>(t);
     }
 
-    std::vector<uint32_t> long_cols, dtkp_long_cols, dtkp_mid_cols;
+    std::vector<uint32_t> long_cols, dtkp_long_cols, dtkp_wave_cols, dtkp_mid_cols;
     for (int32_t c = 0; c < S; ++c) {
         const uint32_t len = col_ptr[c + 1] - col_ptr[c];
         if (len > static_cast<uint32_t>(kLongTableCol)) long_cols.push_back(static_cast<uint32_t>(c));
-        if (len > static_cast<uint32_t>(kWaveDtkpCol)) dtkp_long_cols.push_back(static_cast<uint32_t>(c));
+        if (len > static_cast<uint32_t>(kHugeDtkpCol)) dtkp_long_cols.push_back(static_cast<uint32_t>(c));
+        else if (len > static_cast<uint32_t>(kWaveDtkpCol)) dtkp_wave_cols.push_back(static_cast<uint32_t>(c));
         else if (len > static_cast<uint32_t>(kLongDtkpCol)) dtkp_mid_cols.push_back(static_cast<uint32_t>(c));
     }
-    tb->n_wave_dtkp_cols = static_cast<int32_t>(dtkp_long_cols.size());
+    tb->n_huge_dtkp_cols = static_cast<int32_t>(dtkp_long_cols.size());
+    tb->n_wave_dtkp_cols = static_cast<int32_t>(dtkp_wave_cols.size());
+    dtkp_long_cols.insert(dtkp_long_cols.end(), dtkp_wave_cols.begin(), dtkp_wave_cols.end());
     dtkp_long_cols.insert(dtkp_long_cols.end(), dtkp_mid_cols.begin(), dtkp_mid_cols.end());
 
     const std::vector<uint32_t> col_order = columns_by_length(col_ptr, S, kLongDtkpCol);
+    // (not for a unary function, whose lists are one gather each: there the neighbouring columns' neighbouring symbols matter
+    // more)
+    std::vector<uint32_t> dtkp_order = col_order;
+    if (K == 1) std::iota(dtkp_order.begin(), dtkp_order.end(), 0u);
+    std::vector<uint32_t> dtkp_len(static_cast<size_t>(S), 0);
+    for (int32_t r = 0; r < S; ++r) {
+        const uint32_t len = col_ptr[dtkp_order[r] + 1] - col_ptr[dtkp_order[r]];
+        if (len <= static_cast<uint32_t>(kLongDtkpCol)) dtkp_len[r] = len;
+    }
+    DOL_HIP(tb->dtkp_order.upload(dtkp_order));
+    DOL_HIP(tb->dtkp_len.upload(dtkp_len));
+    if (K == 1) {
+        const uint32_t longest = S ? *std::max_element(dtkp_len.begin(), dtkp_len.end()) : 0;
+        std::vector<uint16_t> tuples(static_cast<size_t>(longest) * S, 0);
+        for (int32_t r = 0; r < S; ++r)
+            for (uint32_t k = 0; k < dtkp_len[r]; ++k) tuples[static_cast<size_t>(k) * S + r] = tup[col_ptr[dtkp_order[r]] + k];
+        DOL_HIP(tb->dtkp_tuples.upload(tuples));
+    }
     if (K == 1) {
         std::vector<uint16_t> head(static_cast<size_t>(S) * 8, 0xFFFFu);
         std::vector<int32_t> col_of(static_cast<size_t>(n_sym[0]), -1);
@@ -719,9 +716,15 @@ dol_status dol_apply_k(int32_t K, const dol_dist *const *in, const dol_fnk_table
     if (dol_status s2 = make_group_masks(prov, &gm)) return s2;
     KProofs pr{};
     for (int l = 0; l < K; ++l) { pr.m[l] = in[l]->proof_mask; pr.p[l] = in[l]->proof_prob; pr.n[l] = in[l]->n_sym; }
-    const int64_t total = static_cast<int64_t>(batch) * f->n_out;
+    ColumnArgs C{};
+    C.batch = batch, C.S = f->n_out;
+    C.n_huge = f->n_huge_dtkp_cols, C.n_wave = f->n_wave_dtkp_cols;
+    C.n_mid = static_cast<int32_t>(f->dtkp_long_cols.n) - C.n_huge - C.n_wave;
+    C.longer = f->dtkp_long_cols.ptr, C.col_ptr = f->col_ptr.ptr, C.order = f->dtkp_order.ptr, C.len = f->dtkp_len.ptr;
+    C.om = out->proof_mask, C.op = out->proof_prob, C.oprob = out->prob, C.ldo = out->ld;
+    const TupleArgs A{f->n_out, f->K, prov->n_facts, f->col_ptr.ptr, f->tup.ptr, f->dtkp_tuples.ptr, prov->fact_prob, pr};
     switch (prov->k) {
-#define CASE(KP) case KP: launch_dtkp_k<KP>(total, f, pr, gm, prov->n_facts, prov->fact_prob, out->proof_mask, out->proof_prob, out->prob, out->ld, st); break;
+#define CASE(KP) case KP: launch_dtkp_k<KP>(C, A, gm, st); break;
         CASE(1) CASE(2) CASE(3) CASE(4) CASE(5) CASE(6) CASE(7) CASE(8)
 #undef CASE
     default: return fail(DOL_EINVAL, "k = %d outside 1..%d", prov->k, DOL_MAX_K);

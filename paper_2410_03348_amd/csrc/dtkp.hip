@@ -7,8 +7,7 @@
 // list held in registers.  Repeated proofs are one proof, so insertion first looks the mask up; the list
 // order (higher probability first, ties by smaller mask) is total on distinct masks, which makes the
 // result independent of the order candidates arrive in.
-#include "dtkp_util.h"
-#include "wave_util.h"
+#include "dtkp_columns.h"
 
 #include <algorithm>
 
@@ -51,184 +50,108 @@ dol_status launch_dtkp_init(int32_t batch, int32_t n_sym, int32_t k, int32_t n_f
 
 // ---------------------------------------------------------------- apply2
 
-// Offers every consistent union of a proof of a's symbol with a proof of b's symbol (tuple ij) to the list.
+struct PairArgs {
+    int32_t S, na, nb, n_facts;
+    const uint32_t *col_ij, *ord_tuples;
+    const float *fact_prob;
+    const uint64_t *am, *bm;
+    const float *ap, *bp;
+    // the second operand is an input Distribution under natural initialisation: its symbol is one fact, its tag the single
+    // proof {that fact} (App. A.1); nothing of it is stored.  fact_b holds four words per symbol: the fact and the mask of
+    // the other facts of its exclusion group (low, high word).
+    const int32_t *fact_b;
+};
+
+// Offers every consistent union of a proof of a's symbol with a proof of b's symbol, tuple by tuple.
 template <int K>
-__device__ __forceinline__ void offer_tuple(TopK<K> &top, uint32_t ij, int64_t a0, int64_t b0, const GroupMasks &gm,
-                                            const float *__restrict__ fp, const uint64_t *__restrict__ am,
-                                            const float *__restrict__ ap, const uint64_t *__restrict__ bm,
-                                            const float *__restrict__ bp, const int32_t *__restrict__ fact_b)
-{
-    const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K, ib = b0 + static_cast<int64_t>(ij >> 16) * K;
-    uint64_t ma[K], mb[K];
-    float pa[K], pb[K];
-    if (fact_b) {
-        // the second operand is an input Distribution under natural initialisation: its symbol is one fact, its
-        // tag the single proof {that fact} (App. A.1); nothing of it is stored.  fact_b holds four words per symbol:
-        // the fact and the mask of the other facts of its exclusion group (low, high word).  The first operand's
-        // proofs hold at most one fact per exclusion group, so the union is inconsistent exactly when such a proof
-        // holds a rival of the one fact the second operand brings.  The product over ascending facts is unchanged
-        // when the fact is already there, takes one more factor when it lies above every fact of the proof
-        // (ma < bit as integers), and is redone from scratch otherwise.
-        const uint4 fr = reinterpret_cast<const uint4 *>(fact_b)[ij >> 16];
-        const int fb = static_cast<int>(fr.x);
-        const uint64_t bit = uint64_t(1) << fb, rival = (static_cast<uint64_t>(fr.z) << 32) | fr.y;
-        const float pbit = 1.0f * fp[fb];
-        load_masks<K>(am + ia, ma);
-        if (ap) load_probs<K>(ap + ia, pa);
+struct PairOffer {
+    const PairArgs &A;
+    const GroupMasks &gm;
+    const float *fp;
+    int64_t a0, b0;
+
+    __device__ __forceinline__ void begin(int64_t s)
+    {
+        fp = A.fact_prob + s * A.n_facts;
+        a0 = s * A.na * K, b0 = s * A.nb * K;
+    }
+    // The first operand's proofs hold at most one fact per exclusion group, so the union is inconsistent exactly when such a
+    // proof holds a rival of the one fact the second operand brings.  The product over ascending facts is unchanged when the
+    // fact is already there, takes one more factor when it lies above every fact of the proof (ma < bit as integers), and
+    // is redone from scratch otherwise.
+    __device__ __forceinline__ void with_fact(TopK<K> &top, const uint4 &f, const uint64_t (&ma)[K], const float (&pa)[K]) const
+    {
+        const uint64_t bit = uint64_t(1) << f.x, rival = (static_cast<uint64_t>(f.z) << 32) | f.y;
+        const float pbit = 1.0f * fp[f.x];
 #pragma unroll
         for (int x = 0; x < K; ++x) {
             if (ma[x] == kAbsent || (ma[x] & rival)) continue;
             const bool held = (ma[x] & bit) != 0;
-            const float pr = ap && (held || ma[x] < bit) ? (held ? pa[x] : pa[x] * pbit) : proof_prob(ma[x] | bit, fp);
+            const float pr = A.ap && (held || ma[x] < bit) ? (held ? pa[x] : pa[x] * pbit) : proof_prob(ma[x] | bit, fp);
             top.insert(ma[x] | bit, pr);
         }
-        return;
     }
-    load_masks<K>(am + ia, ma);
-    load_masks<K>(bm + ib, mb);
+    __device__ __forceinline__ void with_list(TopK<K> &top, uint32_t j, const uint64_t (&ma)[K], const float (&pa)[K]) const
+    {
+        const int64_t ib = b0 + static_cast<int64_t>(j) * K;
+        uint64_t mb[K];
+        float pb[K];
+        load_masks<K>(A.bm + ib, mb);
 #pragma unroll
-    for (int x = 0; x < K; ++x) pa[x] = pb[x] = -1.0f;
-    if (ap) load_probs<K>(ap + ia, pa);
-    if (bp) load_probs<K>(bp + ib, pb);
+        for (int x = 0; x < K; ++x) pb[x] = -1.0f;
+        if (A.bp) load_probs<K>(A.bp + ib, pb);
 #pragma unroll
-    for (int x = 0; x < K; ++x) {
-        if (ma[x] == kAbsent) continue;
+        for (int x = 0; x < K; ++x) {
+            if (ma[x] == kAbsent) continue;
 #pragma unroll
-        for (int y = 0; y < K; ++y) {
-            if (mb[y] == kAbsent) continue;
-            const uint64_t m = ma[x] | mb[y];
-            if (proof_conflict(m, gm)) continue;
-            top.insert(m, union_prob(ma[x], pa[x], mb[y], pb[y], fp));
+            for (int y = 0; y < K; ++y) {
+                if (mb[y] == kAbsent) continue;
+                const uint64_t m = ma[x] | mb[y];
+                if (proof_conflict(m, gm)) continue;
+                top.insert(m, union_prob(ma[x], pa[x], mb[y], pb[y], fp));
+            }
         }
     }
-}
-
-template <int K>
-__global__ void __launch_bounds__(kThreadsT)
-dtkp_apply2_kernel(int64_t total, int32_t S, int32_t na, int32_t nb, int32_t n_facts, const uint32_t *__restrict__ order,
-                   const uint32_t *__restrict__ ord_len, const uint32_t *__restrict__ ord_tuples, GroupMasks gm,
-                   const float *__restrict__ fact_prob, const uint64_t *__restrict__ am,
-                   const float *__restrict__ ap, const uint64_t *__restrict__ bm, const float *__restrict__ bp,
-                   const int32_t *__restrict__ fact_b, uint64_t *__restrict__ om, float *__restrict__ op,
-                   float *__restrict__ oprob, int64_t ldo)
-{
-    // (each XCD takes a contiguous range of samples: a sample's operand lists then fill one L2 and not all eight)
-    const int64_t idx = static_cast<int64_t>(xcd_contiguous(blockIdx.x, gridDim.x)) * kThreadsT + threadIdx.x;
-    if (idx >= total) return;
-    const int64_t s = idx / S;
-    const int64_t r = idx - s * S;
-    const uint32_t len = ord_len[r];                                     // lanes of a wavefront: columns of like length,
-    if (len == 0) return;                                                // the long ones left to the wavefront-per-column kernels
-    const int32_t c = static_cast<int32_t>(order[r]);
-    const float *fp = fact_prob + s * n_facts;
-    const int64_t a0 = s * na * K, b0 = s * nb * K;
-    TopK<K> top;
-    top.clear();
-    for (uint32_t k = 0; k < len; ++k)                                   // (the lists interleaved in that order: coalesced loads)
-        offer_tuple<K>(top, ord_tuples[static_cast<size_t>(k) * S + r], a0, b0, gm, fp, am, ap, bm, bp, fact_b);
-    const int64_t o = s * S + c;
-    oprob[s * ldo + c] = top.store(om + o * K, op + o * K);
-}
-
-// One workgroup of 1, 4 or 16 wavefronts (by the table's longest column) per (sample, long column): every lane streams
-// a share of the column's tuples through a list of its own; the lists of a wavefront then meet by log2(64) exchange
-// rounds in which each lane offers its partner's entries to its own list, the wavefronts' lists through LDS and one
-// more such merge.  The list order is total on distinct proofs and repeated proofs are one proof, so the result does not depend
-// on how the candidates were split.
-template <int K>
-__global__ void __launch_bounds__(1024)
-dtkp_apply2_long_kernel(int32_t n_long, const uint32_t *__restrict__ long_cols, int32_t S, int32_t na, int32_t nb,
-                        int32_t n_facts, const uint32_t *__restrict__ col_ptr, const uint32_t *__restrict__ col_ij,
-                        GroupMasks gm, const float *__restrict__ fact_prob, const uint64_t *__restrict__ am,
-                        const float *__restrict__ ap, const uint64_t *__restrict__ bm, const float *__restrict__ bp,
-                        const int32_t *__restrict__ fact_b, uint64_t *__restrict__ om, float *__restrict__ op,
-                        float *__restrict__ oprob, int64_t ldo)
-{
-    const int64_t wg = xcd_contiguous(blockIdx.x, gridDim.x);       // a sample's columns on one XCD: its lists fill one L2
-    const int64_t s = wg / n_long;
-    const uint32_t c = long_cols[wg - s * n_long];
-    const float *fp = fact_prob + s * n_facts;
-    const int64_t a0 = s * na * K, b0 = s * nb * K;
-    TopK<K> top;
-    top.clear();
-    for (uint32_t q = col_ptr[c] + threadIdx.x, q1 = col_ptr[c + 1]; q < q1; q += blockDim.x)
-        offer_tuple<K>(top, col_ij[q], a0, b0, gm, fp, am, ap, bm, bp, fact_b);
-    merge_lists<K>(top);
-    if (blockDim.x > kWave) {                       // uniform: the wavefronts' lists meet in the first wavefront
-        __shared__ uint64_t lm[16][K];
-        __shared__ float lp[16][K];
-        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
-        if (lane == 0) {
+    // the tuples word(q), word(q + step), .. below q1
+    template <class Word>
+    __device__ __forceinline__ void run(TopK<K> &top, uint32_t q, uint32_t q1, uint32_t step, Word word) const
+    {
+        for (; q < q1; q += step) {
+            const uint32_t ij = word(q), j = ij >> 16;
+            const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K;
+            uint64_t ma[K];
+            float pa[K];
+            load_masks<K>(A.am + ia, ma);
 #pragma unroll
-            for (int x = 0; x < K; ++x) { lm[wave][x] = top.m[x]; lp[wave][x] = top.p[x]; }
+            for (int x = 0; x < K; ++x) pa[x] = -1.0f;
+            if (A.ap) load_probs<K>(A.ap + ia, pa);
+            if (A.fact_b) {
+                with_fact(top, reinterpret_cast<const uint4 *>(A.fact_b)[j], ma, pa);
+            } else with_list(top, j, ma, pa);
         }
-        __syncthreads();
-        if (wave != 0) return;
-        top.clear();
-        if (lane < n_waves) {
-#pragma unroll
-            for (int x = 0; x < K; ++x) { top.m[x] = lm[lane][x]; top.p[x] = lp[lane][x]; }
-        }
-        merge_lists<K>(top);
     }
-    if (threadIdx.x == 0) {
-        const int64_t idx = s * S + c;
-        oprob[s * ldo + c] = top.store(om + idx * K, op + idx * K);
+    __device__ __forceinline__ void listed(TopK<K> &top, uint32_t q, uint32_t q1, uint32_t step) const
+    {
+        run(top, q, q1, step, [&](uint32_t x) { return A.col_ij[x]; });
     }
-}
+    __device__ __forceinline__ void laned(TopK<K> &top, uint32_t len, int32_t r, uint32_t) const
+    {
+        run(top, 0, len, 1, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; });
+    }
+};
 
-// Columns of a few dozen tuples: four to a wavefront, 16 lanes each.
 template <int K>
-__global__ void __launch_bounds__(kWave)
-dtkp_apply2_mid_kernel(int32_t n_mid, const uint32_t *__restrict__ cols, int32_t S, int32_t na, int32_t nb, int32_t n_facts,
-                       const uint32_t *__restrict__ col_ptr, const uint32_t *__restrict__ col_ij, GroupMasks gm,
-                       const float *__restrict__ fact_prob, const uint64_t *__restrict__ am, const float *__restrict__ ap,
-                       const uint64_t *__restrict__ bm, const float *__restrict__ bp, const int32_t *__restrict__ fact_b,
-                       uint64_t *__restrict__ om, float *__restrict__ op, float *__restrict__ oprob, int64_t ldo)
+__global__ void __launch_bounds__(kHugeThreads)
+dtkp_apply2_kernel(ColumnArgs C, PairArgs A, GroupMasks gm)
 {
-    const int32_t quads = (n_mid + 3) / 4;
-    const int64_t wg = xcd_contiguous(blockIdx.x, gridDim.x);       // a sample's columns on one XCD: its lists fill one L2
-    const int64_t s = wg / quads;
-    const int32_t ci = static_cast<int32_t>(wg - s * quads) * 4 + static_cast<int32_t>(threadIdx.x / 16);
-    if (ci >= n_mid) return;                        // a whole group of 16 lanes at once
-    const uint32_t c = cols[ci];
-    const float *fp = fact_prob + s * n_facts;
-    const int64_t a0 = s * na * K, b0 = s * nb * K;
-    TopK<K> top;
-    top.clear();
-    for (uint32_t q = col_ptr[c] + (threadIdx.x & 15), q1 = col_ptr[c + 1]; q < q1; q += 16)
-        offer_tuple<K>(top, col_ij[q], a0, b0, gm, fp, am, ap, bm, bp, fact_b);
-    merge_lists<K, 16>(top);
-    if ((threadIdx.x & 15) == 0) {
-        const int64_t idx = s * S + c;
-        oprob[s * ldo + c] = top.store(om + idx * K, op + idx * K);
-    }
+    dtkp_columns<K>(C, PairOffer<K>{A, gm, nullptr, 0, 0});
 }
 
 template <int K>
-static void launch_apply2_k(int64_t total, const dol_fn_table *f, int32_t n_facts, const GroupMasks &gm,
-                            const float *fact_prob, const uint64_t *am, const float *ap, const uint64_t *bm,
-                            const float *bp, const int32_t *fact_b, uint64_t *om, float *op, float *oprob, int64_t ldo,
-                            hipStream_t st)
+static void launch_apply2_k(ColumnArgs C, const PairArgs &A, const GroupMasks &gm, hipStream_t st)
 {
-    hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid_t(total)), dim3(kThreadsT), 0, st, total, f->n_out, f->na,
-                       f->nb, n_facts, f->col_order.ptr, f->ord_len.ptr, f->ord_tuples.ptr, gm, fact_prob, am, ap, bm, bp,
-                       fact_b, om, op, oprob, ldo);
-    const int64_t n_long = static_cast<int64_t>(f->dtkp_long_cols.n);
-    const int64_t n_huge = f->n_huge_dtkp_cols, batch = total / f->n_out;
-    if (n_huge > 0)                                  // the list's first n_huge columns: 16 wavefronts each
-        hipLaunchKernelGGL(dtkp_apply2_long_kernel<K>, dim3(static_cast<unsigned>(batch * n_huge)), dim3(1024), 0, st,
-                           static_cast<int32_t>(n_huge), f->dtkp_long_cols.ptr, f->n_out, f->na, f->nb, n_facts,
-                           f->col_ptr.ptr, f->col_ij.ptr, gm, fact_prob, am, ap, bm, bp, fact_b, om, op, oprob, ldo);
-    const int64_t n_wave = f->n_wave_dtkp_cols, n_mid = n_long - n_huge - n_wave;
-    if (n_wave > 0)
-        hipLaunchKernelGGL(dtkp_apply2_long_kernel<K>, dim3(static_cast<unsigned>(batch * n_wave)), dim3(kWave), 0, st,
-                           static_cast<int32_t>(n_wave), f->dtkp_long_cols.ptr + n_huge, f->n_out, f->na, f->nb, n_facts,
-                           f->col_ptr.ptr, f->col_ij.ptr, gm, fact_prob, am, ap, bm, bp, fact_b, om, op, oprob, ldo);
-    if (n_mid > 0)
-        hipLaunchKernelGGL(dtkp_apply2_mid_kernel<K>, dim3(static_cast<unsigned>(batch * ((n_mid + 3) / 4))), dim3(kWave), 0, st,
-                           static_cast<int32_t>(n_mid), f->dtkp_long_cols.ptr + n_huge + n_wave, f->n_out, f->na, f->nb,
-                           n_facts, f->col_ptr.ptr, f->col_ij.ptr, gm, fact_prob, am, ap, bm, bp, fact_b, om, op, oprob, ldo);
+    const unsigned grid = column_launch(C);
+    hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid), dim3(column_threads(C)), 0, st, C, A, gm);
 }
 
 #define DOL_DISPATCH_K(k, CALL)                                      \
@@ -253,7 +176,14 @@ dol_status launch_dtkp_apply2(const dol_fn_table *f, int32_t batch, int32_t k, i
     if (total == 0) return DOL_OK;
     if (static_cast<int64_t>(batch) * static_cast<int64_t>(f->dtkp_long_cols.n) > 0x7fffffffLL)
         return fail(DOL_EUNSUPPORTED, "batch x long table columns exceeds 2^31");
-#define CALL(KK) launch_apply2_k<KK>(total, f, n_facts, gm, fact_prob, am, ap, bm, bp, fact_b, om, op, oprob, ldo, st)
+    ColumnArgs C{};
+    C.batch = batch, C.S = f->n_out;
+    C.n_huge = f->n_huge_dtkp_cols, C.n_wave = f->n_wave_dtkp_cols;
+    C.n_mid = static_cast<int32_t>(f->dtkp_long_cols.n) - C.n_huge - C.n_wave;
+    C.longer = f->dtkp_long_cols.ptr, C.col_ptr = f->col_ptr.ptr, C.order = f->col_order.ptr, C.len = f->ord_len.ptr;
+    C.om = om, C.op = op, C.oprob = oprob, C.ldo = ldo;
+    const PairArgs A{f->n_out, f->na, f->nb, n_facts, f->col_ij.ptr, f->ord_tuples.ptr, fact_prob, am, bm, ap, bp, fact_b};
+#define CALL(KK) launch_apply2_k<KK>(C, A, gm, st)
     DOL_DISPATCH_K(k, CALL)
 #undef CALL
     DOL_HIP(hipGetLastError());

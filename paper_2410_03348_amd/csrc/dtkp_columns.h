@@ -1,0 +1,112 @@
+// The columns of a function table under DTKP, in one launch (dtkp.hip, applyk.hip): one lane per (sample, column) for
+// columns of up to kLongDtkpCol tuples, 16 lanes, a wavefront or a workgroup for the longer ones.
+//
+// The workgroups of the longest columns come first, those of the short ones run beside them: as launches of their own, one
+// after the other, they took 40 of the 103 us of a table of 38 400 columns (64 samples, k = 3: 77 us now, where the stores'
+// and gathers' lines take about 50 in the first-level caches and the lists 40 in the vector units), 15 of the 33 us of one of
+// 3 720 columns (19 now).  Results gathered in LDS and stored as whole lines were slower (106 us): a workgroup of neighbours
+// waits for its longest column.
+#pragma once
+
+#include "dtkp_util.h"
+#include "wave_util.h"
+
+#include <algorithm>
+
+namespace dol {
+
+struct ColumnArgs {
+    int32_t batch, S;
+    int32_t n_huge, n_wave, n_mid;          // `longer`: columns of a workgroup each, of a wavefront, of 16 lanes
+    uint32_t b_huge, b_wave, b_mid;         // workgroups of each kind (multiples of eight: the XCDs' turns stay the same)
+    const uint32_t *longer;
+    const uint32_t *col_ptr;                // tuples of a column
+    const uint32_t *order, *len;            // short columns: the r-th one and its length (0: among the longer ones)
+    uint64_t *om;
+    float *op, *oprob;
+    int64_t ldo;
+};
+
+// Threads of a workgroup: more for the sake of huge columns (last table of the seven-symbol expression: 100, 79, 77, 83 us
+// with 64, 128, 256, 512; tables without huge columns: 128 or fewer).
+constexpr int kColumnThreads = 128, kHugeThreads = 256;
+inline int column_threads(const ColumnArgs &A) { return A.n_huge > 0 ? kHugeThreads : kColumnThreads; }
+
+// How the columns go into workgroups; returns how many there are.
+inline unsigned column_launch(ColumnArgs &A)
+{
+    const int threads = column_threads(A);
+    auto eight = [](int64_t n) { return static_cast<uint32_t>((n + 7) / 8 * 8); };
+    auto groups = [&](int32_t n, int lanes) { return eight(static_cast<int64_t>(A.batch) * ((n + threads / lanes - 1) / (threads / lanes))); };
+    A.b_huge = eight(static_cast<int64_t>(A.batch) * A.n_huge);
+    A.b_wave = groups(A.n_wave, kWave);
+    A.b_mid = groups(A.n_mid, 16);
+    const int64_t total = static_cast<int64_t>(A.batch) * A.S;
+    return A.b_huge + A.b_wave + A.b_mid + static_cast<unsigned>((total + threads - 1) / threads);
+}
+
+// Offer: begin(s) - the sample; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
+// laned(top, len, r, c) - those of column c, the r-th in order.
+template <int K, class Offer>
+__device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
+{
+    const int T = blockDim.x, t = threadIdx.x;
+    TopK<K> top;
+    top.clear();
+    uint32_t b = blockIdx.x;
+    if (b < A.b_huge + A.b_wave + A.b_mid) {
+        // ---- a longer column: every lane streams a share of its tuples through a list of its own; the lists of a group of
+        // lanes meet by exchange rounds in which each lane offers its partner's entries to its own list.  (The list order is
+        // total on distinct proofs and repeated proofs are one proof: the result does not depend on the split.)
+        const bool huge = b < A.b_huge, wave = !huge && b < A.b_huge + A.b_wave;
+        const int lanes = huge ? T : wave ? kWave : 16, per = T / lanes;
+        const int32_t n = huge ? A.n_huge : wave ? A.n_wave : A.n_mid, groups = (n + per - 1) / per;
+        if (!huge) b -= wave ? A.b_huge : A.b_huge + A.b_wave;
+        // (a sample's columns on one XCD: its lists fill one L2)
+        const int32_t id = xcd_contiguous(b, huge ? A.b_huge : wave ? A.b_wave : A.b_mid);
+        const int32_t s = id / groups, ci = (id - s * groups) * per + t / lanes;
+        if (s >= A.batch) return;
+        if (ci >= n) return;                        // (all lanes of a group; never a huge column's)
+        const uint32_t c = A.longer[(huge ? 0 : wave ? A.n_huge : A.n_huge + A.n_wave) + ci];
+        offer.begin(s);
+        offer.listed(top, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes);
+        if (lanes == 16) merge_lists<K, 16>(top);
+        else merge_lists<K>(top);
+        if (huge && T > kWave) {                    // uniform: the wavefronts' lists meet in the first wavefront
+            __shared__ uint64_t lm[kHugeThreads / kWave * K];
+            __shared__ float lp[kHugeThreads / kWave * K];
+            const int lane = t & (kWave - 1), w = t / kWave, n_waves = T / kWave;
+            if (lane == 0) {
+#pragma unroll
+                for (int x = 0; x < K; ++x) { lm[w * K + x] = top.m[x]; lp[w * K + x] = top.p[x]; }
+            }
+            __syncthreads();
+            if (w != 0) return;
+            top.clear();
+            if (lane < n_waves) {
+#pragma unroll
+                for (int x = 0; x < K; ++x) { top.m[x] = lm[lane * K + x]; top.p[x] = lp[lane * K + x]; }
+            }
+            merge_lists<K, kHugeThreads / kWave>(top);
+        }
+        if (t % lanes == 0) {
+            const int64_t o = static_cast<int64_t>(s) * A.S + c;
+            A.oprob[s * A.ldo + c] = top.store(A.om + o * K, A.op + o * K);
+        }
+        return;
+    }
+    const uint32_t first = A.b_huge + A.b_wave + A.b_mid;
+    const int32_t id = xcd_contiguous(b - first, gridDim.x - first);
+    const int64_t at = static_cast<int64_t>(id) * T + t;
+    if (at >= static_cast<int64_t>(A.batch) * A.S) return;
+    const int32_t s = static_cast<int32_t>(at / A.S), r = static_cast<int32_t>(at - static_cast<int64_t>(s) * A.S);
+    // lanes of a wavefront: columns of like length
+    const uint32_t len = A.len[r], c = A.order[r];
+    if (len == 0) return;
+    offer.begin(s);
+    offer.laned(top, len, r, c);
+    const int64_t o = static_cast<int64_t>(s) * A.S + c;
+    A.oprob[s * A.ldo + c] = top.store(A.om + o * K, A.op + o * K);
+}
+
+}  // namespace dol

@@ -1877,6 +1877,52 @@ def test_random_tables_differential_dtkp(dol, seed):
     assert_close(host(gf), want, "dtkp random table gradient, seed %d" % seed)
 
 
+@pytest.mark.parametrize("batch,lengths", [(1, (16, 17)), (3, (1, 16, 17, 64, 65)), (9, (1025, 2, 1024, 65, 64, 17, 40, 33, 3)), (5, (1500,) + (20,) * 33)])
+def test_dtkp_columns_of_every_length(dol, batch, lengths):
+    """A lane, 16 lanes, a wavefront and a workgroup per column in one launch: lengths on both sides of each limit, groups of
+    columns that do not fill their workgroup, a second operand given by its facts and by its lists, and a unary function."""
+    k, nb, n_facts = 3, 6, 24
+    n = sum(lengths)
+    na = -(-n // nb)
+    fp = W.uniform01(41, batch * n_facts).astype(np.float32).reshape(batch, n_facts)
+    grp = np.concatenate([np.arange(18), np.full(6, 18)]).astype(np.int32)
+    prov = dol.Prov(dol.DTKP, k, dev(fp), grp)
+    # first operand: up to k proofs of two facts per symbol (a table of 18 x 18 onto its symbols)
+    pair = (W.splitmix64(42, np.arange(18 * 18)) % np.uint64(na)).astype(np.int32).reshape(18, 18)
+    pair.reshape(-1)[:min(na, 324)] = np.arange(min(na, 324))
+    one = oracle.dtkp_init(np.arange(18), fp, k)
+    syms, am, ap, _ = oracle.dtkp_apply2(oracle.dense_to_triples(pair), 18, 18, k, grp, fp, one[0], one[0])
+    which = np.arange(na) % syms.size                  # (symbols past those repeat them)
+    am, ap = np.ascontiguousarray(am[:, which]), np.ascontiguousarray(ap[:, which])
+    fact_b = np.arange(18, 24, dtype=np.int32)
+    bm = oracle.dtkp_init(fact_b, fp, k)
+    col = np.repeat(np.arange(len(lengths)), lengths)[np.argsort(W.splitmix64(43, np.arange(n)))].astype(np.int32)
+    table = np.full(na * nb, -1, np.int32)
+    table[:n] = col
+    so, om, op, opr = oracle.dtkp_apply2(oracle.dense_to_triples(table.reshape(na, nb)), na, nb, k, grp, fp, am, bm[0])
+    f = dol.FnTable.create_dense(table.reshape(na, nb))
+    a = dol.Dist(np.arange(na), torch.zeros((batch, na), device="cuda"), dev(am.view(np.int64)), dev(ap))
+    b = dol.Dist.empty(np.arange(nb), batch, k=k)
+    dol.dtkp_init(b, fact_b, prov)
+    for call in (lambda out: dol.apply2(a, b, f, prov, out), lambda out: dol.dtkp_apply2_input(a, fact_b, f, prov, out)):
+        out = dol.Dist.empty(f.out_syms, batch, k=k)
+        call(out)
+        np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), om)
+        np.testing.assert_array_equal(host(out.proof_prob), op)
+        assert_close(host(out.prob), opr, "dtkp columns")
+    # a unary function with the same columns
+    m1, p1 = np.ascontiguousarray(am[:, np.arange(n) % na]), np.ascontiguousarray(ap[:, np.arange(n) % na])
+    idx, to = oracle.dense_to_tuples(col)
+    s1, um, up, upr = oracle.dtkp_applyk(idx, to, k, grp, fp, [m1])
+    fu = dol.FnkTable.create_dense(col)
+    x = dol.Dist(np.arange(n), torch.zeros((batch, n), device="cuda"), dev(m1.view(np.int64)), dev(p1))
+    out = dol.Dist.empty(fu.out_syms, batch, k=k)
+    dol.apply_k([x], fu, prov, out)
+    np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), um)
+    np.testing.assert_array_equal(host(out.proof_prob), up)
+    assert_close(host(out.prob), upr, "dtkp unary columns")
+
+
 @pytest.mark.parametrize("k", [1, 3])
 def test_dtkp_apply2_input_equals_init_then_apply2(dol, k):
     """The second operand given by its facts: bit for bit what dol_dtkp_init + dol_apply2 give, on a table with
