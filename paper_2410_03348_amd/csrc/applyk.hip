@@ -30,13 +30,9 @@ struct dol_fnk_table {
     dol::DevArray<uint32_t> row_ptr;     // [sum n_sym + 1]
     dol::DevArray<uint32_t> row_tup;     // [n_tuples*K] grouped-tuple numbers of each operand row, ascending
     dol::DevArray<uint32_t> long_cols;   // columns with more than dol::kLongTableCol tuples
-    // ... more than dol::kLongDtkpCol: first those above dol::kHugeDtkpCol (a workgroup each), then those above
-    // dol::kWaveDtkpCol (a wavefront each), then the shorter ones (16 lanes each)
-    dol::DevArray<uint32_t> dtkp_long_cols;
-    int32_t n_huge_dtkp_cols = 0, n_wave_dtkp_cols = 0;
-    dol::DevArray<uint32_t> dtkp_order, dtkp_len;   // the others (by length; length 0: a longer one)
-    dol::DevArray<uint16_t> dtkp_tuples;            // ... of a unary function: symbol k of the r-th column at [k * n_out + r]
-    dol::DevArray<uint32_t> col_order;   // all columns in the order of dol::columns_by_length (limit: kLongDtkpCol)
+    dol::DtkpColumns dtkp_cols;
+    dol::DevArray<uint16_t> dtkp_tuples;            // unary functions: symbol k of the r-th short column at [k * n_out + r]
+    dol::DevArray<uint32_t> col_order;   // all columns in the order of dol::columns_by_length (limit: kLongTableCol)
     // unary functions (K = 1): the first eight symbols of every image again, 16 bytes per column (0xFFFF = none), and
     // the column of every symbol (-1: rejected)
     dol::DevArray<uint16_t> unary_head;
@@ -570,31 +566,15 @@ static dol_status build_k(int32_t K, const int32_t *n_sym, int64_t n, const int3
             for (int l = 0; l < K; ++l) row_tup[fill[tb->row_base[l] + tup[t * K + l]]++] = static_cast<uint32_t>(t);
     }
 
-    std::vector<uint32_t> long_cols, dtkp_long_cols, dtkp_wave_cols, dtkp_mid_cols;
-    for (int32_t c = 0; c < S; ++c) {
-        const uint32_t len = col_ptr[c + 1] - col_ptr[c];
-        if (len > static_cast<uint32_t>(kLongTableCol)) long_cols.push_back(static_cast<uint32_t>(c));
-        if (len > static_cast<uint32_t>(kHugeDtkpCol)) dtkp_long_cols.push_back(static_cast<uint32_t>(c));
-        else if (len > static_cast<uint32_t>(kWaveDtkpCol)) dtkp_wave_cols.push_back(static_cast<uint32_t>(c));
-        else if (len > static_cast<uint32_t>(kLongDtkpCol)) dtkp_mid_cols.push_back(static_cast<uint32_t>(c));
-    }
-    tb->n_huge_dtkp_cols = static_cast<int32_t>(dtkp_long_cols.size());
-    tb->n_wave_dtkp_cols = static_cast<int32_t>(dtkp_wave_cols.size());
-    dtkp_long_cols.insert(dtkp_long_cols.end(), dtkp_wave_cols.begin(), dtkp_wave_cols.end());
-    dtkp_long_cols.insert(dtkp_long_cols.end(), dtkp_mid_cols.begin(), dtkp_mid_cols.end());
-
-    const std::vector<uint32_t> col_order = columns_by_length(col_ptr, S, kLongDtkpCol);
+    std::vector<uint32_t> long_cols;
+    for (int32_t c = 0; c < S; ++c)
+        if (col_ptr[c + 1] - col_ptr[c] > static_cast<uint32_t>(kLongTableCol)) long_cols.push_back(static_cast<uint32_t>(c));
+    const std::vector<uint32_t> col_order = columns_by_length(col_ptr, S, kLongTableCol);
     // (not for a unary function, whose lists are one gather each: there the neighbouring columns' neighbouring symbols matter
     // more)
-    std::vector<uint32_t> dtkp_order = col_order;
+    std::vector<uint32_t> dtkp_order = columns_by_length(col_ptr, S, kLongDtkpCol), dtkp_len;
     if (K == 1) std::iota(dtkp_order.begin(), dtkp_order.end(), 0u);
-    std::vector<uint32_t> dtkp_len(static_cast<size_t>(S), 0);
-    for (int32_t r = 0; r < S; ++r) {
-        const uint32_t len = col_ptr[dtkp_order[r] + 1] - col_ptr[dtkp_order[r]];
-        if (len <= static_cast<uint32_t>(kLongDtkpCol)) dtkp_len[r] = len;
-    }
-    DOL_HIP(tb->dtkp_order.upload(dtkp_order));
-    DOL_HIP(tb->dtkp_len.upload(dtkp_len));
+    DOL_HIP(tb->dtkp_cols.build(col_ptr, dtkp_order, &dtkp_len));
     if (K == 1) {
         const uint32_t longest = S ? *std::max_element(dtkp_len.begin(), dtkp_len.end()) : 0;
         std::vector<uint16_t> tuples(static_cast<size_t>(longest) * S, 0);
@@ -619,7 +599,6 @@ static dol_status build_k(int32_t K, const int32_t *n_sym, int64_t n, const int3
     }
     DOL_HIP(hipGetDevice(&tb->device));
     DOL_HIP(tb->long_cols.upload(long_cols));
-    DOL_HIP(tb->dtkp_long_cols.upload(dtkp_long_cols));
     DOL_HIP(tb->col_order.upload(col_order));
     DOL_HIP(tb->col_ptr.upload(col_ptr));
     DOL_HIP(tb->tup.upload(tup));
@@ -698,7 +677,7 @@ dol_status dol_apply_k(int32_t K, const dol_dist *const *in, const dol_fnk_table
             if (out->sym_ids[c] != f->out_syms[c]) return fail(DOL_EINVAL, "out.sym_ids[%d] = %d, the table produces %d there", c, out->sym_ids[c], f->out_syms[c]);
     if (dol_status st = check_work(batch, f->n_out)) return st;
     if (batch == 0 || f->n_out == 0) return DOL_OK;
-    if (static_cast<int64_t>(batch) * static_cast<int64_t>(std::max(f->long_cols.n, f->dtkp_long_cols.n)) > 0x7fffffffLL)
+    if (static_cast<int64_t>(batch) * static_cast<int64_t>(std::max(f->long_cols.n, f->dtkp_cols.longer.n)) > 0x7fffffffLL)
         return fail(DOL_EUNSUPPORTED, "batch x long table columns exceeds 2^31");
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (!dtkp) {
@@ -718,9 +697,8 @@ dol_status dol_apply_k(int32_t K, const dol_dist *const *in, const dol_fnk_table
     for (int l = 0; l < K; ++l) { pr.m[l] = in[l]->proof_mask; pr.p[l] = in[l]->proof_prob; pr.n[l] = in[l]->n_sym; }
     ColumnArgs C{};
     C.batch = batch, C.S = f->n_out;
-    C.n_huge = f->n_huge_dtkp_cols, C.n_wave = f->n_wave_dtkp_cols;
-    C.n_mid = static_cast<int32_t>(f->dtkp_long_cols.n) - C.n_huge - C.n_wave;
-    C.longer = f->dtkp_long_cols.ptr, C.col_ptr = f->col_ptr.ptr, C.order = f->dtkp_order.ptr, C.len = f->dtkp_len.ptr;
+    C.col_ptr = f->col_ptr.ptr;
+    set_columns(C, f->dtkp_cols);
     C.om = out->proof_mask, C.op = out->proof_prob, C.oprob = out->prob, C.ldo = out->ld;
     const TupleArgs A{f->n_out, f->K, prov->n_facts, f->col_ptr.ptr, f->tup.ptr, f->dtkp_tuples.ptr, prov->fact_prob, pr};
     switch (prov->k) {

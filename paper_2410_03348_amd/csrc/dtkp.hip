@@ -174,15 +174,14 @@ dol_status launch_dtkp_apply2(const dol_fn_table *f, int32_t batch, int32_t k, i
 {
     const int64_t total = static_cast<int64_t>(batch) * f->n_out;
     if (total == 0) return DOL_OK;
-    if (static_cast<int64_t>(batch) * static_cast<int64_t>(f->dtkp_long_cols.n) > 0x7fffffffLL)
+    if (static_cast<int64_t>(batch) * static_cast<int64_t>(f->dtkp_cols.longer.n) > 0x7fffffffLL)
         return fail(DOL_EUNSUPPORTED, "batch x long table columns exceeds 2^31");
     ColumnArgs C{};
     C.batch = batch, C.S = f->n_out;
-    C.n_huge = f->n_huge_dtkp_cols, C.n_wave = f->n_wave_dtkp_cols;
-    C.n_mid = static_cast<int32_t>(f->dtkp_long_cols.n) - C.n_huge - C.n_wave;
-    C.longer = f->dtkp_long_cols.ptr, C.col_ptr = f->col_ptr.ptr, C.order = f->col_order.ptr, C.len = f->ord_len.ptr;
+    C.col_ptr = f->col_ptr.ptr;
+    set_columns(C, f->dtkp_cols);
     C.om = om, C.op = op, C.oprob = oprob, C.ldo = ldo;
-    const PairArgs A{f->n_out, f->na, f->nb, n_facts, f->col_ij.ptr, f->ord_tuples.ptr, fact_prob, am, bm, ap, bp, fact_b};
+    const PairArgs A{f->n_out, f->na, f->nb, n_facts, f->col_ij.ptr, f->dtkp_tuples.ptr, fact_prob, am, bm, ap, bp, fact_b};
 #define CALL(KK) launch_apply2_k<KK>(C, A, gm, st)
     DOL_DISPATCH_K(k, CALL)
 #undef CALL

@@ -1,11 +1,12 @@
 // The columns of a function table under DTKP, in one launch (dtkp.hip, applyk.hip): one lane per (sample, column) for
-// columns of up to kLongDtkpCol tuples, 16 lanes, a wavefront or a workgroup for the longer ones.
+// columns of up to kLongDtkpCol tuples, 4 lanes, 16, a wavefront or a workgroup for the longer ones.
 //
 // The workgroups of the longest columns come first, those of the short ones run beside them: as launches of their own, one
-// after the other, they took 40 of the 103 us of a table of 38 400 columns (64 samples, k = 3: 77 us now, where the stores'
-// and gathers' lines take about 50 in the first-level caches and the lists 40 in the vector units), 15 of the 33 us of one of
-// 3 720 columns (19 now).  Results gathered in LDS and stored as whole lines were slower (106 us): a workgroup of neighbours
-// waits for its longest column.
+// after the other, they took 40 of the 103 us of a table of 38 400 columns (64 samples, k = 3: 77 us in one launch).  A lane
+// waits for every tuple of its column, 0.8 us each, so it gets few: with up to 16 tuples to a lane that table took 77 us and
+// one of 758 columns 16, with up to 8 (then 16 lanes) 79 and 11, with up to 4 and four lanes up to 16, as here, 75 and 8.
+// Results gathered in LDS and stored as whole lines were slower (106 us): a workgroup of neighbours waits for its longest
+// column.
 #pragma once
 
 #include "dtkp_util.h"
@@ -17,8 +18,8 @@ namespace dol {
 
 struct ColumnArgs {
     int32_t batch, S;
-    int32_t n_huge, n_wave, n_mid;          // `longer`: columns of a workgroup each, of a wavefront, of 16 lanes
-    uint32_t b_huge, b_wave, b_mid;         // workgroups of each kind (multiples of eight: the XCDs' turns stay the same)
+    int32_t n_huge, n_wave, n_mid, n_quad;  // `longer`: columns of a workgroup each, of a wavefront, of 16 lanes, of four
+    uint32_t b_huge, b_wave, b_mid, b_quad; // workgroups of each kind (multiples of eight: the XCDs' turns stay the same)
     const uint32_t *longer;
     const uint32_t *col_ptr;                // tuples of a column
     const uint32_t *order, *len;            // short columns: the r-th one and its length (0: among the longer ones)
@@ -26,6 +27,12 @@ struct ColumnArgs {
     float *op, *oprob;
     int64_t ldo;
 };
+
+inline void set_columns(ColumnArgs &A, const DtkpColumns &D)
+{
+    A.n_huge = D.n_huge, A.n_wave = D.n_wave, A.n_mid = D.n_mid, A.n_quad = D.n_quad;
+    A.longer = D.longer.ptr, A.order = D.order.ptr, A.len = D.len.ptr;
+}
 
 // Threads of a workgroup: more for the sake of huge columns (last table of the seven-symbol expression: 100, 79, 77, 83 us
 // with 64, 128, 256, 512; tables without huge columns: 128 or fewer).
@@ -41,8 +48,9 @@ inline unsigned column_launch(ColumnArgs &A)
     A.b_huge = eight(static_cast<int64_t>(A.batch) * A.n_huge);
     A.b_wave = groups(A.n_wave, kWave);
     A.b_mid = groups(A.n_mid, 16);
+    A.b_quad = groups(A.n_quad, 4);
     const int64_t total = static_cast<int64_t>(A.batch) * A.S;
-    return A.b_huge + A.b_wave + A.b_mid + static_cast<unsigned>((total + threads - 1) / threads);
+    return A.b_huge + A.b_wave + A.b_mid + A.b_quad + static_cast<unsigned>((total + threads - 1) / threads);
 }
 
 // Offer: begin(s) - the sample; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
@@ -53,26 +61,36 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
     const int T = blockDim.x, t = threadIdx.x;
     TopK<K> top;
     top.clear();
+    const uint32_t first = A.b_huge + A.b_wave + A.b_mid + A.b_quad;
     uint32_t b = blockIdx.x;
-    if (b < A.b_huge + A.b_wave + A.b_mid) {
+    if (b < first) {
         // ---- a longer column: every lane streams a share of its tuples through a list of its own; the lists of a group of
         // lanes meet by exchange rounds in which each lane offers its partner's entries to its own list.  (The list order is
         // total on distinct proofs and repeated proofs are one proof: the result does not depend on the split.)
-        const bool huge = b < A.b_huge, wave = !huge && b < A.b_huge + A.b_wave;
-        const int lanes = huge ? T : wave ? kWave : 16, per = T / lanes;
-        const int32_t n = huge ? A.n_huge : wave ? A.n_wave : A.n_mid, groups = (n + per - 1) / per;
-        if (!huge) b -= wave ? A.b_huge : A.b_huge + A.b_wave;
-        // (a sample's columns on one XCD: its lists fill one L2)
-        const int32_t id = xcd_contiguous(b, huge ? A.b_huge : wave ? A.b_wave : A.b_mid);
+        int lanes = T;
+        int32_t n = A.n_huge, from = 0;
+        uint32_t blocks = A.b_huge;
+        auto next = [&](int l, int32_t count, uint32_t its) {       // uniform
+            if (b < blocks) return;
+            b -= blocks, from += n;
+            lanes = l, n = count, blocks = its;
+        };
+        next(kWave, A.n_wave, A.b_wave);
+        next(16, A.n_mid, A.b_mid);
+        next(4, A.n_quad, A.b_quad);
+        const bool huge = lanes == T;
+        const int per = T / lanes, groups = (n + per - 1) / per;
+        const int32_t id = xcd_contiguous(b, blocks);               // (a sample's columns on one XCD: its lists fill one L2)
         const int32_t s = id / groups, ci = (id - s * groups) * per + t / lanes;
         if (s >= A.batch) return;
         if (ci >= n) return;                        // (all lanes of a group; never a huge column's)
-        const uint32_t c = A.longer[(huge ? 0 : wave ? A.n_huge : A.n_huge + A.n_wave) + ci];
+        const uint32_t c = A.longer[from + ci];
         offer.begin(s);
         offer.listed(top, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes);
-        if (lanes == 16) merge_lists<K, 16>(top);
+        if (lanes == 4) merge_lists<K, 4>(top);
+        else if (lanes == 16) merge_lists<K, 16>(top);
         else merge_lists<K>(top);
-        if (huge && T > kWave) {                    // uniform: the wavefronts' lists meet in the first wavefront
+        if (huge) {                                 // uniform: the wavefronts' lists meet in the first wavefront
             __shared__ uint64_t lm[kHugeThreads / kWave * K];
             __shared__ float lp[kHugeThreads / kWave * K];
             const int lane = t & (kWave - 1), w = t / kWave, n_waves = T / kWave;
@@ -95,7 +113,6 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
         }
         return;
     }
-    const uint32_t first = A.b_huge + A.b_wave + A.b_mid;
     const int32_t id = xcd_contiguous(b - first, gridDim.x - first);
     const int64_t at = static_cast<int64_t>(id) * T + t;
     if (at >= static_cast<int64_t>(A.batch) * A.S) return;

@@ -66,10 +66,10 @@ struct DevArray {
 
 constexpr int kLongTableRow = 64;   // backward: table rows with more tuples are reduced by a whole wavefront
 constexpr int kLongTableCol = 64;   // forward: output columns with more tuples are summed by a whole wavefront
-constexpr int kLongDtkpCol = 16;    // the same under DTKP, where a tuple costs a few hundred instructions
+constexpr int kLongDtkpCol = 4;     // the same under DTKP, where a tuple costs a few hundred instructions
 constexpr int kHugeTableCol = 4096; // columns with more tuples get a workgroup of 16 wavefronts instead of one wavefront
 constexpr int kHugeDtkpCol = 1024;  // the same under DTKP
-constexpr int kWaveDtkpCol = 64;    // DTKP columns of kLongDtkpCol+1 .. this many tuples share a wavefront four at a time
+constexpr int kMidDtkpCol = 16, kWaveDtkpCol = 64;   // DTKP columns of more than kLongDtkpCol: 4 lanes, 16 lanes, a wavefront
 constexpr int32_t kStageMinRow = 2048;       // operand rows of at least this many tags are staged in LDS before gathers;
 constexpr size_t kStageMaxBytes = 158 * 1024;   // narrower ones stay with the cached gathers; of the 160 KB of a compute unit
 constexpr int kByJMax = 16;         // tables whose second operand has at most this many symbols get dense per-j maps
@@ -97,6 +97,33 @@ struct ListPlan {
     int32_t n_huge = 0, n_wave = 0, n_mid = 0;
     int64_t long_words = 0;             // words of the huge and the wavefront lists
     size_t n_words = 0;                 // words laid out for lanes, filling included
+};
+
+// The columns of a table by length, for the DTKP kernels (dtkp_columns.h).
+struct DtkpColumns {
+    DevArray<uint32_t> order, len;      // columns of up to kLongDtkpCol tuples: the r-th one and its length (0: a longer one)
+    DevArray<uint32_t> longer;          // first those of more than kHugeDtkpCol tuples, then kWaveDtkpCol, kMidDtkpCol, kLongDtkpCol
+    int32_t n_huge = 0, n_wave = 0, n_mid = 0, n_quad = 0;
+    // by_length: all columns in the order the short ones are taken; lengths: a host copy of len
+    hipError_t build(const std::vector<uint32_t> &col_ptr, const std::vector<uint32_t> &by_length, std::vector<uint32_t> *lengths)
+    {
+        const size_t S = by_length.size();
+        std::vector<uint32_t> cls[4], all;
+        auto length = [&](uint32_t c) { return static_cast<int64_t>(col_ptr[c + 1]) - col_ptr[c]; };
+        for (uint32_t c = 0; c < S; ++c) {
+            const int64_t l = length(c);
+            if (l > kLongDtkpCol) cls[l > kHugeDtkpCol ? 0 : l > kWaveDtkpCol ? 1 : l > kMidDtkpCol ? 2 : 3].push_back(c);
+        }
+        for (const auto &x : cls) all.insert(all.end(), x.begin(), x.end());
+        n_huge = static_cast<int32_t>(cls[0].size()), n_wave = static_cast<int32_t>(cls[1].size());
+        n_mid = static_cast<int32_t>(cls[2].size()), n_quad = static_cast<int32_t>(cls[3].size());
+        lengths->assign(S, 0);
+        for (size_t r = 0; r < S; ++r)
+            if (length(by_length[r]) <= kLongDtkpCol) (*lengths)[r] = static_cast<uint32_t>(length(by_length[r]));
+        hipError_t e;
+        if ((e = order.upload(by_length)) != hipSuccess || (e = len.upload(*lengths)) != hipSuccess) return e;
+        return longer.upload(all);
+    }
 };
 
 // Square tables that are a grid (iterate_grid.hip): column c has one tuple (i, j) for each i among c and its neighbours in a
@@ -148,18 +175,13 @@ struct dol_fn_table {
     dol::DevArray<uint32_t> rowb_pos;
     // rows with more than dol::kLongTableRow tuples (x < na: row x of a, else row x - na of b)
     dol::DevArray<uint32_t> long_rows;
-    // output columns with more than dol::kLongTableCol / dol::kLongDtkpCol tuples
-    dol::DevArray<uint32_t> long_cols, dtkp_long_cols;
-    // all columns in the order the thread-per-column kernels over long operand rows take them
-    // (dol::columns_by_length, with the DTKP kernel's limit on the length of a column)
-    dol::DevArray<uint32_t> col_order;
-    // the tuple lists of the columns of at most dol::kLongDtkpCol tuples, interleaved in that order: tuple k of column
-    // col_order[r] is ord_tuples[k * n_out + r] and its list has ord_len[r] entries (0: a longer column), so that lanes on
-    // neighbouring r read neighbouring words
-    dol::DevArray<uint32_t> ord_tuples, ord_len;
-    // each list starts with its huge columns (more than dol::kHugeTableCol / dol::kHugeDtkpCol tuples)
-    int32_t n_huge_cols = 0, n_huge_dtkp_cols = 0;
-    int32_t n_wave_dtkp_cols = 0;        // dtkp_long_cols: huge, then this many one-wavefront columns, then the shorter ones
+    // output columns with more than dol::kLongTableCol tuples, the n_huge_cols with more than dol::kHugeTableCol first
+    dol::DevArray<uint32_t> long_cols;
+    int32_t n_huge_cols = 0;
+    // DTKP: the columns by length, and the tuple lists of those of at most dol::kLongDtkpCol tuples, interleaved: tuple k of
+    // the r-th of them is dtkp_tuples[k * n_out + r], so that lanes on neighbouring r read neighbouring words
+    dol::DtkpColumns dtkp_cols;
+    dol::DevArray<uint32_t> dtkp_tuples;
     // LDS gather kernels (damp_lds.hip): per output column (forward), row of a, row of b (backward) a list of
     // 16-byte packets of four tuples; *_ptr[x] .. *_ptr[x+1] are the packets of x
     bool lds_fwd_ok = false, lds_bwd_ok = false;

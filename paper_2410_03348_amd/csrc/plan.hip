@@ -178,49 +178,33 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
     for (int32_t j = 0; j < nb; ++j)
         if (rowb_ptr[j + 1] - rowb_ptr[j] > static_cast<uint32_t>(kLongTableRow)) long_rows.push_back(static_cast<uint32_t>(na + j));
 
-    // long columns: the huge ones first, then those above `wave_above`, then the rest
-    auto long_list = [&](uint32_t longer_than, uint32_t wave_above, uint32_t huge_above, int32_t *n_huge, int32_t *n_wave) {
-        std::vector<uint32_t> huge, wave, rest;
-        for (int32_t c = 0; c < S; ++c) {
-            const uint32_t len = col_ptr[c + 1] - col_ptr[c];
-            if (len > huge_above) huge.push_back(static_cast<uint32_t>(c));
-            else if (len > wave_above) wave.push_back(static_cast<uint32_t>(c));
-            else if (len > longer_than) rest.push_back(static_cast<uint32_t>(c));
-        }
-        *n_huge = static_cast<int32_t>(huge.size());
-        *n_wave = static_cast<int32_t>(wave.size());
-        huge.insert(huge.end(), wave.begin(), wave.end());
-        huge.insert(huge.end(), rest.begin(), rest.end());
-        return huge;
-    };
-    int32_t unused = 0;
-    const std::vector<uint32_t> long_cols = long_list(kLongTableCol, kLongTableCol, kHugeTableCol, &tb->n_huge_cols, &unused);
-    const std::vector<uint32_t> dtkp_long_cols =
-        long_list(kLongDtkpCol, kWaveDtkpCol, kHugeDtkpCol, &tb->n_huge_dtkp_cols, &tb->n_wave_dtkp_cols);
+    // long columns, the huge ones first
+    std::vector<uint32_t> long_cols, less_long;
+    for (int32_t c = 0; c < S; ++c) {
+        const uint32_t len = col_ptr[c + 1] - col_ptr[c];
+        if (len > static_cast<uint32_t>(kHugeTableCol)) long_cols.push_back(static_cast<uint32_t>(c));
+        else if (len > static_cast<uint32_t>(kLongTableCol)) less_long.push_back(static_cast<uint32_t>(c));
+    }
+    tb->n_huge_cols = static_cast<int32_t>(long_cols.size());
+    long_cols.insert(long_cols.end(), less_long.begin(), less_long.end());
 
     if (hipGetDevice(&tb->device) != hipSuccess) tb->device = 0;
     hipError_t e;
     if ((e = tb->long_rows.upload(long_rows)) != hipSuccess) return hip_fail(e, "uploading the function table");
     const std::vector<uint32_t> col_order = columns_by_length(col_ptr, S, kLongDtkpCol);
-    if ((e = tb->long_cols.upload(long_cols)) != hipSuccess || (e = tb->dtkp_long_cols.upload(dtkp_long_cols)) != hipSuccess ||
-        (e = tb->col_order.upload(col_order)) != hipSuccess)
+    std::vector<uint32_t> lengths;
+    if ((e = tb->long_cols.upload(long_cols)) != hipSuccess || (e = tb->dtkp_cols.build(col_ptr, col_order, &lengths)) != hipSuccess)
         return hip_fail(e, "uploading the function table");
     std::vector<uint32_t> col_head(static_cast<size_t>(S) * 4, 0xFFFFFFFFu);
     for (int32_t c = 0; c < S; ++c)
         for (uint32_t q = col_ptr[c], u = 0; q < col_ptr[c + 1] && u < 4; ++q, ++u) col_head[static_cast<size_t>(c) * 4 + u] = col_ij[q];
     if ((e = tb->col_head.upload(col_head)) != hipSuccess) return hip_fail(e, "uploading the function table");
     {
-        uint32_t longest = 0;
-        std::vector<uint32_t> ord_len(static_cast<size_t>(S), 0);
-        for (int32_t r = 0; r < S; ++r) {
-            const uint32_t len = col_ptr[col_order[r] + 1] - col_ptr[col_order[r]];
-            if (len <= static_cast<uint32_t>(kLongDtkpCol)) { ord_len[r] = len; longest = std::max(longest, len); }
-        }
-        std::vector<uint32_t> ord_tuples(static_cast<size_t>(longest) * S, 0);
+        const uint32_t longest = S ? *std::max_element(lengths.begin(), lengths.end()) : 0;
+        std::vector<uint32_t> tuples(static_cast<size_t>(longest) * S, 0);
         for (int32_t r = 0; r < S; ++r)
-            for (uint32_t k = 0; k < ord_len[r]; ++k) ord_tuples[static_cast<size_t>(k) * S + r] = col_ij[col_ptr[col_order[r]] + k];
-        if ((e = tb->ord_len.upload(ord_len)) != hipSuccess || (e = tb->ord_tuples.upload(ord_tuples)) != hipSuccess)
-            return hip_fail(e, "uploading the function table");
+            for (uint32_t k = 0; k < lengths[r]; ++k) tuples[static_cast<size_t>(k) * S + r] = col_ij[col_ptr[col_order[r]] + k];
+        if ((e = tb->dtkp_tuples.upload(tuples)) != hipSuccess) return hip_fail(e, "uploading the function table");
     }
     if ((e = tb->col_ptr.upload(col_ptr)) != hipSuccess || (e = tb->col_ij.upload(col_ij)) != hipSuccess ||
         (e = tb->rowa_ptr.upload(rowa_ptr)) != hipSuccess || (e = tb->rowa_jc.upload(rowa_jc)) != hipSuccess ||

@@ -1877,9 +1877,9 @@ def test_random_tables_differential_dtkp(dol, seed):
     assert_close(host(gf), want, "dtkp random table gradient, seed %d" % seed)
 
 
-@pytest.mark.parametrize("batch,lengths", [(1, (16, 17)), (3, (1, 16, 17, 64, 65)), (9, (1025, 2, 1024, 65, 64, 17, 40, 33, 3)), (5, (1500,) + (20,) * 33)])
+@pytest.mark.parametrize("batch,lengths", [(1, (4, 5)), (1, (16, 17)), (3, (1, 16, 17, 64, 65, 5, 4)), (9, (1025, 2, 1024, 65, 64, 17, 40, 33, 3, 5, 4, 7)), (5, (1500,) + (20,) * 33)])
 def test_dtkp_columns_of_every_length(dol, batch, lengths):
-    """A lane, 16 lanes, a wavefront and a workgroup per column in one launch: lengths on both sides of each limit, groups of
+    """A lane, 4 lanes, 16, a wavefront and a workgroup per column in one launch: lengths on both sides of each limit, groups of
     columns that do not fill their workgroup, a second operand given by its facts and by its lists, and a unary function."""
     k, nb, n_facts = 3, 6, 24
     n = sum(lengths)
