@@ -330,116 +330,6 @@ dol_status launch_zero_rows(int32_t batch, int32_t n, float *x, int64_t ld, hipS
     return DOL_OK;
 }
 
-// out[s, c] = in[s, src_col[c]], or 0 where src_col[c] < 0: Filter forward (src_col = kept positions) and its
-// transpose (src_col = position in the filtered row or -1).
-__global__ void __launch_bounds__(kThreads)
-damp_gather_cols_kernel(Rows R, const int32_t *__restrict__ src_col, const float *__restrict__ in, int64_t ldi,
-                        float *__restrict__ out, int64_t ldo, int32_t accumulate)
-{
-    for_each_element(R, [&](int64_t s, int c) {
-        const int32_t i = src_col[c];
-        const float v = i >= 0 ? in[s * ldi + i] : 0.0f;
-        out[s * ldo + c] = accumulate ? out[s * ldo + c] + v : v;
-    });
-}
-
-dol_status launch_damp_filter_fwd(const FilterPlan *p, int32_t batch, const float *in, int64_t ldi, float *out,
-                                  int64_t ldo, hipStream_t st)
-{
-    if (batch == 0 || p->n_out == 0) return DOL_OK;
-    bool done = false;
-    if (dol_status s2 = launch_rows_gather(batch, p->n_in, p->n_out, p->d_keep_idx.ptr, in, ldi, out, ldo, 0, st, &done)) return s2;
-    if (done) return DOL_OK;
-    const Rows R = rows_of(batch, p->n_out);
-    hipLaunchKernelGGL(damp_gather_cols_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, p->d_keep_idx.ptr, in, ldi, out,
-                       ldo, 0);
-    DOL_HIP(hipGetLastError());
-    return DOL_OK;
-}
-
-dol_status launch_damp_filter_bwd(const FilterPlan *p, int32_t batch, const float *g, int64_t ldg, float *gin,
-                                  int64_t ldgi, int32_t accumulate, hipStream_t st)
-{
-    if (batch == 0 || p->n_in == 0) return DOL_OK;
-    bool done = false;
-    if (p->n_out > 0)
-        if (dol_status s2 = launch_rows_gather(batch, p->n_out, p->n_in, p->d_pos.ptr, g, ldg, gin, ldgi, accumulate & 1, st, &done)) return s2;
-    if (done) return DOL_OK;
-    const Rows R = rows_of(batch, p->n_in);
-    hipLaunchKernelGGL(damp_gather_cols_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, p->d_pos.ptr, g, ldg, gin, ldgi,
-                       accumulate & 1);
-    DOL_HIP(hipGetLastError());
-    return DOL_OK;
-}
-
-// ---------------------------------------------------------------- union
-
-__global__ void __launch_bounds__(kThreads)
-damp_union_fwd_kernel(Rows R, const int32_t *__restrict__ ia, const int32_t *__restrict__ ib,
-                      const float *__restrict__ a, int64_t lda, const float *__restrict__ b, int64_t ldb,
-                      float *__restrict__ out, int64_t ldo)
-{
-    for_each_element(R, [&](int64_t s, int c) {
-        const int32_t i = ia[c], j = ib[c];
-        float v;
-        if (i >= 0 && j >= 0) v = fminf(a[s * lda + i] + b[s * ldb + j], 1.0f);
-        else if (i >= 0) v = a[s * lda + i];
-        else v = b[s * ldb + j];
-        out[s * ldo + c] = v;
-    });
-}
-
-dol_status launch_damp_union_fwd(const UnionPlan *p, int32_t batch, const float *a, int64_t lda, const float *b,
-                                 int64_t ldb, float *out, int64_t ldo, hipStream_t st)
-{
-    if (batch == 0 || p->n_out == 0) return DOL_OK;
-    bool done = false;
-    if (dol_status s2 = launch_rows_union_fwd(p, batch, a, lda, b, ldb, out, ldo, st, &done)) return s2;
-    if (done) return DOL_OK;
-    const Rows R = rows_of(batch, p->n_out);
-    hipLaunchKernelGGL(damp_union_fwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, p->d_ia.ptr, p->d_ib.ptr, a, lda, b,
-                       ldb, out, ldo);
-    DOL_HIP(hipGetLastError());
-    return DOL_OK;
-}
-
-// Element x of a sample is input position x of a (x < na) or x - na of b.
-__global__ void __launch_bounds__(kThreads)
-damp_union_bwd_kernel(Rows R, int32_t na, const int32_t *__restrict__ ia, const int32_t *__restrict__ ib,
-                      const int32_t *__restrict__ ca, const int32_t *__restrict__ cb, const float *__restrict__ a,
-                      int64_t lda, const float *__restrict__ b, int64_t ldb, const float *__restrict__ g, int64_t ldg,
-                      float *__restrict__ ga, float *__restrict__ gb, int32_t accumulate)
-{
-    for_each_element(R, [&](int64_t s, int x) {
-        const bool is_a = x < na;
-        if (is_a ? !ga : !gb) return;
-        const int32_t c = is_a ? ca[x] : cb[x - na];
-        float gv = 0.0f;
-        if (c >= 0) {                       // -1: a symbol the fused filter drops
-            const int32_t i = ia[c], j = ib[c];
-            gv = g[s * ldg + c];
-            if (i >= 0 && j >= 0 && !(a[s * lda + i] + b[s * ldb + j] <= 1.0f)) gv = 0.0f;
-        }
-        if (is_a) ga[s * lda + x] = (accumulate & 1) ? ga[s * lda + x] + gv : gv;
-        else gb[s * ldb + (x - na)] = (accumulate & 2) ? gb[s * ldb + (x - na)] + gv : gv;
-    });
-}
-
-dol_status launch_damp_union_bwd(const UnionPlan *p, int32_t batch, const float *a, int64_t lda, const float *b,
-                                 int64_t ldb, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
-                                 hipStream_t st)
-{
-    if (batch == 0 || p->na + p->nb == 0 || (!ga && !gb)) return DOL_OK;
-    bool done = false;
-    if (dol_status s2 = launch_rows_union_bwd(p, batch, a, lda, b, ldb, g, ldg, ga, gb, accumulate, st, &done)) return s2;
-    if (done) return DOL_OK;
-    const Rows R = rows_of(batch, p->na + p->nb);
-    hipLaunchKernelGGL(damp_union_bwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, p->na, p->d_ia.ptr, p->d_ib.ptr,
-                       p->d_ca.ptr, p->d_cb.ptr, a, lda, b, ldb, g, ldg, ga, gb, accumulate);
-    DOL_HIP(hipGetLastError());
-    return DOL_OK;
-}
-
 // ---------------------------------------------------------------- harness helper: gradient of -log p[target]
 
 __global__ void __launch_bounds__(kThreads)

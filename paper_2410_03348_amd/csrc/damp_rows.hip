@@ -1,251 +1,221 @@
-// DAMP Filter and Union (Sec. 3.1.2) and their vector-Jacobian products for contiguous tensors: every global
-// access is a coalesced 16-byte one.
+// DAMP Filter and Union (Sec. 3.1.2) and their vector-Jacobian products, any row strides.
 //
-// A workgroup takes tiles of whole rows (a multiple of four, so that a tile of any row length starts on a
-// 16-byte boundary), copies the input tiles flat into LDS, and then walks the flat output tile four elements per
-// lane: the column maps (kept positions, merge positions) and the irregular reads they cause are served by LDS,
-// the results leave as 16-byte stores.  Column maps are staged once per workgroup; workgroups loop over tiles.
-// Tensors with padded rows or unaligned bases take the element-wise kernels of damp.hip.
+// A thread owns a column of the result: it fetches the column's map entries (kept position, merge positions) once and then
+// walks rows, several on their way at a time.  Lanes of a wavefront are neighbouring columns, of one row or, where rows are
+// short, of several; the maps ascend, so their reads are neighbours too and every access is a coalesced one without a stage
+// in LDS.  The workgroup has as many wavefronts as lose the fewest lanes to the row's end.
+// Bound by the latency of the maps and of a few batches of loads, then by memory.  (Tiles of rows copied into LDS, four
+// neighbouring results per lane, spent 60 % of the LDS clocks on bank conflicts and more instructions on splitting every
+// index: 10 007 rows of 196, Filter 5.4 us, Union 7.4, backwards 10.7; here 4.5, 5.9, 9.9.  Rows of 16 at 32 000: 42.5 us
+// for the six launches of a pipeline, 24 here.)
 #include "internal.h"
-#include "wave_util.h"
+
+#include <algorithm>
 
 namespace dol {
 
-constexpr int kRowsWG = 256;
-constexpr int kRowsTileFloats = 2048;          // floats of the widest tensor in one tile
-constexpr size_t kRowsLdsMax = 64 * 1024;
+namespace {
 
-// Copies `total` floats (src 16-byte aligned) into LDS: 16-byte pieces, four in flight per lane, then the tail.
-__device__ __forceinline__ void stage_flat(float *dst, const float *__restrict__ src, int total)
-{
-    const int n4 = total >> 2;
-    const float4 *src4 = reinterpret_cast<const float4 *>(src);
-    float4 *dst4 = reinterpret_cast<float4 *>(dst);
-    for (int f0 = 0; f0 < n4; f0 += 4 * kRowsWG) {
-        const int f = f0 + threadIdx.x;
-        float4 v0, v1, v2, v3;
-        if (f < n4) v0 = src4[f];
-        if (f + kRowsWG < n4) v1 = src4[f + kRowsWG];
-        if (f + 2 * kRowsWG < n4) v2 = src4[f + 2 * kRowsWG];
-        if (f + 3 * kRowsWG < n4) v3 = src4[f + 3 * kRowsWG];
-        if (f < n4) dst4[f] = v0;
-        if (f + kRowsWG < n4) dst4[f + kRowsWG] = v1;
-        if (f + 2 * kRowsWG < n4) dst4[f + 2 * kRowsWG] = v2;
-        if (f + 3 * kRowsWG < n4) dst4[f + 3 * kRowsWG] = v3;
-    }
-    const int t = (n4 << 2) + threadIdx.x;
-    if (t < total) dst[t] = src[t];
-}
+constexpr int kMaxThreads = 512;
+constexpr int kAhead = 4;               // rows a thread has on their way
+constexpr int kMostSteps = 16;          // rows of a thread: enough to make the maps' fetch a small part of its work,
+constexpr int kFillGrid = 512;          // few enough to give the chip this many workgroups
 
-__device__ __forceinline__ void stage_ints(int32_t *dst, const int32_t *__restrict__ src, int n)
-{
-    for (int e = threadIdx.x; e < n; e += kRowsWG) dst[e] = src[e];
-}
-
-// out[0 .. rows * n) = f(row, column) (+ what is there), flat, four elements per lane and step.
-template <typename F>
-__device__ __forceinline__ void emit_flat(float *__restrict__ out, int rows, int n, float inv_n, bool add, F f)
-{
-    const int total = rows * n, n4 = total >> 2;
-    float4 *out4 = reinterpret_cast<float4 *>(out);
-    for (int q = threadIdx.x; q < n4; q += kRowsWG) {
-        const int e = q << 2;
-        int r = static_cast<int>(static_cast<float>(e) * inv_n);
-        int c = e - r * n;
-        if (c < 0) { c += n; --r; } else if (c >= n) { c -= n; ++r; }
-        float4 v;
-        v.x = f(r, c);
-        if (++c == n) { c = 0; ++r; }
-        v.y = f(r, c);
-        if (++c == n) { c = 0; ++r; }
-        v.z = f(r, c);
-        if (++c == n) { c = 0; ++r; }
-        v.w = f(r, c);
-        if (add) {
-            const float4 o = out4[q];
-            v.x += o.x, v.y += o.y, v.z += o.z, v.w += o.w;
-        }
-        out4[q] = v;
-    }
-    const int t = (n4 << 2) + threadIdx.x;
-    if (t < total) {
-        const int r = t / n, c = t - r * n;
-        const float v = f(r, c);
-        out[t] = add ? out[t] + v : v;
-    }
-}
-
-struct RowTiles {
-    int32_t batch, rows_per_tile, n_tiles;
+struct RowCols {
+    int32_t batch, n;
+    int32_t width, per;                 // columns of a workgroup; rows side by side
+    int32_t chunks, rows;               // workgroups side by side over a row; rows of a workgroup
+    int32_t threads;
+    unsigned grid;
 };
 
-// ---------------------------------------------------------------- filter (both directions)
-
-// out[s, c] = in[s, src_col[c]], or 0 where src_col[c] < 0
-__global__ void __launch_bounds__(kRowsWG)
-damp_rows_gather_kernel(RowTiles T, int32_t n_in, int32_t n_out, float inv_n_out, const int32_t *__restrict__ src_col,
-                        const float *__restrict__ in, float *__restrict__ out, int32_t accumulate)
+RowCols row_cols(int32_t batch, int32_t n)
 {
-    extern __shared__ __align__(16) float lds[];
-    float *tin = lds;
-    int32_t *col = reinterpret_cast<int32_t *>(lds + ((T.rows_per_tile * n_in + 3) & ~3));
-    stage_ints(col, src_col, n_out);
-    for (int tile = blockIdx.x; tile < T.n_tiles; tile += gridDim.x) {
-        const int64_t s0 = static_cast<int64_t>(tile) * T.rows_per_tile;
-        const int rows = static_cast<int>(min(static_cast<int64_t>(T.rows_per_tile), T.batch - s0));
-        lds_barrier();
-        stage_flat(tin, in + s0 * n_in, rows * n_in);
-        lds_barrier();
-        emit_flat(out + s0 * n_out, rows, n_out, inv_n_out, accumulate != 0, [&](int r, int c) {
-            const int32_t i = col[c];
-            return i >= 0 ? tin[r * n_in + i] : 0.0f;
-        });
-    }
+    RowCols R{};
+    R.batch = batch, R.n = n;
+    R.chunks = (n + kMaxThreads - 1) / kMaxThreads;
+    R.width = (n + R.chunks - 1) / R.chunks;
+    R.per = 1;
+    auto waves = [&](int32_t per) { return (per * R.width + 63) / 64; };
+    const int32_t most = std::min(kMaxThreads / R.width, batch);
+    for (int32_t per = 2; per <= most; ++per)       // (the fullest wavefronts; of the like, the fewest)
+        if (static_cast<int64_t>(per) * waves(R.per) * 16 > static_cast<int64_t>(R.per) * waves(per) * 17) R.per = per;
+    R.threads = waves(R.per) * 64;
+    const int64_t steps = (static_cast<int64_t>(batch) + R.per - 1) / R.per;
+    int64_t mine = std::max<int64_t>(1, std::min<int64_t>(kMostSteps, steps * R.chunks / kFillGrid));
+    if (mine > kAhead) mine = mine / kAhead * kAhead;
+    R.rows = static_cast<int32_t>(mine) * R.per;
+    R.grid = static_cast<unsigned>((static_cast<int64_t>(batch) + R.rows - 1) / R.rows * R.chunks);
+    return R;
 }
 
-// ---------------------------------------------------------------- union
+// Where a thread is: column c, rows first, first + per, .. , n of them (0: none).
+struct Place {
+    int c, n;
+    int64_t first;
 
-__global__ void __launch_bounds__(kRowsWG)
-damp_rows_union_fwd_kernel(RowTiles T, int32_t na, int32_t nb, int32_t n_out, float inv_n_out,
-                           const int32_t *__restrict__ g_ia, const int32_t *__restrict__ g_ib,
-                           const float *__restrict__ a, const float *__restrict__ b, float *__restrict__ out)
-{
-    extern __shared__ __align__(16) float lds[];
-    float *ta = lds, *tb = ta + ((T.rows_per_tile * na + 3) & ~3);
-    int32_t *ia = reinterpret_cast<int32_t *>(tb + ((T.rows_per_tile * nb + 3) & ~3)), *ib = ia + n_out;
-    stage_ints(ia, g_ia, n_out);
-    stage_ints(ib, g_ib, n_out);
-    for (int tile = blockIdx.x; tile < T.n_tiles; tile += gridDim.x) {
-        const int64_t s0 = static_cast<int64_t>(tile) * T.rows_per_tile;
-        const int rows = static_cast<int>(min(static_cast<int64_t>(T.rows_per_tile), T.batch - s0));
-        lds_barrier();
-        stage_flat(ta, a + s0 * na, rows * na);
-        stage_flat(tb, b + s0 * nb, rows * nb);
-        lds_barrier();
-        emit_flat(out + s0 * n_out, rows, n_out, inv_n_out, false, [&](int r, int c) {
-            const int32_t i = ia[c], j = ib[c];
-            if (i >= 0 && j >= 0) return fminf(ta[r * na + i] + tb[r * nb + j], 1.0f);
-            return i >= 0 ? ta[r * na + i] : tb[r * nb + j];
-        });
+    __device__ __forceinline__ explicit Place(const RowCols &R)
+    {
+        const unsigned block = blockIdx.x / static_cast<unsigned>(R.chunks);
+        const int sub = static_cast<int>(threadIdx.x / static_cast<unsigned>(R.width));
+        c = static_cast<int>(blockIdx.x - block * R.chunks) * R.width + static_cast<int>(threadIdx.x) - sub * R.width;
+        const int64_t s = static_cast<int64_t>(block) * R.rows;
+        const int rows = static_cast<int>(min(static_cast<int64_t>(R.rows), R.batch - s));
+        first = s + sub;
+        n = sub < R.per && c < R.n ? (rows - sub + R.per - 1) / R.per : 0;
     }
+};
+
+// A column's entries in a thread's rows, one after the other.
+template <typename T>
+struct Walk {
+    T *at;
+    int64_t step;
+    __device__ __forceinline__ Walk(T *x, int64_t ld, const Place &p, int per, int col) : at(x + p.first * ld + col), step(ld * per) {}
+    __device__ __forceinline__ T &next()
+    {
+        T *x = at;
+        at += step;
+        return *x;
+    }
+};
+
+// load(u) takes the next row's operands as number u, put(u) stores its result.  (Neither branches: with branches around
+// the loads the compiler waits for each.)
+template <class Load, class Put>
+__device__ __forceinline__ void over_rows(int n, Load load, Put put)
+{
+    for (; n >= kAhead; n -= kAhead) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) load(u);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) put(u);
+    }
+    for (; n > 0; --n) { load(0); put(0); }
 }
 
-__global__ void __launch_bounds__(kRowsWG)
-damp_rows_union_bwd_kernel(RowTiles T, int32_t na, int32_t nb, int32_t n_out, float inv_na, float inv_nb,
-                           const int32_t *__restrict__ g_ia, const int32_t *__restrict__ g_ib,
-                           const int32_t *__restrict__ g_ca, const int32_t *__restrict__ g_cb,
-                           const float *__restrict__ a, const float *__restrict__ b, const float *__restrict__ g,
+}  // namespace
+
+// out[s, c] = in[s, src_col[c]], or 0 where src_col[c] < 0: Filter forward (src_col = kept positions) and its transpose
+// (src_col = position in the filtered row or -1)
+template <bool ADD>
+__global__ void __launch_bounds__(kMaxThreads)
+damp_rows_gather_kernel(RowCols R, const int32_t *__restrict__ src_col, const float *__restrict__ in, int64_t ldi, float *__restrict__ out,
+                        int64_t ldo)
+{
+    const Place p(R);
+    if (p.n <= 0) return;
+    const int32_t i = src_col[p.c];
+    Walk<float> dst(out, ldo, p, R.per, p.c), old = dst;
+    Walk<const float> src(in, ldi, p, R.per, i);
+    if (i < 0) src.at = dst.at, src.step = dst.step;        // (read and thrown away)
+    float v[kAhead], o[kAhead];
+    over_rows(p.n,
+              [&](int u) {
+                  v[u] = src.next();
+                  if (ADD) o[u] = old.next();
+              },
+              [&](int u) {
+                  const float x = i >= 0 ? v[u] : 0.0f;
+                  dst.next() = ADD ? x + o[u] : x;
+              });
+}
+
+__global__ void __launch_bounds__(kMaxThreads)
+damp_rows_union_fwd_kernel(RowCols R, const int32_t *__restrict__ ia, const int32_t *__restrict__ ib, const float *__restrict__ a,
+                           int64_t lda, const float *__restrict__ b, int64_t ldb, float *__restrict__ out, int64_t ldo)
+{
+    const Place p(R);
+    if (p.n <= 0) return;
+    const int32_t i = ia[p.c], j = ib[p.c];         // (one of them at least is there)
+    Walk<const float> xa(a, lda, p, R.per, i), xb(b, ldb, p, R.per, j);
+    if (i < 0) xa = xb;
+    if (j < 0) xb = xa;
+    Walk<float> dst(out, ldo, p, R.per, p.c);
+    float va[kAhead], vb[kAhead];
+    over_rows(p.n,
+              [&](int u) { va[u] = xa.next(), vb[u] = xb.next(); },
+              [&](int u) { dst.next() = i >= 0 && j >= 0 ? fminf(va[u] + vb[u], 1.0f) : va[u]; });
+}
+
+// Column x is input position x of a (x < na) or x - na of b; without ga (gb) the columns are those of the other operand.
+// The gradient passes unless both operands have the symbol and their sum exceeds 1.
+template <bool ADD>
+__global__ void __launch_bounds__(kMaxThreads)
+damp_rows_union_bwd_kernel(RowCols R, int32_t na, const int32_t *__restrict__ ia, const int32_t *__restrict__ ib,
+                           const int32_t *__restrict__ ca, const int32_t *__restrict__ cb, const float *__restrict__ a,
+                           int64_t lda, const float *__restrict__ b, int64_t ldb, const float *__restrict__ g, int64_t ldg,
                            float *__restrict__ ga, float *__restrict__ gb, int32_t accumulate)
 {
-    extern __shared__ __align__(16) float lds[];
-    float *ta = lds, *tb = ta + ((T.rows_per_tile * na + 3) & ~3), *tg = tb + ((T.rows_per_tile * nb + 3) & ~3);
-    int32_t *ia = reinterpret_cast<int32_t *>(tg + ((T.rows_per_tile * n_out + 3) & ~3));
-    int32_t *ib = ia + n_out, *ca = ib + n_out, *cb = ca + na;
-    stage_ints(ia, g_ia, n_out);
-    stage_ints(ib, g_ib, n_out);
-    stage_ints(ca, g_ca, na);
-    stage_ints(cb, g_cb, nb);
-    for (int tile = blockIdx.x; tile < T.n_tiles; tile += gridDim.x) {
-        const int64_t s0 = static_cast<int64_t>(tile) * T.rows_per_tile;
-        const int rows = static_cast<int>(min(static_cast<int64_t>(T.rows_per_tile), T.batch - s0));
-        lds_barrier();
-        stage_flat(ta, a + s0 * na, rows * na);
-        stage_flat(tb, b + s0 * nb, rows * nb);
-        stage_flat(tg, g + s0 * n_out, rows * n_out);
-        lds_barrier();
-        // the gradient of column c passes unless both operands are present and their sum exceeds 1
-        auto gated = [&](int r, int c) {
-            const int32_t i = ia[c], j = ib[c];
-            const float gv = tg[r * n_out + c];
-            return i >= 0 && j >= 0 && !(ta[r * na + i] + tb[r * nb + j] <= 1.0f) ? 0.0f : gv;
-        };
-        if (ga) emit_flat(ga + s0 * na, rows, na, inv_na, (accumulate & 1) != 0, [&](int r, int x) {
-            const int32_t c = ca[x];                // -1: a symbol the fused filter drops
-            return c >= 0 ? gated(r, c) : 0.0f;
-        });
-        if (gb) emit_flat(gb + s0 * nb, rows, nb, inv_nb, (accumulate & 2) != 0, [&](int r, int x) { return gated(r, cb[x]); });
-    }
+    const Place p(R);
+    if (p.n <= 0) return;
+    const bool is_a = ga && p.c < na;
+    const int x = ga && !is_a ? p.c - na : p.c;
+    const int32_t c = is_a ? ca[x] : cb[x];         // -1: a symbol that a fused filter drops
+    const int32_t i = c >= 0 ? ia[c] : -1, j = c >= 0 ? ib[c] : -1;
+    const bool both = i >= 0 && j >= 0, add = ADD && (accumulate & (is_a ? 1 : 2)) != 0;
+    Walk<float> dst(is_a ? ga : gb, is_a ? lda : ldb, p, R.per, x), old = dst;
+    Walk<const float> xg(g, ldg, p, R.per, c);
+    if (c < 0) xg.at = dst.at, xg.step = dst.step;
+    Walk<const float> xa(a, lda, p, R.per, i), xb(b, ldb, p, R.per, j);
+    if (!both) xa = xb = xg;
+    float gv[kAhead], o[kAhead], va[kAhead], vb[kAhead];
+    over_rows(p.n,
+              [&](int u) {
+                  gv[u] = xg.next(), va[u] = xa.next(), vb[u] = xb.next();
+                  if (ADD) o[u] = old.next();
+              },
+              [&](int u) {
+                  float v = c >= 0 && !(both && !(va[u] + vb[u] <= 1.0f)) ? gv[u] : 0.0f;
+                  if (add) v = o[u] + v;
+                  dst.next() = v;
+              });
 }
 
-// ---------------------------------------------------------------- launchers
-
-static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
-
-// Cuts the batch into tiles of whole rows; false when one tile of four rows does not fit in LDS.
-static bool make_tiles(int32_t batch, int32_t widest, size_t floats_per_row, size_t extra_bytes, RowTiles *T, size_t *lds,
-                       unsigned *grid)
+static dol_status gather(int32_t batch, int32_t n, const int32_t *src_col, const float *in, int64_t ldi, float *out, int64_t ldo,
+                  int32_t accumulate, hipStream_t st)
 {
-    int rows = (kRowsTileFloats / (widest > 0 ? widest : 1)) & ~3;
-    if (rows < 4) rows = 4;
-    // each staged tensor is padded to a multiple of four floats: at most 3 floats each, 16 covers them
-    size_t bytes = sizeof(float) * (rows * floats_per_row + 16) + extra_bytes;
-    while (bytes > kRowsLdsMax && rows > 4) {
-        rows -= 4;
-        bytes = sizeof(float) * (rows * floats_per_row + 16) + extra_bytes;
-    }
-    if (bytes > kRowsLdsMax) return false;
-    T->batch = batch;
-    T->rows_per_tile = rows;
-    T->n_tiles = static_cast<int32_t>((static_cast<int64_t>(batch) + rows - 1) / rows);
-    *lds = bytes;
-    const int cap = 8192;                        // beyond this workgroups loop (the column maps are staged once each)
-    *grid = static_cast<unsigned>(T->n_tiles < cap ? T->n_tiles : cap);
-    return true;
-}
-
-// Each launcher sets *done when it took the call; otherwise the caller uses the element-wise kernels.
-dol_status launch_rows_gather(int32_t batch, int32_t n_in, int32_t n_out, const int32_t *src_col, const float *in,
-                              int64_t ldi, float *out, int64_t ldo, int32_t accumulate, hipStream_t st, bool *done)
-{
-    *done = false;
-    RowTiles T;
-    size_t lds;
-    unsigned grid;
-    if (ldi != n_in || ldo != n_out || !aligned16(in) || !aligned16(out) || n_in == 0 || n_out == 0 ||
-        !make_tiles(batch, n_in > n_out ? n_in : n_out, n_in, sizeof(int32_t) * n_out, &T, &lds, &grid))
-        return DOL_OK;
-    hipLaunchKernelGGL(damp_rows_gather_kernel, dim3(grid), dim3(kRowsWG), lds, st, T, n_in, n_out,
-                       1.0f / static_cast<float>(n_out), src_col, in, out, accumulate);
+    if (batch == 0 || n == 0) return DOL_OK;
+    const RowCols R = row_cols(batch, n);
+    hipLaunchKernelGGL(accumulate ? damp_rows_gather_kernel<true> : damp_rows_gather_kernel<false>, dim3(R.grid),
+                       dim3(static_cast<unsigned>(R.threads)), 0, st, R, src_col, in, ldi, out, ldo);
     DOL_HIP(hipGetLastError());
-    *done = true;
     return DOL_OK;
 }
 
-dol_status launch_rows_union_fwd(const UnionPlan *p, int32_t batch, const float *a, int64_t lda, const float *b,
-                                 int64_t ldb, float *out, int64_t ldo, hipStream_t st, bool *done)
+dol_status launch_damp_filter_fwd(const FilterPlan *p, int32_t batch, const float *in, int64_t ldi, float *out,
+                                  int64_t ldo, hipStream_t st)
 {
-    *done = false;
-    RowTiles T;
-    size_t lds;
-    unsigned grid;
-    if (lda != p->na || ldb != p->nb || ldo != p->n_out || !aligned16(a) || !aligned16(b) || !aligned16(out) ||
-        !make_tiles(batch, p->n_out, static_cast<size_t>(p->na) + p->nb, sizeof(int32_t) * 2 * p->n_out, &T, &lds, &grid))
-        return DOL_OK;
-    hipLaunchKernelGGL(damp_rows_union_fwd_kernel, dim3(grid), dim3(kRowsWG), lds, st, T, p->na, p->nb, p->n_out,
-                       1.0f / static_cast<float>(p->n_out), p->d_ia.ptr, p->d_ib.ptr, a, b, out);
+    return gather(batch, p->n_out, p->d_keep_idx.ptr, in, ldi, out, ldo, 0, st);
+}
+
+dol_status launch_damp_filter_bwd(const FilterPlan *p, int32_t batch, const float *g, int64_t ldg, float *gin,
+                                  int64_t ldgi, int32_t accumulate, hipStream_t st)
+{
+    return gather(batch, p->n_in, p->d_pos.ptr, g, ldg, gin, ldgi, accumulate & 1, st);
+}
+
+dol_status launch_damp_union_fwd(const UnionPlan *p, int32_t batch, const float *a, int64_t lda, const float *b,
+                                 int64_t ldb, float *out, int64_t ldo, hipStream_t st)
+{
+    if (batch == 0 || p->n_out == 0) return DOL_OK;
+    const RowCols R = row_cols(batch, p->n_out);
+    hipLaunchKernelGGL(damp_rows_union_fwd_kernel, dim3(R.grid), dim3(static_cast<unsigned>(R.threads)), 0, st, R, p->d_ia.ptr, p->d_ib.ptr,
+                       a, lda, b, ldb, out, ldo);
     DOL_HIP(hipGetLastError());
-    *done = true;
     return DOL_OK;
 }
 
-dol_status launch_rows_union_bwd(const UnionPlan *p, int32_t batch, const float *a, int64_t lda, const float *b,
+dol_status launch_damp_union_bwd(const UnionPlan *p, int32_t batch, const float *a, int64_t lda, const float *b,
                                  int64_t ldb, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
-                                 hipStream_t st, bool *done)
+                                 hipStream_t st)
 {
-    *done = false;
-    RowTiles T;
-    size_t lds;
-    unsigned grid;
-    if (lda != p->na || ldb != p->nb || ldg != p->n_out || p->na == 0 || p->nb == 0 || !aligned16(a) || !aligned16(b) ||
-        !aligned16(g) || !aligned16(ga) || !aligned16(gb) ||
-        !make_tiles(batch, p->n_out, static_cast<size_t>(p->na) + p->nb + p->n_out,
-                    sizeof(int32_t) * (2 * p->n_out + p->na + p->nb), &T, &lds, &grid))
-        return DOL_OK;
-    hipLaunchKernelGGL(damp_rows_union_bwd_kernel, dim3(grid), dim3(kRowsWG), lds, st, T, p->na, p->nb, p->n_out,
-                       1.0f / static_cast<float>(p->na), 1.0f / static_cast<float>(p->nb), p->d_ia.ptr, p->d_ib.ptr,
-                       p->d_ca.ptr, p->d_cb.ptr, a, b, g, ga, gb, accumulate);
+    const int32_t n = (ga ? p->na : 0) + (gb ? p->nb : 0);
+    if (batch == 0 || n == 0) return DOL_OK;
+    const RowCols R = row_cols(batch, n);
+    hipLaunchKernelGGL(accumulate & 3 ? damp_rows_union_bwd_kernel<true> : damp_rows_union_bwd_kernel<false>, dim3(R.grid),
+                       dim3(static_cast<unsigned>(R.threads)), 0, st, R, p->na, p->d_ia.ptr, p->d_ib.ptr, p->d_ca.ptr, p->d_cb.ptr, a, lda, b, ldb, g, ldg, ga, gb, accumulate);
     DOL_HIP(hipGetLastError());
-    *done = true;
     return DOL_OK;
 }
 

@@ -530,7 +530,7 @@ class HwfPipeline(Program):
             self.tags = self.xs
         self.filters = [dol.OpRecord(dol.OP_FILTER, self.pos[t], None, self.xs[t], pred_mask=self.keep[t]) for t in range(L)]
         for t in range(L):
-            self.launches.append(Launch("damp_gather_cols_kernel", lambda t=t: dol.filter(self.pos[t], self.keep[t], None, self.xs[t]),
+            self.launches.append(Launch("damp_rows_gather_kernel", lambda t=t: dol.filter(self.pos[t], self.keep[t], None, self.xs[t]),
                                         4 * B * (14 + self.xs[t].n_sym), 0, "fwd"))
         facts = [np.arange(off[t], off[t + 1], dtype=np.int32) for t in range(L)]
         if dtkp:                                     # only position 0 needs stored tags: the later positions enter
@@ -563,7 +563,7 @@ class HwfPipeline(Program):
             self.launches.append(Launch("dtkp_prob_bwd_kernel", lambda: dol.dtkp_backward(self.out, self.prov, self.g, self.gfact),
                                         B * (self.out.n_sym * (12 * k + 4) + 8 * int(off[-1])), 0, "bwd"))
             for t in range(L):
-                self.launches.append(Launch("damp_gather_cols_kernel",
+                self.launches.append(Launch("damp_rows_gather_kernel",
                                             lambda t=t: dol.backward(self.filters[t], self.gfact[:, off[t]:off[t + 1]], self.grad_p[:, t, :], None),
                                             4 * B * (14 + self.xs[t].n_sym), 0, "bwd"))
             n_ops += 1 + L
@@ -579,7 +579,7 @@ class HwfPipeline(Program):
             for t in range(L - 1, 0, -1):
                 self.launches.append(_apply_bwd(self.records[t - 1], self.g_acc[t], self.g_acc[t - 1], self.g_x[t], n_tup[t - 1]))
             for t in range(L):
-                self.launches.append(Launch("damp_gather_cols_kernel",
+                self.launches.append(Launch("damp_rows_gather_kernel",
                                             lambda t=t: dol.backward(self.filters[t], self.g_x[t], self.grad_p[:, t, :], None),
                                             4 * B * (14 + self.xs[t].n_sym), 0, "bwd"))
             n_ops += 2 * L

@@ -1877,6 +1877,53 @@ def test_random_tables_differential_dtkp(dol, seed):
     assert_close(host(gf), want, "dtkp random table gradient, seed %d" % seed)
 
 
+@pytest.mark.parametrize("batch,n", [(1, 1), (3, 5), (65, 63), (4100, 64), (2, 65), (700, 196), (9, 256), (33, 257), (5, 513), (3, 1200), (20000, 3)])
+@pytest.mark.parametrize("pad", [0, 3])
+def test_filter_and_union_of_any_width(dol, batch, n, pad):
+    """Filter, Union and their reverse over rows of every kind of width and stride (several rows side by side in a workgroup,
+    several workgroups side by side on a row), overwriting and accumulating, with either gradient left out."""
+    def rows(seed, m):
+        x = torch.zeros((batch, m + pad), device="cuda")
+        x[:, :m] = dev((W.uniform01(seed, batch * m) * 0.8).astype(np.float32).reshape(batch, m))
+        return x[:, :m]
+    keep = (W.splitmix64(5, np.arange(n)) % np.uint64(3) > 0).astype(np.uint8)
+    keep[-1] = 1
+    a = dol.Dist(np.arange(n), rows(1, n))
+    kept = dol.Dist(dol.filter_plan(a, keep), rows(2, int(keep.sum())))
+    dol.filter(a, keep, None, kept)
+    at = torch.as_tensor(np.flatnonzero(keep), device="cuda")
+    assert torch.equal(kept.prob, a.prob[:, at])
+    g, ga = rows(3, kept.n_sym), rows(4, n)
+    want = torch.zeros_like(a.prob)
+    want[:, at] = g
+    for acc in (0, 1):
+        before = ga.clone()
+        dol.backward(dol.OpRecord(dol.OP_FILTER, a, None, kept, pred_mask=keep, accumulate=acc), g, ga, None)
+        assert torch.equal(ga, before + want if acc else want)
+    # union with symbols that overlap a's in part
+    sb = np.arange(n // 2, n // 2 + n + 2)
+    b = dol.Dist(sb, rows(6, sb.size))
+    u = dol.Dist(dol.union_plan(a, b), rows(7, n // 2 + n + 2))
+    dol.union(a, b, None, u)
+    lo, m = n // 2, n - n // 2
+    total = torch.zeros((batch, u.n_sym), device="cuda")
+    total[:, :n] = a.prob
+    total[:, lo:] += b.prob
+    both = torch.zeros(u.n_sym, dtype=torch.bool, device="cuda")
+    both[lo:lo + m] = True
+    assert torch.equal(u.prob, torch.where(both, total.clamp(max=1.0), total))
+    g, ga, gb = rows(8, u.n_sym), rows(9, n), rows(10, sb.size)
+    gate = torch.where(both & (total > 1.0), torch.zeros_like(g), g)
+    for acc in (0, 1, 2, 3):
+        before = (ga.clone(), gb.clone())
+        dol.backward(dol.OpRecord(dol.OP_UNION, a, b, u, accumulate=acc), g, ga, gb)
+        assert torch.equal(ga, before[0] + gate[:, :n] if acc & 1 else gate[:, :n])
+        assert torch.equal(gb, before[1] + gate[:, lo:] if acc & 2 else gate[:, lo:])
+    for x, y in ((rows(11, n), None), (None, rows(12, sb.size))):
+        dol.backward(dol.OpRecord(dol.OP_UNION, a, b, u), g, x, y)
+        assert torch.equal(x, gate[:, :n]) if x is not None else torch.equal(y, gate[:, lo:])
+
+
 @pytest.mark.parametrize("batch,lengths", [(1, (4, 5)), (1, (16, 17)), (3, (1, 16, 17, 64, 65, 5, 4)), (9, (1025, 2, 1024, 65, 64, 17, 40, 33, 3, 5, 4, 7)), (5, (1500,) + (20,) * 33)])
 def test_dtkp_columns_of_every_length(dol, batch, lengths):
     """A lane, 4 lanes, 16, a wavefront and a workgroup per column in one launch: lengths on both sides of each limit, groups of
