@@ -279,9 +279,11 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
         }
     }
     o("  fence();\n");
-    // ---- can any sum of this wavefront's samples exceed 1?  max(acc_t) <= max(acc_0) * product of the sums of the short rows
-    // so far, and what rounding adds is far below the distance to 1 that is asked for.  Where none can, and no tag is
-    // negative, the sweeps below run without a clamp, a sign or a gate: 280 of the 2 900 vector instructions of Sum-15.
+    // ---- can any sum of this wavefront's samples exceed 1?  max(acc_t) <= max(acc_0) * product of the sums of the first t
+    // short rows.  A later row with a small sum must not make up for an earlier one with a large sum: with every factor taken
+    // as at least 1 the product over all rows bounds that over any first few.  What rounding adds is far below the distance to
+    // 1 that is asked for.  Where no sum can exceed 1, and no tag is negative, the sweeps below run without a clamp, a sign
+    // or a gate: 280 of the 2 900 vector instructions of Sum-15.
     o("  bool calm;\n  { float top = 0.0f, prod = 1.0f; int bad = 0;\n");
     for (int x = 0; x < Y.m[0]; x += kL)
         o("    if (l + %d < %d) { const float v = base[%d + l]; top = fmaxf(top, v); bad |= !(v >= 0.0f); }\n", x, Y.m[0], Y.off[0] + x);
@@ -297,11 +299,11 @@ std::string chain_source(const std::vector<int> &shape, int kL, bool regs)
         }
         for (int j = 0; j < nb_max; ++j)
             o("      { const float v = row[%d]; %s{ sum += v; bad |= !(v >= 0.0f); } }\n", j, same ? "" : (std::string("if (") + std::to_string(j) + " < len) ").c_str());
-        o("      prod *= sum; }\n");
+        o("      prod *= fmaxf(sum, 1.0f); }\n");
     }
     for (int st = 0; st < 4; ++st) o("    top = fmaxf(top, dppx(top, %d)); prod *= dppx(prod, %d);\n", st, st);
     if (kL == 32) o("    top = fmaxf(top, __shfl_xor(top, 16)); prod *= __shfl_xor(prod, 16);\n");
-    o("    calm = __ballot(bad || !(top * fmaxf(prod, 1.0f) <= 0.999f)) == 0; }\n");
+    o("    calm = __ballot(bad || !(top * prod <= 0.999f)) == 0; }\n");
     auto sweeps = [&](bool calm) {
     auto tag = [&](const std::string &x) { return calm ? x : "__builtin_fabsf(" + x + ")"; };
     // ---- a lane's own block of every running Distribution stays in registers for the reverse sweep (sign = clamp decision)

@@ -166,6 +166,80 @@ def test_fused_fold_with_clamping_and_explicit_gradient(dol, B, widths):
     assert ei.value.status == 5
 
 
+def _row_of_mass(key, B, width, mass):
+    """[B, width] tags in [0, 1] whose rows sum to about mass[s] (as far as tags of at most 1 allow)."""
+    p = W.uniform01(key, B * width).reshape(B, width).astype(np.float64) + 0.05
+    p = p / p.sum(axis=1, keepdims=True) * mass[:, None]
+    return np.minimum(p, 1.0).astype(np.float32)
+
+
+@pytest.mark.parametrize("loss", ["target", "grad_out"])
+@pytest.mark.parametrize("n", [2, 3, 15])
+@pytest.mark.parametrize("B", [77, 6203])
+def test_fused_fold_with_masses_on_either_side_of_one(dol, B, n, loss):
+    """Operands that Union left above mass 1 and Filter below it: a later operand of small mass, or of none at all, does not
+    undo an earlier stage's clamp.  Neighbouring samples share a pattern of masses four at a time (calm: normalised;
+    an overflow made up for later; a row of zeros first, in the middle or last), and in every fifth four the patterns are
+    mixed.  The larger batch takes the kernel's form with the history in registers."""
+    patterns = {0: np.ones(n), 1: np.ones(n), 2: np.ones(n), 3: np.ones(n), 4: np.ones(n), 5: np.full(n, 1.3)}
+    patterns[1][0], patterns[1][1:] = 1.8, np.where(np.arange(1, n) % 2 == 1, 1.6, 0.4)
+    patterns[2][1:], patterns[2][1] = 0.9, 0.0
+    patterns[3][0], patterns[3][1:], patterns[3][n // 2] = 1.8, 1.5, 0.0
+    patterns[4][0], patterns[4][1:], patterns[4][n - 1] = 1.8, 1.5, 0.0
+    s = np.arange(B)
+    which = np.where((s // 4) % 5 == 4, s % 6, (s // 4) % 6)
+    mass = np.stack([patterns[k] for k in range(6)])[which]
+    ins = [_row_of_mass(30 + t, B, 10, mass[:, t]) for t in range(n)]
+    first = which == 1                                    # the largest tags where the sums have to be clamped
+    ins[0][first] = 0.0
+    ins[0][first, :2] = 0.9
+    if n <= 3:
+        ins[1][first] = 0.0
+        ins[1][first, :2] = 0.8
+    if n == 3:
+        ins[2][first] = 0.0
+        ins[2][first, :2] = np.array([0.3, 0.2], np.float32)
+    syms = np.arange(10, dtype=np.int32)
+    tabs, tris, accs, cur, kept = [], [], [ins[0]], syms, np.ones(B, bool)
+    for t in range(1, n):
+        tab = W.sum_table(cur, syms)
+        tri = oracle.dense_to_triples(tab)
+        cur, o, _, pre = oracle.damp_apply2_fwd(tri, tab.shape[0], tab.shape[1], accs[-1], ins[t], want_pre=True)
+        tabs.append(tab); tris.append(tri); accs.append(o)
+        # a stage's ten float32 multiply-adds err by at most 10 x 6e-8 of a sum, 15 stages by 1e-5: closer to 1 the oracle's
+        # running sums and the kernel's may lie on different sides of it
+        kept &= (np.abs(pre - 1.0) > 1e-5).all(axis=1)
+    assert kept.mean() > 0.9
+    at_one = np.stack([(o == 1.0).any(axis=1) for o in accs[1:]]).any(axis=0)
+    small = ins[0].max(axis=1) * np.maximum(np.prod([x.sum(axis=1) for x in ins[1:]], axis=0), 1.0) <= 0.999
+    whole = np.add.reduceat(np.where(small, 1, 0), np.arange(0, B, 4)) == np.minimum(4, B - np.arange(0, B, 4))
+    if n > 2:                                             # clamps that the product of all masses does not show, in whole fours
+        assert (at_one & small & np.repeat(whole, 4)[:B]).any()
+    assert (~at_one).any() and at_one.any()
+    out = dol.Dist.empty(cur, B)
+    gins = [torch.full((B, 10), 7.0, device="cuda") for _ in range(n)]
+    d_in = [dol.Dist(syms, dev(x)) for x in ins]
+    ftabs = [dol.FnTable.create_dense(t) for t in tabs]
+    if loss == "target":
+        target = np.argmax(accs[-1] - 0.01 * W.uniform01(3, accs[-1].size).reshape(accs[-1].shape), axis=1).astype(np.int32)
+        target[accs[-1].max(axis=1) < 1e-3] = -1          # (nothing to be likely: no gradient)
+        g = np.zeros((B, cur.size), np.float32)
+        ok = target >= 0
+        g[ok, target[ok]] = np.float32(-1.0) / accs[-1][ok, target[ok]].astype(np.float32)
+        dol.fold_apply2(dol.Fold(d_in, ftabs, out=out, target_col=dev(target), grad_inputs=gins))
+    else:
+        g = np.abs(W.normal(5, B * cur.size)).astype(np.float32).reshape(B, -1)
+        dol.fold_apply2(dol.Fold(d_in, ftabs, out=out, grad_out=dev(g), grad_inputs=gins))
+    want, gr = [None] * n, g
+    for t in range(n - 1, 0, -1):
+        gr, want[t] = oracle.damp_apply2_bwd(tris[t - 1], tabs[t - 1].shape[0], tabs[t - 1].shape[1], accs[t - 1], ins[t], gr)
+    want[0] = gr
+    assert_close(host(out.prob)[kept], accs[-1][kept], "fold forward")
+    np.testing.assert_array_equal(host(out.prob)[kept] == 1.0, accs[-1][kept] == 1.0)
+    for t in range(n):
+        assert_close(host(gins[t])[kept], want[t][kept], "fold grad %d" % t)
+
+
 # ---------------------------------------------------------------- config 3
 
 @pytest.mark.parametrize("batch,na,nb,n_out", [(16384, 64, 64, 256), (1000, 64, 64, 256), (129, 17, 33, 40), (3, 5, 2, 300)])
