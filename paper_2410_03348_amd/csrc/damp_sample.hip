@@ -579,7 +579,7 @@ struct SampleMerge {
 // further words.
 template <bool FWD, bool BWD>
 __global__ void __launch_bounds__(512)
-damp_merge_sample_kernel(const SampleMerge A)
+damp_merge_sample_kernel(SampleMerge A)
 {
     extern __shared__ __align__(16) float lds[];            // [a][b][0], sums of the Apply, c's row, gated gradient and 0
     const int n = A.na + A.nb;
@@ -820,6 +820,18 @@ bool table_small_batch(const dol_fn_table *f, int64_t batch)
     return batch <= 3072 && f->lists_ok && f->col_lists.longer.n == 0 && f->row_lists.longer.n == 0;
 }
 
+// What damp_merge_sample_kernel keeps in LDS: besides the table's rows the whole second Distribution, of up to 65 535 symbols.
+static size_t merge_bytes(const dol_fn_table *f, const UnionPlan *p)
+{
+    return sizeof(float) * (static_cast<size_t>((f->na + f->nb + 4) & ~3) + f->n_out + p->nb + f->n_out + 1);
+}
+
+// (what does not fit is left to the tiles, which read the second Distribution from memory)
+bool merge_small_batch(const dol_fn_table *f, const UnionPlan *p, int64_t batch)
+{
+    return table_small_batch(f, batch) && merge_bytes(f, p) <= kStageMaxBytes;
+}
+
 dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b, const float *c,
                                float *out, int32_t *saved, const float *g, float *ga, float *gb, float *gc, int32_t accumulate, hipStream_t st)
 {
@@ -828,13 +840,17 @@ dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_
     A.cols = lists_of(f->col_lists), A.rows = lists_of(f->row_lists);
     A.ia = p->d_ia.ptr, A.ib = p->d_ib.ptr, A.ca = p->d_ca.ptr, A.cb = p->d_cb.ptr;
     A.a = a, A.b = b, A.c = c, A.g = g, A.out = out, A.ga = ga, A.gb = gb, A.gc = gc, A.saved = saved;
-    const size_t lds = sizeof(float) * (static_cast<size_t>((f->na + f->nb + 4) & ~3) + f->n_out + p->nb + f->n_out + 1);
+    const size_t lds = merge_bytes(f, p);
     const dim3 grid(static_cast<unsigned>(batch)), block(threads_for(std::max(std::max(f->n_out, f->na + f->nb), p->n_out / 2), 512));
-    if (out && g) hipLaunchKernelGGL((damp_merge_sample_kernel<true, true>), grid, block, lds, st, A);
-    else if (out) hipLaunchKernelGGL((damp_merge_sample_kernel<true, false>), grid, block, lds, st, A);
-    else hipLaunchKernelGGL((damp_merge_sample_kernel<false, true>), grid, block, lds, st, A);
-    DOL_HIP(hipGetLastError());
-    return DOL_OK;
+    auto launch = [&](void (*kernel)(SampleMerge)) -> dol_status {
+        if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kStageMaxBytes));
+        hipLaunchKernelGGL(kernel, grid, block, lds, st, A);
+        DOL_HIP(hipGetLastError());
+        return DOL_OK;
+    };
+    if (out && g) return launch(damp_merge_sample_kernel<true, true>);
+    if (out) return launch(damp_merge_sample_kernel<true, false>);
+    return launch(damp_merge_sample_kernel<false, true>);
 }
 
 }  // namespace dol

@@ -651,7 +651,7 @@ bool table_merge_ok(const dol_fn_table *f) { return table_code_ok(f) && f->n_out
 dol_status launch_damp_table_merge_fwd(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b,
                                        const float *c, float *out, int32_t *saved, hipStream_t st)
 {
-    if (table_small_batch(f, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, nullptr, nullptr, nullptr, nullptr, 0, st);
+    if (merge_small_batch(f, p, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, nullptr, nullptr, nullptr, nullptr, 0, st);
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeFwdAligned : kSlotMergeFwd, build_for(batch), &fn)) return s;
     const JitBuild bd = build_for(batch);
@@ -666,7 +666,7 @@ dol_status launch_damp_table_merge_bwd(const dol_fn_table *f, const UnionPlan *p
                                        const float *c, const float *g, float *ga, float *gb, float *gc, const int32_t *saved,
                                        int32_t accumulate, hipStream_t st)
 {
-    if (table_small_batch(f, batch)) return launch_sample_merge(f, p, batch, a, b, c, nullptr, const_cast<int32_t *>(saved), g, ga, gb, gc, accumulate, st);
+    if (merge_small_batch(f, p, batch)) return launch_sample_merge(f, p, batch, a, b, c, nullptr, const_cast<int32_t *>(saved), g, ga, gb, gc, accumulate, st);
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBwdAligned : kSlotMergeBwd, build_for(batch), &fn)) return s;
     const JitBuild bd = build_for(batch);
@@ -681,7 +681,7 @@ dol_status launch_damp_table_merge_both(const dol_fn_table *f, const UnionPlan *
                                         const float *c, float *out, int32_t *saved, const float *g, float *ga, float *gb, float *gc,
                                         int32_t accumulate, hipStream_t st)
 {
-    if (table_small_batch(f, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, g, ga, gb, gc, accumulate, st);
+    if (merge_small_batch(f, p, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, g, ga, gb, gc, accumulate, st);
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBothAligned : kSlotMergeBoth, build_for(batch), &fn)) return s;
     const JitBuild bd = build_for(batch);

@@ -333,6 +333,7 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
 // The same for tables that damp_table.hip generates code for, at batches too small for its tiles; the merged calls take
 // out == nullptr (backward only) or g == nullptr (forward only).
 bool table_small_batch(const dol_fn_table *f, int64_t batch);
+bool merge_small_batch(const dol_fn_table *f, const UnionPlan *p, int64_t batch);
 dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b, const float *c,
                                float *out, int32_t *saved, const float *g, float *ga, float *gb, float *gc, int32_t accumulate, hipStream_t st);
 // Small arbitrary tables as code written for the table (damp_table.hip); *done = false: the call was not taken

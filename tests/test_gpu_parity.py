@@ -344,6 +344,44 @@ def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, n
         assert n_out == 512 or host(prog.saved).any()
 
 
+@pytest.mark.parametrize("nc", [16000, 40348, 40352, 60000])
+def test_merged_calls_with_a_wide_second_distribution(dol, nc):
+    """The second Distribution has far more symbols than the table produces: rows of more than 64 KB, the widest that a
+    workgroup's LDS holds beside the table's rows (158 KB), the next wider one and one far beyond, at a small batch."""
+    B, na, nb, n_out = 5, 16, 12, 32
+    ids, keep = W.hashed_table(3, na, nb, n_out), W.keep_mask(4, n_out)
+    keep[:8] = [1, 0] * 4
+    tri = oracle.dense_to_triples(ids)
+    pa, pb, pc = ((W.uniform01(k, B * n) * 0.5).astype(np.float32).reshape(B, n) for k, n in ((1, na), (2, nb), (5, nc)))
+    s1, o1 = oracle.damp_apply2_fwd(tri, na, nb, pa, pb)
+    assert s1.size == n_out
+    s2, _ = oracle.filter_plan(s1, keep)
+    o2 = oracle.damp_filter_fwd(keep, o1)
+    sc = np.arange(nc, dtype=np.int32) + 8                 # (the table's first symbols are not among them)
+    s3, ia, ib = oracle.union_plan(s2, sc)
+    assert s3.size == nc + 4
+    o3 = oracle.damp_union_fwd(ia, ib, o2, pc)
+    g = np.abs(W.normal(6, B * s3.size)).astype(np.float32).reshape(B, -1)
+    g2, gc = oracle.damp_union_bwd(ia, ib, o2, pc, g)
+    ga, gb = oracle.damp_apply2_bwd(tri, na, nb, pa, pb, oracle.damp_filter_bwd(keep, g2))
+    f = dol.FnTable.create_dense(ids)
+    a, b, c = dol.Dist(np.arange(na), dev(pa)), dol.Dist(np.arange(nb), dev(pb)), dol.Dist(sc, dev(pc))
+    out = dol.Dist.empty(s3, B)
+    grads = [torch.empty((B, n), device="cuda") for n in (na, nb, nc)]
+    m = dol.ApplyMerge(a, b, f, keep, c, out, torch.empty(B, dtype=torch.int32, device="cuda"))
+    for one in (False, True):
+        for t in [out.prob] + grads:
+            t.fill_(-3.0)
+        if one:
+            dol.apply2_filter_union_forward_backward(m, dev(g), *grads)
+        else:
+            dol.apply2_filter_union(m)
+            dol.apply2_filter_union_backward(m, dev(g), *grads)
+        np.testing.assert_array_equal(host(out.prob) == 1.0, o3 == 1.0)
+        for got, want in zip([out.prob] + grads, (o3, ga, gb, gc)):
+            assert_close(host(got), want, "merged with %d symbols, one launch %s" % (nc, one))
+
+
 @pytest.mark.parametrize("batch,scale", [(16384, 1.0), (16421, 6.0), (12301, 6.0), (333, 12.0), (64, 1.0), (1, 1.0)])
 def test_config3_forward_and_backward_in_one_launch(gp, dol, batch, scale):
     """dol_apply2_filter_union_forward_backward: the results of the two separate calls, bit for bit (clamp words included),
