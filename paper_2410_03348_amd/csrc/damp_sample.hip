@@ -599,7 +599,7 @@ damp_merge_sample_kernel(SampleMerge A)
         int over = 0;
         walk_lists<4>(A.cols, 0, col_chunks, first_cols,
                       [&](uint32_t t, float acc) { return __builtin_fmaf(rows[t & 0xffffu], rows[A.na + (t >> 16)], acc); },
-                      [&](int c, float v) { pre[c] = v; over |= v > 1.0f; });
+                      [&](int c, float v) { pre[c] = v; over |= !(v <= 1.0f); });
         __syncthreads();
         if (FWD) {
             for (int u = tid; u < A.n3; u += T) {

@@ -382,6 +382,53 @@ def test_merged_calls_with_a_wide_second_distribution(dol, nc):
             assert_close(host(got), want, "merged with %d symbols, one launch %s" % (nc, one))
 
 
+@pytest.mark.parametrize("batch", [40, 3072, 3073])
+def test_merged_calls_treat_a_nan_as_the_operators_do(dol, batch):
+    """A tag that is no number: the merged calls clamp, mark and gate what dol_apply2 followed by dol_filter_union does, in the
+    form for small batches and in the tiles."""
+    na, nb, n = 16, 8, 64
+    ids, keep = W.hashed_table(23, na, nb, n), np.ones(n, np.uint8)
+    ids.reshape(-1)[:n] = np.arange(n)                     # (every symbol is produced; columns of one to some tuples)
+    ids[na - 1] = np.arange(nb)                            # (a's last symbol: only what c does not have)
+    keep[::4] = 0
+    x = [(W.uniform01(k, batch * m) * 0.4).astype(np.float32).reshape(batch, m) for k, m in ((1, na), (2, nb), (3, n))]
+    for where, (arr, col) in enumerate(((0, 0), (0, na - 1), (1, nb - 1), (2, 7), (2, 40))):
+        x[arr][where::16, col] = np.nan                    # (most samples have none)
+    f = dol.FnTable.create_dense(ids)
+    a, b, c = dol.Dist(np.arange(na), dev(x[0])), dol.Dist(np.arange(nb), dev(x[1])), dol.Dist(np.arange(n) + n // 2, dev(x[2]))
+    made = dol.Dist.empty(f.out_syms, batch)
+    out = dol.Dist.empty(dol.filter_union_plan(made, keep, c), batch)
+    g = np.abs(W.normal(6, batch * out.n_sym)).astype(np.float32).reshape(batch, -1)
+    want = [torch.empty((batch, m), device="cuda") for m in (na, nb, n)]
+    g_made = torch.empty((batch, n), device="cuda")
+    dol.apply2(a, b, f, None, made)
+    dol.filter_union(made, keep, c, None, out)
+    dol.backward(dol.OpRecord(dol.OP_FILTER_UNION, made, c, out, pred_mask=keep), dev(g), g_made, want[2])
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, a, b, made, f=f), g_made, want[0], want[1])
+    want, want_out = [host(t) for t in want], host(out.prob)
+    assert np.isnan(want[0]).any() and np.isnan(want[1]).any() and np.isnan(want_out).any()
+    clean = ~np.stack([np.isnan(t).any(axis=1) for t in x]).any(axis=0)
+    assert 0 < clean.sum() < batch and not any(np.isnan(t[clean]).any() for t in want)
+    lone = dol.Dist.empty(out.sym_ids, batch)
+    got = [torch.empty((batch, m), device="cuda") for m in (na, nb, n)]
+    saved = torch.empty(batch, dtype=torch.int32, device="cuda")
+    for one in (False, True):
+        m = dol.ApplyMerge(a, b, f, keep, c, lone, saved)
+        for t in [lone.prob] + got:
+            t.fill_(-3.0)
+        if one:
+            dol.apply2_filter_union_forward_backward(m, dev(g), *got)
+        else:
+            dol.apply2_filter_union(m)
+            dol.apply2_filter_union_backward(m, dev(g), *got)
+        np.testing.assert_array_equal(host(lone.prob), want_out)
+        assert (host(saved)[np.isnan(x[0]).any(axis=1) | np.isnan(x[1]).any(axis=1)] != 0).all()
+        for t, w in zip(got, want):
+            t = host(t)
+            np.testing.assert_array_equal(np.isnan(t), np.isnan(w))
+            assert_close(np.nan_to_num(t), np.nan_to_num(w), "merged with NaN, one launch %s" % one)
+
+
 @pytest.mark.parametrize("batch,scale", [(16384, 1.0), (16421, 6.0), (12301, 6.0), (333, 12.0), (64, 1.0), (1, 1.0)])
 def test_config3_forward_and_backward_in_one_launch(gp, dol, batch, scale):
     """dol_apply2_filter_union_forward_backward: the results of the two separate calls, bit for bit (clamp words included),
