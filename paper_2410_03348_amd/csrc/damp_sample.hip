@@ -581,9 +581,10 @@ template <bool FWD, bool BWD>
 __global__ void __launch_bounds__(512)
 damp_merge_sample_kernel(SampleMerge A)
 {
-    extern __shared__ __align__(16) float lds[];            // [a][b][0], sums of the Apply, c's row, gated gradient and 0
+    extern __shared__ __align__(16) float lds[];            // [a][b][0], [a][0], sums of the Apply, c's row, gated gradient and 0
     const int n = A.na + A.nb;
-    float *rows = lds, *pre = rows + ((n + 4) & ~3), *cr = pre + A.S, *gh = cr + A.nc;
+    // (a again, with a 0 behind it, for the columns: their lists' filling must not multiply a tag, which may be no number)
+    float *rows = lds, *ar = rows + n + 1, *pre = lds + ((n + A.na + 5) & ~3), *cr = pre + A.S, *gh = cr + A.nc;
     const int64_t s = blockIdx.x;
     const int T = blockDim.x, tid = threadIdx.x, wave = wave_number();
     const int col_chunks = (A.S + kWave - 1) / kWave, row_chunks = (n + kWave - 1) / kWave;
@@ -591,14 +592,18 @@ damp_merge_sample_kernel(SampleMerge A)
     Chunk<8> first_rows{};
     if (BWD) first_rows = read_chunk<8>(A.rows, min(wave, row_chunks - 1));
     int acted = BWD && !FWD && A.saved ? A.saved[s] : 1;
-    for (int e = tid; e < n; e += T) rows[e] = e < A.na ? A.a[s * A.na + e] : A.b[s * A.nb + (e - A.na)];
+    for (int e = tid; e < n; e += T) {
+        const float v = e < A.na ? A.a[s * A.na + e] : A.b[s * A.nb + (e - A.na)];
+        rows[e] = v;
+        if (e < A.na) ar[e] = v;
+    }
     for (int e = tid; e < A.nc; e += T) cr[e] = A.c[s * A.nc + e];
-    if (tid == 0) { rows[n] = 0.0f; if (BWD) gh[A.S] = 0.0f; }
+    if (tid == 0) { rows[n] = ar[A.na] = 0.0f; if (BWD) gh[A.S] = 0.0f; }
     __syncthreads();
     if (FWD || acted) {                     // (the same for the whole workgroup)
         int over = 0;
         walk_lists<4>(A.cols, 0, col_chunks, first_cols,
-                      [&](uint32_t t, float acc) { return __builtin_fmaf(rows[t & 0xffffu], rows[A.na + (t >> 16)], acc); },
+                      [&](uint32_t t, float acc) { return __builtin_fmaf(ar[t & 0xffffu], rows[A.na + (t >> 16)], acc); },
                       [&](int c, float v) { pre[c] = v; over |= !(v <= 1.0f); });
         __syncthreads();
         if (FWD) {
@@ -823,7 +828,7 @@ bool table_small_batch(const dol_fn_table *f, int64_t batch)
 // What damp_merge_sample_kernel keeps in LDS: besides the table's rows the whole second Distribution, of up to 65 535 symbols.
 static size_t merge_bytes(const dol_fn_table *f, const UnionPlan *p)
 {
-    return sizeof(float) * (static_cast<size_t>((f->na + f->nb + 4) & ~3) + f->n_out + p->nb + f->n_out + 1);
+    return sizeof(float) * (static_cast<size_t>((2 * f->na + f->nb + 5) & ~3) + f->n_out + p->nb + f->n_out + 1);
 }
 
 // (what does not fit is left to the tiles, which read the second Distribution from memory)

@@ -344,7 +344,7 @@ def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, n
         assert n_out == 512 or host(prog.saved).any()
 
 
-@pytest.mark.parametrize("nc", [16000, 40348, 40352, 60000])
+@pytest.mark.parametrize("nc", [16000, 40332, 40336, 60000])
 def test_merged_calls_with_a_wide_second_distribution(dol, nc):
     """The second Distribution has far more symbols than the table produces: rows of more than 64 KB, the widest that a
     workgroup's LDS holds beside the table's rows (158 KB), the next wider one and one far beyond, at a small batch."""
@@ -385,14 +385,14 @@ def test_merged_calls_with_a_wide_second_distribution(dol, nc):
 @pytest.mark.parametrize("batch", [40, 3072, 3073])
 def test_merged_calls_treat_a_nan_as_the_operators_do(dol, batch):
     """A tag that is no number: the merged calls clamp, mark and gate what dol_apply2 followed by dol_filter_union does, in the
-    form for small batches and in the tiles."""
+    form for small batches and in the tiles, and a NaN of one symbol reaches no column that has no tuple with it."""
     na, nb, n = 16, 8, 64
     ids, keep = W.hashed_table(23, na, nb, n), np.ones(n, np.uint8)
     ids.reshape(-1)[:n] = np.arange(n)                     # (every symbol is produced; columns of one to some tuples)
     ids[na - 1] = np.arange(nb)                            # (a's last symbol: only what c does not have)
     keep[::4] = 0
     x = [(W.uniform01(k, batch * m) * 0.4).astype(np.float32).reshape(batch, m) for k, m in ((1, na), (2, nb), (3, n))]
-    for where, (arr, col) in enumerate(((0, 0), (0, na - 1), (1, nb - 1), (2, 7), (2, 40))):
+    for where, (arr, col) in enumerate(((0, 0), (0, na - 1), (1, 0), (1, nb - 1), (2, 7), (2, 40))):
         x[arr][where::16, col] = np.nan                    # (most samples have none)
     f = dol.FnTable.create_dense(ids)
     a, b, c = dol.Dist(np.arange(na), dev(x[0])), dol.Dist(np.arange(nb), dev(x[1])), dol.Dist(np.arange(n) + n // 2, dev(x[2]))
@@ -409,6 +409,9 @@ def test_merged_calls_treat_a_nan_as_the_operators_do(dol, batch):
     assert np.isnan(want[0]).any() and np.isnan(want[1]).any() and np.isnan(want_out).any()
     clean = ~np.stack([np.isnan(t).any(axis=1) for t in x]).any(axis=0)
     assert 0 < clean.sum() < batch and not any(np.isnan(t[clean]).any() for t in want)
+    has = np.zeros((n, nb), bool)                          # a NaN of b's first symbol clamps the columns it is in
+    has[ids.reshape(-1), np.tile(np.arange(nb), na)] = True
+    assert not has[:, 0].all()
     lone = dol.Dist.empty(out.sym_ids, batch)
     got = [torch.empty((batch, m), device="cuda") for m in (na, nb, n)]
     saved = torch.empty(batch, dtype=torch.int32, device="cuda")
