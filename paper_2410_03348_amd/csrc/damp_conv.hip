@@ -43,7 +43,7 @@ std::string damp_kernel_name(const dol_fn_table *f, bool backward, int64_t batch
         if (table_code_ok(f) && !(batch > 0 && table_small_batch(f, batch))) return backward ? "damp_table_bwd_kernel" : "damp_table_fwd_kernel";
         if (backward) {
             if (f->lds_bwd_ok && !lds_small_batch(f, batch, true)) return "damp_lds_bwd_kernel";
-            if (byj_bwd_sample_ok(f)) return byj_bwd_wide(f) ? "damp_byj_bwd_row_kernel" : "damp_byj_bwd_kernel";
+            if (byj_bwd_sample_ok(f)) return !byj_bwd_staged(f) ? "damp_byj_bwd_global_kernel" : byj_bwd_wide(f) ? "damp_byj_bwd_row_kernel" : "damp_byj_bwd_kernel";
             return list_bwd_sample_ok(f) ? "damp_apply2_bwd_staged_kernel" : "damp_apply2_bwd_kernel";
         }
         if (f->lds_fwd_ok && !lds_small_batch(f, batch, false)) return "damp_lds_fwd_kernel";

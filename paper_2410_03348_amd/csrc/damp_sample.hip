@@ -373,68 +373,106 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
 
 // gh[c] = g[c] where the clamp did not act, else 0, for the whole row, and a 0 behind it.  out < 1: it did not act;
 // out == 1 leaves pre == 1 (passes) and pre > 1 (blocks) apart only by pre itself, taken again in its defining order
-// (long columns: by a wavefront each, after the others).
-__device__ __forceinline__ void gated_row(const SampleBwd &A, int64_t s, float *gh, int *n_late, int *late)
+// (long columns: by a wavefront each, after the others).  STAGED: gh is filled with that row; else `closed` gets a bit per
+// column the clamp acted on, and the answer is whether there are any.
+template <bool STAGED>
+__device__ __forceinline__ bool gated_row(const SampleBwd &A, int64_t s, float *gh, uint32_t *closed, int *n_late, int *late)
 {
     const float *ar = A.a + s * A.lda, *br = A.b + s * A.ldb, *outr = A.out + s * A.ldo, *gr = A.g + s * A.ldg;
-    if (threadIdx.x == 0) { *n_late = 0; gh[A.S] = 0.0f; }
+    int any = 0;
+    auto close = [&](int c) {
+        if (STAGED) gh[c] = 0.0f;
+        else atomicOr(closed + (c >> 5), 1u << (c & 31));
+        any = 1;
+    };
+    if (threadIdx.x == 0) { *n_late = 0; if (STAGED) gh[A.S] = 0.0f; }
+    if (!STAGED)
+        for (int w = threadIdx.x; w < (A.S + 31) / 32; w += blockDim.x) closed[w] = 0u;
     __syncthreads();
     for (int c = 4 * static_cast<int>(threadIdx.x); c < A.S; c += 4 * static_cast<int>(blockDim.x)) {
         const int n = A.S - c;
-        const float4 o4 = load4(outr + c, n), g4 = load4(gr + c, n);
+        const float4 o4 = load4(outr + c, n);
         const float o[4] = {o4.x, o4.y, o4.z, o4.w};
-        float g[4] = {g4.x, g4.y, g4.z, g4.w};
+        if (STAGED) {
+            const float4 g4 = load4(gr + c, n);
+            const float g[4] = {g4.x, g4.y, g4.z, g4.w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k < n) gh[c + k] = g[k];
+        }
 #pragma unroll
         for (int k = 0; k < 4; ++k)
             if (o[k] >= 1.0f && k < n) {
                 const uint32_t q0 = A.col_ptr[c + k], q1 = A.col_ptr[c + k + 1];
                 const int slot = q1 - q0 > static_cast<uint32_t>(kLongTableCol) ? atomicAdd(n_late, 1) : kLateMax;
                 if (slot < kLateMax) late[slot] = c + k;
-                else if (!(column_sum(ar, br, A.col_ij, q0, q1) <= 1.0f)) g[k] = 0.0f;
+                else if (!(column_sum(ar, br, A.col_ij, q0, q1) <= 1.0f)) close(c + k);
             }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (k < n) gh[c + k] = g[k];
     }
     __syncthreads();
     const int wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave, n = min(*n_late, kLateMax);
     for (int l = wave; l < n; l += n_waves) {
         const int c = __builtin_amdgcn_readfirstlane(late[l]);
         const float pre = serial_sum(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1]);
-        if (!(pre <= 1.0f) && (threadIdx.x & (kWave - 1)) == 0) gh[c] = 0.0f;
+        if (!(pre <= 1.0f) && (threadIdx.x & (kWave - 1)) == 0) close(c);
     }
+    if (!STAGED) return __syncthreads_or(any) != 0;
     if (n) __syncthreads();
+    return false;
 }
 
 // Dense maps: a thread owns four neighbouring rows of a and adds their shares of gb up in registers; the workgroup's
-// shares meet at the end (so the long rows of b need no launch of their own).
-template <int NBP, int T>
-__device__ __forceinline__ void byj_bwd(const SampleBwd &A, float *gh)
+// shares meet at the end (so the long rows of b need no launch of their own).  STAGED: the gated gradient row is in LDS.
+// Result rows that do not fit there (more than 40 447 symbols) are gathered from memory, and from LDS a bit per column where
+// the clamp acted, if it acted anywhere in the sample: B=256, 41 000 x 4 -> 41 000 234 us, element by element with a look at
+// every column's clamp 2 335; all columns clamped 2 865 and 6 763.
+template <int NBP, int T, bool STAGED>
+__device__ __forceinline__ void byj_bwd(const SampleBwd &A, float *lds)
 {
     __shared__ float red[NBP][T / kWave];
     __shared__ int n_late, late[kLateMax];
     const int64_t s = blockIdx.x;
-    const float *ar = A.a + s * A.lda, *br = A.b + s * A.ldb;
-    gated_row(A, s, gh, &n_late, late);
+    const float *ar = A.a + s * A.lda, *br = A.b + s * A.ldb, *gr = A.g + s * A.ldg;
+    float *gh = lds;
+    uint32_t *closed = reinterpret_cast<uint32_t *>(lds);
+    const bool gates = gated_row<STAGED>(A, s, gh, closed, &n_late, late);
     float bj[NBP], pb[NBP];
 #pragma unroll
     for (int j = 0; j < NBP; ++j) {
         bj[j] = j < A.nb ? br[j] : 0.0f;
         pb[j] = 0.0f;
     }
-    for (int i = 4 * static_cast<int>(threadIdx.x); i < A.na; i += 4 * static_cast<int>(blockDim.x)) {
-        ushort4 m[NBP];
+    constexpr int R = STAGED || NBP < 10 ? 4 : 2;       // rows at a time (gathers from memory: as many as registers hold)
+    typedef uint16_t __attribute__((ext_vector_type(R))) entries;
+    const int last = A.S - 1;
+    for (int i = R * static_cast<int>(threadIdx.x); i < A.na; i += R * static_cast<int>(blockDim.x)) {
+        entries m[NBP];
 #pragma unroll
-        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + i);
-        const int n = A.na - i;
-        const float4 a4 = load4(ar + i, n);
+        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const entries *>(A.map + static_cast<size_t>(j) * A.map_ld + i);
+        const int n = min(R, A.na - i);
+        const float4 a4 = R == 4 ? load4(ar + i, n) : make_float4(ar[i], n > 1 ? ar[i + 1] : 0.0f, 0.0f, 0.0f);
         const float av[4] = {a4.x, a4.y, a4.z, a4.w};
         float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int j = 0; j < NBP; ++j) {
-            const float v[4] = {gh[m[j].x], gh[m[j].y], gh[m[j].z], gh[m[j].w]};
+            int col[R];
+            float v[R];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < R; ++k) col[k] = m[j][k];
+            if (STAGED) {
+#pragma unroll
+                for (int k = 0; k < R; ++k) v[k] = gh[col[k]];
+            } else {
+                uint32_t shut[R];
+#pragma unroll
+                for (int k = 0; k < R; ++k) shut[k] = gates ? closed[min(col[k], last) >> 5] >> (col[k] & 31) : 0u;
+#pragma unroll
+                for (int k = 0; k < R; ++k) v[k] = gr[min(col[k], last)];
+#pragma unroll
+                for (int k = 0; k < R; ++k) v[k] = col[k] > last || (shut[k] & 1u) ? 0.0f : v[k];
+            }
+#pragma unroll
+            for (int k = 0; k < R; ++k) {
                 acc[k] = __builtin_fmaf(v[k], bj[j], acc[k]);
                 pb[j] = __builtin_fmaf(v[k], av[k], pb[j]);
             }
@@ -442,10 +480,16 @@ __device__ __forceinline__ void byj_bwd(const SampleBwd &A, float *gh)
         if (A.ga) {
             float *dst = A.ga + s * A.lda + i;
             if (A.accumulate & 1) {
-                const float4 old = load4(dst, n);
-                acc[0] += old.x, acc[1] += old.y, acc[2] += old.z, acc[3] += old.w;
+#pragma unroll
+                for (int k = 0; k < R; ++k)
+                    if (k < n) acc[k] += dst[k];
             }
-            store4(dst, acc, n);
+            if (R == 4) store4(dst, acc, n);
+            else {
+#pragma unroll
+                for (int k = 0; k < R; ++k)
+                    if (k < n) dst[k] = acc[k];
+            }
         }
     }
     if (!A.gb) return;
@@ -469,7 +513,7 @@ __global__ void __launch_bounds__(kSmallThreads)
 damp_byj_bwd_kernel(const SampleBwd A)
 {
     extern __shared__ __align__(16) float lds[];
-    byj_bwd<NBP, kSmallThreads>(A, lds);
+    byj_bwd<NBP, kSmallThreads, true>(A, lds);
 }
 
 template <int NBP>
@@ -477,7 +521,15 @@ __global__ void __launch_bounds__(kSampleThreads)
 damp_byj_bwd_row_kernel(const SampleBwd A)
 {
     extern __shared__ __align__(16) float lds[];
-    byj_bwd<NBP, kSampleThreads>(A, lds);
+    byj_bwd<NBP, kSampleThreads, true>(A, lds);
+}
+
+template <int NBP>
+__global__ void __launch_bounds__(kSampleThreads)
+damp_byj_bwd_global_kernel(const SampleBwd A)
+{
+    extern __shared__ __align__(16) float lds[];
+    byj_bwd<NBP, kSampleThreads, false>(A, lds);
 }
 
 // Tuple lists: a lane owns a symbol of a or b (element x: symbol x of a, or x - na of b) and adds up its tuples from the
@@ -501,7 +553,7 @@ damp_apply2_bwd_staged_kernel(const SampleBwd A)
         for (int e = threadIdx.x; e < A.nb; e += blockDim.x) rows[A.na + e] = br[e];
         if (threadIdx.x == 0) rows[n] = 0.0f;
     }
-    gated_row(A, s, gh, &n_late, late);                     // (ends after a barrier)
+    gated_row<true>(A, s, gh, nullptr, &n_late, late);      // (ends after a barrier)
     // a list's word: the other operand's symbol, counted from a's first one (b's from na on; na + nb: none), and the column
     auto other = [&](uint32_t x) {
         if (ROWS) return rows[x];
@@ -703,7 +755,9 @@ bool byj_fwd_sample_ok(const dol_fn_table *f)
 
 bool list_fwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && list_fwd_bytes(f) <= kStageMaxBytes; }
 
-bool byj_bwd_sample_ok(const dol_fn_table *f) { return f->byj_ok && gated_bytes(f) <= kStageMaxBytes; }
+bool byj_bwd_sample_ok(const dol_fn_table *f) { return f->byj_ok; }
+
+bool byj_bwd_staged(const dol_fn_table *f) { return gated_bytes(f) <= kStageMaxBytes; }
 
 bool list_bwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && gated_bytes(f) <= kStageMaxBytes; }
 
@@ -782,7 +836,12 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
     if (byj) {
         A.map = f->byj_col.ptr, A.map_ld = f->byj_col_ld;
         const int64_t work = std::max(f->na, f->n_out) / 4 + 1;
-        if (byj_bwd_wide(f)) {
+        if (!byj_bwd_staged(f)) {
+            lds = sizeof(uint32_t) * static_cast<size_t>((f->n_out + 31) / 32);
+#define CALL(N) hipLaunchKernelGGL(damp_byj_bwd_global_kernel<N>, grid, dim3(threads_for(work, kSampleThreads)), lds, st, A)
+            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
+#undef CALL
+        } else if (byj_bwd_wide(f)) {
 #define CALL(N)                                                                                                                \
     {                                                                                                                          \
         if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_byj_bwd_row_kernel<N>), kStageMaxBytes));   \

@@ -325,6 +325,7 @@ bool byj_bwd_sample_ok(const dol_fn_table *f);
 bool list_bwd_sample_ok(const dol_fn_table *f);
 bool byj_fwd_wide(const dol_fn_table *f);
 bool byj_bwd_wide(const dol_fn_table *f);
+bool byj_bwd_staged(const dol_fn_table *f);
 dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb, float *out,
                              int64_t ldo, hipStream_t st, bool *done);
 dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,

@@ -1620,6 +1620,43 @@ def test_wide_operand_rows_staged_in_lds(dol, batch):
     assert np.all(host(ga3)[:, na:] == 5.0)
 
 
+@pytest.mark.parametrize("na,nb,n_out,clamped", [(20000, 10, 40449, 0.01), (20000, 10, 40450, 0.01), (45000, 3, 45001, 0.0), (41003, 4, 41002, 0.5), (60000, 16, 60000, 0.01)])
+def test_result_rows_wider_than_lds_backward(dol, na, nb, n_out, clamped):
+    """Gradients of a table with a short second operand whose result row is the widest that fits LDS, the next wider one, and
+    of up to 60 000 symbols: no column, some and many at the clamp, a long column among them."""
+    B = 2
+    i = np.repeat(np.arange(na, dtype=np.int64), nb)
+    j = np.tile(np.arange(nb), na)
+    o = (i * n_out // na + W.splitmix64(77, np.arange(i.size)).astype(np.int64) % 5) % n_out
+    o[np.argsort(W.splitmix64(78, np.arange(i.size)), kind="stable")[:n_out]] = np.arange(n_out)     # (every symbol is produced)
+    o[(i < 40) & (o != 7)] = 7                                # a long column
+    tri = tuple(x.astype(np.int32) for x in (i, j, o))
+    a = (W.uniform01(1, B * na) * 0.2).astype(np.float32).reshape(B, na)
+    if clamped:
+        a[:, ::max(1, int(1 / clamped))] = 1.0
+    b = (W.uniform01(2, B * nb) * 0.3 + 0.7).astype(np.float32).reshape(B, nb)
+    if not clamped:
+        a, b = a * np.float32(0.01), b * np.float32(0.01)
+    syms, want, pre32, pre64 = oracle.damp_apply2_fwd(tri, na, nb, a, b, want_pre=True)
+    assert ((pre32 > 1).mean() > clamped / 2) if clamped else not (pre32 > 1).any()
+    f = dol.FnTable.create_sparse(na, nb, *tri)
+    assert f.kernel_bwd == ("damp_byj_bwd_row_kernel" if syms.size <= 40447 else "damp_byj_bwd_global_kernel")
+    da, db = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b))
+    out = dol.Dist.empty(syms, B)
+    dol.apply2(da, db, f, None, out)
+    assert_close(host(out.prob), want, "forward")
+    np.testing.assert_array_equal(host(out.prob) == 1.0, pre32 >= 1.0)
+    g = (np.abs(W.normal(901, B * syms.size)) + 0.5).astype(np.float32).reshape(B, -1)
+    wa, wb = oracle.damp_apply2_bwd(tri, na, nb, a, b, g)
+    ga, gb = torch.empty_like(da.prob), torch.empty_like(db.prob)
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), dev(g), ga, gb)
+    assert_close(host(ga), wa, "backward a")
+    assert_close(host(gb), wb, "backward b")
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f, accumulate=3), dev(g), ga, gb)
+    assert_close(host(ga), 2.0 * wa.astype(np.float64), "backward a accumulated")
+    assert_close(host(gb), 2.0 * wb.astype(np.float64), "backward b accumulated")
+
+
 def test_apply_k_two_operands_equal_apply2_bit_for_bit(dol):
     B = 150
     table = W.hashed_table(41, 30, 20, 64)
