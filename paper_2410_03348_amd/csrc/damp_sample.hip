@@ -21,6 +21,7 @@ namespace dol {
 
 constexpr int kSmallThreads = 256;      // workgroups of the kernels over rows of fewer than kStageMinRow tags
 constexpr int kSampleThreads = 1024;
+constexpr int kUnits = 256;             // compute units
 
 constexpr int kLateMax = 64;            // long columns at the clamp that a workgroup re-derives a wavefront each
 
@@ -516,8 +517,9 @@ damp_byj_bwd_kernel(const SampleBwd A)
     byj_bwd<NBP, kSmallThreads, true>(A, lds);
 }
 
+// (at least six wavefronts to a SIMD where the maps of ten j leave 81 registers: two workgroups of twelve share a unit)
 template <int NBP>
-__global__ void __launch_bounds__(kSampleThreads)
+__global__ void __launch_bounds__(kSampleThreads, NBP == 10 ? 6 : 4)
 damp_byj_bwd_row_kernel(const SampleBwd A)
 {
     extern __shared__ __align__(16) float lds[];
@@ -714,6 +716,13 @@ static unsigned threads_for(int64_t work, int most)
     return static_cast<unsigned>(std::max<int64_t>(kWave, std::min<int64_t>(most, t)));
 }
 
+// The same for `work` steps that a workgroup takes `most` at a time, shared out evenly.
+static unsigned even_threads(int64_t work, int most)
+{
+    const int64_t turns = std::max<int64_t>(1, (work + most - 1) / most);
+    return threads_for((work + turns - 1) / turns, most);
+}
+
 static Lists lists_of(const ListPlan &p)
 {
     return Lists{p.order.ptr, p.ptr.ptr, p.words.ptr, p.longer.ptr, p.n_huge, p.n_wave, p.n_mid};
@@ -842,10 +851,12 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
             DOL_DISPATCH_NBP(f->byj_nbp, CALL)
 #undef CALL
         } else if (byj_bwd_wide(f)) {
+            const bool shared = batch > kUnits && 2 * (lds + 2048) <= 160 * 1024;
+            const int most = !shared || f->byj_nbp <= 4 ? kSampleThreads : f->byj_nbp <= 10 ? 768 : 512;
 #define CALL(N)                                                                                                                \
     {                                                                                                                          \
         if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_byj_bwd_row_kernel<N>), kStageMaxBytes));   \
-        hipLaunchKernelGGL(damp_byj_bwd_row_kernel<N>, grid, dim3(threads_for(work, kSampleThreads)), lds, st, A);             \
+        hipLaunchKernelGGL(damp_byj_bwd_row_kernel<N>, grid, dim3(even_threads(work, most)), lds, st, A);                      \
     }
             DOL_DISPATCH_NBP(f->byj_nbp, CALL)
 #undef CALL
