@@ -23,7 +23,7 @@ constexpr int kSmallThreads = 256;      // workgroups of the kernels over rows o
 constexpr int kSampleThreads = 1024;
 constexpr int kUnits = 256;             // compute units
 
-constexpr int kLateMax = 64;            // long columns at the clamp that a workgroup re-derives a wavefront each
+constexpr int kLateMax = 64;            // long columns at the clamp that a workgroup lists
 
 struct Lists {                          // struct ListPlan (internal.h) on the device
     const uint32_t *order, *ptr, *words, *longer;
@@ -105,6 +105,8 @@ __device__ __forceinline__ float serial_sum(const float *ar, const float *br, co
     return s;
 }
 
+__device__ __forceinline__ int wave_number() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave); }
+
 __device__ __forceinline__ float wave_sum(float x)
 {
     x = reduce32<AddOp>(x);
@@ -153,17 +155,6 @@ __device__ __forceinline__ float long_sum(const float *ar, const float *br, cons
     const float parallel = mag * (static_cast<float>((q1 - q0) / step + 40) * 1.1920929e-7f);
     const float serial = mag <= 2.0f ? 1.01f * err : mag * (static_cast<float>(q1 - q0) * 1.1920929e-7f);
     if (!(fabsf(acc - 1.0f) > parallel + serial)) acc = serial_sum(ar, br, ij_of, q0, q1);
-    return acc;
-}
-
-// The same over one thread's own list, in the defining order.
-__device__ __forceinline__ float column_sum(const float *ar, const float *br, const uint32_t *__restrict__ ij_of, uint32_t q0, uint32_t q1)
-{
-    float acc = 0.0f;
-    for (uint32_t q = q0; q < q1; ++q) {
-        const uint32_t ij = ij_of[q];
-        acc = __builtin_fmaf(ar[ij & 0xffffu], br[ij >> 16], acc);
-    }
     return acc;
 }
 
@@ -306,8 +297,6 @@ __device__ __forceinline__ Chunk<N> read_chunk(const Lists &L, int ch)
     return c;
 }
 
-__device__ __forceinline__ int wave_number() { return __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / kWave); }
-
 // Walks the chunks [ch0, ch1), a wavefront every blockDim.x / 64th: term(word, sum) takes a tuple into a list's sum, in list
 // order, and done(list, sum) is called for every list that is walked here.  `now`: this wavefront's first chunk.
 template <int N, typename T, typename D>
@@ -373,8 +362,10 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
 // ---------------------------------------------------------------- backward
 
 // gh[c] = g[c] where the clamp did not act, else 0, for the whole row, and a 0 behind it.  out < 1: it did not act;
-// out == 1 leaves pre == 1 (passes) and pre > 1 (blocks) apart only by pre itself, taken again in its defining order
-// (long columns: by a wavefront each, after the others).  STAGED: gh is filled with that row; else `closed` gets a bit per
+// out == 1 leaves pre == 1 (passes) and pre > 1 (blocks) apart only by pre itself, taken again: by the thread at hand, long
+// columns by a wavefront each after the others.  (45 000 x 10 -> 300, every column of 1 500 tuples clamped, B=256: 2.8 ms with
+// the columns beyond the list summed by the thread that met them, a tuple at a time, and the others in their order of
+// definition.)  STAGED: gh is filled with that row; else `closed` gets a bit per
 // column the clamp acted on, and the answer is whether there are any.
 template <bool STAGED>
 __device__ __forceinline__ bool gated_row(const SampleBwd &A, int64_t s, float *gh, uint32_t *closed, int *n_late, int *late)
@@ -390,32 +381,45 @@ __device__ __forceinline__ bool gated_row(const SampleBwd &A, int64_t s, float *
     if (!STAGED)
         for (int w = threadIdx.x; w < (A.S + 31) / 32; w += blockDim.x) closed[w] = 0u;
     __syncthreads();
-    for (int c = 4 * static_cast<int>(threadIdx.x); c < A.S; c += 4 * static_cast<int>(blockDim.x)) {
-        const int n = A.S - c;
-        const float4 o4 = load4(outr + c, n);
-        const float o[4] = {o4.x, o4.y, o4.z, o4.w};
-        if (STAGED) {
-            const float4 g4 = load4(gr + c, n);
-            const float g[4] = {g4.x, g4.y, g4.z, g4.w};
+    const int lane = threadIdx.x & (kWave - 1), wave = wave_number(), n_waves = blockDim.x / kWave;
+    for (int c0 = 4 * kWave * wave; c0 < A.S; c0 += 4 * kWave * n_waves) {
+        const int c = c0 + 4 * lane, n = A.S - c;
+        bool at_one = false;
+        if (n > 0) {
+            const float4 o4 = load4(outr + c, n);
+            at_one = o4.x >= 1.0f || o4.y >= 1.0f || o4.z >= 1.0f || o4.w >= 1.0f;
+            if (STAGED) {
+                const float4 g4 = load4(gr + c, n);
+                const float g[4] = {g4.x, g4.y, g4.z, g4.w};
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k < n) gh[c + k] = g[k];
-        }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (o[k] >= 1.0f && k < n) {
-                const uint32_t q0 = A.col_ptr[c + k], q1 = A.col_ptr[c + k + 1];
-                const int slot = q1 - q0 > static_cast<uint32_t>(kLongTableCol) ? atomicAdd(n_late, 1) : kLateMax;
-                if (slot < kLateMax) late[slot] = c + k;
-                else if (!(column_sum(ar, br, A.col_ij, q0, q1) <= 1.0f)) close(c + k);
+                for (int k = 0; k < 4; ++k)
+                    if (k < n) gh[c + k] = g[k];
             }
+        }
+        if (!__ballot(at_one)) continue;
+        for (int cc = c0 + lane; cc < min(A.S, c0 + 4 * kWave); cc += kWave) {      // (neighbouring lanes, neighbouring columns)
+            if (!(outr[cc] >= 1.0f)) continue;
+            const uint32_t q0 = A.col_ptr[cc], q1 = A.col_ptr[cc + 1];
+            if (q1 - q0 > static_cast<uint32_t>(kLongTableCol)) {
+                const int slot = atomicAdd(n_late, 1);
+                if (slot < kLateMax) late[slot] = cc;
+            } else if (!(column_sum(ar, br, A.col_ij, q0, q1) <= 1.0f)) close(cc);
+        }
     }
     __syncthreads();
-    const int wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave, n = min(*n_late, kLateMax);
-    for (int l = wave; l < n; l += n_waves) {
-        const int c = __builtin_amdgcn_readfirstlane(late[l]);
-        const float pre = serial_sum(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1]);
-        if (!(pre <= 1.0f) && (threadIdx.x & (kWave - 1)) == 0) close(c);
+    const int n = *n_late;
+    auto decide = [&](int c) {              // by a whole wavefront
+        const float pre = long_sum<false>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], nullptr);
+        if (!(pre <= 1.0f) && lane == 0) close(c);
+    };
+    if (n <= kLateMax) {
+        for (int l = wave; l < n; l += n_waves) decide(__builtin_amdgcn_readfirstlane(late[l]));
+    } else {                                // more than the list holds: every wavefront looks through its share of the columns
+        for (int c0 = wave; c0 < A.S; c0 += kWave * n_waves) {
+            const int c = c0 + lane * n_waves;
+            const bool mine = c < A.S && outr[c] >= 1.0f && A.col_ptr[c + 1] - A.col_ptr[c] > static_cast<uint32_t>(kLongTableCol);
+            for (uint64_t todo = __ballot(mine); todo; todo &= todo - 1) decide(c0 + __builtin_ctzll(todo) * n_waves);
+        }
     }
     if (!STAGED) return __syncthreads_or(any) != 0;
     if (n) __syncthreads();

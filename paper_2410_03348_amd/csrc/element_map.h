@@ -62,6 +62,33 @@ __device__ __forceinline__ void for_each_element(const Rows &R, F f)
     }
 }
 
+// pre[c] = sum over the tuples of column c, ascending (i, j), one fma each.  This order is part of the
+// operator's contract: the backward pass re-derives the clamp decision [pre <= 1] from it.
+// The loads of kGather tuples are issued together (index words first, then the tags they name) so that a column
+// costs a few memory round trips rather than two per tuple; the adds keep their order.
+constexpr int kGather = 4;
+
+__device__ __forceinline__ float column_sum(const float *__restrict__ ar, const float *__restrict__ br,
+                                            const uint32_t *__restrict__ col_ij, uint32_t q0, uint32_t q1)
+{
+    float acc = 0.0f;
+    for (uint32_t q = q0; q < q1; q += kGather) {
+        uint32_t ij[kGather];
+        float x[kGather], y[kGather];
+#pragma unroll
+        for (int u = 0; u < kGather; ++u) ij[u] = col_ij[min(q + u, q1 - 1)];
+#pragma unroll
+        for (int u = 0; u < kGather; ++u) {
+            x[u] = ar[ij[u] & 0xffffu];
+            y[u] = br[ij[u] >> 16];
+        }
+#pragma unroll
+        for (int u = 0; u < kGather; ++u)
+            if (q + u < q1) acc = __builtin_fmaf(x[u], y[u], acc);
+    }
+    return acc;
+}
+
 // ---- operand rows staged whole in LDS: one workgroup of kStageThreads per (sample, part of the output row)
 //
 // A gather from a row of thousands of tags misses the first-level cache on nearly every lane; from LDS it costs a

@@ -1657,6 +1657,38 @@ def test_result_rows_wider_than_lds_backward(dol, na, nb, n_out, clamped):
     assert_close(host(gb), 2.0 * wb.astype(np.float64), "backward b accumulated")
 
 
+@pytest.mark.parametrize("nb", [10, 20])
+@pytest.mark.parametrize("n_out", [60, 64, 65, 200, 1700])
+def test_backward_with_many_long_columns_at_the_clamp(dol, nb, n_out):
+    """Columns of more than 64 tuples that sum to within a few roundings of 1, or well above it: as many as a workgroup lists,
+    one more, and more than a thousand; the decision is the sequential float sum's."""
+    B, per = 3, 4 if nb == 20 else 7
+    na = per * n_out
+    i = np.repeat(np.arange(na), nb).astype(np.int32)
+    j = np.tile(np.arange(nb), na).astype(np.int32)
+    o = (i % n_out).astype(np.int32)
+    w = W.uniform01(70 + nb, B * na).reshape(B, per, n_out) ** 3 + 1e-6
+    want_sum = 1.0 + 1e-7 * ((np.arange(n_out) * 7 + np.arange(B)[:, None] * 3) % 5 - 2)
+    want_sum[:, ::6] = 1.7
+    a = (w / w.sum(axis=1, keepdims=True) * want_sum[:, None, :] / nb).astype(np.float32).reshape(B, na)
+    b = np.ones((B, nb), np.float32)
+    tri = (i, j, o)
+    syms, want, pre32, _ = oracle.damp_apply2_fwd(tri, na, nb, a, b, want_pre=True)
+    assert (pre32 > 1.5).any() and ((pre32 > 1) & (pre32 < 1.1)).any() and (pre32 <= 1).any()
+    f = dol.FnTable.create_sparse(na, nb, *tri)
+    da, db = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b))
+    out = dol.Dist.empty(syms, B)
+    dol.apply2(da, db, f, None, out)
+    assert_close(host(out.prob), want, "forward")
+    np.testing.assert_array_equal(host(out.prob) == 1.0, pre32 >= 1.0)
+    g = (np.abs(W.normal(901, B * syms.size)) + 0.5).astype(np.float32).reshape(B, -1)
+    wa, wb = oracle.damp_apply2_bwd(tri, na, nb, a, b, g)
+    ga, gb = torch.empty_like(da.prob), torch.empty_like(db.prob)
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), dev(g), ga, gb)
+    assert_close(host(ga), wa, "backward a")
+    assert_close(host(gb), wb, "backward b")
+
+
 def test_apply_k_two_operands_equal_apply2_bit_for_bit(dol):
     B = 150
     table = W.hashed_table(41, 30, 20, 64)
