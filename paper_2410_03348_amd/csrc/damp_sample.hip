@@ -221,33 +221,45 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
 #pragma unroll
     for (int j = 0; j < NBP; ++j) y[j] = br[j < A.nb ? j : 0];      // (the maps' extra rows are empty)
     __syncthreads();
-    for (int c = c0 + 4 * static_cast<int>(threadIdx.x); c < c1; c += 4 * static_cast<int>(blockDim.x)) {
-        ushort4 m[NBP];
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int cw = c0 + 4 * kWave * wave_number(); cw < c1; cw += 4 * static_cast<int>(blockDim.x)) {
+        const int c = cw + 4 * lane;
+        uint32_t again = 0;                             // bit k: column c + k is taken from its tuple list
+        if (c < c1) {
+            ushort4 m[NBP];
 #pragma unroll
-        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + c);
-        uint16_t mark[4] = {m[0].x, m[0].y, m[0].z, m[0].w};
-        const uint16_t none = static_cast<uint16_t>(A.na);
-        m[0].x = min(m[0].x, none), m[0].y = min(m[0].y, none), m[0].z = min(m[0].z, none), m[0].w = min(m[0].w, none);
-        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, mag[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+            for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + c);
+            const uint16_t mark[4] = {m[0].x, m[0].y, m[0].z, m[0].w};
+            const uint16_t none = static_cast<uint16_t>(A.na);
+            m[0].x = min(m[0].x, none), m[0].y = min(m[0].y, none), m[0].z = min(m[0].z, none), m[0].w = min(m[0].w, none);
+            float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, mag[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int j = 0; j < NBP; ++j) {
-            const float x[4] = {ar[m[j].x], ar[m[j].y], ar[m[j].z], ar[m[j].w]};
+            for (int j = 0; j < NBP; ++j) {
+                const float x[4] = {ar[m[j].x], ar[m[j].y], ar[m[j].z], ar[m[j].w]};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    acc[k] = __builtin_fmaf(x[k], y[j], acc[k]);
+                    mag[k] = __builtin_fmaf(fabsf(x[k]), fabsf(y[j]), mag[k]);
+                }
+            }
+            uint32_t elsewhere = 0;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                acc[k] = __builtin_fmaf(x[k], y[j], acc[k]);
-                mag[k] = __builtin_fmaf(fabsf(x[k]), fabsf(y[j]), mag[k]);
+                const bool near = !(fabsf(acc[k] - 1.0f) > mag[k] * (static_cast<float>(NBP + 2) * 1.1920929e-7f));
+                if (mark[k] == kByJWave) elsewhere |= 1u << k;      // summed below
+                else if (near || mark[k] == kByJList) again |= 1u << k;     // (list: some j occurs twice)
+                acc[k] = fminf(acc[k], 1.0f);
             }
+            store4(out + c, acc, c1 - c, again | elsewhere);
         }
-        uint32_t skip = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const bool near = !(fabsf(acc[k] - 1.0f) > mag[k] * (static_cast<float>(NBP + 2) * 1.1920929e-7f));
-            if (mark[k] == kByJWave) skip |= 1u << k;               // summed below
-            else if ((near || mark[k] == kByJList) && c + k < c1)   // some j occurs twice: the tuple list itself
-                acc[k] = column_sum(ar, br, A.col_ij, A.col_ptr[c + k], A.col_ptr[c + k + 1]);
-            acc[k] = fminf(acc[k], 1.0f);
+        if (!__ballot(again != 0)) continue;
+        const uint64_t of[4] = {__ballot(again & 1u), __ballot(again & 2u), __ballot(again & 4u), __ballot(again & 8u)};
+        const uint64_t mine = lane & 2 ? (lane & 1 ? of[3] : of[2]) : (lane & 1 ? of[1] : of[0]);
+        for (int r = 0; r < 4; ++r) {                   // (neighbouring lanes, neighbouring columns)
+            const int cc = cw + kWave * r + lane;
+            if (cc < c1 && ((mine >> (16 * r + (lane >> 2))) & 1u))
+                out[cc] = fminf(column_sum(ar, br, A.col_ij, A.col_ptr[cc], A.col_ptr[cc + 1]), 1.0f);
         }
-        store4(out + c, acc, c1 - c, skip);
     }
     if (part == A.parts - 1)
         long_columns(A, ar, br, 0, A.S, scratch, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
