@@ -11,7 +11,8 @@
 //     that a map entry costs two bytes of an 8-byte load and results leave as 16-byte stores;
 //   * other tables: tuple lists of columns (rows) sorted by length inside blocks of 4 096 and interleaved in chunks of 64
 //     (struct ListPlan), so that a wavefront's tuples are one 256-byte load and its lanes end together; the forward results of a block meet in LDS and leave in column order.
-// Lists longer than 64 tuples are summed by a wavefront (rows: by 16 lanes), those above 512 by the workgroup, in the same launch.
+// Lists longer than 64 tuples are summed by 16 lanes, those above 512 by a wavefront or the workgroup (struct ListPlan), in the
+// same launch.
 // Empty map entries and the words past a list's end name one slot past the row, which holds 0.
 #include "element_map.h"
 #include "internal.h"
@@ -113,11 +114,19 @@ __device__ __forceinline__ float wave_sum(float x)
     return x + __shfl_xor(x, 32, kWave);
 }
 
+// Whether the sum `acc` of n terms, added up by `lanes` lanes, is so close to 1 that only the defining order can tell on which
+// side it lies.  How far the two can lie apart: a step of the serial sum errs by at most half a unit in the last place of a
+// partial sum, and by at most the term itself (s is one of the two neighbours of s + t), so by err = the sum of
+// min(|t|, 2^-23) while the terms' magnitudes sum to mag <= 2; the sum over lanes errs by a rounding per step.
+__device__ __forceinline__ bool order_matters(float acc, float mag, float err, uint32_t n, uint32_t lanes)
+{
+    const float parallel = mag * (static_cast<float>(n / lanes + 40) * 1.1920929e-7f);
+    const float serial = mag <= 2.0f ? 1.01f * err : mag * (static_cast<float>(n) * 1.1920929e-7f);
+    return !(fabsf(acc - 1.0f) > parallel + serial);
+}
+
 // A long column's sum: the lanes of a wavefront (WG: of the workgroup) stride over its tuples; whole wavefronts call this.
-// That is not the order the clamp decision is defined in.  How far the two can lie apart: a step of the serial sum errs by at
-// most half a unit in the last place of a partial sum, and by at most the term itself (s is one of the two neighbours of
-// s + t), so by the sum of min(|t|, 2^-23) while the terms' magnitudes sum to at most 2; the sum over lanes errs by a rounding
-// per step.  Only a sum within that distance of 1 is taken again in the defining order.
+// That is not the order the clamp decision is defined in: only a sum within rounding of 1 is taken again in that order.
 template <bool WG>
 __device__ __forceinline__ float long_sum(const float *ar, const float *br, const uint32_t *__restrict__ ij_of, uint32_t q0, uint32_t q1,
                                           float *scratch)
@@ -152,30 +161,71 @@ __device__ __forceinline__ float long_sum(const float *ar, const float *br, cons
         for (int w = 0; w < n_waves; ++w) { acc += scratch[w]; mag += scratch[16 + w]; err += scratch[32 + w]; }
     }
     if (WG && threadIdx.x >= kWave) return acc;     // (the first wavefront's answer is the one that counts)
-    const float parallel = mag * (static_cast<float>((q1 - q0) / step + 40) * 1.1920929e-7f);
-    const float serial = mag <= 2.0f ? 1.01f * err : mag * (static_cast<float>(q1 - q0) * 1.1920929e-7f);
-    if (!(fabsf(acc - 1.0f) > parallel + serial)) acc = serial_sum(ar, br, ij_of, q0, q1);
+    if (order_matters(acc, mag, err, q1 - q0, step)) acc = serial_sum(ar, br, ij_of, q0, q1);
     return acc;
 }
 
-// The columns among [c0, c1) of more than kLaneList tuples: put(c, sum) is called by one lane.
+// Columns of up to kMidList tuples, four to a wavefront, 16 lanes each, the same way: put(c, sum) is called by one lane.
+// `first`: this wavefront's first four, `step` wavefronts share them.
 template <typename F>
-__device__ __forceinline__ void long_columns(const SampleFwd &A, const float *ar, const float *br, int c0, int c1, float *scratch, F put)
+__device__ __forceinline__ void mid_columns(const float *ar, const float *br, const uint32_t *__restrict__ col_ptr,
+                                            const uint32_t *__restrict__ ij_of, const uint32_t *__restrict__ cols, int n, int first, int step, F put)
+{
+    constexpr int kAhead = 4, kLanes = 16;
+    const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t me = lane % kLanes;
+    for (int l0 = 4 * first; l0 < n; l0 += 4 * step) {
+        const int l = l0 + lane / kLanes;
+        const int c = static_cast<int>(cols[min(l, n - 1)]);
+        const uint32_t q0 = col_ptr[c], q1 = col_ptr[c + 1];
+        float acc = 0.0f, mag = 0.0f, err = 0.0f;
+        for (uint32_t q = q0 + me; q < q1; q += kAhead * kLanes) {
+            uint32_t ij[kAhead];
+            float x[kAhead], y[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) ij[u] = ij_of[min(q + u * kLanes, q1 - 1)];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                x[u] = q + u * kLanes < q1 ? ar[ij[u] & 0xffffu] : 0.0f;
+                y[u] = br[ij[u] >> 16];
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                acc = __builtin_fmaf(x[u], y[u], acc);
+                mag = __builtin_fmaf(fabsf(x[u]), fabsf(y[u]), mag);
+                err += fminf(fabsf(x[u] * y[u]), 1.1920929e-7f);
+            }
+        }
+        acc = reduce16<AddOp>(acc), mag = reduce16<AddOp>(mag), err = reduce16<AddOp>(err);
+        const bool near = order_matters(acc, mag, err, q1 - q0, kLanes) && l < n && me == 0;
+        for (uint64_t todo = __ballot(near); todo; todo &= todo - 1) {
+            const int from = __builtin_ctzll(todo);
+            const uint32_t p0 = __builtin_amdgcn_readlane(q0, from), p1 = __builtin_amdgcn_readlane(q1, from);
+            const float exact = serial_sum(ar, br, ij_of, p0, p1);
+            if (lane == from) acc = exact;
+        }
+        if (l < n && me == 0) put(c, acc);
+    }
+}
+
+// The columns of more than kLaneList tuples, part `part` of `parts` (the last one gets the longest): put(c, sum) is called by
+// one lane.
+template <typename F>
+__device__ __forceinline__ void long_columns(const SampleFwd &A, const float *ar, const float *br, int part, float *scratch, F put)
 {
     const Lists &L = A.lists;
-    for (int l = 0; l < L.n_huge; ++l) {
+    for (int l = A.parts - 1 - part; l < L.n_huge; l += A.parts) {
         const int c = static_cast<int>(L.longer[l]);
-        if (c < c0 || c >= c1) continue;
         const float v = long_sum<true>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], scratch);
         if (threadIdx.x == 0) put(c, v);
     }
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
-    for (int l = L.n_huge + wave; l < L.n_huge + L.n_wave; l += n_waves) {
+    const int lane = threadIdx.x & (kWave - 1), n_waves = blockDim.x / kWave, wave = part * n_waves + wave_number(), step = A.parts * n_waves;
+    for (int l = L.n_huge + wave; l < L.n_huge + L.n_wave; l += step) {
         const int c = __builtin_amdgcn_readfirstlane(static_cast<int>(L.longer[l]));
-        if (c < c0 || c >= c1) continue;
         const float v = long_sum<false>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], scratch);
         if (lane == 0) put(c, v);
     }
+    mid_columns(ar, br, A.col_ptr, A.col_ij, L.longer + L.n_huge + L.n_wave, L.n_mid, wave, step, put);
 }
 
 // Four neighbouring floats at a 4-byte aligned address, of which the first n exist.
@@ -211,7 +261,7 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
     __shared__ float scratch[48];
     const int64_t s = blockIdx.x / static_cast<unsigned>(A.parts);
     const int part = static_cast<int>(blockIdx.x - s * A.parts);
-    // the last part also sums the long columns: they weigh as much as `long_weight` columns
+    // the last part also sums the longest column: it weighs as much as `long_weight` columns
     const int per = ((A.S + A.long_weight + A.parts - 1) / A.parts + 3) & ~3;
     const int c0 = min(A.S, part * per), c1 = part == A.parts - 1 ? A.S : min(A.S, c0 + per);
     const float *br = A.b + s * A.ldb;
@@ -261,8 +311,7 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
                 out[cc] = fminf(column_sum(ar, br, A.col_ij, A.col_ptr[cc], A.col_ptr[cc + 1]), 1.0f);
         }
     }
-    if (part == A.parts - 1)
-        long_columns(A, ar, br, 0, A.S, scratch, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
+    long_columns(A, ar, br, part, scratch, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
 }
 
 template <int NBP>
@@ -310,9 +359,10 @@ __device__ __forceinline__ Chunk<N> read_chunk(const Lists &L, int ch)
 }
 
 // Walks the chunks [ch0, ch1), a wavefront every blockDim.x / 64th: term(word, sum) takes a tuple into a list's sum, in list
-// order, and done(list, sum) is called for every list that is walked here.  `now`: this wavefront's first chunk.
-template <int N, typename T, typename D>
-__device__ __forceinline__ void walk_lists(const Lists &L, int ch0, int ch1, Chunk<N> now, T term, D done)
+// order, and done(list, sum) is called for every list that is walked here, elsewhere(list) for the longer ones.  `now`: this
+// wavefront's first chunk.
+template <int N, typename T, typename D, typename E>
+__device__ __forceinline__ void walk_lists(const Lists &L, int ch0, int ch1, Chunk<N> now, T term, D done, E elsewhere)
 {
     const int n_waves = blockDim.x / kWave;
     for (int ch = ch0 + wave_number(); ch < ch1; ch += n_waves) {
@@ -334,14 +384,18 @@ __device__ __forceinline__ void walk_lists(const Lists &L, int ch0, int ch1, Chu
             }
         }
         if (!(now.e & kListElsewhere)) done(static_cast<int>(now.e), acc);
+        else if (now.e != kNoList) elsewhere(static_cast<int>(now.e & ~kListElsewhere));
         now = next;
     }
 }
 
+// RES: a block of results meets in LDS and leaves in column order; without it they are stored where they fall.  Longer columns
+// are shared out over all parts and stored apart.
+template <bool RES>
 __global__ void __launch_bounds__(kSampleThreads)
 damp_apply2_fwd_staged_kernel(const SampleFwd A)
 {
-    extern __shared__ __align__(16) float lds[];            // a's row and a 0, b's and a 0, a block of results
+    extern __shared__ __align__(16) float lds[];            // a's row and a 0, b's and a 0 [a block of results]
     __shared__ float scratch[48];
     float *ar = lds, *br = lds + ((A.na + 4) & ~3), *res = br + ((A.nb + 4) & ~3);
     const int64_t s = blockIdx.x / static_cast<unsigned>(A.parts);
@@ -357,18 +411,23 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
         const int b1 = min(A.S, b0 + kOrderBlock);
         walk_lists<4>(A.lists, b0 / kWave, (b1 + kWave - 1) / kWave, now,
                    [&](uint32_t t, float acc) { return __builtin_fmaf(ar[t & 0xffffu], br[t >> 16], acc); },
-                   [&](int c, float v) { res[c - b0] = v; });
+                   [&](int c, float v) { (RES ? res - b0 : out)[c] = fminf(v, 1.0f); },
+                   [&](int c) { if (RES) res[c - b0] = __builtin_nanf(""); });      // (a result is never a NaN: the clamp makes it 1)
         const int next = b0 + A.parts * kOrderBlock;
         if (next < A.S) now = read_chunk<4>(A.lists, min(next / kWave + wave_number(), n_chunks - 1));
-        long_columns(A, ar, br, b0, b1, scratch, [&](int c, float v) { res[c - b0] = v; });
+        if (!RES) continue;
         __syncthreads();
         for (int c = 4 * static_cast<int>(threadIdx.x); c < b1 - b0; c += 4 * static_cast<int>(blockDim.x)) {
             const float4 v = *reinterpret_cast<const float4 *>(res + c);
-            const float r[4] = {fminf(v.x, 1.0f), fminf(v.y, 1.0f), fminf(v.z, 1.0f), fminf(v.w, 1.0f)};
-            store4(out + b0 + c, r, b1 - b0 - c);
+            const float r[4] = {v.x, v.y, v.z, v.w};
+            uint32_t skip = 0;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) skip |= (r[k] == r[k] ? 0u : 1u) << k;
+            store4(out + b0 + c, r, b1 - b0 - c, skip);
         }
         __syncthreads();
     }
+    long_columns(A, ar, br, part, scratch, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
 }
 
 // ---------------------------------------------------------------- backward
@@ -551,8 +610,8 @@ damp_byj_bwd_global_kernel(const SampleBwd A)
 }
 
 // Tuple lists: a lane owns a symbol of a or b (element x: symbol x of a, or x - na of b) and adds up its tuples from the
-// gated gradient row, in list order; longer lists are summed by 16 lanes, a wavefront or the workgroup, strided partial sums
-// in list order that meet in a fixed order.  ROWS: the operand rows fit in LDS as well.
+// gated gradient row, in list order; longer lists are summed by 16 lanes or the workgroup, strided partial sums in list order
+// that meet in a fixed order.  ROWS: the operand rows fit in LDS as well.
 template <bool ROWS>
 __global__ void __launch_bounds__(kSampleThreads)
 damp_apply2_bwd_staged_kernel(const SampleBwd A)
@@ -585,7 +644,7 @@ damp_apply2_bwd_staged_kernel(const SampleBwd A)
         float *dst = is_a ? A.ga + s * A.lda + x : A.gb + s * A.ldb + (x - A.na);
         *dst = (A.accumulate & (is_a ? 1 : 2)) ? *dst + v : v;
     };
-    walk_lists<8>(A.lists, 0, n_chunks, now, term, put);
+    walk_lists<8>(A.lists, 0, n_chunks, now, term, put, [](int) {});
     const Lists &L = A.lists;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
     // the partial sum of this lane, one of `step` lanes, over the list of element x
@@ -609,14 +668,9 @@ damp_apply2_bwd_staged_kernel(const SampleBwd A)
     };
     for (int l0 = 4 * wave; l0 < L.n_mid; l0 += 4 * n_waves) {
         const int l = l0 + lane / 16;
-        const int x = static_cast<int>(L.longer[L.n_huge + L.n_wave + min(l, L.n_mid - 1)]);
+        const int x = static_cast<int>(L.longer[L.n_huge + min(l, L.n_mid - 1)]);
         const float v = reduce16<AddOp>(partial(x, lane & 15, 16));
         if (l < L.n_mid && (lane & 15) == 0) put(x, v);
-    }
-    for (int l = L.n_huge + wave; l < L.n_huge + L.n_wave; l += n_waves) {
-        const int x = __builtin_amdgcn_readfirstlane(static_cast<int>(L.longer[l]));
-        const float v = wave_sum(partial(x, lane, kWave));
-        if (lane == 0) put(x, v);
     }
     for (int l = 0; l < L.n_huge; ++l) {
         const int x = static_cast<int>(L.longer[l]);
@@ -674,7 +728,7 @@ damp_merge_sample_kernel(SampleMerge A)
         int over = 0;
         walk_lists<4>(A.cols, 0, col_chunks, first_cols,
                       [&](uint32_t t, float acc) { return __builtin_fmaf(ar[t & 0xffffu], rows[A.na + (t >> 16)], acc); },
-                      [&](int c, float v) { pre[c] = v; over |= !(v <= 1.0f); });
+                      [&](int c, float v) { pre[c] = v; over |= !(v <= 1.0f); }, [](int) {});
         __syncthreads();
         if (FWD) {
             for (int u = tid; u < A.n3; u += T) {
@@ -721,7 +775,7 @@ damp_merge_sample_kernel(SampleMerge A)
                       if (is_a ? !A.ga : !A.gb) return;
                       float *dst = is_a ? A.ga + s * A.na + x : A.gb + s * A.nb + (x - A.na);
                       *dst = (A.accumulate & (is_a ? 1 : 2)) ? *dst + v : v;
-                  });
+                  }, [](int) {});
 }
 
 // ---------------------------------------------------------------- which tables, which launch
@@ -750,24 +804,28 @@ static unsigned list_threads(const ListPlan &p, int32_t n, int32_t row)
     return threads_for(std::max<int64_t>(n + 8 * static_cast<int64_t>(p.n_mid), row / 4), kSampleThreads);
 }
 
-// Parts of a sample's output row, at most `most`: a workgroup copies `row` floats and then does `work` floats' worth of
-// gathers, shared by the parts; the grid runs in rounds of what the chip holds at once (256 compute units, 2 048 threads and
-// 160 KB of LDS each), and a round that is nearly empty costs as much as a full one.
-static int32_t best_parts(int64_t batch, int most, double row, double work, unsigned threads, size_t lds)
+// Parts of a sample's output row, at most `most`: a workgroup copies `row` floats and then does work(p) floats' worth of
+// gathers when there are p of them; the grid runs in rounds of what the chip holds at once (256 compute units, 2 048 threads
+// and 160 KB of LDS each), and a round that is nearly empty costs as much as a full one.
+template <typename Work>
+static int32_t best_parts(int64_t batch, int most, double row, Work work, unsigned threads, size_t lds)
 {
-    const int64_t held = 256 * std::max<int64_t>(1, std::min<int64_t>(2048 / threads, static_cast<int64_t>(160 * 1024 / (lds + 1024))));
+    const int64_t held = kUnits * std::max<int64_t>(1, std::min<int64_t>(2048 / threads, static_cast<int64_t>(160 * 1024 / (lds + 1024))));
     int32_t best = 1;
     double best_cost = 0.0;
     for (int p = 1; p <= most && batch * p <= 0x7fffffffLL; ++p) {
-        const double cost = static_cast<double>((batch * p + held - 1) / held) * (row + 1500.0 + work / p);
+        const double cost = static_cast<double>((batch * p + held - 1) / held) * (row + 1500.0 + work(p));
         if (p == 1 || cost < 0.97 * best_cost) { best = p; best_cost = cost; }
     }
     return best;
 }
 
-static size_t list_fwd_bytes(const dol_fn_table *f)
+// As many parts as the longer columns keep busy (64 of 16 lanes each, or 16 of a wavefront, to a part), at least `least`.
+static int long_parts(const ListPlan &p, int least) { return std::max(least, std::min(64, p.n_mid / 64 + p.n_wave / 16)); }
+
+static size_t list_fwd_bytes(const dol_fn_table *f, bool results)
 {
-    return sizeof(float) * (static_cast<size_t>((f->na + 4) & ~3) + ((f->nb + 4) & ~3) + std::min(f->n_out + 3, kOrderBlock));
+    return sizeof(float) * (static_cast<size_t>((f->na + 4) & ~3) + ((f->nb + 4) & ~3) + (results ? std::min(f->n_out + 3, kOrderBlock) : 0));
 }
 
 static size_t gated_bytes(const dol_fn_table *f) { return sizeof(float) * static_cast<size_t>((f->n_out + 4) & ~3); }
@@ -778,7 +836,7 @@ bool byj_fwd_sample_ok(const dol_fn_table *f)
     return f->byj_fwd && !table_code_ok(f) && sizeof(float) * static_cast<size_t>(f->na + 4) <= kStageMaxBytes;
 }
 
-bool list_fwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && list_fwd_bytes(f) <= kStageMaxBytes; }
+bool list_fwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && list_fwd_bytes(f, false) <= kStageMaxBytes; }
 
 bool byj_bwd_sample_ok(const dol_fn_table *f) { return f->byj_ok; }
 
@@ -812,10 +870,11 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
     A.lists = lists_of(f->col_lists);
     if (byj) {
         A.map = f->byj_src.ptr, A.map_ld = f->byj_src_ld;
-        A.long_weight = static_cast<int32_t>(std::min<int64_t>(f->col_lists.long_words / f->byj_nbp, f->n_out));
+        A.long_weight = static_cast<int32_t>(std::min<int64_t>(f->col_lists.huge_words / f->byj_nbp, f->n_out));
         const size_t lds = sizeof(float) * static_cast<size_t>(f->na + 4);
-        A.parts = best_parts(batch, std::min(16, (f->n_out + 4 * kSmallThreads - 1) / (4 * kSmallThreads)), f->na,
-                             static_cast<double>(f->n_out + A.long_weight) * f->byj_nbp, byj_fwd_wide(f) ? kSampleThreads : kSmallThreads, lds);
+        A.parts = best_parts(batch, long_parts(f->col_lists, std::min(16, (f->n_out + 4 * kSmallThreads - 1) / (4 * kSmallThreads))), f->na,
+                             [&](int p) { return (static_cast<double>(f->n_out + A.long_weight) * f->byj_nbp + 4.0 * f->col_lists.mid_words) / p; },
+                             byj_fwd_wide(f) ? kSampleThreads : kSmallThreads, lds);
         const unsigned grid = static_cast<unsigned>(batch) * A.parts;
         const int64_t work = std::max<int64_t>(f->n_out / A.parts + 3, f->na) / 4;
         if (byj_fwd_wide(f)) {
@@ -832,11 +891,23 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
 #undef CALL
         }
     } else {
-        const size_t lds = list_fwd_bytes(f);
-        A.parts = best_parts(batch, (f->n_out + kOrderBlock - 1) / kOrderBlock, f->na + f->nb, 2.0 * f->n_tuples + f->n_out, kSampleThreads, lds);
-        if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_fwd_staged_kernel), kStageMaxBytes));
-        hipLaunchKernelGGL(damp_apply2_fwd_staged_kernel, dim3(static_cast<unsigned>(batch) * A.parts),
-                           dim3(list_threads(f->col_lists, f->n_out, f->na)), lds, st, A);
+        // (stored where they fall the results of lists of many lengths dirty every line many times over: 1 200 x 30 -> 6 500,
+        // 5.5 words to a list, B=4 000 79 us against 63.  Lists of one or two words are in column order but for a few: 1 200 x 7
+        // -> 6 500 44 against 49, 800 x 3 -> 2 400 21 against 24.  Nor is there room beside rows of more than 36 000 symbols.)
+        const bool results = list_fwd_bytes(f, true) <= kStageMaxBytes && f->col_lists.n_words >= 3 * static_cast<size_t>(f->n_out);
+        const size_t lds = list_fwd_bytes(f, results);
+        const int blocks = (f->n_out + kOrderBlock - 1) / kOrderBlock;
+        A.parts = best_parts(batch, long_parts(f->col_lists, blocks), f->na + f->nb, [&](int p) {
+            return (2.0 * f->col_lists.n_words + f->n_out) / std::min(p, blocks) + 4.0 * f->col_lists.mid_words / p + 2.0 * f->col_lists.huge_words;
+        }, kSampleThreads, lds);
+        const dim3 grid(static_cast<unsigned>(batch) * A.parts), block(list_threads(f->col_lists, f->n_out, f->na));
+        if (results) {
+            if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_fwd_staged_kernel<true>), kStageMaxBytes));
+            hipLaunchKernelGGL(damp_apply2_fwd_staged_kernel<true>, grid, block, lds, st, A);
+        } else {
+            DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_fwd_staged_kernel<false>), kStageMaxBytes));
+            hipLaunchKernelGGL(damp_apply2_fwd_staged_kernel<false>, grid, block, lds, st, A);
+        }
     }
     DOL_HIP(hipGetLastError());
     *done = true;

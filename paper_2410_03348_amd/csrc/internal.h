@@ -75,7 +75,8 @@ constexpr size_t kStageMaxBytes = 158 * 1024;   // narrower ones stay with the c
 constexpr int kByJMax = 16;         // tables whose second operand has at most this many symbols get dense per-j maps
 constexpr int kByJMaxNa = 65000;    // ... and whose first operand leaves room for the three marks below
 constexpr uint16_t kByJWave = 0xFFFE, kByJList = 0xFFFD;
-constexpr uint32_t kListElsewhere = 0x80000000u;   // struct ListPlan: this list is summed elsewhere
+constexpr uint32_t kListElsewhere = 0x80000000u;   // struct ListPlan: this list is summed elsewhere,
+constexpr uint32_t kNoList = 0xFFFFFFFFu;          // there is no such list
 
 // Code compiled for one function table on its first use (damp_table.hip)
 struct JitState;
@@ -87,15 +88,16 @@ struct JitDeleter {
 // blocks of kOrderBlock consecutive lists the longest come first (longer lists than that last, as empty ones), and the lists
 // are taken 64 at a time: word k of the 64 lists of chunk ch stands at words[(ptr[ch] + k) * 64 + lane], filled up to the
 // longest of the 64 with a word whose product is 0.  order[r] is the list that lane r % 64 of chunk r / 64 walks, with
-// kListElsewhere set for the longer ones, which are named by `longer`: first those above kHugeList words (summed by a
-// workgroup each), then those summed by a wavefront each, then those summed by 16 lanes (rows only).
+// kListElsewhere set for the longer ones, which are named by `longer`: first those that a workgroup sums, then those that a
+// wavefront sums (columns only), then those of up to kMidList words, which 16 lanes sum.  A row of more than that takes a
+// workgroup.  A column takes one only if it has more than a sixteenth of all such columns' words, and would keep one wavefront
+// of the workgroup's sixteen busy after the others have ended.
 constexpr int kLaneList = 64;
-constexpr int kHugeList = 512;
-constexpr int kMidRow = 512;            // rows of up to this many tuples are summed by 16 lanes
+constexpr int kMidList = 512;
 struct ListPlan {
     DevArray<uint32_t> order, ptr, words, longer;
     int32_t n_huge = 0, n_wave = 0, n_mid = 0;
-    int64_t long_words = 0;             // words of the huge and the wavefront lists
+    int64_t huge_words = 0, mid_words = 0;      // words of the workgroups' lists; of the other longer ones
     size_t n_words = 0;                 // words laid out for lanes, filling included
 };
 

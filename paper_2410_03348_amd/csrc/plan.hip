@@ -65,9 +65,9 @@ struct Tuple {
     int32_t i, j, id;
 };
 
-// struct ListPlan from lists ptr[x] .. ptr[x + 1] of word(q); lists above `wave_above` words get a wavefront.
+// struct ListPlan from lists ptr[x] .. ptr[x + 1] of word(q), of columns or of rows.
 template <typename F>
-static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, uint32_t wave_above, F word, uint32_t filling, ListPlan *plan)
+static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, bool columns, F word, uint32_t filling, ListPlan *plan)
 {
     std::vector<uint32_t> order = columns_by_length(ptr, n, kLaneList), start{0}, words, huge, wave, mid;
     auto length = [&](uint32_t x) { const uint32_t l = ptr[x + 1] - ptr[x]; return l > static_cast<uint32_t>(kLaneList) ? 0u : l; };
@@ -84,12 +84,15 @@ static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, uint
     words.resize(words.size() + 8 * 64, filling);           // up to eight words are read at a time
     for (uint32_t &x : order)
         if (ptr[x + 1] - ptr[x] > static_cast<uint32_t>(kLaneList)) x |= kListElsewhere;
-    while (order.size() % 64) order.push_back(kListElsewhere);
+    while (order.size() % 64) order.push_back(kNoList);
+    int64_t above = 0;                      // words of the lists too long for 16 lanes
+    for (int32_t x = 0; x < n; ++x) above += ptr[x + 1] - ptr[x] > static_cast<uint32_t>(kMidList) ? ptr[x + 1] - ptr[x] : 0;
     for (int32_t x = 0; x < n; ++x) {
-        const uint32_t l = ptr[x + 1] - ptr[x];
-        if (l <= static_cast<uint32_t>(kLaneList)) continue;
-        if (l > wave_above) plan->long_words += l;
-        (l > static_cast<uint32_t>(kHugeList) ? huge : l > wave_above ? wave : mid).push_back(static_cast<uint32_t>(x));
+        const int64_t l = static_cast<int64_t>(ptr[x + 1]) - ptr[x];
+        if (l <= kLaneList) continue;
+        const bool by_workgroup = l > kMidList && (!columns || 16 * l > above);
+        (by_workgroup ? plan->huge_words : plan->mid_words) += l;
+        (by_workgroup ? huge : l > kMidList ? wave : mid).push_back(static_cast<uint32_t>(x));
     }
     plan->n_huge = static_cast<int32_t>(huge.size()), plan->n_wave = static_cast<int32_t>(wave.size()), plan->n_mid = static_cast<int32_t>(mid.size());
     huge.insert(huge.end(), wave.begin(), wave.end());
@@ -215,7 +218,7 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
     if (!conv_path_ok(tb.get()))
         if (dol_status s2 = lds_plan_build(tb.get(), col_ptr, col_ij, rowa_ptr, rowa_jc, rowb_ptr, rowb_ic)) return s2;
     if (!conv_path_ok(tb.get()) && na >= 1 && nb >= 1 && S >= 1 && na + nb < 0xFFFF && S < 0xFFFF) {
-        if ((e = upload_lists(col_ptr, S, kLaneList, [&](uint32_t q) { return col_ij[q]; }, pack16(na, nb), &tb->col_lists)) != hipSuccess)
+        if ((e = upload_lists(col_ptr, S, true, [&](uint32_t q) { return col_ij[q]; }, pack16(na, nb), &tb->col_lists)) != hipSuccess)
             return hip_fail(e, "uploading the function table");
         std::vector<uint32_t> row_ptr(rowa_ptr);
         for (int32_t j = 0; j < nb; ++j) row_ptr.push_back(rowa_ptr[na] + rowb_ptr[j + 1]);
@@ -224,7 +227,7 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
             if (q < n_a) return pack16(na + (rowa_jc[q] & 0xffffu), rowa_jc[q] >> 16);
             return rowb_ic[q - n_a];
         };
-        if ((e = upload_lists(row_ptr, na + nb, kMidRow, word, pack16(na + nb, S), &tb->row_lists)) != hipSuccess)
+        if ((e = upload_lists(row_ptr, na + nb, false, word, pack16(na + nb, S), &tb->row_lists)) != hipSuccess)
             return hip_fail(e, "uploading the function table");
         tb->lists_ok = true;
     }

@@ -1689,6 +1689,42 @@ def test_backward_with_many_long_columns_at_the_clamp(dol, nb, n_out):
     assert_close(host(gb), wb, "backward b")
 
 
+@pytest.mark.parametrize("na,nb,n_long,n_short,B", [(36300, 20, 900, 6000, 2), (36344, 20, 3, 12000, 2), (37000, 20, 1500, 3000, 1), (37000, 4, 40, 30000, 3),
+                                                    (700, 30, 90, 10, 300), (500, 12, 31, 700, 5)])
+def test_forward_with_long_columns_shared_over_workgroups(dol, na, nb, n_long, n_short, B):
+    """Columns of 65 to some thousand tuples among short ones, few and many of them, beside rows that leave room in LDS for a
+    block of results and rows that do not; every third long column sums to within roundings of 1, where the order of
+    definition decides, the others above and below."""
+    r = W.splitmix64(31, np.arange(na * nb))
+    i, j = np.repeat(np.arange(na), nb), np.tile(np.arange(nb), na)
+    long_rows = na // 2
+    n_tail = min(na - long_rows, max(1, 3 * n_short // nb))                  # rows whose tuples go to the short columns
+    keep = (i < long_rows) | (i >= na - n_tail)
+    i, j, r = i[keep], j[keep], r[keep]
+    o = np.where(i < long_rows, i % n_long, n_long + (r % np.uint64(n_short)).astype(np.int64))
+    syms, o = np.unique(o, return_inverse=True)
+    tri = (i.astype(np.int32), j.astype(np.int32), o.astype(np.int32))
+    lengths = np.bincount(o)
+    assert (lengths[:n_long] > 64).all() and (lengths[n_long:] <= 64).all()
+    b = np.ones((B, nb), np.float32)
+    a = (W.uniform01(33, B * na).reshape(B, na) ** 2 + 1e-4).astype(np.float64)
+    for c in range(n_long):
+        rows = np.arange(c, long_rows, n_long)
+        want_sum = (1.0 + 1e-7 * ((c + np.arange(B)) % 5 - 2), 1.5, 0.6)[c % 3]
+        a[:, rows] *= (np.asarray(want_sum) / (a[:, rows].sum(axis=1) * nb)).reshape(-1, 1)
+    a[:, long_rows:] *= 0.2
+    a = a.astype(np.float32)
+    _, want, pre32, pre64 = oracle.damp_apply2_fwd(tri, na, nb, a, b, want_pre=True)
+    near = pre32[:, :n_long][:, ::3]
+    assert np.abs(near - 1).max() < 1e-5 and (near > 1).any() and (near <= 1).any()
+    f = dol.FnTable.create_sparse(na, nb, *tri)
+    da, db = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b))
+    out = dol.Dist.empty(f.out_syms, B)
+    dol.apply2(da, db, f, None, out)
+    assert_close(host(out.prob), want, "forward")
+    np.testing.assert_array_equal(host(out.prob) == 1.0, pre32 >= 1.0)
+
+
 def test_apply_k_two_operands_equal_apply2_bit_for_bit(dol):
     B = 150
     table = W.hashed_table(41, 30, 20, 64)
