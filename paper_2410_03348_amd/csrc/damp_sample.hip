@@ -798,10 +798,17 @@ static Lists lists_of(const ListPlan &p)
     return Lists{p.order.ptr, p.ptr.ptr, p.words.ptr, p.longer.ptr, p.n_huge, p.n_wave, p.n_mid};
 }
 
-// Threads for n lists (a lane each, eight for one that 16 lanes sum) beside the copying of a row.
-static unsigned list_threads(const ListPlan &p, int32_t n, int32_t row)
+// Threads for n lists (a lane each, eight for one that 16 lanes sum) beside the copying of a row: 2 048 for all the workgroups
+// that a unit gets of the launch, or has LDS for.  A workgroup's phases run one after the other, those of several side by
+// side, so more than one to a unit shall mean smaller ones, down to `least` threads.  (B=4 000, us, with 1 024 / 512 / 256 / 128
+// threads, LDS for 14 workgroups, rows of 40 and of 700 tuples: backward 356 / 196 / 131 / 139, forward 47 / 41 / 41 / 49;
+// 1 200 x 7 -> 6 500, LDS for seven: forward 60 / 49 / 50 / 75; 9 000 x 20 -> 9 000, LDS for two: backward 627 / 755 / 1 189.)
+static unsigned list_threads(const ListPlan &p, int32_t n, int32_t row, int64_t groups, size_t lds, int least)
 {
-    return threads_for(std::max<int64_t>(n + 8 * static_cast<int64_t>(p.n_mid), row / 4), kSampleThreads);
+    const int64_t held = std::max<int64_t>(1, std::min<int64_t>((groups + kUnits - 1) / kUnits, static_cast<int64_t>(160 * 1024 / (lds + 1024))));
+    const int64_t share = held >= 16 ? 128 : held >= 8 ? 256 : held >= 4 ? 512 : kSampleThreads;
+    return threads_for(std::max<int64_t>(n + 8 * static_cast<int64_t>(p.n_mid), row / 4),
+                       static_cast<int>(std::min<int64_t>(kSampleThreads, std::max<int64_t>(least, share))));
 }
 
 // Parts of a sample's output row, at most `most`: a workgroup copies `row` floats and then does work(p) floats' worth of
@@ -900,7 +907,7 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
         A.parts = best_parts(batch, long_parts(f->col_lists, blocks), f->na + f->nb, [&](int p) {
             return (2.0 * f->col_lists.n_words + f->n_out) / std::min(p, blocks) + 4.0 * f->col_lists.mid_words / p + 2.0 * f->col_lists.huge_words;
         }, kSampleThreads, lds);
-        const dim3 grid(static_cast<unsigned>(batch) * A.parts), block(list_threads(f->col_lists, f->n_out, f->na));
+        const dim3 grid(static_cast<unsigned>(batch) * A.parts), block(list_threads(f->col_lists, f->n_out, f->na, batch * static_cast<int64_t>(A.parts), lds, 512));
         if (results) {
             if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_fwd_staged_kernel<true>), kStageMaxBytes));
             hipLaunchKernelGGL(damp_apply2_fwd_staged_kernel<true>, grid, block, lds, st, A);
@@ -959,7 +966,7 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
     } else {
         A.rowa_ptr = f->rowa_ptr.ptr, A.rowa_jc = f->rowa_jc.ptr, A.rowb_ptr = f->rowb_ptr.ptr, A.rowb_ic = f->rowb_ic.ptr;
         const size_t with_rows = lds + sizeof(float) * static_cast<size_t>(f->na + f->nb + 1);
-        const dim3 block(list_threads(f->row_lists, f->na + f->nb, f->n_out));
+        const dim3 block(list_threads(f->row_lists, f->na + f->nb, f->n_out, batch, with_rows <= kStageMaxBytes ? with_rows : lds, 128));
         if (with_rows <= kStageMaxBytes) {
             if (with_rows > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_bwd_staged_kernel<true>), kStageMaxBytes));
             hipLaunchKernelGGL(damp_apply2_bwd_staged_kernel<true>, grid, block, with_rows, st, A);
