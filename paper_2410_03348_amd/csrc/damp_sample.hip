@@ -34,6 +34,7 @@ struct Lists {                          // struct ListPlan (internal.h) on the d
 struct SampleFwd {
     int32_t na, nb, S, parts;
     int32_t map_ld, long_weight;        // dense maps
+    int32_t exact;                      // every column in its tuples' order (lists only)
     const uint16_t *map;
     Lists lists;                        // of the columns
     const uint32_t *col_ptr, *col_ij;   // a column's tuples in their order
@@ -208,6 +209,81 @@ __device__ __forceinline__ void mid_columns(const float *ar, const float *br, co
     }
 }
 
+// s + x * y of this lane and the 15 behind it in the row of 16, one after the other, for a row's first lane: two instructions
+// a term, the multiply-add takes x from the other lane by itself.  (Left to the compiler x is moved as well, into one register
+// for all terms, and a term takes 29 clocks.)
+__device__ __forceinline__ float chain16(float x, float y, float s)
+{
+    float t0, t1, t2;
+#define DOL_Y(t, k) "v_mov_b32_dpp " t ", %5 row_shl:" #k " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+#define DOL_S(t, k) "v_fmac_f32_dpp %0, %4, " t " row_shl:" #k " row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
+    asm("s_nop 1\n\t"                          // (x and y may have been written just now)
+        DOL_Y("%1", 1) DOL_Y("%2", 2) "v_fmac_f32 %0, %4, %5\n\t"
+        DOL_Y("%3", 3) DOL_S("%1", 1) DOL_Y("%1", 4) DOL_S("%2", 2) DOL_Y("%2", 5) DOL_S("%3", 3)
+        DOL_Y("%3", 6) DOL_S("%1", 4) DOL_Y("%1", 7) DOL_S("%2", 5) DOL_Y("%2", 8) DOL_S("%3", 6)
+        DOL_Y("%3", 9) DOL_S("%1", 7) DOL_Y("%1", 10) DOL_S("%2", 8) DOL_Y("%2", 11) DOL_S("%3", 9)
+        DOL_Y("%3", 12) DOL_S("%1", 10) DOL_Y("%1", 13) DOL_S("%2", 11) DOL_Y("%2", 14) DOL_S("%3", 12)
+        DOL_Y("%3", 15) DOL_S("%1", 13) DOL_S("%2", 14) DOL_S("%3", 15)
+        : "+v"(s), "=&v"(t0), "=&v"(t1), "=&v"(t2)
+        : "v"(x), "v"(y));
+#undef DOL_Y
+#undef DOL_S
+    return s;
+}
+
+// The columns cols[0 .. n) in the order of their tuples, 16 lanes each, four to a wavefront: the lanes fetch 64 tuples' tags,
+// the first one adds them up.  `first`, `step` as for mid_columns; the first columns' words are asked for when the object is
+// made, which needs no rows yet.
+struct ChainColumns {
+    static constexpr uint32_t kLanes = 16;
+    static constexpr int kSteps = 4;
+    const uint32_t *col_ptr, *ij_of, *cols;
+    int n, l0, step, c;
+    uint32_t me, q0, q1, ij[kSteps];
+
+    __device__ __forceinline__ ChainColumns(const SampleFwd &A, int first, int wavefronts)
+        : col_ptr(A.col_ptr), ij_of(A.col_ij), cols(A.lists.longer), n(A.lists.n_huge + A.lists.n_wave + A.lists.n_mid), l0(4 * first),
+          step(4 * wavefronts), me(threadIdx.x % kLanes)
+    {
+        if (l0 < n) fetch();
+    }
+    __device__ __forceinline__ int which() const { return l0 + static_cast<int>(threadIdx.x & (kWave - 1)) / static_cast<int>(kLanes); }
+    __device__ __forceinline__ void fetch()
+    {
+        c = static_cast<int>(cols[min(which(), n - 1)]);
+        q0 = col_ptr[c], q1 = col_ptr[c + 1];
+        words(q0);
+    }
+    __device__ __forceinline__ void words(uint32_t q)
+    {
+#pragma unroll
+        for (int u = 0; u < kSteps; ++u) ij[u] = ij_of[min(q + u * kLanes + me, q1 - 1)];
+    }
+    // put(c, sum) is called by one lane
+    template <typename F>
+    __device__ __forceinline__ void run(const float *ar, const float *br, F put)
+    {
+        while (l0 < n) {
+            float s = 0.0f;
+            for (uint32_t q = q0; q < q1; q += kSteps * kLanes) {
+                float x[kSteps], y[kSteps];
+#pragma unroll
+                for (int u = 0; u < kSteps; ++u) {
+                    const bool there = q + u * kLanes + me < q1;
+                    x[u] = there ? ar[ij[u] & 0xffffu] : 0.0f, y[u] = there ? br[ij[u] >> 16] : 0.0f;   // (the filling adds 0 * 0)
+                }
+                words(q + kSteps * kLanes);                 // (on their way meanwhile)
+#pragma unroll
+                for (int u = 0; u < kSteps; ++u)
+                    if (u == 0 || q + u * kLanes < q1) s = chain16(x[u], y[u], s);
+            }
+            if (which() < n && me == 0) put(c, s);
+            l0 += step;
+            if (l0 < n) fetch();
+        }
+    }
+};
+
 // The columns of more than kLaneList tuples, part `part` of `parts` (the last one gets the longest): put(c, sum) is called by
 // one lane.
 template <typename F>
@@ -259,6 +335,7 @@ template <int NBP>
 __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
 {
     __shared__ float scratch[48];
+    __shared__ int some;
     const int64_t s = blockIdx.x / static_cast<unsigned>(A.parts);
     const int part = static_cast<int>(blockIdx.x - s * A.parts);
     // the last part also sums the longest column: it weighs as much as `long_weight` columns
@@ -266,49 +343,50 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
     const int c0 = min(A.S, part * per), c1 = part == A.parts - 1 ? A.S : min(A.S, c0 + per);
     const float *br = A.b + s * A.ldb;
     float *out = A.out + s * A.ldo;
+    if (threadIdx.x == 0) some = 0;
     copy_row(ar, A.a + s * A.lda, A.na);
     float y[NBP];
 #pragma unroll
     for (int j = 0; j < NBP; ++j) y[j] = br[j < A.nb ? j : 0];      // (the maps' extra rows are empty)
     __syncthreads();
-    const int lane = threadIdx.x & (kWave - 1);
-    for (int cw = c0 + 4 * kWave * wave_number(); cw < c1; cw += 4 * static_cast<int>(blockDim.x)) {
-        const int c = cw + 4 * lane;
-        uint32_t again = 0;                             // bit k: column c + k is taken from its tuple list
-        if (c < c1) {
-            ushort4 m[NBP];
+    bool again = false;
+    for (int c = c0 + 4 * static_cast<int>(threadIdx.x); c < c1; c += 4 * static_cast<int>(blockDim.x)) {
+        ushort4 m[NBP];
 #pragma unroll
-            for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + c);
-            const uint16_t mark[4] = {m[0].x, m[0].y, m[0].z, m[0].w};
-            const uint16_t none = static_cast<uint16_t>(A.na);
-            m[0].x = min(m[0].x, none), m[0].y = min(m[0].y, none), m[0].z = min(m[0].z, none), m[0].w = min(m[0].w, none);
-            float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, mag[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + c);
+        const uint16_t mark[4] = {m[0].x, m[0].y, m[0].z, m[0].w};
+        const uint16_t none = static_cast<uint16_t>(A.na);
+        m[0].x = min(m[0].x, none), m[0].y = min(m[0].y, none), m[0].z = min(m[0].z, none), m[0].w = min(m[0].w, none);
+        float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, mag[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-            for (int j = 0; j < NBP; ++j) {
-                const float x[4] = {ar[m[j].x], ar[m[j].y], ar[m[j].z], ar[m[j].w]};
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    acc[k] = __builtin_fmaf(x[k], y[j], acc[k]);
-                    mag[k] = __builtin_fmaf(fabsf(x[k]), fabsf(y[j]), mag[k]);
-                }
-            }
-            uint32_t elsewhere = 0;
+        for (int j = 0; j < NBP; ++j) {
+            const float x[4] = {ar[m[j].x], ar[m[j].y], ar[m[j].z], ar[m[j].w]};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const bool near = !(fabsf(acc[k] - 1.0f) > mag[k] * (static_cast<float>(NBP + 2) * 1.1920929e-7f));
-                if (mark[k] == kByJWave) elsewhere |= 1u << k;      // summed below
-                else if (near || mark[k] == kByJList) again |= 1u << k;     // (list: some j occurs twice)
-                acc[k] = fminf(acc[k], 1.0f);
+                acc[k] = __builtin_fmaf(x[k], y[j], acc[k]);
+                mag[k] = __builtin_fmaf(fabsf(x[k]), fabsf(y[j]), mag[k]);
             }
-            store4(out + c, acc, c1 - c, again | elsewhere);
         }
-        if (!__ballot(again != 0)) continue;
-        const uint64_t of[4] = {__ballot(again & 1u), __ballot(again & 2u), __ballot(again & 4u), __ballot(again & 8u)};
-        const uint64_t mine = lane & 2 ? (lane & 1 ? of[3] : of[2]) : (lane & 1 ? of[1] : of[0]);
-        for (int r = 0; r < 4; ++r) {                   // (neighbouring lanes, neighbouring columns)
-            const int cc = cw + kWave * r + lane;
-            if (cc < c1 && ((mine >> (16 * r + (lane >> 2))) & 1u))
-                out[cc] = fminf(column_sum(ar, br, A.col_ij, A.col_ptr[cc], A.col_ptr[cc + 1]), 1.0f);
+        uint32_t skip = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const bool near = !(fabsf(acc[k] - 1.0f) > mag[k] * (static_cast<float>(NBP + 2) * 1.1920929e-7f));
+            if (mark[k] == kByJWave) skip |= 1u << k;               // (many tuples: summed last)
+            const bool list = (near || mark[k] == kByJList) && mark[k] != kByJWave && c + k < c1;   // (list: some j twice)
+            again |= list;
+            acc[k] = list ? __builtin_nanf("") : fminf(acc[k], 1.0f);
+        }
+        store4(out + c, acc, c1 - c, skip);
+    }
+    if (again) some = 1;
+    lds_barrier();                          // (does not wait for the results to be in memory)
+    if (some) {                             // columns marked by a NaN, which no result is: neighbouring lanes, neighbouring columns
+        __syncthreads();
+        for (int c = c0 + static_cast<int>(threadIdx.x); c < c1; c += static_cast<int>(blockDim.x)) {
+            const float v = out[c];
+            if (v == v) continue;
+            const uint32_t q0 = A.col_ptr[c], q1 = A.col_ptr[c + 1];
+            if (q1 - q0 <= static_cast<uint32_t>(kLaneList)) out[c] = fminf(column_sum(ar, br, A.col_ij, q0, q1), 1.0f);
         }
     }
     long_columns(A, ar, br, part, scratch, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
@@ -322,8 +400,9 @@ damp_byj_fwd_kernel(const SampleFwd A)
     byj_fwd<NBP>(A, lds);
 }
 
+// (64 registers, for two workgroups of 1 024 threads to a unit)
 template <int NBP>
-__global__ void __launch_bounds__(kSampleThreads)
+__global__ void __launch_bounds__(kSampleThreads, 8)
 damp_byj_fwd_staged_kernel(const SampleFwd A)
 {
     extern __shared__ __align__(16) float lds[];
@@ -403,10 +482,14 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
     constexpr int kBlockChunks = kOrderBlock / kWave;
     const int n_chunks = (A.S + kWave - 1) / kWave;
     Chunk<4> now = read_chunk<4>(A.lists, min(part * kBlockChunks + wave_number(), n_chunks - 1));
+    const int n_waves = blockDim.x / kWave;                 // (the last wavefronts have the fewest lists)
+    ChainColumns chain(A, A.exact ? part + A.parts * (n_waves - 1 - wave_number()) : INT32_MAX / 4, A.parts * n_waves);
     copy_row(ar, A.a + s * A.lda, A.na);
     copy_row(br, A.b + s * A.ldb, A.nb);
     __syncthreads();
     float *out = A.out + s * A.ldo;
+    auto put_long = [&](int c, float v) { out[c] = fminf(v, 1.0f); };
+    chain.run(ar, br, put_long);
     for (int b0 = part * kOrderBlock; b0 < A.S; b0 += A.parts * kOrderBlock) {
         const int b1 = min(A.S, b0 + kOrderBlock);
         walk_lists<4>(A.lists, b0 / kWave, (b1 + kWave - 1) / kWave, now,
@@ -427,7 +510,7 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
         }
         __syncthreads();
     }
-    long_columns(A, ar, br, part, scratch, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
+    if (!A.exact) long_columns(A, ar, br, part, scratch, put_long);
 }
 
 // ---------------------------------------------------------------- backward
@@ -832,20 +915,26 @@ static int long_parts(const ListPlan &p, int least) { return std::max(least, std
 
 static size_t list_fwd_bytes(const dol_fn_table *f, bool results)
 {
-    return sizeof(float) * (static_cast<size_t>((f->na + 4) & ~3) + ((f->nb + 4) & ~3) + (results ? std::min(f->n_out + 3, kOrderBlock) : 0));
+    return sizeof(float) * (static_cast<size_t>((f->na + 4) & ~3) + ((f->nb + 4) & ~3) + (results ? std::min((f->n_out + 3) & ~3, kOrderBlock) : 0));
 }
 
 static size_t gated_bytes(const dol_fn_table *f) { return sizeof(float) * static_cast<size_t>((f->n_out + 4) & ~3); }
 
-// (tables that have generated code add their columns up in the defining order at every batch: the lists do, the map does not)
+// Tables that tiles of samples serve as well (damp_lds.hip, damp_table.hip) have every column added up in the order of its
+// tuples, as the tiles do, so that a sample's result does not depend on the batch it is in: through the lists, long columns by
+// a chain.  (The map goes one j at a time.)
+static bool exact_fwd(const dol_fn_table *f) { return f->lds_fwd_ok || table_code_ok(f); }
+
 bool byj_fwd_sample_ok(const dol_fn_table *f)
 {
-    return f->byj_fwd && !table_code_ok(f) && sizeof(float) * static_cast<size_t>(f->na + 4) <= kStageMaxBytes;
+    return f->byj_fwd && !exact_fwd(f) && sizeof(float) * static_cast<size_t>(f->na + 4) <= kStageMaxBytes;
 }
 
 bool list_fwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && list_fwd_bytes(f, false) <= kStageMaxBytes; }
 
-bool byj_bwd_sample_ok(const dol_fn_table *f) { return f->byj_ok; }
+// (without the maps' long rows of b the lists have a lane for every row: 16 x 16 -> 32, B=4 096, 7.5 us through the map, 5.0
+// through the lists; 101 x 10 6.5 and 8.3)
+bool byj_bwd_sample_ok(const dol_fn_table *f) { return f->byj_ok && (f->byj_nbp <= 4 || f->row_lists.longer.n > 0); }
 
 bool byj_bwd_staged(const dol_fn_table *f) { return gated_bytes(f) <= kStageMaxBytes; }
 
@@ -902,12 +991,15 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
         // 5.5 words to a list, B=4 000 79 us against 63.  Lists of one or two words are in column order but for a few: 1 200 x 7
         // -> 6 500 44 against 49, 800 x 3 -> 2 400 21 against 24.  Nor is there room beside rows of more than 36 000 symbols.)
         const bool results = list_fwd_bytes(f, true) <= kStageMaxBytes && f->col_lists.n_words >= 3 * static_cast<size_t>(f->n_out);
+        A.exact = exact_fwd(f) ? 1 : 0;
         const size_t lds = list_fwd_bytes(f, results);
         const int blocks = (f->n_out + kOrderBlock - 1) / kOrderBlock;
         A.parts = best_parts(batch, long_parts(f->col_lists, blocks), f->na + f->nb, [&](int p) {
             return (2.0 * f->col_lists.n_words + f->n_out) / std::min(p, blocks) + 4.0 * f->col_lists.mid_words / p + 2.0 * f->col_lists.huge_words;
         }, kSampleThreads, lds);
-        const dim3 grid(static_cast<unsigned>(batch) * A.parts), block(list_threads(f->col_lists, f->n_out, f->na, batch * static_cast<int64_t>(A.parts), lds, 512));
+        unsigned threads = list_threads(f->col_lists, f->n_out, f->na, batch * static_cast<int64_t>(A.parts), lds, 512);
+        if (A.exact && f->col_lists.longer.n && threads < kSampleThreads) threads += kWave;        // (the chain runs beside the lists)
+        const dim3 grid(static_cast<unsigned>(batch) * A.parts), block(threads);
         if (results) {
             if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_fwd_staged_kernel<true>), kStageMaxBytes));
             hipLaunchKernelGGL(damp_apply2_fwd_staged_kernel<true>, grid, block, lds, st, A);

@@ -2050,6 +2050,27 @@ def test_tiles_of_64_samples_at_large_batches(dol, na, nb, n_ids, batch):
     assert_close(host(gb), wb, "tiles backward b")
 
 
+@pytest.mark.parametrize("na,nb,n_ids", [(13, 12, 30), (50, 37, 201), (101, 10, 226), (101, 10, 9), (226, 10, 442), (442, 10, 785), (100, 100, 50),
+                                         (128, 30, 700), (30, 30, 2), (64, 64, 32), (16, 16, 200)])
+def test_a_result_does_not_depend_on_the_batch_it_is_in(dol, na, nb, n_ids):
+    """Tables that are served by tiles in large batches and by a workgroup per sample in small ones: every bit of a sample's
+    result is the same, for short and long columns, sums on either side of the clamp and infinities and NaN among the tags."""
+    B, few = 8200, 37
+    f = dol.FnTable.create_dense(W.hashed_table(71, na, nb, n_ids))
+    assert f.kernel_at(False, B) in ("damp_lds_fwd_kernel", "damp_table_fwd_kernel")
+    a = torch.from_numpy((W.uniform01(72, B * na) ** 4 * (6.0 * n_ids / (na * nb))).astype(np.float32).reshape(B, na)).cuda()
+    b = torch.from_numpy(W.uniform01(73, B * nb).astype(np.float32).reshape(B, nb)).cuda()
+    a[few - 1, 1], a[few - 2, 0] = float("nan"), float("inf")
+    whole = dol.Dist.empty(f.out_syms, B)
+    dol.apply2(dol.Dist(np.arange(na), a), dol.Dist(np.arange(nb), b), f, None, whole)
+    for first in (0, B - few):
+        part = dol.Dist.empty(f.out_syms, few)
+        dol.apply2(dol.Dist(np.arange(na), a[first:first + few].contiguous()), dol.Dist(np.arange(nb), b[first:first + few].contiguous()), f, None, part)
+        np.testing.assert_array_equal(host(part.prob).view(np.int32), host(whole.prob[first:first + few].contiguous()).view(np.int32))
+    p = host(whole.prob)
+    assert (p < 1.0).any() and (p == 1.0).any()
+
+
 # ---------------------------------------------------------------- seeded random tables over every kernel choice
 
 @pytest.mark.parametrize("seed", range(24))
