@@ -45,6 +45,15 @@ static void make_packets(int32_t n_cols, const std::vector<uint32_t> &ptr, const
     }
 }
 
+// The most packets that one of a tile's 64 groups of 16 lanes walks, two more for each of its columns' starts.
+static uint32_t longest_group(const std::vector<uint32_t> &pk_ptr, const std::vector<uint32_t> &more)
+{
+    uint32_t work[64] = {}, block = 0;
+    for (const auto *ptr : {&pk_ptr, &more})
+        for (size_t c = 0; c + 4 < ptr->size(); c += 4, ++block) work[block % 64] += (*ptr)[c + 4] - (*ptr)[c] + 2;
+    return *std::max_element(work, work + 64);
+}
+
 // Builds the packet lists of the three gather products.  Leaves tb->lds_fwd_ok / lds_bwd_ok false when the rows
 // and lists are too large for LDS: the direct kernels serve those.
 dol_status lds_plan_build(dol_fn_table *tb, const std::vector<uint32_t> &col_ptr, const std::vector<uint32_t> &col_ij,
@@ -67,6 +76,9 @@ dol_status lds_plan_build(dol_fn_table *tb, const std::vector<uint32_t> &col_ptr
             if ((e = tb->lds_pk.upload(pk)) != hipSuccess || (e = tb->lds_pk_ptr.upload(pk_ptr)) != hipSuccess)
                 return hip_fail(e, "uploading the LDS packet lists");
             tb->lds_fwd_ok = true;
+            // (staging, whose 16-byte pieces span two samples where a row is not a multiple of four; the longest group; all tuples)
+            const double ragged = (na & 3 ? na : 0) + (nb & 3 ? nb : 0);
+            tb->tile_fwd_us = static_cast<float>(4.6 + 0.016 * (na + nb) + 0.022 * ragged + 0.034 * longest_group(pk_ptr, {}) + 1.45e-3 * col_ij.size());
         }
     }
     // backward: rows [gh: S][a: na][b: nb][zeros]
@@ -85,6 +97,7 @@ dol_status lds_plan_build(dol_fn_table *tb, const std::vector<uint32_t> &col_ptr
                 (e = tb->lds_pkb.upload(pkb)) != hipSuccess || (e = tb->lds_pkb_ptr.upload(pkb_ptr)) != hipSuccess)
                 return hip_fail(e, "uploading the LDS packet lists");
             tb->lds_bwd_ok = true;
+            tb->tile_bwd_us = static_cast<float>(5.0 + 0.15 * longest_group(pka_ptr, pkb_ptr) + 1.6e-3 * col_ij.size());
         }
     }
     return DOL_OK;
@@ -397,17 +410,6 @@ static unsigned lds_grid(int n_tiles, size_t lds_bytes)
     const int per_cu = static_cast<int>(kLdsBytesMax / lds_bytes) > 0 ? static_cast<int>(kLdsBytesMax / lds_bytes) : 1;
     const int cap = 256 * per_cu;
     return static_cast<unsigned>(n_tiles < cap ? n_tiles : cap);
-}
-
-// Up to 4 096 samples (8 192 where the per-sample kernel walks a dense map) a workgroup per sample is faster than one per
-// tile of 64: 64 tiles leave most of the chip idle, and a tile's time does not depend on how many there are until each compute
-// unit has one.  Forward / backward in us, per sample against tiles, table 50 x 37 -> 201: B=64 4.3 / 5.1 against 10.4 / 14.4,
-// B=4096 10.5 / 10.0 against 11.1 / 15.1, B=8192 17.9 / 16.7 against 11.5 / 15.3; 442 x 10 -> 785 forward (dense map): B=256
-// 4.8 against 29.6, B=8192 22.8 against 32.7, B=16384 41.6 against 37.9.
-bool lds_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
-{
-    const bool map = backward ? byj_bwd_sample_ok(f) : byj_fwd_sample_ok(f), lists = backward ? list_bwd_sample_ok(f) : list_fwd_sample_ok(f);
-    return batch > 0 && (map || lists) && batch <= (map ? 8192 : 4096);
 }
 
 // *done = the call was taken (otherwise the caller uses the direct kernels).

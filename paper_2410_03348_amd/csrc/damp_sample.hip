@@ -18,6 +18,8 @@
 #include "internal.h"
 #include "wave_util.h"
 
+#include <cmath>
+
 namespace dol {
 
 constexpr int kSmallThreads = 256;      // workgroups of the kernels over rows of fewer than kStageMinRow tags
@@ -1072,13 +1074,47 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
     return DOL_OK;
 }
 
-// Batches that the generated tile kernels (damp_table.hip) leave most of the chip idle with: a tile's time does not depend on
-// how many there are until each compute unit has one.  Apply + Filter + Union both ways, tiles against a workgroup per
-// sample: 64 x 64 -> 256 at B=256 20.0 against 8.0 us, 2048 20.7 / 15.5, 4096 20.9 / 23.4; 32 x 40 -> 128 at B=256 11.8 / 6.3,
-// 2048 12.0 / 8.0, 4096 12.5 / 13.2.  Only tables of which a lane walks every list: their sums are then the tiles' bit for bit.
-bool table_small_batch(const dol_fn_table *f, int64_t batch)
+// What a launch with a workgroup per sample takes, in us, for the choice against tiles of 64 samples, whose time does not
+// depend on how many tiles there are until each compute unit has one (struct dol_fn_table: tile_fwd_us, tile_bwd_us).  Wavefronts
+// come and go at a rate, lists cost by their words, long ones more: fitted to 36 tables from 4 x 4 -> 4 to 442 x 10 -> 785 at 16
+// to 8 192 samples, most within 20 %; dense maps' rows come out up to 1.6 times too long, far from the tiles' time.
+static double sample_fwd_us(const dol_fn_table *f, int64_t batch)
 {
-    return batch <= 3072 && f->lists_ok && f->col_lists.longer.n == 0 && f->row_lists.longer.n == 0;
+    const ListPlan &p = f->col_lists;
+    const double waves = list_threads(p, f->n_out, f->na, batch, list_fwd_bytes(f, true), 512) / static_cast<double>(kWave);
+    const double n_long = static_cast<double>(p.longer.n), longer = p.huge_words + p.mid_words + 48.0 * n_long;   // (in 64s)
+    const double chain = n_long > 0 ? std::ceil(n_long / (4.0 * waves)) * longer / n_long : 0.0;                    // one wavefront's
+    return 3.4 + 7.5e-3 * chain + 0.18e-3 * p.n_words + 0.31e-3 * std::max(0.0, batch * waves - 1500.0) +
+           batch * (0.86e-6 * longer + 0.18e-6 * p.n_words);
+}
+
+static double sample_bwd_us(const dol_fn_table *f, int64_t batch)
+{
+    const ListPlan &p = f->row_lists;
+    const double waves = list_threads(p, f->na + f->nb, f->n_out, batch, gated_bytes(f), 128) / static_cast<double>(kWave);
+    return 3.8 + 0.11e-3 * p.n_words + 0.21e-3 * std::max(0.0, batch * waves - 1500.0) +
+           batch * (0.44e-6 * (p.huge_words + p.mid_words) + 0.13e-6 * p.n_words);
+}
+
+// Tables that damp_lds.hip tiles: a workgroup per sample where that is faster.  (Tiles against samples, us: 50 x 37 -> 201
+// forward B=64 10.3 / 4.3, 4 096 11.0 / 10.2, 8 192 11.4 / 18.2, backward 4 096 15.1 / 8.8, 8 192 15.3 / 15.3; 128 x 128 -> 200
+// forward B=64 33 / 9, 1 024 34 / 34, 4 096 33 / 134; 300 x 8 -> 20 forward 2 048 23 / 11, 8 192 23 / 32; 13 x 12 -> 30 backward
+// 4 096 7.5 / 5.1.  Above 8 192 samples, or 4 096 without a dense map, tiles: from there each sample costs more than its share.)
+bool lds_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
+{
+    if (batch < 1 || !(backward ? byj_bwd_sample_ok(f) || list_bwd_sample_ok(f) : list_fwd_sample_ok(f))) return false;
+    if (batch > (f->byj_ok ? 8192 : 4096)) return false;
+    return backward ? sample_bwd_us(f, batch) < f->tile_bwd_us : sample_fwd_us(f, batch) < f->tile_fwd_us;
+}
+
+// Tables with generated code (damp_table.hip).  Forward the tiles are the faster ones at any batch (64 x 64 -> 256 4.3 us and
+// a workgroup per sample 4.1 to 4.6 up to 512 samples, smaller tables 2.8 and 3.5).  Backward: 64 x 64 -> 256 B=256 12.3 / 4.8,
+// 4 096 12.4 / 11.5; 32 x 40 -> 128 2 048 7.4 / 5.5, 4 096 7.4 / 7.4; 16 x 16 -> 32 3.5 / 4.4.
+bool table_small_batch_bwd(const dol_fn_table *f, int64_t batch)
+{
+    if (batch < 1 || batch > 4096 || !(byj_bwd_sample_ok(f) || list_bwd_sample_ok(f))) return false;
+    const double tiles = 3.0 + 2.5e-3 * static_cast<double>(f->n_tuples) + 6e-3 * f->n_out;
+    return sample_bwd_us(f, batch) < tiles;
 }
 
 // What damp_merge_sample_kernel keeps in LDS: besides the table's rows the whole second Distribution, of up to 65 535 symbols.
@@ -1087,10 +1123,16 @@ static size_t merge_bytes(const dol_fn_table *f, const UnionPlan *p)
     return sizeof(float) * (static_cast<size_t>((2 * f->na + f->nb + 5) & ~3) + f->n_out + p->nb + f->n_out + 1);
 }
 
-// (what does not fit is left to the tiles, which read the second Distribution from memory)
+// Apply + Filter + Union both ways in tiles against a workgroup per sample, us: 64 x 64 -> 256 B=256 20.0 / 7.6, 2 048 20.7 /
+// 15.3, 4 096 20.9 / 23.4; 32 x 40 -> 128 B=256 11.8 / 6.1, 3 072 12.3 / 9.9; 4 x 4 -> 4 up to 3 072 the same.  Only tables of
+// which a lane walks every list: their sums are then the tiles' bit for bit.  What does not fit LDS is left to the tiles, which
+// read the second Distribution from memory; where only one workgroup fits a unit its turns end the gain earlier (32 x 40 -> 128
+// and 40 000 symbols: B=2 048 1 017 / 943, 3 072 1 079 / 1 409).
 bool merge_small_batch(const dol_fn_table *f, const UnionPlan *p, int64_t batch)
 {
-    return table_small_batch(f, batch) && merge_bytes(f, p) <= kStageMaxBytes;
+    const size_t bytes = merge_bytes(f, p);
+    return f->lists_ok && f->col_lists.longer.n == 0 && f->row_lists.longer.n == 0 && bytes <= kStageMaxBytes &&
+           batch <= (2 * bytes <= 160 * 1024 ? 3072 : 2048);
 }
 
 dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b, const float *c,

@@ -615,7 +615,7 @@ dol_status launch_damp_table_fwd(const dol_fn_table *f, int32_t batch, const flo
                                  int64_t ldb, float *out, int64_t ldo, hipStream_t st, bool *done)
 {
     *done = false;
-    if (!table_code_ok(f) || batch < 1 || table_small_batch(f, batch)) return DOL_OK;
+    if (!table_code_ok(f) || batch < 1) return DOL_OK;
     if (lda != f->na || ldb != f->nb || ldo != f->n_out || !aligned16(a) || !aligned16(b) || !aligned16(out)) return DOL_OK;
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, kSlotFwd, build_for(batch), &fn)) return s;
@@ -632,7 +632,7 @@ dol_status launch_damp_table_bwd(const dol_fn_table *f, int32_t batch, const flo
                                  hipStream_t st, bool *done)
 {
     *done = false;
-    if (!table_code_ok(f) || batch < 1 || (ga && ga == gb) || table_small_batch(f, batch)) return DOL_OK;
+    if (!table_code_ok(f) || batch < 1 || (ga && ga == gb) || table_small_batch_bwd(f, batch)) return DOL_OK;
     if (lda != f->na || ldb != f->nb || ldg != f->n_out || !aligned16(a) || !aligned16(b) || !aligned16(g) || !aligned16(ga) ||
         !aligned16(gb))
         return DOL_OK;

@@ -188,6 +188,7 @@ struct dol_fn_table {
     // 16-byte packets of four tuples; *_ptr[x] .. *_ptr[x+1] are the packets of x
     bool lds_fwd_ok = false, lds_bwd_ok = false;
     size_t lds_fwd_bytes = 0, lds_bwd_bytes = 0;
+    float tile_fwd_us = 0.0f, tile_bwd_us = 0.0f;      // what up to 256 tiles take, for the choice against a workgroup per sample
     dol::DevArray<uint32_t> lds_pk, lds_pk_ptr, lds_pka, lds_pka_ptr, lds_pkb, lds_pkb_ptr;
     // Workgroup-per-sample kernels (damp_sample.hip).  Any table of fewer than 65 535 symbols in all: the columns' tuples
     // (i | j << 16; filling (na, nb)), and for every symbol x of a, then of b, (other symbol counted from a's first one |
@@ -333,9 +334,9 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
 dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
                              const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
                              hipStream_t st, bool *done);
-// The same for tables that damp_table.hip generates code for, at batches too small for its tiles; the merged calls take
-// out == nullptr (backward only) or g == nullptr (forward only).
-bool table_small_batch(const dol_fn_table *f, int64_t batch);
+// The choice for tables that damp_table.hip generates code for: a workgroup per sample is faster than tiles, backward and in
+// the merged calls.
+bool table_small_batch_bwd(const dol_fn_table *f, int64_t batch);
 bool merge_small_batch(const dol_fn_table *f, const UnionPlan *p, int64_t batch);
 dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b, const float *c,
                                float *out, int32_t *saved, const float *g, float *ga, float *gb, float *gc, int32_t accumulate, hipStream_t st);

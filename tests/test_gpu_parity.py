@@ -2071,6 +2071,37 @@ def test_a_result_does_not_depend_on_the_batch_it_is_in(dol, na, nb, n_ids):
     assert (p < 1.0).any() and (p == 1.0).any()
 
 
+@pytest.mark.parametrize("na,nb,n_ids,backward", [(128, 128, 200, False), (300, 8, 20, False), (13, 12, 30, False), (100, 100, 50, True),
+                                                  (32, 40, 128, True), (20, 20, 20, True)])
+def test_both_sides_of_the_choice_between_tiles_and_a_workgroup_per_sample(dol, na, nb, n_ids, backward):
+    """The last batch that goes by samples and the first one in tiles: one such place for a table, the earlier the more work
+    its samples are, and the same results on both sides."""
+    tab = W.hashed_table(81, na, nb, n_ids)
+    f = dol.FnTable.create_dense(tab)
+    tiles = f.kernel_at(backward, 100000)
+    assert tiles.startswith(("damp_lds_", "damp_table_"))
+    by_sample = [f.kernel_at(backward, batch) != tiles for batch in range(1, 8300)]
+    few = by_sample.index(False)
+    assert few > 256 and not any(by_sample[few:])
+    for batch in (few, few + 1):
+        a = (W.uniform01(82, batch * na) * (2.0 * n_ids / (na * nb))).astype(np.float32).reshape(batch, na)
+        b = W.uniform01(83, batch * nb).astype(np.float32).reshape(batch, nb)
+        tri = oracle.dense_to_triples(tab)
+        syms, want, pre32, _ = oracle.damp_apply2_fwd(tri, na, nb, a, b, want_pre=True)
+        da, db = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b))
+        out = dol.Dist.empty(syms, batch)
+        dol.apply2(da, db, f, None, out)
+        assert_close(host(out.prob), want, "forward")
+        np.testing.assert_array_equal(host(out.prob) == 1.0, pre32 >= 1.0)
+        if backward:
+            g = np.abs(W.normal(84, batch * syms.size)).astype(np.float32).reshape(batch, -1)
+            wa, wb = oracle.damp_apply2_bwd(tri, na, nb, a, b, g)
+            ga, gb = torch.empty_like(da.prob), torch.empty_like(db.prob)
+            dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), dev(g), ga, gb)
+            assert_close(host(ga), wa, "backward a")
+            assert_close(host(gb), wb, "backward b")
+
+
 # ---------------------------------------------------------------- seeded random tables over every kernel choice
 
 @pytest.mark.parametrize("seed", range(24))
