@@ -883,6 +883,9 @@ static Lists lists_of(const ListPlan &p)
     return Lists{p.order.ptr, p.ptr.ptr, p.words.ptr, p.longer.ptr, p.n_huge, p.n_wave, p.n_mid};
 }
 
+// Workgroups of one launch: it may have 2^32 - 1 threads.  Larger batches go in several.
+constexpr int32_t kMostGroups = 0xffffffffu / kSampleThreads;
+
 // Threads for n lists (a lane each, eight for one that 16 lanes sum) beside the copying of a row: 2 048 for all the workgroups
 // that a unit gets of the launch, or has LDS for.  A workgroup's phases run one after the other, those of several side by
 // side, so more than one to a unit shall mean smaller ones, down to `least` threads.  (B=4 000, us, with 1 024 / 512 / 256 / 128
@@ -905,7 +908,7 @@ static int32_t best_parts(int64_t batch, int most, double row, Work work, unsign
     const int64_t held = kUnits * std::max<int64_t>(1, std::min<int64_t>(2048 / threads, static_cast<int64_t>(160 * 1024 / (lds + 1024))));
     int32_t best = 1;
     double best_cost = 0.0;
-    for (int p = 1; p <= most && batch * p <= 0x7fffffffLL; ++p) {
+    for (int p = 1; p <= most && batch * p <= kMostGroups; ++p) {
         const double cost = static_cast<double>((batch * p + held - 1) / held) * (row + 1500.0 + work(p));
         if (p == 1 || cost < 0.97 * best_cost) { best = p; best_cost = cost; }
     }
@@ -961,6 +964,8 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
     *done = false;
     const bool byj = byj_fwd_sample_ok(f);
     if (!byj && !list_fwd_sample_ok(f)) return DOL_OK;
+    for (; batch > kMostGroups; batch -= kMostGroups, a += kMostGroups * lda, b += kMostGroups * ldb, out += kMostGroups * ldo)
+        if (dol_status s = launch_sample_fwd(f, kMostGroups, a, lda, b, ldb, out, ldo, st, done)) return s;
     SampleFwd A{};
     A.na = f->na, A.nb = f->nb, A.S = f->n_out;
     A.a = a, A.lda = lda, A.b = b, A.ldb = ldb, A.out = out, A.ldo = ldo;
@@ -1022,6 +1027,12 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
     *done = false;
     const bool byj = byj_bwd_sample_ok(f);
     if (!byj && !list_bwd_sample_ok(f)) return DOL_OK;
+    for (; batch > kMostGroups; batch -= kMostGroups) {
+        if (dol_status s = launch_sample_bwd(f, kMostGroups, a, lda, b, ldb, out, ldo, g, ldg, ga, gb, accumulate, st, done)) return s;
+        a += kMostGroups * lda, b += kMostGroups * ldb, out += kMostGroups * ldo, g += kMostGroups * ldg;
+        if (ga) ga += kMostGroups * lda;
+        if (gb) gb += kMostGroups * ldb;
+    }
     SampleBwd A{};
     A.na = f->na, A.nb = f->nb, A.S = f->n_out;
     A.a = a, A.lda = lda, A.b = b, A.ldb = ldb, A.out = out, A.ldo = ldo, A.g = g, A.ldg = ldg, A.ga = ga, A.gb = gb;

@@ -2102,6 +2102,33 @@ def test_both_sides_of_the_choice_between_tiles_and_a_workgroup_per_sample(dol, 
             assert_close(host(gb), wb, "backward b")
 
 
+def test_more_samples_than_one_launch_has_workgroups(dol):
+    """A workgroup per sample for one sample more than a launch of 2^32 - 1 threads holds at 1 024 threads each: the samples
+    around the border and at both ends."""
+    B, na, nb, n_ids = (1 << 22), 700, 1, 5
+    if torch.cuda.mem_get_info()[0] < 40 << 30:
+        pytest.skip("needs 30 GB of GPU memory")
+    tab = W.hashed_table(91, na, nb, n_ids)
+    f = dol.FnTable.create_dense(tab)
+    assert not f.kernel_at(False, B).startswith(("damp_lds", "damp_table", "damp_conv"))
+    rows = (W.uniform01(92, 1024 * na) * 0.01).astype(np.float32).reshape(1024, na)
+    a = dev(rows).repeat(B // 1024, 1)
+    b = torch.ones(B, nb, device="cuda")
+    tri = oracle.dense_to_triples(tab)
+    g = np.abs(W.normal(93, 1024 * n_ids)).astype(np.float32).reshape(1024, -1)
+    _, want, pre32, _ = oracle.damp_apply2_fwd(tri, na, nb, rows, np.ones((1024, nb), np.float32), want_pre=True)
+    wa, wb = oracle.damp_apply2_bwd(tri, na, nb, rows, np.ones((1024, nb), np.float32), g)
+    da, db = dol.Dist(np.arange(na), a), dol.Dist(np.arange(nb), b)
+    out = dol.Dist(f.out_syms, torch.full((B, f.n_out), -1.0, device="cuda"))
+    dol.apply2(da, db, f, None, out)
+    ga, gb = torch.full_like(a, -1.0), torch.full_like(b, -1.0)
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), dev(g).repeat(B // 1024, 1), ga, gb)
+    for first in (0, B - 1024):                     # (the border lies in the last 1 024)
+        assert_close(host(out.prob[first:first + 1024]), want, "forward")
+        assert_close(host(ga[first:first + 1024]), wa, "backward a")
+        assert_close(host(gb[first:first + 1024]), wb, "backward b")
+
+
 # ---------------------------------------------------------------- seeded random tables over every kernel choice
 
 @pytest.mark.parametrize("seed", range(24))
