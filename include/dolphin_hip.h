@@ -162,7 +162,8 @@ dol_status dol_filter_union(const dol_dist *d, const uint8_t *pred_mask, const d
  *   out         n_sym and sym_ids as dol_filter_union_plan gives for (a Distribution over f's symbols, pred_mask, c)
  *   saved       device [batch] int32 or NULL: the forward call leaves 1 for a sample in which some clamp acted (a sum
  *               of the Apply or of the union above 1) and 0 otherwise; the reverse call reads it and re-derives the
- *               clamp decisions only for tiles of 64 samples that hold such a sample (with NULL: for every tile)
+ *               clamp decisions only where one is marked: for that sample alone at small batches, which take a workgroup per
+ *               sample, else for its tile of 64 or 32 samples (with NULL: for every sample)
  * dol_apply2_filter_union_backward: grad_out device [batch, grad_out_ld] w.r.t. out; grad_a, grad_b, grad_c device
  * [batch, n_sym] of a, b, c, each overwritten, or added to where `accumulate` has bit 0, 1, 2 set; any may be NULL.
  *   gh = grad_out gated by the union's clamp (symbols of both sides) -> grad_c, and, for the kept symbols of the

@@ -1,11 +1,13 @@
 // DAMP provenance kernels (Sec. 3.2, Table 1: conjunction t*t', disjunction min(1, t+t')) for gfx950:
-// Apply with an arbitrary function table, Filter, Union and their vector-Jacobian products.
+// Apply with an arbitrary function table and its vector-Jacobian products, for what no other form takes (operand or result
+// rows beyond LDS); the entry points of Apply, which try those forms first: sums of digits (damp_conv.hip), code generated
+// for small tables (damp_table.hip), tiles of samples (damp_lds.hip), a workgroup per sample (damp_sample.hip).  Filter and
+// Union are in damp_rows.hip.
 //
 // Thread mapping: one thread per (sample, output element), consecutive lanes on consecutive elements of one
 // row, so that every store is coalesced and, for tables with regular structure (grids), lane-adjacent gathers
 // touch adjacent addresses.  A workgroup owns a chunk of whole rows (about 2048 elements) and splits its
 // flat element index into (row, column) with a float reciprocal, which is exact for such small indices.
-// Sum-shaped tables take the LDS kernels of damp_conv.hip instead.
 #include "element_map.h"
 #include "internal.h"
 #include "wave_util.h"

@@ -13,7 +13,8 @@
 //
 // Any shape is taken: symbol counts need not be multiples of four, rows may be padded (ld > n_sym), the batch
 // need not be a multiple of the tile.  Contiguous 16-byte aligned tensors are staged with 16-byte loads and
-// written with 16-byte stores; others element by element.
+// written with 16-byte stores; others element by element.  A tile takes as long whether there is one or one for every
+// compute unit; where a workgroup per sample is faster, damp_sample.hip takes the call (lds_small_batch there).
 #include "internal.h"
 #include "wave_util.h"
 

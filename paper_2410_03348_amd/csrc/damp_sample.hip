@@ -10,9 +10,10 @@
 //   * second operands of at most 16 symbols: dense maps, one j at a time, four neighbouring columns (rows) a thread, so
 //     that a map entry costs two bytes of an 8-byte load and results leave as 16-byte stores;
 //   * other tables: tuple lists of columns (rows) sorted by length inside blocks of 4 096 and interleaved in chunks of 64
-//     (struct ListPlan), so that a wavefront's tuples are one 256-byte load and its lanes end together; the forward results of a block meet in LDS and leave in column order.
+//     (struct ListPlan), so that a wavefront's tuples are one 256-byte load and its lanes end together; the forward results
+//     of a block meet in LDS and leave in column order.
 // Lists longer than 64 tuples are summed by 16 lanes, those above 512 by a wavefront or the workgroup (struct ListPlan), in the
-// same launch.
+// same launch; forward, where tiles of samples serve the table in large batches, in the order of definition (ChainColumns).
 // Empty map entries and the words past a list's end name one slot past the row, which holds 0.
 #include "element_map.h"
 #include "internal.h"

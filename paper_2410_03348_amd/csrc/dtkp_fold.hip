@@ -90,7 +90,8 @@ __device__ __forceinline__ void sort_valley(float (&p)[K], int (&id)[K], int at)
 // cut, are the only cases in which masks matter: such a tuple is redone candidate by candidate from the list before it.
 // (Compare/select code bound by the vector ALUs: k = 5 costs about 65 instructions a tuple, against 5 x 33 when every
 // candidate was inserted by itself.  Sum-5, k = 3, B = 1024: 16.2 -> 10.5 us a pass; Sum-6, k = 5 with a target's
-// gradient, B = 12 000: 870 -> 132 us, of which the gradient, which walked every proof of every column, was most.)
+// gradient, B = 12 000: 870 -> 132 us, of which the gradient, which walked every proof of every column, was most; 87
+// since the merge network exchanges loaded values instead of choosing between array elements.)
 template <int K, int KA, bool FRESH>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,

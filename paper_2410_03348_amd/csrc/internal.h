@@ -335,7 +335,7 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
                              const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
                              hipStream_t st, bool *done);
 // The choice for tables that damp_table.hip generates code for: a workgroup per sample is faster than tiles, backward and in
-// the merged calls.
+// the merged calls, whose launch takes out == nullptr (backward only) or g == nullptr (forward only).
 bool table_small_batch_bwd(const dol_fn_table *f, int64_t batch);
 bool merge_small_batch(const dol_fn_table *f, const UnionPlan *p, int64_t batch);
 dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b, const float *c,

@@ -13,7 +13,8 @@
 namespace dol {
 
 // Hash of a key, eight bytes at a time (a byte-wise hash of a kilobyte of symbol ids costs as much as a launch): multiply,
-// fold the high half down, finish with one more round.  Equal keys are compared byte by byte, so only speed rests on it.
+// fold the high half down, finish with one more round (multiplier and fold by 32 as in the published 64-bit mixer degski64,
+// the start is 2^64 over the golden ratio).  Equal keys are compared byte by byte, so only speed rests on it.
 inline uint64_t hash_bytes(const void *data, size_t n)
 {
     const unsigned char *p = static_cast<const unsigned char *>(data);
