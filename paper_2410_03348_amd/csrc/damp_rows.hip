@@ -7,7 +7,9 @@
 // Bound by the latency of the maps and of a few batches of loads, then by memory.  (Tiles of rows copied into LDS, four
 // neighbouring results per lane, spent 60 % of the LDS clocks on bank conflicts and more instructions on splitting every
 // index: 10 007 rows of 196, Filter 5.4 us, Union 7.4, backwards 10.7; here 4.5, 5.9, 9.9.  Rows of 16 at 32 000: 42.5 us
-// for the six launches of a pipeline, 24 here.)
+// for the six launches of a pipeline, 24 here.  At 262 144 rows of 256, of which 3/4 are kept: Filter 84 and 86
+// backwards, where dropped columns that read the result's old row, to throw it away, cost 136; Union 151 and 239 (168 and 262
+// in tiles).  Rows in several chunks lose there: 100 000 of 700, Filter backwards 98 (77 in tiles), Union 168 (150) and 228 (313).)
 #include "internal.h"
 
 #include <algorithm>
@@ -80,6 +82,15 @@ struct Walk {
     }
 };
 
+// The column that a lane without one (x < 0) reads instead, to throw it away: another lane's, whose line is fetched anyway;
+// -1 where no lane of the wavefront has one.
+__device__ __forceinline__ int stand_in(int x)
+{
+    const uint64_t there = __ballot(x >= 0);
+    const int other = __shfl(x, there ? __builtin_ctzll(there) : 0);
+    return x >= 0 ? x : there ? other : -1;
+}
+
 // load(u) takes the next row's operands as number u, put(u) stores its result.  (Neither branches: with branches around
 // the loads the compiler waits for each.)
 template <class Load, class Put>
@@ -107,8 +118,9 @@ damp_rows_gather_kernel(RowCols R, const int32_t *__restrict__ src_col, const fl
     if (p.n <= 0) return;
     const int32_t i = src_col[p.c];
     Walk<float> dst(out, ldo, p, R.per, p.c), old = dst;
-    Walk<const float> src(in, ldi, p, R.per, i);
-    if (i < 0) src.at = dst.at, src.step = dst.step;        // (read and thrown away)
+    const int32_t from = stand_in(i);
+    Walk<const float> src(in, ldi, p, R.per, from);
+    if (from < 0) src.at = dst.at, src.step = dst.step;
     float v[kAhead], o[kAhead];
     over_rows(p.n,
               [&](int u) {
@@ -155,8 +167,9 @@ damp_rows_union_bwd_kernel(RowCols R, int32_t na, const int32_t *__restrict__ ia
     const int32_t i = c >= 0 ? ia[c] : -1, j = c >= 0 ? ib[c] : -1;
     const bool both = i >= 0 && j >= 0, add = ADD && (accumulate & (is_a ? 1 : 2)) != 0;
     Walk<float> dst(is_a ? ga : gb, is_a ? lda : ldb, p, R.per, x), old = dst;
-    Walk<const float> xg(g, ldg, p, R.per, c);
-    if (c < 0) xg.at = dst.at, xg.step = dst.step;
+    const int32_t from = stand_in(c);
+    Walk<const float> xg(g, ldg, p, R.per, from);
+    if (from < 0) xg.at = dst.at, xg.step = dst.step;
     Walk<const float> xa(a, lda, p, R.per, i), xb(b, ldb, p, R.per, j);
     if (!both) xa = xb = xg;
     float gv[kAhead], o[kAhead], va[kAhead], vb[kAhead];

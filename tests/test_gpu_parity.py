@@ -2270,6 +2270,42 @@ def test_filter_and_union_of_any_width(dol, batch, n, pad):
         assert torch.equal(x, gate[:, :n]) if x is not None else torch.equal(y, gate[:, lo:])
 
 
+@pytest.mark.parametrize("batch,n", [(1, 64), (70, 40), (5, 300), (600, 200), (3, 1100)])
+@pytest.mark.parametrize("kept_at", ["none", "first", "last", "every 70th"])
+def test_filter_backward_where_few_columns_have_a_source(dol, batch, n, kept_at):
+    """Wavefronts of columns of which none, one or a few were kept; the fused filter-union's reverse beside it, and tags of NaN
+    and infinity in the operand, which no dropped column may pick up."""
+    keep = np.zeros(n, np.uint8)
+    keep[{"none": [], "first": [0], "last": [n - 1], "every 70th": list(range(0, n, 70))}[kept_at]] = 1
+    a = dol.Dist(np.arange(n), dev((W.uniform01(1, batch * n) * 0.8).astype(np.float32).reshape(batch, n)))
+    a.prob[:, keep == 0] = float("nan")
+    kept = dol.Dist.empty(np.flatnonzero(keep), batch) if keep.any() else dol.Dist(np.empty(0, np.int32), torch.empty((batch, 0), device="cuda"))
+    at = torch.as_tensor(np.flatnonzero(keep), device="cuda")
+    g = dev(W.normal(2, batch * kept.n_sym).astype(np.float32).reshape(batch, -1))
+    want = torch.zeros_like(a.prob)
+    want[:, at] = g
+    ga = torch.full_like(a.prob, float("nan"))
+    for acc in (0, 1):
+        dol.backward(dol.OpRecord(dol.OP_FILTER, a, None, kept, pred_mask=keep, accumulate=acc), g, ga, None)
+        assert torch.equal(ga, (1 + acc) * want)
+    c = dol.Dist(np.arange(n // 2, n // 2 + n), dev((W.uniform01(3, batch * n) * 0.8).astype(np.float32).reshape(batch, n)))
+    u = dol.Dist.empty(dol.filter_union_plan(a, keep, c), batch)
+    dol.filter_union(a, keep, c, None, u)
+    g = dev(W.normal(4, batch * u.n_sym).astype(np.float32).reshape(batch, -1))
+    gc = torch.full_like(c.prob, float("nan"))
+    dol.backward(dol.OpRecord(dol.OP_FILTER_UNION, a, c, u, pred_mask=keep), g, ga, gc)
+    pos = {int(x): i for i, x in enumerate(u.sym_ids)}
+    wa, wc = torch.zeros_like(a.prob), g[:, [pos[int(x)] for x in c.sym_ids]].clone()
+    for x in np.flatnonzero(keep):
+        gx = g[:, pos[int(x)]].clone()
+        if x >= n // 2:
+            over = a.prob[:, x] + c.prob[:, x - n // 2] > 1.0
+            gx[over] = 0.0
+            wc[over, x - n // 2] = 0.0
+        wa[:, x] = gx
+    assert torch.equal(ga, wa) and torch.equal(gc, wc)
+
+
 @pytest.mark.parametrize("batch,lengths", [(1, (4, 5)), (1, (16, 17)), (3, (1, 16, 17, 64, 65, 5, 4)), (9, (1025, 2, 1024, 65, 64, 17, 40, 33, 3, 5, 4, 7)), (5, (1500,) + (20,) * 33)])
 def test_dtkp_columns_of_every_length(dol, batch, lengths):
     """A lane, 4 lanes, 16, a wavefront and a workgroup per column in one launch: lengths on both sides of each limit, groups of
