@@ -240,6 +240,77 @@ def test_fused_fold_with_masses_on_either_side_of_one(dol, B, n, loss):
         assert_close(host(gins[t])[kept], want[t][kept], "fold grad %d" % t)
 
 
+@pytest.mark.parametrize("B", [5, 8203])
+@pytest.mark.parametrize("kind", ["calm", "large", "clamped"])
+@pytest.mark.parametrize("widths", [[10] * 15, [3, 10], [255, 16], [40, 1, 16, 16], [1, 1, 2], [16] * 9, [7] * 18, [2, 13, 1, 5, 16, 3, 9, 9, 9]],
+                         ids=lambda w: "%dx%d" % (len(w), max(w)))
+def test_fold_code_for_chain_shapes(dol, widths, kind, B):
+    """The code written for a chain: blocks of every width and changes between them, short operands of 1 to 16 symbols, rows
+    that wait in LDS, both builds (the larger batch takes the one for large grids), rows apart by different distances,
+    targets on either end and outside, a target of probability 0.  calm: no sum reaches 1, the late stages count from the
+    target; large: the same with a first operand so small that the others' sums may exceed 2, where they do not; clamped:
+    sums beyond 1.  A third of the samples, the last ones among them, are looked at.
+    Tolerance: sums of non-negative terms, at most 16 x 18 multiply-adds deep, and products with one upstream value: 300 x
+    6e-8 < 2e-5 relative; with an explicit gradient of one sign the same."""
+    n, look = len(widths), np.unique(np.concatenate([np.arange(0, B, 3), np.arange(max(0, B - 9), B)]))
+    scale = {"calm": np.ones(n), "large": np.r_[0.9 / 3.0 ** (n - 1), np.full(n - 1, 3.0)], "clamped": np.r_[1.0, np.where(np.arange(1, n) % 2, 1.7, 0.6)]}[kind]
+    ins = []
+    for t, m in enumerate(widths):
+        x = W.uniform01(60 + t, B * m).reshape(B, m) + 0.01
+        ins.append((x / x.sum(axis=1, keepdims=True) * scale[t] * 0.998 ** (1.0 / n)).astype(np.float32))
+    if kind == "clamped" and widths[0] > 1:
+        ins[0][:, 1:], ins[0][:, 0] = 0.0, 1.0
+        for t in range(1, n):
+            ins[t][1::2, 1:] = 0.0
+            ins[t][1::2, 0] = scale[t]
+    ins[-1][2, :] = 0.0
+    syms = [np.arange(m, dtype=np.int32) for m in widths]
+    tabs, tris, accs, cur, kept = [], [], [ins[0][look]], syms[0], np.ones(look.size, bool)
+    for t in range(1, n):
+        tabs.append(W.sum_table(cur, syms[t]))
+        tris.append(oracle.dense_to_triples(tabs[-1]))
+        cur, o, _, pre = oracle.damp_apply2_fwd(tris[-1], tabs[-1].shape[0], tabs[-1].shape[1], accs[-1], ins[t][look], want_pre=True)
+        accs.append(o)
+        kept &= (np.abs(pre - 1.0) > 2e-5).all(axis=1) | (kind != "clamped")
+    assert kept.mean() > 0.4
+    d_in, gins = [], []
+    for t, m in enumerate(widths):
+        pad = (0, 3, 3, 1)[t % 4]
+        buf = torch.zeros((B, m + pad), device="cuda")
+        buf[:, :m] = dev(ins[t])
+        d_in.append(dol.Dist(syms[t], buf[:, :m]))
+        gins.append(torch.full((B, m + pad), 7.0, device="cuda"))
+    ftabs, out = [dol.FnTable.create_dense(t) for t in tabs], dol.Dist.empty(cur, B)
+    target = (W.uniform01(9, B) * cur.size).astype(np.int32)
+    target[0], target[1], target[3], target[4] = 0, cur.size - 1, -1, cur.size
+    assert np.all(accs[-1][look == 2] == 0.0)
+    g_t = np.zeros((look.size, cur.size), np.float32)
+    for r, s in enumerate(look):
+        if 0 <= target[s] < cur.size:
+            p32 = np.float32(accs[-1][r, target[s]])
+            g_t[r, target[s]] = np.float32(-1.0) / np.maximum(p32, np.float32(1.17549435e-38))
+    g_x = (np.abs(W.normal(5, B * cur.size)) + 0.1).astype(np.float32).reshape(B, -1)
+    for which in ("target", "grad_out"):
+        for g in gins:
+            g.fill_(7.0)
+        if which == "target":
+            dol.fold_apply2(dol.Fold(d_in, ftabs, out=out, target_col=dev(target), grad_inputs=gins))
+        else:
+            dol.fold_apply2(dol.Fold(d_in, ftabs, out=out, grad_out=dev(g_x), grad_inputs=gins))
+        want, gr = [None] * n, (g_t if which == "target" else g_x[look])
+        for t in range(n - 1, 0, -1):
+            gr, want[t] = oracle.damp_apply2_bwd(tris[t - 1], tabs[t - 1].shape[0], tabs[t - 1].shape[1], accs[t - 1], ins[t][look], gr)
+        want[0] = gr
+        got = host(out.prob)[look]
+        assert np.all(np.abs(got - accs[-1])[kept] <= 2e-5 * accs[-1][kept] + 1e-37)
+        np.testing.assert_array_equal(got[kept] == 1.0, accs[-1][kept] == 1.0)
+        for t, m in enumerate(widths):
+            x = host(gins[t])
+            assert np.all(x[:, m:] == 7.0)
+            bad = np.abs(x[look, :m] - want[t]) > 2e-5 * np.abs(want[t]) + 1e-30
+            assert not bad[kept].any(), "%s: grad %d" % (which, t)
+
+
 # ---------------------------------------------------------------- config 3
 
 @pytest.mark.parametrize("batch,na,nb,n_out", [(16384, 64, 64, 256), (1000, 64, 64, 256), (129, 17, 33, 40), (3, 5, 2, 300)])
