@@ -25,8 +25,9 @@ constexpr int kDfWaves = 4;             // most wavefronts (samples) of one work
 //   [0] number of inputs n, then for t = 0 .. n-1 four words: S_t, p_t, r_t, fresh_t
 //   t = 0:  S_0 words at p_0: the facts of the first input's symbols
 //   t >= 1: S_t + 1 words at p_t: where each output column's tuples start and end inside the stage's records;
-//           the records at r_t, one per tuple in column order: first operand's symbol | second operand's FACT << 16
-//           (two spare records at the end so that the read-ahead stays inside)
+//           the records at r_t, one per tuple in column order: the first operand's list, counted in bytes of
+//           probabilities, | 4 x the second operand's FACT << 16 (two spare records at the end so that the read-ahead
+//           stays inside)
 //   fresh_t = 1: every fact of input t lies above every fact of the inputs before it and shares no exclusion group
 //           with any of them.  A proof of the running Distribution then never holds the new fact or a rival of it, and
 //           the product over ascending facts is the proof's stored probability times the new fact's: the stage needs
@@ -45,57 +46,68 @@ struct DtkpFoldArgs {
     float *gfact;
 };
 
-// Sorts p[0 .. N-1] (with the ids beside them) in descending order when p falls and then rises, as the elementwise maxima
-// of a descending and an ascending list do: the bitonic network of the next power of two with its tail taken as +infinity,
-// of which only the exchanges between real entries remain (2 for N = 3, 5 for N = 5, 9 for N = 7).
-template <int N, int K>
-__device__ __forceinline__ void sort_valley(float (&p)[K], int (&id)[K], int at)
+// A proof as one number that ranks: its probability's bits above, where it came from below.  For numbers of one sign that is
+// the order of the probabilities, equal ones apart (negative ones stand for absent proofs), and the larger and the smaller of
+// two cost an instruction each, where comparing probabilities and choosing both words costs five.
+__device__ __forceinline__ double key_of(float p, int id) { return __hiloint2double(__float_as_int(p), id); }
+__device__ __forceinline__ double key_max(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));      // (fmax makes either operand quiet first)
+    return r;
+}
+__device__ __forceinline__ double key_min(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Sorts k[at .. at + N) in descending order when it falls and then rises, as the elementwise maxima of a descending and an
+// ascending list do: the bitonic network of the next power of two with its tail taken as +infinity, of which only the
+// exchanges between real entries remain (4 for N = 4, 7 for N = 6, 12 for N = 8).
+template <int N, int L>
+__device__ __forceinline__ void sort_valley(double (&k)[L], int at)
 {
     if constexpr (N > 1) {
-        constexpr int M = N > 4 ? 4 : N > 2 ? 2 : 1;     // half of the next power of two: N <= 8
+        constexpr int M = N > 8 ? 8 : N > 4 ? 4 : N > 2 ? 2 : 1;     // half of the next power of two
         constexpr int H = N - M;
-        float hp[H], lp[M];
-        int hi[H], li[M];
+        double hi[H], lo[M];
 #pragma unroll
         for (int x = 0; x < M; ++x) {
             if (x < H) {
-                const int xh = x < H ? x : 0;
-                // (values first: a choice between array elements becomes a chain of selects over the whole array)
-                const float pa = p[at + x], pb = p[at + x + M];
-                const int ia = id[at + x], ib = id[at + x + M];
-                const bool keep = pa > pb;
-                hp[xh] = keep ? pa : pb, lp[x] = keep ? pb : pa;
-                hi[xh] = keep ? ia : ib, li[x] = keep ? ib : ia;
+                const double a = k[at + x], b = k[at + x + M];
+                hi[x < H ? x : 0] = key_max(a, b), lo[x] = key_min(a, b);
             } else {
-                lp[x] = p[at + x], li[x] = id[at + x];
+                lo[x] = k[at + x];
             }
         }
 #pragma unroll
-        for (int x = 0; x < H; ++x) p[at + x] = hp[x], id[at + x] = hi[x];
+        for (int x = 0; x < H; ++x) k[at + x] = hi[x];
 #pragma unroll
-        for (int x = 0; x < M; ++x) p[at + H + x] = lp[x], id[at + H + x] = li[x];
-        sort_valley<H, K>(p, id, at);
-        sort_valley<M, K>(p, id, at + H);
+        for (int x = 0; x < M; ++x) k[at + H + x] = lo[x];
+        sort_valley<H, L>(k, at);
+        sort_valley<M, L>(k, at + H);
     }
 }
 
 // One stage of the fold for this wavefront's sample: the columns of the stage's table, a lane each.  KA: slots of the
 // first operand's lists that can hold a proof (1 right after the natural initialisation); FRESH: see fresh_t above.
-// Absent slots carry the probability -1 in LDS (0 in the result tensors); in the registers slot x is -1 - x, so that
-// absent slots never tie.
+// Absent slots carry the probability -1 in LDS (0 in the result tensors).
 // The list keeps, per rank, the probability and where the proof came from (record, slot of the first operand's list);
 // the masks are put together for the k winners only.  In a FRESH stage a tuple's k candidates are the first operand's
-// list times one factor, i.e. in descending order already: the k best of both lists are the elementwise maxima of one and
-// the other reversed, sorted again by a short network.  Equal probabilities among the kept ones, or on either side of the
-// cut, are the only cases in which masks matter: such a tuple is redone candidate by candidate from the list before it.
-// (Compare/select code bound by the vector ALUs: k = 5 costs about 65 instructions a tuple, against 5 x 33 when every
-// candidate was inserted by itself.  Sum-5, k = 3, B = 1024: 16.2 -> 10.5 us a pass; Sum-6, k = 5 with a target's
-// gradient, B = 12 000: 870 -> 132 us, of which the gradient, which walked every proof of every column, was most; 87
-// since the merge network exchanges loaded values instead of choosing between array elements.)
+// list times one factor, i.e. in descending order already: the k + 1 best of both lists are the elementwise maxima of one
+// and the other reversed, sorted again by a short network.  Masks matter only where probabilities are equal: two of the kept
+// ones, or the last one and the best that dropped out, which is what the list's entry behind the k-th holds (of all that
+// dropped out on the way none is larger).  Such a column is done again, candidate by candidate (exact_column), and so is
+// every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number.
+// (Bound by the vector ALUs.  k = 5 costs about 35 instructions a tuple, none of them a choice; 65 with probabilities and
+// origins exchanged by compare and select, which the units take 1.9 ns a piece for, and repeated choices by one condition
+// longer.)
 template <int K, int KA, bool FRESH>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,
-                                                float *np, const uint64_t *rival, const float *fp, float *gh)
+                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain)
 {
     const int lane = threadIdx.x & (kWave - 1);
     for (int c = lane; c < S; c += kWave) {
@@ -105,7 +117,7 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
         for (int x = 0; x < K; ++x) { tp[x] = -1.0f - x; tid_[x] = -1; }
         auto mask_of = [&](int id) -> uint64_t {            // id = record << 3 | slot (at most DOL_MAX_K = 8 slots)
             const uint32_t r = l_rec[id >> 3];
-            return cm[static_cast<int>(r & 0xffffu) * K + (id & 7)] | (uint64_t(1) << (r >> 16));
+            return cm[static_cast<int>((r & 0xffffu) >> 2) + (id & 7)] | (uint64_t(1) << (r >> 18));
         };
         // the full comparison: equal masks are one proof, order by probability, then by mask
         auto insert_tied = [&](uint64_t mask, float pr, int id) {
@@ -141,75 +153,91 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
             }
         };
         const uint32_t q0 = l_ptr[c], q1 = l_ptr[c + 1];
+        auto list_of = [&](uint32_t r) { return reinterpret_cast<const float *>(reinterpret_cast<const char *>(cp) + (r & 0xffffu)); };
+        auto fact_of = [&](uint32_t r) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(fp) + (r >> 16)); };
         if constexpr (FRESH) {
-            // a tuple's record is read two tuples ahead and its operands one ahead; records past the last one are the
-            // spare ones behind every array, which name operands that exist
-            float pa[KA], pb;
-            auto fetch = [&](uint32_t r) {
-                pb = fp[r >> 16];
+            auto exact_column = [&]() {
 #pragma unroll
-                for (int x = 0; x < KA; ++x) pa[x] = cp[static_cast<int>(r & 0xffffu) * K + x];
-            };
-            uint32_t rec = l_rec[q0], rec_next = l_rec[q0 + 1];
-            fetch(rec);
-            for (uint32_t q = q0; q < q1; ++q) {
-                const uint32_t cur = rec;
-                float offer[KA];
-#pragma unroll
-                for (int x = 0; x < KA; ++x) offer[x] = pa[x] >= 0.0f ? pa[x] * pb : kNone;
-                rec = rec_next;
-                rec_next = l_rec[q + 2];
-                fetch(rec);
-                const int id0 = static_cast<int>(q) << 3;
-                bool tie = false;
-                if constexpr (KA == K && K > 1) {
-                    float mp[K];
-                    int mi[K];
-                    float cut = 2.0f * kNone;           // the best of the candidates and kept ones that drop out
-#pragma unroll
-                    for (int x = 0; x < K; ++x) {
-                        const float o = offer[K - 1 - x], t = tp[x];
-                        const int i_o = id0 + (K - 1 - x), i_t = tid_[x];
-                        const bool keep = t > o;
-                        mp[x] = keep ? t : o;
-                        mi[x] = keep ? i_t : i_o;
-                        cut = fmaxf(cut, keep ? o : t);
-                    }
-                    sort_valley<K, K>(mp, mi, 0);
-#pragma unroll
-                    for (int x = 0; x + 1 < K; ++x) tie |= mp[x] == mp[x + 1];
-                    tie |= mp[K - 1] == cut;
-                    if (!tie) {
-#pragma unroll
-                        for (int x = 0; x < K; ++x) { tp[x] = mp[x]; tid_[x] = mi[x]; }
-                    }
-                } else {
-#pragma unroll
-                    for (int y = 0; y < K; ++y) tie |= offer[0] == tp[y];
-                    insert_untied(tie ? kNone : offer[0], id0);
-                }
-                if (__builtin_expect(tie, 0)) {
-#pragma unroll
+                for (int x = 0; x < K; ++x) { tp[x] = -1.0f - x; tid_[x] = -1; }
+                for (uint32_t q = q0; q < q1; ++q) {
+                    const uint32_t cur = l_rec[q];
+                    const float *pa = list_of(cur);
+                    const float pb = fact_of(cur);
+#pragma unroll 1
                     for (int x = 0; x < KA; ++x) {
-                        if (offer[x] < 0.0f) continue;
-                        bool t2 = false;
+                        if (!(pa[x] >= 0.0f)) continue;
+                        const float offer = pa[x] * pb;
+                        const int id = static_cast<int>(q) << 3 | x;
+                        bool tie = false;
 #pragma unroll
-                        for (int y = 0; y < K; ++y) t2 |= offer[x] == tp[y];
-                        if (t2) insert_tied(cm[static_cast<int>(cur & 0xffffu) * K + x] | (uint64_t(1) << (cur >> 16)), offer[x], id0 | x);
-                        else insert_untied(offer[x], id0 | x);
+                        for (int y = 0; y < K; ++y) tie |= offer == tp[y];
+                        if (tie) insert_tied(mask_of(id), offer, id);
+                        else insert_untied(offer, id);
                     }
                 }
+            };
+            if (plain) {
+                // a tuple's record is read two tuples ahead and its operands one ahead; records past the last one are the
+                // spare ones behind every array, which name operands that exist
+                double top[K + 1];
+#pragma unroll
+                for (int x = 0; x <= K; ++x) top[x] = -1.0;
+                float pa[KA], pb;
+                auto fetch = [&](uint32_t r) {
+                    pb = fact_of(r);
+                    const float *list = list_of(r);
+#pragma unroll
+                    for (int x = 0; x < KA; ++x) pa[x] = list[x];
+                };
+                uint32_t rec = l_rec[q0], rec_next = l_rec[q0 + 1];
+                fetch(rec);
+                for (uint32_t q = q0; q < q1; ++q) {
+                    double offer[KA];       // (an absent proof's is negative or -0: below every proof)
+#pragma unroll
+                    for (int x = 0; x < KA; ++x) offer[x] = key_of(pa[x] * pb, static_cast<int>(q) << 3 | x);
+                    rec = rec_next;
+                    rec_next = l_rec[q + 2];
+                    fetch(rec);
+                    if constexpr (KA == K && K > 1) {
+                        double best[K + 1];
+                        best[0] = top[0];
+#pragma unroll
+                        for (int x = 1; x <= K; ++x) best[x] = key_max(top[x], offer[K - x]);
+                        sort_valley<K + 1, K + 1>(best, 0);
+#pragma unroll
+                        for (int x = 0; x <= K; ++x) top[x] = best[x];
+                    } else {
+                        double o = offer[0];
+#pragma unroll
+                        for (int x = 0; x <= K; ++x) {
+                            const double t = top[x];
+                            top[x] = key_max(t, o);
+                            if (x < K) o = key_min(t, o);
+                        }
+                    }
+                }
+                bool tie = false;
+#pragma unroll
+                for (int x = 0; x < K; ++x) {
+                    const int hi = __double2hiint(top[x]), next = __double2hiint(top[x + 1]);
+                    tp[x] = __int_as_float(hi);
+                    tid_[x] = hi >= 0 ? __double2loint(top[x]) : -1;
+                    tie |= hi == next && hi >= 0;
+                }
+                if (__builtin_expect(tie, 0)) exact_column();
+            } else {
+                exact_column();
             }
         } else {
             uint32_t rec = l_rec[q0];
             for (uint32_t q = q0; q < q1; ++q) {
-                const int i = static_cast<int>(rec & 0xffffu), fb = static_cast<int>(rec >> 16);
+                const int i = static_cast<int>((rec & 0xffffu) >> 2), fb = static_cast<int>(rec >> 18);
                 rec = l_rec[q + 1];                 // the next tuple's record is on its way while this one is worked on
                 const float pb = fp[fb];
                 uint64_t ma[KA];
                 float pa[KA];
 #pragma unroll
-                for (int x = 0; x < KA; ++x) { ma[x] = cm[i * K + x]; pa[x] = cp[i * K + x]; }
+                for (int x = 0; x < KA; ++x) { ma[x] = cm[i + x]; pa[x] = cp[i + x]; }
                 const uint64_t mb = uint64_t(1) << fb, bad = rival[fb];
                 // kept proofs hold at most one fact per exclusion group, so the union is inconsistent exactly when
                 // the first operand's proof holds a rival of the one fact the second brings.  The product over
@@ -292,6 +320,7 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         if (threadIdx.x < 64) rival[threadIdx.x] = static_cast<int>(threadIdx.x) < A.n_facts ? A.rival[threadIdx.x] : 0;
     }
     fp[lane] = my_fp;
+    const bool plain = __ballot(__float_as_uint(my_fp) >= 0x7f800000u) == 0;
     __syncthreads();
     if (!live) return;                          // no barrier of the workgroup follows
     {   // natural initialisation (App. A.1)
@@ -316,11 +345,11 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         const uint32_t *l_ptr = w + w[2 + 4 * t], *l_rec = w + w[3 + 4 * t];
         const bool last = t == A.n - 1, fresh = __builtin_amdgcn_readfirstlane(static_cast<int>(w[4 + 4 * t])) != 0;
         if (t == 1) {                       // the first operand is naturally initialised: one proof per symbol
-            if (fresh) dtkp_fold_stage<K, 1, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh);
-            else dtkp_fold_stage<K, 1, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh);
+            if (fresh) dtkp_fold_stage<K, 1, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain);
+            else dtkp_fold_stage<K, 1, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain);
         } else {
-            if (fresh) dtkp_fold_stage<K, K, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh);
-            else dtkp_fold_stage<K, K, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh);
+            if (fresh) dtkp_fold_stage<K, K, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain);
+            else dtkp_fold_stage<K, K, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain);
         }
         wave_lds_fence();
     }
@@ -384,7 +413,7 @@ Cache<DtkpFoldPlan> &g_fold_plans = *new Cache<DtkpFoldPlan>;      // never dest
 
 dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldPlan *p)
 {
-    const int n = fold->n_inputs;
+    const int n = fold->n_inputs, K = prov->k;
     std::vector<int32_t> words(1 + 4 * static_cast<size_t>(n), 0);
     words[0] = n;
     int32_t s_prev = 0;
@@ -421,6 +450,8 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
         if (f->na != s_prev || f->nb != d->n_sym)
             return fail(DOL_ESHAPE, "tables[%d] is %d x %d, its operands have %d and %d symbols", t - 1, f->na, f->nb, s_prev, d->n_sym);
         if (f->n_out < 1) return fail(DOL_EUNSUPPORTED, "tables[%d] produces no symbol", t - 1);
+        // (a list's place in 16 bits; wider Distributions' lists do not fit in LDS either)
+        if (4 * static_cast<int64_t>(K) * s_prev > 0xffff) return fail(DOL_EUNSUPPORTED, "the proofs of the fold do not fit in LDS");
         if (words.size() + static_cast<size_t>(f->n_out) + static_cast<size_t>(f->n_tuples) + 3 > 16000)
             return fail(DOL_EUNSUPPORTED, "the tables of the fold do not fit in LDS");
         words[1 + 4 * t] = f->n_out;
@@ -429,7 +460,7 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
         words[3 + 4 * t] = static_cast<int32_t>(words.size());
         for (int64_t q = 0; q < f->n_tuples; ++q) {
             const uint32_t ij = f->h_col_ij[static_cast<size_t>(q)];
-            words.push_back(static_cast<int32_t>((ij & 0xffffu) | (static_cast<uint32_t>(fos[ij >> 16]) << 16)));
+            words.push_back(static_cast<int32_t>((4u * K * (ij & 0xffffu)) | (static_cast<uint32_t>(fos[ij >> 16]) << 18)));
         }
         words.insert(words.end(), 2, 0);
         s_prev = p->s_last = f->n_out;
@@ -452,8 +483,8 @@ dol_status get_plan(const dol_dtkp_fold *fold, const dol_prov *prov, const DtkpF
     int device = 0;
     (void)hipGetDevice(&device);
     const int n = fold->n_inputs;
-    std::vector<int32_t> desc{n, prov->n_facts, prov->fact_group ? 1 : 0};
-    desc.reserve(3 + static_cast<size_t>(prov->n_facts) + 24 * static_cast<size_t>(n));
+    std::vector<int32_t> desc{n, prov->k, prov->n_facts, prov->fact_group ? 1 : 0};
+    desc.reserve(4 + static_cast<size_t>(prov->n_facts) + 24 * static_cast<size_t>(n));
     if (prov->fact_group) desc.insert(desc.end(), prov->fact_group, prov->fact_group + prov->n_facts);
     for (int t = 0; t < n; ++t) {
         const uint64_t uid = t ? fold->tables[t - 1]->uid : 0;
