@@ -40,7 +40,7 @@ bool conv_path_ok(const dol_fn_table *f)
 std::string damp_kernel_name(const dol_fn_table *f, bool backward, int64_t batch)
 {
     if (!conv_path_ok(f)) {
-        if (table_code_ok(f) && !(backward && table_small_batch_bwd(f, batch))) return backward ? "damp_table_bwd_kernel" : "damp_table_fwd_kernel";
+        if (table_code_ok(f) && !table_small_batch(f, batch, backward)) return backward ? "damp_table_bwd_kernel" : "damp_table_fwd_kernel";
         if (backward) {
             if (f->lds_bwd_ok && !lds_small_batch(f, batch, true)) return "damp_lds_bwd_kernel";
             if (byj_bwd_sample_ok(f)) return !byj_bwd_staged(f) ? "damp_byj_bwd_global_kernel" : byj_bwd_wide(f) ? "damp_byj_bwd_row_kernel" : "damp_byj_bwd_kernel";

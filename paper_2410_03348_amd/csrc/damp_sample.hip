@@ -1119,12 +1119,16 @@ bool lds_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
     return backward ? sample_bwd_us(f, batch) < f->tile_bwd_us : sample_fwd_us(f, batch) < f->tile_fwd_us;
 }
 
-// Tables with generated code (damp_table.hip).  Forward the tiles are the faster ones at any batch (64 x 64 -> 256 4.3 us and
-// a workgroup per sample 4.1 to 4.6 up to 512 samples, smaller tables 2.8 and 3.5).  Backward: 64 x 64 -> 256 B=256 12.3 / 4.8,
-// 4 096 12.4 / 11.5; 32 x 40 -> 128 2 048 7.4 / 5.5, 4 096 7.4 / 7.4; 16 x 16 -> 32 3.5 / 4.4.
-bool table_small_batch_bwd(const dol_fn_table *f, int64_t batch)
+// Tables with generated code (damp_table.hip).  Rows that are not whole 16-byte pieces: from 2^24 multiply-adds a pass on, where
+// it saves 6 us and more a pass in either direction (50 x 37 -> 201, gathers / generated code, forward B=10 007 11.7 / 5.3,
+// backward 15.4 / 9.2), so that the second it takes to compile is soon made up for; below, the kernels that need none.  Others
+// (64 x 64 -> 256 forward 4.3 us and a workgroup per sample 4.1 to 4.6 up to 512 samples, smaller tables 2.8 and 3.5): forward
+// at any batch, backward, samples / tiles: 64 x 64 -> 256 B=256 4.8 / 12.3, 4 096 11.5 / 12.4; 32 x 40 -> 128 2 048 5.5 / 7.4,
+// 4 096 7.4 / 7.4; 16 x 16 -> 32 4.4 / 3.5.
+bool table_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
 {
-    if (batch < 1 || batch > 4096 || !(byj_bwd_sample_ok(f) || list_bwd_sample_ok(f))) return false;
+    if (!whole_pieces(f)) return batch < (int64_t{1} << 24) / std::max<int64_t>(1, f->n_tuples);
+    if (!backward || batch < 1 || batch > 4096 || !(byj_bwd_sample_ok(f) || list_bwd_sample_ok(f))) return false;
     const double tiles = 3.0 + 2.5e-3 * static_cast<double>(f->n_tuples) + 6e-3 * f->n_out;
     return sample_bwd_us(f, batch) < tiles;
 }

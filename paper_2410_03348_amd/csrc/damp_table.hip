@@ -14,10 +14,12 @@
 //
 // Layout of a launch: a workgroup of four wavefronts owns a tile of 64 samples (batches too small to give every compute
 // unit two such tiles: eight wavefronts, or tiles of 32 samples; see build_for).  The tile's operand rows travel
-// HBM -> LDS with flat 16-byte loads (rows padded to a pitch of n + 4 floats, which keeps a lane's 16-byte reads of
-// its own row off its neighbours' banks), each lane pulls its sample's rows into registers, the wavefronts split
-// the work (forward: 64 output columns at a time each; backward: half of the rows of one operand each), results go back
-// through LDS and leave as flat 16-byte stores.
+// HBM -> LDS with flat 16-byte loads (rows of whole 16-byte pieces padded to a pitch of n + 4 floats, which keeps a lane's
+// 16-byte reads of its own row off its neighbours' banks; rows of any other length as they lie in memory, read word by word),
+// each lane pulls its sample's rows into registers, the wavefronts split the work (forward: 64 output columns at a time each;
+// backward: half of the rows of one operand each), results go back through LDS and leave as flat 16-byte stores.
+// Symbol counts that are no multiples of four came here late: 50 x 37 -> 201, us forward / backward, B=10 007 11.7 / 15.4 through
+// the gathers of damp_lds.hip, 5.3 / 9.2 here, B=100 000 74.5 / 87.1 and 27.2 / 41.8; 61 x 5 -> 77 at 100 000 38 / 88, 18 / 24.
 //
 // Backward needs gh = g * [pre <= 1].  For tags in [0, 1] a column's sum is bounded by max(a) * sum(b) * M, M = the
 // most tuples of one column that share a second-operand symbol (and the same with the operands' roles swapped): a
@@ -67,8 +69,10 @@ void JitDeleter::operator()(JitState *p) const { delete p; }
 bool table_code_ok(const dol_fn_table *f)
 {
     return f->na >= 4 && f->nb >= 4 && f->n_out >= 4 && f->na <= kJitMaxSym && f->nb <= kJitMaxSym && f->n_out <= kJitMaxOut &&
-           !((f->na | f->nb | f->n_out) & 3) && f->n_tuples > 0 && f->n_tuples <= kJitMaxTuples && !f->h_col_ptr.empty();
+           f->n_tuples > 0 && f->n_tuples <= kJitMaxTuples && !f->h_col_ptr.empty();
 }
+
+bool whole_pieces(const dol_fn_table *f) { return !((f->na | f->nb | f->n_out) & 3); }
 
 namespace {
 
@@ -90,9 +94,18 @@ thread_local int t_waves = kJitWavesLarge, t_tile_rows = kJitTile;
 #define kJitWaves t_waves
 #define kThreads (kJitTile * t_waves)
 
-// Declares r0 .. r{n-1} and fills them from the lane's row of the staged tile (pitch n + 4 floats).
+// Floats from one sample's row to the next in LDS: four more than it has where it is whole 16-byte pieces, which are then
+// read and written by their lanes as such; any other row has its own length, so that the tile is the block of memory it came
+// from (and an odd length keeps the lanes' words off one another's banks).
+int pitch_of(int n) { return n & 3 ? n : n + 4; }
+
+// Declares r0 .. r{n-1} and fills them from the lane's row of the staged tile.
 void emit_row_to_regs(Src &o, const char *r, const char *tile, int n)
 {
+    if (n & 3) {
+        for (int i = 0; i < n; ++i) o("  const float %s%d = %s[lane * %d + %d];\n", r, i, tile, n, i);
+        return;
+    }
     for (int i = 0; i < n; i += 4)
         o("  float %s%d, %s%d, %s%d, %s%d; { const float4 t = *reinterpret_cast<const float4 *>(%s + lane * %d + %d); %s%d = t.x; %s%d = t.y; "
           "%s%d = t.z; %s%d = t.w; }\n", r, i, r, i + 1, r, i + 2, r, i + 3, tile, n + 4, i, r, i, r, i + 1, r, i + 2, r, i + 3);
@@ -104,6 +117,13 @@ void emit_stage_load(Src &o, const char *tag, const char *src_ptr, int n)
 {
     const int per_thread = (kJitTile * n / 4 + kThreads - 1) / kThreads;
     for (int x = 0; x < per_thread; ++x) o("  float4 ld%s%d;\n", tag, x);
+    if (n & 3) {            // (the last tile's words need not be whole pieces: the rest one by one)
+        o("  const int whole%s = valid * %d >> 2, rest%s = valid * %d & 3;\n  float one%s = 0.0f;\n", tag, n, tag, n, tag);
+        o("  { const float *g1 = %s + s0 * %d; const float4 *g4 = reinterpret_cast<const float4 *>(g1);\n", src_ptr, n);
+        for (int x = 0; x < per_thread; ++x) o("    { const int q = tid + %d; ld%s%d = g4[q < whole%s ? q : whole%s - 1]; }\n", kThreads * x, tag, x, tag, tag);
+        o("    if (tid < rest%s) one%s = g1[4 * whole%s + tid];\n  }\n", tag, tag, tag);
+        return;
+    }
     o("  { const float4 *g4 = reinterpret_cast<const float4 *>(%s + s0 * %d);\n", src_ptr, n);
     for (int x = 0; x < per_thread; ++x)
         o("    { const int q = tid + %d; ld%s%d = g4[q < valid * %d ? q : valid * %d - 1]; }\n", kThreads * x, tag, x, n / 4, n / 4);
@@ -113,6 +133,12 @@ void emit_stage_load(Src &o, const char *tag, const char *src_ptr, int n)
 void emit_stage_store(Src &o, const char *tag, const char *dst, int n)
 {
     const int per_thread = (kJitTile * n / 4 + kThreads - 1) / kThreads;
+    if (n & 3) {
+        for (int x = 0; x < per_thread; ++x)
+            o("  { const int q = tid + %d; if (q < whole%s) reinterpret_cast<float4 *>(%s)[q] = ld%s%d; }\n", kThreads * x, tag, dst, tag, x);
+        o("  if (tid < rest%s) %s[4 * whole%s + tid] = one%s;\n", tag, dst, tag, tag);
+        return;
+    }
     for (int x = 0; x < per_thread; ++x)
         o("  { const int q = tid + %d; %s{ const int s = q / %d, k = q - s * %d; *reinterpret_cast<float4 *>(%s + s * %d + 4 * k) = ld%s%d; } }\n",
           kThreads * x, kThreads * (x + 1) <= kJitTile * n / 4 ? "" : (std::string("if (q < ") + std::to_string(kJitTile * n / 4) + ") ").c_str(), n / 4, n / 4,
@@ -131,6 +157,7 @@ void emit_columns(Src &o, const dol_fn_table *f, int c0, int c1, const char *ind
 
 const char *kPrologue =
     "typedef unsigned int u32;\n"
+    "typedef float __attribute__((ext_vector_type(4), aligned(4))) float4u;\n"
     "__device__ __forceinline__ void wave_lds_fence() {\n"
     "  __builtin_amdgcn_fence(__ATOMIC_RELEASE, \"wavefront\"); __builtin_amdgcn_wave_barrier(); __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, \"wavefront\"); }\n";
 
@@ -148,7 +175,7 @@ void emit_tile_head(Src &o)
 std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = false, bool body = false, int *lds_floats = nullptr)
 {
     const int na = f->na, nb = f->nb, S = f->n_out;
-    const int pa = na + 4, pb = nb + 4;
+    const int pa = pitch_of(na), pb = pitch_of(nb);
     const int fcols = kJitGroup * kJitWavesLarge / kJitWaves;       // columns a wavefront takes at a time: 64, or 32 of eight wavefronts
     const int po = merged ? S + 4 : fcols + 4;         // pitch of the result stage: the whole tile, or a wavefront's columns
     const int in_floats = kJitTile * (pa + pb), out_floats = merged ? kJitTile * po : kJitWaves * kJitTile * po;
@@ -186,9 +213,10 @@ std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = fa
         const int c0 = g * fcols, c1 = std::min(S, c0 + fcols);
         o("  if (wave == %d) {\n", g % kJitWaves);
         emit_columns(o, f, c0, c1, "    ");
+        auto clamped = [&](int c) { return c < c1 ? "fminf(p" + std::to_string(c) + ", 1.0f)" : std::string("0.0f"); };
         for (int c = c0; c < c1; c += 4)
-            o("    *reinterpret_cast<float4 *>(so + lane * %d + %d) = make_float4(fminf(p%d, 1.0f), fminf(p%d, 1.0f), fminf(p%d, 1.0f), fminf(p%d, 1.0f));\n",
-              po, merged ? c : c - c0, c, c + 1, c + 2, c + 3);
+            o("    *reinterpret_cast<float4 *>(so + lane * %d + %d) = make_float4(%s, %s, %s, %s);\n", po, merged ? c : c - c0, clamped(c).c_str(),
+              clamped(c + 1).c_str(), clamped(c + 2).c_str(), clamped(c + 3).c_str());
         if (merged) {
             o("    { bool over = false;\n");
             for (int c = c0; c < c1; ++c) o("      over |= !(p%d <= 1.0f);\n", c);
@@ -196,9 +224,18 @@ std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = fa
         } else {
             // the wavefront's own stage: program order within the wavefront is all the ordering it needs
             o("    wave_lds_fence();\n");
-            const int chunks = (c1 - c0) / 4;       // 16-byte pieces per sample
-            o("    for (int q = lane; q < valid * %d; q += 64) { const int s = q / %d, k = q - s * %d;\n", chunks, chunks, chunks);
-            o("      *reinterpret_cast<float4 *>(out + (s0 + s) * %d + %d + 4 * k) = *reinterpret_cast<const float4 *>(so + s * %d + 4 * k); }\n", S, c0, po);
+            const int chunks = (c1 - c0) / 4, rest = (c1 - c0) & 3;     // 16-byte pieces per sample (S & 3: at any 4-byte boundary)
+            if (chunks && (S & 3)) {
+                o("    for (int q = lane; q < valid * %d; q += 64) { const int s = q / %d, k = q - s * %d;\n", chunks, chunks, chunks);
+                o("      const float4 t = *reinterpret_cast<const float4 *>(so + s * %d + 4 * k); float4u v; v.x = t.x; v.y = t.y; v.z = t.z; v.w = t.w;\n", po);
+                o("      *reinterpret_cast<float4u *>(out + (s0 + s) * %d + %d + 4 * k) = v; }\n", S, c0);
+            }
+            if (rest) {
+                o("    for (int q = lane; q < valid * %d; q += 64) { const int s = q / %d, k = q - s * %d;\n", rest, rest, rest);
+                o("      out[(s0 + s) * %d + %d + k] = so[s * %d + %d + k]; }\n", S, c0 + 4 * chunks, po, 4 * chunks);
+            }
+            if (!(S & 3)) o("    for (int q = lane; q < valid * %d; q += 64) { const int s = q / %d, k = q - s * %d;\n", chunks, chunks, chunks);
+            if (!(S & 3)) o("      *reinterpret_cast<float4 *>(out + (s0 + s) * %d + %d + 4 * k) = *reinterpret_cast<const float4 *>(so + s * %d + 4 * k); }\n", S, c0, po);
             o("    wave_lds_fence();\n");
         }
         o("  }\n");
@@ -267,7 +304,7 @@ int max_multiplicity(const dol_fn_table *f, bool by_b)
 // into the LDS stage.  merged: column c of the Apply is column ca[c] of the upstream gradient (or dropped).
 void emit_gh_load(Src &o, int S, int c0, int c1, bool merged, bool aligned, const char *ind)
 {
-    const int chunks = (c1 - c0) / 4, per_thread = (kJitTile * chunks + kThreads - 1) / kThreads;
+    const int chunks = (c1 - c0 + 3) / 4, per_thread = (kJitTile * chunks + kThreads - 1) / kThreads, over = 4 * chunks - (c1 - c0);
     for (int x = 0; x < per_thread; ++x) {
         // (no branches: a conditional block here would invite the compiler to sink the multiply-adds before it past it)
         o("%s{ int q = tid + %d; q = q < valid * %d ? q : valid * %d - 1; const int s = q / %d, k = q - s * %d;\n", ind, kThreads * x, chunks, chunks,
@@ -279,6 +316,14 @@ void emit_gh_load(Src &o, int S, int c0, int c1, bool merged, bool aligned, cons
             else
                 o("%s  const float4 t = make_float4(gr[oc.x > 0 ? oc.x : 0], gr[oc.y > 0 ? oc.y : 0], gr[oc.z > 0 ? oc.z : 0], gr[oc.w > 0 ? oc.w : 0]);\n", ind);
             o("%s  th%d = make_float4(oc.x >= 0 ? t.x : 0.0f, oc.y >= 0 ? t.y : 0.0f, oc.z >= 0 ? t.z : 0.0f, oc.w >= 0 ? t.w : 0.0f); }\n", ind, x);
+        } else if (S & 3) {
+            // (a row's last piece is the one that ends with the row, moved down in registers)
+            o("%s  const float4u t = *reinterpret_cast<const float4u *>(g + (s0 + s) * %d + %d + 4 * k%s);\n", ind, S, c0,
+              over ? (" - (k == " + std::to_string(chunks - 1) + " ? " + std::to_string(over) + " : 0)").c_str() : "");
+            static const char *const down[4] = {"make_float4(t.x, t.y, t.z, t.w)", "make_float4(t.y, t.z, t.w, 0.0f)", "make_float4(t.z, t.w, 0.0f, 0.0f)",
+                                                "make_float4(t.w, 0.0f, 0.0f, 0.0f)"};
+            if (over) o("%s  th%d = k == %d ? %s : %s; }\n", ind, x, chunks - 1, down[over], down[0]);
+            else o("%s  th%d = %s; }\n", ind, x, down[0]);
         } else {
             o("%s  th%d = reinterpret_cast<const float4 *>(g)[((s0 + s) * %d + %d) / 4 + k]; }\n", ind, x, S, c0);
         }
@@ -288,7 +333,7 @@ void emit_gh_load(Src &o, int S, int c0, int c1, bool merged, bool aligned, cons
 // The group's way from registers into its LDS stage, gated on the way by the words of sm (all ones where no clamp acted).
 void emit_gh_store(Src &o, int c0, int c1, int g, int n_groups, const char *dst, bool masked, const char *ind)
 {
-    const int chunks = (c1 - c0) / 4, per_thread = (kJitTile * chunks + kThreads - 1) / kThreads;
+    const int chunks = (c1 - c0 + 3) / 4, per_thread = (kJitTile * chunks + kThreads - 1) / kThreads;
     for (int x = 0; x < per_thread; ++x) {
         const bool whole = kThreads * (x + 1) <= kJitTile * chunks;
         o("%s{ const int q = tid + %d; %s{ const int s = q / %d, k = q - s * %d;\n", ind, kThreads * x,
@@ -304,7 +349,7 @@ void emit_gh_store(Src &o, int c0, int c1, int g, int n_groups, const char *dst,
 std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = false, bool body = false, int *lds_floats = nullptr)
 {
     const int na = f->na, nb = f->nb, S = f->n_out;
-    const int pa = na + 4, pb = nb + 4, pg = kJitGroup + 4;
+    const int pa = pitch_of(na), pb = pitch_of(nb), pg = kJitGroup + 4;
     const int n_groups = (S + kJitGroup - 1) / kJitGroup;
     // LDS: a tile, b tile, two stages for one group of gh each (the first re-used as the result stage), gate words
     const int off_b = kJitTile * pa, off_g = off_b + kJitTile * pb;
@@ -395,7 +440,7 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
     }
     o("    __syncthreads();\n");
     {   // the first group is already staged: gate it in place
-        const int c1 = std::min(S, kJitGroup), chunks = c1 / 4;
+        const int c1 = std::min(S, kJitGroup), chunks = (c1 + 3) / 4;
         o("    for (int q = tid; q < %d; q += %d) { const int s = q / %d, k = q - s * %d;\n", kJitTile * chunks, kThreads, chunks, chunks);
         o("      const u32 mw = sm[(s * %d) * 2 + (k >> 3)] >> ((4 * k) & 31); float4 *p4 = reinterpret_cast<float4 *>(sg0 + s * %d + 4 * k);\n", n_groups, pg);
         o("      const float4 t = *p4; *p4 = make_float4(mw & 1u ? t.x : 0.0f, mw & 2u ? t.y : 0.0f, mw & 4u ? t.z : 0.0f, mw & 8u ? t.w : 0.0f); }\n");
@@ -441,14 +486,24 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
         // results: through LDS (one operand's tile at a time, in the first stage), out with flat 16-byte accesses
         for (int pass = 0; pass < 2; ++pass) {
             const bool pass_a = pass == 0;
-            const int pn = pass_a ? na : nb, pp = pn + 4;
+            const int pn = pass_a ? na : nb, pp = pitch_of(pn);
             if (pass) o("    __syncthreads();\n");
-            if (pass_a == is_a)
+            if (pass_a == is_a && (pn & 3))
+                for (int r = r0; r < r1; ++r) o("    sg0[lane * %d + %d] = %s%d;\n", pp, r, acc, r);
+            if (pass_a == is_a && !(pn & 3))
                 for (int r = r0; r < r1; r += 4)
                     o("    *reinterpret_cast<float4 *>(sg0 + lane * %d + %d) = make_float4(%s%d, %s%d, %s%d, %s%d);\n", pp, r, acc, r, acc, r + 1, acc,
                       r + 2, acc, r + 3);
             o("    __syncthreads();\n");
             o("    if (%s) { float4 *d4 = reinterpret_cast<float4 *>(%s + s0 * %d);\n", pass_a ? "ga" : "gb", pass_a ? "ga" : "gb", pn);
+            if (pn & 3) {
+                o("      const int whole = valid * %d >> 2, rest = valid * %d & 3;\n", pn, pn);
+                o("      for (int q = tid; q < whole; q += %d) { float4 v = reinterpret_cast<const float4 *>(sg0)[q];\n", kThreads);
+                o("        if (accumulate & %d) { const float4 old = d4[q]; v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w; }\n        d4[q] = v; }\n", pass_a ? 1 : 2);
+                o("      if (tid < rest) { float *d1 = reinterpret_cast<float *>(d4 + whole) + tid; const float v = sg0[4 * whole + tid]; *d1 = accumulate & %d ? v + *d1 : v; } }\n",
+                  pass_a ? 1 : 2);
+                continue;
+            }
             o("      for (int q = tid; q < valid * %d; q += %d) { const int s = q / %d, k = q - s * %d;\n", pn / 4, kThreads, pn / 4, pn / 4);
             o("        float4 v = *reinterpret_cast<const float4 *>(sg0 + s * %d + 4 * k);\n", pp);
             o("        if (accumulate & %d) { const float4 old = d4[q]; v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w; }\n", pass_a ? 1 : 2);
@@ -615,7 +670,7 @@ dol_status launch_damp_table_fwd(const dol_fn_table *f, int32_t batch, const flo
                                  int64_t ldb, float *out, int64_t ldo, hipStream_t st, bool *done)
 {
     *done = false;
-    if (!table_code_ok(f) || batch < 1) return DOL_OK;
+    if (!table_code_ok(f) || batch < 1 || table_small_batch(f, batch, false)) return DOL_OK;
     if (lda != f->na || ldb != f->nb || ldo != f->n_out || !aligned16(a) || !aligned16(b) || !aligned16(out)) return DOL_OK;
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, kSlotFwd, build_for(batch), &fn)) return s;
@@ -632,7 +687,7 @@ dol_status launch_damp_table_bwd(const dol_fn_table *f, int32_t batch, const flo
                                  hipStream_t st, bool *done)
 {
     *done = false;
-    if (!table_code_ok(f) || batch < 1 || (ga && ga == gb) || table_small_batch_bwd(f, batch)) return DOL_OK;
+    if (!table_code_ok(f) || batch < 1 || (ga && ga == gb) || table_small_batch(f, batch, true)) return DOL_OK;
     if (lda != f->na || ldb != f->nb || ldg != f->n_out || !aligned16(a) || !aligned16(b) || !aligned16(g) || !aligned16(ga) ||
         !aligned16(gb))
         return DOL_OK;
@@ -646,7 +701,7 @@ dol_status launch_damp_table_bwd(const dol_fn_table *f, int32_t batch, const flo
     return DOL_OK;
 }
 
-bool table_merge_ok(const dol_fn_table *f) { return table_code_ok(f) && f->n_out <= kJitMaxMergeOut; }
+bool table_merge_ok(const dol_fn_table *f) { return table_code_ok(f) && whole_pieces(f) && f->n_out <= kJitMaxMergeOut; }
 
 dol_status launch_damp_table_merge_fwd(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b,
                                        const float *c, float *out, int32_t *saved, hipStream_t st)

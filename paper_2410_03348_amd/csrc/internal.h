@@ -336,7 +336,8 @@ dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *
                              hipStream_t st, bool *done);
 // The choice for tables that damp_table.hip generates code for: a workgroup per sample is faster than tiles, backward and in
 // the merged calls, whose launch takes out == nullptr (backward only) or g == nullptr (forward only).
-bool table_small_batch_bwd(const dol_fn_table *f, int64_t batch);
+bool table_small_batch(const dol_fn_table *f, int64_t batch, bool backward);
+bool whole_pieces(const dol_fn_table *f);       // rows of whole 16-byte pieces
 bool merge_small_batch(const dol_fn_table *f, const UnionPlan *p, int64_t batch);
 dol_status launch_sample_merge(const dol_fn_table *f, const UnionPlan *p, int32_t batch, const float *a, const float *b, const float *c,
                                float *out, int32_t *saved, const float *g, float *ga, float *gb, float *gc, int32_t accumulate, hipStream_t st);

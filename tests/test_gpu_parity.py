@@ -2121,6 +2121,55 @@ def test_tiles_of_64_samples_at_large_batches(dol, na, nb, n_ids, batch):
     assert_close(host(gb), wb, "tiles backward b")
 
 
+@pytest.mark.parametrize("na,nb,n_ids,batch", [(63, 61, 255, 8193), (50, 37, 201, 10007), (5, 64, 66, 53000), (64, 6, 64, 45001), (33, 47, 1023, 16390),
+                                               (29, 64, 5, 9101), (50, 40, 129, 17000)])
+def test_generated_tables_of_any_symbol_counts(dol, na, nb, n_ids, batch):
+    """The code written for a table whose rows are not whole 16-byte pieces: every remainder of each count, result rows of one
+    to sixteen groups, last tiles of which the words are no whole pieces, both builds (up to 16 384 samples and above), columns
+    on either side of the clamp, a sample of NaN and one of infinities, accumulation and one-sided calls."""
+    tab = W.hashed_table(65, na, nb, n_ids)
+    f = dol.FnTable.create_dense(tab)
+    assert f.kernel_at(False, batch) == "damp_table_fwd_kernel" and f.kernel_at(True, batch) == "damp_table_bwd_kernel"
+    a = (W.uniform01(66, batch * na) * (2.0 * n_ids / (na * nb))).astype(np.float32).reshape(batch, na)
+    b = W.uniform01(67, batch * nb).astype(np.float32).reshape(batch, nb)
+    a[1::4] *= 2.2                                # (long columns all lie near half the scale)
+    a[batch // 3] *= 1e-3
+    odd = [64, 65]
+    a[64, 1], b[65, 2] = np.nan, np.inf
+    look = np.unique(np.concatenate([np.arange(0, batch, max(1, batch // 700)), np.arange(batch - 70, batch), np.arange(0, 70)]))
+    look = look[~np.isin(look, odd)]
+    tri = oracle.dense_to_triples(tab)
+    syms, want, pre32, _ = oracle.damp_apply2_fwd(tri, na, nb, a[look], b[look], want_pre=True)
+    da, db = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b))
+    buf = torch.full((batch * syms.size + 16,), -3.0, device="cuda")          # (nothing past the last row is written)
+    out = dol.Dist(syms, buf[:batch * syms.size].view(batch, syms.size))
+    dol.apply2(da, db, f, None, out)
+    got = host(out.prob)
+    assert_close(got[look], want, "forward")
+    np.testing.assert_array_equal(got[look] == 1.0, pre32 >= 1.0)
+    assert np.all(host(buf[batch * syms.size:]) == -3.0) and (want == 1.0).any() and (want < 1.0).any()
+    # (a sum with NaN or infinity in it is clamped to 1, wherever the kernels meet it)
+    hit = np.zeros(syms.size, bool)
+    for c in np.searchsorted(syms, np.unique(tab[1][tab[1] >= 0])):
+        hit[c] = True
+    np.testing.assert_array_equal(got[64][hit], 1.0)
+    g = np.abs(W.normal(68, batch * syms.size)).astype(np.float32).reshape(batch, -1)
+    wa, wb = oracle.damp_apply2_bwd(tri, na, nb, a[look], b[look], g[look])
+    rec = dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f)
+    ga, gb = torch.full_like(da.prob, 5.0), torch.full_like(db.prob, 5.0)
+    dol.backward(rec, dev(g), ga, gb)
+    assert_close(host(ga)[look], wa, "backward a")
+    assert_close(host(gb)[look], wb, "backward b")
+    only = torch.full_like(db.prob, 5.0)
+    dol.backward(rec, dev(g), None, only)
+    np.testing.assert_array_equal(host(only)[look], host(gb)[look])
+    acc = dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f, accumulate=3)
+    once_a, once_b = host(ga)[look].astype(np.float64), host(gb)[look].astype(np.float64)
+    dol.backward(acc, dev(g), ga, gb)
+    assert_close(host(ga)[look], 2.0 * once_a, "backward a accumulated")
+    assert_close(host(gb)[look], 2.0 * once_b, "backward b accumulated")
+
+
 @pytest.mark.parametrize("na,nb,n_ids", [(13, 12, 30), (50, 37, 201), (101, 10, 226), (101, 10, 9), (226, 10, 442), (442, 10, 785), (100, 100, 50),
                                          (128, 30, 700), (30, 30, 2), (64, 64, 32), (16, 16, 200)])
 def test_a_result_does_not_depend_on_the_batch_it_is_in(dol, na, nb, n_ids):
