@@ -173,14 +173,15 @@ damp_apply1_bwd_kernel(Rows R, const float *__restrict__ x, int64_t ldx, const i
 // column are gathered from it, in the same order.  Backward: the gradient row, gated by the clamp, is staged and
 // every operand symbol picks its column's entry.
 __global__ void __launch_bounds__(kStageThreads)
-damp_apply1_fwd_staged_kernel(int32_t n_in, int32_t S, int32_t parts, const float *__restrict__ x, int64_t ldx,
+damp_apply1_fwd_staged_kernel(int32_t n_in, int32_t S, int32_t parts, uint32_t shared, const float *__restrict__ x, int64_t ldx,
                               const uint32_t *__restrict__ order, const uint32_t *__restrict__ col_ptr, const uint16_t *__restrict__ tup,
                               const uint4 *__restrict__ head, float *__restrict__ out, int64_t ldo)
 {
     extern __shared__ __align__(16) float xr[];
-    const int64_t s = blockIdx.x / static_cast<unsigned>(parts);
+    const unsigned id = xcd_shared(blockIdx.x, shared);
+    const int64_t s = id / static_cast<unsigned>(parts);
     int c0, c1;
-    stage_part(S, parts, static_cast<int>(blockIdx.x - s * parts), c0, c1);
+    stage_part(S, parts, static_cast<int>(id - s * parts), c0, c1);
     stage_row(xr, x + s * ldx, n_in);
     __syncthreads();
     // kStageUnroll columns per thread and pass, so that their index and head loads are in flight together
@@ -225,15 +226,16 @@ damp_apply1_fwd_staged_kernel(int32_t n_in, int32_t S, int32_t parts, const floa
 }
 
 __global__ void __launch_bounds__(kStageThreads)
-damp_apply1_bwd_staged_kernel(int32_t n_in, int32_t S, int32_t parts, const float *__restrict__ x, int64_t ldx,
+damp_apply1_bwd_staged_kernel(int32_t n_in, int32_t S, int32_t parts, uint32_t shared, const float *__restrict__ x, int64_t ldx,
                               const int32_t *__restrict__ col_of, const uint32_t *__restrict__ col_ptr,
                               const uint16_t *__restrict__ tup, const float *__restrict__ out, int64_t ldo,
                               const float *__restrict__ g, int64_t ldg, float *__restrict__ gx)
 {
     extern __shared__ __align__(16) float gh[];
-    const int64_t s = blockIdx.x / static_cast<unsigned>(parts);
+    const unsigned id = xcd_shared(blockIdx.x, shared);
+    const int64_t s = id / static_cast<unsigned>(parts);
     int i0, i1;
-    stage_part(n_in, parts, static_cast<int>(blockIdx.x - s * parts), i0, i1);
+    stage_part(n_in, parts, static_cast<int>(id - s * parts), i0, i1);
     for (int c = threadIdx.x; c < S; c += kStageThreads) {
         float v = g[s * ldg + c];
         if (out[s * ldo + c] >= 1.0f) {             // pre == 1 passes, pre > 1 blocks: only pre itself tells
@@ -340,7 +342,7 @@ static void launch_fwd_k(const Rows &R, const KOperands &in, const dol_fnk_table
         const int32_t parts = stage_parts(R.batch, f->n_out);
         (void)allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply1_fwd_staged_kernel), kStageMaxBytes);
         hipLaunchKernelGGL(damp_apply1_fwd_staged_kernel, dim3(static_cast<unsigned>(R.batch) * parts), dim3(kStageThreads),
-                           sizeof(float) * f->n_sym[0], st, f->n_sym[0], f->n_out, parts, in.p[0], in.ld[0], f->col_order.ptr,
+                           sizeof(float) * f->n_sym[0], st, f->n_sym[0], f->n_out, parts, shared_ranges(R.batch, parts, f->n_sym[0]), in.p[0], in.ld[0], f->col_order.ptr,
                            f->col_ptr.ptr, f->tup.ptr, reinterpret_cast<const uint4 *>(f->unary_head_ord.ptr), out, ldo);
     } else if (K == 1)
         hipLaunchKernelGGL(damp_apply1_fwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, in.p[0], in.ld[0], f->col_ptr.ptr,
@@ -362,7 +364,7 @@ static void launch_bwd_k(const Rows &R, const KOperands &in, const KGrads &gin, 
         const int32_t parts = stage_parts(R.batch, f->n_sym[0]);
         (void)allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply1_bwd_staged_kernel), kStageMaxBytes);
         hipLaunchKernelGGL(damp_apply1_bwd_staged_kernel, dim3(static_cast<unsigned>(R.batch) * parts), dim3(kStageThreads),
-                           sizeof(float) * f->n_out, st, f->n_sym[0], f->n_out, parts, in.p[0], in.ld[0], f->unary_col.ptr,
+                           sizeof(float) * f->n_out, st, f->n_sym[0], f->n_out, parts, shared_ranges(R.batch, parts, f->n_out), in.p[0], in.ld[0], f->unary_col.ptr,
                            f->col_ptr.ptr, f->tup.ptr, out, ldo, g, ldg, gin.p[0]);
     } else if (K == 1)
         hipLaunchKernelGGL(damp_apply1_bwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, in.p[0], in.ld[0], f->unary_col.ptr,

@@ -38,6 +38,7 @@ struct SampleFwd {
     int32_t na, nb, S, parts;
     int32_t map_ld, long_weight;        // dense maps
     int32_t exact;                      // every column in its tuples' order (lists only)
+    uint32_t shared;                    // see xcd_shared
     const uint16_t *map;
     Lists lists;                        // of the columns
     const uint32_t *col_ptr, *col_ij;   // a column's tuples in their order
@@ -339,8 +340,9 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
 {
     __shared__ float scratch[48];
     __shared__ int some;
-    const int64_t s = blockIdx.x / static_cast<unsigned>(A.parts);
-    const int part = static_cast<int>(blockIdx.x - s * A.parts);
+    const unsigned id = xcd_shared(blockIdx.x, A.shared);
+    const int64_t s = id / static_cast<unsigned>(A.parts);
+    const int part = static_cast<int>(id - s * A.parts);
     // the last part also sums the longest column: it weighs as much as `long_weight` columns
     const int per = ((A.S + A.long_weight + A.parts - 1) / A.parts + 3) & ~3;
     const int c0 = min(A.S, part * per), c1 = part == A.parts - 1 ? A.S : min(A.S, c0 + per);
@@ -480,8 +482,9 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
     extern __shared__ __align__(16) float lds[];            // a's row and a 0, b's and a 0 [a block of results]
     __shared__ float scratch[48];
     float *ar = lds, *br = lds + ((A.na + 4) & ~3), *res = br + ((A.nb + 4) & ~3);
-    const int64_t s = blockIdx.x / static_cast<unsigned>(A.parts);
-    const int part = static_cast<int>(blockIdx.x - s * A.parts);
+    const unsigned id = xcd_shared(blockIdx.x, A.shared);
+    const int64_t s = id / static_cast<unsigned>(A.parts);
+    const int part = static_cast<int>(id - s * A.parts);
     constexpr int kBlockChunks = kOrderBlock / kWave;
     const int n_chunks = (A.S + kWave - 1) / kWave;
     Chunk<4> now = read_chunk<4>(A.lists, min(part * kBlockChunks + wave_number(), n_chunks - 1));
@@ -979,6 +982,7 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
         A.parts = best_parts(batch, long_parts(f->col_lists, std::min(16, (f->n_out + 4 * kSmallThreads - 1) / (4 * kSmallThreads))), f->na,
                              [&](int p) { return (static_cast<double>(f->n_out + A.long_weight) * f->byj_nbp + 4.0 * f->col_lists.mid_words) / p; },
                              byj_fwd_wide(f) ? kSampleThreads : kSmallThreads, lds);
+        A.shared = shared_ranges(batch, A.parts, f->na);
         const unsigned grid = static_cast<unsigned>(batch) * A.parts;
         const int64_t work = std::max<int64_t>(f->n_out / A.parts + 3, f->na) / 4;
         if (byj_fwd_wide(f)) {
@@ -1007,6 +1011,7 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
         }, kSampleThreads, lds);
         unsigned threads = list_threads(f->col_lists, f->n_out, f->na, batch * static_cast<int64_t>(A.parts), lds, 512);
         if (A.exact && f->col_lists.longer.n && threads < kSampleThreads) threads += kWave;        // (the chain runs beside the lists)
+        A.shared = shared_ranges(batch, A.parts, f->na);
         const dim3 grid(static_cast<unsigned>(batch) * A.parts), block(threads);
         if (results) {
             if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply2_fwd_staged_kernel<true>), kStageMaxBytes));
