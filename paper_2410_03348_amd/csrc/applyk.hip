@@ -479,6 +479,45 @@ struct TupleOffer {
         else
             for (; q < q1; q += step) offer_tuple_k<KP>(top, A.tup + static_cast<size_t>(q) * A.arity, s, A.arity, A.in, gm, fp);
     }
+    __device__ __forceinline__ bool has_short() const { return A.arity == 1 && A.in.p[0]; }
+    template <class Symbol, class Put>
+    __device__ __forceinline__ void unary_short(TopKeys<KP> &keys, uint32_t q, uint32_t q1, uint32_t step, int id, Symbol symbol, Put put) const
+    {
+        for (; q < q1; q += step * kAhead, id += kAhead * KP) {
+            uint64_t m[kAhead][KP];
+            float p[kAhead][KP];
+            uint32_t i[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) i[u] = symbol(q + u * step < q1 ? q + u * step : q);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (u > 0 && q + u * step >= q1) continue;
+                const int64_t o = (s * A.in.n[0] + i[u]) * KP;
+                load_masks<KP>(A.in.m[0] + o, m[u]);
+                load_probs<KP>(A.in.p[0] + o, p[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                if (u > 0 && q + u * step >= q1) continue;
+#pragma unroll
+                for (int x = 0; x < KP; ++x) {
+                    if (m[u][x] == kAbsent) continue;
+                    put(id + u * KP + x, m[u][x]);
+                    keys.offer(p[u][x], id + u * KP + x);
+                }
+            }
+        }
+    }
+    template <class Put>
+    __device__ __forceinline__ void short_listed(TopKeys<KP> &keys, uint32_t q, uint32_t q1, uint32_t step, int id, Put put) const
+    {
+        unary_short(keys, q, q1, step, id, [&](uint32_t x) { return A.tup[x]; }, put);
+    }
+    template <class Put>
+    __device__ __forceinline__ void short_laned(TopKeys<KP> &keys, uint32_t len, int32_t r, int id, Put put) const
+    {
+        unary_short(keys, 0, len, 1, id, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; }, put);
+    }
     __device__ __forceinline__ void laned(TopK<KP> &top, uint32_t len, int32_t r, uint32_t c) const
     {
         if (A.arity == 1) unary(top, 0, len, 1, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; });
@@ -497,7 +536,7 @@ template <int KP>
 static void launch_dtkp_k(ColumnArgs C, const TupleArgs &A, const GroupMasks &gm, hipStream_t st)
 {
     const unsigned grid = column_launch(C);
-    hipLaunchKernelGGL(dtkp_applyk_kernel<KP>, dim3(grid), dim3(column_threads(C)), 0, st, C, A, gm);
+    hipLaunchKernelGGL(dtkp_applyk_kernel<KP>, dim3(grid), dim3(column_threads(C)), column_lds<KP>(column_threads(C)), st, C, A, gm);
 }
 
 // ---------------------------------------------------------------- plan

@@ -134,6 +134,40 @@ struct PairOffer {
     {
         run(top, q, q1, step, [&](uint32_t x) { return A.col_ij[x]; });
     }
+    __device__ __forceinline__ bool has_short() const { return A.fact_b && A.ap; }
+    template <class Word, class Put>
+    __device__ __forceinline__ void run_short(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, int id, Word word, Put put) const
+    {
+        for (; q < q1; q += step, id += K) {
+            const uint32_t ij = word(q);
+            const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K;
+            const uint4 f = reinterpret_cast<const uint4 *>(A.fact_b)[ij >> 16];
+            uint64_t ma[K];
+            float pa[K];
+            load_masks<K>(A.am + ia, ma);
+            load_probs<K>(A.ap + ia, pa);
+            const uint64_t bit = uint64_t(1) << f.x, rival = (static_cast<uint64_t>(f.z) << 32) | f.y;
+            const float pbit = 1.0f * fp[f.x];
+#pragma unroll
+            for (int x = 0; x < K; ++x) {                       // (see with_fact)
+                if (ma[x] == kAbsent || (ma[x] & rival)) continue;
+                const bool held = (ma[x] & bit) != 0;
+                const float pr = held || ma[x] < bit ? (held ? pa[x] : pa[x] * pbit) : proof_prob(ma[x] | bit, fp);
+                put(id + x, ma[x] | bit);
+                keys.offer(pr, id + x);
+            }
+        }
+    }
+    template <class Put>
+    __device__ __forceinline__ void short_listed(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, int id, Put put) const
+    {
+        run_short(keys, q, q1, step, id, [&](uint32_t x) { return A.col_ij[x]; }, put);
+    }
+    template <class Put>
+    __device__ __forceinline__ void short_laned(TopKeys<K> &keys, uint32_t len, int32_t r, int id, Put put) const
+    {
+        run_short(keys, 0, len, 1, id, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; }, put);
+    }
     __device__ __forceinline__ void laned(TopK<K> &top, uint32_t len, int32_t r, uint32_t) const
     {
         run(top, 0, len, 1, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; });
@@ -151,7 +185,7 @@ template <int K>
 static void launch_apply2_k(ColumnArgs C, const PairArgs &A, const GroupMasks &gm, hipStream_t st)
 {
     const unsigned grid = column_launch(C);
-    hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid), dim3(column_threads(C)), 0, st, C, A, gm);
+    hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid), dim3(column_threads(C)), column_lds<K>(column_threads(C)), st, C, A, gm);
 }
 
 #define DOL_DISPATCH_K(k, CALL)                                      \

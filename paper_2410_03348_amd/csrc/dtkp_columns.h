@@ -7,6 +7,9 @@
 // one of 758 columns 16, with up to 8 (then 16 lanes) 79 and 11, with up to 4 and four lanes up to 16, as here, 75 and 8.
 // Results gathered in LDS and stored as whole lines were slower (106 us): a workgroup of neighbours waits for its longest
 // column.
+// With lists ranked by keys that table takes 61 us (73 before), k = 3, and 147 MB leave for 98 MB of results, whose order is
+// that of the columns' lengths.  Lengths sorted inside fewer than 4 096 columns leave fewer bytes (129 MB) but unequal lanes:
+// the pass of that expression took 206 us and more instead of 204.  Lists read four tuples ahead: 80 us, for want of wavefronts.
 #pragma once
 
 #include "dtkp_util.h"
@@ -54,10 +57,33 @@ inline unsigned column_launch(ColumnArgs &A)
 }
 
 // Offer: begin(s) - the sample; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
-// laned(top, len, r, c) - those of column c, the r-th in order.
+// laned(top, len, r, c) - those of column c, the r-th in order; where it has_short(), short_listed and short_laned offer the same,
+// of at most kLongDtkpCol tuples a lane, to a list of keys, put(id, mask) keeping the masks.
+// (A candidate's way into a list of probabilities and masks takes some thirty instructions, most of them choices, and so does each
+// entry of another lane's list; into a list of keys seven, and a whole list of three twelve and the lane shifts.  The masks of a
+// lane's few tuples wait in LDS for the winners.)
+constexpr int kKeyProofs = 4;           // longest lists ranked by keys: 96 bytes of LDS a lane at three proofs, 128 at four
+template <int K>
+inline size_t column_lds(int threads) { return K <= kKeyProofs ? sizeof(uint64_t) * threads * kLongDtkpCol * K : 0; }
+
+static_assert(kKeyProofs * kLongDtkpCol <= 256 && kMidDtkpCol <= 4 * kLongDtkpCol && kWaveDtkpCol <= 16 * kLongDtkpCol, "a lane's tuples");
+
+// A key's id: the candidate's number in its lane, and the lane's thread << 8.
+template <int K>
+__device__ __forceinline__ void take_keys(TopK<K> &top, const TopKeys<K> &keys, const uint64_t *masks, int T)
+{
+#pragma unroll
+    for (int x = 0; x < K; ++x) {
+        if (!keys.present(x)) continue;
+        top.m[x] = masks[(keys.id(x) & 255) * T + (keys.id(x) >> 8)];
+        top.p[x] = keys.prob(x);
+    }
+}
+
 template <int K, class Offer>
 __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
 {
+    extern __shared__ __align__(16) uint64_t lane_masks[];
     const int T = blockDim.x, t = threadIdx.x;
     TopK<K> top;
     top.clear();
@@ -86,6 +112,21 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
         if (ci >= n) return;                        // (all lanes of a group; never a huge column's)
         const uint32_t c = A.longer[from + ci];
         offer.begin(s);
+        if constexpr (K <= kKeyProofs) {
+            if (lanes <= 16 && offer.has_short()) {             // (at most kLongDtkpCol tuples a lane)
+                TopKeys<K> keys;
+                offer.short_listed(keys, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes, t << 8, [&](int id, uint64_t m) { lane_masks[(id & 255) * T + t] = m; });
+                keys.merge(lanes);
+                if (!keys.unclear()) {                          // (the same for all lanes of the group)
+                    wave_lds_fence();
+                    if (t % lanes != 0) return;
+                    take_keys(top, keys, lane_masks, T);
+                    const int64_t o = static_cast<int64_t>(s) * A.S + c;
+                    A.oprob[s * A.ldo + c] = top.store(A.om + o * K, A.op + o * K);
+                    return;
+                }
+            }
+        }
         offer.listed(top, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes);
         if (lanes == 4) merge_lists<K, 4>(top);
         else if (lanes == 16) merge_lists<K, 16>(top);
@@ -121,7 +162,16 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
     const uint32_t len = A.len[r], c = A.order[r];
     if (len == 0) return;
     offer.begin(s);
-    offer.laned(top, len, r, c);
+    bool todo = true;
+    if constexpr (K <= kKeyProofs) {
+        if (offer.has_short()) {            // (the same for all)
+            TopKeys<K> keys;
+            offer.short_laned(keys, len, r, t << 8, [&](int id, uint64_t m) { lane_masks[(id & 255) * T + t] = m; });
+            todo = keys.unclear();
+            if (!todo) take_keys(top, keys, lane_masks, T);
+        }
+    }
+    if (__builtin_expect(todo, 0)) offer.laned(top, len, r, c);
     const int64_t o = static_cast<int64_t>(s) * A.S + c;
     A.oprob[s * A.ldo + c] = top.store(A.om + o * K, A.op + o * K);
 }

@@ -46,51 +46,6 @@ struct DtkpFoldArgs {
     float *gfact;
 };
 
-// A proof as one number that ranks: its probability's bits above, where it came from below.  For numbers of one sign that is
-// the order of the probabilities, equal ones apart (negative ones stand for absent proofs), and the larger and the smaller of
-// two cost an instruction each, where comparing probabilities and choosing both words costs five.
-__device__ __forceinline__ double key_of(float p, int id) { return __hiloint2double(__float_as_int(p), id); }
-__device__ __forceinline__ double key_max(double a, double b)
-{
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));      // (fmax makes either operand quiet first)
-    return r;
-}
-__device__ __forceinline__ double key_min(double a, double b)
-{
-    double r;
-    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-// Sorts k[at .. at + N) in descending order when it falls and then rises, as the elementwise maxima of a descending and an
-// ascending list do: the bitonic network of the next power of two with its tail taken as +infinity, of which only the
-// exchanges between real entries remain (4 for N = 4, 7 for N = 6, 12 for N = 8).
-template <int N, int L>
-__device__ __forceinline__ void sort_valley(double (&k)[L], int at)
-{
-    if constexpr (N > 1) {
-        constexpr int M = N > 8 ? 8 : N > 4 ? 4 : N > 2 ? 2 : 1;     // half of the next power of two
-        constexpr int H = N - M;
-        double hi[H], lo[M];
-#pragma unroll
-        for (int x = 0; x < M; ++x) {
-            if (x < H) {
-                const double a = k[at + x], b = k[at + x + M];
-                hi[x < H ? x : 0] = key_max(a, b), lo[x] = key_min(a, b);
-            } else {
-                lo[x] = k[at + x];
-            }
-        }
-#pragma unroll
-        for (int x = 0; x < H; ++x) k[at + x] = hi[x];
-#pragma unroll
-        for (int x = 0; x < M; ++x) k[at + H + x] = lo[x];
-        sort_valley<H, L>(k, at);
-        sort_valley<M, L>(k, at + H);
-    }
-}
-
 // One stage of the fold for this wavefront's sample: the columns of the stage's table, a lane each.  KA: slots of the
 // first operand's lists that can hold a proof (1 right after the natural initialisation); FRESH: see fresh_t above.
 // Absent slots carry the probability -1 in LDS (0 in the result tensors).

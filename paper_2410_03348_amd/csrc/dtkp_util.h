@@ -3,6 +3,7 @@
 #pragma once
 
 #include "internal.h"
+#include "wave_util.h"
 
 namespace dol {
 
@@ -83,6 +84,110 @@ __device__ __forceinline__ void store_probs(float *__restrict__ dst, const float
         dst[B] = p[B];
     }
 }
+
+// A proof as one number that ranks: its probability's bits above, where it came from below.  For numbers of one sign that is
+// the order of the probabilities, equal ones apart (negative ones stand for absent proofs), and the larger and the smaller of
+// two cost an instruction each, where comparing probabilities and choosing both words costs five.
+__device__ __forceinline__ double key_of(float p, int id) { return __hiloint2double(__float_as_int(p), id); }
+__device__ __forceinline__ double key_max(double a, double b)
+{
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));      // (fmax makes either operand quiet first)
+    return r;
+}
+__device__ __forceinline__ double key_min(double a, double b)
+{
+    double r;
+    asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// Sorts k[at .. at + N) in descending order when it falls and then rises, as the elementwise maxima of a descending and an
+// ascending list do: the bitonic network of the next power of two with its tail taken as +infinity, of which only the
+// exchanges between real entries remain (4 for N = 4, 7 for N = 6, 12 for N = 8).
+template <int N, int L>
+__device__ __forceinline__ void sort_valley(double (&k)[L], int at)
+{
+    if constexpr (N > 1) {
+        constexpr int M = N > 8 ? 8 : N > 4 ? 4 : N > 2 ? 2 : 1;     // half of the next power of two
+        constexpr int H = N - M;
+        double hi[H], lo[M];
+#pragma unroll
+        for (int x = 0; x < M; ++x) {
+            if (x < H) {
+                const double a = k[at + x], b = k[at + x + M];
+                hi[x < H ? x : 0] = key_max(a, b), lo[x] = key_min(a, b);
+            } else {
+                lo[x] = k[at + x];
+            }
+        }
+#pragma unroll
+        for (int x = 0; x < H; ++x) k[at + x] = hi[x];
+#pragma unroll
+        for (int x = 0; x < M; ++x) k[at + H + x] = lo[x];
+        sort_valley<H, L>(k, at);
+        sort_valley<M, L>(k, at + H);
+    }
+}
+
+// The K best of a few candidates by their keys, and the best of the others behind them: where two neighbours' probabilities are
+// equal, or one is no number to rank by (its sign set, or not finite), only the masks tell and the keys' order means nothing.
+template <int K>
+struct TopKeys {
+    double top[K + 1];
+    uint32_t most = 0;                  // the largest candidate's bits as a whole number
+
+    __device__ __forceinline__ TopKeys()
+    {
+#pragma unroll
+        for (int x = 0; x <= K; ++x) top[x] = -1.0;
+    }
+    __device__ __forceinline__ void offer(float p, int id)
+    {
+        most = max(most, __float_as_uint(p));
+        double o = key_of(p, id);
+#pragma unroll
+        for (int x = 0; x <= K; ++x) {
+            const double t = top[x];
+            top[x] = key_max(t, o);
+            if (x < K) o = key_min(t, o);
+        }
+    }
+    // takes in the list of the lane that CTRL (wave_util.h) pairs this one with
+    template <int CTRL>
+    __device__ __forceinline__ void take()
+    {
+        double best[K + 1];
+#pragma unroll
+        for (int x = 0; x <= K; ++x) {
+            const double t = top[K - x];
+            best[x] = key_max(top[x], __hiloint2double(dpp_i<CTRL>(__double2hiint(t)), dpp_i<CTRL>(__double2loint(t))));
+        }
+        sort_valley<K + 1, K + 1>(best, 0);
+#pragma unroll
+        for (int x = 0; x <= K; ++x) top[x] = best[x];
+        most = max(most, static_cast<uint32_t>(dpp_i<CTRL>(static_cast<int>(most))));
+    }
+    // all lanes of a group of 4 or 16 end with its list
+    __device__ __forceinline__ void merge(int lanes)
+    {
+        take<0xB1>();                       // quad_perm [1,0,3,2]
+        take<0x4E>();                       // quad_perm [2,3,0,1]
+        if (lanes == 4) return;
+        take<0x141>();                      // row_half_mirror
+        take<0x140>();                      // row_mirror
+    }
+    __device__ __forceinline__ bool unclear() const
+    {
+        bool tie = most >= 0x7f800000u;
+#pragma unroll
+        for (int x = 0; x < K; ++x) tie |= __double2hiint(top[x]) == __double2hiint(top[x + 1]) && __double2hiint(top[x]) >= 0;
+        return tie;
+    }
+    __device__ __forceinline__ bool present(int x) const { return __double2hiint(top[x]) >= 0; }
+    __device__ __forceinline__ int id(int x) const { return __double2loint(top[x]); }
+    __device__ __forceinline__ float prob(int x) const { return __int_as_float(__double2hiint(top[x])); }
+};
 
 template <int K>
 struct TopK {

@@ -2472,6 +2472,49 @@ def test_dtkp_columns_of_every_length(dol, batch, lengths):
     assert_close(host(out.prob), upr, "dtkp unary columns")
 
 
+@pytest.mark.parametrize("k", [1, 2, 4, 5])
+@pytest.mark.parametrize("values", [None, (0.5, 0.25, 1.0, 0.0), (0.5, 1e-30, 3e-39, 1.0)], ids=["random", "equal", "tiny"])
+def test_dtkp_columns_ranked_by_keys(dol, k, values):
+    """Columns of 1 to 70 tuples (a lane, four, 16 and a wavefront) where a list is ranked by probability and origin alone, on
+    both sides of the longest such list: probabilities all different, drawn from four values (equal ones within a lane, between
+    lanes and on the cut, proofs of probability 0), and so small that products underflow."""
+    lengths, batch, nb, n_facts = (1, 2, 3, 4, 5, 8, 16, 17, 40, 64, 65, 70, 1, 4, 12), 6, 6, 30
+    n = sum(lengths)
+    na = -(-n // nb)
+    fp = W.uniform01(141, batch * n_facts).astype(np.float32).reshape(batch, n_facts)
+    if values is not None:
+        fp = np.asarray(values, np.float32)[(fp * len(values)).astype(int)]
+    grp = np.concatenate([np.arange(24), np.full(6, 24)]).astype(np.int32)
+    prov = dol.Prov(dol.DTKP, k, dev(fp), grp)
+    pair = (W.splitmix64(142, np.arange(24 * 24)) % np.uint64(na)).astype(np.int32).reshape(24, 24)
+    pair.reshape(-1)[:na] = np.arange(na)
+    one = oracle.dtkp_init(np.arange(24), fp, k)
+    _, am, ap, _ = oracle.dtkp_apply2(oracle.dense_to_triples(pair), 24, 24, k, grp, fp, one[0], one[0])
+    fact_b = np.arange(24, 30, dtype=np.int32)
+    bm = oracle.dtkp_init(fact_b, fp, k)
+    col = np.repeat(np.arange(len(lengths)), lengths)[np.argsort(W.splitmix64(143, np.arange(n)))].astype(np.int32)
+    table = np.full(na * nb, -1, np.int32)
+    table[:n] = col
+    _, om, op, opr = oracle.dtkp_apply2(oracle.dense_to_triples(table.reshape(na, nb)), na, nb, k, grp, fp, am, bm[0])
+    f = dol.FnTable.create_dense(table.reshape(na, nb))
+    a = dol.Dist(np.arange(na), torch.zeros((batch, na), device="cuda"), dev(am.view(np.int64)), dev(ap))
+    out = dol.Dist.empty(f.out_syms, batch, k=k)
+    dol.dtkp_apply2_input(a, fact_b, f, prov, out)
+    np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), om)
+    np.testing.assert_array_equal(host(out.proof_prob), op)
+    assert_close(host(out.prob), opr, "ranked by keys")
+    m1, p1 = np.ascontiguousarray(am[:, np.arange(n) % na]), np.ascontiguousarray(ap[:, np.arange(n) % na])
+    idx, to = oracle.dense_to_tuples(col)
+    _, um, up, upr = oracle.dtkp_applyk(idx, to, k, grp, fp, [m1])
+    x = dol.Dist(np.arange(n), torch.zeros((batch, n), device="cuda"), dev(m1.view(np.int64)), dev(p1))
+    fu = dol.FnkTable.create_dense(col)
+    got = dol.Dist.empty(fu.out_syms, batch, k=k)
+    dol.apply_k([x], fu, prov, got)
+    np.testing.assert_array_equal(host(got.proof_mask).view(np.uint64), um)
+    np.testing.assert_array_equal(host(got.proof_prob), up)
+    assert_close(host(got.prob), upr, "unary, ranked by keys")
+
+
 @pytest.mark.parametrize("k", [1, 3])
 def test_dtkp_apply2_input_equals_init_then_apply2(dol, k):
     """The second operand given by its facts: bit for bit what dol_dtkp_init + dol_apply2 give, on a table with
