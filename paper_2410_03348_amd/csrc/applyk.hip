@@ -445,6 +445,7 @@ struct TupleOffer {
     const GroupMasks &gm;
     const float *fp;
     int64_t s;
+    int at[kLongDtkpCol];               // unary_short(): lists of the lane with a slot of probability 0, -1 without
 
     __device__ __forceinline__ void begin(int64_t sample) { s = sample, fp = A.fact_prob + sample * A.n_facts; }
     // a unary function's symbols are one list each: several on their way at a time
@@ -480,43 +481,70 @@ struct TupleOffer {
             for (; q < q1; q += step) offer_tuple_k<KP>(top, A.tup + static_cast<size_t>(q) * A.arity, s, A.arity, A.in, gm, fp);
     }
     __device__ __forceinline__ bool has_short() const { return A.arity == 1 && A.in.p[0]; }
-    template <class Symbol, class Put>
-    __device__ __forceinline__ void unary_short(TopKeys<KP> &keys, uint32_t q, uint32_t q1, uint32_t step, int id, Symbol symbol, Put put) const
+    // A key's id is the proof's number among the operand's, so that only the winners' masks are read, once they are known: two thirds
+    // of what the gathers fetched were masks, most of them of proofs that lose (38 400 symbols onto 8 333 values, 64 samples, k = 3:
+    // 39 us with every mask read, 29 so; 38 where the mask behind every probability of 0 was waited for in turn).  A slot of
+    // probability 0 is an absent proof or a real one, which its mask tells: it matters to a list that stays short only, and a real
+    // one there leaves the column to the general way.  (So does an absent proof with a probability, if it wins.)
+    template <class Symbol>
+    __device__ __forceinline__ void unary_short(TopKeys<KP> &keys, uint32_t q, uint32_t q1, uint32_t step, Symbol symbol)
     {
-        for (; q < q1; q += step * kAhead, id += kAhead * KP) {
-            uint64_t m[kAhead][KP];
-            float p[kAhead][KP];
-            uint32_t i[kAhead];
+        const float *probs = A.in.p[0] + s * A.in.n[0] * KP;
+        float p[kLongDtkpCol][KP];
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) i[u] = symbol(q + u * step < q1 ? q + u * step : q);
+        for (int u = 0; u < kLongDtkpCol; ++u) at[u] = symbol(q + u * step < q1 ? q + u * step : q) * KP;
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                if (u > 0 && q + u * step >= q1) continue;
-                const int64_t o = (s * A.in.n[0] + i[u]) * KP;
-                load_masks<KP>(A.in.m[0] + o, m[u]);
-                load_probs<KP>(A.in.p[0] + o, p[u]);
-            }
+        for (int u = 0; u < kLongDtkpCol; ++u)
+            if (q + u * step < q1) load_probs<KP>(probs + at[u], p[u]);
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                if (u > 0 && q + u * step >= q1) continue;
+        for (int u = 0; u < kLongDtkpCol; ++u) {
+            bool zero = false;
+            if (q + u * step < q1) {
 #pragma unroll
                 for (int x = 0; x < KP; ++x) {
-                    if (m[u][x] == kAbsent) continue;
-                    put(id + u * KP + x, m[u][x]);
-                    keys.offer(p[u][x], id + u * KP + x);
+                    if (p[u][x] != 0.0f) keys.offer(p[u][x], at[u] + x);
+                    else zero = true;
                 }
             }
+            if (!zero) at[u] = -1;
         }
     }
-    template <class Put>
-    __device__ __forceinline__ void short_listed(TopKeys<KP> &keys, uint32_t q, uint32_t q1, uint32_t step, int id, Put put) const
+    __device__ __forceinline__ void short_listed(TopKeys<KP> &keys, uint32_t q, uint32_t q1, uint32_t step)
     {
-        unary_short(keys, q, q1, step, id, [&](uint32_t x) { return A.tup[x]; }, put);
+        if (q < q1) unary_short(keys, q, q1, step, [&](uint32_t x) { return A.tup[x]; });
+        else
+            for (int u = 0; u < kLongDtkpCol; ++u) at[u] = -1;
     }
-    template <class Put>
-    __device__ __forceinline__ void short_laned(TopKeys<KP> &keys, uint32_t len, int32_t r, int id, Put put) const
+    __device__ __forceinline__ void short_laned(TopKeys<KP> &keys, uint32_t len, int32_t r)
     {
-        unary_short(keys, 0, len, 1, id, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; }, put);
+        unary_short(keys, 0, len, 1, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; });
+    }
+    __device__ __forceinline__ bool short_take(TopK<KP> &top, const TopKeys<KP> &keys, int lanes) const
+    {
+        const uint64_t *masks = A.in.m[0] + s * A.in.n[0] * KP;
+        bool bad = false;
+#pragma unroll
+        for (int x = 0; x < KP; ++x)
+            if (keys.present(x)) top.m[x] = masks[keys.id(x)], top.p[x] = keys.prob(x);
+        if (!keys.present(KP - 1)) {                                        // (the same for a group's lanes)
+            const float *probs = A.in.p[0] + s * A.in.n[0] * KP;
+            uint64_t m[kLongDtkpCol][KP];
+            float p[kLongDtkpCol][KP];
+#pragma unroll
+            for (int u = 0; u < kLongDtkpCol; ++u)
+                if (at[u] >= 0) load_masks<KP>(masks + at[u], m[u]), load_probs<KP>(probs + at[u], p[u]);
+#pragma unroll
+            for (int u = 0; u < kLongDtkpCol; ++u)
+                if (at[u] >= 0) {
+#pragma unroll
+                    for (int x = 0; x < KP; ++x) bad |= p[u][x] == 0.0f && m[u][x] != kAbsent;
+                }
+            if (lanes > 1) bad = (__ballot(bad) >> (threadIdx.x & (kWave - lanes)) & ((uint64_t(1) << lanes) - 1)) != 0;
+        }
+#pragma unroll
+        for (int x = 0; x < KP; ++x)
+            if (keys.present(x)) bad |= top.m[x] == kAbsent;
+        return !bad;
     }
     __device__ __forceinline__ void laned(TopK<KP> &top, uint32_t len, int32_t r, uint32_t c) const
     {
@@ -529,14 +557,14 @@ template <int KP>
 __global__ void __launch_bounds__(kHugeThreads)
 dtkp_applyk_kernel(ColumnArgs C, TupleArgs A, GroupMasks gm)
 {
-    dtkp_columns<KP>(C, TupleOffer<KP>{A, gm, nullptr, 0});
+    dtkp_columns<KP>(C, TupleOffer<KP>{A, gm, nullptr, 0, {}});
 }
 
 template <int KP>
 static void launch_dtkp_k(ColumnArgs C, const TupleArgs &A, const GroupMasks &gm, hipStream_t st)
 {
     const unsigned grid = column_launch(C);
-    hipLaunchKernelGGL(dtkp_applyk_kernel<KP>, dim3(grid), dim3(column_threads(C)), column_lds<KP>(column_threads(C)), st, C, A, gm);
+    hipLaunchKernelGGL(dtkp_applyk_kernel<KP>, dim3(grid), dim3(column_threads(C)), 0, st, C, A, gm);
 }
 
 // ---------------------------------------------------------------- plan

@@ -135,10 +135,16 @@ struct PairOffer {
         run(top, q, q1, step, [&](uint32_t x) { return A.col_ij[x]; });
     }
     __device__ __forceinline__ bool has_short() const { return A.fact_b && A.ap; }
-    template <class Word, class Put>
-    __device__ __forceinline__ void run_short(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, int id, Word word, Put put) const
+    // (the masks of a lane's few tuples wait in LDS for the winners; a key's id is the candidate's number in its lane, and the
+    // lane's thread << 8)
+    template <class Word>
+    __device__ __forceinline__ void run_short(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, Word word) const
     {
-        for (; q < q1; q += step, id += K) {
+        extern __shared__ __align__(16) uint64_t lane_masks[];
+        static_assert(K * kLongDtkpCol <= 256 || K > kKeyProofs, "a candidate's number");
+        uint64_t *put = lane_masks + threadIdx.x;
+        int id = threadIdx.x << 8;
+        for (; q < q1; q += step, id += K, put += K * blockDim.x) {
             const uint32_t ij = word(q);
             const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K;
             const uint4 f = reinterpret_cast<const uint4 *>(A.fact_b)[ij >> 16];
@@ -153,20 +159,30 @@ struct PairOffer {
                 if (ma[x] == kAbsent || (ma[x] & rival)) continue;
                 const bool held = (ma[x] & bit) != 0;
                 const float pr = held || ma[x] < bit ? (held ? pa[x] : pa[x] * pbit) : proof_prob(ma[x] | bit, fp);
-                put(id + x, ma[x] | bit);
+                put[x * blockDim.x] = ma[x] | bit;
                 keys.offer(pr, id + x);
             }
         }
     }
-    template <class Put>
-    __device__ __forceinline__ void short_listed(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, int id, Put put) const
+    __device__ __forceinline__ void short_listed(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step) const
     {
-        run_short(keys, q, q1, step, id, [&](uint32_t x) { return A.col_ij[x]; }, put);
+        run_short(keys, q, q1, step, [&](uint32_t x) { return A.col_ij[x]; });
     }
-    template <class Put>
-    __device__ __forceinline__ void short_laned(TopKeys<K> &keys, uint32_t len, int32_t r, int id, Put put) const
+    __device__ __forceinline__ void short_laned(TopKeys<K> &keys, uint32_t len, int32_t r) const
     {
-        run_short(keys, 0, len, 1, id, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; }, put);
+        run_short(keys, 0, len, 1, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; });
+    }
+    __device__ __forceinline__ bool short_take(TopK<K> &top, const TopKeys<K> &keys, int) const
+    {
+        extern __shared__ __align__(16) uint64_t lane_masks[];
+        wave_lds_fence();
+#pragma unroll
+        for (int x = 0; x < K; ++x) {
+            if (!keys.present(x)) continue;
+            top.m[x] = lane_masks[(keys.id(x) & 255) * blockDim.x + (keys.id(x) >> 8)];
+            top.p[x] = keys.prob(x);
+        }
+        return true;
     }
     __device__ __forceinline__ void laned(TopK<K> &top, uint32_t len, int32_t r, uint32_t) const
     {
@@ -185,7 +201,8 @@ template <int K>
 static void launch_apply2_k(ColumnArgs C, const PairArgs &A, const GroupMasks &gm, hipStream_t st)
 {
     const unsigned grid = column_launch(C);
-    hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid), dim3(column_threads(C)), column_lds<K>(column_threads(C)), st, C, A, gm);
+    const size_t lds = K <= kKeyProofs && A.fact_b ? sizeof(uint64_t) * column_threads(C) * kLongDtkpCol * K : 0;     // a lane's masks: 96 bytes at three proofs
+    hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid), dim3(column_threads(C)), lds, st, C, A, gm);
 }
 
 #define DOL_DISPATCH_K(k, CALL)                                      \

@@ -58,32 +58,17 @@ inline unsigned column_launch(ColumnArgs &A)
 
 // Offer: begin(s) - the sample; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
 // laned(top, len, r, c) - those of column c, the r-th in order; where it has_short(), short_listed and short_laned offer the same,
-// of at most kLongDtkpCol tuples a lane, to a list of keys, put(id, mask) keeping the masks.
+// of at most kLongDtkpCol tuples a lane, to a list of keys, and short_take() finds the proofs of the list, the same of
+// `lanes` lanes, or says that it cannot (to each of them).
 // (A candidate's way into a list of probabilities and masks takes some thirty instructions, most of them choices, and so does each
-// entry of another lane's list; into a list of keys seven, and a whole list of three twelve and the lane shifts.  The masks of a
-// lane's few tuples wait in LDS for the winners.)
-constexpr int kKeyProofs = 4;           // longest lists ranked by keys: 96 bytes of LDS a lane at three proofs, 128 at four
-template <int K>
-inline size_t column_lds(int threads) { return K <= kKeyProofs ? sizeof(uint64_t) * threads * kLongDtkpCol * K : 0; }
+// entry of another lane's list; into a list of keys seven, and a whole list of three twelve and the lane shifts.)
+constexpr int kKeyProofs = 4;           // longest lists ranked by keys
 
-static_assert(kKeyProofs * kLongDtkpCol <= 256 && kMidDtkpCol <= 4 * kLongDtkpCol && kWaveDtkpCol <= 16 * kLongDtkpCol, "a lane's tuples");
-
-// A key's id: the candidate's number in its lane, and the lane's thread << 8.
-template <int K>
-__device__ __forceinline__ void take_keys(TopK<K> &top, const TopKeys<K> &keys, const uint64_t *masks, int T)
-{
-#pragma unroll
-    for (int x = 0; x < K; ++x) {
-        if (!keys.present(x)) continue;
-        top.m[x] = masks[(keys.id(x) & 255) * T + (keys.id(x) >> 8)];
-        top.p[x] = keys.prob(x);
-    }
-}
+static_assert(kMidDtkpCol <= 4 * kLongDtkpCol && kWaveDtkpCol <= 16 * kLongDtkpCol, "a lane's tuples");
 
 template <int K, class Offer>
 __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
 {
-    extern __shared__ __align__(16) uint64_t lane_masks[];
     const int T = blockDim.x, t = threadIdx.x;
     TopK<K> top;
     top.clear();
@@ -115,16 +100,15 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
         if constexpr (K <= kKeyProofs) {
             if (lanes <= 16 && offer.has_short()) {             // (at most kLongDtkpCol tuples a lane)
                 TopKeys<K> keys;
-                offer.short_listed(keys, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes, t << 8, [&](int id, uint64_t m) { lane_masks[(id & 255) * T + t] = m; });
+                offer.short_listed(keys, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes);
                 keys.merge(lanes);
-                if (!keys.unclear()) {                          // (the same for all lanes of the group)
-                    wave_lds_fence();
+                if (!keys.unclear() && offer.short_take(top, keys, lanes)) {       // (the same for all lanes of the group)
                     if (t % lanes != 0) return;
-                    take_keys(top, keys, lane_masks, T);
                     const int64_t o = static_cast<int64_t>(s) * A.S + c;
                     A.oprob[s * A.ldo + c] = top.store(A.om + o * K, A.op + o * K);
                     return;
                 }
+                top.clear();
             }
         }
         offer.listed(top, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes);
@@ -166,12 +150,14 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
     if constexpr (K <= kKeyProofs) {
         if (offer.has_short()) {            // (the same for all)
             TopKeys<K> keys;
-            offer.short_laned(keys, len, r, t << 8, [&](int id, uint64_t m) { lane_masks[(id & 255) * T + t] = m; });
-            todo = keys.unclear();
-            if (!todo) take_keys(top, keys, lane_masks, T);
+            offer.short_laned(keys, len, r);
+            todo = keys.unclear() || !offer.short_take(top, keys, 1);
         }
     }
-    if (__builtin_expect(todo, 0)) offer.laned(top, len, r, c);
+    if (__builtin_expect(todo, 0)) {
+        top.clear();
+        offer.laned(top, len, r, c);
+    }
     const int64_t o = static_cast<int64_t>(s) * A.S + c;
     A.oprob[s * A.ldo + c] = top.store(A.om + o * K, A.op + o * K);
 }

@@ -2513,6 +2513,10 @@ def test_dtkp_columns_ranked_by_keys(dol, k, values):
     np.testing.assert_array_equal(host(got.proof_mask).view(np.uint64), um)
     np.testing.assert_array_equal(host(got.proof_prob), up)
     assert_close(host(got.prob), upr, "unary, ranked by keys")
+    x.proof_prob[x.proof_mask == -1] = 0.7          # what an absent proof's probability says counts for nothing
+    dol.apply_k([x], fu, prov, got)
+    np.testing.assert_array_equal(host(got.proof_mask).view(np.uint64), um)
+    np.testing.assert_array_equal(host(got.proof_prob), up)
 
 
 @pytest.mark.parametrize("k", [1, 3])
