@@ -563,7 +563,7 @@ dtkp_applyk_kernel(ColumnArgs C, TupleArgs A, GroupMasks gm)
 template <int KP>
 static void launch_dtkp_k(ColumnArgs C, const TupleArgs &A, const GroupMasks &gm, hipStream_t st)
 {
-    const unsigned grid = column_launch(C);
+    const unsigned grid = column_launch<KP>(C);
     hipLaunchKernelGGL(dtkp_applyk_kernel<KP>, dim3(grid), dim3(column_threads(C)), 0, st, C, A, gm);
 }
 
@@ -765,7 +765,7 @@ dol_status dol_apply_k(int32_t K, const dol_dist *const *in, const dol_fnk_table
     KProofs pr{};
     for (int l = 0; l < K; ++l) { pr.m[l] = in[l]->proof_mask; pr.p[l] = in[l]->proof_prob; pr.n[l] = in[l]->n_sym; }
     ColumnArgs C{};
-    C.batch = batch, C.S = f->n_out;
+    C.batch = batch, C.S = f->n_out, C.n_in = f->row_base[K];
     C.col_ptr = f->col_ptr.ptr;
     set_columns(C, f->dtkp_cols);
     C.om = out->proof_mask, C.op = out->proof_prob, C.oprob = out->prob, C.ldo = out->ld;

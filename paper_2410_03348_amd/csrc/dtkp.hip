@@ -200,7 +200,7 @@ dtkp_apply2_kernel(ColumnArgs C, PairArgs A, GroupMasks gm)
 template <int K>
 static void launch_apply2_k(ColumnArgs C, const PairArgs &A, const GroupMasks &gm, hipStream_t st)
 {
-    const unsigned grid = column_launch(C);
+    const unsigned grid = column_launch<K>(C);
     const size_t lds = K <= kKeyProofs && A.fact_b ? sizeof(uint64_t) * column_threads(C) * kLongDtkpCol * K : 0;     // a lane's masks: 96 bytes at three proofs
     hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid), dim3(column_threads(C)), lds, st, C, A, gm);
 }
@@ -228,7 +228,7 @@ dol_status launch_dtkp_apply2(const dol_fn_table *f, int32_t batch, int32_t k, i
     if (static_cast<int64_t>(batch) * static_cast<int64_t>(f->dtkp_cols.longer.n) > 0x7fffffffLL)
         return fail(DOL_EUNSUPPORTED, "batch x long table columns exceeds 2^31");
     ColumnArgs C{};
-    C.batch = batch, C.S = f->n_out;
+    C.batch = batch, C.S = f->n_out, C.n_in = f->na + (fact_b ? 0 : f->nb);
     C.col_ptr = f->col_ptr.ptr;
     set_columns(C, f->dtkp_cols);
     C.om = om, C.op = op, C.oprob = oprob, C.ldo = ldo;

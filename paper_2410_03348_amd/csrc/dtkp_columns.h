@@ -19,10 +19,17 @@
 
 namespace dol {
 
+// Workgroups of the columns of 16 lanes, four and one in a set of samples (multiples of eight: the XCDs' turns stay the same).
+struct SetBlocks {
+    uint32_t mid, quad, lane;
+};
+
 struct ColumnArgs {
-    int32_t batch, S;
+    int32_t batch, S, n_in;                 // n_in: the operands' symbols, of lists of their own
     int32_t n_huge, n_wave, n_mid, n_quad;  // `longer`: columns of a workgroup each, of a wavefront, of 16 lanes, of four
-    uint32_t b_huge, b_wave, b_mid, b_quad; // workgroups of each kind (multiples of eight: the XCDs' turns stay the same)
+    uint32_t b_huge, b_wave;                // workgroups of these kinds, all samples'
+    int32_t set, sets;                      // the other columns: samples of a set (the last one holds the remainder too), sets
+    SetBlocks full, last;
     const uint32_t *longer;
     const uint32_t *col_ptr;                // tuples of a column
     const uint32_t *order, *len;            // short columns: the r-th one and its length (0: among the longer ones)
@@ -43,17 +50,35 @@ constexpr int kColumnThreads = 128, kHugeThreads = 256;
 inline int column_threads(const ColumnArgs &A) { return A.n_huge > 0 ? kHugeThreads : kColumnThreads; }
 
 // How the columns go into workgroups; returns how many there are.
+//
+// Where the lists of all samples exceed the L2s, the samples go in sets, one sample's columns of all lengths (the very long
+// ones apart: they start first) close together: a line of results holds columns of several lengths and leaves the L2 whole, and
+// its lists are read once.  A set is eight samples, one for each XCD, or more where they are small, so that a set has work for the whole chip.
+// (Seven-symbol expression, k = 3: with 64 samples the last table writes 116 instead of 149 MB and the unary Apply behind it takes
+// 26.6 instead of 29.1 us, the pass 177 instead of 180; with 128 samples 288 instead of 311 us, with 1 024 2 186 instead of
+// 2 668.  Sets of 16 or 32: 178 and 179, 2 237 and 2 252.  With 16 samples, 27 MB, two sets cost 2 %.  The very long columns in
+// their sets: 185, the last set's workgroup columns ending late.)
+constexpr int64_t kL2Bytes = int64_t(32) << 20, kSetBytes = int64_t(8) << 20;
+template <int K>
 inline unsigned column_launch(ColumnArgs &A)
 {
     const int threads = column_threads(A);
+    const int64_t sample = (static_cast<int64_t>(A.S) + A.n_in) * (K * (sizeof(uint64_t) + sizeof(float)));
+    A.set = A.batch, A.sets = 1;
+    if (A.batch * sample > kL2Bytes) {
+        const int64_t set = std::max<int64_t>(8, kSetBytes / sample / 8 * 8);
+        if (A.batch >= 2 * set) A.set = static_cast<int32_t>(set), A.sets = static_cast<int32_t>(A.batch / set);
+    }
     auto eight = [](int64_t n) { return static_cast<uint32_t>((n + 7) / 8 * 8); };
-    auto groups = [&](int32_t n, int lanes) { return eight(static_cast<int64_t>(A.batch) * ((n + threads / lanes - 1) / (threads / lanes))); };
+    auto groups = [&](int32_t samples, int32_t n, int lanes) { return eight(static_cast<int64_t>(samples) * ((n + threads / lanes - 1) / (threads / lanes))); };
+    auto blocks = [&](int32_t samples) {
+        return SetBlocks{groups(samples, A.n_mid, 16), groups(samples, A.n_quad, 4), eight((static_cast<int64_t>(samples) * A.S + threads - 1) / threads)};
+    };
+    auto all = [](const SetBlocks &b) { return b.mid + b.quad + b.lane; };
     A.b_huge = eight(static_cast<int64_t>(A.batch) * A.n_huge);
-    A.b_wave = groups(A.n_wave, kWave);
-    A.b_mid = groups(A.n_mid, 16);
-    A.b_quad = groups(A.n_quad, 4);
-    const int64_t total = static_cast<int64_t>(A.batch) * A.S;
-    return A.b_huge + A.b_wave + A.b_mid + A.b_quad + static_cast<unsigned>((total + threads - 1) / threads);
+    A.b_wave = groups(A.batch, A.n_wave, kWave);
+    A.full = blocks(A.set), A.last = blocks(A.batch - (A.sets - 1) * A.set);
+    return A.b_huge + A.b_wave + (A.sets - 1) * all(A.full) + all(A.last);
 }
 
 // Offer: begin(s) - the sample; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
@@ -72,8 +97,18 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
     const int T = blockDim.x, t = threadIdx.x;
     TopK<K> top;
     top.clear();
-    const uint32_t first = A.b_huge + A.b_wave + A.b_mid + A.b_quad;
     uint32_t b = blockIdx.x;
+    int32_t s0 = 0, samples = A.batch;
+    SetBlocks B{0, 0, 0};
+    const uint32_t very_long = A.b_huge + A.b_wave;
+    if (b >= very_long) {
+        const uint32_t per_set = A.full.mid + A.full.quad + A.full.lane, set = min((b - very_long) / per_set, static_cast<uint32_t>(A.sets - 1));
+        const bool last = set == static_cast<uint32_t>(A.sets - 1);
+        B = last ? A.last : A.full;
+        s0 = set * A.set, samples = last ? A.batch - s0 : A.set;
+        b -= set * per_set;
+    }
+    const uint32_t first = very_long + B.mid + B.quad;
     if (b < first) {
         // ---- a longer column: every lane streams a share of its tuples through a list of its own; the lists of a group of
         // lanes meet by exchange rounds in which each lane offers its partner's entries to its own list.  (The list order is
@@ -87,13 +122,13 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
             lanes = l, n = count, blocks = its;
         };
         next(kWave, A.n_wave, A.b_wave);
-        next(16, A.n_mid, A.b_mid);
-        next(4, A.n_quad, A.b_quad);
+        next(16, A.n_mid, B.mid);
+        next(4, A.n_quad, B.quad);
         const bool huge = lanes == T;
         const int per = T / lanes, groups = (n + per - 1) / per;
         const int32_t id = xcd_contiguous(b, blocks);               // (a sample's columns on one XCD: its lists fill one L2)
-        const int32_t s = id / groups, ci = (id - s * groups) * per + t / lanes;
-        if (s >= A.batch) return;
+        const int32_t in_set = id / groups, ci = (id - in_set * groups) * per + t / lanes, s = s0 + in_set;
+        if (in_set >= samples) return;
         if (ci >= n) return;                        // (all lanes of a group; never a huge column's)
         const uint32_t c = A.longer[from + ci];
         offer.begin(s);
@@ -138,10 +173,10 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
         }
         return;
     }
-    const int32_t id = xcd_contiguous(b - first, gridDim.x - first);
+    const int32_t id = xcd_contiguous(b - first, B.lane);
     const int64_t at = static_cast<int64_t>(id) * T + t;
-    if (at >= static_cast<int64_t>(A.batch) * A.S) return;
-    const int32_t s = static_cast<int32_t>(at / A.S), r = static_cast<int32_t>(at - static_cast<int64_t>(s) * A.S);
+    if (at >= static_cast<int64_t>(samples) * A.S) return;
+    const int32_t in_set = static_cast<int32_t>(at / A.S), r = static_cast<int32_t>(at - static_cast<int64_t>(in_set) * A.S), s = s0 + in_set;
     // lanes of a wavefront: columns of like length
     const uint32_t len = A.len[r], c = A.order[r];
     if (len == 0) return;

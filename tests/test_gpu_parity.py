@@ -2519,6 +2519,43 @@ def test_dtkp_columns_ranked_by_keys(dol, k, values):
     np.testing.assert_array_equal(host(got.proof_prob), up)
 
 
+@pytest.mark.parametrize("k,batch", [(1, 1200), (3, 400), (3, 433), (4, 290), (5, 231), (8, 140)])
+def test_dtkp_columns_in_sets_of_samples(dol, k, batch):
+    """Batches whose lists exceed the L2s are worked on in sets of samples, the last one larger: each sample's results are those of
+    the same sample in a batch of one set."""
+    lengths = [3000, 90, 70, 40, 17, 16, 9, 5] * 2 + [4] * 30 + [3] * 40 + [2] * 300 + [1] * 1200
+    na, nb, n_facts, part = 1001, 10, 24, 25
+    n, S = sum(lengths), len(lengths)
+    assert n <= na * nb and batch * (S + na) * 12 * k > 32 << 20
+    fp = W.uniform01(151, batch * n_facts).astype(np.float32).reshape(batch, n_facts)
+    grp = np.concatenate([np.arange(14), np.full(10, 14)]).astype(np.int32)
+    table = np.full(na * nb, -1, np.int32)
+    col = np.repeat(np.arange(S), lengths).astype(np.int32)
+    table[np.argsort(W.splitmix64(152, np.arange(na * nb)))[:n]] = col
+    f = dol.FnTable.create_dense(table.reshape(na, nb))
+    final = (W.splitmix64(153, np.arange(S)) % np.uint64(400)).astype(np.int32)
+    fu = dol.FnkTable.create_dense(final)
+    fact_b = np.arange(14, 24, dtype=np.int32)
+    gen = torch.Generator(device="cuda").manual_seed(154)
+    bits = torch.randint(0, 14, (batch, na, k), generator=gen, device="cuda")
+    am = torch.sort(torch.bitwise_or(torch.ones_like(bits) << bits, torch.ones_like(bits) << (bits * 5 + 3) % 14), -1).values
+    ap = torch.rand((batch, na, k), generator=gen, device="cuda")
+
+    def run(s0, s1):
+        prov = dol.Prov(dol.DTKP, k, dev(fp[s0:s1]), grp)
+        a = dol.Dist(np.arange(na), torch.zeros((s1 - s0, na), device="cuda"), am[s0:s1].contiguous(), ap[s0:s1].contiguous())
+        out = dol.Dist.empty(f.out_syms, s1 - s0, k=k)
+        dol.dtkp_apply2_input(a, fact_b, f, prov, out)
+        end = dol.Dist.empty(fu.out_syms, s1 - s0, k=k)
+        dol.apply_k([out], fu, prov, end)
+        return out.proof_mask, out.proof_prob, out.prob, end.proof_mask, end.proof_prob, end.prob
+
+    whole = run(0, batch)
+    parts = [run(s, min(s + part, batch)) for s in range(0, batch, part)]
+    for x, got in enumerate(whole):
+        assert torch.equal(got, torch.cat([p[x] for p in parts])), x
+
+
 @pytest.mark.parametrize("k", [1, 3])
 def test_dtkp_apply2_input_equals_init_then_apply2(dol, k):
     """The second operand given by its facts: bit for bit what dol_dtkp_init + dol_apply2 give, on a table with
