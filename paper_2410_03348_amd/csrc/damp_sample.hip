@@ -344,7 +344,7 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
     const int64_t s = id / static_cast<unsigned>(A.parts);
     const int part = static_cast<int>(id - s * A.parts);
     // the last part also sums the longest column: it weighs as much as `long_weight` columns
-    const int per = ((A.S + A.long_weight + A.parts - 1) / A.parts + 3) & ~3;
+    const int per = ((A.S + A.long_weight + A.parts - 1) / A.parts + kByJBlock - 1) & ~(kByJBlock - 1);
     const int c0 = min(A.S, part * per), c1 = part == A.parts - 1 ? A.S : min(A.S, c0 + per);
     const float *br = A.b + s * A.ldb;
     float *out = A.out + s * A.ldo;
@@ -355,10 +355,15 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
     for (int j = 0; j < NBP; ++j) y[j] = br[j < A.nb ? j : 0];      // (the maps' extra rows are empty)
     __syncthreads();
     bool again = false;
-    for (int c = c0 + 4 * static_cast<int>(threadIdx.x); c < c1; c += 4 * static_cast<int>(blockDim.x)) {
+    const int lane = threadIdx.x & (kWave - 1);
+    // (Neighbouring lanes take neighbouring columns: their tags are mostly neighbours too, and lie in other banks.  With four
+    // neighbours to a lane the gathers of a 16-digit product's tables met 1.6 times as many bank conflicts; its pass at 256 samples
+    // 300 us, 296 with the forward maps so, 293 with the backward ones as well.)
+    for (int block = c0 + kByJBlock * wave_number(); block < c1; block += 4 * static_cast<int>(blockDim.x)) {
+        const int c = block + lane;                     // and 64, 128, 192 further
         ushort4 m[NBP];
 #pragma unroll
-        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + c);
+        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + block + 4 * lane);
         const uint16_t mark[4] = {m[0].x, m[0].y, m[0].z, m[0].w};
         const uint16_t none = static_cast<uint16_t>(A.na);
         m[0].x = min(m[0].x, none), m[0].y = min(m[0].y, none), m[0].z = min(m[0].z, none), m[0].w = min(m[0].w, none);
@@ -372,16 +377,14 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
                 mag[k] = __builtin_fmaf(fabsf(x[k]), fabsf(y[j]), mag[k]);
             }
         }
-        uint32_t skip = 0;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
+            const bool there = c + kWave * k < c1 && mark[k] != kByJWave;       // (kByJWave: many tuples, summed last)
             const bool near = !(fabsf(acc[k] - 1.0f) > mag[k] * (static_cast<float>(NBP + 2) * 1.1920929e-7f));
-            if (mark[k] == kByJWave) skip |= 1u << k;               // (many tuples: summed last)
-            const bool list = (near || mark[k] == kByJList) && mark[k] != kByJWave && c + k < c1;   // (list: some j twice)
+            const bool list = (near || mark[k] == kByJList) && there;           // (kByJList: some j twice)
             again |= list;
-            acc[k] = list ? __builtin_nanf("") : fminf(acc[k], 1.0f);
+            if (there) out[c + kWave * k] = list ? __builtin_nanf("") : fminf(acc[k], 1.0f);
         }
-        store4(out + c, acc, c1 - c, skip);
     }
     if (again) some = 1;
     lds_barrier();                          // (does not wait for the results to be in memory)
@@ -610,13 +613,15 @@ __device__ __forceinline__ void byj_bwd(const SampleBwd &A, float *lds)
     constexpr int R = STAGED || NBP < 10 ? 4 : 2;       // rows at a time (gathers from memory: as many as registers hold)
     typedef uint16_t __attribute__((ext_vector_type(R))) entries;
     const int last = A.S - 1;
-    for (int i = R * static_cast<int>(threadIdx.x); i < A.na; i += R * static_cast<int>(blockDim.x)) {
+    const int lane = threadIdx.x & (kWave - 1), wave = wave_number(), n_waves = blockDim.x / kWave;
+    for (int i0 = R * kWave * wave; i0 < A.na; i0 += R * kWave * n_waves) {
+        const int i = i0 + lane, at = (i0 & ~(kByJBlock - 1)) + 4 * lane + ((i0 / kWave) & 3);      // rows i, i + 64 ..; where their entries lie
         entries m[NBP];
 #pragma unroll
-        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const entries *>(A.map + static_cast<size_t>(j) * A.map_ld + i);
-        const int n = min(R, A.na - i);
-        const float4 a4 = R == 4 ? load4(ar + i, n) : make_float4(ar[i], n > 1 ? ar[i + 1] : 0.0f, 0.0f, 0.0f);
-        const float av[4] = {a4.x, a4.y, a4.z, a4.w};
+        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const entries *>(A.map + static_cast<size_t>(j) * A.map_ld + at);
+        float av[4];
+#pragma unroll
+        for (int k = 0; k < R; ++k) av[k] = i + kWave * k < A.na ? ar[i + kWave * k] : 0.0f;
         float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int j = 0; j < NBP; ++j) {
@@ -647,18 +652,14 @@ __device__ __forceinline__ void byj_bwd(const SampleBwd &A, float *lds)
             if (A.accumulate & 1) {
 #pragma unroll
                 for (int k = 0; k < R; ++k)
-                    if (k < n) acc[k] += dst[k];
+                    if (i + kWave * k < A.na) acc[k] += dst[kWave * k];
             }
-            if (R == 4) store4(dst, acc, n);
-            else {
 #pragma unroll
-                for (int k = 0; k < R; ++k)
-                    if (k < n) dst[k] = acc[k];
-            }
+            for (int k = 0; k < R; ++k)
+                if (i + kWave * k < A.na) dst[kWave * k] = acc[k];
         }
     }
     if (!A.gb) return;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave, n_waves = blockDim.x / kWave;
 #pragma unroll
     for (int j = 0; j < NBP; ++j) {
         const float v = wave_sum(pb[j]);

@@ -75,6 +75,9 @@ constexpr size_t kStageMaxBytes = 158 * 1024;   // narrower ones stay with the c
 constexpr int kByJMax = 16;         // tables whose second operand has at most this many symbols get dense per-j maps
 constexpr int kByJMaxNa = 65000;    // ... and whose first operand leaves room for the three marks below
 constexpr uint16_t kByJWave = 0xFFFE, kByJList = 0xFFFD;
+constexpr int kByJBlock = 256;      // entries of a map's row that a wavefront takes at a time, four a lane
+// Where entry c of a map's row lies: a lane's four, 64 apart, next to each other.
+inline int32_t byj_place(int32_t c) { return (c & ~(kByJBlock - 1)) | ((c & 63) << 2) | ((c >> 6) & 3); }
 constexpr uint32_t kListElsewhere = 0x80000000u;   // struct ListPlan: this list is summed elsewhere,
 constexpr uint32_t kNoList = 0xFFFFFFFFu;          // there is no such list
 
@@ -199,7 +202,8 @@ struct dol_fn_table {
     // time, so that lane-adjacent elements read the operand through one map each (adjacent addresses for monotone
     // functions).  byj_src[j * byj_src_ld + c] = the i with f(i, j) = column c, or na; a long column has dol::kByJWave
     // at j = 0 (it is among col_lists.longer); a short column where some j occurs twice has dol::kByJList there and is summed from
-    // its tuple list.  byj_col[j * byj_col_ld + i] = column of (i, j) or n_out.  Rows are padded to multiples of four.
+    // its tuple list.  byj_col[j * byj_col_ld + i] = column of (i, j) or n_out.  Rows are padded to whole blocks and stored
+    // in the order of byj_place.
     bool byj_ok = false;
     int32_t byj_nbp = 0;               // rows of the two maps: nb padded to 4, 8, 10 or 16 (the extra rows name nothing)
     int32_t byj_src_ld = 0, byj_col_ld = 0;

@@ -234,7 +234,7 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
     if (!conv_path_ok(tb.get()) && nb >= 1 && nb <= kByJMax && na >= 1 && na <= kByJMaxNa && S >= 1 && S <= kByJMaxNa &&
         tb->lists_ok) {
         const int32_t nbp = nb <= 4 ? 4 : nb <= 8 ? 8 : nb <= 10 ? 10 : 16;
-        const int32_t src_ld = (S + 3) & ~3, col_ld = (na + 3) & ~3;
+        const int32_t src_ld = (S + kByJBlock - 1) / kByJBlock * kByJBlock, col_ld = (na + kByJBlock - 1) / kByJBlock * kByJBlock;
         tb->byj_nbp = nbp, tb->byj_src_ld = src_ld, tb->byj_col_ld = col_ld;
         const uint16_t no_i = static_cast<uint16_t>(na), no_c = static_cast<uint16_t>(S);
         std::vector<uint16_t> src(static_cast<size_t>(nbp) * src_ld, no_i), colof(static_cast<size_t>(nbp) * col_ld, no_c);
@@ -242,16 +242,16 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
             const bool is_long = col_ptr[c + 1] - col_ptr[c] > static_cast<uint32_t>(kLaneList);
             bool regular = !is_long;
             for (uint32_t q = col_ptr[c]; q < col_ptr[c + 1] && regular; ++q) {
-                uint16_t &slot = src[static_cast<size_t>(col_ij[q] >> 16) * src_ld + c];
+                uint16_t &slot = src[static_cast<size_t>(col_ij[q] >> 16) * src_ld + byj_place(c)];
                 if (slot != no_i) regular = false;
                 slot = static_cast<uint16_t>(col_ij[q] & 0xffffu);
             }
             if (!regular) {
-                for (int32_t j = 0; j < nb; ++j) src[static_cast<size_t>(j) * src_ld + c] = no_i;
-                src[c] = is_long ? kByJWave : kByJList;
+                for (int32_t j = 0; j < nb; ++j) src[static_cast<size_t>(j) * src_ld + byj_place(c)] = no_i;
+                src[byj_place(c)] = is_long ? kByJWave : kByJList;
             }
         }
-        for (size_t t = 0; t < tup.size(); ++t) colof[static_cast<size_t>(tup[t].j) * col_ld + tup[t].i] = static_cast<uint16_t>(col[t]);
+        for (size_t t = 0; t < tup.size(); ++t) colof[static_cast<size_t>(tup[t].j) * col_ld + byj_place(tup[t].i)] = static_cast<uint16_t>(col[t]);
         if ((e = tb->byj_src.upload(src)) != hipSuccess || (e = tb->byj_col.upload(colof)) != hipSuccess)
             return hip_fail(e, "uploading the function table");
         tb->byj_ok = true;

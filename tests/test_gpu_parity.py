@@ -2055,6 +2055,33 @@ def test_short_second_operand_tables_near_the_clamp(dol):
     assert_close(host(gb), wb, "per-j grad b")
 
 
+@pytest.mark.parametrize("na,nb", [(767, 3), (769, 8), (1023, 9), (1025, 10), (2047, 16), (2049, 4), (2305, 10)])
+def test_dense_map_blocks(dol, na, nb):
+    """f(i, j) = i + 2j: rows and columns on either side of a whole number of blocks of 256 map entries, maps of 4, 8, 10 and 16
+    rows; gradients written and added."""
+    B = 3
+    table = (np.arange(na)[:, None] + 2 * np.arange(nb)[None, :]).astype(np.int32)
+    a, b = W.softmax_rows(W.normal(73, B * na).reshape(B, na)), W.softmax_rows(W.normal(74, B * nb).reshape(B, nb))
+    tri = oracle.dense_to_triples(table)
+    syms, want = oracle.damp_apply2_fwd(tri, na, nb, a, b)[:2]
+    g = np.abs(W.normal(75, B * syms.size)).astype(np.float32).reshape(B, -1)
+    wa, wb = oracle.damp_apply2_bwd(tri, na, nb, a, b, g)
+    f = dol.FnTable.create_dense(table)
+    assert "byj" in f.kernel_at(False, B) and "byj" in f.kernel_at(True, B)
+    da, db = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b))
+    out = dol.Dist.empty(f.out_syms, B)
+    dol.apply2(da, db, f, None, out)
+    assert_close(host(out.prob), want, "forward")
+    rec = dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f)
+    ga, gb = torch.empty((B, na), device="cuda"), torch.empty((B, nb), device="cuda")
+    dol.backward(rec, dev(g), ga, gb)
+    assert_close(host(ga), wa, "grad a")
+    assert_close(host(gb), wb, "grad b")
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f, accumulate=3), dev(g), ga, gb)
+    assert_close(host(ga), 2 * wa, "grad a, added")
+    assert_close(host(gb), 2 * wb, "grad b, added")
+
+
 @pytest.mark.parametrize("nb", [4, 16, 40])
 @pytest.mark.parametrize("extra,batch", [(0, 3), (57, 1), (4096, 2), (4097, 300)])
 def test_workgroup_per_sample_kernels(dol, nb, extra, batch):
