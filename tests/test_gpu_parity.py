@@ -2688,3 +2688,43 @@ def test_sum_shaped_apply_with_short_first_operand(dol, m, nb, batch):
     dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), dev(g), ga, gb)
     assert_close(host(ga), wa, "short first operand grad a")
     assert_close(host(gb), wb, "short first operand grad b")
+
+
+def test_first_call_of_a_generated_kernel_while_capturing(dol):
+    """A graph may be recorded from the very first call: a table of 30 x 21 symbols whose kernels are made at that moment, both
+    directions, and a sum of 20 digits, which the generated fold takes."""
+    B, na, nb = 30000, 30, 21
+    f = dol.FnTable.create_dense(_rand_table(81, (na, nb), 77))
+    da, db = dol.Dist(np.arange(na), dev(W.softmax_rows(W.normal(82, B * na).reshape(B, na)))), dol.Dist(
+        np.arange(nb), dev(W.softmax_rows(W.normal(83, B * nb).reshape(B, nb))))
+    out = dol.Dist.empty(f.out_syms, B)
+    g = dev(W.normal(84, B * out.n_sym).reshape(B, -1).astype(np.float32))
+    ga, gb = torch.empty((B, na), device="cuda"), torch.empty((B, nb), device="cuda")
+    rec = dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f)
+    p = dev(W.softmax_rows(W.normal(85, 20 * 40 * 10).reshape(-1, 10)).reshape(20, 40, 10))
+    tables, syms = [], np.arange(10, dtype=np.int32)
+    for _ in range(19):
+        tables.append(dol.FnTable.create_dense(syms[:, None] + np.arange(10, dtype=np.int32)[None, :]))
+        syms = tables[-1].out_syms
+    total, grads = dol.Dist.empty(syms, 40), torch.empty_like(p)
+    fold = dol.Fold([dol.Dist(np.arange(10), p[t]) for t in range(20)], tables, out=total,
+                    target_col=torch.arange(40, device="cuda", dtype=torch.int32), grad_inputs=list(grads))
+
+    def step():
+        dol.apply2(da, db, f, None, out)
+        dol.backward(rec, g, ga, gb)
+        dol.fold_apply2(fold)
+
+    results = (out.prob, ga, gb, total.prob, grads)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    step()
+    want = [x.clone() for x in results]
+    for _ in range(3):
+        for x in results:
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(results, want):
+            assert torch.equal(x, y)
