@@ -7,8 +7,8 @@
 // The rows a sample's tuples gather from are copied into LDS first (a cached gather from a row of thousands of tags touches
 // another cache line on every lane, and a compute unit looks up about one line a clock); everything else is read and
 // written coalesced:
-//   * second operands of at most 16 symbols: dense maps, one j at a time, four neighbouring columns (rows) a thread, so
-//     that a map entry costs two bytes of an 8-byte load and results leave as 16-byte stores;
+//   * second operands of at most 16 symbols: dense maps, one j at a time, four columns (rows) a thread, 64 apart, so that a
+//     map entry costs two bytes of an 8-byte load and the lanes of a gather are neighbours, whose tags lie in other banks;
 //   * other tables: tuple lists of columns (rows) sorted by length inside blocks of 4 096 and interleaved in chunks of 64
 //     (struct ListPlan), so that a wavefront's tuples are one 256-byte load and its lanes end together; the forward results
 //     of a block meet in LDS and leave in column order.
@@ -589,7 +589,7 @@ __device__ __forceinline__ bool gated_row(const SampleBwd &A, int64_t s, float *
     return false;
 }
 
-// Dense maps: a thread owns four neighbouring rows of a and adds their shares of gb up in registers; the workgroup's
+// Dense maps: a thread owns four rows of a, 64 apart (see byj_fwd), and adds their shares of gb up in registers; the workgroup's
 // shares meet at the end (so the long rows of b need no launch of their own).  STAGED: the gated gradient row is in LDS.
 // Result rows that do not fit there (more than 40 447 symbols) are gathered from memory, and from LDS a bit per column where
 // the clamp acted, if it acted anywhere in the sample: B=256, 41 000 x 4 -> 41 000 234 us, element by element with a look at
