@@ -14,9 +14,10 @@
 // share.  With every stage's row in LDS a wavefront used 2 556 LDS cycles and 2 806 vector instructions and held 13 KB, so
 // that three shared a SIMD: B=524 288 802 us, B=4 096 11.8.  Now 1 190 cycles, 2 320 instructions, 9 KB and four: 486 and 9.6.
 //
-// A stage's result is kept as x = pre where pre <= 1 and -1 where the clamp acted: |x| is the tag (the absolute value is
-// free in a multiply-add) and the sign is the clamp's decision, read by the reverse sweep with the operand it needs
-// anyway - no stage is ever summed twice.
+// A stage's result is kept as x = pre where pre <= 1 and -1 where the clamp acted: |x| is the tag and the sign is the clamp's
+// decision, read by the reverse sweep with the operand it needs anyway - no stage is ever summed twice.  The tag is taken once
+// an entry: as a modifier of every multiply-add the absolute value asks for the long encoding (Sum-15 with sums at the clamp,
+// B=262 144, us, target / explicit gradient: 586 / 650 so, 293 / 338 once an entry).
 //
 // Under a target the gradient of a late stage is zero but for the few columns from which the remaining digits can reach
 // the target: counted from the target these are the same for every sample, so the reverse sweep of the late stages holds
@@ -41,8 +42,8 @@ constexpr int kL = 16;                  // lanes per sample
 constexpr int kSP = 64 / kL;            // samples per wavefront
 constexpr int kNBR = 16;                // most symbols of a short input
 // Two builds: up to kRoomyGroups workgroups, two to a SIMD, may take 256 registers, larger grids keep to 128 for four
-// (Sum-15, us, roomy / dense: B=4 096 9.5 / 9.9, 8 192 12.3 / 13.1, 12 288 18.1 / 16.4, 262 144 285 / 242; where sums reach the
-// clamp 10.8 / 13.4, -, 20.5 / 20.3, 293 / 281).  kLaneRegs: those for the running Distributions and a stage's operands; what
+// (Sum-15, us, roomy / dense: B=4 096 9.3 / 9.6, 8 192 12.6 / 13.0, 12 288 16.6 / 16.8, 262 144 252 / 254; where sums reach the
+// clamp 10.7 / 11.3, 14.1 / 14.8, 18.6 / 19.1, 290 / 289).  kLaneRegs: those for the running Distributions and a stage's operands; what
 // is too much, from the first Distribution on, waits in LDS, each lane's words apart (Sum-15 keeps 64 words in 128 registers,
 // and 9 KB of LDS leave room for sixteen wavefronts to a unit; B=262 144: 70 words 242 us, 64 242, 60 and 11 KB 250).
 constexpr int kLaneRegs = 111, kLaneRegsRoomy = 220;
@@ -325,7 +326,7 @@ struct Sweep {
         return v;
     }
 
-    // dst<k> = sum over j of the entries k - j of a row with the short operand: descending j (forward) or ascending
+    // dst<k> = sum over j of the entries k - j of a row (of tags) with the short operand: descending j (forward) or ascending
     void convolve(const char *dst, int w, const char *d, int t, const std::vector<std::string> &own, const char *before, bool ascending)
     {
         const int nb = Y.nb[t];
@@ -334,20 +335,21 @@ struct Sweep {
             for (int x = 0; x < nb; ++x) {
                 const int j = ascending ? x : nb - 1 - x, e = k - j;
                 const std::string src = e >= 0 ? own[e] : num(before, -1 - e);
-                o("    %s%d = __builtin_fmaf(%s, %s, %s%d);\n", dst, k, tag(src).c_str(), at(d, t, j).c_str(), dst, k);
+                o("    %s%d = __builtin_fmaf(%s, %s, %s%d);\n", dst, k, src.c_str(), at(d, t, j).c_str(), dst, k);
             }
         }
     }
 
+    // v<t>_<k>: acc_t's block, signs and all; u<t>_<k>: its tags, where there can be signs
     void forward()
     {
         for (int k = 0; k < Y.w[0]; ++k) o("  const float v0_%d = base[%d + l * %d + %d];\n", k, Y.row, Y.w[0], k);
         if (Y.hist[0] >= 0) keep(0);
         for (int t = 1; t <= n1; ++t)
-            for (int k = 0; k < Y.w[t]; ++k) o("  float v%d_%d;\n", t, k);
+            for (int k = 0; k < Y.w[t]; ++k) o(calm ? "  float v%d_%d;\n" : "  float v%d_%d, u%d_%d;\n", t, k, t, k);
         for (int t = 1; t <= n1; ++t) {
             const int nb = Y.nb[t], w = Y.w[t], w1 = Y.w[t - 1];
-            std::vector<std::string> own = block("v", t - 1, w1);
+            std::vector<std::string> own = block(calm || t == 1 ? "v" : "u", t - 1, w1);
             if (w != w1 && t > 1) put_row(own, kL * w);
             if (t == 1) load_d("f", 1);
             if (t < n1) load_d("f", t + 1);             // (on its way meanwhile)
@@ -364,7 +366,7 @@ struct Sweep {
             convolve("p", w, "f", t, own, "e", false);
             for (int k = 0; k < w; ++k) {
                 if (calm) o("    v%d_%d = p%d;\n", t, k, k);
-                else o("    v%d_%d = p%d <= 1.0f ? p%d : -1.0f;\n", t, k, k, k);
+                else o("    v%d_%d = p%d <= 1.0f ? p%d : -1.0f; u%d_%d = fminf(p%d, 1.0f);\n", t, k, k, k, t, k, k);
             }
             o("  }\n");
             fence();
@@ -444,7 +446,12 @@ struct Sweep {
             if ((kL - 1) * w + k >= m) cond = "l < " + std::to_string(ceil_div(m - k, w));
             if (t > 1 && !calm) cond += (cond.empty() ? "!(" : " && !(") + x[k] + " < 0.0f)";
             o("      g%d_%d = %s; }\n", t - 1, k, cond.empty() ? "acc" : (cond + " ? acc : 0.0f").c_str());
-            for (int j = 0; j < nb; ++j) o("    s%d = __builtin_fmaf(gw%d, %s, s%d);\n", j, k + j, tag(x[k]).c_str(), j);
+            std::string y = x[k];
+            if (t > 1 && !calm) {
+                o("    float y%d = __builtin_fabsf(%s); opaque(y%d);\n", k, x[k].c_str(), k);
+                y = num("y", k);
+            }
+            for (int j = 0; j < nb; ++j) o("    s%d = __builtin_fmaf(gw%d, %s, s%d);\n", j, k + j, y.c_str(), j);
         }
         give_gb(t);
         o("  }\n");
