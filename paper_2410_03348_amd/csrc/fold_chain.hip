@@ -10,9 +10,9 @@
 // are registers of the lanes before and come by lane shifts inside the sample's 16 lanes (a shift fills with the zeros that
 // lie outside the row); where the width changes the row passes through LDS.  The widths are chosen for that (plan_widths):
 // Sum-15 takes 1 2 2 3 3 5 5 5 7 7 7 7 9 9 9 columns a lane.  What bounds it is the issue of vector instructions; a lane
-// shift costs two multiply-adds (1.8 and 1.0 ns a SIMD with four wavefronts on it), an LDS word 2 clocks of what four SIMDs
+// shift costs two multiply-adds (1.8 and 1.0 ns a SIMD with four wavefronts of a test of its own on it), an LDS word 2 clocks of what four SIMDs
 // share.  With every stage's row in LDS a wavefront used 2 556 LDS cycles and 2 806 vector instructions and held 13 KB, so
-// that three shared a SIMD: B=524 288 802 us, B=4 096 11.8.  Now 1 190 cycles, 2 320 instructions, 9 KB and four: 486 and 9.6.
+// that three shared a SIMD: B=524 288 802 us, B=4 096 11.8.  Now it holds 7 KB: 493 and 9.2.
 //
 // A stage's result is kept as x = pre where pre <= 1 and -1 where the clamp acted: |x| is the tag and the sign is the clamp's
 // decision, read by the reverse sweep with the operand it needs anyway - no stage is ever summed twice.  The tag is taken once
@@ -41,14 +41,13 @@ namespace {
 constexpr int kL = 16;                  // lanes per sample
 constexpr int kSP = 64 / kL;            // samples per wavefront
 constexpr int kNBR = 16;                // most symbols of a short input
-// Two builds: up to kRoomyGroups workgroups, two to a SIMD, may take 256 registers, larger grids keep to 128 for four
-// (Sum-15, us, roomy / dense: B=4 096 9.3 / 9.6, 8 192 12.6 / 13.0, 12 288 16.6 / 16.8, 262 144 252 / 254; where sums reach the
-// clamp 10.7 / 11.3, 14.1 / 14.8, 18.6 / 19.1, 290 / 289).  kLaneRegs: those for the running Distributions and a stage's operands; what
-// is too much, from the first Distribution on, waits in LDS, each lane's words apart (Sum-15 keeps 64 words in 128 registers,
-// and 9 KB of LDS leave room for sixteen wavefronts to a unit; B=262 144: 70 words 242 us, 64 242, 60 and 11 KB 250).
-constexpr int kLaneRegs = 111, kLaneRegsRoomy = 220;
-constexpr int64_t kRoomyGroups = 2048;
-constexpr size_t kChainLdsMax = 40 * 1024;   // per wavefront: at least four wavefronts per compute unit
+// Registers of a lane for the running Distributions and a stage's operands; what is too much, from the first Distribution on,
+// waits in LDS, each lane's words apart.  (Sum-15 keeps all 75 words, in 140 registers and 7 KB of LDS.  A build of 128 registers
+// and four wavefronts to a SIMD for large grids, with up to 27 KB of LDS, was no faster: Sum-15 B=524 288 488 us, 493 so; 64 and
+// six of 16 symbols, B=262 144, 220 / 221; Sum-20 635 / 426; the most lost 100 and six of ten with an explicit gradient, 237 / 246;
+// and every shape was compiled once for either.)
+constexpr int kLaneRegs = 220;
+constexpr size_t kChainLdsMax = 16 * 1024;   // per wavefront: ten to a compute unit
 
 struct Src {
     std::string s;
@@ -116,7 +115,7 @@ struct Layout {
     int stride = 0;
 };
 
-Layout lay_out(const std::vector<int> &shape, bool roomy)
+Layout lay_out(const std::vector<int> &shape)
 {
     Layout Y;
     const int n = Y.n = shape[0], n1 = n - 1;
@@ -170,7 +169,7 @@ Layout lay_out(const std::vector<int> &shape, bool roomy)
     for (int t = n1 - 1; t >= 0; --t) {
         regs += Y.w[t];
         Y.hist[t] = -1;
-        if (regs <= (roomy ? kLaneRegsRoomy : kLaneRegs)) continue;
+        if (regs <= kLaneRegs) continue;
         Y.hist[t] = pos;
         pos += kL * Y.w[t];
     }
@@ -608,10 +607,10 @@ struct Sweep {
     }
 };
 
-// cls[t]: the first input whose leading dimension is that of input t.
-std::string chain_source(const std::vector<int> &shape, const std::vector<int> &cls, bool roomy)
+// cls[t]: the first input that shares the registers of its rows' addresses with input t (see launch_fold_chain).
+std::string chain_source(const std::vector<int> &shape, const std::vector<int> &cls)
 {
-    const Layout Y = lay_out(shape, roomy);
+    const Layout Y = lay_out(shape);
     const int n = Y.n;
     Src o;
     // (leading dimensions as 32-bit words: a row's offset is then one 32 x 32 -> 64 bit multiply-add)
@@ -629,7 +628,7 @@ std::string chain_source(const std::vector<int> &shape, const std::vector<int> &
     // a multiply-add that shifts its operand takes twice as long and there are up to 16 of them to a shift
     o("template <int CTRL> __device__ __forceinline__ float from_lane(float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true)); }\n"
       "#define opaque(x) asm(\"\" : \"+v\"(x))\n");
-    o("extern \"C\" __global__ void __launch_bounds__(64%s) damp_fold_chain_kernel(const Args A)\n{\n", roomy ? ", 2" : ", 4");
+    o("extern \"C\" __global__ void __launch_bounds__(64, 2) damp_fold_chain_kernel(const Args A)\n{\n");
     o("  __shared__ __align__(16) float lds[%d];\n", kSP * Y.stride);
     o("  const int lane = threadIdx.x, l = lane & %d, q = lane >> 4;\n", kL - 1);
     // workgroups are dealt round-robin to the 8 XCDs: give every XCD a contiguous range of samples
@@ -746,7 +745,7 @@ bool fold_chain_ok(int n, const int32_t *m, const int32_t *nb, const int64_t *ld
     std::lock_guard<std::mutex> lock(mu);
     auto it = known.find(shape);
     if (it == known.end()) {
-        const Layout Y = lay_out(shape, false);
+        const Layout Y = lay_out(shape);
         if (known.size() >= 4096) known.clear();
         it = known.emplace(std::move(shape), sizeof(float) * kSP * static_cast<size_t>(Y.stride) <= kChainLdsMax).first;
     }
@@ -758,25 +757,34 @@ dol_status launch_fold_chain(int n, const int32_t *m, const int32_t *nb, int32_t
                              int32_t backward, hipStream_t st)
 {
     static std::mutex mu;
-    static std::map<std::pair<int, std::vector<int>>, ChainKernel> cache;    // per device, shape, leading dimensions and build; lives until the process ends
+    static std::map<std::pair<int, std::vector<int>>, ChainKernel> cache;    // per device, shape and kind of strides; lives until the process ends
     std::vector<int> shape{n, m[0]};
     for (int t = 1; t < n; ++t) shape.push_back(nb[t]);
     const unsigned grid = static_cast<unsigned>((static_cast<int64_t>(batch) + kSP - 1) / kSP);
-    const bool roomy = grid <= kRoomyGroups;
     int dev = 0;
     DOL_HIP(hipGetDevice(&dev));
     hipFunction_t fn = nullptr;
     {
         std::lock_guard<std::mutex> lock(mu);
+        // Inputs of one number of symbols mostly lie one row length apart and then share their addresses; where any two of them
+        // do not, every input has its own, in a build that serves all strides.  (Sum-15, us, shared / not: B=64 8.0 / 8.55,
+        // 4 096 9.2 / 9.9, 524 288 493 / 507; to compile takes 0.45 s, and 0.15 to 1 s for other chains.)
         std::vector<int> cls(n), keyed(shape);
-        for (int t = 0; t < n; ++t) cls[t] = static_cast<int>(std::find(ld, ld + t, ld[t]) - ld);
-        keyed.insert(keyed.end(), cls.begin(), cls.end());
-        keyed.push_back(roomy);
+        bool shared = true;
+        for (int t = 0; t < n; ++t) {
+            const auto width = [&](int u) { return u ? nb[u] : m[0]; };
+            cls[t] = 0;
+            while (width(cls[t]) != width(t)) ++cls[t];
+            shared = shared && ld[cls[t]] == ld[t];
+        }
+        if (!shared)
+            for (int t = 0; t < n; ++t) cls[t] = t;
+        keyed.push_back(shared);
         auto key = std::make_pair(dev, keyed);
         auto it = cache.find(key);
         if (it == cache.end()) {
             ChainKernel k;
-            k.status = jit_compile(chain_source(shape, cls, roomy), "damp_fold_chain_kernel", &k.mod, &k.fn);
+            k.status = jit_compile(chain_source(shape, cls), "damp_fold_chain_kernel", &k.mod, &k.fn);
             it = cache.emplace(key, k).first;
             if (k.status != DOL_OK) return k.status;                        // with the compiler's message
         } else if (it->second.status != DOL_OK) {

@@ -242,11 +242,11 @@ def test_fused_fold_with_masses_on_either_side_of_one(dol, B, n, loss):
 
 @pytest.mark.parametrize("B", [5, 8203])
 @pytest.mark.parametrize("kind", ["calm", "large", "clamped"])
-@pytest.mark.parametrize("widths", [[10] * 15, [3, 10], [255, 16], [40, 1, 16, 16], [1, 1, 2], [16] * 9, [7] * 18, [2, 13, 1, 5, 16, 3, 9, 9, 9]],
+@pytest.mark.parametrize("widths", [[10] * 15, [3, 10], [255, 16], [40, 1, 16, 16], [1, 1, 2], [16] * 9, [7] * 18, [2, 13, 1, 5, 16, 3, 9, 9, 9], [10] * 24],
                          ids=lambda w: "%dx%d" % (len(w), max(w)))
 def test_fold_code_for_chain_shapes(dol, widths, kind, B):
     """The code written for a chain: blocks of every width and changes between them, short operands of 1 to 16 symbols, rows
-    that wait in LDS, both builds (the larger batch takes the one for large grids), rows apart by different distances,
+    that wait in LDS, rows apart by different distances,
     targets on either end and outside, a target of probability 0.  calm: no sum reaches 1, the late stages count from the
     target; large: the same with a first operand so small that the others' sums may exceed 2, where they do not; clamped:
     sums beyond 1.  A third of the samples, the last ones among them, are looked at.
@@ -309,6 +309,38 @@ def test_fold_code_for_chain_shapes(dol, widths, kind, B):
             assert np.all(x[:, m:] == 7.0)
             bad = np.abs(x[look, :m] - want[t]) > 2e-5 * np.abs(want[t]) + 1e-30
             assert not bad[kept].any(), "%s: grad %d" % (which, t)
+
+
+def test_fold_code_serves_all_strides(dol, monkeypatch, tmp_path):
+    """A chain's code is built twice at most, for rows of like inputs at one distance and for any, whatever distances and batches
+    follow, and gives the same bits."""
+    monkeypatch.setenv("DOL_JIT_DUMP_DIR", str(tmp_path))
+    widths, builds = [9, 11, 11, 11], 0
+    syms, tabs, cur = [np.arange(m, dtype=np.int32) for m in widths], [], np.arange(widths[0], dtype=np.int32)
+    for t in range(1, len(widths)):
+        tabs.append(dol.FnTable.create_dense(W.sum_table(cur, syms[t])))
+        cur = tabs[-1].out_syms
+    for B in (70, 9000):
+        target, first = dev((W.uniform01(19, B) * cur.size).astype(np.int32)), None
+        for pads in ((0, 0, 0, 0), (2, 2, 2, 2), (0, 1, 2, 3), (3, 0, 0, 5), (0, 4, 0, 0)):
+            ins, gins = [], []
+            for t, m in enumerate(widths):
+                buf = torch.zeros((B, m + pads[t]), device="cuda")
+                buf[:, :m] = dev(W.uniform01(70 + t, B * m).reshape(B, m).astype(np.float32) * (1.9 / m))
+                ins.append(dol.Dist(syms[t], buf[:, :m]))
+                gins.append(torch.zeros((B, m + pads[t]), device="cuda"))
+            out = dol.Dist.empty(cur, B)
+            fold = dol.Fold(ins, tabs, out=out, target_col=target, grad_inputs=gins)
+            assert dol.fold_kernel(fold) == "damp_fold_chain_kernel"
+            dol.fold_apply2(fold)
+            for f in tmp_path.iterdir():
+                builds += 1
+                f.unlink()
+            got = [host(out.prob)] + [host(g)[:, :m] for g, m in zip(gins, widths)]
+            first = first or got
+            for x, y in zip(got, first):
+                np.testing.assert_array_equal(x, y)
+    assert builds == 2
 
 
 # ---------------------------------------------------------------- config 3
