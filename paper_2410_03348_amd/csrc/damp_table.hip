@@ -673,7 +673,7 @@ dol_status launch_damp_table_fwd(const dol_fn_table *f, int32_t batch, const flo
     if (!table_code_ok(f) || batch < 1 || table_small_batch(f, batch, false)) return DOL_OK;
     if (lda != f->na || ldb != f->nb || ldo != f->n_out || !aligned16(a) || !aligned16(b) || !aligned16(out)) return DOL_OK;
     hipFunction_t fn = nullptr;
-    if (dol_status s = kernel_of(f, kSlotFwd, build_for(batch), &fn)) return s;
+    if (dol_status s = kernel_of(f, kSlotFwd, build_for(batch), &fn)) return whole_pieces(f) ? s : DOL_OK;      // (the others have kernels that need no compiler)
     const JitBuild bd = build_for(batch);
     int n_tiles = (batch + bd.rows - 1) / bd.rows;
     void *args[] = {&a, &b, &out, &batch, &n_tiles};
@@ -692,7 +692,7 @@ dol_status launch_damp_table_bwd(const dol_fn_table *f, int32_t batch, const flo
         !aligned16(gb))
         return DOL_OK;
     hipFunction_t fn = nullptr;
-    if (dol_status s = kernel_of(f, kSlotBwd, build_for(batch), &fn)) return s;
+    if (dol_status s = kernel_of(f, kSlotBwd, build_for(batch), &fn)) return whole_pieces(f) ? s : DOL_OK;
     const JitBuild bd = build_for(batch);
     int n_tiles = (batch + bd.rows - 1) / bd.rows;
     void *args[] = {&a, &b, &g, &ga, &gb, &batch, &n_tiles, &accumulate};

@@ -620,9 +620,12 @@ extern "C" dol_status dol_fold_apply2(const dol_fold *fold, void *hip_stream)
     if (dol_status s = fold_prepare(fold, P)) return s;
     const FoldArgs &A = P.A;
     if (A.batch == 0) return DOL_OK;
-    if (fold_chain_ok(A.n, A.m, A.nb, A.ld, A.ldo, A.ldg))      // the sweep written for this chain's shape
-        return launch_fold_chain(A.n, A.m, A.nb, A.batch, A.in, A.ld, A.gin, A.out, A.ldo, A.target, A.gout, A.ldg, A.backward,
-                                 static_cast<hipStream_t>(hip_stream));
+    if (fold_chain_ok(A.n, A.m, A.nb, A.ld, A.ldo, A.ldg)) {    // the sweep written for this chain's shape
+        bool done = false;
+        const dol_status s = launch_fold_chain(A.n, A.m, A.nb, A.batch, A.in, A.ld, A.gin, A.out, A.ldo, A.target, A.gout, A.ldg, A.backward,
+                                               static_cast<hipStream_t>(hip_stream), &done);
+        if (s || done) return s;
+    }
     const unsigned grid = P.grid;
     const size_t lds = P.lds;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);

@@ -324,7 +324,7 @@ constexpr int kFoldChainMax = 32;
 bool fold_chain_ok(int n, const int32_t *m, const int32_t *nb, const int64_t *ld, int64_t ldo, int64_t ldg);
 dol_status launch_fold_chain(int n, const int32_t *m, const int32_t *nb, int32_t batch, const float *const *in, const int64_t *ld,
                              float *const *gin, float *out, int64_t ldo, const int32_t *target, const float *gout, int64_t ldg,
-                             int32_t backward, hipStream_t st);
+                             int32_t backward, hipStream_t st, bool *done);
 // A workgroup per sample, rows staged in LDS (damp_sample.hip); *done = false: the rows do not fit
 bool byj_fwd_sample_ok(const dol_fn_table *f);       // forward through the dense map
 bool list_fwd_sample_ok(const dol_fn_table *f);      // forward through the tuple lists

@@ -5,6 +5,10 @@ Integer / index / proof-mask bar: bit-exact.
 Stress cases with unnormalised tags use a one-signed upstream gradient: a float32 sum of mixed-sign terms of order 1
 cannot meet an absolute 1e-7 where it cancels to ~0, whatever the kernel.
 """
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -341,6 +345,68 @@ def test_fold_code_serves_all_strides(dol, monkeypatch, tmp_path):
             for x, y in zip(got, first):
                 np.testing.assert_array_equal(x, y)
     assert builds == 2
+
+
+NO_COMPILER = r"""
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+import numpy as np, torch
+import workloads as W
+from paper_2410_03348_amd import binding as dol
+
+def apply2(f, a, b, g):
+    da, db, out = dol.Dist(np.arange(f.na), a), dol.Dist(np.arange(f.nb), b), dol.Dist.empty(f.out_syms, a.shape[0])
+    dol.apply2(da, db, f, None, out)
+    ga, gb = torch.empty_like(a), torch.empty_like(b)
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), g, ga, gb)
+    return out.prob, ga, gb
+
+whole = dol.FnTable.create_dense(W.hashed_table(65, 16, 16, 32))
+try:
+    apply2(whole, torch.rand(64, 16, device="cuda"), torch.rand(64, 16, device="cuda"), torch.rand(64, whole.n_out, device="cuda"))
+    sys.exit("the compiler was there")
+except RuntimeError:
+    pass
+f, B, few = dol.FnTable.create_dense(W.hashed_table(65, 63, 61, 255)), 4400, 4300
+assert f.kernel_at(False, B) == "damp_table_fwd_kernel" and f.kernel_at(False, few) != "damp_table_fwd_kernel"
+x = [torch.rand(B, n, device="cuda") * s for n, s in ((63, 0.1), (61, 0.1), (f.n_out, 1.0))]
+for _ in range(2):
+    for got, want in zip(apply2(f, *x), apply2(f, *(t[:few].contiguous() for t in x))):
+        assert torch.equal(got[:few], want)
+for n in (4, 18):
+    sym, tabs, cur, p = np.arange(10, dtype=np.int32), [], np.arange(10, dtype=np.int32), torch.softmax(torch.randn(n, 70, 10, device="cuda"), -1)
+    for t in range(1, n):
+        tabs.append(dol.FnTable.create_dense(W.sum_table(cur, sym)))
+        cur = tabs[-1].out_syms
+    ins, grads = [dol.Dist(sym, p[t]) for t in range(n)], torch.zeros_like(p)
+    out, g = dol.Dist.empty(cur, 70), torch.rand(70, cur.size, device="cuda")
+    fold = dol.Fold(ins, tabs, out=out, grad_out=g, grad_inputs=list(grads))
+    assert dol.fold_kernel(fold) == "damp_fold_chain_kernel"
+    dol.fold_apply2(fold)
+    accs, want = [ins[0]], torch.zeros_like(p)
+    for t in range(1, n):
+        accs.append(dol.Dist.empty(tabs[t - 1].out_syms, 70))
+        dol.apply2(accs[-2], ins[t], tabs[t - 1], None, accs[-1])
+    for t in range(n - 1, 0, -1):
+        ga = want[0] if t == 1 else torch.empty(70, accs[t - 1].n_sym, device="cuda")
+        dol.backward(dol.OpRecord(dol.OP_APPLY2, accs[t - 1], ins[t], accs[t], f=tabs[t - 1]), g, ga, want[t])
+        g = ga
+    torch.testing.assert_close(out.prob, accs[-1].prob, rtol=1e-5, atol=1e-7)
+    torch.testing.assert_close(grads, want, rtol=1e-5, atol=1e-7)
+print("served")
+"""
+
+
+def test_calls_that_have_other_kernels_need_no_compiler(tmp_path):
+    """With a run-time compiler that fails, folds and tables of ragged rows run in the kernels that were built ahead; a table that
+    has always had generated code for these rows says what failed."""
+    stub = tmp_path / "stub.c"
+    stub.write_text("int hiprtcCompileProgram(void *p, int n, const char **o) { return 6; }")      # HIPRTC_ERROR_COMPILATION
+    so = str(tmp_path / "stub.so")
+    subprocess.run([os.environ.get("CC", "gcc"), "-shared", "-fPIC", "-o", so, str(stub)], check=True)
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-c", NO_COMPILER, so], capture_output=True, text=True, cwd=root, timeout=100)
+    assert run.returncode == 0 and "served" in run.stdout, run.stdout + run.stderr
 
 
 # ---------------------------------------------------------------- config 3
