@@ -1125,16 +1125,22 @@ bool lds_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
     return backward ? sample_bwd_us(f, batch) < f->tile_bwd_us : sample_fwd_us(f, batch) < f->tile_fwd_us;
 }
 
-// Tables with generated code (damp_table.hip).  Rows that are not whole 16-byte pieces: from 2^24 multiply-adds a pass on, where
-// it saves 6 us and more a pass in either direction (50 x 37 -> 201, gathers / generated code, forward B=10 007 11.7 / 5.3,
-// backward 15.4 / 9.2), so that the second it takes to compile is soon made up for; below, the kernels that need none.  Others
-// (64 x 64 -> 256 forward 4.3 us and a workgroup per sample 4.1 to 4.6 up to 512 samples, smaller tables 2.8 and 3.5): forward
-// at any batch, backward, samples / tiles: 64 x 64 -> 256 B=256 4.8 / 12.3, 4 096 11.5 / 12.4; 32 x 40 -> 128 2 048 5.5 / 7.4,
-// 4 096 7.4 / 7.4; 16 x 16 -> 32 4.4 / 3.5.
+// Tables with generated code (damp_table.hip): whether another kernel takes the call.  Rows of whole 16-byte pieces (64 x 64 -> 256
+// forward 4.3 us and a workgroup per sample 4.1 to 4.6 up to 512 samples, smaller tables 2.8 and 3.5): forward never, backward,
+// samples / tiles: 64 x 64 -> 256 B=256 4.8 / 12.3, 4 096 11.5 / 12.4; 32 x 40 -> 128 2 048 5.5 / 7.4, 4 096 7.4 / 7.4;
+// 16 x 16 -> 32 4.4 / 3.5.
+// Other rows, gathers / generated code, forward and backward: from 2^24 multiply-adds a pass on, 50 x 37 -> 201 B=9 069 12.0 / 5.6
+// and 15.8 / 9.4, 72 552 57 / 22 and 65 / 33; 61 x 5 -> 76 55 008 19 / 10 and 55 / 14; an eighth of 63 x 61 -> 216 35 621 22.9 / 14.5 and
+// 33 / 21; 33 x 47 -> 784 10 818 20 / 9.4 and 25 / 15.7.  The first pass of a direction and a range of batches (of three, build_for)
+// waits for the compiler, 0.11 to 0.37 s forward, 0.16 to 1.4 backward: at the line the gain of 20 000 to 200 000 passes, as for
+// whole pieces, where it is so at any size.  The line leaves calls of less work to kernels that need no compiler.  Backward a
+// workgroup per sample is the faster a little longer, 63 x 63 -> 1 000 B=4 228 17.6 / 19.7, 8 456 27.8 / 22.9.
 bool table_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
 {
-    if (!whole_pieces(f)) return batch < (int64_t{1} << 24) / std::max<int64_t>(1, f->n_tuples);
-    if (!backward || batch < 1 || batch > 4096 || !(byj_bwd_sample_ok(f) || list_bwd_sample_ok(f))) return false;
+    const bool whole = whole_pieces(f);
+    if (!whole && batch < (int64_t{1} << 24) / std::max<int64_t>(1, f->n_tuples)) return true;
+    if (!backward || batch < 1 || batch > (whole ? 4096 : 8192) || !(byj_bwd_sample_ok(f) || list_bwd_sample_ok(f))) return false;
+    if (!whole && f->lds_bwd_ok) return false;                      // (tiles of damp_lds.hip would take it)
     const double tiles = 3.0 + 2.5e-3 * static_cast<double>(f->n_tuples) + 6e-3 * f->n_out;
     return sample_bwd_us(f, batch) < tiles;
 }

@@ -338,8 +338,9 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
 dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
                              const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
                              hipStream_t st, bool *done);
-// The choice for tables that damp_table.hip generates code for: a workgroup per sample is faster than tiles, backward and in
-// the merged calls, whose launch takes out == nullptr (backward only) or g == nullptr (forward only).
+// The choice for tables that damp_table.hip generates code for: another kernel takes a call of this size, because a workgroup per
+// sample is faster than tiles or because so little work is not worth compiling for.  In the merged calls, whose launch takes
+// out == nullptr (backward only) or g == nullptr (forward only): a workgroup per sample is faster.
 bool table_small_batch(const dol_fn_table *f, int64_t batch, bool backward);
 bool whole_pieces(const dol_fn_table *f);       // rows of whole 16-byte pieces
 bool merge_small_batch(const dol_fn_table *f, const UnionPlan *p, int64_t batch);

@@ -2316,7 +2316,16 @@ def test_a_result_does_not_depend_on_the_batch_it_is_in(dol, na, nb, n_ids):
     assert (p < 1.0).any() and (p == 1.0).any()
 
 
-@pytest.mark.parametrize("na,nb,n_ids,backward", [(128, 128, 200, False), (300, 8, 20, False), (13, 12, 30, False), (100, 100, 50, True),
+def test_ragged_backward_goes_by_samples_a_little_longer(dol):
+    """Result rows of hundreds of symbols, whose reverse pass no other tile serves: a workgroup per sample past the line at
+    which forward passes take generated code, and generated code above."""
+    f = dol.FnTable.create_dense(W.hashed_table(81, 63, 63, 1021))
+    at = (1 << 24) // (63 * 63) + 1
+    assert f.kernel_at(False, at) == "damp_table_fwd_kernel" and f.kernel_at(True, at) == "damp_apply2_bwd_staged_kernel"
+    assert f.kernel_at(True, 8456) == "damp_table_bwd_kernel"
+
+
+@pytest.mark.parametrize("na,nb,n_ids,backward", [(63, 63, 1021, True), (128, 128, 200, False), (300, 8, 20, False), (13, 12, 30, False), (100, 100, 50, True),
                                                   (32, 40, 128, True), (20, 20, 20, True)])
 def test_both_sides_of_the_choice_between_tiles_and_a_workgroup_per_sample(dol, na, nb, n_ids, backward):
     """The last batch that goes by samples and the first one in tiles: one such place for a table, the earlier the more work
