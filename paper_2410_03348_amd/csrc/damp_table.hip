@@ -111,7 +111,7 @@ void emit_row_to_regs(Src &o, const char *r, const char *tile, int n)
           "%s%d = t.z; %s%d = t.w; }\n", r, i, r, i + 1, r, i + 2, r, i + 3, tile, n + 4, i, r, i, r, i + 1, r, i + 2, r, i + 3);
 }
 
-// Flat copy of a tile of `valid` rows of n floats from memory into LDS rows of pitch n + 4: the loads of all pieces
+// Flat copy of a tile of `valid` rows of n floats from memory into LDS rows (pitch_of): the loads of all pieces
 // of a thread first (into t<tag>_*), the LDS writes in a second step so that several tiles' loads can be in flight.
 void emit_stage_load(Src &o, const char *tag, const char *src_ptr, int n)
 {

@@ -254,8 +254,8 @@ def test_fold_code_for_chain_shapes(dol, widths, kind, B):
     targets on either end and outside, a target of probability 0.  calm: no sum reaches 1, the late stages count from the
     target; large: the same with a first operand so small that the others' sums may exceed 2, where they do not; clamped:
     sums beyond 1.  A third of the samples, the last ones among them, are looked at.
-    Tolerance: sums of non-negative terms, at most 16 x 18 multiply-adds deep, and products with one upstream value: 300 x
-    6e-8 < 2e-5 relative; with an explicit gradient of one sign the same."""
+    Tolerance: the bar of 1e-5 relative (sums of non-negative terms and products with one upstream value, under a target and with
+    an explicit gradient of one sign: a term's roundings, one a stage and one an addition behind it, mostly cancel)."""
     n, look = len(widths), np.unique(np.concatenate([np.arange(0, B, 3), np.arange(max(0, B - 9), B)]))
     scale = {"calm": np.ones(n), "large": np.r_[0.9 / 3.0 ** (n - 1), np.full(n - 1, 3.0)], "clamped": np.r_[1.0, np.where(np.arange(1, n) % 2, 1.7, 0.6)]}[kind]
     ins = []
@@ -306,12 +306,12 @@ def test_fold_code_for_chain_shapes(dol, widths, kind, B):
             gr, want[t] = oracle.damp_apply2_bwd(tris[t - 1], tabs[t - 1].shape[0], tabs[t - 1].shape[1], accs[t - 1], ins[t][look], gr)
         want[0] = gr
         got = host(out.prob)[look]
-        assert np.all(np.abs(got - accs[-1])[kept] <= 2e-5 * accs[-1][kept] + 1e-37)
+        assert np.all(np.abs(got - accs[-1])[kept] <= 1e-5 * accs[-1][kept] + 1e-37)
         np.testing.assert_array_equal(got[kept] == 1.0, accs[-1][kept] == 1.0)
         for t, m in enumerate(widths):
             x = host(gins[t])
             assert np.all(x[:, m:] == 7.0)
-            bad = np.abs(x[look, :m] - want[t]) > 2e-5 * np.abs(want[t]) + 1e-30
+            bad = np.abs(x[look, :m] - want[t]) > 1e-5 * np.abs(want[t]) + 1e-30
             assert not bad[kept].any(), "%s: grad %d" % (which, t)
 
 
@@ -784,14 +784,19 @@ def test_fused_dtkp_fold_when_a_stage_brings_no_new_facts(dol, k):
     assert_close(host(gf), oracle.dtkp_prob_bwd(m, fp, g), "fold gradient")
 
 
+@pytest.mark.parametrize("draw", ["four", "apart"])
 @pytest.mark.parametrize("batch", [1, 6])
 @pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6, 7, 8])
-def test_fused_dtkp_fold_list_merge_with_ties(dol, k, batch):
+def test_fused_dtkp_fold_list_merge_with_ties(dol, k, batch, draw):
     """The fused fold where every input brings new facts, for every list length: probabilities from four values only (equal
     probabilities inside a list, between lists and on either side of the k-th place, zeros among them), Distributions of
-    10, 100 and 109 symbols (in place up to 64, two buffers above), a last workgroup that is not full."""
+    10, 100 and 109 symbols (in place up to 64, two buffers above), a last workgroup that is not full.  apart: no fact has its
+    neighbour's probability in every other sample, so that columns are ranked first, and all have it in the rest."""
     sym = np.arange(10, dtype=np.int32)
     fp = (W.splitmix64(k, np.arange(batch * 40)) % np.uint64(4)).astype(np.float32).reshape(batch, 40) / 4
+    if draw == "apart":
+        fp[::2] = np.array([0.25, 0.5, 0.0, 0.75, 0.5], np.float32)[np.arange(40) % 5]
+        fp[1::2] = 0.25
     grp = (np.arange(40) // 10).astype(np.int32)
     for tabs in ([sym[:, None] * 10 + sym[None, :]] + [None, None], [None, None, None]):
         m, pp, pr = oracle.dtkp_init(sym, fp, k)
@@ -2316,6 +2321,30 @@ def test_a_result_does_not_depend_on_the_batch_it_is_in(dol, na, nb, n_ids):
     assert (p < 1.0).any() and (p == 1.0).any()
 
 
+@pytest.mark.parametrize("na,nb,n_ids,large", [(50, 37, 201, 0), (63, 61, 255, 16385), (61, 5, 77, 0), (33, 47, 1023, 0), (63, 63, 1021, 0)])
+def test_ragged_rows_keep_their_bits_where_generated_code_takes_over(dol, na, nb, n_ids, large):
+    """The first batch that generated code serves and the last one below it, a few samples, and a batch of another build: every
+    bit of a sample's result is the same, sums on either side of the clamp and samples with NaN and infinity among them."""
+    f = dol.FnTable.create_dense(W.hashed_table(74, na, nb, n_ids))
+    at = (1 << 24) // (na * nb)
+    assert f.kernel_at(False, at) == "damp_table_fwd_kernel" and f.kernel_at(False, at - 1) != "damp_table_fwd_kernel"
+    B = max(at, large)
+    a = torch.from_numpy((W.uniform01(75, B * na) ** 4 * (6.0 * n_ids / (na * nb))).astype(np.float32).reshape(B, na)).cuda()
+    b = torch.from_numpy(W.uniform01(76, B * nb).astype(np.float32).reshape(B, nb)).cuda()
+    a[5, 1], a[6, 0], b[7, 2] = float("nan"), float("inf"), float("inf")
+
+    def run(n):
+        out = dol.Dist.empty(f.out_syms, n)
+        dol.apply2(dol.Dist(np.arange(na), a[:n].contiguous()), dol.Dist(np.arange(nb), b[:n].contiguous()), f, None, out)
+        return host(out.prob).view(np.int32)
+
+    whole = run(B)
+    for n in (at, at - 1, 37):
+        np.testing.assert_array_equal(run(n), whole[:n])
+    p = whole.view(np.float32)
+    assert (p < 1.0).any() and (p == 1.0).any()
+
+
 def test_ragged_backward_goes_by_samples_a_little_longer(dol):
     """Result rows of hundreds of symbols, whose reverse pass no other tile serves: a workgroup per sample past the line at
     which forward passes take generated code, and generated code above."""
@@ -2607,17 +2636,21 @@ def test_dtkp_columns_of_every_length(dol, batch, lengths):
 
 
 @pytest.mark.parametrize("k", [1, 2, 4, 5])
+@pytest.mark.parametrize("apart", [False, True])
 @pytest.mark.parametrize("values", [None, (0.5, 0.25, 1.0, 0.0), (0.5, 1e-30, 3e-39, 1.0)], ids=["random", "equal", "tiny"])
-def test_dtkp_columns_ranked_by_keys(dol, k, values):
+def test_dtkp_columns_ranked_by_keys(dol, k, values, apart):
     """Columns of 1 to 70 tuples (a lane, four, 16 and a wavefront) where a list is ranked by probability and origin alone, on
     both sides of the longest such list: probabilities all different, drawn from four values (equal ones within a lane, between
-    lanes and on the cut, proofs of probability 0), and so small that products underflow."""
+    lanes and on the cut, proofs of probability 0), and so small that products underflow.  apart: the same where the first
+    facts' neighbours differ in every other sample, which lets columns with equal probabilities be ranked all the same."""
     lengths, batch, nb, n_facts = (1, 2, 3, 4, 5, 8, 16, 17, 40, 64, 65, 70, 1, 4, 12), 6, 6, 30
     n = sum(lengths)
     na = -(-n // nb)
     fp = W.uniform01(141, batch * n_facts).astype(np.float32).reshape(batch, n_facts)
     if values is not None:
         fp = np.asarray(values, np.float32)[(fp * len(values)).astype(int)]
+    if apart:
+        fp[::2, :8] = np.asarray(values or (0.5, 0.25), np.float32)[np.arange(8) % 2]
     grp = np.concatenate([np.arange(24), np.full(6, 24)]).astype(np.int32)
     prov = dol.Prov(dol.DTKP, k, dev(fp), grp)
     pair = (W.splitmix64(142, np.arange(24 * 24)) % np.uint64(na)).astype(np.int32).reshape(24, 24)
