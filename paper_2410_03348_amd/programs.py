@@ -45,6 +45,15 @@ def _n_tuples(table: np.ndarray) -> int:
     return int((np.asarray(table) >= 0).sum())
 
 
+def target_fold_macs(symbols) -> int:
+    """Multiply-adds of a left fold of sums under one target symbol, forward and backward; symbols: of each input.  Forward and
+    in both gradients a tuple costs one, but a target's gradient reaches no more columns of stage t than the inputs after t
+    can make up for, and is zero in the rest."""
+    rows = np.cumsum([m - 1 for m in symbols]) + 1                          # symbols of the running Distributions
+    seen = np.minimum(rows, rows[-1] - rows + 1)                            # those that reach the target
+    return int(sum(nb * (int(rows[t]) + int(seen[t]) + int(seen[t + 1])) for t, nb in enumerate(symbols[1:])))
+
+
 class Program:
     launches: List[Launch]
     sample_ops: int
@@ -168,13 +177,11 @@ class SumChainFused(Program):
         sym = np.asarray(w["sym"], np.int32)
         self.p_dev = _dev(p, device)
         self.digits = [dol.Dist(sym, self.p_dev[t]) for t in range(self.n)]
-        self.tables, syms, macs = [], sym, 0
+        self.tables, syms = [], sym
         for t in range(1, self.n):
-            tab = sum_table_of(syms, sym)
-            tb = dol.FnTable.create_dense(tab)
+            tb = dol.FnTable.create_dense(sum_table_of(syms, sym))
             self.tables.append(tb)
             syms = tb.out_syms
-            macs += 3 * _n_tuples(tab)
         self.out = dol.Dist.empty(syms, self.batch, device)
         self.target = _dev(w["target"].astype(np.int32), device)
         self.grad_p = torch.empty_like(self.p_dev)
@@ -182,7 +189,8 @@ class SumChainFused(Program):
                              grad_inputs=[self.grad_p[t] for t in range(self.n)])
         n_in = sum(d.n_sym for d in self.digits)
         self.launches = [Launch(dol.fold_kernel(self.fold), lambda: dol.fold_apply2(self.fold),
-                                4 * self.batch * (2 * n_in + self.out.n_sym + 1), self.batch * macs, "fwd")]
+                                4 * self.batch * (2 * n_in + self.out.n_sym + 1),
+                                self.batch * target_fold_macs([d.n_sym for d in self.digits]), "fwd")]
         self.sample_ops = 2 * (self.n - 1) * self.batch
         self.min_bytes = self.launches[0].bytes
         self.flops = 2 * self.launches[0].macs
