@@ -9,7 +9,8 @@
 // column.
 // With lists ranked by keys that table takes 61 us (73 before), k = 3, and 147 MB leave for 98 MB of results, whose order is
 // that of the columns' lengths.  Lengths sorted inside fewer than 4 096 columns leave fewer bytes (129 MB) but unequal lanes:
-// the pass of that expression took 206 us and more instead of 204.  Lists read four tuples ahead: 80 us, for want of wavefronts.
+// the pass of that expression took 206 us and more instead of 204 (passes in this file repeat the same inputs; where these change
+// from pass to pass they take some ten us more).  Lists read four tuples ahead: 80 us, for want of wavefronts.
 #pragma once
 
 #include "dtkp_util.h"

@@ -58,9 +58,9 @@ struct DtkpFoldArgs {
 // every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where a quarter
 // of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3, B=1 024,
 // facts of one probability: 65 us, 58.6 so).
-// (Bound by the vector ALUs.  k = 5 costs about 35 instructions a tuple, none of them a choice; 65 with probabilities and
-// origins exchanged by compare and select, which the units take 1.9 ns a piece for, and repeated choices by one condition
-// longer.)
+// (Bound by the vector ALUs.  k = 5 costs about 35 instructions a tuple by the compiled code, none of them a choice; 65 with
+// probabilities and origins exchanged by compare and select, which the units take 1.9 ns a piece for, and repeated choices by one
+// condition longer.)
 template <int K, int KA, bool FRESH>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,

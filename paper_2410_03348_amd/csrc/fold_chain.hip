@@ -12,7 +12,7 @@
 // Sum-15 takes 1 2 2 3 3 5 5 5 7 7 7 7 9 9 9 columns a lane.  What bounds it is the issue of vector instructions; a lane
 // shift costs two multiply-adds (1.8 and 1.0 ns a SIMD with four wavefronts of a test of its own on it), an LDS word 2 clocks of what four SIMDs
 // share.  With every stage's row in LDS a wavefront used 2 556 LDS cycles and 2 806 vector instructions and held 13 KB, so
-// that three shared a SIMD: B=524 288 802 us, B=4 096 11.8.  Now it holds 7 KB: 493 and 9.2.
+// that three shared a SIMD: B=524 288 802 us, B=4 096 11.8.  Now 1 262 cycles, 2 305 instructions and 7 KB: 493 and 9.2.
 //
 // A stage's result is kept as x = pre where pre <= 1 and -1 where the clamp acted: |x| is the tag and the sign is the clamp's
 // decision, read by the reverse sweep with the operand it needs anyway - no stage is ever summed twice.  The tag is taken once

@@ -18,10 +18,13 @@ __device__ __forceinline__ int xcd_contiguous(unsigned id, unsigned n)
     return static_cast<int>(x * q + (x < r ? x : r) + k);
 }
 
-// The same where several workgroups share a sample's rows of 32 KB and more and the chip holds all of them at once
-// (shared_ranges): they then read the rows through one L2.  n == 0: as they come.  (Formula of seven symbols at 200 samples, last Apply 28 -> 25 us, evaluation 29 ->
-// 23.5.  Longer grids lose 1 %, every XCD walking a part of memory of its own; the size comes as an argument because reading it
-// off the grid costs each launch 0.3 us.)
+// The same where several workgroups take parts of a sample's rows of 32 KB and more (shared_ranges; n == 0: as they come): a
+// program's launches then have a sample on the XCD that has just made its rows.  That is what gains: passes replayed as graphs,
+// us, in order of arrival / so, formula of seven symbols under DAMP at 16, 64, 200 samples 132.9 / 115.0, 160.5 / 152.6,
+// 190.1 / 180.2, 16-digit product at 32, 256 220.5 / 212.4, 283.9 / 276.8; the same kernels alone, over rows that no launch has
+// just written, lie within 1 % of each other at 16 to 512 samples, whether the chip holds all workgroups at once or not.
+// (Launches of more than 1 024 lose 1 %, every XCD walking a part of memory of its own.  The size comes as an argument because
+// reading it off the grid costs each launch 0.3 us.)
 __device__ __forceinline__ unsigned xcd_shared(unsigned id, unsigned n) { return n ? static_cast<unsigned>(xcd_contiguous(id, n)) : id; }
 inline unsigned shared_ranges(int64_t batch, int parts, int row)
 {
