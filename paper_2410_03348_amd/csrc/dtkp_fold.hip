@@ -55,9 +55,9 @@ struct DtkpFoldArgs {
 // and the other reversed, sorted again by a short network.  Masks matter only where probabilities are equal: two of the kept
 // ones, or the last one and the best that dropped out, which is what the list's entry behind the k-th holds (of all that
 // dropped out on the way none is larger).  Such a column is done again, candidate by candidate (exact_column), and so is
-// every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where a quarter
-// of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3, B=1 024,
-// facts of one probability: 65 us, 58.6 so).
+// every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where an
+// eighth of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3,
+// B=1 024, facts of one probability: 65 us, 58.4 so; facts in steps of 1/16 64 and 58.2; Sum-6, k = 5, B=12 000 560 and 516).
 // (Bound by the vector ALUs.  k = 5 costs about 35 instructions a tuple by the compiled code, none of them a choice; 65 with
 // probabilities and origins exchanged by compare and select, which the units take 1.9 ns a piece for, and repeated choices by one
 // condition longer.)
@@ -113,7 +113,6 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
         auto list_of = [&](uint32_t r) { return reinterpret_cast<const float *>(reinterpret_cast<const char *>(cp) + (r & 0xffffu)); };
         auto fact_of = [&](uint32_t r) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(fp) + (r >> 16)); };
         if constexpr (FRESH) {
-            constexpr int kTurn = KA <= 3 ? KA : 1;     // (whole lists of five and more are no faster)
             auto exact_column = [&]() {
 #pragma unroll
                 for (int x = 0; x < K; ++x) { tp[x] = -1.0f - x; tid_[x] = -1; }
@@ -121,7 +120,7 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                     const uint32_t cur = l_rec[q];
                     const float *pa = list_of(cur);
                     const float pb = fact_of(cur);
-#pragma unroll kTurn
+#pragma unroll
                     for (int x = 0; x < KA; ++x) {
                         if (!(pa[x] >= 0.0f)) continue;
                         const float offer = pa[x] * pb;
@@ -280,7 +279,7 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
     fp[lane] = my_fp;
     const float next_fp = dpp<0x101>(my_fp);                                // row_shl:1
     const bool equal = lane + 1 < A.n_facts && (lane & 15) != 15 && my_fp == next_fp;
-    const bool plain = __ballot(__float_as_uint(my_fp) >= 0x7f800000u) == 0 && 4 * __builtin_popcountll(__ballot(equal)) <= A.n_facts;
+    const bool plain = __ballot(__float_as_uint(my_fp) >= 0x7f800000u) == 0 && 8 * __builtin_popcountll(__ballot(equal)) <= A.n_facts;
     __syncthreads();
     if (!live) return;                          // no barrier of the workgroup follows
     {   // natural initialisation (App. A.1)
