@@ -19,7 +19,9 @@
 // sample per unit, then by the arithmetic.  Flags in the exchanged words instead of barriers were slower (polling takes more
 // instructions than it saves waits), and so were the shares added up a round late.
 // Both sweeps of 64 rounds, general kernels and these: 8 x 8 grid, B = 256 33.2 and 15.8 us; 16 x 16 27.2 and 21.2;
-// 32 x 32 39.3 and 35.5; B = 1024 8 x 8 78 and 18, 16 x 16 74 and 29, 32 x 32 134 and 83.
+// 32 x 32 39.3 and 30.1; B = 1024 8 x 8 78 and 18, 16 x 16 74 and 29, 32 x 32 134 and 83.
+// (32 x 32: LDS holds the tags of half the rounds.  With one sample to a unit the registers hold the other half, and no round
+// is run forward twice: 35.3 us with 32 rounds replayed from a checkpoint, 30.1 so.)
 #include "iterate.h"
 
 namespace dol {
@@ -181,6 +183,41 @@ __device__ __forceinline__ void rounds(Strip<R> &s, int len, const float (&k)[R]
     }
 }
 
+// Rounds whose tags a lane can keep in registers (at one or two wavefronts to a SIMD there are 256 of them).
+template <int R>
+constexpr int kept_rounds = 68 / R;
+
+template <int R>
+using Kept = float[kept_rounds<R>][R];
+
+// (a scalar to compare with here and now: all comparisons of an unrolled loop made ahead fill the scalar registers)
+__device__ __forceinline__ int compared(int x)
+{
+    asm volatile("" : "+s"(x));
+    return x;
+}
+
+// `len` rounds as rounds() runs them, len <= kept_rounds; the tags that round t starts from are left in kept[t].
+template <int R>
+__device__ __forceinline__ void rounds_kept(Strip<R> &s, int len, const float (&k)[R][kSlots], float (&x)[R], float (&pre)[R], Kept<R> &kept)
+{
+#pragma unroll
+    for (int t = 0; t < kept_rounds<R>; ++t) {
+        if (t >= compared(len)) continue;
+        const Ends &from = s.ends[t & 1], &to = s.ends[(t + 1) & 1];
+        const float up = masked(lds_at(from.up), s.from_up), down = masked(lds_at(from.down), s.from_down);
+#pragma unroll
+        for (int r = 0; r < R; ++r) kept[t][r] = x[r];
+#pragma unroll
+        for (int r = 0; r < R; ++r) pre[r] = row_sum(s, r, up, down, x, k);
+#pragma unroll
+        for (int r = 0; r < R; ++r) x[r] = signed_tag(pre[r]);
+        put_ends(to, x);
+        lds_barrier();
+    }
+    if (len & 1) { const Ends sw = s.ends[0]; s.ends[0] = s.ends[1]; s.ends[1] = sw; }
+}
+
 // A strip's entries in the row of node `first`; past the grid: `else_`.
 template <int R>
 __device__ __forceinline__ void load_nodes(const Strip<R> &s, const float *__restrict__ row, float else_, float (&x)[R])
@@ -213,9 +250,10 @@ __device__ __forceinline__ void stage(float *le, const float *__restrict__ e, in
     for (int j = threadIdx.x; j <= nb; j += blockDim.x) le[j] = j < nb ? e[j] : 0.0f;
 }
 
-// Forward sweep.  PRE (both sweeps in one launch): the rounds of the last segment are left in the rows of tags.
-template <int R, bool PRE>
-__device__ __forceinline__ void grid_forward(const ItFwdArgs &A, Strip<R> &s, const float (&k)[R][kSlots])
+// Forward sweep.  PRE (both sweeps in one launch): the rounds of the last segment are left in the rows of tags; KEEP: those of
+// the segment before it in registers.
+template <int R, bool PRE, bool KEEP>
+__device__ __forceinline__ void grid_forward(const ItFwdArgs &A, Strip<R> &s, const float (&k)[R][kSlots], Kept<R> &kept)
 {
     const int na = A.na;
     const int64_t b = blockIdx.x, plane = static_cast<int64_t>(A.batch) * na;
@@ -231,17 +269,26 @@ __device__ __forceinline__ void grid_forward(const ItFwdArgs &A, Strip<R> &s, co
     begin_phase(s, x);
     const int stride = A.hist ? 1 : A.every;
     const int t_keep = PRE && A.rounds > 0 ? (A.rounds - 1) / A.every * A.every : A.rounds;    // first round of the kept segment
+    const int t_reg = KEEP ? max(0, t_keep - A.every) : t_keep;
     int t = 0, n_ckpt = 0;
-    while (t < t_keep) {
-        const int stop = min(A.rounds, (t / stride + 1) * stride);
-        rounds<R, false>(s, stop - t, k, x, pre, 0u);
-        t = stop;
+    auto leave = [&]() {
         float v[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) v[r] = fminf(pre[r], 1.0f);
         if (A.hist) store(A.hist + t * plane + b * na, v);
         else if (t < A.rounds && A.ckpt) store(A.ckpt + (n_ckpt++) * plane + b * na, v);
         if (t == A.rounds && A.out) store(A.out + b * A.ldo, v);
+    };
+    while (t < t_reg) {
+        const int stop = min(A.rounds, (t / stride + 1) * stride);
+        rounds<R, false>(s, stop - t, k, x, pre, 0u);
+        t = stop;
+        leave();
+    }
+    if (KEEP && t < t_keep) {
+        rounds_kept<R>(s, t_keep - t, k, x, pre, kept);
+        t = t_keep;
+        leave();
     }
     if constexpr (PRE) {
         if (A.rounds > 0) {
@@ -262,10 +309,11 @@ struct GridSums {
 };
 
 // Reverse sweep, a segment of `every` rounds at a time: its rounds forward into the rows of tags, then backwards (the general
-// kernel's comment in iterate.hip tells the arithmetic).
-template <int R, bool PRE>
+// kernel's comment in iterate.hip tells the arithmetic).  KEEP: the last segment but one's tags wait in `kept`, and it is not
+// run forward again.
+template <int R, bool PRE, bool KEEP>
 __device__ __forceinline__ void grid_backward(const ItBwdArgs &A, const GridSums &S, Strip<R> &s, const float (&kc)[R][kSlots],
-                                              const float (&kr)[R][kSlots], float *share_buf)
+                                              const float (&kr)[R][kSlots], const Kept<R> &kept, float *share_buf)
 {
     const int na = A.na, nb = A.nb, T = blockDim.x;
     const int64_t b = blockIdx.x, plane = static_cast<int64_t>(A.batch) * na;
@@ -282,12 +330,41 @@ __device__ __forceinline__ void grid_backward(const ItBwdArgs &A, const GridSums
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int y = 0; y < kSlots; ++y) share[r][y] = 0.0f;
+    // One round backwards: gh, whose ends are in `from`, to the next one's ends in `to`; xi: the tags it started from.
+    auto reverse_round = [&](const Ends &from, const Ends &to, float (&gh)[R], const float (&xi)[R], auto fetch) {
+        const float up = lds_at(from.up), down = lds_at(from.down);
+        float v[R][kSlots];
+        fetch();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            v[r][kUp] = r ? gh[r ? r - 1 : 0] : masked(up, s.from_up);
+            v[r][kLeft] = left_of(gh[r], s.from_left);
+            v[r][kSelf] = gh[r];
+            v[r][kRight] = right_of(gh[r], s.from_right);
+            v[r][kDown] = r + 1 < R ? gh[r + 1 < R ? r + 1 : r] : masked(down, s.from_down);
+            float acc = kr[r][kSelf] * v[r][kSelf];
+            acc = __builtin_fmaf(kr[r][kLeft], v[r][kLeft], acc);
+            acc = __builtin_fmaf(kr[r][kRight], v[r][kRight], acc);
+            acc = __builtin_fmaf(kr[r][kUp], v[r][kUp], acc);
+            g[r] = __builtin_fmaf(kr[r][kDown], v[r][kDown], acc);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) gh[r] = xi[r] < 0.0f ? 0.0f : g[r];
+        put_ends(to, gh);
+        __builtin_amdgcn_sched_barrier(0);      // (the ends first, the shares while they are written)
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int y = 0; y < kSlots; ++y) share[r][y] = __builtin_fmaf(fabsf(xi[r]), v[r][y], share[r][y]);
+        lds_barrier();
+    };
     const int n_seg = (A.rounds + A.every - 1) / A.every;
-    for (int sg = n_seg - 1; sg >= 0; --sg) {
+    // ready: the forward sweep has left the segment's rounds in the rows of tags
+    auto segment = [&](int sg, bool ready) {
         const int t0 = sg * A.every, len = min(A.every, A.rounds - t0);
         float x[R], pre[R];
-        // ---- the rounds of this segment into the rows 0 .. len (PRE: the forward sweep has left the last segment there)
-        if (PRE && sg == n_seg - 1) {
+        // ---- the rounds of this segment into the rows 0 .. len
+        if (ready) {
             get_tags(s.tags + len * s.tag_row, x);
         } else {
             const float *first = A.hist ? A.hist + t0 * plane + b * na : sg == 0 ? A.r0 + b * A.ldr : A.ckpt + (sg - 1) * plane + b * na;
@@ -323,34 +400,11 @@ __device__ __forceinline__ void grid_backward(const ItBwdArgs &A, const GridSums
         float xi[R];
         get_tags(row, xi);
         auto one = [&](const Ends &from, const Ends &to, bool last) {
-            const float up = lds_at(from.up), down = lds_at(from.down);
-            float next[R], v[R][kSlots];
+            float next[R];
             row -= last ? 0u : s.tag_row;
-            get_tags(row, next);
+            reverse_round(from, to, gh, xi, [&] { get_tags(row, next); });
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
-                v[r][kUp] = r ? gh[r ? r - 1 : 0] : masked(up, s.from_up);
-                v[r][kLeft] = left_of(gh[r], s.from_left);
-                v[r][kSelf] = gh[r];
-                v[r][kRight] = right_of(gh[r], s.from_right);
-                v[r][kDown] = r + 1 < R ? gh[r + 1 < R ? r + 1 : r] : masked(down, s.from_down);
-                float acc = kr[r][kSelf] * v[r][kSelf];
-                acc = __builtin_fmaf(kr[r][kLeft], v[r][kLeft], acc);
-                acc = __builtin_fmaf(kr[r][kRight], v[r][kRight], acc);
-                acc = __builtin_fmaf(kr[r][kUp], v[r][kUp], acc);
-                g[r] = __builtin_fmaf(kr[r][kDown], v[r][kDown], acc);
-            }
-#pragma unroll
-            for (int r = 0; r < R; ++r) gh[r] = xi[r] < 0.0f ? 0.0f : g[r];
-            put_ends(to, gh);
-            __builtin_amdgcn_sched_barrier(0);      // (the ends first, the shares while they are written)
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-#pragma unroll
-                for (int y = 0; y < kSlots; ++y) share[r][y] = __builtin_fmaf(fabsf(xi[r]), v[r][y], share[r][y]);
-                xi[r] = next[r];
-            }
-            lds_barrier();
+            for (int r = 0; r < R; ++r) xi[r] = next[r];
         };
         int left = len;
         for (; left > 1; left -= 2) {
@@ -361,7 +415,28 @@ __device__ __forceinline__ void grid_backward(const ItBwdArgs &A, const GridSums
             one(s.ends[0], s.ends[1], true);
             const Ends sw = s.ends[0]; s.ends[0] = s.ends[1]; s.ends[1] = sw;
         }
+    };
+    int sg = n_seg - 1;
+    if constexpr (PRE) {
+        if (sg >= 0) segment(sg--, true);
     }
+    if constexpr (KEEP) {
+        if (sg >= 0) {
+            const int len = A.every;
+            float x[R], gh[R];
+            get_tags(s.tags, x);                // (those after the segment's last round; the last segment began with them)
+#pragma unroll
+            for (int r = 0; r < R; ++r) gh[r] = x[r] < 0.0f ? 0.0f : g[r];
+            if (len & 1) put_ends(s.ends[0], gh);
+            else put_ends(s.ends[1], gh);
+            lds_barrier();
+#pragma unroll
+            for (int t = kept_rounds<R> - 1; t >= 0; --t)
+                if (t < compared(len)) reverse_round(s.ends[t & 1], s.ends[(t + 1) & 1], gh, kept[t], [] {});
+            --sg;
+        }
+    }
+    for (; sg >= 0; --sg) segment(sg, false);
     if (A.grad_r0) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -428,11 +503,12 @@ damp_iterate_grid_fwd_kernel(const ItFwdArgs A, const GridLayout L, const uint32
     take_values(le, second, k);
 #pragma unroll
     for (int r = 0; r < R; ++r) k[r][kSelf] = r < s.n_valid ? k[r][kSelf] : 2.0f;
-    grid_forward<R, false>(A, s, k);
+    Kept<R> none;
+    grid_forward<R, false, false>(A, s, k, none);
 }
 
-// Both kernels with a reverse sweep.
-template <int R, bool PRE>
+// The kernels with a reverse sweep.
+template <int R, bool PRE, bool KEEP>
 __device__ __forceinline__ void grid_reverse(const ItFwdArgs *F, const ItBwdArgs &B, const GridLayout &L, const uint32_t *__restrict__ slots,
                                              const GridSums &S, float *lds)
 {
@@ -448,11 +524,12 @@ __device__ __forceinline__ void grid_reverse(const ItFwdArgs *F, const ItBwdArgs
     take_values(le, as_row, kr);
 #pragma unroll
     for (int r = 0; r < R; ++r) kc[r][kSelf] = r < s.n_valid ? kc[r][kSelf] : 2.0f;
+    Kept<R> kept;
     if constexpr (PRE) {
-        grid_forward<R, true>(*F, s, kc);
+        grid_forward<R, true, KEEP>(*F, s, kc, kept);
         __syncthreads();                            // (the result is read back where the loss is taken from it)
     }
-    grid_backward<R, PRE>(B, S, s, kc, kr, B.shares_in_seg ? tags : le + B.nb + 1);
+    grid_backward<R, PRE, KEEP>(B, S, s, kc, kr, kept, B.shares_in_seg ? tags : le + B.nb + 1);
 }
 
 template <int R>
@@ -460,7 +537,7 @@ __global__ void __launch_bounds__(kMaxWaves * kWave, 4)
 damp_iterate_grid_bwd_kernel(const ItBwdArgs B, const GridLayout L, const uint32_t *__restrict__ slots, const GridSums S)
 {
     extern __shared__ float lds[];
-    grid_reverse<R, false>(nullptr, B, L, slots, S, lds);
+    grid_reverse<R, false, false>(nullptr, B, L, slots, S, lds);
 }
 
 template <int R>
@@ -468,7 +545,17 @@ __global__ void __launch_bounds__(kMaxWaves * kWave, 4)
 damp_iterate_grid_fwd_bwd_kernel(const ItFwdArgs F, const ItBwdArgs B, const GridLayout L, const uint32_t *__restrict__ slots, const GridSums S)
 {
     extern __shared__ float lds[];
-    grid_reverse<R, true>(&F, B, L, slots, S, lds);
+    grid_reverse<R, true, false>(&F, B, L, slots, S, lds);
+}
+
+// The last segment's rounds in LDS, those of the segment before it in registers: up to twice as many rounds in all are run
+// forward once only.
+template <int R>
+__global__ void __launch_bounds__(kMaxWaves * kWave, 2)
+damp_iterate_grid_fwd_bwd_kept_kernel(const ItFwdArgs F, const ItBwdArgs B, const GridLayout L, const uint32_t *__restrict__ slots, const GridSums S)
+{
+    extern __shared__ float lds[];
+    grid_reverse<R, true, true>(&F, B, L, slots, S, lds);
 }
 
 GridLayout layout_of(const dol_fn_table *f, int R)
@@ -618,8 +705,9 @@ dol_status launch_grid_bwd(const dol_fn_table *f, const ItBwdArgs &A, size_t lds
 dol_status launch_grid_fwd_bwd(const dol_fn_table *f, const ItFwdArgs &F, const ItBwdArgs &B, size_t lds, hipStream_t st)
 {
     return with_rows(f, F.batch, [&](auto R) {
-        return launch(f, F.batch, reinterpret_cast<const void *>(&damp_iterate_grid_fwd_bwd_kernel<R()>), R(), lds, st, F, B, layout_of(f, R()), slots_of(f),
-                      sums_of(f));
+        const bool keep = F.batch <= kUnits && B.every < B.rounds && B.every <= kept_rounds<R()>;
+        const auto kernel = keep ? &damp_iterate_grid_fwd_bwd_kept_kernel<R()> : &damp_iterate_grid_fwd_bwd_kernel<R()>;
+        return launch(f, F.batch, reinterpret_cast<const void *>(kernel), R(), lds, st, F, B, layout_of(f, R()), slots_of(f), sums_of(f));
     });
 }
 

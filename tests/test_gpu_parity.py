@@ -1130,6 +1130,40 @@ def test_fused_iteration_over_a_grid(dol, B, w, h):
         torch.testing.assert_close(a, b, rtol=0, atol=0)
 
 
+@pytest.mark.parametrize("w,h,every,rounds", [(32, 32, 33, 34), (32, 32, 33, 66), (32, 32, 32, 71), (32, 32, 1, 3), (8, 8, 68, 69), (8, 8, 67, 140),
+                                              (64, 20, 17, 34), (64, 20, 16, 23)])
+def test_both_sweeps_with_a_segment_in_registers(dol, w, h, every, rounds):
+    """dol_iterate_apply2_backward of a small batch, whose last segment but one waits in registers: segments of as many rounds as
+    fit there and fewer, of odd and even counts, a last segment of one round, segments before them; strips of one, two and four
+    nodes.  Bit for bit what the two calls give."""
+    na, B = w * h, 3
+    x, y = np.arange(na) % w, np.arange(na) // w
+    ti, tj = [np.arange(na)], [np.zeros(na, np.int64)]
+    to = [np.arange(na)]
+    for d, (dx, dy) in enumerate(((1, 0), (-1, 0), (0, 1), (0, -1))):
+        ok = (x + dx >= 0) & (x + dx < w) & (y + dy >= 0) & (y + dy < h)
+        ti.append(np.arange(na)[ok]), to.append(np.arange(na)[ok] + dx + w * dy), tj.append(np.full(ok.sum(), d + 1))
+    ti, tj, to = (np.concatenate(v) for v in (ti, tj, to))
+    order = np.lexsort((tj, ti))
+    f = dol.FnTable.create_sparse(na, 5, *(np.asarray(v, np.int32)[order] for v in (ti, tj, to)))
+    d0 = dol.Dist(np.arange(na), dev((W.uniform01(1, B * na) * 0.9).astype(np.float32).reshape(B, na)))
+    de = dol.Dist(np.arange(5), dev((W.uniform01(2, B * 5) * 0.3).astype(np.float32).reshape(B, 5)))
+    g = dev(W.normal(3, B * na).astype(np.float32).reshape(B, na))
+    ck = torch.empty((dol.iterate_ckpt_count(rounds, every), B, na), device="cuda")
+    got = []
+    for one_call in (False, True):
+        out, g0, ge = dol.Dist.empty(np.arange(na), B), torch.empty((B, na), device="cuda"), torch.empty((B, 5), device="cuda")
+        ck.fill_(7.0)
+        if one_call:
+            dol.iterate_apply2_backward(d0, de, f, rounds, every, out, ck, None, g, g0, ge)
+        else:
+            dol.iterate_apply2_ckpt(d0, de, f, rounds, every, out, ck)
+            dol.iterate_backward_ckpt(d0, de, f, rounds, every, ck, g, g0, ge)
+        got.append([host(t) for t in (out.prob, ck, g0, ge)])
+    for a, b in zip(*got):
+        np.testing.assert_array_equal(a, b)
+
+
 def test_fused_iteration_with_more_than_1024_symbols(dol):
     """Four symbols of the first operand per thread (the widest build of the fused sweeps)."""
     na, nb, B, rounds = 1100, 40, 3, 4
