@@ -32,12 +32,13 @@ struct dol_fnk_table {
     dol::DevArray<uint32_t> long_cols;   // columns with more than dol::kLongTableCol tuples
     dol::DtkpColumns dtkp_cols;
     dol::DevArray<uint16_t> dtkp_tuples;            // unary functions: symbol k of the r-th short column at [k * n_out + r]
-    dol::DevArray<uint32_t> col_order;   // all columns in the order of dol::columns_by_length (limit: kLongTableCol)
     // unary functions (K = 1): the first eight symbols of every image again, 16 bytes per column (0xFFFF = none), and
     // the column of every symbol (-1: rejected)
     dol::DevArray<uint16_t> unary_head;
-    dol::DevArray<uint16_t> unary_head_ord;   // the same, entry r being that of column col_order[r]
     dol::DevArray<int32_t> unary_col;
+    dol::DevArray<uint16_t> unary_pick;       // the same as a 16-bit number, n_out: rejected (wide operand rows)
+    dol::DevArray<uint32_t> unary_ij;         // tup as 32-bit words, and as lists of pairs (wide operand rows)
+    dol::ListPlan unary_lists;
     int device = 0;
 };
 
@@ -169,85 +170,66 @@ damp_apply1_bwd_kernel(Rows R, const float *__restrict__ x, int64_t ldx, const i
     });
 }
 
-// The same two for wide rows, staged in LDS (element_map.h).  Forward: the operand row is staged and the symbols of a
-// column are gathered from it, in the same order.  Backward: the gradient row, gated by the clamp, is staged and
-// every operand symbol picks its column's entry.
-__global__ void __launch_bounds__(kStageThreads)
-damp_apply1_fwd_staged_kernel(int32_t n_in, int32_t S, int32_t parts, uint32_t shared, const float *__restrict__ x, int64_t ldx,
-                              const uint32_t *__restrict__ order, const uint32_t *__restrict__ col_ptr, const uint16_t *__restrict__ tup,
-                              const uint4 *__restrict__ head, float *__restrict__ out, int64_t ldo)
-{
-    extern __shared__ __align__(16) float xr[];
-    const unsigned id = xcd_shared(blockIdx.x, shared);
-    const int64_t s = id / static_cast<unsigned>(parts);
-    int c0, c1;
-    stage_part(S, parts, static_cast<int>(id - s * parts), c0, c1);
-    stage_row(xr, x + s * ldx, n_in);
-    __syncthreads();
-    // kStageUnroll columns per thread and pass, so that their index and head loads are in flight together
-    for (int r0 = c0 + threadIdx.x; r0 < c1; r0 += kStageUnroll * kStageThreads) {
-        uint32_t c[kStageUnroll];
-        uint4 h[kStageUnroll];
-#pragma unroll
-        for (int v = 0; v < kStageUnroll; ++v) {
-            const int r = min(r0 + v * kStageThreads, c1 - 1);
-            c[v] = order[r];                                               // lanes of a wavefront: columns of like length
-            h[v] = head[r];                                                // (the head table in that order: a coalesced load)
-        }
-#pragma unroll
-        for (int v = 0; v < kStageUnroll; ++v) {
-            if (r0 + v * kStageThreads >= c1) continue;
-            const uint32_t w[4] = {h[v].x, h[v].y, h[v].z, h[v].w};
-            float val[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {                                  // all eight reads at once (slot 0 for "none")
-                const uint32_t pos = (w[u / 2] >> (16 * (u & 1))) & 0xffffu;
-                val[u] = xr[pos != 0xffffu ? pos : 0u];
-            }
-            float acc = 0.0f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (((w[u / 2] >> (16 * (u & 1))) & 0xffffu) != 0xffffu) acc = acc + val[u];
-            if ((w[3] >> 16) != 0xffffu) {                                 // eight or more symbols: the rest of the list
-                const uint32_t q0 = col_ptr[c[v]], q1 = col_ptr[c[v] + 1];
-                if (q1 - q0 > static_cast<uint32_t>(kLongTableCol)) continue;   // left to the wavefront-per-column kernel
-                for (uint32_t q = q0 + 8; q < q1; q += kGatherK) {
-                    uint32_t pos[kGatherK];
-#pragma unroll
-                    for (int u = 0; u < kGatherK; ++u) pos[u] = tup[min(q + u, q1 - 1)];
-#pragma unroll
-                    for (int u = 0; u < kGatherK; ++u)
-                        if (q + u < q1) acc = acc + xr[pos[u]];
-                }
-            }
-            out[s * ldo + c[v]] = fminf(acc, 1.0f);
-        }
-    }
-}
-
-__global__ void __launch_bounds__(kStageThreads)
+// The same for wide result rows (forward: launch_unary_fwd): the gradient row, gated by the clamp, is staged in LDS and every operand
+// symbol picks its column's entry, four neighbours a thread.
+// 38 400 symbols -> 8 333: us, a symbol at a time by a 32-bit column number B=16 5.3, 64 6.9, 200 15.7; so 4.1, 5.4, 9.7 (with two
+// workgroups to a unit 4.5, 7.0, 10.6).
+__global__ void __launch_bounds__(kStageThreads, 8)
 damp_apply1_bwd_staged_kernel(int32_t n_in, int32_t S, int32_t parts, uint32_t shared, const float *__restrict__ x, int64_t ldx,
-                              const int32_t *__restrict__ col_of, const uint32_t *__restrict__ col_ptr,
+                              const uint16_t *__restrict__ col_of, const uint32_t *__restrict__ col_ptr,
                               const uint16_t *__restrict__ tup, const float *__restrict__ out, int64_t ldo,
                               const float *__restrict__ g, int64_t ldg, float *__restrict__ gx)
 {
-    extern __shared__ __align__(16) float gh[];
+    extern __shared__ __align__(16) float gh[];             // the gated row and a 0
+    constexpr int kAhead = 2;
     const unsigned id = xcd_shared(blockIdx.x, shared);
     const int64_t s = id / static_cast<unsigned>(parts);
-    int i0, i1;
-    stage_part(n_in, parts, static_cast<int>(id - s * parts), i0, i1);
-    for (int c = threadIdx.x; c < S; c += kStageThreads) {
-        float v = g[s * ldg + c];
-        if (out[s * ldo + c] >= 1.0f) {             // pre == 1 passes, pre > 1 blocks: only pre itself tells
-            const float *row[1] = {x + s * ldx};
-            if (!(column_sum_k<1>(row, tup, col_ptr[c], col_ptr[c + 1]) <= 1.0f)) v = 0.0f;
+    const int part = static_cast<int>(id - s * parts), per = ((n_in + parts - 1) / parts + 3) & ~3, T = blockDim.x;
+    const int i0 = part * per, i1 = min(n_in, i0 + per);
+    const float *gr = g + s * ldg, *outr = out + s * ldo;
+    ushort4 c[kAhead];
+    auto columns = [&](int i) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)                    // (the map is padded to whole fours)
+            if (i + 4 * T * u < i1) c[u] = *reinterpret_cast<const ushort4 *>(col_of + i + 4 * T * u);
+    };
+    columns(i0 + 4 * static_cast<int>(threadIdx.x));
+    bool at_one = false;
+    for (int k0 = 4 * static_cast<int>(threadIdx.x); k0 < S; k0 += 8 * T) {
+        float4 v[2], o[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int k = k0 + 4 * T * u;
+            if (k < S) v[u] = load4(gr + k, S - k), o[u] = load4(outr + k, S - k);
         }
-        gh[c] = v;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int k = k0 + 4 * T * u;
+            if (k >= S) continue;
+            at_one |= o[u].x >= 1.0f || o[u].y >= 1.0f || o[u].z >= 1.0f || o[u].w >= 1.0f;
+            *reinterpret_cast<float4 *>(gh + k) = v[u];     // (words past the row are 0)
+        }
     }
+    if (at_one) {                                           // pre == 1 passes, pre > 1 blocks: only pre itself tells
+        const float *row[1] = {x + s * ldx};
+        for (int k0 = 4 * static_cast<int>(threadIdx.x); k0 < S; k0 += 4 * T)
+            for (int k = k0; k < min(S, k0 + 4); ++k)
+                if (outr[k] >= 1.0f && !(column_sum_k<1>(row, tup, col_ptr[k], col_ptr[k + 1]) <= 1.0f)) gh[k] = 0.0f;
+    }
+    if (threadIdx.x == 0 && (S & 3) == 0) gh[S] = 0.0f;
     __syncthreads();
-    for (int i = i0 + threadIdx.x; i < i1; i += kStageThreads) {
-        const int32_t c = col_of[i];
-        gx[s * ldx + i] = c >= 0 ? gh[c] : 0.0f;
+    float *dst = gx + s * ldx;
+    for (int i = i0 + 4 * static_cast<int>(threadIdx.x); i < i1; i += 4 * T * kAhead) {
+        float v[kAhead][4];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (i + 4 * T * u >= i1) continue;
+            v[u][0] = gh[c[u].x], v[u][1] = gh[c[u].y], v[u][2] = gh[c[u].z], v[u][3] = gh[c[u].w];
+        }
+        columns(i + 4 * T * kAhead);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (i + 4 * T * u < i1) store4(dst + i + 4 * T * u, v[u], i1 - (i + 4 * T * u));
     }
 }
 
@@ -329,22 +311,18 @@ damp_applyk_bwd_kernel(Rows R, KOperands in, KGrads gin, const uint32_t *__restr
 }
 
 // Unary functions over wide rows go through the kernels that stage a row in LDS.
-static bool staged_unary_fwd(const dol_fnk_table *f) { return f->K == 1 && stage_fits(f->n_sym[0]); }
+static bool staged_unary_fwd(const dol_fnk_table *f) { return f->K == 1 && unary_rows_ok(f->n_sym[0]); }
 static bool staged_unary_bwd(const dol_fnk_table *f)
 {
     return f->K == 1 && f->n_sym[0] >= kStageMinRow && sizeof(float) * f->n_out <= kStageMaxBytes;
 }
 
 template <int K>
-static void launch_fwd_k(const Rows &R, const KOperands &in, const dol_fnk_table *f, float *out, int64_t ldo, hipStream_t st)
+static dol_status launch_fwd_k(const Rows &R, const KOperands &in, const dol_fnk_table *f, float *out, int64_t ldo, hipStream_t st)
 {
-    if (K == 1 && staged_unary_fwd(f)) {
-        const int32_t parts = stage_parts(R.batch, f->n_out);
-        (void)allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply1_fwd_staged_kernel), kStageMaxBytes);
-        hipLaunchKernelGGL(damp_apply1_fwd_staged_kernel, dim3(static_cast<unsigned>(R.batch) * parts), dim3(kStageThreads),
-                           sizeof(float) * f->n_sym[0], st, f->n_sym[0], f->n_out, parts, shared_ranges(R.batch, parts, f->n_sym[0]), in.p[0], in.ld[0], f->col_order.ptr,
-                           f->col_ptr.ptr, f->tup.ptr, reinterpret_cast<const uint4 *>(f->unary_head_ord.ptr), out, ldo);
-    } else if (K == 1)
+    if (K == 1 && staged_unary_fwd(f))
+        return launch_unary_fwd(f->n_sym[0], f->n_out, f->unary_lists, f->col_ptr.ptr, f->unary_ij.ptr, R.batch, in.p[0], in.ld[0], out, ldo, st);
+    if (K == 1)
         hipLaunchKernelGGL(damp_apply1_fwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, in.p[0], in.ld[0], f->col_ptr.ptr,
                            f->tup.ptr, reinterpret_cast<const uint4 *>(f->unary_head.ptr), out, ldo);
     else
@@ -354,6 +332,7 @@ static void launch_fwd_k(const Rows &R, const KOperands &in, const dol_fnk_table
     if (n_long > 0)
         hipLaunchKernelGGL(damp_applyk_fwd_long_kernel<K>, dim3(static_cast<unsigned>(R.batch * n_long)), dim3(kWave), 0, st,
                            static_cast<int32_t>(n_long), f->long_cols.ptr, in, f->col_ptr.ptr, f->tup.ptr, out, ldo);
+    return DOL_OK;
 }
 
 template <int K>
@@ -362,10 +341,11 @@ static void launch_bwd_k(const Rows &R, const KOperands &in, const KGrads &gin, 
 {
     if (K == 1 && staged_unary_bwd(f)) {
         const int32_t parts = stage_parts(R.batch, f->n_sym[0]);
-        (void)allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply1_bwd_staged_kernel), kStageMaxBytes);
-        hipLaunchKernelGGL(damp_apply1_bwd_staged_kernel, dim3(static_cast<unsigned>(R.batch) * parts), dim3(kStageThreads),
-                           sizeof(float) * f->n_out, st, f->n_sym[0], f->n_out, parts, shared_ranges(R.batch, parts, f->n_out), in.p[0], in.ld[0], f->unary_col.ptr,
-                           f->col_ptr.ptr, f->tup.ptr, out, ldo, g, ldg, gin.p[0]);
+        (void)allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply1_bwd_staged_kernel), kStageMaxBytes + 16);
+        const int32_t fours = (std::max((f->n_sym[0] + parts - 1) / parts, f->n_out) + 3) / 4;
+        hipLaunchKernelGGL(damp_apply1_bwd_staged_kernel, dim3(static_cast<unsigned>(R.batch) * parts), dim3(std::min(kStageThreads, (fours + 63) & ~63)),
+                           sizeof(float) * ((f->n_out + 4) & ~3), st, f->n_sym[0], f->n_out, parts, shared_ranges(R.batch, parts, f->n_out), in.p[0], in.ld[0],
+                           f->unary_pick.ptr, f->col_ptr.ptr, f->tup.ptr, out, ldo, g, ldg, gin.p[0]);
     } else if (K == 1)
         hipLaunchKernelGGL(damp_apply1_bwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, in.p[0], in.ld[0], f->unary_col.ptr,
                            f->col_ptr.ptr, f->tup.ptr, out, ldo, g, ldg, gin.p[0]);
@@ -638,7 +618,6 @@ static dol_status build_k(int32_t K, const int32_t *n_sym, int64_t n, const int3
     std::vector<uint32_t> long_cols;
     for (int32_t c = 0; c < S; ++c)
         if (col_ptr[c + 1] - col_ptr[c] > static_cast<uint32_t>(kLongTableCol)) long_cols.push_back(static_cast<uint32_t>(c));
-    const std::vector<uint32_t> col_order = columns_by_length(col_ptr, S, kLongTableCol);
     // (not for a unary function, whose lists are one gather each: there the neighbouring columns' neighbouring symbols matter
     // more)
     std::vector<uint32_t> dtkp_order = columns_by_length(col_ptr, S, kLongDtkpCol), dtkp_len;
@@ -661,14 +640,25 @@ static dol_status build_k(int32_t K, const int32_t *n_sym, int64_t n, const int3
             }
         DOL_HIP(tb->unary_head.upload(head));
         DOL_HIP(tb->unary_col.upload(col_of));
-        std::vector<uint16_t> ord(head.size());
-        for (int32_t r = 0; r < S; ++r)
-            for (int u = 0; u < 8; ++u) ord[static_cast<size_t>(r) * 8 + u] = head[static_cast<size_t>(col_order[r]) * 8 + u];
-        DOL_HIP(tb->unary_head_ord.upload(ord));
+        if (staged_unary_bwd(tb.get())) {
+            std::vector<uint16_t> pick((static_cast<size_t>(n_sym[0]) + 3) & ~size_t(3), static_cast<uint16_t>(S));
+            for (int32_t i = 0; i < n_sym[0]; ++i)
+                if (col_of[i] >= 0) pick[i] = static_cast<uint16_t>(col_of[i]);
+            DOL_HIP(tb->unary_pick.upload(pick));
+        }
+        if (staged_unary_fwd(tb.get())) {
+            DOL_HIP(tb->unary_ij.upload(std::vector<uint32_t>(tup.begin(), tup.end())));
+            std::vector<uint32_t> pair_ptr(S + 1, 0), pairs;
+            const uint16_t none = static_cast<uint16_t>(n_sym[0]);
+            for (int32_t c = 0; c < S; ++c) {
+                for (uint32_t q = col_ptr[c]; q < col_ptr[c + 1]; q += 2) pairs.push_back(pack16(tup[q], q + 1 < col_ptr[c + 1] ? tup[q + 1] : none));
+                pair_ptr[c + 1] = static_cast<uint32_t>(pairs.size());
+            }
+            DOL_HIP(upload_column_lists(pair_ptr, S, pairs, pack16(none, none), &tb->unary_lists));
+        }
     }
     DOL_HIP(hipGetDevice(&tb->device));
     DOL_HIP(tb->long_cols.upload(long_cols));
-    DOL_HIP(tb->col_order.upload(col_order));
     DOL_HIP(tb->col_ptr.upload(col_ptr));
     DOL_HIP(tb->tup.upload(tup));
     DOL_HIP(tb->tup_col.upload(tup_col));
@@ -753,9 +743,11 @@ dol_status dol_apply_k(int32_t K, const dol_dist *const *in, const dol_fnk_table
         KOperands ops{};
         for (int l = 0; l < K; ++l) { ops.p[l] = in[l]->prob; ops.ld[l] = in[l]->ld; }
         const Rows R = rows_of(batch, f->n_out);
-#define CALL(KK) launch_fwd_k<KK>(R, ops, f, out->prob, out->ld, st)
+        dol_status launched = DOL_OK;
+#define CALL(KK) launched = launch_fwd_k<KK>(R, ops, f, out->prob, out->ld, st)
         DOL_DISPATCH_ARITY(K, CALL)
 #undef CALL
+        if (launched != DOL_OK) return launched;
         DOL_HIP(hipGetLastError());
         return DOL_OK;
     }

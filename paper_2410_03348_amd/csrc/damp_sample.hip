@@ -308,29 +308,6 @@ __device__ __forceinline__ void long_columns(const SampleFwd &A, const float *ar
     mid_columns(ar, br, A.col_ptr, A.col_ij, L.longer + L.n_huge + L.n_wave, L.n_mid, wave, step, put);
 }
 
-// Four neighbouring floats at a 4-byte aligned address, of which the first n exist.
-__device__ __forceinline__ float4 load4(const float *__restrict__ p, int n)
-{
-    if (n >= 4) {
-        const f32x4_u v = *reinterpret_cast<const f32x4_u *>(p);
-        return make_float4(v.x, v.y, v.z, v.w);
-    }
-    return make_float4(p[0], n > 1 ? p[1] : 0.0f, n > 2 ? p[2] : 0.0f, 0.0f);
-}
-
-__device__ __forceinline__ void store4(float *__restrict__ p, const float (&v)[4], int n, uint32_t skip = 0)
-{
-    if (n >= 4 && skip == 0) {
-        f32x4_u w;
-        w.x = v[0], w.y = v[1], w.z = v[2], w.w = v[3];
-        *reinterpret_cast<f32x4_u *>(p) = w;
-        return;
-    }
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-        if (k < n && !((skip >> k) & 1u)) p[k] = v[k];
-}
-
 // ---------------------------------------------------------------- forward, dense maps
 
 // One j at a time is not the order the clamp decision is defined in; the terms' magnitudes bound how far the two sums can
@@ -520,6 +497,75 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
         __syncthreads();
     }
     if (!A.exact) long_columns(A, ar, br, part, scratch, put_long);
+}
+
+// Unary Apply over wide rows: out[c] = min(1, sum of the tags of column c's symbols).  The lists hold two symbols to a word.  A
+// wavefront walks C chunks of them at a time, N words of each per step, so that short lists have as much on the way as long
+// ones; all parts' wavefronts share the chunks out, each every parts * wavefronts-th, which get shorter by steps.  38 400 -> 8 333 (a seven-symbol formula's value), us,
+// with the first eight symbols of a column in a 16-byte word, the others four at a time out of the column's list and
+// the columns above 64 in a launch of their own: B=16 11.6, 64 19.4, 200 27.4; so 5.9, 8.8, 14.9.  Bound by the row's way into LDS.
+template <int C, int N>
+struct Walk {
+    uint32_t e[C], w0[C], len[C], t[C][N];
+
+    __device__ __forceinline__ void start(const Lists &L, int ch, int step, int n_chunks)
+    {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const int at = min(ch + c * step, n_chunks - 1);
+            w0[c] = L.ptr[at], len[c] = ch + c * step < n_chunks ? L.ptr[at + 1] - w0[c] : 0u;
+            e[c] = ch + c * step < n_chunks ? L.order[at * kWave + (threadIdx.x & (kWave - 1))] : kNoList;
+            read_words(t[c], L, w0[c]);
+        }
+    }
+};
+
+template <int C, int N>
+__global__ void __launch_bounds__(kSampleThreads)
+damp_apply1_fwd_staged_kernel(const SampleFwd A)
+{
+    extern __shared__ __align__(16) float lds[];            // the row and a 0
+    __shared__ float scratch[48], one;
+    const unsigned id = xcd_shared(blockIdx.x, A.shared);
+    const int64_t s = id / static_cast<unsigned>(A.parts);
+    const int part = static_cast<int>(id - s * A.parts);
+    const int n_chunks = (A.S + kWave - 1) / kWave, step = A.parts * (blockDim.x / kWave);
+    int ch = part + A.parts * wave_number();
+    Walk<C, N> now, next;
+    now.start(A.lists, ch, step, n_chunks);
+    copy_row(lds, A.a + s * A.lda, A.na);
+    if (threadIdx.x == 0) one = 1.0f;
+    __syncthreads();
+    float *out = A.out + s * A.ldo;
+    auto put = [&](int c, float v) { out[c] = fminf(v, 1.0f); };
+    for (; ch < n_chunks; ch += C * step) {
+        const bool more = ch + C * step < n_chunks;
+        if (more) next.start(A.lists, ch + C * step, step, n_chunks);
+        float acc[C] = {};
+        uint32_t most = 0;
+#pragma unroll
+        for (int c = 0; c < C; ++c) most = max(most, now.len[c]);
+        for (uint32_t w = 0; w < most; w += N) {
+            float v[C][N][2];                               // (a word past a list's end is another's: read, not added)
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int u = 0; u < N; ++u) v[c][u][0] = lds[now.t[c][u] & 0xffffu], v[c][u][1] = lds[now.t[c][u] >> 16];
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (w + N < now.len[c]) read_words(now.t[c], A.lists, now.w0[c] + w + N);
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+#pragma unroll
+                for (int u = 0; u < N; ++u) acc[c] = w + u < now.len[c] ? acc[c] + v[c][u][0] + v[c][u][1] : acc[c];
+        }
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+            if (!(now.e[c] & kListElsewhere)) put(static_cast<int>(now.e[c]), acc[c]);
+        if (!more) break;
+        now = next;
+    }
+    long_columns(A, lds, &one, part, scratch, put);         // (a tuple's word: the symbol, times symbol 0 of `one`)
 }
 
 // ---------------------------------------------------------------- backward
@@ -1024,6 +1070,28 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
     }
     DOL_HIP(hipGetLastError());
     *done = true;
+    return DOL_OK;
+}
+
+dol_status launch_unary_fwd(int32_t n_in, int32_t S, const ListPlan &lists, const uint32_t *col_ptr, const uint32_t *col_ij, int32_t batch,
+                            const float *x, int64_t ldx, float *out, int64_t ldo, hipStream_t st)
+{
+    for (; batch > kMostGroups; batch -= kMostGroups, x += kMostGroups * ldx, out += kMostGroups * ldo)
+        if (dol_status s = launch_unary_fwd(n_in, S, lists, col_ptr, col_ij, kMostGroups, x, ldx, out, ldo, st)) return s;
+    SampleFwd A{};
+    A.na = n_in, A.nb = 1, A.S = S, A.a = x, A.lda = ldx, A.out = out, A.ldo = ldo;
+    A.col_ptr = col_ptr, A.col_ij = col_ij, A.lists = lists_of(lists);
+    const size_t lds = sizeof(float) * static_cast<size_t>((n_in + 4) & ~3);
+    A.parts = best_parts(batch, long_parts(lists, std::min(16, (S + kSampleThreads / 2 - 1) / (kSampleThreads / 2))), n_in,
+                         [&](int p) { return (2.0 * lists.n_words + S + 4.0 * lists.mid_words) / p + 2.0 * lists.huge_words; }, kSampleThreads, lds);
+    A.shared = shared_ranges(batch, A.parts, n_in);
+    const unsigned threads = list_threads(lists, S, n_in, batch * static_cast<int64_t>(A.parts), lds, 512);
+    // (us, two chunks and four pairs a step / one and sixteen: 20 000 -> 4 128, most columns of hundreds of symbols, B=200 14.4 / 13.0,
+    // 38 400 -> 8 333 16-19 / 14.9; 38 400 -> 21 636 B=200 17.7 / 27.6, a permutation of 9 000 B=600 17.4 / 25.1)
+    const auto kernel = lists.n_words < 2 * static_cast<size_t>(S) ? &damp_apply1_fwd_staged_kernel<2, 2> : &damp_apply1_fwd_staged_kernel<1, 8>;
+    if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kStageMaxBytes + 16));
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(batch) * A.parts), dim3(threads), lds, st, A);
+    DOL_HIP(hipGetLastError());
     return DOL_OK;
 }
 

@@ -89,46 +89,41 @@ __device__ __forceinline__ float column_sum(const float *__restrict__ ar, const 
     return acc;
 }
 
-// ---- operand rows staged whole in LDS: one workgroup of kStageThreads per (sample, part of the output row)
+// Four neighbouring floats at a 4-byte aligned address, of which the first n exist.
+__device__ __forceinline__ float4 load4(const float *__restrict__ p, int n)
+{
+    if (n >= 4) {
+        const f32x4_u v = *reinterpret_cast<const f32x4_u *>(p);
+        return make_float4(v.x, v.y, v.z, v.w);
+    }
+    return make_float4(p[0], n > 1 ? p[1] : 0.0f, n > 2 ? p[2] : 0.0f, 0.0f);
+}
+
+__device__ __forceinline__ void store4(float *__restrict__ p, const float (&v)[4], int n, uint32_t skip = 0)
+{
+    if (n >= 4 && skip == 0) {
+        f32x4_u w;
+        w.x = v[0], w.y = v[1], w.z = v[2], w.w = v[3];
+        *reinterpret_cast<f32x4_u *>(p) = w;
+        return;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+        if (k < n && !((skip >> k) & 1u)) p[k] = v[k];
+}
+
+// ---- rows staged whole in LDS: one workgroup of kStageThreads per (sample, part of the output row)
 //
 // A gather from a row of thousands of tags misses the first-level cache on nearly every lane; from LDS it costs a
 // bank conflict or two.  So for wide operand rows a workgroup first copies the sample's row(s) into LDS with
 // coalesced loads and then gathers there.  Small batches are cut into several parts per sample (each stages the row
 // again) so that the chip still fills.
 constexpr int kStageThreads = 1024;
-constexpr int kStageUnroll = 4;                       // outputs a thread works on at a time (their loads in flight together)
 
-static inline bool stage_fits(int64_t row_floats) { return row_floats >= kStageMinRow && row_floats * 4 <= static_cast<int64_t>(kStageMaxBytes); }
-
-// Parts per sample: enough workgroups for about two per compute unit, at most one per kStageThreads outputs.
-static inline int32_t stage_parts(int32_t batch, int32_t n_out)
+// Parts per sample of a row of n outputs: one workgroup per compute unit, each with at least four outputs a thread.
+static inline int32_t stage_parts(int32_t batch, int32_t n)
 {
-    const int32_t most = (n_out + kStageThreads - 1) / kStageThreads;
-    const int32_t want = (512 + batch - 1) / batch;
-    return std::max(1, std::min(most, want));
-}
-
-// Copies n floats into LDS with every thread of the workgroup; 16-byte pieces when the source row allows.
-__device__ __forceinline__ void stage_row(float *__restrict__ dst, const float *__restrict__ src, int n)
-{
-    if ((reinterpret_cast<uintptr_t>(src) & 15u) == 0) {
-        const int n4 = n >> 2;
-#pragma unroll 4
-        for (int e = threadIdx.x; e < n4; e += kStageThreads)
-            reinterpret_cast<float4 *>(dst)[e] = reinterpret_cast<const float4 *>(src)[e];
-        for (int e = (n4 << 2) + threadIdx.x; e < n; e += kStageThreads) dst[e] = src[e];
-    } else {
-#pragma unroll 4
-        for (int e = threadIdx.x; e < n; e += kStageThreads) dst[e] = src[e];
-    }
-}
-
-// The columns [c0, c1) of part `part` of `parts` of a row of n.
-__device__ __forceinline__ void stage_part(int n, int parts, int part, int &c0, int &c1)
-{
-    const int per = (n + parts - 1) / parts;
-    c0 = part * per;
-    c1 = min(n, c0 + per);
+    return std::max(1, std::min((n + 4 * kStageThreads - 1) / (4 * kStageThreads), 256 / batch));
 }
 
 }  // namespace dol

@@ -335,6 +335,12 @@ bool byj_bwd_wide(const dol_fn_table *f);
 bool byj_bwd_staged(const dol_fn_table *f);
 dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb, float *out,
                              int64_t ldo, hipStream_t st, bool *done);
+// Unary Apply over rows of n_in tags (unary_rows_ok) to S columns: col_ij = the symbols of column c in ascending order at col_ptr[c] ..
+// col_ptr[c + 1], lists = the same two to a word (upload_column_lists; filling: n_in).
+hipError_t upload_column_lists(const std::vector<uint32_t> &ptr, int32_t n, const std::vector<uint32_t> &ij, uint32_t filling, ListPlan *plan);
+inline bool unary_rows_ok(int32_t n_in) { return n_in >= kStageMinRow && sizeof(float) * n_in <= kStageMaxBytes; }
+dol_status launch_unary_fwd(int32_t n_in, int32_t S, const ListPlan &lists, const uint32_t *col_ptr, const uint32_t *col_ij, int32_t batch,
+                            const float *x, int64_t ldx, float *out, int64_t ldo, hipStream_t st);
 dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
                              const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
                              hipStream_t st, bool *done);

@@ -103,6 +103,11 @@ static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, bool
     return plan->words.upload(words);
 }
 
+hipError_t upload_column_lists(const std::vector<uint32_t> &ptr, int32_t n, const std::vector<uint32_t> &ij, uint32_t filling, ListPlan *plan)
+{
+    return upload_lists(ptr, n, true, [&](uint32_t q) { return ij[q]; }, filling, plan);
+}
+
 static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, dol_fn_table **out)
 {
     // ascending (i, j); a function has one value per argument tuple

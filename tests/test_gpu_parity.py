@@ -2050,6 +2050,46 @@ def test_apply_k_argument_errors_and_empty(dol):
     dol.apply_k([dol.Dist(np.arange(2), torch.ones((0, 2), device="cuda")), dol.Dist(np.arange(3), torch.ones((0, 3), device="cuda"))], f, None, e)
 
 
+@pytest.mark.parametrize("n", [2047, 2048, 40445, 40448, 40449])
+@pytest.mark.parametrize("lengths", [[1], [2, 1], [1, 2, 3, 4, 5, 127, 128, 129, 255], [1024, 1025, 7]], ids=lambda x: "-".join(map(str, x)))
+@pytest.mark.parametrize("B", [1, 70, 300])
+def test_unary_apply_of_wide_rows(dol, n, lengths, B):
+    """Unary Apply, forward and backward, on either side of the shortest and longest rows that are staged in LDS: columns of one to
+    a thousand symbols (two to a word of the lists; 128 are the most that a lane sums), short lists and long ones in their two
+    kernels, a last chunk that is not full, rejected symbols, rows of other strides, columns at the clamp and beyond.
+    Tolerance: the bar of 1e-5; where a sum of at most 128 tags is exactly 1 or beyond it, the decision is the oracle's."""
+    if B == 300 and n > 3000:
+        n, B = n, 3
+    col, c = np.full(n, -1, np.int32), 0
+    place, at = W.splitmix64(5, np.arange(n)).argsort(kind="stable"), 0
+    while at < n - 5:
+        take = min(lengths[c % len(lengths)], n - 5 - at)
+        col[place[at:at + take]] = 3 * c
+        at, c = at + take, c + 1
+    x = (W.uniform01(8, B * n).reshape(B, n) * (1.2 / np.bincount(col[col >= 0])[np.maximum(col, 0)])).astype(np.float32)
+    x[0] = 0.0
+    x[0, col == 0] = 1.0                                         # a sum of exactly 1, or of more
+    kept = np.nonzero(col >= 0)[0]
+    look = np.unique(np.r_[0:min(B, 6), B - 1])
+    syms, want, _, pre = oracle.damp_applyk_fwd(kept[:, None], col[kept], [x[look]], want_pre=True)
+    g = W.normal(9, B * syms.size).astype(np.float32).reshape(B, -1)
+    want_g, = oracle.damp_applyk_bwd(kept[:, None], col[kept], [x[look]], g[look])
+    f = dol.FnkTable.create_dense(col)
+    buf, gbuf, out = torch.zeros((B, n + 3), device="cuda"), torch.zeros((B, n + 3), device="cuda"), torch.full((B, syms.size + 5), 7.0, device="cuda")
+    buf[:, :n] = dev(x)
+    d, o = dol.Dist(np.arange(n), buf[:, :n]), dol.Dist(syms, out[:, :syms.size])
+    dol.apply_k([d], f, None, o)
+    dol.apply_k_backward([d], f, o, dev(g), [gbuf])
+    got, got_g = host(out)[look], host(gbuf)[look, :n]
+    assert np.all(got[:, syms.size:] == 7.0)
+    assert_close(got[:, :syms.size], want, "unary forward")
+    sure = np.abs(pre - 1.0) > (0 if max(lengths) <= 128 else 1e-4)
+    np.testing.assert_array_equal((got[:, :syms.size] == 1.0)[sure], (want == 1.0)[sure])
+    passes = np.ones((look.size, n), bool)
+    passes[:, kept] = sure[:, np.searchsorted(syms, col[kept])] | (pre == 1.0)[:, np.searchsorted(syms, col[kept])]
+    np.testing.assert_array_equal(got_g[passes], want_g.astype(np.float32)[passes])
+
+
 # ---------------------------------------------------------------- Product-N fold (irregular growing symbol sets)
 
 @pytest.mark.parametrize("batch,n", [(64, 4), (256, 8), (33, 11)])
