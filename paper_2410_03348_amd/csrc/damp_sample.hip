@@ -37,6 +37,8 @@ struct Lists {                          // struct ListPlan (internal.h) on the d
 struct SampleFwd {
     int32_t na, nb, S, parts;
     int32_t map_ld, long_weight;        // dense maps
+    int32_t huge;                       // the longest column, if a workgroup sums it (else -1), and its tuples
+    uint32_t huge_q0, huge_q1;
     int32_t exact;                      // every column in its tuples' order (lists only)
     uint32_t shared;                    // see xcd_shared
     const uint16_t *map;
@@ -288,13 +290,13 @@ struct ChainColumns {
     }
 };
 
-// The columns of more than kLaneList tuples, part `part` of `parts` (the last one gets the longest): put(c, sum) is called by
-// one lane.
+// The columns of more than kLaneList tuples but the first `skip`, part `part` of `parts` (the last one gets the longest): put(c, sum)
+// is called by one lane.
 template <typename F>
-__device__ __forceinline__ void long_columns(const SampleFwd &A, const float *ar, const float *br, int part, float *scratch, F put)
+__device__ __forceinline__ void long_columns(const SampleFwd &A, int skip, const float *ar, const float *br, int part, float *scratch, F put)
 {
     const Lists &L = A.lists;
-    for (int l = A.parts - 1 - part; l < L.n_huge; l += A.parts) {
+    for (int l = skip + A.parts - 1 - part; l < L.n_huge; l += A.parts) {
         const int c = static_cast<int>(L.longer[l]);
         const float v = long_sum<true>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], scratch);
         if (threadIdx.x == 0) put(c, v);
@@ -310,12 +312,84 @@ __device__ __forceinline__ void long_columns(const SampleFwd &A, const float *ar
 
 // ---------------------------------------------------------------- forward, dense maps
 
-// One j at a time is not the order the clamp decision is defined in; the terms' magnitudes bound how far the two sums can
-// lie apart, and only a sum within that distance of 1 is taken again in the defining order.
-template <int NBP>
+typedef __attribute__((address_space(3))) float lds_float;
+
+__device__ __forceinline__ uint32_t lds_address(float *p) { return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_float *)p)); }
+
+// The row's entry that half H of two map entries names; the row lies at `base` in LDS.  One instruction makes the address (the
+// compiler takes the half out and adds it shifted, two of the five that a tuple cost).
+template <int H>
+__device__ __forceinline__ float entry_of(uint32_t base, uint32_t two)
+{
+    uint32_t at;
+    if constexpr (H == 0) asm("v_mad_u32_u16 %0, %1, 4, %2" : "=v"(at) : "v"(two), "s"(base));
+    else asm("v_mad_u32_u16 %0, %1, 4, %2 op_sel:[1,0,0,0]" : "=v"(at) : "v"(two), "s"(base));
+    return *reinterpret_cast<const lds_float *>(at);
+}
+
+// The longest column of a dense-map table, which the last part's workgroup sums (in a product's table that of 0: as many tuples
+// as the first operand has symbols).  Its words are on their way while the row is copied and while the words before them
+// are used; the wavefronts' shares of the sum wait in LDS until the other columns are done.  (18 506 tuples: the words asked for
+// one step after another at the end held the launch up by 3 to 5 us.)
+struct HugeColumn {
+    static constexpr int kAhead = 8;
+    uint32_t ij[kAhead], q, q1;
+
+    __device__ __forceinline__ void words(const SampleFwd &A)
+    {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) ij[u] = A.col_ij[min(q + u * blockDim.x, q1 - 1)];
+    }
+    __device__ __forceinline__ void ask(const SampleFwd &A)
+    {
+        q = A.huge_q0 + threadIdx.x, q1 = A.huge_q1;
+        words(A);
+    }
+    // br: the second operand's tags, in LDS
+    __device__ __forceinline__ void run(const SampleFwd &A, const float *ar, const float *br, float *shares)
+    {
+        float acc = 0.0f, mag = 0.0f, err = 0.0f;
+        while (q - threadIdx.x < q1) {                      // (the same for all threads)
+            float x[kAhead], y[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                x[u] = q + u * blockDim.x < q1 ? ar[ij[u] & 0xffffu] : 0.0f;
+                y[u] = q + u * blockDim.x < q1 ? br[ij[u] >> 16] : 0.0f;
+            }
+            q += kAhead * blockDim.x;
+            if (q - threadIdx.x < q1) words(A);
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                acc = __builtin_fmaf(x[u], y[u], acc);
+                mag = __builtin_fmaf(fabsf(x[u]), fabsf(y[u]), mag);
+                err += fminf(fabsf(x[u] * y[u]), 1.1920929e-7f);
+            }
+        }
+        acc = wave_sum(acc), mag = wave_sum(mag), err = wave_sum(err);
+        const int wave = wave_number();
+        if ((threadIdx.x & (kWave - 1)) == 0) shares[wave] = acc, shares[16 + wave] = mag, shares[32 + wave] = err;
+    }
+    // The sum, by a whole wavefront after a barrier.
+    static __device__ __forceinline__ float finish(const SampleFwd &A, const float *ar, const float *br, const float *shares)
+    {
+        float acc = 0.0f, mag = 0.0f, err = 0.0f;
+        const int n_waves = blockDim.x / kWave;
+        for (int w = 0; w < n_waves; ++w) acc += shares[w], mag += shares[16 + w], err += shares[32 + w];
+        if (order_matters(acc, mag, err, A.huge_q1 - A.huge_q0, blockDim.x)) acc = serial_sum(ar, br, A.col_ij, A.huge_q0, A.huge_q1);
+        return acc;
+    }
+};
+
+// A column's tuples are defined to be added up in the order of i.  FALLING: in every column j falls as i rises (any function that
+// grows with both operands), and one j at a time, the last one first, is that order: 18 497 x 10 -> 23 410, B=256 20.2 us, 19.7 so.
+// Else the terms' magnitudes bound how far the two sums can lie apart, and only a sum within that distance of 1 is taken again
+// in the defining order.  With one instruction to an address and the longest column's words ahead 18.7 us, of which an empty launch
+// takes 3.6, the row's copy 2 and the columns 11 (30 M gathers of 4 bytes and 0.5 MB of map a sample, from L2).  Two samples to a
+// workgroup, side by side in LDS and a map entry read once for both: 17.8, but nothing gained at 100 samples and below.
+template <int NBP, bool FALLING>
 __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
 {
-    __shared__ float scratch[48];
+    __shared__ float shares[48], yl[kByJMax];
     __shared__ int some;
     const unsigned id = xcd_shared(blockIdx.x, A.shared);
     const int64_t s = id / static_cast<unsigned>(A.parts);
@@ -325,40 +399,48 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
     const int c0 = min(A.S, part * per), c1 = part == A.parts - 1 ? A.S : min(A.S, c0 + per);
     const float *br = A.b + s * A.ldb;
     float *out = A.out + s * A.ldo;
+    const bool sums_huge = A.huge >= 0 && part == A.parts - 1;
+    HugeColumn huge;
+    if (sums_huge) huge.ask(A);
     if (threadIdx.x == 0) some = 0;
     copy_row(ar, A.a + s * A.lda, A.na);
+    if (static_cast<int>(threadIdx.x) < A.nb) yl[threadIdx.x] = br[threadIdx.x];
     float y[NBP];
 #pragma unroll
     for (int j = 0; j < NBP; ++j) y[j] = br[j < A.nb ? j : 0];      // (the maps' extra rows are empty)
     __syncthreads();
+    if (sums_huge) huge.run(A, ar, yl, shares);
     bool again = false;
     const int lane = threadIdx.x & (kWave - 1);
+    const uint32_t base = lds_address(ar);
     // (Neighbouring lanes take neighbouring columns: their tags are mostly neighbours too, and lie in other banks.  With four
     // neighbours to a lane the gathers of a 16-digit product's tables met 1.6 times as many bank conflicts; its pass at 256 samples
     // 300 us, 296 with the forward maps so, 293 with the backward ones as well.)
     for (int block = c0 + kByJBlock * wave_number(); block < c1; block += 4 * static_cast<int>(blockDim.x)) {
         const int c = block + lane;                     // and 64, 128, 192 further
-        ushort4 m[NBP];
+        uint2 m[NBP];                                   // four entries each
 #pragma unroll
-        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const ushort4 *>(A.map + static_cast<size_t>(j) * A.map_ld + block + 4 * lane);
-        const uint16_t mark[4] = {m[0].x, m[0].y, m[0].z, m[0].w};
-        const uint16_t none = static_cast<uint16_t>(A.na);
-        m[0].x = min(m[0].x, none), m[0].y = min(m[0].y, none), m[0].z = min(m[0].z, none), m[0].w = min(m[0].w, none);
+        for (int j = 0; j < NBP; ++j) m[j] = *reinterpret_cast<const uint2 *>(A.map + static_cast<size_t>(j) * A.map_ld + block + 4 * lane);
+        const uint32_t mark[4] = {m[0].x & 0xffffu, m[0].x >> 16, m[0].y & 0xffffu, m[0].y >> 16};
+        const uint32_t none = static_cast<uint32_t>(A.na);
+        m[0].x = min(mark[0], none) | min(mark[1], none) << 16, m[0].y = min(mark[2], none) | min(mark[3], none) << 16;
         float acc[4] = {0.0f, 0.0f, 0.0f, 0.0f}, mag[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int j = 0; j < NBP; ++j) {
-            const float x[4] = {ar[m[j].x], ar[m[j].y], ar[m[j].z], ar[m[j].w]};
+        for (int jj = 0; jj < NBP; ++jj) {
+            const int j = FALLING ? NBP - 1 - jj : jj;
+            const float x[4] = {entry_of<0>(base, m[j].x), entry_of<1>(base, m[j].x), entry_of<0>(base, m[j].y), entry_of<1>(base, m[j].y)};
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 acc[k] = __builtin_fmaf(x[k], y[j], acc[k]);
-                mag[k] = __builtin_fmaf(fabsf(x[k]), fabsf(y[j]), mag[k]);
+                if (!FALLING) mag[k] = __builtin_fmaf(fabsf(x[k]), fabsf(y[j]), mag[k]);
             }
         }
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const bool there = c + kWave * k < c1 && mark[k] != kByJWave;       // (kByJWave: many tuples, summed last)
-            const bool near = !(fabsf(acc[k] - 1.0f) > mag[k] * (static_cast<float>(NBP + 2) * 1.1920929e-7f));
-            const bool list = (near || mark[k] == kByJList) && there;           // (kByJList: some j twice)
+            const bool there = c + kWave * k < c1 && mark[k] != kByJWave;           // (kByJWave: many tuples, summed apart)
+            const bool near = FALLING ? acc[k] != acc[k]                            // (0 for no tuple, times an infinity)
+                                      : !(fabsf(acc[k] - 1.0f) > mag[k] * (static_cast<float>(NBP + 2) * 1.1920929e-7f));
+            const bool list = (near || mark[k] == kByJList) && there;               // (kByJList: some j twice)
             again |= list;
             if (there) out[c + kWave * k] = list ? __builtin_nanf("") : fminf(acc[k], 1.0f);
         }
@@ -374,24 +456,29 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
             if (q1 - q0 <= static_cast<uint32_t>(kLaneList)) out[c] = fminf(column_sum(ar, br, A.col_ij, q0, q1), 1.0f);
         }
     }
-    long_columns(A, ar, br, part, scratch, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
+    if (sums_huge && wave_number() == 0) {
+        const float v = HugeColumn::finish(A, ar, br, shares);
+        if (lane == 0) out[A.huge] = fminf(v, 1.0f);
+    }
+    if (A.lists.n_huge > 1) __syncthreads();            // (they use the shares' place)
+    long_columns(A, A.huge >= 0 ? 1 : 0, ar, br, part, shares, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
 }
 
-template <int NBP>
+template <int NBP, bool FALLING>
 __global__ void __launch_bounds__(kSmallThreads)
 damp_byj_fwd_kernel(const SampleFwd A)
 {
     extern __shared__ __align__(16) float lds[];
-    byj_fwd<NBP>(A, lds);
+    byj_fwd<NBP, FALLING>(A, lds);
 }
 
 // (64 registers, for two workgroups of 1 024 threads to a unit)
-template <int NBP>
+template <int NBP, bool FALLING>
 __global__ void __launch_bounds__(kSampleThreads, 8)
 damp_byj_fwd_staged_kernel(const SampleFwd A)
 {
     extern __shared__ __align__(16) float lds[];
-    byj_fwd<NBP>(A, lds);
+    byj_fwd<NBP, FALLING>(A, lds);
 }
 
 // ---------------------------------------------------------------- forward, tuple lists
@@ -496,7 +583,7 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
         }
         __syncthreads();
     }
-    if (!A.exact) long_columns(A, ar, br, part, scratch, put_long);
+    if (!A.exact) long_columns(A, 0, ar, br, part, scratch, put_long);
 }
 
 // Unary Apply over wide rows: out[c] = min(1, sum of the tags of column c's symbols).  The lists hold two symbols to a word.  A
@@ -565,7 +652,7 @@ damp_apply1_fwd_staged_kernel(const SampleFwd A)
         if (!more) break;
         now = next;
     }
-    long_columns(A, lds, &one, part, scratch, put);         // (a tuple's word: the symbol, times symbol 0 of `one`)
+    long_columns(A, 0, lds, &one, part, scratch, put);         // (a tuple's word: the symbol, times symbol 0 of `one`)
 }
 
 // ---------------------------------------------------------------- backward
@@ -591,28 +678,39 @@ __device__ __forceinline__ bool gated_row(const SampleBwd &A, int64_t s, float *
         for (int w = threadIdx.x; w < (A.S + 31) / 32; w += blockDim.x) closed[w] = 0u;
     __syncthreads();
     const int lane = threadIdx.x & (kWave - 1), wave = wave_number(), n_waves = blockDim.x / kWave;
-    for (int c0 = 4 * kWave * wave; c0 < A.S; c0 += 4 * kWave * n_waves) {
-        const int c = c0 + 4 * lane, n = A.S - c;
-        bool at_one = false;
-        if (n > 0) {
-            const float4 o4 = load4(outr + c, n);
-            at_one = o4.x >= 1.0f || o4.y >= 1.0f || o4.z >= 1.0f || o4.w >= 1.0f;
-            if (STAGED) {
-                const float4 g4 = load4(gr + c, n);
-                const float g[4] = {g4.x, g4.y, g4.z, g4.w};
+    constexpr int U = 2;                    // pieces of both rows that a lane asks for before it waits
+    for (int first = 4 * kWave * wave; first < A.S; first += U * 4 * kWave * n_waves) {
+        float4 o4[U], g4[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c0 = first + u * 4 * kWave * n_waves, c = c0 + 4 * lane;
+            if (c0 >= A.S) break;           // (uniform)
+            o4[u] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (c >= A.S) continue;
+            o4[u] = load4(outr + c, A.S - c);
+            if (STAGED) g4[u] = load4(gr + c, A.S - c);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c0 = first + u * 4 * kWave * n_waves, c = c0 + 4 * lane;
+            if (c0 >= A.S) break;
+            if (STAGED && c + 4 <= A.S) {
+                *reinterpret_cast<float4 *>(gh + c) = g4[u];
+            } else if (STAGED) {
+                const float g[4] = {g4[u].x, g4[u].y, g4[u].z, g4[u].w};
 #pragma unroll
                 for (int k = 0; k < 4; ++k)
-                    if (k < n) gh[c + k] = g[k];
+                    if (c + k < A.S) gh[c + k] = g[k];
             }
-        }
-        if (!__ballot(at_one)) continue;
-        for (int cc = c0 + lane; cc < min(A.S, c0 + 4 * kWave); cc += kWave) {      // (neighbouring lanes, neighbouring columns)
-            if (!(outr[cc] >= 1.0f)) continue;
-            const uint32_t q0 = A.col_ptr[cc], q1 = A.col_ptr[cc + 1];
-            if (q1 - q0 > static_cast<uint32_t>(kLongTableCol)) {
-                const int slot = atomicAdd(n_late, 1);
-                if (slot < kLateMax) late[slot] = cc;
-            } else if (!(column_sum(ar, br, A.col_ij, q0, q1) <= 1.0f)) close(cc);
+            if (!__ballot(o4[u].x >= 1.0f || o4[u].y >= 1.0f || o4[u].z >= 1.0f || o4[u].w >= 1.0f)) continue;
+            for (int cc = c0 + lane; cc < min(A.S, c0 + 4 * kWave); cc += kWave) {      // (neighbouring lanes, neighbouring columns)
+                if (!(outr[cc] >= 1.0f)) continue;
+                const uint32_t q0 = A.col_ptr[cc], q1 = A.col_ptr[cc + 1];
+                if (q1 - q0 > static_cast<uint32_t>(kLongTableCol)) {
+                    const int slot = atomicAdd(n_late, 1);
+                    if (slot < kLateMax) late[slot] = cc;
+                } else if (!(column_sum(ar, br, A.col_ij, q0, q1) <= 1.0f)) close(cc);
+            }
         }
     }
     __syncthreads();
@@ -659,6 +757,7 @@ __device__ __forceinline__ void byj_bwd(const SampleBwd &A, float *lds)
     constexpr int R = STAGED || NBP < 10 ? 4 : 2;       // rows at a time (gathers from memory: as many as registers hold)
     typedef uint16_t __attribute__((ext_vector_type(R))) entries;
     const int last = A.S - 1;
+    const uint32_t base = lds_address(gh);
     const int lane = threadIdx.x & (kWave - 1), wave = wave_number(), n_waves = blockDim.x / kWave;
     for (int i0 = R * kWave * wave; i0 < A.na; i0 += R * kWave * n_waves) {
         const int i = i0 + lane, at = (i0 & ~(kByJBlock - 1)) + 4 * lane + ((i0 / kWave) & 3);      // rows i, i + 64 ..; where their entries lie
@@ -673,12 +772,12 @@ __device__ __forceinline__ void byj_bwd(const SampleBwd &A, float *lds)
         for (int j = 0; j < NBP; ++j) {
             int col[R];
             float v[R];
-#pragma unroll
-            for (int k = 0; k < R; ++k) col[k] = m[j][k];
-            if (STAGED) {
-#pragma unroll
-                for (int k = 0; k < R; ++k) v[k] = gh[col[k]];
+            if constexpr (STAGED) {
+                const uint2 two = __builtin_bit_cast(uint2, m[j]);
+                v[0] = entry_of<0>(base, two.x), v[1] = entry_of<1>(base, two.x), v[2] = entry_of<0>(base, two.y), v[3] = entry_of<1>(base, two.y);
             } else {
+#pragma unroll
+                for (int k = 0; k < R; ++k) col[k] = m[j][k];
                 uint32_t shut[R];
 #pragma unroll
                 for (int k = 0; k < R; ++k) shut[k] = gates ? closed[min(col[k], last) >> 5] >> (col[k] & 31) : 0u;
@@ -1025,26 +1124,24 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
     if (byj) {
         A.map = f->byj_src.ptr, A.map_ld = f->byj_src_ld;
         A.long_weight = static_cast<int32_t>(std::min<int64_t>(f->col_lists.huge_words / f->byj_nbp, f->n_out));
+        A.huge = f->col_lists.first_huge;
+        if (A.huge >= 0) A.huge_q0 = f->h_col_ptr[A.huge], A.huge_q1 = f->h_col_ptr[A.huge + 1];
         const size_t lds = sizeof(float) * static_cast<size_t>(f->na + 4);
         A.parts = best_parts(batch, long_parts(f->col_lists, std::min(16, (f->n_out + 4 * kSmallThreads - 1) / (4 * kSmallThreads))), f->na,
                              [&](int p) { return (static_cast<double>(f->n_out + A.long_weight) * f->byj_nbp + 4.0 * f->col_lists.mid_words) / p; },
                              byj_fwd_wide(f) ? kSampleThreads : kSmallThreads, lds);
         A.shared = shared_ranges(batch, A.parts, f->na);
-        const unsigned grid = static_cast<unsigned>(batch) * A.parts;
-        const int64_t work = std::max<int64_t>(f->n_out / A.parts + 3, f->na) / 4;
-        if (byj_fwd_wide(f)) {
+        const dim3 grid(static_cast<unsigned>(batch) * A.parts);
+        const dim3 block(threads_for(std::max<int64_t>(f->n_out / A.parts + 3, f->na) / 4, byj_fwd_wide(f) ? kSampleThreads : kSmallThreads));
 #define CALL(N)                                                                                                                \
     {                                                                                                                          \
-        if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_byj_fwd_staged_kernel<N>), kStageMaxBytes));   \
-        hipLaunchKernelGGL(damp_byj_fwd_staged_kernel<N>, dim3(grid), dim3(threads_for(work, kSampleThreads)), lds, st, A);    \
+        const auto kernel = byj_fwd_wide(f) ? (f->byj_falling ? &damp_byj_fwd_staged_kernel<N, true> : &damp_byj_fwd_staged_kernel<N, false>)  \
+                                            : (f->byj_falling ? &damp_byj_fwd_kernel<N, true> : &damp_byj_fwd_kernel<N, false>);               \
+        if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kStageMaxBytes));               \
+        hipLaunchKernelGGL(kernel, grid, block, lds, st, A);                                                                   \
     }
-            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
+        DOL_DISPATCH_NBP(f->byj_nbp, CALL)
 #undef CALL
-        } else {
-#define CALL(N) hipLaunchKernelGGL(damp_byj_fwd_kernel<N>, dim3(grid), dim3(threads_for(work, kSmallThreads)), lds, st, A)
-            DOL_DISPATCH_NBP(f->byj_nbp, CALL)
-#undef CALL
-        }
     } else {
         // (stored where they fall the results of lists of many lengths dirty every line many times over: 1 200 x 30 -> 6 500,
         // 5.5 words to a list, B=4 000 79 us against 63.  Lists of one or two words are in column order but for a few: 1 200 x 7

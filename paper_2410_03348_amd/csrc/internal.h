@@ -100,6 +100,7 @@ constexpr int kMidList = 512;
 struct ListPlan {
     DevArray<uint32_t> order, ptr, words, longer;
     int32_t n_huge = 0, n_wave = 0, n_mid = 0;
+    int32_t first_huge = -1;                    // the first of n_huge
     int64_t huge_words = 0, mid_words = 0;      // words of the workgroups' lists; of the other longer ones
     size_t n_words = 0;                 // words laid out for lanes, filling included
 };
@@ -208,6 +209,7 @@ struct dol_fn_table {
     int32_t byj_nbp = 0;               // rows of the two maps: nb padded to 4, 8, 10 or 16 (the extra rows name nothing)
     int32_t byj_src_ld = 0, byj_col_ld = 0;
     bool byj_fwd = false;              // forward uses the map only where it is at least half full (else the tuple lists)
+    bool byj_falling = false;          // every column of the map has its tuples' j falling: j by j from the last one is their order
     dol::DevArray<uint16_t> byj_src, byj_col;
     // tables whose operand rows fit in registers: straight-line kernels written for the table (built on first use)
     mutable std::unique_ptr<dol::JitState, dol::JitDeleter> jit;

@@ -95,6 +95,7 @@ static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, bool
         (by_workgroup ? huge : l > kMidList ? wave : mid).push_back(static_cast<uint32_t>(x));
     }
     plan->n_huge = static_cast<int32_t>(huge.size()), plan->n_wave = static_cast<int32_t>(wave.size()), plan->n_mid = static_cast<int32_t>(mid.size());
+    if (!huge.empty()) plan->first_huge = static_cast<int32_t>(huge[0]);
     huge.insert(huge.end(), wave.begin(), wave.end());
     huge.insert(huge.end(), mid.begin(), mid.end());
     hipError_t e;
@@ -243,9 +244,11 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
         tb->byj_nbp = nbp, tb->byj_src_ld = src_ld, tb->byj_col_ld = col_ld;
         const uint16_t no_i = static_cast<uint16_t>(na), no_c = static_cast<uint16_t>(S);
         std::vector<uint16_t> src(static_cast<size_t>(nbp) * src_ld, no_i), colof(static_cast<size_t>(nbp) * col_ld, no_c);
+        bool falling = true;
         for (int32_t c = 0; c < S; ++c) {
             const bool is_long = col_ptr[c + 1] - col_ptr[c] > static_cast<uint32_t>(kLaneList);
             bool regular = !is_long;
+            for (uint32_t q = col_ptr[c] + 1; q < col_ptr[c + 1] && !is_long; ++q) falling &= col_ij[q] >> 16 < col_ij[q - 1] >> 16;
             for (uint32_t q = col_ptr[c]; q < col_ptr[c + 1] && regular; ++q) {
                 uint16_t &slot = src[static_cast<size_t>(col_ij[q] >> 16) * src_ld + byj_place(c)];
                 if (slot != no_i) regular = false;
@@ -260,6 +263,7 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
         if ((e = tb->byj_src.upload(src)) != hipSuccess || (e = tb->byj_col.upload(colof)) != hipSuccess)
             return hip_fail(e, "uploading the function table");
         tb->byj_ok = true;
+        tb->byj_falling = falling;
         tb->byj_fwd = 2 * tup.size() >= static_cast<size_t>(nb) * static_cast<size_t>(S);
     }
     tb->h_col_ptr.swap(col_ptr);

@@ -2259,6 +2259,33 @@ def test_dense_map_blocks(dol, na, nb):
     assert_close(host(gb), 2 * wb, "grad b, added")
 
 
+@pytest.mark.parametrize("grows", [True, False])
+@pytest.mark.parametrize("na,nb,B", [(600, 3, 2), (2047, 10, 3), (2049, 8, 40), (8193, 16, 2), (18001, 10, 5)])
+def test_dense_maps_in_and_out_of_the_defining_order(dol, na, nb, B, grows):
+    """f(i, j) = i + 3j, whose columns' tuples have j falling as i rises, and i - 3j, where it rises; the last j maps every i to one
+    symbol, a column that a workgroup sums where it has more than 512 tuples.  One second tag is infinite: columns without it stay
+    finite.  Where j falls the sums are those of the defining order, float32 for float32; the long column's tolerance is the bar."""
+    table = (np.arange(na)[:, None] + (3 if grows else -3) * np.arange(nb)[None, :] + 3 * nb).astype(np.int32)
+    table[:, nb - 1] = na + 6 * nb
+    a = W.softmax_rows(W.normal(76, B * na).reshape(B, na)) * np.float32(na / 3.0)      # columns on both sides of the clamp
+    b = W.softmax_rows(W.normal(77, B * nb).reshape(B, nb))
+    b[:, nb - 1] = 0.7 / na * 3.0
+    b[1, 0] = np.inf
+    tri = oracle.dense_to_triples(table)
+    syms, want, pre32, pre64 = oracle.damp_apply2_fwd(tri, na, nb, a, b, want_pre=True)
+    f = dol.FnTable.create_dense(table)
+    assert "byj" in f.kernel_at(False, B)
+    da, db = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b))
+    out = dol.Dist.empty(f.out_syms, B)
+    dol.apply2(da, db, f, None, out)
+    got = host(out.prob)
+    assert (want[1] < 1).any() and np.isinf(pre32[1]).any() and (want[0] == 1).any()
+    assert_close(got, want, "forward")
+    np.testing.assert_array_equal(got[:, :-1] == 1.0, pre32[:, :-1] >= 1.0)
+    if grows:
+        np.testing.assert_array_equal(got[:, :-1], np.minimum(pre32[:, :-1], np.float32(1)))
+
+
 @pytest.mark.parametrize("nb", [4, 16, 40])
 @pytest.mark.parametrize("extra,batch", [(0, 3), (57, 1), (4096, 2), (4097, 300)])
 def test_workgroup_per_sample_kernels(dol, nb, extra, batch):
