@@ -14,7 +14,7 @@
 //
 // Layout of a launch: a workgroup of four wavefronts owns a tile of 64 samples (batches too small to give every compute
 // unit two such tiles: eight wavefronts, or tiles of 32 samples; see build_for).  The tile's operand rows travel
-// HBM -> LDS with flat 16-byte loads (rows of whole 16-byte pieces padded to a pitch of n + 4 floats, which keeps a lane's
+// HBM -> LDS with flat 16-byte loads (rows of whole 16-byte pieces an odd number of them apart, which keeps a lane's
 // 16-byte reads of its own row off its neighbours' banks; rows of any other length as they lie in memory, read word by word),
 // each lane pulls its sample's rows into registers, the wavefronts split the work (forward: 64 output columns at a time each;
 // backward: half of the rows of one operand each), results go back through LDS and leave as flat 16-byte stores.
@@ -29,7 +29,13 @@
 // Merged forms (dol_apply2_filter_union and its reverse): the same kernels with Filter and Union folded into their
 // epilogues, so the Apply's result never leaves the chip; the forward pass leaves one word per sample saying whether
 // any clamp acted, and the reverse pass re-derives decisions only for tiles that hold such a sample.  The two merged
-// bodies are also emitted as device functions of one kernel (dol_apply2_filter_union_forward_backward).
+// bodies are also emitted one after the other into one kernel (dol_apply2_filter_union_forward_backward): the operands' rows stay
+// in registers and the clamp words in LDS.  Where the result has the third Distribution's symbols in its order (an aligned plan)
+// the first pieces of that operand and of the gradient are asked for together with a's and b's, the kept columns are bits in
+// LDS, and where no clamp acted the third gradient leaves from the registers that bring the gradient in.  One tile to a unit,
+// its phases one after the other, bounds it: 64 x 64 -> 256 at B = 16 384 (84 MB) took 27.6 us with the bodies apart, each staging
+// a and b and the second reading the gradient twice; 20.5 so, where a copy takes 16.7.  (Two groups of the gradient on their way
+// instead of one: 24.4.)
 #include "internal.h"
 
 #include <hip/hiprtc.h>
@@ -94,10 +100,11 @@ thread_local int t_waves = kJitWavesLarge, t_tile_rows = kJitTile;
 #define kJitWaves t_waves
 #define kThreads (kJitTile * t_waves)
 
-// Floats from one sample's row to the next in LDS: four more than it has where it is whole 16-byte pieces, which are then
-// read and written by their lanes as such; any other row has its own length, so that the tile is the block of memory it came
+// Floats from one sample's row to the next in LDS: an odd number of 16-byte pieces where it is whole pieces, which are then
+// read and written by their lanes as such (an even number puts lanes on one another's banks: 60 x 60 -> 64 both ways in one launch with
+// rows 16 pieces apart 22.4 us at B = 8 192, 15 apart 16.3); any other row has its own length, so that the tile is the block of memory it came
 // from (and an odd length keeps the lanes' words off one another's banks).
-int pitch_of(int n) { return n & 3 ? n : n + 4; }
+int pitch_of(int n) { return n & 3 || n & 4 ? n : n + 4; }
 
 // Declares r0 .. r{n-1} and fills them from the lane's row of the staged tile.
 void emit_row_to_regs(Src &o, const char *r, const char *tile, int n)
@@ -108,7 +115,7 @@ void emit_row_to_regs(Src &o, const char *r, const char *tile, int n)
     }
     for (int i = 0; i < n; i += 4)
         o("  float %s%d, %s%d, %s%d, %s%d; { const float4 t = *reinterpret_cast<const float4 *>(%s + lane * %d + %d); %s%d = t.x; %s%d = t.y; "
-          "%s%d = t.z; %s%d = t.w; }\n", r, i, r, i + 1, r, i + 2, r, i + 3, tile, n + 4, i, r, i, r, i + 1, r, i + 2, r, i + 3);
+          "%s%d = t.z; %s%d = t.w; }\n", r, i, r, i + 1, r, i + 2, r, i + 3, tile, pitch_of(n), i, r, i, r, i + 1, r, i + 2, r, i + 3);
 }
 
 // Flat copy of a tile of `valid` rows of n floats from memory into LDS rows (pitch_of): the loads of all pieces
@@ -142,7 +149,7 @@ void emit_stage_store(Src &o, const char *tag, const char *dst, int n)
     for (int x = 0; x < per_thread; ++x)
         o("  { const int q = tid + %d; %s{ const int s = q / %d, k = q - s * %d; *reinterpret_cast<float4 *>(%s + s * %d + 4 * k) = ld%s%d; } }\n",
           kThreads * x, kThreads * (x + 1) <= kJitTile * n / 4 ? "" : (std::string("if (q < ") + std::to_string(kJitTile * n / 4) + ") ").c_str(), n / 4, n / 4,
-          dst, n + 4, tag, x);
+          dst, pitch_of(n), tag, x);
 }
 
 // The forward sums of the columns [c0, c1): declares p<c> and leaves the unclamped sum in it.
@@ -169,24 +176,90 @@ void emit_tile_head(Src &o)
     o("  const long long s0 = (long long)tile * %d;\n  const int valid = batch - s0 < %d ? (int)(batch - s0) : %d;\n", t_tile_rows, t_tile_rows, t_tile_rows);
 }
 
+// Loads of one group of the gradient reaching the Apply's columns [c0, c1) into registers (th[]), and their way
+// into the LDS stage.  merged: column c of the Apply is column ca[c] of the upstream gradient (or dropped).
+// (raw: the gradient as it is; the dropped columns, of an aligned plan, are taken out on the way into the stage)
+void emit_gh_regs(Src &o)
+{
+    for (int x = 0; x < (kJitTile * (kJitGroup / 4) + kThreads - 1) / kThreads; ++x) o("  float4 th%d;\n", x);
+}
+
+void emit_gh_load(Src &o, int S, int c0, int c1, bool merged, bool aligned, const char *ind, bool raw)
+{
+    const int chunks = (c1 - c0 + 3) / 4, per_thread = (kJitTile * chunks + kThreads - 1) / kThreads, over = 4 * chunks - (c1 - c0);
+    for (int x = 0; x < per_thread; ++x) {
+        // (no branches: a conditional block here would invite the compiler to sink the multiply-adds before it past it)
+        o("%s{ int q = tid + %d; q = q < valid * %d ? q : valid * %d - 1; const int s = q / %d, k = q - s * %d;\n", ind, kThreads * x, chunks, chunks,
+          chunks, chunks);
+        if (raw) {
+            o("%s  th%d = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(g + s0 * n3) + (u32)(s * (4 * n3) + (%d + 16 * k))); }\n", ind, x, 4 * c0);
+        } else if (merged) {
+            o("%s  const int4 oc = reinterpret_cast<const int4 *>(ca)[%d + k]; const float *gr = g + (s0 + s) * n3;\n", ind, c0 / 4);
+            if (aligned)    // a kept column of the Apply is the same column of the result: one 16-byte load
+                o("%s  const float4 t = *reinterpret_cast<const float4 *>(gr + %d + 4 * k);\n", ind, c0);
+            else
+                o("%s  const float4 t = make_float4(gr[oc.x > 0 ? oc.x : 0], gr[oc.y > 0 ? oc.y : 0], gr[oc.z > 0 ? oc.z : 0], gr[oc.w > 0 ? oc.w : 0]);\n", ind);
+            o("%s  th%d = make_float4(oc.x >= 0 ? t.x : 0.0f, oc.y >= 0 ? t.y : 0.0f, oc.z >= 0 ? t.z : 0.0f, oc.w >= 0 ? t.w : 0.0f); }\n", ind, x);
+        } else if (S & 3) {
+            // (a row's last piece is the one that ends with the row, moved down in registers)
+            o("%s  const float4u t = *reinterpret_cast<const float4u *>(g + (s0 + s) * %d + %d + 4 * k%s);\n", ind, S, c0,
+              over ? (" - (k == " + std::to_string(chunks - 1) + " ? " + std::to_string(over) + " : 0)").c_str() : "");
+            static const char *const down[4] = {"make_float4(t.x, t.y, t.z, t.w)", "make_float4(t.y, t.z, t.w, 0.0f)", "make_float4(t.z, t.w, 0.0f, 0.0f)",
+                                                "make_float4(t.w, 0.0f, 0.0f, 0.0f)"};
+            if (over) o("%s  th%d = k == %d ? %s : %s; }\n", ind, x, chunks - 1, down[over], down[0]);
+            else o("%s  th%d = %s; }\n", ind, x, down[0]);
+        } else {
+            o("%s  th%d = reinterpret_cast<const float4 *>(g)[((s0 + s) * %d + %d) / 4 + k]; }\n", ind, x, S, c0);
+        }
+    }
+}
+
+// The group's way from registers into its LDS stage, gated on the way by the words of sm (all ones where no clamp acted).
+// raw: where no clamp acted the pieces are c's gradient as well, and leave from here.
+void emit_gh_store(Src &o, int c0, int c1, int g, int n_groups, const char *dst, bool masked, const char *ind, bool raw)
+{
+    const int chunks = (c1 - c0 + 3) / 4, per_thread = (kJitTile * chunks + kThreads - 1) / kThreads;
+    for (int x = 0; x < per_thread; ++x) {
+        const bool whole = kThreads * (x + 1) <= kJitTile * chunks;
+        o("%s{ const int q = tid + %d; %s{ const int s = q / %d, k = q - s * %d;\n", ind, kThreads * x,
+          whole ? "" : (std::string("if (q < ") + std::to_string(kJitTile * chunks) + ") ").c_str(), chunks, chunks);
+        if (raw) {
+            o("%s    if (gc_here && s < valid) { float4 *d4 = reinterpret_cast<float4 *>(reinterpret_cast<char *>(gc + s0 * n3) + (u32)(s * (4 * n3) + (%d + 16 * k))); float4 v = th%d;\n", ind, 4 * c0, x);
+            o("%s      if (accumulate & 4) { const float4 old = *d4; v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w; }\n%s      *d4 = v; }\n", ind, ind);
+            o("%s    const u32 kw = s_keep[%d + k];\n", ind, c0 / 4);
+            o("%s    th%d = make_float4(kw & 1u ? th%d.x : 0.0f, kw & 2u ? th%d.y : 0.0f, kw & 4u ? th%d.z : 0.0f, kw & 8u ? th%d.w : 0.0f);\n", ind, x, x, x, x, x);
+        }
+        if (masked) {
+            o("%s    const u32 mw = sm[(s * %d + %d) * 2 + (k >> 3)] >> ((4 * k) & 31);\n", ind, n_groups, g);
+            o("%s    th%d = make_float4(mw & 1u ? th%d.x : 0.0f, mw & 2u ? th%d.y : 0.0f, mw & 4u ? th%d.z : 0.0f, mw & 8u ? th%d.w : 0.0f);\n", ind, x, x, x, x, x);
+        }
+        o("%s    *reinterpret_cast<float4 *>(%s + s * %d + 4 * k) = th%d; } }\n", ind, dst, kJitGroup + 4, x);
+    }
+}
+
+// The next four pieces of c (of an aligned plan: its columns are the result's) of a thread, pieces qb, qb + threads, ..
+void emit_union_load(Src &o, const char *qb, const char *ind)
+{
+    for (int u = 0; u < 4; ++u)
+        o("%s{ int q = %s + %d; q = q < total3 ? q : total3 - 1; y%d = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(c + s0 * n3) + 16u * (u32)q); }\n", ind, qb, kThreads * u, u);
+}
+
 // Forward.  merged: the kept symbols of the result are merged with a third Distribution c in the same launch
 // (out = union(filter(apply2(a, b)), c)); the Apply's own result then lives in LDS only.
-// (body: a device function over an LDS array handed in, for the kernel that runs both passes; returns its LDS floats in *lds_floats)
-std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = false, bool body = false, int *lds_floats = nullptr)
+// (both: the first half of the kernel that runs both passes; both_source has its head)
+std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = false, bool both = false)
 {
     const int na = f->na, nb = f->nb, S = f->n_out;
+    const bool ahead = both && aligned;
     const int pa = pitch_of(na), pb = pitch_of(nb);
     const int fcols = kJitGroup * kJitWavesLarge / kJitWaves;       // columns a wavefront takes at a time: 64, or 32 of eight wavefronts
-    const int po = merged ? S + 4 : fcols + 4;         // pitch of the result stage: the whole tile, or a wavefront's columns
+    const int po = merged ? pitch_of(S) : fcols + 4;         // pitch of the result stage: the whole tile, or a wavefront's columns
     const int in_floats = kJitTile * (pa + pb), out_floats = merged ? kJitTile * po : kJitWaves * kJitTile * po;
     const int stage_floats = std::max(in_floats, out_floats);
     Src o;
-    if (!body) o.s = kPrologue;
-    if (lds_floats) *lds_floats = stage_floats + (merged ? kJitTile : 0);
-    if (body)
-        o("static __device__ __forceinline__ void damp_table_merge_fwd_body(float *lds, const float *__restrict__ a, const float *__restrict__ b, "
-          "const float *__restrict__ c, float *__restrict__ out, const int *__restrict__ ia, const int *__restrict__ ib, int *saved, "
-          "int batch, int n_tiles, int nc, int n3)\n{\n");
+    if (!both) o.s = kPrologue;
+    if (both)
+        ;
     else if (merged)
         o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_merge_fwd_kernel(const float *__restrict__ a, const float *__restrict__ b, "
           "const float *__restrict__ c, float *__restrict__ out, const int *__restrict__ ia, const int *__restrict__ ib, int *__restrict__ saved, "
@@ -194,17 +267,36 @@ std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = fa
     else
         o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_fwd_kernel(const float *__restrict__ a, const float *__restrict__ b, "
           "float *__restrict__ out, int batch, int n_tiles)\n{\n", kThreads);
-    if (!body) o("  __shared__ __align__(16) float lds[%d];\n", stage_floats + (merged ? kJitTile : 0));
-    o("  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a scalar: branches on it are uniform)\n");
+    if (!both) {
+        o("  __shared__ __align__(16) float lds[%d];\n", stage_floats + (merged ? kJitTile : 0));
+        o("  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a scalar: branches on it are uniform)\n");
+        if (merged) o("  int *sflag = reinterpret_cast<int *>(lds + %d);\n", stage_floats);
+        emit_tile_head(o);
+        o("  __syncthreads();\n");
+    }
     o("  float *sa = lds, *sb = lds + %d, *so = lds + wave * %d;\n", kJitTile * pa, merged ? 0 : kJitTile * po);
-    if (merged) o("  int *sflag = reinterpret_cast<int *>(lds + %d);\n", stage_floats);
-    emit_tile_head(o);
-    o("  __syncthreads();\n");
     if (merged) o("  if (tid < 64) sflag[tid] = 0;\n");
     emit_stage_load(o, "a", "a", na);
     emit_stage_load(o, "b", "b", nb);
+    // What both passes want next, c's first pieces and the gradient's first group, is asked for behind the operands, or, where a
+    // wavefront has 64 columns to sum and long rows in its registers, behind the sums.
+    constexpr int kEarlySyms = 96;
+    auto ask_ahead = [&](bool now) {
+        if (!now) return;
+        emit_union_load(o, "tid", "  ");
+        emit_gh_load(o, S, 0, std::min(S, kJitGroup), true, true, "  ", true);
+    };
+    const bool early = kJitWaves > kJitWavesLarge || na + nb <= kEarlySyms;
+    if (ahead) {
+        o("  const int4 kept4 = reinterpret_cast<const int4 *>(ia)[tid < %d ? tid : %d];\n", S / 4, S / 4 - 1);
+        o("  const int chunks3 = n3 >> 2, total3 = valid * chunks3;\n  float4 y0, y1, y2, y3;\n");
+        emit_gh_regs(o);
+        ask_ahead(early);
+    }
     emit_stage_store(o, "a", "sa", na);
     emit_stage_store(o, "b", "sb", nb);
+    if (ahead)
+        o("  if (tid < %d) s_keep[tid] = (kept4.x >= 0 ? 1u : 0u) | (kept4.y >= 0 ? 2u : 0u) | (kept4.z >= 0 ? 4u : 0u) | (kept4.w >= 0 ? 8u : 0u);\n", S / 4);
     o("  __syncthreads();\n");
     emit_row_to_regs(o, "a", "sa", na);
     emit_row_to_regs(o, "b", "sb", nb);
@@ -240,7 +332,29 @@ std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = fa
         }
         o("  }\n");
     }
-    if (merged) {
+    if (ahead) {
+        // out[s, c] from the Apply's column c, where it is kept (in LDS), and c's column c: 16-byte pieces of the result tile, four
+        // per thread and pass, the next pass's loads on their way
+        ask_ahead(!early);
+        o("  __syncthreads();\n");
+        o("  const int dq = %d / chunks3, dr = %d - dq * chunks3;\n  int ps = tid / chunks3, pk = tid - ps * chunks3;\n", kThreads, kThreads);
+        o("  for (int qb = tid; qb < total3; qb += %d) {\n", 4 * kThreads);
+        o("    const float4 z0 = y0, z1 = y1, z2 = y2, z3 = y3;\n");
+        o("    if (qb + %d < total3) {\n", 4 * kThreads);
+        emit_union_load(o, ("qb + " + std::to_string(4 * kThreads)).c_str(), "      ");
+        o("    }\n");
+        for (int u = 0; u < 4; ++u) {
+            o("    { const int pq = qb + %d;\n", kThreads * u);
+            o("      if (pq < total3) { const u32 kw = pk < %d ? s_keep[pk] : 0u; float4 x4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);\n", S / 4);
+            o("        if (pk < %d) x4 = *reinterpret_cast<const float4 *>(so + ps * %d + 4 * pk);\n", S / 4, po);
+            o("        const float xx[4] = {x4.x, x4.y, x4.z, x4.w}, yy[4] = {z%d.x, z%d.y, z%d.z, z%d.w}; float v[4]; bool over = false;\n", u, u, u, u);
+            o("        for (int e = 0; e < 4; ++e) { const float t = xx[e] + yy[e]; const bool two = (kw >> e) & 1u; over |= two && !(t <= 1.0f); v[e] = two ? fminf(t, 1.0f) : yy[e]; }\n");
+            o("        *reinterpret_cast<float4 *>(reinterpret_cast<char *>(out + s0 * n3) + 16u * (u32)pq) = make_float4(v[0], v[1], v[2], v[3]);\n");
+            o("        if (over) atomicOr(&sflag[ps], 1); }\n");
+            o("      ps += dq; pk += dr; if (pk >= chunks3) { pk -= chunks3; ++ps; } }\n");
+        }
+        o("  }\n  __syncthreads();\n  if (saved && tid < valid) saved[s0 + tid] = sflag[tid];\n");
+    } else if (merged) {
         // out[s, oc] from the Apply's column ia[oc] (in LDS) and c's column ib[oc]: 16-byte pieces of the result tile, four
         // per thread and pass with their loads in flight together; a piece whose four columns of c are neighbours comes
         // with one 16-byte load
@@ -281,7 +395,7 @@ std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = fa
         o("    } }\n");
         o("  __syncthreads();\n  if (saved && tid < valid) saved[s0 + tid] = sflag[tid];\n");
     }
-    o("  }\n}\n");
+    if (!both) o("  }\n}\n");
     return o.s;
 }
 
@@ -300,59 +414,16 @@ int max_multiplicity(const dol_fn_table *f, bool by_b)
     return best;
 }
 
-// Loads of one group of the gradient reaching the Apply's columns [c0, c1) into registers (th[]), and their way
-// into the LDS stage.  merged: column c of the Apply is column ca[c] of the upstream gradient (or dropped).
-void emit_gh_load(Src &o, int S, int c0, int c1, bool merged, bool aligned, const char *ind)
+// (both: the second half of the kernel that runs both passes: the operands' rows are in registers, sflag says which samples a
+// clamp acted in, and of an aligned plan th<x> holds the first group)
+std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = false, bool both = false, int *lds_floats = nullptr)
 {
-    const int chunks = (c1 - c0 + 3) / 4, per_thread = (kJitTile * chunks + kThreads - 1) / kThreads, over = 4 * chunks - (c1 - c0);
-    for (int x = 0; x < per_thread; ++x) {
-        // (no branches: a conditional block here would invite the compiler to sink the multiply-adds before it past it)
-        o("%s{ int q = tid + %d; q = q < valid * %d ? q : valid * %d - 1; const int s = q / %d, k = q - s * %d;\n", ind, kThreads * x, chunks, chunks,
-          chunks, chunks);
-        if (merged) {
-            o("%s  const int4 oc = reinterpret_cast<const int4 *>(ca)[%d + k]; const float *gr = g + (s0 + s) * n3;\n", ind, c0 / 4);
-            if (aligned)    // a kept column of the Apply is the same column of the result: one 16-byte load
-                o("%s  const float4 t = *reinterpret_cast<const float4 *>(gr + %d + 4 * k);\n", ind, c0);
-            else
-                o("%s  const float4 t = make_float4(gr[oc.x > 0 ? oc.x : 0], gr[oc.y > 0 ? oc.y : 0], gr[oc.z > 0 ? oc.z : 0], gr[oc.w > 0 ? oc.w : 0]);\n", ind);
-            o("%s  th%d = make_float4(oc.x >= 0 ? t.x : 0.0f, oc.y >= 0 ? t.y : 0.0f, oc.z >= 0 ? t.z : 0.0f, oc.w >= 0 ? t.w : 0.0f); }\n", ind, x);
-        } else if (S & 3) {
-            // (a row's last piece is the one that ends with the row, moved down in registers)
-            o("%s  const float4u t = *reinterpret_cast<const float4u *>(g + (s0 + s) * %d + %d + 4 * k%s);\n", ind, S, c0,
-              over ? (" - (k == " + std::to_string(chunks - 1) + " ? " + std::to_string(over) + " : 0)").c_str() : "");
-            static const char *const down[4] = {"make_float4(t.x, t.y, t.z, t.w)", "make_float4(t.y, t.z, t.w, 0.0f)", "make_float4(t.z, t.w, 0.0f, 0.0f)",
-                                                "make_float4(t.w, 0.0f, 0.0f, 0.0f)"};
-            if (over) o("%s  th%d = k == %d ? %s : %s; }\n", ind, x, chunks - 1, down[over], down[0]);
-            else o("%s  th%d = %s; }\n", ind, x, down[0]);
-        } else {
-            o("%s  th%d = reinterpret_cast<const float4 *>(g)[((s0 + s) * %d + %d) / 4 + k]; }\n", ind, x, S, c0);
-        }
-    }
-}
-
-// The group's way from registers into its LDS stage, gated on the way by the words of sm (all ones where no clamp acted).
-void emit_gh_store(Src &o, int c0, int c1, int g, int n_groups, const char *dst, bool masked, const char *ind)
-{
-    const int chunks = (c1 - c0 + 3) / 4, per_thread = (kJitTile * chunks + kThreads - 1) / kThreads;
-    for (int x = 0; x < per_thread; ++x) {
-        const bool whole = kThreads * (x + 1) <= kJitTile * chunks;
-        o("%s{ const int q = tid + %d; %s{ const int s = q / %d, k = q - s * %d;\n", ind, kThreads * x,
-          whole ? "" : (std::string("if (q < ") + std::to_string(kJitTile * chunks) + ") ").c_str(), chunks, chunks);
-        if (masked) {
-            o("%s    const u32 mw = sm[(s * %d + %d) * 2 + (k >> 3)] >> ((4 * k) & 31);\n", ind, n_groups, g);
-            o("%s    th%d = make_float4(mw & 1u ? th%d.x : 0.0f, mw & 2u ? th%d.y : 0.0f, mw & 4u ? th%d.z : 0.0f, mw & 8u ? th%d.w : 0.0f);\n", ind, x, x, x, x, x);
-        }
-        o("%s    *reinterpret_cast<float4 *>(%s + s * %d + 4 * k) = th%d; } }\n", ind, dst, kJitGroup + 4, x);
-    }
-}
-
-std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = false, bool body = false, int *lds_floats = nullptr)
-{
+    const bool ahead = both && aligned;
     const int na = f->na, nb = f->nb, S = f->n_out;
     const int pa = pitch_of(na), pb = pitch_of(nb), pg = kJitGroup + 4;
     const int n_groups = (S + kJitGroup - 1) / kJitGroup;
     // LDS: a tile, b tile, two stages for one group of gh each (the first re-used as the result stage), gate words
-    const int off_b = kJitTile * pa, off_g = off_b + kJitTile * pb;
+    const int off_b = kJitTile * pa, off_g = both ? 0 : off_b + kJitTile * pb;
     const int stage = std::max(kJitTile * pg, kJitTile * std::max(pa, pb));
     const int off_m = off_g + 2 * stage, off_u = off_m + kJitTile * n_groups * 2;
     const int off_x = off_u + (merged ? kJitTile * n_groups * 2 : 0), off_f = off_x + (merged ? 2 * S : 0);
@@ -360,15 +431,11 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
     // parts each, multiples of four rows
     const int parts = kJitWaves / 2;
     const int ha = std::min(na, std::max(4, (na / parts + 3) & ~3)), hb = std::min(nb, std::max(4, (nb / parts + 3) & ~3));
-    const int gh_per_thread = (kJitTile * (kJitGroup / 4) + kThreads - 1) / kThreads;
     Src o;
-    if (!body) o.s = kPrologue;
+    if (!both) o.s = kPrologue;
     if (lds_floats) *lds_floats = off_f + 4;
-    if (body)
-        o("static __device__ __forceinline__ void damp_table_merge_bwd_body(float *lds, const float *__restrict__ a, const float *__restrict__ b, "
-          "const float *__restrict__ c, const float *__restrict__ g, float *__restrict__ ga, float *__restrict__ gb, float *__restrict__ gc, "
-          "const int *__restrict__ ia, const int *__restrict__ ib, const int *__restrict__ ca, const int *__restrict__ cb, "
-          "const int *saved, int batch, int n_tiles, int nc, int n3, int accumulate)\n{\n");
+    if (both)
+        ;
     else if (merged)
         o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_merge_bwd_kernel(const float *__restrict__ a, const float *__restrict__ b, "
           "const float *__restrict__ c, const float *__restrict__ g, float *__restrict__ ga, float *__restrict__ gb, float *__restrict__ gc, "
@@ -377,29 +444,43 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
     else
         o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_bwd_kernel(const float *__restrict__ a, const float *__restrict__ b, "
           "const float *__restrict__ g, float *__restrict__ ga, float *__restrict__ gb, int batch, int n_tiles, int accumulate)\n{\n", kThreads);
-    if (!body) o("  __shared__ __align__(16) float lds[%d];\n", off_f + 4);
-    o("  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a scalar: branches on it are uniform)\n");
-    o("  float *sa = lds, *sb = lds + %d, *sg0 = lds + %d, *sg1 = lds + %d;\n", off_b, off_g, off_g + stage);
-    o("  u32 *sm = reinterpret_cast<u32 *>(lds + %d);\n  int *flag = reinterpret_cast<int *>(lds + %d);\n", off_m, off_f);
+    if (!both) {
+        o("  __shared__ __align__(16) float lds[%d];\n", off_f + 4);
+        o("  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a scalar: branches on it are uniform)\n");
+        o("  float *sa = lds, *sb = lds + %d;\n  int *flag = reinterpret_cast<int *>(lds + %d);\n", off_b, off_f);
+    }
+    o("  float *sg0 = lds + %d, *sg1 = lds + %d;\n  u32 *sm = reinterpret_cast<u32 *>(lds + %d);\n", off_g, off_g + stage, off_m);
     if (merged) {
         // where each column of the Apply lands in the result (-1: dropped), and which column of c it meets there (-1: none)
         o("  u32 *su = reinterpret_cast<u32 *>(lds + %d);\n  int *s_oc = reinterpret_cast<int *>(lds + %d), *s_jc = s_oc + %d;\n", off_u, off_x, S);
-        o("  for (int x = tid; x < %d; x += %d) { const int oc = ca[x]; s_oc[x] = oc; s_jc[x] = oc >= 0 ? ib[oc] : -1; }\n", S, kThreads);
     }
-    emit_tile_head(o);
-    o("  __syncthreads();\n  if (tid == 0) *flag = 0;\n");
-    for (int x = 0; x < gh_per_thread; ++x) o("  float4 th%d;\n", x);
-    emit_stage_load(o, "a", "a", na);
-    emit_stage_load(o, "b", "b", nb);
-    emit_gh_load(o, S, 0, std::min(S, kJitGroup), merged, aligned, "  ");
-    if (merged) o("  int was_clamped = 1; if (saved) was_clamped = lane < valid ? saved[s0 + lane] : 0;\n");
-    emit_stage_store(o, "a", "sa", na);
-    emit_stage_store(o, "b", "sb", nb);
-    emit_gh_store(o, 0, std::min(S, kJitGroup), 0, n_groups, "sg0", false, "  ");
-    o("  __syncthreads();\n");
-    emit_row_to_regs(o, "a", "sa", na);
-    emit_row_to_regs(o, "b", "sb", nb);
-    if (merged) {
+    if (!both) {
+        emit_tile_head(o);
+        o("  __syncthreads();\n  if (tid == 0) *flag = 0;\n");
+        emit_stage_load(o, "a", "a", na);
+        emit_stage_load(o, "b", "b", nb);
+    }
+    if (!ahead) {
+        emit_gh_regs(o);
+        emit_gh_load(o, S, 0, std::min(S, kJitGroup), merged, aligned, "  ", false);
+    }
+    if (both) {
+        // (the same in every wavefront)
+        o("  const bool gate = __ballot(lane < valid && sflag[lane] != 0) != 0;\n");
+        if (ahead) o("  const bool gc_here = gc && !gate;\n");
+    } else {
+        if (merged) o("  int was_clamped = 1; if (saved) was_clamped = lane < valid ? saved[s0 + lane] : 0;\n");
+        emit_stage_store(o, "a", "sa", na);
+        emit_stage_store(o, "b", "sb", nb);
+    }
+    emit_gh_store(o, 0, std::min(S, kJitGroup), 0, n_groups, "sg0", false, "  ", ahead);
+    if (!both) {
+        o("  __syncthreads();\n");
+        emit_row_to_regs(o, "a", "sa", na);
+        emit_row_to_regs(o, "b", "sb", nb);
+    }
+    if (both) {
+    } else if (merged) {
         // the forward launch left word: did any clamp act in this sample?
         o("  if (was_clamped && lane < valid) *flag = 1;\n");
     } else {
@@ -410,9 +491,10 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
         o("    const float bound = fminf(ma * tb * %d.0f, mb * ta * %d.0f);\n", max_multiplicity(f, true), max_multiplicity(f, false));
         o("    if (lane < valid && !(bound <= 0.9999f)) *flag = 1; }\n");
     }
-    o("  __syncthreads();\n  const bool gate = *flag != 0;\n");
+    if (!both) o("  __syncthreads();\n  const bool gate = *flag != 0;\n");
     // rare: recompute pre, one group of columns per wavefront, and leave one bit per (sample, column)
     o("  if (gate) {\n");
+    if (merged) o("    for (int x = tid; x < %d; x += %d) { const int oc = ca[x]; s_oc[x] = oc; s_jc[x] = oc >= 0 ? ib[oc] : -1; }\n    __syncthreads();\n", S, kThreads);
     if (merged) o("    const long long sr = s0 + (lane < valid ? lane : 0);\n");
     for (int g = 0; g < n_groups; ++g) {
         const int c0 = g * kJitGroup, c1 = std::min(S, c0 + kJitGroup);
@@ -458,7 +540,7 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
         for (int g = 0; g < n_groups; ++g) {
             const int c0 = g * kJitGroup, c1 = std::min(S, c0 + kJitGroup);
             const char *cur = g & 1 ? "sg1" : "sg0", *nxt = g & 1 ? "sg0" : "sg1";
-            if (g + 1 < n_groups) emit_gh_load(o, S, c1, std::min(S, c1 + kJitGroup), merged, aligned, "    ");
+            if (g + 1 < n_groups) emit_gh_load(o, S, c1, std::min(S, c1 + kJitGroup), merged, aligned, "    ", ahead);
             // 16 columns at a time, fenced for the instruction scheduler: it would otherwise fetch the whole group first and
             // run out of registers
             o("    {\n");
@@ -480,44 +562,47 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
                 o("    }\n    __builtin_amdgcn_sched_barrier(0);\n");
             }
             o("    }\n");
-            if (g + 1 < n_groups) emit_gh_store(o, c1, std::min(S, c1 + kJitGroup), g + 1, n_groups, nxt, true, "    ");
+            if (g + 1 < n_groups) emit_gh_store(o, c1, std::min(S, c1 + kJitGroup), g + 1, n_groups, nxt, true, "    ", ahead);
             o("    __syncthreads();\n");
         }
-        // results: through LDS (one operand's tile at a time, in the first stage), out with flat 16-byte accesses
-        for (int pass = 0; pass < 2; ++pass) {
-            const bool pass_a = pass == 0;
-            const int pn = pass_a ? na : nb, pp = pitch_of(pn);
-            if (pass) o("    __syncthreads();\n");
-            if (pass_a == is_a && (pn & 3))
-                for (int r = r0; r < r1; ++r) o("    sg0[lane * %d + %d] = %s%d;\n", pp, r, acc, r);
-            if (pass_a == is_a && !(pn & 3))
-                for (int r = r0; r < r1; r += 4)
-                    o("    *reinterpret_cast<float4 *>(sg0 + lane * %d + %d) = make_float4(%s%d, %s%d, %s%d, %s%d);\n", pp, r, acc, r, acc, r + 1, acc,
-                      r + 2, acc, r + 3);
-            o("    __syncthreads();\n");
-            o("    if (%s) { float4 *d4 = reinterpret_cast<float4 *>(%s + s0 * %d);\n", pass_a ? "ga" : "gb", pass_a ? "ga" : "gb", pn);
-            if (pn & 3) {
-                o("      const int whole = valid * %d >> 2, rest = valid * %d & 3;\n", pn, pn);
-                o("      for (int q = tid; q < whole; q += %d) { float4 v = reinterpret_cast<const float4 *>(sg0)[q];\n", kThreads);
-                o("        if (accumulate & %d) { const float4 old = d4[q]; v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w; }\n        d4[q] = v; }\n", pass_a ? 1 : 2);
-                o("      if (tid < rest) { float *d1 = reinterpret_cast<float *>(d4 + whole) + tid; const float v = sg0[4 * whole + tid]; *d1 = accumulate & %d ? v + *d1 : v; } }\n",
-                  pass_a ? 1 : 2);
-                continue;
-            }
-            o("      for (int q = tid; q < valid * %d; q += %d) { const int s = q / %d, k = q - s * %d;\n", pn / 4, kThreads, pn / 4, pn / 4);
-            o("        float4 v = *reinterpret_cast<const float4 *>(sg0 + s * %d + 4 * k);\n", pp);
-            o("        if (accumulate & %d) { const float4 old = d4[q]; v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w; }\n", pass_a ? 1 : 2);
-            o("        d4[q] = v; } }\n");
-        }
+        // results: through LDS (a's in the first stage, b's in the second)
+        const char *dst = is_a ? "sg0" : "sg1";
+        const int pp = pitch_of(n);
+        if (n & 3)
+            for (int r = r0; r < r1; ++r) o("    %s[lane * %d + %d] = %s%d;\n", dst, pp, r, acc, r);
+        else
+            for (int r = r0; r < r1; r += 4)
+                o("    *reinterpret_cast<float4 *>(%s + lane * %d + %d) = make_float4(%s%d, %s%d, %s%d, %s%d);\n", dst, pp, r, acc, r, acc, r + 1, acc, r + 2, acc,
+                  r + 3);
         o("  }\n");
+    }
+    // .. out with flat 16-byte accesses
+    o("  __syncthreads();\n");
+    for (int pass = 0; pass < 2; ++pass) {
+        const char *src = pass ? "sg1" : "sg0", *to = pass ? "gb" : "ga";
+        const int pn = pass ? nb : na, pp = pitch_of(pn), bit = pass ? 2 : 1;
+        o("  if (%s) { float4 *d4 = reinterpret_cast<float4 *>(%s + s0 * %d);\n", to, to, pn);
+        if (pn & 3) {
+            o("    const int whole = valid * %d >> 2, rest = valid * %d & 3;\n", pn, pn);
+            o("    for (int q = tid; q < whole; q += %d) { float4 v = reinterpret_cast<const float4 *>(%s)[q];\n", kThreads, src);
+            o("      if (accumulate & %d) { const float4 old = d4[q]; v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w; }\n      d4[q] = v; }\n", bit);
+            o("    if (tid < rest) { float *d1 = reinterpret_cast<float *>(d4 + whole) + tid; const float v = %s[4 * whole + tid]; *d1 = accumulate & %d ? v + *d1 : v; } }\n",
+              src, bit);
+            continue;
+        }
+        o("    for (int q = tid; q < valid * %d; q += %d) { const int s = q / %d, k = q - s * %d;\n", pn / 4, kThreads, pn / 4, pn / 4);
+        o("      float4 v = *reinterpret_cast<const float4 *>(%s + s * %d + 4 * k);\n", src, pp);
+        o("      if (accumulate & %d) { const float4 old = d4[q]; v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w; }\n", bit);
+        o("      d4[q] = v; } }\n");
     }
     if (merged) {
         // gradient of c: column jc of c is column cb[jc] of the result; a symbol of both sides is gated by the union's clamp.
         // 16-byte pieces, four per thread and pass, one 16-byte load where the four columns are neighbours in the result.
-        o("  if (gc) { const int chunks = nc >> 2, total = valid * chunks;\n");
+        // (ahead: where no clamp acted the columns that the Apply has are written)
+        o("  if (gc) { const int from = %s, chunks = (nc >> 2) - from, total = valid * chunks;\n", ahead ? ("gc_here ? " + std::to_string(S / 4) + " : 0").c_str() : "0");
         o("    for (int qb = tid; qb < total; qb += %d) {\n", 4 * kThreads);
         for (int u = 0; u < 4; ++u) {
-            o("      int pq%d = qb + %d; pq%d = pq%d < total ? pq%d : total - 1; const int ps%d = pq%d / chunks, pk%d = pq%d - ps%d * chunks;\n", u, kThreads * u, u, u, u, u,
+            o("      int pq%d = qb + %d; pq%d = pq%d < total ? pq%d : total - 1; const int ps%d = pq%d / chunks, pk%d = pq%d - ps%d * chunks + from;\n", u, kThreads * u, u, u, u, u,
               u, u, u, u);
             o("      const int4 oc%d = reinterpret_cast<const int4 *>(cb)[pk%d];\n", u, u);
         }
@@ -542,26 +627,27 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
     return o.s;
 }
 
-// Apply + Filter + Union forward and backward in one launch: the two bodies above over one LDS array.  The backward
-// body reads the per-sample clamp words the forward body has just written (other threads' words: the workgroup's
-// barrier between the two orders them).
+// Apply + Filter + Union forward and backward in one launch: the operands' rows stay in registers from one pass to the other,
+// and the words that say where a clamp acted in LDS.
 std::string both_source(const dol_fn_table *f, bool aligned)
 {
-    int lf = 0, lb = 0;
-    const std::string fwd = forward_source(f, true, aligned, true, &lf), bwd = backward_source(f, true, aligned, true, &lb);
+    int lb = 0;
+    const std::string bwd = backward_source(f, true, aligned, true, &lb);
+    const int in_floats = kJitTile * (pitch_of(f->na) + pitch_of(f->nb)), floats = std::max({in_floats, kJitTile * pitch_of(f->n_out), lb});
     Src o;
     o.s = kPrologue;
-    o.s += fwd;
-    o.s += bwd;
     o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_merge_fwd_bwd_kernel("
       "const float *__restrict__ a, const float *__restrict__ b, const float *__restrict__ c, float *__restrict__ out, "
       "const float *__restrict__ g, float *__restrict__ ga, float *__restrict__ gb, float *__restrict__ gc, const int *__restrict__ ia, "
       "const int *__restrict__ ib, const int *__restrict__ ca, const int *__restrict__ cb, int *saved, int batch, int n_tiles, int nc, int n3, "
       "int accumulate)\n{\n", kThreads);
-    o("  __shared__ __align__(16) float lds[%d];\n", std::max(lf, lb));
-    o("  damp_table_merge_fwd_body(lds, a, b, c, out, ia, ib, saved, batch, n_tiles, nc, n3);\n");
-    o("  __syncthreads();\n");
-    o("  damp_table_merge_bwd_body(lds, a, b, c, g, ga, gb, gc, ia, ib, ca, cb, saved, batch, n_tiles, nc, n3, accumulate);\n}\n");
+    o("  __shared__ __align__(16) float lds[%d];\n", floats + kJitTile + f->n_out / 4);
+    o("  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a scalar: branches on it are uniform)\n");
+    o("  int *sflag = reinterpret_cast<int *>(lds + %d);\n", floats);
+    if (aligned) o("  u32 *s_keep = reinterpret_cast<u32 *>(lds + %d);\n", floats + kJitTile);
+    emit_tile_head(o);
+    o.s += forward_source(f, true, aligned, true);
+    o.s += bwd;
     return o.s;
 }
 
@@ -614,8 +700,6 @@ unsigned tile_grid(int n_tiles) { return static_cast<unsigned>(n_tiles); }
 // wavefront per SIMD and the tile's loads, arithmetic and stores one after the other.  Such a batch gets a build of its
 // own: up to 128 tiles' worth of samples are cut into tiles of 32 (half of the lanes idle, twice the workgroups), more
 // keep tiles of 64 and give each to eight wavefronts, which share its columns (rows, in the reverse pass) out finer.
-// Config 3 in one launch: 22.7 us at B = 8192 (tiles of 32; 23.2 with eight wavefronts), 27.3 us at B = 16384 (eight
-// wavefronts; 28.9 in tiles of 32, 32.2 in the build for large batches).
 struct JitBuild {
     int rows, waves;        // samples per tile, wavefronts per workgroup
     int variant;            // which of the table's builds
@@ -625,6 +709,18 @@ JitBuild build_for(int32_t batch)
     if (batch > 256 * kJitTile) return {kJitTile, kJitWavesLarge, 0};
     if (batch > 128 * kJitTile) return {kJitTile, 2 * kJitWavesLarge, 1};
     return {kJitTile / 2, kJitWavesLarge, 2};
+}
+
+// Both passes in one launch: eight wavefronts to a tile of 64 samples while every unit has one tile at most (us at B = 8 192 in tiles of 32 /
+// so: 64 x 64 -> 256 24.3 / 17.4, 60 x 60 -> 64 16.3 / 12.7, 48 x 40 -> 128 11.9 / 11.1, 64 x 32 -> 256 15.4 / 14.9, which at 3 200
+// samples takes 13.4 / 14.0).  Above that two tiles to a unit, four wavefronts each, overlap (at 30 000 samples, eight / four: 56 x 56 -> 200
+// 35.6 / 30.4, 60 x 60 -> 64 28.2 / 26.5, 16 x 64 -> 64 17.8 / 15.9), unless the rows of both operands, which stay in registers from pass to
+// pass, leave too few of those to a wavefront that does twice as much (64 x 60 -> 256 43.4 / 46.4, 64 x 64 -> 256 42.7 / 47.6).
+constexpr int kFourWaveSyms = 120;
+JitBuild build_for_both(const dol_fn_table *f, int32_t batch)
+{
+    if (batch > 256 * kJitTile && f->na + f->nb <= kFourWaveSyms) return {kJitTile, kJitWavesLarge, 0};
+    return {kJitTile, 2 * kJitWavesLarge, 1};
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -738,8 +834,8 @@ dol_status launch_damp_table_merge_both(const dol_fn_table *f, const UnionPlan *
 {
     if (merge_small_batch(f, p, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, g, ga, gb, gc, accumulate, st);
     hipFunction_t fn = nullptr;
-    if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBothAligned : kSlotMergeBoth, build_for(batch), &fn)) return s;
-    const JitBuild bd = build_for(batch);
+    const JitBuild bd = build_for_both(f, batch);
+    if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBothAligned : kSlotMergeBoth, bd, &fn)) return s;
     int n_tiles = (batch + bd.rows - 1) / bd.rows, nc = p->nb, n3 = p->n_out;
     const int32_t *ia = p->d_ia.ptr, *ib = p->d_ib.ptr, *ca = p->d_ca.ptr, *cb = p->d_cb.ptr;
     void *args[] = {&a, &b, &c, &out, &g, &ga, &gb, &gc, &ia, &ib, &ca, &cb, &saved, &batch, &n_tiles, &nc, &n3, &accumulate};

@@ -513,6 +513,53 @@ def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, n
         assert n_out == 512 or host(prog.saved).any()
 
 
+@pytest.mark.parametrize("clamps", [False, True])
+@pytest.mark.parametrize("batch,na,nb,n_out,nc,shift", [
+    (3100, 64, 60, 512, 512, 0),        # tiles of 32 samples; widest result
+    (8200, 16, 20, 132, 132, 0),        # eight wavefronts; a last group of one piece
+    (16390, 12, 16, 36, 100, 0),        # four wavefronts; the second Distribution has symbols that the Apply has not
+    (8200, 16, 20, 132, 64, 96),        # symbols of one side only, on both sides
+])
+def test_merged_call_in_one_launch_equals_the_two_calls(dol, batch, na, nb, n_out, nc, shift, clamps):
+    """dol_apply2_filter_union_forward_backward against its two halves, bit for bit: with the result's symbols those of the
+    second Distribution and not, in every build for a batch, where no clamp acts and where some samples' do, gradients written, added to
+    and left out."""
+    ids = W.hashed_table(29, na, nb, n_out)
+    if n_out <= na * nb:
+        ids.reshape(-1)[:n_out] = np.arange(n_out)
+    keep = W.keep_mask(30, n_out)
+    keep[:shift] = np.arange(shift) % 2                    # (the call takes rows of whole fours)
+    x = [(W.uniform01(k, batch * m) / m).astype(np.float32).reshape(batch, m) for k, m in ((1, na), (2, nb), (3, nc))]
+    if clamps:
+        for t in x:
+            t[::37] = np.minimum(t[::37] * t.shape[1], 1.0)
+    f = dol.FnTable.create_dense(ids)
+    a, b, c = dol.Dist(np.arange(na), dev(x[0])), dol.Dist(np.arange(nb), dev(x[1])), dol.Dist(np.arange(nc) + shift, dev(x[2]))
+    made = dol.Dist(f.out_syms, None, batch=batch)
+    n3 = len(dol.filter_union_plan(made, keep, c))
+    g = dev(W.normal(6, batch * n3).astype(np.float32).reshape(batch, n3))
+
+    def run(one, accumulate, with_gc):
+        out = dol.Dist.empty(dol.filter_union_plan(made, keep, c), batch)
+        grads = [torch.full((batch, m), 0.5, device="cuda") for m in (na, nb, nc)]
+        if not with_gc:
+            grads[2] = None
+        saved = torch.full((batch,), -1, dtype=torch.int32, device="cuda")
+        m = dol.ApplyMerge(a, b, f, keep, c, out, saved)
+        if one:
+            dol.apply2_filter_union_forward_backward(m, g, *grads, accumulate=accumulate)
+        else:
+            dol.apply2_filter_union(m)
+            dol.apply2_filter_union_backward(m, g, *grads, accumulate=accumulate)
+        return [out.prob, saved] + [t for t in grads if t is not None]
+
+    for accumulate, with_gc in ((0, True), (7, True), (0, False)):
+        want = run(False, accumulate, with_gc)
+        assert bool(host(want[1]).any()) == clamps
+        for got, w in zip(run(True, accumulate, with_gc), want):
+            np.testing.assert_array_equal(host(got), host(w))
+
+
 @pytest.mark.parametrize("nc", [16000, 40332, 40336, 60000])
 def test_merged_calls_with_a_wide_second_distribution(dol, nc):
     """The second Distribution has far more symbols than the table produces: rows of more than 64 KB, the widest that a
