@@ -1296,7 +1296,7 @@ bool lds_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
 // 16 x 16 -> 32 4.4 / 3.5.
 // Other rows, gathers / generated code, forward and backward: from 2^24 multiply-adds a pass on, 50 x 37 -> 201 B=9 069 12.0 / 5.6
 // and 15.8 / 9.4, 72 552 57 / 22 and 65 / 33; 61 x 5 -> 76 55 008 19 / 10 and 55 / 14; an eighth of 63 x 61 -> 216 35 621 22.9 / 14.5 and
-// 33 / 21; 33 x 47 -> 784 10 818 20 / 9.4 and 25 / 15.7.  The first pass of a direction and a range of batches (of three, build_for)
+// 33 / 21; 33 x 47 -> 784 10 818 20 / 9.4 and 25 / 15.7.  The first pass of a direction and a range of batches (of two, build_for)
 // waits for the compiler, 0.11 to 0.37 s forward, 0.16 to 1.4 backward: at the line the gain of 20 000 to 200 000 passes, as for
 // whole pieces, where it is so at any size.  The line leaves calls of less work to kernels that need no compiler.  Backward a
 // workgroup per sample is the faster a little longer, 63 x 63 -> 1 000 B=4 228 17.6 / 19.7, 8 456 27.8 / 22.9.

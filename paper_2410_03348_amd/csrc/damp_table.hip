@@ -13,7 +13,7 @@
 // start from 0, so the sum is bit for bit the one dol_apply2 defines and the clamp decisions agree.
 //
 // Layout of a launch: a workgroup of four wavefronts owns a tile of 64 samples (batches too small to give every compute
-// unit two such tiles: eight wavefronts, or tiles of 32 samples; see build_for).  The tile's operand rows travel
+// unit two such tiles: eight wavefronts; see build_for).  The tile's operand rows travel
 // HBM -> LDS with flat 16-byte loads (rows of whole 16-byte pieces an odd number of them apart, which keeps a lane's
 // 16-byte reads of its own row off its neighbours' banks; rows of any other length as they lie in memory, read word by word),
 // each lane pulls its sample's rows into registers, the wavefronts split the work (forward: 64 output columns at a time each;
@@ -59,10 +59,10 @@ enum { kSlotFwd = 0, kSlotBwd = 1, kSlotMergeFwd = 2, kSlotMergeBwd = 3, kSlotMe
 
 struct JitState {
     std::mutex mu;
-    hipModule_t mod[3 * kSlots] = {};        // (a table has up to three builds of each kernel, see build_for)
-    hipFunction_t fn[3 * kSlots] = {};
-    dol_status status[3 * kSlots] = {};
-    bool tried[3 * kSlots] = {};
+    hipModule_t mod[2 * kSlots] = {};        // (a table has up to two builds of each kernel, see build_for)
+    hipFunction_t fn[2 * kSlots] = {};
+    dol_status status[2 * kSlots] = {};
+    bool tried[2 * kSlots] = {};
     ~JitState()
     {
         for (hipModule_t m : mod)
@@ -95,8 +95,8 @@ struct Src {
     }
 };
 
-// Wavefronts per workgroup and samples per tile of the source being written.
-thread_local int t_waves = kJitWavesLarge, t_tile_rows = kJitTile;
+// Wavefronts per workgroup of the source being written.
+thread_local int t_waves = kJitWavesLarge;
 #define kJitWaves t_waves
 #define kThreads (kJitTile * t_waves)
 
@@ -173,7 +173,7 @@ void emit_tile_head(Src &o)
     // (one tile per workgroup: inside a loop over tiles the compiler keeps every thread-constant offset of the body alive
     // across it, in registers the body needs)
     o("  {\n  const int tile = blockIdx.x;\n");
-    o("  const long long s0 = (long long)tile * %d;\n  const int valid = batch - s0 < %d ? (int)(batch - s0) : %d;\n", t_tile_rows, t_tile_rows, t_tile_rows);
+    o("  const long long s0 = (long long)tile * %d;\n  const int valid = batch - s0 < %d ? (int)(batch - s0) : %d;\n", kJitTile, kJitTile, kJitTile);
 }
 
 // Loads of one group of the gradient reaching the Apply's columns [c0, c1) into registers (th[]), and their way
@@ -695,33 +695,26 @@ namespace {
 
 unsigned tile_grid(int n_tiles) { return static_cast<unsigned>(n_tiles); }
 
-// How a batch is cut up.  The registers of these kernels allow two wavefronts on a SIMD, and the chip has 256 compute
-// units.  With tiles of 64 samples and four wavefronts to a tile, a batch of up to 256 tiles leaves every unit with one
-// wavefront per SIMD and the tile's loads, arithmetic and stores one after the other.  Such a batch gets a build of its
-// own: up to 128 tiles' worth of samples are cut into tiles of 32 (half of the lanes idle, twice the workgroups), more
-// keep tiles of 64 and give each to eight wavefronts, which share its columns (rows, in the reverse pass) out finer.
+// How many wavefronts a tile gets.  The registers of these kernels allow two wavefronts on a SIMD, and the chip has 256 compute
+// units.  With four wavefronts to a tile, a batch of up to 256 tiles leaves every unit with one wavefront per SIMD and the
+// tile's loads, arithmetic and stores one after the other.  Such a batch gets a build of its own, of eight wavefronts, which
+// share the tile's columns (rows, in the reverse pass) out finer.  (Tiles of 32 samples, half of the lanes idle but twice the workgroups,
+// are slower up to 8 192 samples too: Apply, Filter and Union one by one both ways at 8 192 / 2 500 samples, us in tiles of 32
+// and so: 64 x 64 -> 256 45.8 / 31.4 and 43.4 / 30.9, 60 x 60 -> 64 40.9 / 29.4 and 36.3 / 26.7, 32 x 40 -> 128 30.6 / 25.2 and 30.4 / 24.7,
+// 16 x 64 -> 400 47.3 / 30.9 and 47.5 / 30.7.)
 struct JitBuild {
-    int rows, waves;        // samples per tile, wavefronts per workgroup
+    int waves;              // wavefronts per workgroup
     int variant;            // which of the table's builds
 };
-JitBuild build_for(int32_t batch)
-{
-    if (batch > 256 * kJitTile) return {kJitTile, kJitWavesLarge, 0};
-    if (batch > 128 * kJitTile) return {kJitTile, 2 * kJitWavesLarge, 1};
-    return {kJitTile / 2, kJitWavesLarge, 2};
-}
+constexpr JitBuild kFourWaves = {kJitWavesLarge, 0}, kEightWaves = {2 * kJitWavesLarge, 1};
+JitBuild build_for(int32_t batch) { return batch > 256 * kJitTile ? kFourWaves : kEightWaves; }
 
-// Both passes in one launch: eight wavefronts to a tile of 64 samples while every unit has one tile at most (us at B = 8 192 in tiles of 32 /
-// so: 64 x 64 -> 256 24.3 / 17.4, 60 x 60 -> 64 16.3 / 12.7, 48 x 40 -> 128 11.9 / 11.1, 64 x 32 -> 256 15.4 / 14.9, which at 3 200
-// samples takes 13.4 / 14.0).  Above that two tiles to a unit, four wavefronts each, overlap (at 30 000 samples, eight / four: 56 x 56 -> 200
-// 35.6 / 30.4, 60 x 60 -> 64 28.2 / 26.5, 16 x 64 -> 64 17.8 / 15.9), unless the rows of both operands, which stay in registers from pass to
+// Both passes in one launch: two tiles to a unit, four wavefronts each, overlap (at 30 000 samples, eight / four: 56 x 56 -> 200 35.6 / 30.4 us,
+// 60 x 60 -> 64 28.2 / 26.5, 16 x 64 -> 64 17.8 / 15.9), unless the rows of both operands, which stay in registers from pass to
 // pass, leave too few of those to a wavefront that does twice as much (64 x 60 -> 256 43.4 / 46.4, 64 x 64 -> 256 42.7 / 47.6).
+// (Tiles of 32 samples at B = 8 192, and eight wavefronts: 64 x 64 -> 256 24.3 / 17.4, 60 x 60 -> 64 16.3 / 12.7, 64 x 32 -> 256 15.4 / 14.9.)
 constexpr int kFourWaveSyms = 120;
-JitBuild build_for_both(const dol_fn_table *f, int32_t batch)
-{
-    if (batch > 256 * kJitTile && f->na + f->nb <= kFourWaveSyms) return {kJitTile, kJitWavesLarge, 0};
-    return {kJitTile, 2 * kJitWavesLarge, 1};
-}
+JitBuild build_for_both(const dol_fn_table *f, int32_t batch) { return f->na + f->nb <= kFourWaveSyms ? build_for(batch) : kEightWaves; }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -746,12 +739,12 @@ static dol_status kernel_of(const dol_fn_table *f, int kind, const JitBuild &bd,
     std::lock_guard<std::mutex> lock(js->mu);
     if (!js->tried[slot]) {
         js->tried[slot] = true;
-        t_tile_rows = bd.rows, t_waves = bd.waves;
+        t_waves = bd.waves;
         const std::string src = kind == kSlotFwd ? forward_source(f, false) : kind == kSlotBwd ? backward_source(f, false) :
                                 kind == kSlotMergeFwd ? forward_source(f, true) : kind == kSlotMergeBwd ? backward_source(f, true) :
                                 kind == kSlotMergeFwdAligned ? forward_source(f, true, true) :
                                 kind == kSlotMergeBwdAligned ? backward_source(f, true, true) : both_source(f, kind == kSlotMergeBothAligned);
-        t_tile_rows = kJitTile, t_waves = kJitWavesLarge;
+        t_waves = kJitWavesLarge;
         js->status[slot] = jit_compile(src, names[kind], &js->mod[slot], &js->fn[slot]);
         if (js->status[slot] != DOL_OK) return js->status[slot];      // with the compiler's message
     } else if (js->status[slot] != DOL_OK) {
@@ -771,7 +764,7 @@ dol_status launch_damp_table_fwd(const dol_fn_table *f, int32_t batch, const flo
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, kSlotFwd, build_for(batch), &fn)) return whole_pieces(f) ? s : DOL_OK;      // (the others have kernels that need no compiler)
     const JitBuild bd = build_for(batch);
-    int n_tiles = (batch + bd.rows - 1) / bd.rows;
+    int n_tiles = (batch + kJitTile - 1) / kJitTile;
     void *args[] = {&a, &b, &out, &batch, &n_tiles};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));
     *done = true;
@@ -790,7 +783,7 @@ dol_status launch_damp_table_bwd(const dol_fn_table *f, int32_t batch, const flo
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, kSlotBwd, build_for(batch), &fn)) return whole_pieces(f) ? s : DOL_OK;
     const JitBuild bd = build_for(batch);
-    int n_tiles = (batch + bd.rows - 1) / bd.rows;
+    int n_tiles = (batch + kJitTile - 1) / kJitTile;
     void *args[] = {&a, &b, &g, &ga, &gb, &batch, &n_tiles, &accumulate};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));
     *done = true;
@@ -806,7 +799,7 @@ dol_status launch_damp_table_merge_fwd(const dol_fn_table *f, const UnionPlan *p
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeFwdAligned : kSlotMergeFwd, build_for(batch), &fn)) return s;
     const JitBuild bd = build_for(batch);
-    int n_tiles = (batch + bd.rows - 1) / bd.rows, nc = p->nb, n3 = p->n_out;
+    int n_tiles = (batch + kJitTile - 1) / kJitTile, nc = p->nb, n3 = p->n_out;
     const int32_t *ia = p->d_ia.ptr, *ib = p->d_ib.ptr;
     void *args[] = {&a, &b, &c, &out, &ia, &ib, &saved, &batch, &n_tiles, &nc, &n3};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));
@@ -821,7 +814,7 @@ dol_status launch_damp_table_merge_bwd(const dol_fn_table *f, const UnionPlan *p
     hipFunction_t fn = nullptr;
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBwdAligned : kSlotMergeBwd, build_for(batch), &fn)) return s;
     const JitBuild bd = build_for(batch);
-    int n_tiles = (batch + bd.rows - 1) / bd.rows, nc = p->nb, n3 = p->n_out;
+    int n_tiles = (batch + kJitTile - 1) / kJitTile, nc = p->nb, n3 = p->n_out;
     const int32_t *ia = p->d_ia.ptr, *ib = p->d_ib.ptr, *ca = p->d_ca.ptr, *cb = p->d_cb.ptr;
     void *args[] = {&a, &b, &c, &g, &ga, &gb, &gc, &ia, &ib, &ca, &cb, &saved, &batch, &n_tiles, &nc, &n3, &accumulate};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));
@@ -836,7 +829,7 @@ dol_status launch_damp_table_merge_both(const dol_fn_table *f, const UnionPlan *
     hipFunction_t fn = nullptr;
     const JitBuild bd = build_for_both(f, batch);
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBothAligned : kSlotMergeBoth, bd, &fn)) return s;
-    int n_tiles = (batch + bd.rows - 1) / bd.rows, nc = p->nb, n3 = p->n_out;
+    int n_tiles = (batch + kJitTile - 1) / kJitTile, nc = p->nb, n3 = p->n_out;
     const int32_t *ia = p->d_ia.ptr, *ib = p->d_ib.ptr, *ca = p->d_ca.ptr, *cb = p->d_cb.ptr;
     void *args[] = {&a, &b, &c, &out, &g, &ga, &gb, &gc, &ia, &ib, &ca, &cb, &saved, &batch, &n_tiles, &nc, &n3, &accumulate};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));

@@ -498,7 +498,7 @@ def test_config3_apply_filter_union_in_one_launch(gp, dol, batch, na, nb, n_out,
 @pytest.mark.parametrize("batch,na,nb,n_out", [(3072, 32, 16, 64), (3073, 32, 16, 64), (7, 12, 20, 36), (3, 64, 64, 512)])
 def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, na, nb, n_out):
     """dol_apply2_filter_union both ways, in two calls and in one, at the batch up to which a sample gets a workgroup and above
-    it (tiles of 32 samples), for the smallest and widest symbol sets: against the oracle, clamps acting in many samples."""
+    it (tiles), for the smallest and widest symbol sets: against the oracle, clamps acting in many samples."""
     w = W.config3(batch=batch, na=na, nb=nb, n_out=n_out, seed=31)
     for key in ("pa", "pb", "p2"):
         w.arrays[key] = np.minimum(w[key] * np.float32(6.0), np.float32(1.0))
@@ -515,7 +515,7 @@ def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, n
 
 @pytest.mark.parametrize("clamps", [False, True])
 @pytest.mark.parametrize("batch,na,nb,n_out,nc,shift", [
-    (3100, 64, 60, 512, 512, 0),        # tiles of 32 samples; widest result
+    (3100, 64, 60, 512, 512, 0),        # the widest result
     (8200, 16, 20, 132, 132, 0),        # eight wavefronts; a last group of one piece
     (16390, 12, 16, 36, 100, 0),        # four wavefronts; the second Distribution has symbols that the Apply has not
     (8200, 16, 20, 132, 64, 96),        # symbols of one side only, on both sides
