@@ -30,7 +30,7 @@
 // epilogues, so the Apply's result never leaves the chip; the forward pass leaves one word per sample saying whether
 // any clamp acted, and the reverse pass re-derives decisions only for tiles that hold such a sample.  The two merged
 // bodies are also emitted one after the other into one kernel (dol_apply2_filter_union_forward_backward): the operands' rows stay
-// in registers and the clamp words in LDS.  Where the result has the third Distribution's symbols in its order (an aligned plan)
+// in registers (see keeps_rows) and the clamp words in LDS.  Where the result has the third Distribution's symbols in its order (an aligned plan)
 // the first pieces of that operand and of the gradient are asked for together with a's and b's, the kept columns are bits in
 // LDS, and where no clamp acted the third gradient leaves from the registers that bring the gradient in.  One tile to a unit,
 // its phases one after the other, bounds it: 64 x 64 -> 256 at B = 16 384 (84 MB) took 27.6 us with the bodies apart, each staging
@@ -244,11 +244,15 @@ void emit_union_load(Src &o, const char *qb, const char *ind)
         o("%s{ int q = %s + %d; q = q < total3 ? q : total3 - 1; y%d = *reinterpret_cast<const float4 *>(reinterpret_cast<const char *>(c + s0 * n3) + 16u * (u32)q); }\n", ind, qb, kThreads * u, u);
 }
 
+// What a source is written for: a kernel of its own, one half of the kernel that runs both passes with the operands' rows kept in
+// registers (both_source has its head), or a device function over an LDS array handed in, of the kernel that runs two such.
+enum class Form { kernel, half, body };
+
 // Forward.  merged: the kept symbols of the result are merged with a third Distribution c in the same launch
 // (out = union(filter(apply2(a, b)), c)); the Apply's own result then lives in LDS only.
-// (both: the first half of the kernel that runs both passes; both_source has its head)
-std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = false, bool both = false)
+std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = false, Form form = Form::kernel, int *lds_floats = nullptr)
 {
+    const bool both = form == Form::half, body = form == Form::body;
     const int na = f->na, nb = f->nb, S = f->n_out;
     const bool ahead = both && aligned;
     const int pa = pitch_of(na), pb = pitch_of(nb);
@@ -257,9 +261,14 @@ std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = fa
     const int in_floats = kJitTile * (pa + pb), out_floats = merged ? kJitTile * po : kJitWaves * kJitTile * po;
     const int stage_floats = std::max(in_floats, out_floats);
     Src o;
-    if (!both) o.s = kPrologue;
+    if (form == Form::kernel) o.s = kPrologue;
+    if (lds_floats) *lds_floats = stage_floats + kJitTile;
     if (both)
         ;
+    else if (body)
+        o("static __device__ __forceinline__ void damp_table_merge_fwd_body(float *lds, const float *__restrict__ a, const float *__restrict__ b, "
+          "const float *__restrict__ c, float *__restrict__ out, const int *__restrict__ ia, const int *__restrict__ ib, int *saved, "
+          "int batch, int n_tiles, int nc, int n3)\n{\n");
     else if (merged)
         o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_merge_fwd_kernel(const float *__restrict__ a, const float *__restrict__ b, "
           "const float *__restrict__ c, float *__restrict__ out, const int *__restrict__ ia, const int *__restrict__ ib, int *__restrict__ saved, "
@@ -268,7 +277,7 @@ std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = fa
         o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_fwd_kernel(const float *__restrict__ a, const float *__restrict__ b, "
           "float *__restrict__ out, int batch, int n_tiles)\n{\n", kThreads);
     if (!both) {
-        o("  __shared__ __align__(16) float lds[%d];\n", stage_floats + (merged ? kJitTile : 0));
+        if (!body) o("  __shared__ __align__(16) float lds[%d];\n", stage_floats + (merged ? kJitTile : 0));
         o("  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a scalar: branches on it are uniform)\n");
         if (merged) o("  int *sflag = reinterpret_cast<int *>(lds + %d);\n", stage_floats);
         emit_tile_head(o);
@@ -414,10 +423,11 @@ int max_multiplicity(const dol_fn_table *f, bool by_b)
     return best;
 }
 
-// (both: the second half of the kernel that runs both passes: the operands' rows are in registers, sflag says which samples a
-// clamp acted in, and of an aligned plan th<x> holds the first group)
-std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = false, bool both = false, int *lds_floats = nullptr)
+// (as a half: the operands' rows are in registers, sflag says which samples a clamp acted in, and of an aligned plan th<x> holds the
+// first group)
+std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = false, Form form = Form::kernel, int *lds_floats = nullptr)
 {
+    const bool both = form == Form::half, body = form == Form::body;
     const bool ahead = both && aligned;
     const int na = f->na, nb = f->nb, S = f->n_out;
     const int pa = pitch_of(na), pb = pitch_of(nb), pg = kJitGroup + 4;
@@ -432,10 +442,15 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
     const int parts = kJitWaves / 2;
     const int ha = std::min(na, std::max(4, (na / parts + 3) & ~3)), hb = std::min(nb, std::max(4, (nb / parts + 3) & ~3));
     Src o;
-    if (!both) o.s = kPrologue;
+    if (form == Form::kernel) o.s = kPrologue;
     if (lds_floats) *lds_floats = off_f + 4;
     if (both)
         ;
+    else if (body)
+        o("static __device__ __forceinline__ void damp_table_merge_bwd_body(float *lds, const float *__restrict__ a, const float *__restrict__ b, "
+          "const float *__restrict__ c, const float *__restrict__ g, float *__restrict__ ga, float *__restrict__ gb, float *__restrict__ gc, "
+          "const int *__restrict__ ia, const int *__restrict__ ib, const int *__restrict__ ca, const int *__restrict__ cb, "
+          "const int *saved, int batch, int n_tiles, int nc, int n3, int accumulate)\n{\n");
     else if (merged)
         o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_merge_bwd_kernel(const float *__restrict__ a, const float *__restrict__ b, "
           "const float *__restrict__ c, const float *__restrict__ g, float *__restrict__ ga, float *__restrict__ gb, float *__restrict__ gc, "
@@ -445,7 +460,7 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
         o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_bwd_kernel(const float *__restrict__ a, const float *__restrict__ b, "
           "const float *__restrict__ g, float *__restrict__ ga, float *__restrict__ gb, int batch, int n_tiles, int accumulate)\n{\n", kThreads);
     if (!both) {
-        o("  __shared__ __align__(16) float lds[%d];\n", off_f + 4);
+        if (!body) o("  __shared__ __align__(16) float lds[%d];\n", off_f + 4);
         o("  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a scalar: branches on it are uniform)\n");
         o("  float *sa = lds, *sb = lds + %d;\n  int *flag = reinterpret_cast<int *>(lds + %d);\n", off_b, off_f);
     }
@@ -627,27 +642,40 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
     return o.s;
 }
 
-// Apply + Filter + Union forward and backward in one launch: the operands' rows stay in registers from one pass to the other,
-// and the words that say where a clamp acted in LDS.
+// Whether the kernel that runs both passes keeps the operands' rows in registers from one to the other, and the clamp words in LDS.  The
+// Union of a plan that is not aligned takes most of a wavefront's registers by itself: there long rows are staged again, by two bodies
+// (64 x 64 -> 256 and 256 symbols, 192 of them the same, kept / so, us at B = 40 000 99.9 / 87.7, at 4 000 27.6 / 26.4).
+constexpr int kKeptSyms = 120;
+bool keeps_rows(const dol_fn_table *f, bool aligned) { return aligned || f->na + f->nb <= kKeptSyms; }
+
+// Apply + Filter + Union forward and backward in one launch.  (As bodies the second reads the clamp words that the first has just written,
+// other threads' words: the workgroup's barrier between the two orders them.)
 std::string both_source(const dol_fn_table *f, bool aligned)
 {
-    int lb = 0;
-    const std::string bwd = backward_source(f, true, aligned, true, &lb);
-    const int in_floats = kJitTile * (pitch_of(f->na) + pitch_of(f->nb)), floats = std::max({in_floats, kJitTile * pitch_of(f->n_out), lb});
+    const bool kept = keeps_rows(f, aligned);
+    const Form form = kept ? Form::half : Form::body;
+    int lf = 0, lb = 0;
+    const std::string fwd = forward_source(f, true, aligned, form, &lf), bwd = backward_source(f, true, aligned, form, &lb);
     Src o;
     o.s = kPrologue;
+    if (!kept) o.s += fwd + bwd;
     o("extern \"C\" __global__ void __launch_bounds__(%d) __attribute__((amdgpu_waves_per_eu(2, 2))) damp_table_merge_fwd_bwd_kernel("
       "const float *__restrict__ a, const float *__restrict__ b, const float *__restrict__ c, float *__restrict__ out, "
       "const float *__restrict__ g, float *__restrict__ ga, float *__restrict__ gb, float *__restrict__ gc, const int *__restrict__ ia, "
       "const int *__restrict__ ib, const int *__restrict__ ca, const int *__restrict__ cb, int *saved, int batch, int n_tiles, int nc, int n3, "
       "int accumulate)\n{\n", kThreads);
-    o("  __shared__ __align__(16) float lds[%d];\n", floats + kJitTile + f->n_out / 4);
+    const int floats = std::max(lf, lb);
+    o("  __shared__ __align__(16) float lds[%d];\n", floats + (kept ? kJitTile + f->n_out / 4 : 0));
+    if (!kept) {
+        o("  damp_table_merge_fwd_body(lds, a, b, c, out, ia, ib, saved, batch, n_tiles, nc, n3);\n  __syncthreads();\n");
+        o("  damp_table_merge_bwd_body(lds, a, b, c, g, ga, gb, gc, ia, ib, ca, cb, saved, batch, n_tiles, nc, n3, accumulate);\n}\n");
+        return o.s;
+    }
     o("  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // (a scalar: branches on it are uniform)\n");
     o("  int *sflag = reinterpret_cast<int *>(lds + %d);\n", floats);
     if (aligned) o("  u32 *s_keep = reinterpret_cast<u32 *>(lds + %d);\n", floats + kJitTile);
     emit_tile_head(o);
-    o.s += forward_source(f, true, aligned, true);
-    o.s += bwd;
+    o.s += fwd + bwd;
     return o.s;
 }
 
@@ -713,8 +741,10 @@ JitBuild build_for(int32_t batch) { return batch > 256 * kJitTile ? kFourWaves :
 // 60 x 60 -> 64 28.2 / 26.5, 16 x 64 -> 64 17.8 / 15.9), unless the rows of both operands, which stay in registers from pass to
 // pass, leave too few of those to a wavefront that does twice as much (64 x 60 -> 256 43.4 / 46.4, 64 x 64 -> 256 42.7 / 47.6).
 // (Tiles of 32 samples at B = 8 192, and eight wavefronts: 64 x 64 -> 256 24.3 / 17.4, 60 x 60 -> 64 16.3 / 12.7, 64 x 32 -> 256 15.4 / 14.9.)
-constexpr int kFourWaveSyms = 120;
-JitBuild build_for_both(const dol_fn_table *f, int32_t batch) { return f->na + f->nb <= kFourWaveSyms ? build_for(batch) : kEightWaves; }
+JitBuild build_for_both(const dol_fn_table *f, bool aligned, int32_t batch)
+{
+    return keeps_rows(f, aligned) && f->na + f->nb > kKeptSyms ? kEightWaves : build_for(batch);
+}
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 
@@ -827,7 +857,7 @@ dol_status launch_damp_table_merge_both(const dol_fn_table *f, const UnionPlan *
 {
     if (merge_small_batch(f, p, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, g, ga, gb, gc, accumulate, st);
     hipFunction_t fn = nullptr;
-    const JitBuild bd = build_for_both(f, batch);
+    const JitBuild bd = build_for_both(f, p->aligned, batch);
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBothAligned : kSlotMergeBoth, bd, &fn)) return s;
     int n_tiles = (batch + kJitTile - 1) / kJitTile, nc = p->nb, n3 = p->n_out;
     const int32_t *ia = p->d_ia.ptr, *ib = p->d_ib.ptr, *ca = p->d_ca.ptr, *cb = p->d_cb.ptr;

@@ -519,6 +519,7 @@ def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, n
     (8200, 16, 20, 132, 132, 0),        # eight wavefronts; a last group of one piece
     (16390, 12, 16, 36, 100, 0),        # four wavefronts; the second Distribution has symbols that the Apply has not
     (8200, 16, 20, 132, 64, 96),        # symbols of one side only, on both sides
+    (16390, 64, 64, 256, 192, 96),      # .. and rows too long to stay in registers
 ])
 def test_merged_call_in_one_launch_equals_the_two_calls(dol, batch, na, nb, n_out, nc, shift, clamps):
     """dol_apply2_filter_union_forward_backward against its two halves, bit for bit: with the result's symbols those of the
