@@ -13,7 +13,7 @@
 // start from 0, so the sum is bit for bit the one dol_apply2 defines and the clamp decisions agree.
 //
 // Layout of a launch: a workgroup of four wavefronts owns a tile of 64 samples (batches too small to give every compute
-// unit two such tiles: eight wavefronts; see build_for).  The tile's operand rows travel
+// unit two such tiles: eight wavefronts, or tiles of 32 samples; see build_for).  The tile's operand rows travel
 // HBM -> LDS with flat 16-byte loads (rows of whole 16-byte pieces an odd number of them apart, which keeps a lane's
 // 16-byte reads of its own row off its neighbours' banks; rows of any other length as they lie in memory, read word by word),
 // each lane pulls its sample's rows into registers, the wavefronts split the work (forward: 64 output columns at a time each;
@@ -59,10 +59,10 @@ enum { kSlotFwd = 0, kSlotBwd = 1, kSlotMergeFwd = 2, kSlotMergeBwd = 3, kSlotMe
 
 struct JitState {
     std::mutex mu;
-    hipModule_t mod[2 * kSlots] = {};        // (a table has up to two builds of each kernel, see build_for)
-    hipFunction_t fn[2 * kSlots] = {};
-    dol_status status[2 * kSlots] = {};
-    bool tried[2 * kSlots] = {};
+    hipModule_t mod[3 * kSlots] = {};        // (a table has up to three builds of each kernel, see build_for)
+    hipFunction_t fn[3 * kSlots] = {};
+    dol_status status[3 * kSlots] = {};
+    bool tried[3 * kSlots] = {};
     ~JitState()
     {
         for (hipModule_t m : mod)
@@ -95,8 +95,8 @@ struct Src {
     }
 };
 
-// Wavefronts per workgroup of the source being written.
-thread_local int t_waves = kJitWavesLarge;
+// Wavefronts per workgroup and samples per tile of the source being written.
+thread_local int t_waves = kJitWavesLarge, t_tile_rows = kJitTile;
 #define kJitWaves t_waves
 #define kThreads (kJitTile * t_waves)
 
@@ -173,7 +173,7 @@ void emit_tile_head(Src &o)
     // (one tile per workgroup: inside a loop over tiles the compiler keeps every thread-constant offset of the body alive
     // across it, in registers the body needs)
     o("  {\n  const int tile = blockIdx.x;\n");
-    o("  const long long s0 = (long long)tile * %d;\n  const int valid = batch - s0 < %d ? (int)(batch - s0) : %d;\n", kJitTile, kJitTile, kJitTile);
+    o("  const long long s0 = (long long)tile * %d;\n  const int valid = batch - s0 < %d ? (int)(batch - s0) : %d;\n", t_tile_rows, t_tile_rows, t_tile_rows);
 }
 
 // Loads of one group of the gradient reaching the Apply's columns [c0, c1) into registers (th[]), and their way
@@ -642,17 +642,25 @@ std::string backward_source(const dol_fn_table *f, bool merged, bool aligned = f
     return o.s;
 }
 
-// Whether the kernel that runs both passes keeps the operands' rows in registers from one to the other, and the clamp words in LDS.  The
-// Union of a plan that is not aligned takes most of a wavefront's registers by itself: there long rows are staged again, by two bodies
-// (64 x 64 -> 256 and 256 symbols, 192 of them the same, kept / so, us at B = 40 000 99.9 / 87.7, at 4 000 27.6 / 26.4).
+// Whether the result's tile leaves room for one workgroup to a unit only.
+bool wide_result(const dol_fn_table *f) { return 4 * kJitTile * pitch_of(f->n_out) > 80 * 1024; }
+
+// Whether the kernel that runs both passes keeps the operands' rows in registers from one to the other, and the clamp words in LDS.
+// Long rows are staged again, by two bodies, where registers are short: beside the Union of a plan that is not aligned, which takes
+// most of a wavefront's by itself (64 x 64 -> 256 and 256 symbols, 192 of them the same, kept / so, us at B = 32 000 41.8 / 40.6, at 6 000
+// 25.7 / 24.1), and in the four wavefronts of a tile, where two tiles share a unit (64 x 64 -> 256 aligned, at 32 000 and 131 072
+// 45.9 / 42.9 and 208 / 170, eight wavefronts and rows kept 48.0 and 185; 64 x 64 -> 64 at 32 000 29.4 / 27.0).
 constexpr int kKeptSyms = 120;
-bool keeps_rows(const dol_fn_table *f, bool aligned) { return aligned || f->na + f->nb <= kKeptSyms; }
+bool keeps_rows(const dol_fn_table *f, bool aligned, int waves)
+{
+    return f->na + f->nb <= kKeptSyms || (aligned && (waves > kJitWavesLarge || wide_result(f)));
+}
 
 // Apply + Filter + Union forward and backward in one launch.  (As bodies the second reads the clamp words that the first has just written,
 // other threads' words: the workgroup's barrier between the two orders them.)
 std::string both_source(const dol_fn_table *f, bool aligned)
 {
-    const bool kept = keeps_rows(f, aligned);
+    const bool kept = keeps_rows(f, aligned, kJitWaves);
     const Form form = kept ? Form::half : Form::body;
     int lf = 0, lb = 0;
     const std::string fwd = forward_source(f, true, aligned, form, &lf), bwd = backward_source(f, true, aligned, form, &lb);
@@ -723,27 +731,54 @@ namespace {
 
 unsigned tile_grid(int n_tiles) { return static_cast<unsigned>(n_tiles); }
 
-// How many wavefronts a tile gets.  The registers of these kernels allow two wavefronts on a SIMD, and the chip has 256 compute
-// units.  With four wavefronts to a tile, a batch of up to 256 tiles leaves every unit with one wavefront per SIMD and the
-// tile's loads, arithmetic and stores one after the other.  Such a batch gets a build of its own, of eight wavefronts, which
-// share the tile's columns (rows, in the reverse pass) out finer.  (Tiles of 32 samples, half of the lanes idle but twice the workgroups,
-// are slower up to 8 192 samples too: Apply, Filter and Union one by one both ways at 8 192 / 2 500 samples, us in tiles of 32
-// and so: 64 x 64 -> 256 45.8 / 31.4 and 43.4 / 30.9, 60 x 60 -> 64 40.9 / 29.4 and 36.3 / 26.7, 32 x 40 -> 128 30.6 / 25.2 and 30.4 / 24.7,
-// 16 x 64 -> 400 47.3 / 30.9 and 47.5 / 30.7.)
+// How a batch is cut up.  The registers of these kernels allow two wavefronts on a SIMD, and the chip has 256 compute
+// units.  With tiles of 64 samples and four wavefronts to a tile, a batch of up to 256 tiles leaves every unit with one
+// wavefront per SIMD and the tile's loads, arithmetic and stores one after the other.  Such a batch gets a build of its
+// own, of eight wavefronts, which share the tile's columns (rows, in the reverse pass) out finer, and one of up to 128 tiles may
+// be cut into tiles of 32 samples instead: half of the lanes idle, but all units at work.
 struct JitBuild {
-    int waves;              // wavefronts per workgroup
+    int rows, waves;        // samples per tile, wavefronts per workgroup
     int variant;            // which of the table's builds
 };
-constexpr JitBuild kFourWaves = {kJitWavesLarge, 0}, kEightWaves = {2 * kJitWavesLarge, 1};
-JitBuild build_for(int32_t batch) { return batch > 256 * kJitTile ? kFourWaves : kEightWaves; }
+constexpr JitBuild kFourWaves = {kJitTile, kJitWavesLarge, 0}, kEightWaves = {kJitTile, 2 * kJitWavesLarge, 1},
+                   kHalfTiles = {kJitTile / 2, kJitWavesLarge, 2};
 
-// Both passes in one launch: two tiles to a unit, four wavefronts each, overlap (at 30 000 samples, eight / four: 56 x 56 -> 200 35.6 / 30.4 us,
-// 60 x 60 -> 64 28.2 / 26.5, 16 x 64 -> 64 17.8 / 15.9), unless the rows of both operands, which stay in registers from pass to
-// pass, leave too few of those to a wavefront that does twice as much (64 x 60 -> 256 43.4 / 46.4, 64 x 64 -> 256 42.7 / 47.6).
-// (Tiles of 32 samples at B = 8 192, and eight wavefronts: 64 x 64 -> 256 24.3 / 17.4, 60 x 60 -> 64 16.3 / 12.7, 64 x 32 -> 256 15.4 / 14.9.)
+// Tiles of 32 samples or eight wavefronts, up to 8 192 samples (us at 6 000, eight / tiles of 32).  By tuples an output symbol has:
+// the more, the longer a wavefront's arithmetic, which eight of them halve.
+//   Apply forward: eight, but for the smallest tables.  32 x 40 -> 128 4.2 / 4.7, 24 x 24 -> 100 3.7 / 4.1, 16 x 64 -> 400 5.5 / 5.8,
+//     64 x 64 -> 64 7.0 / 10.2; 20 x 20 -> 20 3.6 / 3.5, 16 x 16 -> 32 3.5 / 3.3.
+//   Apply backward: each wavefront reads the gradient that its rows need from LDS.  With many tuples to a symbol the arithmetic hides
+//     that, with few most of it is not needed: eight, 64 x 64 -> 256 (16) 9.4 / 10.4, 63 x 61 -> 216 8.8 / 10.4, 60 x 60 -> 64 6.6 / 7.6;
+//     36 x 36 -> 300 (4.3) 7.3 / 7.9, 64 x 32 -> 1 000 13.8 / 15.6.  In between tiles of 32: 32 x 40 -> 128 (10) 6.1 / 5.9,
+//     64 x 32 -> 256 8.3 / 8.0, 32 x 16 -> 64 4.3 / 4.1, 48 x 48 -> 512 (4.5) 12.3 / 10.4.
+//   Apply + Filter + Union, which stages the union's operand and result besides, and moves more bytes to a tuple: forward
+//     36 x 36 -> 300 11.2 / 10.1, 56 x 56 -> 200 (15.7) 10.4 / 9.7, 64 x 64 -> 256 9.7 / 9.5; 40 x 64 -> 64 (40) 8.1 / 9.6,
+//     60 x 60 -> 64 9.4 / 11.6; up to 128 symbols, two of four wavefronts' columns, 32 x 40 -> 128 6.2 / 6.5 where the plan is
+//     aligned, 6.9 / 6.8 where not.  Backward 16 x 64 -> 400 16.8 / 15.4, 56 x 56 -> 200 12.3 / 11.8, 60 x 60 -> 64 8.3 / 8.9.
+JitBuild build_for(const dol_fn_table *f, int kind, int32_t batch)
+{
+    if (batch > 256 * kJitTile) return kFourWaves;
+    if (batch > 128 * kJitTile) return kEightWaves;
+    const int64_t tuples = f->n_tuples, symbols = f->n_out;
+    if (kind == kSlotFwd) return tuples <= 400 ? kHalfTiles : kEightWaves;
+    if (kind == kSlotBwd) return 10 * tuples >= 44 * symbols && tuples <= 12 * symbols ? kHalfTiles : kEightWaves;
+    return tuples >= (kind == kSlotMergeFwdAligned && symbols <= 128 ? 10 : 20) * symbols ? kEightWaves : kHalfTiles;
+}
+
+// Both passes in one launch, us.  Of a plan that is not aligned as above (at 6 000, eight / tiles of 32: 48 x 48 -> 512 38.4 / 33.4,
+// 64 x 64 -> 256 24.1 / 22.7, 32 x 40 -> 128 13.3 / 12.2; 60 x 60 -> 64 15.7 / 18.4).  Of an aligned one eight up to 16 384 samples: what
+// both passes want is on its way at once, and tiles of 32 would ask for half as much (64 x 64 -> 256 20.2 / 27.9, 32 x 40 -> 128 9.8 /
+// 10.0, 24 x 24 -> 100 8.7 / 8.0).  But eight wavefronts have 256 registers each also where LDS has room for one workgroup only
+// and four have 512: with a wide result (48 x 48 -> 512, at 6 000 36.9 / 23.7, and at 16 384, eight / four 42.5 / 32.2) the rows of both
+// operands and the pieces on their way are too much for 256, up to 229 of them spilled; shorter rows are not (16 x 64 -> 400,
+// at 16 384 28.8 / 25.3, where clamps act 60.7 / 71.3).
+constexpr int kShortRows = 88;
 JitBuild build_for_both(const dol_fn_table *f, bool aligned, int32_t batch)
 {
-    return keeps_rows(f, aligned) && f->na + f->nb > kKeptSyms ? kEightWaves : build_for(batch);
+    const JitBuild b = build_for(f, aligned ? kSlotMergeBothAligned : kSlotMergeBoth, batch);
+    if (!aligned || batch > 256 * kJitTile) return b;
+    if (!wide_result(f)) return kEightWaves;
+    return batch <= 128 * kJitTile ? kHalfTiles : f->na + f->nb <= kShortRows ? kEightWaves : kFourWaves;
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -769,12 +804,12 @@ static dol_status kernel_of(const dol_fn_table *f, int kind, const JitBuild &bd,
     std::lock_guard<std::mutex> lock(js->mu);
     if (!js->tried[slot]) {
         js->tried[slot] = true;
-        t_waves = bd.waves;
+        t_tile_rows = bd.rows, t_waves = bd.waves;
         const std::string src = kind == kSlotFwd ? forward_source(f, false) : kind == kSlotBwd ? backward_source(f, false) :
                                 kind == kSlotMergeFwd ? forward_source(f, true) : kind == kSlotMergeBwd ? backward_source(f, true) :
                                 kind == kSlotMergeFwdAligned ? forward_source(f, true, true) :
                                 kind == kSlotMergeBwdAligned ? backward_source(f, true, true) : both_source(f, kind == kSlotMergeBothAligned);
-        t_waves = kJitWavesLarge;
+        t_tile_rows = kJitTile, t_waves = kJitWavesLarge;
         js->status[slot] = jit_compile(src, names[kind], &js->mod[slot], &js->fn[slot]);
         if (js->status[slot] != DOL_OK) return js->status[slot];      // with the compiler's message
     } else if (js->status[slot] != DOL_OK) {
@@ -792,9 +827,9 @@ dol_status launch_damp_table_fwd(const dol_fn_table *f, int32_t batch, const flo
     if (!table_code_ok(f) || batch < 1 || table_small_batch(f, batch, false)) return DOL_OK;
     if (lda != f->na || ldb != f->nb || ldo != f->n_out || !aligned16(a) || !aligned16(b) || !aligned16(out)) return DOL_OK;
     hipFunction_t fn = nullptr;
-    if (dol_status s = kernel_of(f, kSlotFwd, build_for(batch), &fn)) return whole_pieces(f) ? s : DOL_OK;      // (the others have kernels that need no compiler)
-    const JitBuild bd = build_for(batch);
-    int n_tiles = (batch + kJitTile - 1) / kJitTile;
+    const JitBuild bd = build_for(f, kSlotFwd, batch);
+    if (dol_status s = kernel_of(f, kSlotFwd, bd, &fn)) return whole_pieces(f) ? s : DOL_OK;      // (the others have kernels that need no compiler)
+    int n_tiles = (batch + bd.rows - 1) / bd.rows;
     void *args[] = {&a, &b, &out, &batch, &n_tiles};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));
     *done = true;
@@ -811,9 +846,9 @@ dol_status launch_damp_table_bwd(const dol_fn_table *f, int32_t batch, const flo
         !aligned16(gb))
         return DOL_OK;
     hipFunction_t fn = nullptr;
-    if (dol_status s = kernel_of(f, kSlotBwd, build_for(batch), &fn)) return whole_pieces(f) ? s : DOL_OK;
-    const JitBuild bd = build_for(batch);
-    int n_tiles = (batch + kJitTile - 1) / kJitTile;
+    const JitBuild bd = build_for(f, kSlotBwd, batch);
+    if (dol_status s = kernel_of(f, kSlotBwd, bd, &fn)) return whole_pieces(f) ? s : DOL_OK;
+    int n_tiles = (batch + bd.rows - 1) / bd.rows;
     void *args[] = {&a, &b, &g, &ga, &gb, &batch, &n_tiles, &accumulate};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));
     *done = true;
@@ -827,9 +862,10 @@ dol_status launch_damp_table_merge_fwd(const dol_fn_table *f, const UnionPlan *p
 {
     if (merge_small_batch(f, p, batch)) return launch_sample_merge(f, p, batch, a, b, c, out, saved, nullptr, nullptr, nullptr, nullptr, 0, st);
     hipFunction_t fn = nullptr;
-    if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeFwdAligned : kSlotMergeFwd, build_for(batch), &fn)) return s;
-    const JitBuild bd = build_for(batch);
-    int n_tiles = (batch + kJitTile - 1) / kJitTile, nc = p->nb, n3 = p->n_out;
+    const int kind = p->aligned ? kSlotMergeFwdAligned : kSlotMergeFwd;
+    const JitBuild bd = build_for(f, kind, batch);
+    if (dol_status s = kernel_of(f, kind, bd, &fn)) return s;
+    int n_tiles = (batch + bd.rows - 1) / bd.rows, nc = p->nb, n3 = p->n_out;
     const int32_t *ia = p->d_ia.ptr, *ib = p->d_ib.ptr;
     void *args[] = {&a, &b, &c, &out, &ia, &ib, &saved, &batch, &n_tiles, &nc, &n3};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));
@@ -842,9 +878,10 @@ dol_status launch_damp_table_merge_bwd(const dol_fn_table *f, const UnionPlan *p
 {
     if (merge_small_batch(f, p, batch)) return launch_sample_merge(f, p, batch, a, b, c, nullptr, const_cast<int32_t *>(saved), g, ga, gb, gc, accumulate, st);
     hipFunction_t fn = nullptr;
-    if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBwdAligned : kSlotMergeBwd, build_for(batch), &fn)) return s;
-    const JitBuild bd = build_for(batch);
-    int n_tiles = (batch + kJitTile - 1) / kJitTile, nc = p->nb, n3 = p->n_out;
+    const int kind = p->aligned ? kSlotMergeBwdAligned : kSlotMergeBwd;
+    const JitBuild bd = build_for(f, kind, batch);
+    if (dol_status s = kernel_of(f, kind, bd, &fn)) return s;
+    int n_tiles = (batch + bd.rows - 1) / bd.rows, nc = p->nb, n3 = p->n_out;
     const int32_t *ia = p->d_ia.ptr, *ib = p->d_ib.ptr, *ca = p->d_ca.ptr, *cb = p->d_cb.ptr;
     void *args[] = {&a, &b, &c, &g, &ga, &gb, &gc, &ia, &ib, &ca, &cb, &saved, &batch, &n_tiles, &nc, &n3, &accumulate};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));
@@ -859,7 +896,7 @@ dol_status launch_damp_table_merge_both(const dol_fn_table *f, const UnionPlan *
     hipFunction_t fn = nullptr;
     const JitBuild bd = build_for_both(f, p->aligned, batch);
     if (dol_status s = kernel_of(f, p->aligned ? kSlotMergeBothAligned : kSlotMergeBoth, bd, &fn)) return s;
-    int n_tiles = (batch + kJitTile - 1) / kJitTile, nc = p->nb, n3 = p->n_out;
+    int n_tiles = (batch + bd.rows - 1) / bd.rows, nc = p->nb, n3 = p->n_out;
     const int32_t *ia = p->d_ia.ptr, *ib = p->d_ib.ptr, *ca = p->d_ca.ptr, *cb = p->d_cb.ptr;
     void *args[] = {&a, &b, &c, &out, &g, &ga, &gb, &gc, &ia, &ib, &ca, &cb, &saved, &batch, &n_tiles, &nc, &n3, &accumulate};
     DOL_HIP(hipModuleLaunchKernel(fn, tile_grid(n_tiles), 1, 1, kJitTile * bd.waves, 1, 1, 0, st, args, nullptr));

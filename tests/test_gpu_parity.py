@@ -520,11 +520,20 @@ def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, n
     (16390, 12, 16, 36, 100, 0),        # four wavefronts; the second Distribution has symbols that the Apply has not
     (8200, 16, 20, 132, 64, 96),        # symbols of one side only, on both sides
     (16390, 64, 64, 256, 192, 96),      # .. and rows too long to stay in registers
+    (16390, 64, 64, 256, 256, 0),       # .. in four wavefronts of an aligned plan
+    (16390, 56, 56, 200, 200, 0),       # what both passes want is asked for behind the sums
+    (16390, 16, 20, 132, 64, 96),       # four wavefronts, rows kept, symbols of one side only
+    (3100, 16, 20, 132, 64, 96),        # .. in tiles of 32 samples
+    (8199, 64, 64, 256, 192, 96),       # eight wavefronts, rows staged again
+    (3100, 64, 64, 256, 192, 96),       # .. in tiles of 32 samples
+    (3137, 64, 64, 64, 64, 0),          # eight wavefronts either way, many tuples to a symbol
+    (8200, 64, 60, 512, 512, 0),        # the widest result in four wavefronts
+    (8200, 16, 64, 320, 320, 0),        # a wide result in eight
 ])
 def test_merged_call_in_one_launch_equals_the_two_calls(dol, batch, na, nb, n_out, nc, shift, clamps):
     """dol_apply2_filter_union_forward_backward against its two halves, bit for bit: with the result's symbols those of the
     second Distribution and not, in every build for a batch, where no clamp acts and where some samples' do, gradients written, added to
-    and left out."""
+    and left out.  Some samples, at the edges of tiles among them, against the oracle, with a one-signed upstream gradient."""
     ids = W.hashed_table(29, na, nb, n_out)
     if n_out <= na * nb:
         ids.reshape(-1)[:n_out] = np.arange(n_out)
@@ -559,6 +568,17 @@ def test_merged_call_in_one_launch_equals_the_two_calls(dol, batch, na, nb, n_ou
         assert bool(host(want[1]).any()) == clamps
         for got, w in zip(run(True, accumulate, with_gc), want):
             np.testing.assert_array_equal(host(got), host(w))
+    g = g.abs()
+    got = run(True, 0, True)
+    look = np.r_[0, 1, 31:34, 63:66, 37 * 40, batch - 2, batch - 1]
+    tri, (xa, xb, xc), gl = oracle.dense_to_triples(ids), (t[look] for t in x), host(g)[look]
+    syms, made_l = oracle.damp_apply2_fwd(tri, na, nb, xa, xb)
+    kept = oracle.damp_filter_fwd(keep[syms], made_l)
+    _, ia, ib = oracle.union_plan(oracle.filter_plan(syms, keep[syms])[0], np.arange(nc, dtype=np.int32) + shift)
+    g_kept, gc = oracle.damp_union_bwd(ia, ib, kept, xc, gl)
+    ga, gb = oracle.damp_apply2_bwd(tri, na, nb, xa, xb, oracle.damp_filter_bwd(keep[syms], g_kept))
+    for name, i, ref in (("result", 0, oracle.damp_union_fwd(ia, ib, kept, xc)), ("grad a", 2, ga), ("grad b", 3, gb), ("grad c", 4, gc)):
+        assert_close(host(got[i])[look], ref, name)
 
 
 @pytest.mark.parametrize("nc", [16000, 40332, 40336, 60000])
@@ -2401,10 +2421,10 @@ def test_tiles_of_64_samples_at_large_batches(dol, na, nb, n_ids, batch):
 
 
 @pytest.mark.parametrize("na,nb,n_ids,batch", [(63, 61, 255, 8193), (50, 37, 201, 10007), (5, 64, 66, 53000), (64, 6, 64, 45001), (33, 47, 1023, 16390),
-                                               (29, 64, 5, 9101), (50, 40, 129, 17000)])
+                                               (29, 64, 5, 9101), (50, 40, 129, 17000), (63, 61, 330, 5001)])
 def test_generated_tables_of_any_symbol_counts(dol, na, nb, n_ids, batch):
     """The code written for a table whose rows are not whole 16-byte pieces: every remainder of each count, result rows of one
-    to sixteen groups, last tiles of which the words are no whole pieces, both builds (up to 16 384 samples and above), columns
+    to sixteen groups, last tiles of which the words are no whole pieces, every build (up to 8 192 and 16 384 samples and above), columns
     on either side of the clamp, a sample of NaN and one of infinities, accumulation and one-sided calls."""
     tab = W.hashed_table(65, na, nb, n_ids)
     f = dol.FnTable.create_dense(tab)
