@@ -37,7 +37,7 @@ struct Lists {                          // struct ListPlan (internal.h) on the d
 struct SampleFwd {
     int32_t na, nb, S, parts;
     int32_t map_ld, long_weight;        // dense maps
-    int32_t huge;                       // the longest column, if a workgroup sums it (else -1), and its tuples
+    int32_t huge;                       // dense maps: the one column that a workgroup sums (else -1), and its tuples
     uint32_t huge_q0, huge_q1;
     int32_t exact;                      // every column in its tuples' order (lists only)
     uint32_t shared;                    // see xcd_shared
@@ -290,13 +290,13 @@ struct ChainColumns {
     }
 };
 
-// The columns of more than kLaneList tuples but the first `skip`, part `part` of `parts` (the last one gets the longest): put(c, sum)
+// The columns of more than kLaneList tuples (from the `first` on), part `part` of `parts` (the last one gets the longest): put(c, sum)
 // is called by one lane.
 template <typename F>
-__device__ __forceinline__ void long_columns(const SampleFwd &A, int skip, const float *ar, const float *br, int part, float *scratch, F put)
+__device__ __forceinline__ void long_columns(const SampleFwd &A, int first, const float *ar, const float *br, int part, float *scratch, F put)
 {
     const Lists &L = A.lists;
-    for (int l = skip + A.parts - 1 - part; l < L.n_huge; l += A.parts) {
+    for (int l = first + A.parts - 1 - part; l < L.n_huge; l += A.parts) {
         const int c = static_cast<int>(L.longer[l]);
         const float v = long_sum<true>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], scratch);
         if (threadIdx.x == 0) put(c, v);
@@ -327,42 +327,51 @@ __device__ __forceinline__ float entry_of(uint32_t base, uint32_t two)
     return *reinterpret_cast<const lds_float *>(at);
 }
 
-// The longest column of a dense-map table, which the last part's workgroup sums (in a product's table that of 0: as many tuples
+// The one column of a dense-map table that a workgroup sums, the last part's (in a product's table that of 0: as many tuples
 // as the first operand has symbols).  Its words are on their way while the row is copied and while the words before them
-// are used; the wavefronts' shares of the sum wait in LDS until the other columns are done.  (18 506 tuples: the words asked for
-// one step after another at the end held the launch up by 3 to 5 us.)
+// are used; the wavefronts' shares of the sum wait in LDS until the other columns are done.  A step takes four tuples a thread, as in
+// long_sum: of 8 195 and 1 024 threads eight at a time make 16 of 8, and cost as much.  A step of its own for every word asked
+// for at the end / so, us at 256 samples: 6 085 x 10 -> 8 282 11.3 / 9.9, 18 497 x 10 -> 23 410 19.0 / 17.7; at 16 6.0 / 5.5, 6.9 / 7.0.
+// Tables with several such columns share them out over the parts instead (long_columns): one part for the first and the
+// others too took 1.5 times as long, two columns of 8 193 at 16 samples 5.3 / 7.9.
 struct HugeColumn {
-    static constexpr int kAhead = 8;
+    static constexpr int kAhead = 12, kStep = 4;
     uint32_t ij[kAhead], q, q1;
 
-    __device__ __forceinline__ void words(const SampleFwd &A)
+    __device__ __forceinline__ void words(const SampleFwd &A, int of, uint32_t from)
     {
 #pragma unroll
-        for (int u = 0; u < kAhead; ++u) ij[u] = A.col_ij[min(q + u * blockDim.x, q1 - 1)];
+        for (int u = of; u < of + kStep; ++u) ij[u] = A.col_ij[min(from + (u - of) * blockDim.x, q1 - 1)];
     }
     __device__ __forceinline__ void ask(const SampleFwd &A)
     {
         q = A.huge_q0 + threadIdx.x, q1 = A.huge_q1;
-        words(A);
+#pragma unroll
+        for (int of = 0; of < kAhead; of += kStep) words(A, of, q + of * blockDim.x);
     }
     // br: the second operand's tags, in LDS
     __device__ __forceinline__ void run(const SampleFwd &A, const float *ar, const float *br, float *shares)
     {
+        const uint32_t T = blockDim.x;
         float acc = 0.0f, mag = 0.0f, err = 0.0f;
         while (q - threadIdx.x < q1) {                      // (the same for all threads)
-            float x[kAhead], y[kAhead];
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                x[u] = q + u * blockDim.x < q1 ? ar[ij[u] & 0xffffu] : 0.0f;
-                y[u] = q + u * blockDim.x < q1 ? br[ij[u] >> 16] : 0.0f;
-            }
-            q += kAhead * blockDim.x;
-            if (q - threadIdx.x < q1) words(A);
+            for (int of = 0; of < kAhead; of += kStep) {
+                if (q - threadIdx.x >= q1) break;
+                float x[kStep], y[kStep];
 #pragma unroll
-            for (int u = 0; u < kAhead; ++u) {
-                acc = __builtin_fmaf(x[u], y[u], acc);
-                mag = __builtin_fmaf(fabsf(x[u]), fabsf(y[u]), mag);
-                err += fminf(fabsf(x[u] * y[u]), 1.1920929e-7f);
+                for (int u = 0; u < kStep; ++u) {
+                    x[u] = q + u * T < q1 ? ar[ij[of + u] & 0xffffu] : 0.0f;
+                    y[u] = q + u * T < q1 ? br[ij[of + u] >> 16] : 0.0f;
+                }
+                if (q + kAhead * T - threadIdx.x < q1) words(A, of, q + kAhead * T);
+                q += kStep * T;
+#pragma unroll
+                for (int u = 0; u < kStep; ++u) {
+                    acc = __builtin_fmaf(x[u], y[u], acc);
+                    mag = __builtin_fmaf(fabsf(x[u]), fabsf(y[u]), mag);
+                    err += fminf(fabsf(x[u] * y[u]), 1.1920929e-7f);
+                }
             }
         }
         acc = wave_sum(acc), mag = wave_sum(mag), err = wave_sum(err);
@@ -383,13 +392,13 @@ struct HugeColumn {
 // A column's tuples are defined to be added up in the order of i.  FALLING: in every column j falls as i rises (any function that
 // grows with both operands), and one j at a time, the last one first, is that order: 18 497 x 10 -> 23 410, B=256 20.2 us, 19.7 so.
 // Else the terms' magnitudes bound how far the two sums can lie apart, and only a sum within that distance of 1 is taken again
-// in the defining order.  With one instruction to an address and the longest column's words ahead 18.7 us, of which an empty launch
-// takes 3.6, the row's copy 2 and the columns 11 (30 M gathers of 4 bytes and 0.5 MB of map a sample, from L2).  Two samples to a
+// in the defining order.  With one instruction to an address and the longest column's words ahead 17.7 us, of which an empty launch
+// takes 3.6, the row's copy 2 and the columns 11 (60 M gathers of 4 bytes and 0.5 MB of map a sample, from L2).  Two samples to a
 // workgroup, side by side in LDS and a map entry read once for both: 17.8, but nothing gained at 100 samples and below.
-template <int NBP, bool FALLING>
+template <int NBP, bool FALLING, bool HUGE>
 __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
 {
-    __shared__ float shares[48], yl[kByJMax];
+    __shared__ float shares[48], yl[HUGE ? kByJMax : 1];
     __shared__ int some;
     const unsigned id = xcd_shared(blockIdx.x, A.shared);
     const int64_t s = id / static_cast<unsigned>(A.parts);
@@ -399,12 +408,12 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
     const int c0 = min(A.S, part * per), c1 = part == A.parts - 1 ? A.S : min(A.S, c0 + per);
     const float *br = A.b + s * A.ldb;
     float *out = A.out + s * A.ldo;
-    const bool sums_huge = A.huge >= 0 && part == A.parts - 1;
+    const bool sums_huge = HUGE && part == A.parts - 1;
     HugeColumn huge;
     if (sums_huge) huge.ask(A);
     if (threadIdx.x == 0) some = 0;
     copy_row(ar, A.a + s * A.lda, A.na);
-    if (static_cast<int>(threadIdx.x) < A.nb) yl[threadIdx.x] = br[threadIdx.x];
+    if (HUGE && static_cast<int>(threadIdx.x) < A.nb) yl[threadIdx.x] = br[threadIdx.x];
     float y[NBP];
 #pragma unroll
     for (int j = 0; j < NBP; ++j) y[j] = br[j < A.nb ? j : 0];      // (the maps' extra rows are empty)
@@ -460,25 +469,24 @@ __device__ __forceinline__ void byj_fwd(const SampleFwd &A, float *ar)
         const float v = HugeColumn::finish(A, ar, br, shares);
         if (lane == 0) out[A.huge] = fminf(v, 1.0f);
     }
-    if (A.lists.n_huge > 1) __syncthreads();            // (they use the shares' place)
-    long_columns(A, A.huge >= 0 ? 1 : 0, ar, br, part, shares, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
+    long_columns(A, HUGE ? 1 : 0, ar, br, part, shares, [&](int c, float v) { out[c] = fminf(v, 1.0f); });
 }
 
-template <int NBP, bool FALLING>
+template <int NBP, bool FALLING, bool HUGE>
 __global__ void __launch_bounds__(kSmallThreads)
 damp_byj_fwd_kernel(const SampleFwd A)
 {
     extern __shared__ __align__(16) float lds[];
-    byj_fwd<NBP, FALLING>(A, lds);
+    byj_fwd<NBP, FALLING, HUGE>(A, lds);
 }
 
 // (64 registers, for two workgroups of 1 024 threads to a unit)
-template <int NBP, bool FALLING>
+template <int NBP, bool FALLING, bool HUGE>
 __global__ void __launch_bounds__(kSampleThreads, 8)
 damp_byj_fwd_staged_kernel(const SampleFwd A)
 {
     extern __shared__ __align__(16) float lds[];
-    byj_fwd<NBP, FALLING>(A, lds);
+    byj_fwd<NBP, FALLING, HUGE>(A, lds);
 }
 
 // ---------------------------------------------------------------- forward, tuple lists
@@ -1108,6 +1116,13 @@ bool list_bwd_sample_ok(const dol_fn_table *f) { return f->lists_ok && gated_byt
 bool byj_fwd_wide(const dol_fn_table *f) { return f->na >= kStageMinRow; }
 bool byj_bwd_wide(const dol_fn_table *f) { return f->na + f->nb > 1024; }
 
+template <int NBP, bool FALLING>
+static void (*byj_fwd_kernel(bool wide, bool huge))(SampleFwd)
+{
+    if (wide) return huge ? &damp_byj_fwd_staged_kernel<NBP, FALLING, true> : &damp_byj_fwd_staged_kernel<NBP, FALLING, false>;
+    return huge ? &damp_byj_fwd_kernel<NBP, FALLING, true> : &damp_byj_fwd_kernel<NBP, FALLING, false>;
+}
+
 dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb, float *out,
                              int64_t ldo, hipStream_t st, bool *done)
 {
@@ -1124,8 +1139,6 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
     if (byj) {
         A.map = f->byj_src.ptr, A.map_ld = f->byj_src_ld;
         A.long_weight = static_cast<int32_t>(std::min<int64_t>(f->col_lists.huge_words / f->byj_nbp, f->n_out));
-        A.huge = f->col_lists.first_huge;
-        if (A.huge >= 0) A.huge_q0 = f->h_col_ptr[A.huge], A.huge_q1 = f->h_col_ptr[A.huge + 1];
         const size_t lds = sizeof(float) * static_cast<size_t>(f->na + 4);
         A.parts = best_parts(batch, long_parts(f->col_lists, std::min(16, (f->n_out + 4 * kSmallThreads - 1) / (4 * kSmallThreads))), f->na,
                              [&](int p) { return (static_cast<double>(f->n_out + A.long_weight) * f->byj_nbp + 4.0 * f->col_lists.mid_words) / p; },
@@ -1133,10 +1146,14 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
         A.shared = shared_ranges(batch, A.parts, f->na);
         const dim3 grid(static_cast<unsigned>(batch) * A.parts);
         const dim3 block(threads_for(std::max<int64_t>(f->n_out / A.parts + 3, f->na) / 4, byj_fwd_wide(f) ? kSampleThreads : kSmallThreads));
+        // (a column that long_sum would take in one step has nothing to ask for ahead: 785 x 10 -> 1 297 4.9 us, 4.7 without)
+        const int32_t huge_col = f->col_lists.only_huge;
+        A.huge = huge_col >= 0 && f->h_col_ptr[huge_col + 1] - f->h_col_ptr[huge_col] > 4 * block.x ? huge_col : -1;
+        if (A.huge >= 0) A.huge_q0 = f->h_col_ptr[A.huge], A.huge_q1 = f->h_col_ptr[A.huge + 1];
 #define CALL(N)                                                                                                                \
     {                                                                                                                          \
-        const auto kernel = byj_fwd_wide(f) ? (f->byj_falling ? &damp_byj_fwd_staged_kernel<N, true> : &damp_byj_fwd_staged_kernel<N, false>)  \
-                                            : (f->byj_falling ? &damp_byj_fwd_kernel<N, true> : &damp_byj_fwd_kernel<N, false>);               \
+        const bool wide = byj_fwd_wide(f), huge = A.huge >= 0;                                                                 \
+        const auto kernel = f->byj_falling ? byj_fwd_kernel<N, true>(wide, huge) : byj_fwd_kernel<N, false>(wide, huge);       \
         if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kStageMaxBytes));               \
         hipLaunchKernelGGL(kernel, grid, block, lds, st, A);                                                                   \
     }

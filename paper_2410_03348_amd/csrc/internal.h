@@ -100,7 +100,7 @@ constexpr int kMidList = 512;
 struct ListPlan {
     DevArray<uint32_t> order, ptr, words, longer;
     int32_t n_huge = 0, n_wave = 0, n_mid = 0;
-    int32_t first_huge = -1;                    // the first of n_huge
+    int32_t only_huge = -1;                     // the list, where n_huge == 1
     int64_t huge_words = 0, mid_words = 0;      // words of the workgroups' lists; of the other longer ones
     size_t n_words = 0;                 // words laid out for lanes, filling included
 };

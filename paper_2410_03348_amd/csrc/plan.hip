@@ -95,7 +95,8 @@ static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, bool
         (by_workgroup ? huge : l > kMidList ? wave : mid).push_back(static_cast<uint32_t>(x));
     }
     plan->n_huge = static_cast<int32_t>(huge.size()), plan->n_wave = static_cast<int32_t>(wave.size()), plan->n_mid = static_cast<int32_t>(mid.size());
-    if (!huge.empty()) plan->first_huge = static_cast<int32_t>(huge[0]);
+    std::stable_sort(huge.begin(), huge.end(), [&](uint32_t x, uint32_t y) { return ptr[x + 1] - ptr[x] > ptr[y + 1] - ptr[y]; });
+    if (huge.size() == 1) plan->only_huge = static_cast<int32_t>(huge[0]);
     huge.insert(huge.end(), wave.begin(), wave.end());
     huge.insert(huge.end(), mid.begin(), mid.end());
     hipError_t e;

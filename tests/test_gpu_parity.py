@@ -2354,6 +2354,29 @@ def test_dense_maps_in_and_out_of_the_defining_order(dol, na, nb, B, grows):
         np.testing.assert_array_equal(got[:, :-1], np.minimum(pre32[:, :-1], np.float32(1)))
 
 
+@pytest.mark.parametrize("na,nb", [(1200, 8), (2060, 3), (4098, 10), (12300, 16)])
+@pytest.mark.parametrize("n_long", [1, 2, 3])
+@pytest.mark.parametrize("B", [1, 70, 300])
+def test_dense_maps_with_one_and_several_long_columns(dol, na, nb, n_long, B):
+    """The first second-operand symbol maps the first operand to one, two or three symbols only, columns that a workgroup sums, of
+    unequal lengths: one is asked for ahead where it is long enough for that, several are shared out over a sample's parts.
+    Some samples' long columns lie at the clamp.  Tolerance: the bar."""
+    i, j = np.arange(na)[:, None], np.arange(nb)[None, :]
+    table = np.where(j == 0, 10 ** 6 + np.minimum(i * 2 * n_long // (na + na // 2), n_long - 1), i + j).astype(np.int32)
+    a = (W.uniform01(86, B * na) * (2.0 / na)).astype(np.float32).reshape(B, na)
+    b = W.uniform01(87, B * nb).astype(np.float32).reshape(B, nb)
+    b[::3, 0] = 1.6 * n_long
+    look = np.unique(np.r_[0:min(B, 4), B - 1])
+    tri = oracle.dense_to_triples(table)
+    syms, want, pre32, _ = oracle.damp_apply2_fwd(tri, na, nb, a[look], b[look], want_pre=True)
+    f = dol.FnTable.create_dense(table)
+    assert "byj" in f.kernel_at(False, B) or na == 1200
+    out = dol.Dist.empty(f.out_syms, B)
+    dol.apply2(dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b)), f, None, out)
+    assert_close(host(out.prob)[look], want, "forward")
+    np.testing.assert_array_equal(host(out.prob)[look] == 1.0, pre32 >= 1.0)
+
+
 @pytest.mark.parametrize("nb", [4, 16, 40])
 @pytest.mark.parametrize("extra,batch", [(0, 3), (57, 1), (4096, 2), (4097, 300)])
 def test_workgroup_per_sample_kernels(dol, nb, extra, batch):
