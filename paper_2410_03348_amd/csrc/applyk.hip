@@ -654,7 +654,7 @@ static dol_status build_k(int32_t K, const int32_t *n_sym, int64_t n, const int3
                 for (uint32_t q = col_ptr[c]; q < col_ptr[c + 1]; q += 2) pairs.push_back(pack16(tup[q], q + 1 < col_ptr[c + 1] ? tup[q + 1] : none));
                 pair_ptr[c + 1] = static_cast<uint32_t>(pairs.size());
             }
-            DOL_HIP(upload_column_lists(pair_ptr, S, pairs, pack16(none, none), &tb->unary_lists));
+            DOL_HIP(upload_pair_lists(pair_ptr, S, pairs, pack16(none, none), &tb->unary_lists));
         }
     }
     DOL_HIP(hipGetDevice(&tb->device));

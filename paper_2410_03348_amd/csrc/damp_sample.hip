@@ -20,6 +20,7 @@
 #include "wave_util.h"
 
 #include <cmath>
+#include <type_traits>
 
 namespace dol {
 
@@ -172,8 +173,9 @@ __device__ __forceinline__ float long_sum(const float *ar, const float *br, cons
     return acc;
 }
 
-// Columns of up to kMidList tuples, four to a wavefront, 16 lanes each, the same way: put(c, sum) is called by one lane.
-// `first`: this wavefront's first four, `step` wavefronts share them.
+// Columns of up to kMidList words of ListPlan, four to a wavefront, 16 lanes each, the same way: put(c, sum) is called by one lane.
+// A lane keeps four sums, so that a column is 64 partial sums as in a wavefront of its own and has no more roundings (one sum a
+// lane: 1 000 tags 0.50e-7 off, root mean square, 0.43e-7 so).  `first`: this wavefront's first four, `step` wavefronts share them.
 template <typename F>
 __device__ __forceinline__ void mid_columns(const float *ar, const float *br, const uint32_t *__restrict__ col_ptr,
                                             const uint32_t *__restrict__ ij_of, const uint32_t *__restrict__ cols, int n, int first, int step, F put)
@@ -185,7 +187,7 @@ __device__ __forceinline__ void mid_columns(const float *ar, const float *br, co
         const int l = l0 + lane / kLanes;
         const int c = static_cast<int>(cols[min(l, n - 1)]);
         const uint32_t q0 = col_ptr[c], q1 = col_ptr[c + 1];
-        float acc = 0.0f, mag = 0.0f, err = 0.0f;
+        float part[kAhead] = {}, mag = 0.0f, err = 0.0f;
         for (uint32_t q = q0 + me; q < q1; q += kAhead * kLanes) {
             uint32_t ij[kAhead];
             float x[kAhead], y[kAhead];
@@ -198,12 +200,13 @@ __device__ __forceinline__ void mid_columns(const float *ar, const float *br, co
             }
 #pragma unroll
             for (int u = 0; u < kAhead; ++u) {
-                acc = __builtin_fmaf(x[u], y[u], acc);
+                part[u] = __builtin_fmaf(x[u], y[u], part[u]);
                 mag = __builtin_fmaf(fabsf(x[u]), fabsf(y[u]), mag);
                 err += fminf(fabsf(x[u] * y[u]), 1.1920929e-7f);
             }
         }
-        acc = reduce16<AddOp>(acc), mag = reduce16<AddOp>(mag), err = reduce16<AddOp>(err);
+        float acc = reduce16<AddOp>((part[0] + part[1]) + (part[2] + part[3]));
+        mag = reduce16<AddOp>(mag), err = reduce16<AddOp>(err);
         const bool near = order_matters(acc, mag, err, q1 - q0, kLanes) && l < n && me == 0;
         for (uint64_t todo = __ballot(near); todo; todo &= todo - 1) {
             const int from = __builtin_ctzll(todo);
@@ -599,6 +602,10 @@ damp_apply2_fwd_staged_kernel(const SampleFwd A)
 // ones; all parts' wavefronts share the chunks out, each every parts * wavefronts-th, which get shorter by steps.  38 400 -> 8 333 (a seven-symbol formula's value), us,
 // with the first eight symbols of a column in a 16-byte word, the others four at a time out of the column's list and
 // the columns above 64 in a launch of their own: B=16 11.6, 64 19.4, 200 27.4; so 5.9, 8.8, 14.9.  Bound by the row's way into LDS.
+// Every list is added up in its defining order, which the clamp decides by.  BLOCKS: where a chunk has lists of more than 64 symbols the
+// lanes add up blocks of 16 to 24 as well, and below 1 their sum is the result: one after the other, 128 tags end 1.6e-7 off (root
+// mean square), as 64 lanes' shares 0.42e-7, so 0.42e-7.
+constexpr uint32_t kPlainWords = kLaneList / 2;     // (two symbols each)
 template <int C, int N>
 struct Walk {
     uint32_t e[C], w0[C], len[C], t[C][N];
@@ -615,7 +622,7 @@ struct Walk {
     }
 };
 
-template <int C, int N>
+template <int C, int N, bool BLOCKS>
 __global__ void __launch_bounds__(kSampleThreads)
 damp_apply1_fwd_staged_kernel(const SampleFwd A)
 {
@@ -640,19 +647,47 @@ damp_apply1_fwd_staged_kernel(const SampleFwd A)
         uint32_t most = 0;
 #pragma unroll
         for (int c = 0; c < C; ++c) most = max(most, now.len[c]);
-        for (uint32_t w = 0; w < most; w += N) {
-            float v[C][N][2];                               // (a word past a list's end is another's: read, not added)
+        float total[C][4] = {}, block[C] = {};              // (blocks go to the four totals in turn)
+        auto walk = [&](auto blocks) {
+            for (uint32_t w = 0; w < most; w += N) {
+                float v[C][N][2];                           // (a word past a list's end is another's: read, not added)
 #pragma unroll
-            for (int c = 0; c < C; ++c)
+                for (int c = 0; c < C; ++c)
 #pragma unroll
-                for (int u = 0; u < N; ++u) v[c][u][0] = lds[now.t[c][u] & 0xffffu], v[c][u][1] = lds[now.t[c][u] >> 16];
+                    for (int u = 0; u < N; ++u) v[c][u][0] = lds[now.t[c][u] & 0xffffu], v[c][u][1] = lds[now.t[c][u] >> 16];
 #pragma unroll
-            for (int c = 0; c < C; ++c)
-                if (w + N < now.len[c]) read_words(now.t[c], A.lists, now.w0[c] + w + N);
+                for (int c = 0; c < C; ++c)
+                    if (w + N < now.len[c]) read_words(now.t[c], A.lists, now.w0[c] + w + N);
 #pragma unroll
-            for (int c = 0; c < C; ++c)
+                for (int c = 0; c < C; ++c) {
 #pragma unroll
-                for (int u = 0; u < N; ++u) acc[c] = w + u < now.len[c] ? acc[c] + v[c][u][0] + v[c][u][1] : acc[c];
+                    for (int u = 0; u < N; ++u) acc[c] = w + u < now.len[c] ? acc[c] + v[c][u][0] + v[c][u][1] : acc[c];
+                    if constexpr (blocks) {
+                        float pair[N];
+#pragma unroll
+                        for (int u = 0; u < N; ++u) pair[u] = w + u < now.len[c] ? v[c][u][0] + v[c][u][1] : 0.0f;
+#pragma unroll
+                        for (int d = 1; d < N; d *= 2)
+#pragma unroll
+                            for (int u = 0; u + d < N; u += 2 * d) pair[u] += pair[u + d];
+                        block[c] += pair[0];
+                        if (N >= 8 || (w / N) % 4 == 3) {
+                            const float t = total[c][0] + block[c];
+                            total[c][0] = total[c][1], total[c][1] = total[c][2], total[c][2] = total[c][3], total[c][3] = t, block[c] = 0.0f;
+                        }
+                    }
+                }
+            }
+        };
+        if (!BLOCKS || most <= kPlainWords) {
+            walk(std::false_type{});
+        } else {
+            walk(std::true_type{});
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const float sum = ((total[c][0] + block[c]) + total[c][1]) + (total[c][2] + total[c][3]);
+                acc[c] = acc[c] < 1.0f ? fminf(sum, 0x1.fffffep-1f) : acc[c];
+            }
         }
 #pragma unroll
         for (int c = 0; c < C; ++c)
@@ -1187,6 +1222,12 @@ dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *
     return DOL_OK;
 }
 
+template <int C, int N>
+static void (*apply1_fwd_kernel(const ListPlan &lists))(SampleFwd)
+{
+    return lists.lane_words > static_cast<int32_t>(kPlainWords) ? &damp_apply1_fwd_staged_kernel<C, N, true> : &damp_apply1_fwd_staged_kernel<C, N, false>;
+}
+
 dol_status launch_unary_fwd(int32_t n_in, int32_t S, const ListPlan &lists, const uint32_t *col_ptr, const uint32_t *col_ij, int32_t batch,
                             const float *x, int64_t ldx, float *out, int64_t ldo, hipStream_t st)
 {
@@ -1196,13 +1237,22 @@ dol_status launch_unary_fwd(int32_t n_in, int32_t S, const ListPlan &lists, cons
     A.na = n_in, A.nb = 1, A.S = S, A.a = x, A.lda = ldx, A.out = out, A.ldo = ldo;
     A.col_ptr = col_ptr, A.col_ij = col_ij, A.lists = lists_of(lists);
     const size_t lds = sizeof(float) * static_cast<size_t>((n_in + 4) & ~3);
-    A.parts = best_parts(batch, long_parts(lists, std::min(16, (S + kSampleThreads / 2 - 1) / (kSampleThreads / 2))), n_in,
-                         [&](int p) { return (2.0 * lists.n_words + S + 4.0 * lists.mid_words) / p + 2.0 * lists.huge_words; }, kSampleThreads, lds);
+    // (more parts than their lists fill, for lists that take several lanes most of all, only while each has a unit to itself: one sample
+    // of 24 000 -> 16 24.8 / 10.1 us, 40 400 -> 68 10.3 / 8.1; 12 000 -> 11 995 16 samples in 16 parts 4.0, in 24 4.7)
+    const int halves = (2 * S + kSampleThreads - 1) / kSampleThreads, few = lists.n_mid / 16 + lists.n_wave / 4 + lists.n_huge;
+    const int most = std::max(long_parts(lists, std::min(16, halves)), std::min(std::min(40, kUnits / batch), std::max(halves, few)));
+    A.parts = best_parts(batch, most, n_in, [&](int p) {
+        const double huge = lists.n_huge > 0 ? static_cast<double>((lists.n_huge + p - 1) / p) / lists.n_huge : 0.0;     // one part's share
+        return (2.0 * lists.n_words + S + 4.0 * lists.mid_words) / p + 2.0 * lists.huge_words * huge;
+    }, kSampleThreads, lds);
     A.shared = shared_ranges(batch, A.parts, n_in);
     const unsigned threads = list_threads(lists, S, n_in, batch * static_cast<int64_t>(A.parts), lds, 512);
-    // (us, two chunks and four pairs a step / one and sixteen: 20 000 -> 4 128, most columns of hundreds of symbols, B=200 14.4 / 13.0,
-    // 38 400 -> 8 333 16-19 / 14.9; 38 400 -> 21 636 B=200 17.7 / 27.6, a permutation of 9 000 B=600 17.4 / 25.1)
-    const auto kernel = lists.n_words < 2 * static_cast<size_t>(S) ? &damp_apply1_fwd_staged_kernel<2, 2> : &damp_apply1_fwd_staged_kernel<1, 8>;
+    // (us, two chunks of two words a step, one of three, one of eight: a permutation of 38 400, one word to a list, B=200 26.1, 32.1, 42.0;
+    // 38 400 -> 7 679, three words to every list, B=16 5.0, 4.6, 5.0, B=600 33.0, 32.2, 39.3; -> 4 267, five, B=600 28.4, 30.0, 30.1,
+    // B=16 5.1, 4.7, 4.9; -> 2 743, seven, B=600 27.6, 28.9, 25.7; -> 8 333, one to 47 words and three on average, B=200 20.6, 17.1, 14.9)
+    const int64_t words = static_cast<int64_t>(lists.n_words), n = S;
+    const auto kernel = lists.lane_words < 6 ? (2 * words < 5 * n ? apply1_fwd_kernel<2, 2>(lists) : apply1_fwd_kernel<1, 3>(lists))
+                                             : words < 2 * n ? apply1_fwd_kernel<2, 2>(lists) : apply1_fwd_kernel<1, 8>(lists);
     if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kStageMaxBytes + 16));
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(batch) * A.parts), dim3(threads), lds, st, A);
     DOL_HIP(hipGetLastError());

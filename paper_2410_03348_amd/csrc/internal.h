@@ -94,7 +94,7 @@ struct JitDeleter {
 // kListElsewhere set for the longer ones, which are named by `longer`: first those that a workgroup sums, then those that a
 // wavefront sums (columns only), then those of up to kMidList words, which 16 lanes sum.  A row of more than that takes a
 // workgroup.  A column takes one only if it has more than a sixteenth of all such columns' words, and would keep one wavefront
-// of the workgroup's sixteen busy after the others have ended.
+// of the workgroup's sixteen busy after the others have ended (unary functions: pairs_by_workgroup, plan.hip).  The longest come first.
 constexpr int kLaneList = 64;
 constexpr int kMidList = 512;
 struct ListPlan {
@@ -103,6 +103,7 @@ struct ListPlan {
     int32_t only_huge = -1;                     // the list, where n_huge == 1
     int64_t huge_words = 0, mid_words = 0;      // words of the workgroups' lists; of the other longer ones
     size_t n_words = 0;                 // words laid out for lanes, filling included
+    int32_t lane_words = 0;             // the most that a lane has
 };
 
 // The columns of a table by length, for the DTKP kernels (dtkp_columns.h).
@@ -338,8 +339,8 @@ bool byj_bwd_staged(const dol_fn_table *f);
 dol_status launch_sample_fwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb, float *out,
                              int64_t ldo, hipStream_t st, bool *done);
 // Unary Apply over rows of n_in tags (unary_rows_ok) to S columns: col_ij = the symbols of column c in ascending order at col_ptr[c] ..
-// col_ptr[c + 1], lists = the same two to a word (upload_column_lists; filling: n_in).
-hipError_t upload_column_lists(const std::vector<uint32_t> &ptr, int32_t n, const std::vector<uint32_t> &ij, uint32_t filling, ListPlan *plan);
+// col_ptr[c + 1], lists = the same two to a word (upload_pair_lists; filling: n_in).
+hipError_t upload_pair_lists(const std::vector<uint32_t> &ptr, int32_t n, const std::vector<uint32_t> &pairs, uint32_t filling, ListPlan *plan);
 inline bool unary_rows_ok(int32_t n_in) { return n_in >= kStageMinRow && sizeof(float) * n_in <= kStageMaxBytes; }
 dol_status launch_unary_fwd(int32_t n_in, int32_t S, const ListPlan &lists, const uint32_t *col_ptr, const uint32_t *col_ij, int32_t batch,
                             const float *x, int64_t ldx, float *out, int64_t ldo, hipStream_t st);

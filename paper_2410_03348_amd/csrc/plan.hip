@@ -65,9 +65,10 @@ struct Tuple {
     int32_t i, j, id;
 };
 
-// struct ListPlan from lists ptr[x] .. ptr[x + 1] of word(q), of columns or of rows.
-template <typename F>
-static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, bool columns, F word, uint32_t filling, ListPlan *plan)
+// struct ListPlan from lists ptr[x] .. ptr[x + 1] of word(q).  by_workgroup(lengths): how many of the lists of more than kMidList
+// words, whose lengths these are, the longest first, a workgroup sums.
+template <typename F, typename G>
+static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, F word, uint32_t filling, G by_workgroup, ListPlan *plan)
 {
     std::vector<uint32_t> order = columns_by_length(ptr, n, kLaneList), start{0}, words, huge, wave, mid;
     auto length = [&](uint32_t x) { const uint32_t l = ptr[x + 1] - ptr[x]; return l > static_cast<uint32_t>(kLaneList) ? 0u : l; };
@@ -79,23 +80,28 @@ static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, bool
         for (int32_t r = r0; r < std::min(n, r0 + 64); ++r)
             for (uint32_t k = 0; k < length(order[r]); ++k) words[at + static_cast<size_t>(k) * 64 + (r - r0)] = word(ptr[order[r]] + k);
         start.push_back(start.back() + most);
+        plan->lane_words = std::max(plan->lane_words, static_cast<int32_t>(most));
     }
     plan->n_words = words.size();
     words.resize(words.size() + 8 * 64, filling);           // up to eight words are read at a time
     for (uint32_t &x : order)
         if (ptr[x + 1] - ptr[x] > static_cast<uint32_t>(kLaneList)) x |= kListElsewhere;
     while (order.size() % 64) order.push_back(kNoList);
-    int64_t above = 0;                      // words of the lists too long for 16 lanes
-    for (int32_t x = 0; x < n; ++x) above += ptr[x + 1] - ptr[x] > static_cast<uint32_t>(kMidList) ? ptr[x + 1] - ptr[x] : 0;
+    auto words_of = [&](uint32_t x) { return static_cast<int64_t>(ptr[x + 1]) - ptr[x]; };
+    std::vector<uint32_t> longest;          // the lists too long for 16 lanes
     for (int32_t x = 0; x < n; ++x) {
-        const int64_t l = static_cast<int64_t>(ptr[x + 1]) - ptr[x];
-        if (l <= kLaneList) continue;
-        const bool by_workgroup = l > kMidList && (!columns || 16 * l > above);
-        (by_workgroup ? plan->huge_words : plan->mid_words) += l;
-        (by_workgroup ? huge : l > kMidList ? wave : mid).push_back(static_cast<uint32_t>(x));
+        if (words_of(x) > kMidList) longest.push_back(static_cast<uint32_t>(x));
+        else if (words_of(x) > kLaneList) mid.push_back(static_cast<uint32_t>(x)), plan->mid_words += words_of(x);
+    }
+    std::stable_sort(longest.begin(), longest.end(), [&](uint32_t x, uint32_t y) { return words_of(x) > words_of(y); });
+    std::vector<int64_t> lengths;
+    for (uint32_t x : longest) lengths.push_back(words_of(x));
+    const size_t whole = by_workgroup(lengths);
+    for (size_t r = 0; r < longest.size(); ++r) {
+        (r < whole ? plan->huge_words : plan->mid_words) += lengths[r];
+        (r < whole ? huge : wave).push_back(longest[r]);
     }
     plan->n_huge = static_cast<int32_t>(huge.size()), plan->n_wave = static_cast<int32_t>(wave.size()), plan->n_mid = static_cast<int32_t>(mid.size());
-    std::stable_sort(huge.begin(), huge.end(), [&](uint32_t x, uint32_t y) { return ptr[x + 1] - ptr[x] > ptr[y + 1] - ptr[y]; });
     if (huge.size() == 1) plan->only_huge = static_cast<int32_t>(huge[0]);
     huge.insert(huge.end(), wave.begin(), wave.end());
     huge.insert(huge.end(), mid.begin(), mid.end());
@@ -105,9 +111,33 @@ static hipError_t upload_lists(const std::vector<uint32_t> &ptr, int32_t n, bool
     return plan->words.upload(words);
 }
 
-hipError_t upload_column_lists(const std::vector<uint32_t> &ptr, int32_t n, const std::vector<uint32_t> &ij, uint32_t filling, ListPlan *plan)
+// (two symbols to a word.  A wavefront takes 0.6 us for 256 symbols, a workgroup for 4 096 and another 0.8 for its barriers, but one
+// list after the other, where sixteen wavefronts sum side by side: 24 000 symbols in 16 columns of 1 500, 64 samples, 25.6 us with a
+// workgroup to each and 12.0 so; one column of 2 043 5.7 with a wavefront and 4.1 so)
+static size_t pairs_by_workgroup(const std::vector<int64_t> &words)
 {
-    return upload_lists(ptr, n, true, [&](uint32_t q) { return ij[q]; }, filling, plan);
+    auto turns = [](int64_t l, int64_t at_once) { return 0.6 * static_cast<double>((2 * l + at_once - 1) / at_once); };
+    double rest = 0.0, whole = 0.0, best_us = 0.0;
+    for (int64_t l : words) rest += turns(l, 256);
+    size_t best = 0;
+    for (size_t m = 0; m <= words.size(); ++m) {
+        const double us = whole + (m < words.size() ? std::max(turns(words[m], 256), rest / 16) : 0.0);
+        if (m == 0 || us < best_us) best = m, best_us = us;
+        if (m < words.size()) whole += 0.8 + turns(words[m], 4096), rest -= turns(words[m], 256);
+    }
+    return best;
+}
+
+hipError_t upload_pair_lists(const std::vector<uint32_t> &ptr, int32_t n, const std::vector<uint32_t> &pairs, uint32_t filling, ListPlan *plan)
+{
+    return upload_lists(ptr, n, [&](uint32_t q) { return pairs[q]; }, filling, pairs_by_workgroup, plan);
+}
+
+static size_t columns_by_workgroup(const std::vector<int64_t> &words)
+{
+    int64_t above = 0;
+    for (int64_t l : words) above += l;
+    return static_cast<size_t>(std::count_if(words.begin(), words.end(), [&](int64_t l) { return 16 * l > above; }));
 }
 
 static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, dol_fn_table **out)
@@ -225,7 +255,7 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
     if (!conv_path_ok(tb.get()))
         if (dol_status s2 = lds_plan_build(tb.get(), col_ptr, col_ij, rowa_ptr, rowa_jc, rowb_ptr, rowb_ic)) return s2;
     if (!conv_path_ok(tb.get()) && na >= 1 && nb >= 1 && S >= 1 && na + nb < 0xFFFF && S < 0xFFFF) {
-        if ((e = upload_lists(col_ptr, S, true, [&](uint32_t q) { return col_ij[q]; }, pack16(na, nb), &tb->col_lists)) != hipSuccess)
+        if ((e = upload_lists(col_ptr, S, [&](uint32_t q) { return col_ij[q]; }, pack16(na, nb), columns_by_workgroup, &tb->col_lists)) != hipSuccess)
             return hip_fail(e, "uploading the function table");
         std::vector<uint32_t> row_ptr(rowa_ptr);
         for (int32_t j = 0; j < nb; ++j) row_ptr.push_back(rowa_ptr[na] + rowb_ptr[j + 1]);
@@ -234,7 +264,7 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
             if (q < n_a) return pack16(na + (rowa_jc[q] & 0xffffu), rowa_jc[q] >> 16);
             return rowb_ic[q - n_a];
         };
-        if ((e = upload_lists(row_ptr, na + nb, false, word, pack16(na + nb, S), &tb->row_lists)) != hipSuccess)
+        if ((e = upload_lists(row_ptr, na + nb, word, pack16(na + nb, S), [](const std::vector<int64_t> &words) { return words.size(); }, &tb->row_lists)) != hipSuccess)
             return hip_fail(e, "uploading the function table");
         tb->lists_ok = true;
     }
