@@ -38,6 +38,7 @@ struct dol_fnk_table {
     dol::DevArray<int32_t> unary_col;
     dol::DevArray<uint16_t> unary_pick;       // the same as a 16-bit number, n_out: rejected (wide operand rows)
     dol::DevArray<uint32_t> unary_ij;         // tup as 32-bit words, and as lists of pairs (wide operand rows)
+    dol::DevArray<float> unary_one;           // 1.0
     dol::ListPlan unary_lists;
     int device = 0;
 };
@@ -170,69 +171,6 @@ damp_apply1_bwd_kernel(Rows R, const float *__restrict__ x, int64_t ldx, const i
     });
 }
 
-// The same for wide result rows (forward: launch_unary_fwd): the gradient row, gated by the clamp, is staged in LDS and every operand
-// symbol picks its column's entry, four neighbours a thread.
-// 38 400 symbols -> 8 333: us, a symbol at a time by a 32-bit column number B=16 5.3, 64 6.9, 200 15.7; so 4.1, 5.4, 9.7 (with two
-// workgroups to a unit 4.5, 7.0, 10.6).
-__global__ void __launch_bounds__(kStageThreads, 8)
-damp_apply1_bwd_staged_kernel(int32_t n_in, int32_t S, int32_t parts, uint32_t shared, const float *__restrict__ x, int64_t ldx,
-                              const uint16_t *__restrict__ col_of, const uint32_t *__restrict__ col_ptr,
-                              const uint16_t *__restrict__ tup, const float *__restrict__ out, int64_t ldo,
-                              const float *__restrict__ g, int64_t ldg, float *__restrict__ gx)
-{
-    extern __shared__ __align__(16) float gh[];             // the gated row and a 0
-    constexpr int kAhead = 2;
-    const unsigned id = xcd_shared(blockIdx.x, shared);
-    const int64_t s = id / static_cast<unsigned>(parts);
-    const int part = static_cast<int>(id - s * parts), per = ((n_in + parts - 1) / parts + 3) & ~3, T = blockDim.x;
-    const int i0 = part * per, i1 = min(n_in, i0 + per);
-    const float *gr = g + s * ldg, *outr = out + s * ldo;
-    ushort4 c[kAhead];
-    auto columns = [&](int i) {
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u)                    // (the map is padded to whole fours)
-            if (i + 4 * T * u < i1) c[u] = *reinterpret_cast<const ushort4 *>(col_of + i + 4 * T * u);
-    };
-    columns(i0 + 4 * static_cast<int>(threadIdx.x));
-    bool at_one = false;
-    for (int k0 = 4 * static_cast<int>(threadIdx.x); k0 < S; k0 += 8 * T) {
-        float4 v[2], o[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int k = k0 + 4 * T * u;
-            if (k < S) v[u] = load4(gr + k, S - k), o[u] = load4(outr + k, S - k);
-        }
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int k = k0 + 4 * T * u;
-            if (k >= S) continue;
-            at_one |= o[u].x >= 1.0f || o[u].y >= 1.0f || o[u].z >= 1.0f || o[u].w >= 1.0f;
-            *reinterpret_cast<float4 *>(gh + k) = v[u];     // (words past the row are 0)
-        }
-    }
-    if (at_one) {                                           // pre == 1 passes, pre > 1 blocks: only pre itself tells
-        const float *row[1] = {x + s * ldx};
-        for (int k0 = 4 * static_cast<int>(threadIdx.x); k0 < S; k0 += 4 * T)
-            for (int k = k0; k < min(S, k0 + 4); ++k)
-                if (outr[k] >= 1.0f && !(column_sum_k<1>(row, tup, col_ptr[k], col_ptr[k + 1]) <= 1.0f)) gh[k] = 0.0f;
-    }
-    if (threadIdx.x == 0 && (S & 3) == 0) gh[S] = 0.0f;
-    __syncthreads();
-    float *dst = gx + s * ldx;
-    for (int i = i0 + 4 * static_cast<int>(threadIdx.x); i < i1; i += 4 * T * kAhead) {
-        float v[kAhead][4];
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u) {
-            if (i + 4 * T * u >= i1) continue;
-            v[u][0] = gh[c[u].x], v[u][1] = gh[c[u].y], v[u][2] = gh[c[u].z], v[u][3] = gh[c[u].w];
-        }
-        columns(i + 4 * T * kAhead);
-#pragma unroll
-        for (int u = 0; u < kAhead; ++u)
-            if (i + 4 * T * u < i1) store4(dst + i + 4 * T * u, v[u], i1 - (i + 4 * T * u));
-    }
-}
-
 // One wavefront per (sample, long column): lanes stride over the tuples and their partial sums meet by shuffles.
 // That is not the order the clamp decision is defined in, so the lanes also add up the terms' magnitudes, which
 // bounds how far the two orders can lie apart (about n roundings of relative size 2^-24 each way); only a sum within
@@ -336,22 +274,19 @@ static dol_status launch_fwd_k(const Rows &R, const KOperands &in, const dol_fnk
 }
 
 template <int K>
-static void launch_bwd_k(const Rows &R, const KOperands &in, const KGrads &gin, const dol_fnk_table *f, const float *out,
+static dol_status launch_bwd_k(const Rows &R, const KOperands &in, const KGrads &gin, const dol_fnk_table *f, const float *out,
                          int64_t ldo, const float *g, int64_t ldg, hipStream_t st)
 {
-    if (K == 1 && staged_unary_bwd(f)) {
-        const int32_t parts = stage_parts(R.batch, f->n_sym[0]);
-        (void)allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply1_bwd_staged_kernel), kStageMaxBytes + 16);
-        const int32_t fours = (std::max((f->n_sym[0] + parts - 1) / parts, f->n_out) + 3) / 4;
-        hipLaunchKernelGGL(damp_apply1_bwd_staged_kernel, dim3(static_cast<unsigned>(R.batch) * parts), dim3(std::min(kStageThreads, (fours + 63) & ~63)),
-                           sizeof(float) * ((f->n_out + 4) & ~3), st, f->n_sym[0], f->n_out, parts, shared_ranges(R.batch, parts, f->n_out), in.p[0], in.ld[0],
-                           f->unary_pick.ptr, f->col_ptr.ptr, f->tup.ptr, out, ldo, g, ldg, gin.p[0]);
-    } else if (K == 1)
+    if (K == 1 && staged_unary_bwd(f))
+        return launch_unary_bwd(f->n_sym[0], f->n_out, f->unary_pick.ptr, f->col_ptr.ptr, f->unary_ij.ptr, f->unary_one.ptr, R.batch, in.p[0], in.ld[0], out,
+                                ldo, g, ldg, gin.p[0], st);
+    if (K == 1)
         hipLaunchKernelGGL(damp_apply1_bwd_kernel, dim3(R.grid), dim3(kThreads), 0, st, R, in.p[0], in.ld[0], f->unary_col.ptr,
                            f->col_ptr.ptr, f->tup.ptr, out, ldo, g, ldg, gin.p[0]);
     else
         hipLaunchKernelGGL(damp_applyk_bwd_kernel<K>, dim3(R.grid), dim3(kThreads), 0, st, R, in, gin, f->col_ptr.ptr,
                            f->tup.ptr, f->tup_col.ptr, f->row_ptr.ptr, f->row_tup.ptr, out, ldo, g, ldg);
+    return DOL_OK;
 }
 
 #define DOL_DISPATCH_ARITY(K, CALL)  \
@@ -645,9 +580,10 @@ static dol_status build_k(int32_t K, const int32_t *n_sym, int64_t n, const int3
             for (int32_t i = 0; i < n_sym[0]; ++i)
                 if (col_of[i] >= 0) pick[i] = static_cast<uint16_t>(col_of[i]);
             DOL_HIP(tb->unary_pick.upload(pick));
+            DOL_HIP(tb->unary_one.upload(std::vector<float>{1.0f}));
         }
+        if (staged_unary_fwd(tb.get()) || staged_unary_bwd(tb.get())) DOL_HIP(tb->unary_ij.upload(std::vector<uint32_t>(tup.begin(), tup.end())));
         if (staged_unary_fwd(tb.get())) {
-            DOL_HIP(tb->unary_ij.upload(std::vector<uint32_t>(tup.begin(), tup.end())));
             std::vector<uint32_t> pair_ptr(S + 1, 0), pairs;
             const uint16_t none = static_cast<uint16_t>(n_sym[0]);
             for (int32_t c = 0; c < S; ++c) {
@@ -794,9 +730,11 @@ dol_status dol_apply_k_backward(int32_t K, const dol_dist *const *in, const dol_
     for (int l = 0; l <= K; ++l) gr.row_base[l] = f->row_base[l];
     const Rows R = rows_of(batch, rows);
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-#define CALL(KK) launch_bwd_k<KK>(R, ops, gr, f, out->prob, out->ld, grad_out, grad_out_ld, st)
+    dol_status launched = DOL_OK;
+#define CALL(KK) launched = launch_bwd_k<KK>(R, ops, gr, f, out->prob, out->ld, grad_out, grad_out_ld, st)
     DOL_DISPATCH_ARITY(K, CALL)
 #undef CALL
+    if (launched != DOL_OK) return launched;
     DOL_HIP(hipGetLastError());
     return DOL_OK;
 }

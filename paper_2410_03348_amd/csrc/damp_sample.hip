@@ -700,6 +700,26 @@ damp_apply1_fwd_staged_kernel(const SampleFwd A)
 
 // ---------------------------------------------------------------- backward
 
+// The long columns at the clamp, n of them, by a wavefront each: close(c), by one lane, where it acted.
+template <typename F>
+__device__ __forceinline__ void late_columns(const SampleBwd &A, const float *ar, const float *br, const float *outr, int n, const int *late, F close)
+{
+    const int lane = threadIdx.x & (kWave - 1), wave = wave_number(), n_waves = blockDim.x / kWave;
+    auto decide = [&](int c) {              // by a whole wavefront
+        const float pre = long_sum<false>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], nullptr);
+        if (!(pre <= 1.0f) && lane == 0) close(c);
+    };
+    if (n <= kLateMax) {
+        for (int l = wave; l < n; l += n_waves) decide(__builtin_amdgcn_readfirstlane(late[l]));
+    } else {                                // more than the list holds: every wavefront looks through its share of the columns
+        for (int c0 = wave; c0 < A.S; c0 += kWave * n_waves) {
+            const int c = c0 + lane * n_waves;
+            const bool mine = c < A.S && outr[c] >= 1.0f && A.col_ptr[c + 1] - A.col_ptr[c] > static_cast<uint32_t>(kLongTableCol);
+            for (uint64_t todo = __ballot(mine); todo; todo &= todo - 1) decide(c0 + __builtin_ctzll(todo) * n_waves);
+        }
+    }
+}
+
 // gh[c] = g[c] where the clamp did not act, else 0, for the whole row, and a 0 behind it.  out < 1: it did not act;
 // out == 1 leaves pre == 1 (passes) and pre > 1 (blocks) apart only by pre itself, taken again: by the thread at hand, long
 // columns by a wavefront each after the others.  (45 000 x 10 -> 300, every column of 1 500 tuples clamped, B=256: 2.8 ms with
@@ -758,22 +778,85 @@ __device__ __forceinline__ bool gated_row(const SampleBwd &A, int64_t s, float *
     }
     __syncthreads();
     const int n = *n_late;
-    auto decide = [&](int c) {              // by a whole wavefront
-        const float pre = long_sum<false>(ar, br, A.col_ij, A.col_ptr[c], A.col_ptr[c + 1], nullptr);
-        if (!(pre <= 1.0f) && lane == 0) close(c);
-    };
-    if (n <= kLateMax) {
-        for (int l = wave; l < n; l += n_waves) decide(__builtin_amdgcn_readfirstlane(late[l]));
-    } else {                                // more than the list holds: every wavefront looks through its share of the columns
-        for (int c0 = wave; c0 < A.S; c0 += kWave * n_waves) {
-            const int c = c0 + lane * n_waves;
-            const bool mine = c < A.S && outr[c] >= 1.0f && A.col_ptr[c + 1] - A.col_ptr[c] > static_cast<uint32_t>(kLongTableCol);
-            for (uint64_t todo = __ballot(mine); todo; todo &= todo - 1) decide(c0 + __builtin_ctzll(todo) * n_waves);
-        }
-    }
+    late_columns(A, ar, br, outr, n, late, close);
     if (!STAGED) return __syncthreads_or(any) != 0;
     if (n) __syncthreads();
     return false;
+}
+
+// Unary Apply over wide rows: every operand symbol picks its column's entry of the gated gradient row, four neighbours a thread.
+// 38 400 symbols -> 8 333: us, a symbol at a time by a 32-bit column number B=16 5.3, 64 6.9, 200 15.7; so 4.1, 5.4, 9.7 (with two
+// workgroups to a unit 4.5, 7.0, 10.6).  Columns at the clamp: one to a thread, neighbouring ones to neighbouring lanes, those of more
+// than 64 symbols to a wavefront.  (By the thread that meets them, four neighbours each, 40 400 -> 242, one to 1 300 symbols to a column,
+// B=16 470 us, one each 157; so 16.  That somebody has to look costs rows of 5 000 0.8 us of 12 at 2 000 samples.)
+__global__ void __launch_bounds__(kSampleThreads, 8)
+damp_apply1_bwd_staged_kernel(const SampleBwd A, int32_t parts, uint32_t shared)
+{
+    extern __shared__ __align__(16) float gh[];             // the gated row and a 0
+    __shared__ int n_late, late[kLateMax];
+    __shared__ bool acted[kSampleThreads / kWave];
+    constexpr int kAhead = 2;
+    const unsigned id = xcd_shared(blockIdx.x, shared);
+    const int64_t s = id / static_cast<unsigned>(parts);
+    const int part = static_cast<int>(id - s * parts), per = ((A.na + parts - 1) / parts + 3) & ~3, T = blockDim.x;
+    const int i0 = part * per, i1 = min(A.na, i0 + per);
+    ushort4 c[kAhead];
+    auto columns = [&](int i) {
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)                    // (the map is padded to whole fours)
+            if (i + 4 * T * u < i1) c[u] = *reinterpret_cast<const ushort4 *>(A.map + i + 4 * T * u);
+    };
+    columns(i0 + 4 * static_cast<int>(threadIdx.x));
+    const float *gr = A.g + s * A.ldg, *outr = A.out + s * A.ldo;
+    bool at_one = false;
+    for (int k0 = 4 * static_cast<int>(threadIdx.x); k0 < A.S; k0 += 8 * T) {
+        float4 v[2], o[2];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int k = k0 + 4 * T * u;
+            if (k < A.S) v[u] = load4(gr + k, A.S - k), o[u] = load4(outr + k, A.S - k);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int k = k0 + 4 * T * u;
+            if (k >= A.S) continue;
+            at_one |= o[u].x >= 1.0f || o[u].y >= 1.0f || o[u].z >= 1.0f || o[u].w >= 1.0f;
+            *reinterpret_cast<float4 *>(gh + k) = v[u];     // (words past the row are 0)
+        }
+    }
+    const int lane = threadIdx.x & (kWave - 1);
+    const bool some = __ballot(at_one) != 0;
+    if (lane == 0) acted[wave_number()] = some;
+    if (threadIdx.x == 0) n_late = 0;
+    if (threadIdx.x == 0 && (A.S & 3) == 0) gh[A.S] = 0.0f;
+    __syncthreads();
+    if (__ballot(lane < T / kWave && acted[lane & 15]) != 0) {      // (the same for all wavefronts)
+        const float *ar = A.a + s * A.lda;
+        for (int k = threadIdx.x; k < A.S; k += T) {        // (neighbouring lanes, neighbouring columns)
+            if (!(outr[k] >= 1.0f)) continue;
+            const uint32_t q0 = A.col_ptr[k], q1 = A.col_ptr[k + 1];
+            if (q1 - q0 > static_cast<uint32_t>(kLongTableCol)) {
+                const int slot = atomicAdd(&n_late, 1);
+                if (slot < kLateMax) late[slot] = k;
+            } else if (!(column_sum(ar, A.b, A.col_ij, q0, q1) <= 1.0f)) gh[k] = 0.0f;
+        }
+        __syncthreads();
+        late_columns(A, ar, A.b, outr, n_late, late, [&](int k) { gh[k] = 0.0f; });
+        __syncthreads();
+    }
+    float *dst = A.ga + s * A.lda;
+    for (int i = i0 + 4 * static_cast<int>(threadIdx.x); i < i1; i += 4 * T * kAhead) {
+        float v[kAhead][4];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+            if (i + 4 * T * u >= i1) continue;
+            v[u][0] = gh[c[u].x], v[u][1] = gh[c[u].y], v[u][2] = gh[c[u].z], v[u][3] = gh[c[u].w];
+        }
+        columns(i + 4 * T * kAhead);
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u)
+            if (i + 4 * T * u < i1) store4(dst + i + 4 * T * u, v[u], i1 - (i + 4 * T * u));
+    }
 }
 
 // Dense maps: a thread owns four rows of a, 64 apart (see byj_fwd), and adds their shares of gb up in registers; the workgroup's
@@ -1255,6 +1338,24 @@ dol_status launch_unary_fwd(int32_t n_in, int32_t S, const ListPlan &lists, cons
                                              : words < 2 * n ? apply1_fwd_kernel<2, 2>(lists) : apply1_fwd_kernel<1, 8>(lists);
     if (lds > 48 * 1024) DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kStageMaxBytes + 16));
     hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(batch) * A.parts), dim3(threads), lds, st, A);
+    DOL_HIP(hipGetLastError());
+    return DOL_OK;
+}
+
+dol_status launch_unary_bwd(int32_t n_in, int32_t S, const uint16_t *pick, const uint32_t *col_ptr, const uint32_t *col_ij, const float *one, int32_t batch,
+                            const float *x, int64_t ldx, const float *out, int64_t ldo, const float *g, int64_t ldg, float *gx, hipStream_t st)
+{
+    for (; batch > kMostGroups; batch -= kMostGroups, x += kMostGroups * ldx, out += kMostGroups * ldo, g += kMostGroups * ldg, gx += kMostGroups * ldx)
+        if (dol_status s = launch_unary_bwd(n_in, S, pick, col_ptr, col_ij, one, kMostGroups, x, ldx, out, ldo, g, ldg, gx, st)) return s;
+    SampleBwd A{};
+    A.na = n_in, A.nb = 1, A.S = S, A.map = pick, A.col_ptr = col_ptr, A.col_ij = col_ij;
+    A.a = x, A.lda = ldx, A.b = one, A.out = out, A.ldo = ldo, A.g = g, A.ldg = ldg, A.ga = gx;
+    // (while each part has a unit to itself: one sample of 38 400 -> 8 333 in parts of 4 096 symbols 3.9 us, of 1 024 3.8; -> 26 3.3 and 3.0)
+    const int32_t parts = std::max(1, std::min((n_in + kSampleThreads - 1) / kSampleThreads, kUnits / batch)), fours = (std::max((n_in + parts - 1) / parts, S) + 3) / 4;
+    const size_t lds = sizeof(float) * static_cast<size_t>((S + 4) & ~3);
+    DOL_HIP(allow_dynamic_lds(reinterpret_cast<const void *>(damp_apply1_bwd_staged_kernel), kStageMaxBytes + 16));
+    hipLaunchKernelGGL(damp_apply1_bwd_staged_kernel, dim3(static_cast<unsigned>(batch) * parts), dim3(threads_for(fours, kSampleThreads)), lds, st, A, parts,
+                       shared_ranges(batch, parts, S));
     DOL_HIP(hipGetLastError());
     return DOL_OK;
 }

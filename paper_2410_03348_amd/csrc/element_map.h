@@ -112,18 +112,4 @@ __device__ __forceinline__ void store4(float *__restrict__ p, const float (&v)[4
         if (k < n && !((skip >> k) & 1u)) p[k] = v[k];
 }
 
-// ---- rows staged whole in LDS: one workgroup of kStageThreads per (sample, part of the output row)
-//
-// A gather from a row of thousands of tags misses the first-level cache on nearly every lane; from LDS it costs a
-// bank conflict or two.  So for wide operand rows a workgroup first copies the sample's row(s) into LDS with
-// coalesced loads and then gathers there.  Small batches are cut into several parts per sample (each stages the row
-// again) so that the chip still fills.
-constexpr int kStageThreads = 1024;
-
-// Parts per sample of a row of n outputs: one workgroup per compute unit, each with at least four outputs a thread.
-static inline int32_t stage_parts(int32_t batch, int32_t n)
-{
-    return std::max(1, std::min((n + 4 * kStageThreads - 1) / (4 * kStageThreads), 256 / batch));
-}
-
 }  // namespace dol

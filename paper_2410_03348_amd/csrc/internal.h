@@ -344,6 +344,9 @@ hipError_t upload_pair_lists(const std::vector<uint32_t> &ptr, int32_t n, const 
 inline bool unary_rows_ok(int32_t n_in) { return n_in >= kStageMinRow && sizeof(float) * n_in <= kStageMaxBytes; }
 dol_status launch_unary_fwd(int32_t n_in, int32_t S, const ListPlan &lists, const uint32_t *col_ptr, const uint32_t *col_ij, int32_t batch,
                             const float *x, int64_t ldx, float *out, int64_t ldo, hipStream_t st);
+// .. and back, to result rows of S (S + 4 tags fit LDS): pick = the column of every symbol, S for none, padded to whole fours; one = 1.0.
+dol_status launch_unary_bwd(int32_t n_in, int32_t S, const uint16_t *pick, const uint32_t *col_ptr, const uint32_t *col_ij, const float *one, int32_t batch,
+                            const float *x, int64_t ldx, const float *out, int64_t ldo, const float *g, int64_t ldg, float *gx, hipStream_t st);
 dol_status launch_sample_bwd(const dol_fn_table *f, int32_t batch, const float *a, int64_t lda, const float *b, int64_t ldb,
                              const float *out, int64_t ldo, const float *g, int64_t ldg, float *ga, float *gb, int32_t accumulate,
                              hipStream_t st, bool *done);
