@@ -203,7 +203,7 @@ __device__ __forceinline__ void rounds_kept(Strip<R> &s, int len, const float (&
 {
 #pragma unroll
     for (int t = 0; t < kept_rounds<R>; ++t) {
-        if (t >= compared(len)) continue;
+        if (t >= compared(len)) break;
         const Ends &from = s.ends[t & 1], &to = s.ends[(t + 1) & 1];
         const float up = masked(lds_at(from.up), s.from_up), down = masked(lds_at(from.down), s.from_down);
 #pragma unroll
@@ -430,9 +430,14 @@ __device__ __forceinline__ void grid_backward(const ItBwdArgs &A, const GridSums
             if (len & 1) put_ends(s.ends[0], gh);
             else put_ends(s.ends[1], gh);
             lds_barrier();
+            // (short segments skip eight rounds at a time: 8 x 8, segments of 4 rounds where 68 fit, 10 rounds 10.9 us one by one both ways, 9.1 so)
 #pragma unroll
-            for (int t = kept_rounds<R> - 1; t >= 0; --t)
-                if (t < compared(len)) reverse_round(s.ends[t & 1], s.ends[(t + 1) & 1], gh, kept[t], [] {});
+            for (int t8 = (kept_rounds<R> - 1) & ~7; t8 >= 0; t8 -= 8) {
+                if (t8 >= compared(len)) continue;
+#pragma unroll
+                for (int t = t8 + 7; t >= t8; --t)
+                    if (t < kept_rounds<R> && t < compared(len)) reverse_round(s.ends[t & 1], s.ends[(t + 1) & 1], gh, kept[t < kept_rounds<R> ? t : 0], [] {});
+            }
             --sg;
         }
     }

@@ -1199,7 +1199,7 @@ def test_fused_iteration_over_a_grid(dol, B, w, h):
 
 
 @pytest.mark.parametrize("w,h,every,rounds", [(32, 32, 33, 34), (32, 32, 33, 66), (32, 32, 32, 71), (32, 32, 1, 3), (8, 8, 68, 69), (8, 8, 67, 140),
-                                              (64, 20, 17, 34), (64, 20, 16, 23)])
+                                              (64, 20, 17, 34), (64, 20, 16, 23), (8, 8, 4, 10), (8, 8, 9, 20), (16, 16, 24, 41)])
 def test_both_sweeps_with_a_segment_in_registers(dol, w, h, every, rounds):
     """dol_iterate_apply2_backward of a small batch, whose last segment but one waits in registers: segments of as many rounds as
     fit there and fewer, of odd and even counts, a last segment of one round, segments before them; strips of one, two and four
