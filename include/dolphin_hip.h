@@ -365,6 +365,9 @@ int32_t dol_iterate_ckpt_count(int32_t rounds, int32_t ckpt_every);
  * calls below; this is the one the library's own measurements favour (App. B, Fig. 9: the recursion with a fixed round
  * count). */
 int32_t dol_iterate_ckpt_every(const dol_fn_table *f, int32_t batch, int32_t rounds);
+/* Name of the HIP kernel that dol_iterate_apply2_backward launches for these sizes, as dol_fn_table_kernel gives those of the
+ * table's own calls; "" where the sweeps are two launches, or f is NULL. */
+const char *dol_iterate_kernel(const dol_fn_table *f, int32_t batch, int32_t rounds, int32_t ckpt_every);
 dol_status dol_iterate_apply2_ckpt(const dol_dist *r0, const dol_dist *e, const dol_fn_table *f, int32_t rounds,
                                    int32_t ckpt_every, dol_dist *out, float *ckpt, void *hip_stream);
 dol_status dol_iterate_backward_ckpt(const dol_dist *r0, const dol_dist *e, const dol_fn_table *f, int32_t rounds,

@@ -567,6 +567,8 @@ _lib.dol_iterate_ckpt_count.argtypes = [C.c_int32, C.c_int32]
 _lib.dol_iterate_ckpt_count.restype = C.c_int32
 _lib.dol_iterate_ckpt_every.argtypes = [C.c_void_p, C.c_int32, C.c_int32]
 _lib.dol_iterate_ckpt_every.restype = C.c_int32
+_lib.dol_iterate_kernel.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32]
+_lib.dol_iterate_kernel.restype = C.c_char_p
 _lib.dol_iterate_apply2_ckpt.argtypes = [C.POINTER(_Dist), C.POINTER(_Dist), C.c_void_p, C.c_int32, C.c_int32,
                                          C.POINTER(_Dist), C.c_void_p, C.c_void_p]
 _lib.dol_iterate_backward_ckpt.argtypes = [C.POINTER(_Dist), C.POINTER(_Dist), C.c_void_p, C.c_int32, C.c_int32,
@@ -580,6 +582,11 @@ def iterate_ckpt_count(rounds: int, ckpt_every: int) -> int:
 def iterate_ckpt_every(f: FnTable, batch: int, rounds: int) -> int:
     """The checkpoint interval the library favours for this table, batch and round count."""
     return int(_lib.dol_iterate_ckpt_every(f._h, batch, rounds))
+
+
+def iterate_kernel(f: FnTable, batch: int, rounds: int, ckpt_every: int) -> str:
+    """The kernel that iterate_apply2_backward launches; "" where its sweeps are two launches."""
+    return _lib.dol_iterate_kernel(f._h, batch, rounds, ckpt_every).decode()
 
 
 def iterate_apply2_ckpt(r0: Dist, e: Dist, f: FnTable, rounds: int, ckpt_every: int, out: Dist,

@@ -74,6 +74,7 @@ size_t grid_bwd_lds(const dol_fn_table *f, int32_t batch, int32_t every);
 bool grid_shares_in_seg(const dol_fn_table *f, int32_t batch, int32_t every);
 dol_status launch_grid_fwd(const dol_fn_table *f, const ItFwdArgs &A, hipStream_t st);
 dol_status launch_grid_bwd(const dol_fn_table *f, const ItBwdArgs &A, size_t lds, hipStream_t st);
+const char *grid_fwd_bwd_kernel(const dol_fn_table *f, int32_t batch, int32_t rounds, int32_t every);      // the name of what this launches:
 dol_status launch_grid_fwd_bwd(const dol_fn_table *f, const ItFwdArgs &F, const ItBwdArgs &B, size_t lds, hipStream_t st);
 
 }  // namespace dol

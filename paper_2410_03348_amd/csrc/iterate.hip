@@ -788,6 +788,14 @@ dol_status dol_iterate_backward_ckpt(const dol_dist *r0, const dol_dist *e, cons
                               grad_e, static_cast<hipStream_t>(hip_stream));
 }
 
+const char *dol_iterate_kernel(const dol_fn_table *f, int32_t batch, int32_t rounds, int32_t ckpt_every)
+{
+    if (!f || ckpt_every < 1) return "";
+    const int32_t every = std::max(1, std::min(ckpt_every, std::max(rounds, 1)));
+    if (grid_sweep(f, batch, every)) return grid_fwd_bwd_kernel(f, batch, rounds, every);
+    return batch > kOneLaunchBatch ? "" : "damp_iterate_fwd_bwd_kernel";
+}
+
 dol_status dol_iterate_apply2_backward(const dol_dist *r0, const dol_dist *e, const dol_fn_table *f, int32_t rounds,
                                        int32_t ckpt_every, dol_dist *out, float *ckpt, const int32_t *target_col,
                                        const float *grad_out, int64_t grad_out_ld, float *grad_r0, float *grad_e,

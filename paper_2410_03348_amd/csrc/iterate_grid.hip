@@ -707,11 +707,18 @@ dol_status launch_grid_bwd(const dol_fn_table *f, const ItBwdArgs &A, size_t lds
     });
 }
 
+template <int R>
+static bool keeps(int32_t batch, int32_t rounds, int32_t every) { return batch <= kUnits && every < rounds && every <= kept_rounds<R>; }
+
+const char *grid_fwd_bwd_kernel(const dol_fn_table *f, int32_t batch, int32_t rounds, int32_t every)
+{
+    return with_rows(f, batch, [&](auto R) { return keeps<R()>(batch, rounds, every) ? "damp_iterate_grid_fwd_bwd_kept_kernel" : "damp_iterate_grid_fwd_bwd_kernel"; });
+}
+
 dol_status launch_grid_fwd_bwd(const dol_fn_table *f, const ItFwdArgs &F, const ItBwdArgs &B, size_t lds, hipStream_t st)
 {
     return with_rows(f, F.batch, [&](auto R) {
-        const bool keep = F.batch <= kUnits && B.every < B.rounds && B.every <= kept_rounds<R()>;
-        const auto kernel = keep ? &damp_iterate_grid_fwd_bwd_kept_kernel<R()> : &damp_iterate_grid_fwd_bwd_kernel<R()>;
+        const auto kernel = keeps<R()>(F.batch, B.rounds, B.every) ? &damp_iterate_grid_fwd_bwd_kept_kernel<R()> : &damp_iterate_grid_fwd_bwd_kernel<R()>;
         return launch(f, F.batch, reinterpret_cast<const void *>(kernel), R(), lds, st, F, B, layout_of(f, R()), slots_of(f), sums_of(f));
     });
 }

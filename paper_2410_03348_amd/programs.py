@@ -450,8 +450,7 @@ class GridReachFused(Program):
             assert ckpt_every, "the one-launch form keeps checkpoints"
             both = lambda: dol.iterate_apply2_backward(self.r0, self.edges, self.table, R, ckpt_every, self.out, self.ckpt,
                                                        None, self.g_out, None, self.g_e)
-            kept = B <= 256 and ckpt_every < R       # a sample to a unit: a segment's tags wait in registers
-            self.launches = [Launch("damp_iterate_grid_fwd_bwd_%skernel" % ("kept_" if kept else ""), both, 4 * B * (3 * n + 3 * (E + 1)), 3 * B * R * n_tup, "fwd+bwd")]
+            self.launches = [Launch(dol.iterate_kernel(self.table, B, R, ckpt_every), both, 4 * B * (3 * n + 3 * (E + 1)), 3 * B * R * n_tup, "fwd+bwd")]
         self.sample_ops = 2 * R * B
         self.min_bytes = 4 * B * (2 * E + 2 * n)
         self.flops = 2 * 3 * B * R * n_tup

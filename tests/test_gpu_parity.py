@@ -1232,6 +1232,16 @@ def test_both_sweeps_with_a_segment_in_registers(dol, w, h, every, rounds):
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("side,rounds,every,batch,want", [
+    (32, 64, 32, 256, "damp_iterate_grid_fwd_bwd_kept_kernel"), (32, 64, 32, 257, "damp_iterate_grid_fwd_bwd_kernel"),
+    (24, 100, 34, 20, "damp_iterate_grid_fwd_bwd_kept_kernel"), (24, 100, 50, 20, "damp_iterate_grid_fwd_bwd_kernel"),      # 34 rounds fit the registers
+    (8, 10, 10, 20, "damp_iterate_grid_fwd_bwd_kernel")])                                                                    # one segment
+def test_programs_name_the_kernel_of_both_sweeps(gp, dol, side, rounds, every, batch, want):
+    """The launch of a reachability program carries the name of the kernel that the library runs for its sizes."""
+    prog = gp.GridReachFused(W.config5(batch=batch, side=side, rounds=rounds, seed=5), ckpt_every=every, one_launch=True)
+    assert [l.kernel for l in prog.launches] == [want] == [dol.iterate_kernel(prog.table, batch, rounds, every)]
+
+
 def test_fused_iteration_with_more_than_1024_symbols(dol):
     """Four symbols of the first operand per thread (the widest build of the fused sweeps)."""
     na, nb, B, rounds = 1100, 40, 3, 4
