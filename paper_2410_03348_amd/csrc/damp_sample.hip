@@ -1459,15 +1459,16 @@ bool lds_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
 }
 
 // Tables with generated code (damp_table.hip): whether another kernel takes the call.  Rows of whole 16-byte pieces (64 x 64 -> 256
-// forward 4.3 us and a workgroup per sample 4.1 to 4.6 up to 512 samples, smaller tables 2.8 and 3.5): forward never, backward,
-// samples / tiles: 64 x 64 -> 256 B=256 4.8 / 12.3, 4 096 11.5 / 12.4; 32 x 40 -> 128 2 048 5.5 / 7.4, 4 096 7.4 / 7.4;
-// 16 x 16 -> 32 4.4 / 3.5.
+// forward 4.3 us and a workgroup per sample 4.1 to 4.6 up to 512 samples, smaller tables 2.8 and 3.5): forward never, backward while
+// a workgroup per sample is estimated below a time of tiles of 64 samples.  With eight wavefronts to a tile, or 32 samples, tiles
+// are faster than that time, and the kernels break even earlier than the line, us, samples / tiles: 64 x 64 -> 256 B=256 4.7 / 8.6,
+// 2 048 8.0 / 8.7, 3 072 10.8 / 8.8, 4 096 13.3 / 8.8; 48 x 48 -> 512 2 048 7.9 / 9.7, 4 096 12.1 / 10.2; 32 x 40 -> 128 1 024 4.6 / 5.2,
+// 2 048 5.6 / 5.3, 4 096 7.9 / 5.4; 16 x 16 -> 32 3.2 / 2.7.  Up to the line a backward call has no compiler to wait for.
 // Other rows, gathers / generated code, forward and backward: from 2^24 multiply-adds a pass on, 50 x 37 -> 201 B=9 069 12.0 / 5.6
 // and 15.8 / 9.4, 72 552 57 / 22 and 65 / 33; 61 x 5 -> 76 55 008 19 / 10 and 55 / 14; an eighth of 63 x 61 -> 216 35 621 22.9 / 14.5 and
-// 33 / 21; 33 x 47 -> 784 10 818 20 / 9.4 and 25 / 15.7.  The first pass of a direction and a range of batches (of two, build_for)
+// 33 / 21; 33 x 47 -> 784 10 818 20 / 9.4 and 25 / 15.7.  The first pass of a direction and a range of batches (of two or three, build_for)
 // waits for the compiler, 0.11 to 0.37 s forward, 0.16 to 1.4 backward: at the line the gain of 20 000 to 200 000 passes, as for
-// whole pieces, where it is so at any size.  The line leaves calls of less work to kernels that need no compiler.  Backward a
-// workgroup per sample is the faster a little longer, 63 x 63 -> 1 000 B=4 228 17.6 / 19.7, 8 456 27.8 / 22.9.
+// whole pieces, where it is so at any size.  The line leaves calls of less work to kernels that need no compiler.
 bool table_small_batch(const dol_fn_table *f, int64_t batch, bool backward)
 {
     const bool whole = whole_pieces(f);
@@ -1484,11 +1485,14 @@ static size_t merge_bytes(const dol_fn_table *f, const UnionPlan *p)
     return sizeof(float) * (static_cast<size_t>((2 * f->na + f->nb + 5) & ~3) + f->n_out + p->nb + f->n_out + 1);
 }
 
-// Apply + Filter + Union both ways in tiles against a workgroup per sample, us: 64 x 64 -> 256 B=256 20.0 / 7.6, 2 048 20.7 /
-// 15.3, 4 096 20.9 / 23.4; 32 x 40 -> 128 B=256 11.8 / 6.1, 3 072 12.3 / 9.9; 4 x 4 -> 4 up to 3 072 the same.  Only tables of
-// which a lane walks every list: their sums are then the tiles' bit for bit.  What does not fit LDS is left to the tiles, which
-// read the second Distribution from memory; where only one workgroup fits a unit its turns end the gain earlier (32 x 40 -> 128
-// and 40 000 symbols: B=2 048 1 017 / 943, 3 072 1 079 / 1 409).
+// Apply + Filter + Union, a workgroup per sample / tiles, us, forward, backward, both in one launch.  64 x 64 -> 256 B=512 4.3 / 8.3, 5.8 / 12.1,
+// 7.9 / 15.9, 2 048 6.5 / 8.5, 8.8 / 12.5, 14.1 / 16.9, 3 072 8.5 / 8.6, 12.9 / 12.7, 19.0 / 17.5, 4 096 10.8 / 9.1, 16.0 / 13.2, 24.4 / 18.0
+// (where the plan is not aligned, 4 096 10.6 / 9.3, 15.9 / 13.6, 24.5 / 22.5); 32 x 40 -> 128 2 048 4.6 / 5.5, 6.0 / 6.7, 7.9 / 8.6, 3 072 5.3 / 5.6,
+// 7.2 / 6.8, 9.5 / 8.8.  So the line of two calls; one call breaks even from 2 048 samples on, the soonest with a wide result (16 x 64 -> 400 1 024
+// 10.5 / 15.7, 2 048 19.0 / 16.7, 3 072 26.0 / 17.3; 48 x 48 -> 512 20.5 / 21.1, 28.4 / 22.0), but up to the line waits for no compiler.
+// Only tables of which a lane walks every list: their sums are then the tiles' bit for bit.  What does not fit LDS is left to the
+// tiles, which read the second Distribution from memory; where only one workgroup fits a unit its turns end the gain earlier
+// (32 x 40 -> 128 and 40 000 symbols: tiles / samples, B=2 048 1 017 / 943, 3 072 1 079 / 1 409).
 bool merge_small_batch(const dol_fn_table *f, const UnionPlan *p, int64_t batch)
 {
     const size_t bytes = merge_bytes(f, p);

@@ -288,7 +288,10 @@ std::string forward_source(const dol_fn_table *f, bool merged, bool aligned = fa
     emit_stage_load(o, "a", "a", na);
     emit_stage_load(o, "b", "b", nb);
     // What both passes want next, c's first pieces and the gradient's first group, is asked for behind the operands, or, where a
-    // wavefront has 64 columns to sum and long rows in its registers, behind the sums.
+    // wavefront has 64 columns to sum and long rows in its registers, behind the sums.  (Four wavefronts, behind the operands / the sums, us
+    // at 40 000 and 131 072 samples: 56 x 56 -> 200 59.0 / 58.0, 140.6 / 136.6, 60 x 60 -> 64 42.3 / 41.1, 94.7 / 92.5, 64 x 56 -> 256 81.0 both,
+    // 182.3 / 177.8; shorter rows go either way, 48 x 48 -> 256 54.2 / 55.8, 128.6 / 131.0, 32 x 32 -> 128 29.5 both, 69.4 / 70.3,
+    // 48 x 44 -> 160 40.3 / 39.9, 93.8 / 89.5, 64 x 32 -> 400 85.8 / 82.7, 228 / 221.)
     constexpr int kEarlySyms = 96;
     auto ask_ahead = [&](bool now) {
         if (!now) return;

@@ -14,9 +14,9 @@
 // the general kernels bit for bit.  Nodes past the grid (the last strips' ends, lanes without a strip) have the tag 1 and a
 // product of 2 with themselves: they are clamped in every round, no gradient leaves them.
 //
-// Bound by the chain of a round - ends from LDS, five sums one after the other, ends to LDS, barrier: about 0.17 us in a
-// forward round and 0.22 us in a reverse round at 32 x 32, where the arithmetic alone would take 0.07 and 0.12 - up to one
-// sample per unit, then by the arithmetic.  Flags in the exchanged words instead of barriers were slower (polling takes more
+// Bound by the chain of a round - ends from LDS, five sums one after the other, ends to LDS, barrier: 0.17 us in a
+// forward round and 0.18 to 0.20 in a reverse round at 32 x 32 (what 8 to 64 rounds take more), where the arithmetic alone would
+// take 0.07 and 0.12 - up to one sample per unit, then by the arithmetic.  Flags in the exchanged words instead of barriers were slower (polling takes more
 // instructions than it saves waits), and so were the shares added up a round late.
 // Both sweeps of 64 rounds, general kernels and these: 8 x 8 grid, B = 256 33.2 and 15.8 us; 16 x 16 27.2 and 21.2;
 // 32 x 32 39.3 and 30.1; B = 1024 8 x 8 78 and 18, 16 x 16 74 and 29, 32 x 32 134 and 83.

@@ -2136,8 +2136,6 @@ def test_unary_apply_of_wide_rows(dol, n, lengths, B):
     a thousand symbols (two to a word of the lists; 128 are the most that a lane sums), short lists and long ones in their
     kernels, a last chunk that is not full, rejected symbols, rows of other strides, columns at the clamp and beyond.
     Tolerance: the bar of 1e-5; where a sum of at most 128 tags is exactly 1 or beyond it, the decision is the oracle's."""
-    if B == 300 and n > 3000:
-        n, B = n, 3
     col, c = np.full(n, -1, np.int32), 0
     place, at = W.splitmix64(5, np.arange(n)).argsort(kind="stable"), 0
     while at < n - 5:
