@@ -775,11 +775,19 @@ JitBuild build_for(const dol_fn_table *f, int kind, int32_t batch)
 // and four have 512: with a wide result (48 x 48 -> 512, at 6 000 36.9 / 23.7, and at 16 384, eight / four 42.5 / 32.2) the rows of both
 // operands and the pieces on their way are too much for 256, up to 229 of them spilled; shorter rows are not (16 x 64 -> 400,
 // at 16 384 28.8 / 25.3, where clamps act 60.7 / 71.3).
+// Above 16 384 samples two tiles of four wavefronts share a unit.  Long rows, which are staged again there (keeps_rows), keep eight
+// wavefronts while few units get a second tile, us with eight / four, and where clamps act: 64 x 64 -> 256 at 17 000 35.7 / 39.8 and 61.6 / 71.3,
+// at 20 000 37.7 / 40.6 and 64.3 / 75.1, 22 000 40.1 / 41.0 and 70.3 / 75.9, 24 000 41.4 / 41.7 and 85.0 / 76.9, 30 000 45.5 / 44.4 and 91.4 / 79.6.
+// Not with many tuples to a symbol: 64 x 60 -> 64 (60) at 20 000 27.0 / 31.4, but 63.0 / 50.5.
 constexpr int kShortRows = 88;
 JitBuild build_for_both(const dol_fn_table *f, bool aligned, int32_t batch)
 {
     const JitBuild b = build_for(f, aligned ? kSlotMergeBothAligned : kSlotMergeBoth, batch);
-    if (!aligned || batch > 256 * kJitTile) return b;
+    if (!aligned) return b;
+    if (batch > 256 * kJitTile) {
+        const bool few_second = batch <= 352 * kJitTile && static_cast<int64_t>(f->n_tuples) <= 20 * static_cast<int64_t>(f->n_out);
+        return few_second && f->na + f->nb > kKeptSyms && !wide_result(f) ? kEightWaves : b;
+    }
     if (!wide_result(f)) return kEightWaves;
     return batch <= 128 * kJitTile ? kHalfTiles : f->na + f->nb <= kShortRows ? kEightWaves : kFourWaves;
 }

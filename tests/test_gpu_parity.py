@@ -520,7 +520,8 @@ def test_merged_calls_on_either_side_of_a_workgroup_per_sample(gp, dol, batch, n
     (16390, 12, 16, 36, 100, 0),        # four wavefronts; the second Distribution has symbols that the Apply has not
     (8200, 16, 20, 132, 64, 96),        # symbols of one side only, on both sides
     (16390, 64, 64, 256, 192, 96),      # .. and rows too long to stay in registers
-    (16390, 64, 64, 256, 256, 0),       # .. in four wavefronts of an aligned plan
+    (16390, 64, 64, 256, 256, 0),       # eight wavefronts above 256 tiles of an aligned plan
+    (22599, 64, 64, 256, 256, 0),       # .. and four, rows staged again
     (16390, 56, 56, 200, 200, 0),       # what both passes want is asked for behind the sums
     (16390, 16, 20, 132, 64, 96),       # four wavefronts, rows kept, symbols of one side only
     (3100, 16, 20, 132, 64, 96),        # .. in tiles of 32 samples
