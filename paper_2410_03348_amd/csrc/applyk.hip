@@ -362,6 +362,10 @@ struct TupleOffer {
     int64_t s;
     int at[kLongDtkpCol];               // unary_short(): lists of the lane with a slot of probability 0, -1 without
 
+    __device__ __forceinline__ void ask() {}
+    __device__ __forceinline__ void share() const {}
+    __device__ __forceinline__ void ahead(uint32_t) {}
+    __device__ __forceinline__ bool single(TopK<KP> &) const { return false; }
     __device__ __forceinline__ void begin(int64_t sample) { s = sample, fp = A.fact_prob + sample * A.n_facts; }
     // a unary function's symbols are one list each: several on their way at a time
     template <class Symbol>
@@ -417,7 +421,7 @@ struct TupleOffer {
             if (q + u * step < q1) {
 #pragma unroll
                 for (int x = 0; x < KP; ++x) {
-                    if (p[u][x] != 0.0f) keys.offer(p[u][x], at[u] + x);
+                    if (p[u][x] != 0.0f) keys.offer(true, p[u][x], at[u] + x);
                     else zero = true;
                 }
             }

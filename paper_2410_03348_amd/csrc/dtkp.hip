@@ -60,7 +60,10 @@ struct PairArgs {
     // proof {that fact} (App. A.1); nothing of it is stored.  fact_b holds four words per symbol: the fact and the mask of
     // the other facts of its exclusion group (low, high word).
     const int32_t *fact_b;
+    int32_t shared_facts;               // the second operand's symbols whose four words wait in LDS: all or none
 };
+
+constexpr int kSharedFacts = 64;        // most of them
 
 // Offers every consistent union of a proof of a's symbol with a proof of b's symbol, tuple by tuple.
 template <int K>
@@ -69,7 +72,29 @@ struct PairOffer {
     const GroupMasks &gm;
     const float *fp;
     int64_t a0, b0;
+    uint4 mine;                         // what this thread brings to LDS
+    uint32_t first;                     // the lane's first tuple
 
+    // in LDS: the facts, then a lane's masks (run_short)
+    static __device__ __forceinline__ uint4 *facts()
+    {
+        extern __shared__ __align__(16) uint64_t dtkp_lds[];
+        return reinterpret_cast<uint4 *>(dtkp_lds);
+    }
+    __device__ __forceinline__ uint64_t *lane_masks() const { return reinterpret_cast<uint64_t *>(facts() + A.shared_facts); }
+    __device__ __forceinline__ void ask()
+    {
+        if (static_cast<int>(threadIdx.x) < A.shared_facts) mine = reinterpret_cast<const uint4 *>(A.fact_b)[threadIdx.x];
+    }
+    __device__ __forceinline__ void share() const
+    {
+        if (A.shared_facts == 0) return;
+        if (static_cast<int>(threadIdx.x) < A.shared_facts) facts()[threadIdx.x] = mine;
+        lds_barrier();
+    }
+    // (a tuple's fact is known before its probability can be asked for: from LDS that costs no round trip to memory)
+    __device__ __forceinline__ uint4 fact_of(uint32_t j) const { return A.shared_facts ? facts()[j] : reinterpret_cast<const uint4 *>(A.fact_b)[j]; }
+    __device__ __forceinline__ void ahead(uint32_t r) { first = A.ord_tuples[r]; }
     __device__ __forceinline__ void begin(int64_t s)
     {
         fp = A.fact_prob + s * A.n_facts;
@@ -112,12 +137,14 @@ struct PairOffer {
             }
         }
     }
-    // the tuples word(q), word(q + step), .. below q1
+    // the tuples word(q), word(q + step), .. below q1 (a tuple's word is read while the one before it is worked on)
     template <class Word>
     __device__ __forceinline__ void run(TopK<K> &top, uint32_t q, uint32_t q1, uint32_t step, Word word) const
     {
+        uint32_t ahead = q < q1 ? word(q) : 0;
         for (; q < q1; q += step) {
-            const uint32_t ij = word(q), j = ij >> 16;
+            const uint32_t ij = ahead, j = ij >> 16;
+            ahead = word(min(q + step, q1 - 1));
             const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K;
             uint64_t ma[K];
             float pa[K];
@@ -126,7 +153,7 @@ struct PairOffer {
             for (int x = 0; x < K; ++x) pa[x] = -1.0f;
             if (A.ap) load_probs<K>(A.ap + ia, pa);
             if (A.fact_b) {
-                with_fact(top, reinterpret_cast<const uint4 *>(A.fact_b)[j], ma, pa);
+                with_fact(top, fact_of(j), ma, pa);
             } else with_list(top, j, ma, pa);
         }
     }
@@ -135,51 +162,94 @@ struct PairOffer {
         run(top, q, q1, step, [&](uint32_t x) { return A.col_ij[x]; });
     }
     __device__ __forceinline__ bool has_short() const { return A.fact_b && A.ap; }
-    // (the masks of a lane's few tuples wait in LDS for the winners; a key's id is the candidate's number in its lane, and the
-    // lane's thread << 8)
-    template <class Word>
-    __device__ __forceinline__ void run_short(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, Word word) const
+    // A tuple's candidates: which of the operand's proofs there are, joined to the fact, and their probabilities; the answer is
+    // whether they are in descending order.
+    __device__ __forceinline__ bool candidates(uint32_t ij, uint64_t (&m)[K], float (&pr)[K], bool (&ok)[K]) const
     {
-        extern __shared__ __align__(16) uint64_t lane_masks[];
-        static_assert(K * kLongDtkpCol <= 256 || K > kKeyProofs, "a candidate's number");
-        uint64_t *put = lane_masks + threadIdx.x;
-        int id = threadIdx.x << 8;
-        for (; q < q1; q += step, id += K, put += K * blockDim.x) {
-            const uint32_t ij = word(q);
-            const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K;
-            const uint4 f = reinterpret_cast<const uint4 *>(A.fact_b)[ij >> 16];
-            uint64_t ma[K];
-            float pa[K];
-            load_masks<K>(A.am + ia, ma);
-            load_probs<K>(A.ap + ia, pa);
-            const uint64_t bit = uint64_t(1) << f.x, rival = (static_cast<uint64_t>(f.z) << 32) | f.y;
-            const float pbit = 1.0f * fp[f.x];
+        const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K;
+        const uint4 f = fact_of(ij >> 16);
+        uint64_t ma[K];
+        float pa[K];
+        load_masks<K>(A.am + ia, ma);
+        load_probs<K>(A.ap + ia, pa);
+        const float pbit = 1.0f * fp[f.x];
+        const uint64_t bit = uint64_t(1) << f.x, rival = (static_cast<uint64_t>(f.z) << 32) | f.y;
+        uint64_t any = 0;
+#pragma unroll
+        for (int x = 0; x < K; ++x) {
+            ok[x] = ma[x] != kAbsent;
+            any |= ok[x] ? ma[x] : 0;
+            pr[x] = pa[x] * pbit;
+            m[x] = ma[x] | bit;
+        }
+        // (mostly the fact is new to all proofs, above every one of theirs and no rival: one look for all of them)
+        if (__builtin_expect((any & rival) || any >= bit, 0)) {
 #pragma unroll
             for (int x = 0; x < K; ++x) {                       // (see with_fact)
-                if (ma[x] == kAbsent || (ma[x] & rival)) continue;
-                const bool held = (ma[x] & bit) != 0;
-                const float pr = held || ma[x] < bit ? (held ? pa[x] : pa[x] * pbit) : proof_prob(ma[x] | bit, fp);
-                put[x * blockDim.x] = ma[x] | bit;
-                keys.offer(pr, id + x);
+                ok[x] = ok[x] && !(ma[x] & rival);
+                if (ma[x] & bit) pr[x] = pa[x];
+                else if (ok[x] && !(ma[x] < bit)) pr[x] = proof_prob(m[x], fp);
+            }
+        }
+        bool falls = true;
+#pragma unroll
+        for (int x = 1; x < K; ++x) falls &= !ok[x] || (ok[x - 1] && pr[x - 1] >= pr[x]);
+        return falls;
+    }
+    // (the masks of a lane's few tuples wait in LDS for the winners; a key's id is the candidate's number in its lane, and the
+    // lane's thread << 8.  Read again from memory once the winners are known: 192.6 us for the formula's pass, 184.2 so.)
+    // ahead: word(q)
+    template <class Word>
+    __device__ __forceinline__ void run_short(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, uint32_t ahead, Word word) const
+    {
+        static_assert(K * kLongDtkpCol <= 256 || K > kKeyProofs, "a candidate's number");
+        uint64_t *put = lane_masks() + threadIdx.x;
+        int id = threadIdx.x << 8;
+        for (; q < q1; q += step, id += K, put += K * blockDim.x) {
+            const uint32_t ij = ahead;
+            ahead = word(min(q + step, q1 - 1));
+            uint64_t m[K];
+            float pr[K];
+            bool ok[K];
+            const bool falls = candidates(ij, m, pr, ok);
+#pragma unroll
+            for (int x = 0; x < K; ++x) put[x * blockDim.x] = m[x];
+            if (__builtin_expect(falls, 1)) {
+                keys.offer_falling(ok, pr, id);
+            } else {
+#pragma unroll
+                for (int x = 0; x < K; ++x) keys.offer(ok[x], pr[x], id + x);
             }
         }
     }
+    // A column of one tuple: its candidates are the result unless two probabilities are equal or some candidate is no proof; where that may be
+    // it says so.
+    __device__ __forceinline__ bool single(TopK<K> &top) const
+    {
+        bool ok[K], clear = candidates(first, top.m, top.p, ok);
+#pragma unroll
+        for (int x = 0; x < K; ++x) {
+            clear &= !ok[x] || (__float_as_uint(top.p[x]) < 0x7f800000u && (x == 0 || top.p[x > 0 ? x - 1 : 0] != top.p[x]));
+            if (!ok[x]) top.m[x] = kAbsent, top.p[x] = -1.0f;
+        }
+        return clear;
+    }
     __device__ __forceinline__ void short_listed(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step) const
     {
-        run_short(keys, q, q1, step, [&](uint32_t x) { return A.col_ij[x]; });
+        run_short(keys, q, q1, step, q < q1 ? A.col_ij[q] : 0, [&](uint32_t x) { return A.col_ij[x]; });
     }
     __device__ __forceinline__ void short_laned(TopKeys<K> &keys, uint32_t len, int32_t r) const
     {
-        run_short(keys, 0, len, 1, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; });
+        run_short(keys, 0, len, 1, first, [&](uint32_t k) { return A.ord_tuples[static_cast<size_t>(k) * A.S + r]; });
     }
     __device__ __forceinline__ bool short_take(TopK<K> &top, const TopKeys<K> &keys, int) const
     {
-        extern __shared__ __align__(16) uint64_t lane_masks[];
+        const uint64_t *masks = lane_masks();
         wave_lds_fence();
 #pragma unroll
         for (int x = 0; x < K; ++x) {
             if (!keys.present(x)) continue;
-            top.m[x] = lane_masks[(keys.id(x) & 255) * blockDim.x + (keys.id(x) >> 8)];
+            top.m[x] = masks[(keys.id(x) & 255) * blockDim.x + (keys.id(x) >> 8)];
             top.p[x] = keys.prob(x);
         }
         return true;
@@ -194,14 +264,15 @@ template <int K>
 __global__ void __launch_bounds__(kHugeThreads)
 dtkp_apply2_kernel(ColumnArgs C, PairArgs A, GroupMasks gm)
 {
-    dtkp_columns<K>(C, PairOffer<K>{A, gm, nullptr, 0, 0});
+    dtkp_columns<K>(C, PairOffer<K>{A, gm, nullptr, 0, 0, {}, 0});
 }
 
 template <int K>
 static void launch_apply2_k(ColumnArgs C, const PairArgs &A, const GroupMasks &gm, hipStream_t st)
 {
     const unsigned grid = column_launch<K>(C);
-    const size_t lds = K <= kKeyProofs && A.fact_b ? sizeof(uint64_t) * column_threads(C) * kLongDtkpCol * K : 0;     // a lane's masks: 96 bytes at three proofs
+    const size_t lds = sizeof(uint4) * A.shared_facts +
+                       (K <= kKeyProofs && A.fact_b ? sizeof(uint64_t) * column_threads(C) * kLongDtkpCol * K : 0);     // a lane's masks: 96 bytes at three proofs
     hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid), dim3(column_threads(C)), lds, st, C, A, gm);
 }
 
@@ -232,7 +303,8 @@ dol_status launch_dtkp_apply2(const dol_fn_table *f, int32_t batch, int32_t k, i
     C.col_ptr = f->col_ptr.ptr;
     set_columns(C, f->dtkp_cols);
     C.om = om, C.op = op, C.oprob = oprob, C.ldo = ldo;
-    const PairArgs A{f->n_out, f->na, f->nb, n_facts, f->col_ij.ptr, f->dtkp_tuples.ptr, fact_prob, am, bm, ap, bp, fact_b};
+    const PairArgs A{f->n_out, f->na, f->nb, n_facts, f->col_ij.ptr, f->dtkp_tuples.ptr, fact_prob, am, bm, ap, bp, fact_b,
+                     fact_b && f->nb <= kSharedFacts ? f->nb : 0};
 #define CALL(KK) launch_apply2_k<KK>(C, A, gm, st)
     DOL_DISPATCH_K(k, CALL)
 #undef CALL

@@ -7,7 +7,12 @@
 // one of 758 columns 16, with up to 8 (then 16 lanes) 79 and 11, with up to 4 and four lanes up to 16, as here, 75 and 8.
 // Results gathered in LDS and stored as whole lines were slower (106 us): a workgroup of neighbours waits for its longest
 // column.
-// With lists ranked by keys that table takes 61 us (73 before), k = 3, and 147 MB leave for 98 MB of results, whose order is
+// With lists ranked by keys that table took 61 us (73 before), k = 3, and 57 now: a tuple waits for its lists only (its word is read
+// one tuple ahead, the first with the column's length, its fact lies in LDS), where the fact is new to all proofs one look at them
+// says so and the lists meet as two lanes' do, columns of one tuple go from the operand's list to the result.  Not bound by
+// issue (347 -> 308 vector instructions a wavefront between the first of these and all, no time) but by what a wavefront waits for:
+// 14 us are its way to the first tuple, 21 the short columns, 13 those of 5 to 16 tuples, 10 the longer ones.  Those by a quarter of
+// the lanes: a third fewer instructions, 68 us.  147 MB leave for 98 MB of results, whose order is
 // that of the columns' lengths.  Lengths sorted inside fewer than 4 096 columns leave fewer bytes (129 MB) but unequal lanes:
 // the pass of that expression took 206 us and more instead of 204 (passes in this file repeat the same inputs; where these change
 // from pass to pass they take some ten us more).  Lists read four tuples ahead: 80 us, for want of wavefronts.
@@ -34,6 +39,7 @@ struct ColumnArgs {
     const uint32_t *longer;
     const uint32_t *col_ptr;                // tuples of a column
     const uint32_t *order, *len;            // short columns: the r-th one and its length (0: among the longer ones)
+    uint64_t per_S;                         // 2^64 / S, rounded up (0: S = 1)
     uint64_t *om;
     float *op, *oprob;
     int64_t ldo;
@@ -70,6 +76,7 @@ inline unsigned column_launch(ColumnArgs &A)
         const int64_t set = std::max<int64_t>(8, kSetBytes / sample / 8 * 8);
         if (A.batch >= 2 * set) A.set = static_cast<int32_t>(set), A.sets = static_cast<int32_t>(A.batch / set);
     }
+    A.per_S = A.S > 1 ? ~uint64_t(0) / static_cast<uint32_t>(A.S) + 1 : 0;
     auto eight = [](int64_t n) { return static_cast<uint32_t>((n + 7) / 8 * 8); };
     auto groups = [&](int32_t samples, int32_t n, int lanes) { return eight(static_cast<int64_t>(samples) * ((n + threads / lanes - 1) / (threads / lanes))); };
     auto blocks = [&](int32_t samples) {
@@ -82,7 +89,8 @@ inline unsigned column_launch(ColumnArgs &A)
     return A.b_huge + A.b_wave + (A.sets - 1) * all(A.full) + all(A.last);
 }
 
-// Offer: begin(s) - the sample; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
+// Offer: ask() and share() - what all threads of a workgroup need is on its way, is there; begin(s) - the sample; ahead(r) - the first tuple of the r-th
+// short column, asked for before anything is known about it; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
 // laned(top, len, r, c) - those of column c, the r-th in order; where it has_short(), short_listed and short_laned offer the same,
 // of at most kLongDtkpCol tuples a lane, to a list of keys, and short_take() finds the proofs of the list, the same of
 // `lanes` lanes, or says that it cannot (to each of them).
@@ -113,6 +121,7 @@ template <int K, class Offer>
 __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
 {
     const int T = blockDim.x, t = threadIdx.x;
+    offer.ask();
     TopK<K> top;
     top.clear();
     uint32_t b = blockIdx.x;
@@ -147,8 +156,9 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
         const int32_t id = xcd_contiguous(b, blocks);               // (a sample's columns on one XCD: its lists fill one L2)
         const int32_t in_set = id / groups, ci = (id - in_set * groups) * per + t / lanes, s = s0 + in_set;
         if (in_set >= samples) return;
+        const uint32_t c = A.longer[from + min(ci, n - 1)];
+        offer.share();
         if (ci >= n) return;                        // (all lanes of a group; never a huge column's)
-        const uint32_t c = A.longer[from + ci];
         offer.begin(s);
         if constexpr (K <= kKeyProofs) {
             if (lanes <= 16 && offer.has_short() && !equal_facts(offer.A.fact_prob, offer.A.n_facts, s)) {      // (at most kLongDtkpCol tuples a lane)
@@ -192,19 +202,35 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
         return;
     }
     const int32_t id = xcd_contiguous(b - first, B.lane);
-    const int64_t at = static_cast<int64_t>(id) * T + t;
-    if (at >= static_cast<int64_t>(samples) * A.S) return;
-    const int32_t in_set = static_cast<int32_t>(at / A.S), r = static_cast<int32_t>(at - static_cast<int64_t>(in_set) * A.S), s = s0 + in_set;
+    // the workgroup's first (sample, column), by a multiplication (a division of 64 bits by each lane took a tenth of a short
+    // column's instructions); a lane's from there
+    const uint32_t S = static_cast<uint32_t>(A.S);
+    const uint64_t from = static_cast<uint64_t>(static_cast<uint32_t>(id)) * T, total = static_cast<uint64_t>(samples) * S;
+    if (from >= total) return;
+    uint32_t q0 = static_cast<uint32_t>(from);
+    if (from >> 32) q0 = static_cast<uint32_t>(from / S);
+    else if (S > 1) q0 = static_cast<uint32_t>((from * (A.per_S >> 32) + __umulhi(q0, static_cast<uint32_t>(A.per_S))) >> 32);
+    uint32_t r = static_cast<uint32_t>(from - static_cast<uint64_t>(q0) * S) + t;
+    const uint32_t over = S >= static_cast<uint32_t>(T) ? (r >= S ? 1u : 0u) : r / S;
+    r -= over * S;
+    const bool live = from + t < total;
+    r = live ? r : 0;
+    const int32_t s = s0 + static_cast<int32_t>(q0 + (live ? over : 0));
     // lanes of a wavefront: columns of like length
     const uint32_t len = A.len[r], c = A.order[r];
+    offer.ahead(r);
+    offer.share();
+    if (!live) return;
     offer.begin(s);
     bool keys_ok = false;
     if constexpr (K <= kKeyProofs) keys_ok = offer.has_short() && !equal_facts(offer.A.fact_prob, offer.A.n_facts, s);      // (the same for all)
     if (len == 0) return;
     bool todo = true;
     if constexpr (K <= kKeyProofs) {
-        if (keys_ok) {
+        if (keys_ok && len == 1) todo = !offer.single(top);
+        if (keys_ok && todo) {
             TopKeys<K> keys;
+            top.clear();
             offer.short_laned(keys, len, r);
             todo = keys.unclear() || !offer.short_take(top, keys, 1);
         }

@@ -135,23 +135,38 @@ __device__ __forceinline__ void sort_valley(double (&k)[L], int at)
 template <int K>
 struct TopKeys {
     double top[K + 1];
-    uint32_t most = 0;                  // the largest candidate's bits as a whole number
+    uint32_t most = 0;                  // the candidates' bits, all of them (above 0x7f800000 if one's are; else only if one is 2 or more)
 
     __device__ __forceinline__ TopKeys()
     {
 #pragma unroll
         for (int x = 0; x <= K; ++x) top[x] = -1.0;
     }
-    __device__ __forceinline__ void offer(float p, int id)
+    // (ok = false: an absent proof, whatever p is)
+    __device__ __forceinline__ void offer(bool ok, float p, int id)
     {
-        most = max(most, __float_as_uint(p));
-        double o = key_of(p, id);
+        most |= __float_as_uint(p);
+        double o = key_of(ok ? p : -1.0f, id);
 #pragma unroll
         for (int x = 0; x <= K; ++x) {
             const double t = top[x];
             top[x] = key_max(t, o);
             if (x < K) o = key_min(t, o);
         }
+    }
+    // K candidates in descending order, the absent ones last, as id, id + 1, ..: as two lanes' lists meet (take)
+    __device__ __forceinline__ void offer_falling(const bool (&ok)[K], const float (&p)[K], int id)
+    {
+        double best[K + 1];
+        best[0] = top[0];
+#pragma unroll
+        for (int x = 0; x < K; ++x) {
+            most |= __float_as_uint(p[x]);
+            best[K - x] = key_max(top[K - x], key_of(ok[x] ? p[x] : -1.0f, id + x));
+        }
+        sort_valley<K + 1, K + 1>(best, 0);
+#pragma unroll
+        for (int x = 0; x <= K; ++x) top[x] = best[x];
     }
     // takes in the list of the lane that CTRL (wave_util.h) pairs this one with
     template <int CTRL>
@@ -166,7 +181,7 @@ struct TopKeys {
         sort_valley<K + 1, K + 1>(best, 0);
 #pragma unroll
         for (int x = 0; x <= K; ++x) top[x] = best[x];
-        most = max(most, static_cast<uint32_t>(dpp_i<CTRL>(static_cast<int>(most))));
+        most |= static_cast<uint32_t>(dpp_i<CTRL>(static_cast<int>(most)));
     }
     // all lanes of a group of 4 or 16 end with its list
     __device__ __forceinline__ void merge(int lanes)

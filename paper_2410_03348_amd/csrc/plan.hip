@@ -240,7 +240,8 @@ static dol_status build_table(int32_t na, int32_t nb, std::vector<Tuple> &tup, d
         for (uint32_t q = col_ptr[c], u = 0; q < col_ptr[c + 1] && u < 4; ++q, ++u) col_head[static_cast<size_t>(c) * 4 + u] = col_ij[q];
     if ((e = tb->col_head.upload(col_head)) != hipSuccess) return hip_fail(e, "uploading the function table");
     {
-        const uint32_t longest = S ? *std::max_element(lengths.begin(), lengths.end()) : 0;
+        // (a row even where every column is a longer one: first words are asked for before lengths are known)
+        const uint32_t longest = S ? std::max(1u, *std::max_element(lengths.begin(), lengths.end())) : 0;
         std::vector<uint32_t> tuples(static_cast<size_t>(longest) * S, 0);
         for (int32_t r = 0; r < S; ++r)
             for (uint32_t k = 0; k < lengths[r]; ++k) tuples[static_cast<size_t>(k) * S + r] = col_ij[col_ptr[col_order[r]] + k];

@@ -3011,6 +3011,41 @@ def test_dtkp_apply2_input_equals_init_then_apply2(dol, k):
         dol.dtkp_apply2_input(a, np.full(fact_b.size, 18, np.int32), f, prov, got)
 
 
+@pytest.mark.parametrize("facts", ["new", "mixed"])
+@pytest.mark.parametrize("na,nb,S,B", [(5, 3, 1, 3), (31, 1, 31, 77), (128, 1, 128, 9), (130, 2, 129, 20), (36, 64, 700, 5), (36, 65, 300, 11), (4, 9, 1, 130)])
+@pytest.mark.parametrize("k", [1, 3, 4])
+def test_dtkp_input_columns_at_the_edges_of_workgroups(dol, k, na, nb, S, B, facts):
+    """The second operand given by its facts, over columns of one tuple and of a few, workgroups that end in another sample and
+    samples of many to a workgroup, up to 64 symbols whose facts wait in LDS and one more; facts above all others, and facts
+    held already, below others and rivals.  Bit for bit what dol_dtkp_init + dol_apply2 give."""
+    n0, n1, low = 12, 12, 24
+    n_facts = 60
+    fp = W.uniform01(6100 + na, B * n_facts).astype(np.float32).reshape(B, n_facts)
+    fp[:, 3] = fp[:, 5]                                     # (equal proofs now and then)
+    grp = np.concatenate([np.repeat(np.arange(4), 6), np.full(n_facts - low, 9)]).astype(np.int32)
+    prov = dol.Prov(dol.DTKP, k, dev(fp), grp)
+    d0, d1 = dol.Dist.empty(np.arange(n0), B, k=k), dol.Dist.empty(np.arange(n1), B, k=k)
+    dol.dtkp_init(d0, np.arange(n0), prov)
+    dol.dtkp_init(d1, np.arange(n1) + n0, prov)
+    first = dol.FnTable.create_dense((np.arange(n0 * n1) * 7 % na).astype(np.int32).reshape(n0, n1))
+    a = dol.Dist.empty(first.out_syms, B, k=k)
+    assert a.n_sym == na
+    dol.apply2(d0, d1, first, prov, a)
+    fact_b = (low + np.arange(nb) * 5 % (n_facts - low) if facts == "new" else np.arange(nb) * 11 % n_facts).astype(np.int32)
+    ids = (W.splitmix64(6200, np.arange(na * nb)) % np.uint64(S)).astype(np.int32)
+    ids[np.argsort(W.splitmix64(6300, np.arange(na * nb)), kind="stable")[:S]] = np.arange(S)
+    f = dol.FnTable.create_dense(ids.reshape(na, nb))
+    assert f.out_syms.size == S
+    b = dol.Dist.empty(np.arange(nb), B, k=k)
+    dol.dtkp_init(b, fact_b, prov)
+    want, got = dol.Dist.empty(f.out_syms, B, k=k), dol.Dist.empty(f.out_syms, B, k=k)
+    dol.apply2(a, b, f, prov, want)
+    dol.dtkp_apply2_input(a, fact_b, f, prov, got)
+    np.testing.assert_array_equal(host(got.proof_mask), host(want.proof_mask))
+    np.testing.assert_array_equal(host(got.proof_prob), host(want.proof_prob))
+    np.testing.assert_array_equal(host(got.prob), host(want.prob))
+
+
 @pytest.mark.parametrize("k,nv", [(1, 6), (3, 6), (3, 20), (8, 12)])
 def test_dtkp_gradient_with_impossible_facts(dol, k, nv):
     """Fact probabilities of exactly 0 and far below 1e-30 in some samples: there the product of a proof's other facts
