@@ -28,10 +28,11 @@ constexpr int kDfWaves = 4;             // most wavefronts (samples) of one work
 //           the records at r_t, one per tuple in column order: the first operand's list, counted in bytes of
 //           probabilities, | 4 x the second operand's FACT << 16 (two spare records at the end so that the read-ahead
 //           stays inside)
-//   fresh_t = 1: every fact of input t lies above every fact of the inputs before it and shares no exclusion group
+//   fresh_t = 1 or 2: every fact of input t lies above every fact of the inputs before it and shares no exclusion group
 //           with any of them.  A proof of the running Distribution then never holds the new fact or a rival of it, and
 //           the product over ascending facts is the proof's stored probability times the new fact's: the stage needs
-//           no mask at all until its k winners are known.
+//           no mask at all until its k winners are known.  2: and each input so far gives every symbol a fact of its own, none of them
+//           known before: a proof says which symbols it is of, and no two symbols of a Distribution have one in common.
 struct DtkpFoldArgs {
     int32_t n, batch, n_facts, max_s, n_words, wave_bytes;
     const int32_t *words;
@@ -46,6 +47,74 @@ struct DtkpFoldArgs {
     float *gfact;
 };
 
+// The K best distinct proofs of one column, by the whole wavefront: lane y < K ends with the y-th (id -1: none).  Lanes K .. 63 take
+// the candidates as they come, the first K lanes keep the best so far; K times the best of all is taken, the smallest mask among equal
+// probabilities, and with it whatever has its mask.  For probabilities that are finite and not below 0.
+// (Two facts of one probability, in one of a thousand samples of softmax outputs, make tens of such columns.  By its lane, a candidate at
+// a time, through code that no wavefront had fetched yet, a column took 4 us (k = 3) to 60 (k = 7) and the others of the stage with it:
+// Sum-6, k = 5, 2 048 samples 50 us with one such sample and 17.7 without any, k = 7 83 and 22.6, Sum-5, k = 3, 1 024 12.9 and 9.1;
+// so 28 and 17.8, 51 and 22.6, 9.5 and 9.1.)
+struct Ranked {
+    float p;
+    int id;
+};
+
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
+{
+    x = max(x, static_cast<uint32_t>(dpp_i<0xB1>(static_cast<int>(x))));
+    x = max(x, static_cast<uint32_t>(dpp_i<0x4E>(static_cast<int>(x))));
+    x = max(x, static_cast<uint32_t>(dpp_i<0x141>(static_cast<int>(x))));
+    x = max(x, static_cast<uint32_t>(dpp_i<0x140>(static_cast<int>(x))));
+    const uint32_t a = __builtin_amdgcn_readlane(static_cast<int>(x), 0), b = __builtin_amdgcn_readlane(static_cast<int>(x), 16);
+    const uint32_t c = __builtin_amdgcn_readlane(static_cast<int>(x), 32), d = __builtin_amdgcn_readlane(static_cast<int>(x), 48);
+    return max(max(a, b), max(c, d));
+}
+
+template <int K, int KA>
+__device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const uint32_t *l_rec, const uint64_t *cm, const float *cp, const float *fp)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    Ranked best{-1.0f, -1};
+    uint64_t best_mask = kAbsent;
+    const int total = static_cast<int>(q1 - q0) * KA;
+#pragma unroll 1
+    for (int first = 0; first < total; first += kWave - K) {
+        float p = best.p;
+        int id = best.id;
+        uint64_t mask = best_mask;
+        const int k = first + lane - K;
+        if (lane >= K) {
+            p = -1.0f, id = -1, mask = kAbsent;
+            if (k < total) {
+                const uint32_t q = q0 + static_cast<uint32_t>(k) / KA, x = static_cast<uint32_t>(k) % KA, r = l_rec[q];
+                const int at = static_cast<int>((r & 0xffffu) >> 2) + static_cast<int>(x);
+                const float pa = cp[at];
+                if (pa >= 0.0f) p = pa * fp[r >> 18], id = static_cast<int>(q << 3 | x), mask = cm[at] | (uint64_t(1) << (r >> 18));
+            }
+        }
+        best = Ranked{-1.0f, -1}, best_mask = kAbsent;
+#pragma unroll 1
+        for (int y = 0; y < K; ++y) {
+            const uint32_t key = p >= 0.0f ? __float_as_uint(p) + 1 : 0, top = wave_max_u32(key);
+            if (top == 0) break;
+            const uint32_t lo = static_cast<uint32_t>(mask), hi = static_cast<uint32_t>(mask >> 32);
+            int from = -1;
+            uint64_t least = kAbsent;
+            for (uint64_t equal = __ballot(key == top); equal; equal &= equal - 1) {
+                const int at = __builtin_ctzll(equal);
+                const uint64_t m = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hi), at))) << 32 |
+                                   static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lo), at));
+                if (from < 0 || m < least) from = at, least = m;
+            }
+            if (lane == y) best.p = __uint_as_float(top - 1), best_mask = least;
+            const int id_from = __builtin_amdgcn_readlane(id, from);
+            if (lane == y) best.id = id_from;
+            if (mask == least) p = -1.0f;
+        }
+    }
+    return best;
+}
+
 // One stage of the fold for this wavefront's sample: the columns of the stage's table, a lane each.  KA: slots of the
 // first operand's lists that can hold a proof (1 right after the natural initialisation); FRESH: see fresh_t above.
 // Absent slots carry the probability -1 in LDS (0 in the result tensors).
@@ -54,8 +123,8 @@ struct DtkpFoldArgs {
 // list times one factor, i.e. in descending order already: the k + 1 best of both lists are the elementwise maxima of one
 // and the other reversed, sorted again by a short network.  Masks matter only where probabilities are equal: two of the kept
 // ones, or the last one and the best that dropped out, which is what the list's entry behind the k-th holds (of all that
-// dropped out on the way none is larger).  Such a column is done again, candidate by candidate (exact_column), and so is
-// every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where an
+// dropped out on the way none is larger).  Such a column is ranked again by the whole wavefront (rank_column); candidate by candidate
+// (exact_column) is every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where an
 // eighth of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3,
 // B=1 024, facts of one probability: 65 us, 58.4 so; facts in steps of 1/16 64 and 58.2; Sum-6, k = 5, B=12 000 560 and 516).
 // (Bound by the vector ALUs.  k = 5 costs about 35 instructions a tuple by the compiled code, none of them a choice; 65 with
@@ -64,10 +133,12 @@ struct DtkpFoldArgs {
 template <int K, int KA, bool FRESH>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,
-                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain)
+                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain, bool distinct)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    for (int c = lane; c < S; c += kWave) {
+    for (int base = 0; base < S; base += kWave) {
+        const int c = base + lane;
+        const bool there = c < S;                           // (the others help where a column has ties)
         float tp[K];
         int tid_[K];
 #pragma unroll
@@ -109,7 +180,8 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                 tid_[y] = above ? tid_[y - 1] : gt[y] ? id : tid_[y];
             }
         };
-        const uint32_t q0 = l_ptr[c], q1 = l_ptr[c + 1];
+        uint32_t q0 = 0, q1 = 0;
+        if (there) q0 = l_ptr[c], q1 = l_ptr[c + 1];
         auto list_of = [&](uint32_t r) { return reinterpret_cast<const float *>(reinterpret_cast<const char *>(cp) + (r & 0xffffu)); };
         auto fact_of = [&](uint32_t r) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(fp) + (r >> 16)); };
         if constexpr (FRESH) {
@@ -133,7 +205,9 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                     }
                 }
             };
-            if (plain) {
+            if (!plain) {
+                if (there) exact_column();
+            } else {
                 // a tuple's record is read two tuples ahead and its operands one ahead; records past the last one are the
                 // spare ones behind every array, which name operands that exist
                 double top[K + 1];
@@ -173,19 +247,29 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                         }
                     }
                 }
-                bool tie = false;
+                bool inner = false, again = false;
 #pragma unroll
                 for (int x = 0; x < K; ++x) {
                     const int hi = __double2hiint(top[x]), next = __double2hiint(top[x + 1]);
                     tp[x] = __int_as_float(hi);
                     tid_[x] = hi >= 0 ? __double2loint(top[x]) : -1;
-                    tie |= hi == next && hi >= 0;
+                    (x + 1 < K ? inner : again) |= hi == next && hi >= 0;
                 }
-                if (__builtin_expect(tie, 0)) exact_column();
-            } else {
-                exact_column();
+                // Equal probabilities among the kept ones: the masks' order, which only the result shows, unless a proof may be there
+                // twice.  The last of them as probable as the best that dropped out: the kept ones may be others.
+                again |= inner && (last || !distinct);
+                for (uint64_t todo = __ballot(again); __builtin_expect(todo != 0, 0); todo &= todo - 1) {
+                    const int from = __builtin_ctzll(todo);
+                    const Ranked r = rank_column<K, KA>(__builtin_amdgcn_readlane(static_cast<int>(q0), from), __builtin_amdgcn_readlane(static_cast<int>(q1), from), l_rec, cm, cp, fp);
+#pragma unroll
+                    for (int x = 0; x < K; ++x) {
+                        const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r.p), x));
+                        const int id = __builtin_amdgcn_readlane(r.id, x);
+                        if (lane == from) tp[x] = p, tid_[x] = id;
+                    }
+                }
             }
-        } else {
+        } else if (there) {
             uint32_t rec = l_rec[q0];
             for (uint32_t q = q0; q < q1; ++q) {
                 const int i = static_cast<int>((rec & 0xffffu) >> 2), fb = static_cast<int>(rec >> 18);
@@ -226,6 +310,7 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
         }
         // a Distribution of at most 64 symbols is replaced in place: every lane has read what it needs by now
         wave_lds_fence();
+        if (!there) continue;
 #pragma unroll
         for (int x = 0; x < K; ++x) {
             nm[c * K + x] = wm[x];
@@ -302,13 +387,14 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         float *np = bufp + (t & 1) * flip;
         S = __builtin_amdgcn_readfirstlane(static_cast<int>(w[1 + 4 * t]));
         const uint32_t *l_ptr = w + w[2 + 4 * t], *l_rec = w + w[3 + 4 * t];
-        const bool last = t == A.n - 1, fresh = __builtin_amdgcn_readfirstlane(static_cast<int>(w[4 + 4 * t])) != 0;
+        const int kind = __builtin_amdgcn_readfirstlane(static_cast<int>(w[4 + 4 * t]));
+        const bool last = t == A.n - 1, fresh = kind != 0, distinct = kind == 2;
         if (t == 1) {                       // the first operand is naturally initialised: one proof per symbol
-            if (fresh) dtkp_fold_stage<K, 1, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain);
-            else dtkp_fold_stage<K, 1, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain);
+            if (fresh) dtkp_fold_stage<K, 1, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
+            else dtkp_fold_stage<K, 1, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
         } else {
-            if (fresh) dtkp_fold_stage<K, K, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain);
-            else dtkp_fold_stage<K, K, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain);
+            if (fresh) dtkp_fold_stage<K, K, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
+            else dtkp_fold_stage<K, K, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
         }
         wave_lds_fence();
     }
@@ -377,6 +463,7 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
     words[0] = n;
     int32_t s_prev = 0;
     int32_t fact_hi = -1;                   // highest fact of the inputs so far
+    bool distinct = true;                   // see fresh_t = 2
     uint64_t facts_seen = 0;
     for (int t = 0; t < n; ++t) {
         const dol_dist *d = fold->inputs[t];
@@ -394,7 +481,8 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
             for (int f = 0; f < prov->n_facts && prov->fact_group && fresh; ++f)
                 for (int h = 0; h < prov->n_facts && ((mine >> f) & 1); ++h)
                     if (((facts_seen >> h) & 1) && prov->fact_group[h] == prov->fact_group[f]) fresh = false;
-            words[4 + 4 * t] = fresh ? 1 : 0;
+            distinct = distinct && fresh && __builtin_popcountll(mine) == d->n_sym;
+            words[4 + 4 * t] = distinct ? 2 : fresh ? 1 : 0;
             for (int32_t i = 0; i < d->n_sym; ++i) fact_hi = std::max(fact_hi, fos[i]);
             facts_seen |= mine;
         }

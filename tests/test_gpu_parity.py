@@ -889,6 +889,37 @@ def test_fused_dtkp_fold_list_merge_with_ties(dol, k, batch, draw):
         assert_close(host(gf), oracle.dtkp_prob_bwd(m, fp, g), "fold gradient")
 
 
+@pytest.mark.parametrize("shared", [0, 1])
+@pytest.mark.parametrize("k", [1, 2, 3, 5, 8])
+def test_fused_dtkp_fold_where_two_proofs_are_equally_probable(dol, k, shared):
+    """Facts of which two of one input, or of two inputs, have one probability in some samples, so that single columns have ties: at
+    the last place, inside the list, in the last stage and before it, in columns of more candidates than lanes.  shared: every
+    input gives one fact to two of its symbols, so that a proof comes twice.  Against the oracle's composition, bit for bit."""
+    batch, nv, n = 37, 10, 4
+    n_facts = n * nv
+    fp = W.uniform01(171 + k, batch * n_facts).astype(np.float32).reshape(batch, n_facts)
+    fp[::3, 12], fp[::3, 4], fp[1::6, 33] = fp[::3, 17], fp[::3, 25], 0.0
+    facts = [(nv * t + np.arange(nv)).astype(np.int32) for t in range(n)]
+    if shared:
+        for f in facts:
+            f[6] = f[2]
+    grp = (np.arange(n_facts) // nv).astype(np.int32)
+    sym = np.arange(nv, dtype=np.int32)
+    m, _, _ = oracle.dtkp_init(facts[0], fp, k)
+    syms, tables = sym, []
+    for t in range(1, n):
+        dm, _, _ = oracle.dtkp_init(facts[t], fp, k)
+        tab = W.sum_table(syms, sym) // (2 if t == 2 else 1)
+        syms, m, pp, pr = oracle.dtkp_apply2(oracle.dense_to_triples(tab), syms.size, nv, k, grp, fp, m, dm)
+        tables.append(dol.FnTable.create_dense(tab))
+    out = dol.Dist.empty(syms, batch, k=k)
+    digits = [dol.Dist(sym, torch.empty((batch, nv), device="cuda")) for _ in range(n)]
+    dol.dtkp_fold_apply2(dol.DtkpFold(digits, facts, tables, out), dol.Prov(dol.DTKP, k, dev(fp), grp))
+    np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), m)
+    np.testing.assert_array_equal(host(out.proof_prob), pp)
+    assert_close(host(out.prob), pr, "fold tag prob")
+
+
 # ---------------------------------------------------------------- config 5
 
 @pytest.mark.parametrize("batch,side,rounds", [(256, 32, 64), (33, 7, 20), (2, 3, 5)])
