@@ -26,7 +26,7 @@ constexpr int kDfWaves = 4;             // most wavefronts (samples) of one work
 //   t = 0:  S_0 words at p_0: the facts of the first input's symbols
 //   t >= 1: S_t + 1 words at p_t: where each output column's tuples start and end inside the stage's records;
 //           the records at r_t, one per tuple in column order: the first operand's list, counted in bytes of
-//           probabilities, | 4 x the second operand's FACT << 16 (two spare records at the end so that the read-ahead
+//           probabilities, | 4 x the second operand's FACT << 16 (spare records at the end so that the read-ahead
 //           stays inside)
 //   fresh_t = 1 or 2: every fact of input t lies above every fact of the inputs before it and shares no exclusion group
 //           with any of them.  A proof of the running Distribution then never holds the new fact or a rival of it, and
@@ -127,9 +127,10 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
 // (exact_column) is every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where an
 // eighth of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3,
 // B=1 024, facts of one probability: 65 us, 58.4 so; facts in steps of 1/16 64 and 58.2; Sum-6, k = 5, B=12 000 560 and 516).
-// (Bound by the vector ALUs.  k = 5 costs about 35 instructions a tuple by the compiled code, none of them a choice; 65 with
+// (Bound by the vector ALUs.  k = 5 costs 33 instructions a tuple by the compiled code, none of them a choice; 65 with
 // probabilities and origins exchanged by compare and select, which the units take 1.9 ns a piece for, and repeated choices by one
-// condition longer.)
+// condition longer.  Of the 33, 19 are the list's maxima and minima in twice the time of the others, and 14 the products, the
+// origins, the addresses and the loop.)
 template <int K, int KA, bool FRESH>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,
@@ -180,8 +181,8 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                 tid_[y] = above ? tid_[y - 1] : gt[y] ? id : tid_[y];
             }
         };
-        uint32_t q0 = 0, q1 = 0;
-        if (there) q0 = l_ptr[c], q1 = l_ptr[c + 1];
+        const int like = min(c, S - 1);                     // lanes without a column go along with the last one
+        const uint32_t q0 = l_ptr[like], q1 = l_ptr[like + 1];
         auto list_of = [&](uint32_t r) { return reinterpret_cast<const float *>(reinterpret_cast<const char *>(cp) + (r & 0xffffu)); };
         auto fact_of = [&](uint32_t r) { return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(fp) + (r >> 16)); };
         if constexpr (FRESH) {
@@ -208,27 +209,25 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
             if (!plain) {
                 if (there) exact_column();
             } else {
-                // a tuple's record is read two tuples ahead and its operands one ahead; records past the last one are the
-                // spare ones behind every array, which name operands that exist
+                // The next tuple's record is on its way while this one is worked on; past the last one lies the next column's or a
+                // spare one.  (Read where it is used: Sum-5, k = 3, 1 024 samples 9.1 us, 8.2 so; Sum-6, k = 5, 12 000 57.2 and
+                // 56.5.  Operands read a tuple ahead as well cost moves and registers: 8.4, and 58.5.)
                 double top[K + 1];
 #pragma unroll
                 for (int x = 0; x <= K; ++x) top[x] = -1.0;
-                float pa[KA], pb;
-                auto fetch = [&](uint32_t r) {
-                    pb = fact_of(r);
-                    const float *list = list_of(r);
+                uint32_t rec = l_rec[q0];
+                asm volatile("" : "+v"(rec));       // (or the compiler folds this read and the loop's into one before its use)
+                int id = static_cast<int>(q0) << 3;
+                for (const uint32_t *next = l_rec + q0 + 1, *const end = l_rec + q1; next <= end; ++next, id += 8) {
+                    const float *list = list_of(rec);
+                    const float pb = fact_of(rec);
+                    float pa[KA];
 #pragma unroll
                     for (int x = 0; x < KA; ++x) pa[x] = list[x];
-                };
-                uint32_t rec = l_rec[q0], rec_next = l_rec[q0 + 1];
-                fetch(rec);
-                for (uint32_t q = q0; q < q1; ++q) {
+                    rec = *next;
                     double offer[KA];       // (an absent proof's is negative or -0: below every proof)
 #pragma unroll
-                    for (int x = 0; x < KA; ++x) offer[x] = key_of(pa[x] * pb, static_cast<int>(q) << 3 | x);
-                    rec = rec_next;
-                    rec_next = l_rec[q + 2];
-                    fetch(rec);
+                    for (int x = 0; x < KA; ++x) offer[x] = key_of(pa[x] * pb, id + x);
                     if constexpr (KA == K && K > 1) {
                         double best[K + 1];
                         best[0] = top[0];
@@ -258,7 +257,7 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                 // Equal probabilities among the kept ones: the masks' order, which only the result shows, unless a proof may be there
                 // twice.  The last of them as probable as the best that dropped out: the kept ones may be others.
                 again |= inner && (last || !distinct);
-                for (uint64_t todo = __ballot(again); __builtin_expect(todo != 0, 0); todo &= todo - 1) {
+                for (uint64_t todo = __ballot(again && there); __builtin_expect(todo != 0, 0); todo &= todo - 1) {
                     const int from = __builtin_ctzll(todo);
                     const Ranked r = rank_column<K, KA>(__builtin_amdgcn_readlane(static_cast<int>(q0), from), __builtin_amdgcn_readlane(static_cast<int>(q1), from), l_rec, cm, cp, fp);
 #pragma unroll
