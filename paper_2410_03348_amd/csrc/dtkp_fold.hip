@@ -130,7 +130,11 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
 // (Bound by the vector ALUs.  k = 5 costs 33 instructions a tuple by the compiled code, none of them a choice; 65 with
 // probabilities and origins exchanged by compare and select, which the units take 1.9 ns a piece for, and repeated choices by one
 // condition longer.  Of the 33, 19 are the list's maxima and minima in twice the time of the others, and 14 the products, the
-// origins, the addresses and the loop.)
+// origins, the addresses and the loop.  What a stage does besides is half as much again: a rank without a proof keeps an origin that can be
+// read and a word of ones for its mask and probability to be put together with, and only the last stage adds probabilities up: Sum-6,
+// k = 5, 12 000 samples 56.5 us, 55.6 so; k = 7, 1 024 samples 16.8 and 16.5.  A lone wavefront also waits for code that it has not
+// run yet, so it lies in the order it is run in: Sum-5, k = 3, 1 024 samples 8.4 us with the first stage's behind the others' and what
+// is seldom run between them, 8.1 so.)
 template <int K, int KA, bool FRESH>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,
@@ -142,8 +146,13 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
         const bool there = c < S;                           // (the others help where a column has ties)
         float tp[K];
         int tid_[K];
+        int gone[K];                                        // all bits: no proof
 #pragma unroll
         for (int x = 0; x < K; ++x) { tp[x] = -1.0f - x; tid_[x] = -1; }
+        auto by_origin = [&]() {
+#pragma unroll
+            for (int x = 0; x < K; ++x) gone[x] = tid_[x] >> 31, tid_[x] &= ~gone[x];
+        };
         auto mask_of = [&](int id) -> uint64_t {            // id = record << 3 | slot (at most DOL_MAX_K = 8 slots)
             const uint32_t r = l_rec[id >> 3];
             return cm[static_cast<int>((r & 0xffffu) >> 2) + (id & 7)] | (uint64_t(1) << (r >> 18));
@@ -206,8 +215,9 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                     }
                 }
             };
-            if (!plain) {
+            if (__builtin_expect(!plain, 0)) {
                 if (there) exact_column();
+                by_origin();
             } else {
                 // The next tuple's record is on its way while this one is worked on; past the last one lies the next column's or a
                 // spare one.  (Read where it is used: Sum-5, k = 3, 1 024 samples 9.1 us, 8.2 so; Sum-6, k = 5, 12 000 57.2 and
@@ -251,7 +261,7 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                 for (int x = 0; x < K; ++x) {
                     const int hi = __double2hiint(top[x]), next = __double2hiint(top[x + 1]);
                     tp[x] = __int_as_float(hi);
-                    tid_[x] = hi >= 0 ? __double2loint(top[x]) : -1;
+                    tid_[x] = __double2loint(top[x]);       // (0, or that of an absent proof, where there is none)
                     (x + 1 < K ? inner : again) |= hi == next && hi >= 0;
                 }
                 // Equal probabilities among the kept ones: the masks' order, which only the result shows, unless a proof may be there
@@ -264,13 +274,15 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                     for (int x = 0; x < K; ++x) {
                         const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r.p), x));
                         const int id = __builtin_amdgcn_readlane(r.id, x);
-                        if (lane == from) tp[x] = p, tid_[x] = id;
+                        if (lane == from) tp[x] = p, tid_[x] = max(id, 0);
                     }
                 }
+#pragma unroll
+                for (int x = 0; x < K; ++x) gone[x] = __float_as_int(tp[x]) >> 31;
             }
-        } else if (there) {
+        } else {
             uint32_t rec = l_rec[q0];
-            for (uint32_t q = q0; q < q1; ++q) {
+            for (uint32_t q = q0; q < (there ? q1 : q0); ++q) {
                 const int i = static_cast<int>((rec & 0xffffu) >> 2), fb = static_cast<int>(rec >> 18);
                 rec = l_rec[q + 1];                 // the next tuple's record is on its way while this one is worked on
                 const float pb = fp[fb];
@@ -297,25 +309,23 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                     else insert_untied(ok ? pr : kNone, id);
                 }
             }
+            by_origin();
         }
-        float sum = 0.0f;
         uint64_t wm[K];
 #pragma unroll
-        for (int x = 0; x < K; ++x) {
-            const bool present = tid_[x] >= 0;
-            const uint64_t m = mask_of(max(tid_[x], 0));
-            wm[x] = present ? m : kAbsent;
-            sum = present ? sum + tp[x] : sum;
-        }
+        for (int x = 0; x < K; ++x) wm[x] = mask_of(tid_[x]) | static_cast<uint64_t>(static_cast<int64_t>(gone[x]));
         // a Distribution of at most 64 symbols is replaced in place: every lane has read what it needs by now
         wave_lds_fence();
         if (!there) continue;
 #pragma unroll
         for (int x = 0; x < K; ++x) {
             nm[c * K + x] = wm[x];
-            np[c * K + x] = tid_[x] >= 0 ? tp[x] : -1.0f;
+            np[c * K + x] = __int_as_float((gone[x] & __float_as_int(-1.0f)) | (~gone[x] & __float_as_int(tp[x])));
         }
         if (last) {
+            float sum = 0.0f;
+#pragma unroll
+            for (int x = 0; x < K; ++x) sum = gone[x] ? sum : sum + tp[x];
             const float pr = fminf(sum, 1.0f);
             A.oprob[s * A.ldo + c] = pr;
             if (A.gfact) {                      // upstream gradient, gated by the clamp (passes on sum <= 1)
@@ -373,13 +383,13 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
             const int f = static_cast<int>(fact0[i]);
             bufm[i * K] = uint64_t(1) << f;
             bufp[i * K] = 1.0f * fp[f];
-#pragma unroll
-            for (int x = 1; x < K; ++x) { bufm[i * K + x] = kAbsent; bufp[i * K + x] = -1.0f; }
+            // (one proof to a symbol, and the first stage reads no more)
         }
     }
     wave_lds_fence();
     int S = 0;
-    for (int t = 1; t < A.n; ++t) {
+    auto stage = [&](int t, auto slots) {
+        constexpr int KA = decltype(slots)::value;
         const uint64_t *cm = bufm + ((t - 1) & 1) * flip;
         const float *cp = bufp + ((t - 1) & 1) * flip;
         uint64_t *nm = bufm + (t & 1) * flip;
@@ -387,16 +397,13 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         S = __builtin_amdgcn_readfirstlane(static_cast<int>(w[1 + 4 * t]));
         const uint32_t *l_ptr = w + w[2 + 4 * t], *l_rec = w + w[3 + 4 * t];
         const int kind = __builtin_amdgcn_readfirstlane(static_cast<int>(w[4 + 4 * t]));
-        const bool last = t == A.n - 1, fresh = kind != 0, distinct = kind == 2;
-        if (t == 1) {                       // the first operand is naturally initialised: one proof per symbol
-            if (fresh) dtkp_fold_stage<K, 1, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
-            else dtkp_fold_stage<K, 1, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
-        } else {
-            if (fresh) dtkp_fold_stage<K, K, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
-            else dtkp_fold_stage<K, K, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
-        }
+        const bool last = t == A.n - 1, distinct = kind == 2;
+        if (__builtin_expect(kind != 0, 1)) dtkp_fold_stage<K, KA, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
+        else dtkp_fold_stage<K, KA, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
         wave_lds_fence();
-    }
+    };
+    stage(1, std::integral_constant<int, 1>{});         // the first operand is naturally initialised: one proof per symbol
+    for (int t = 2; t < A.n; ++t) stage(t, std::integral_constant<int, K>{});
     // the proofs leave as one contiguous run per sample, in the order they have in LDS
     const uint64_t *fm = bufm + ((A.n - 1) & 1) * flip;
     {
@@ -430,7 +437,8 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
                 for (uint64_t r = mm; r; r &= r - 1) {
                     const int j = __builtin_ctzll(r);
                     const float pj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_fp), j));
-                    others = others * (j == lane ? 1.0f : pj);
+                    // (1 to the lane whose fact it is)
+                    others = others * (__builtin_amdgcn_inverse_ballot_w64(r & -r) ? 1.0f : pj);
                 }
                 if (mm & mine) acc = __builtin_fmaf(g, others, acc);
             }
