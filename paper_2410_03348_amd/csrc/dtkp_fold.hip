@@ -28,11 +28,12 @@ constexpr int kDfWaves = 4;             // most wavefronts (samples) of one work
 //           the records at r_t, one per tuple in column order: the first operand's list, counted in bytes of
 //           probabilities, | 4 x the second operand's FACT << 16 (spare records at the end so that the read-ahead
 //           stays inside)
-//   fresh_t = 1 or 2: every fact of input t lies above every fact of the inputs before it and shares no exclusion group
+//   fresh_t, bit 0: every fact of input t lies above every fact of the inputs before it and shares no exclusion group
 //           with any of them.  A proof of the running Distribution then never holds the new fact or a rival of it, and
 //           the product over ascending facts is the proof's stored probability times the new fact's: the stage needs
-//           no mask at all until its k winners are known.  2: and each input so far gives every symbol a fact of its own, none of them
+//           no mask at all until its k winners are known.  Bit 1: and each input so far gives every symbol a fact of its own, none of them
 //           known before: a proof says which symbols it is of, and no two symbols of a Distribution have one in common.
+//           Bit 2: twins work on the stage (dtkp_fold_stage).
 struct DtkpFoldArgs {
     int32_t n, batch, n_facts, max_s, n_words, wave_bytes;
     const int32_t *words;
@@ -135,15 +136,29 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
 // k = 5, 12 000 samples 56.5 us, 55.6 so; k = 7, 1 024 samples 16.8 and 16.5.  A lone wavefront also waits for code that it has not
 // run yet, so it lies in the order it is run in: Sum-5, k = 3, 1 024 samples 8.4 us with the first stage's behind the others' and what
 // is seldom run between them, 8.1 so.)
+// TWINS (twins, FRESH stages of at most 32 columns): the wavefront's halves have the same columns, each works on half of a column's tuples, and
+// the two lists become one as a tuple's and the running one do.  A list with another costs one to two tuples' worth: from
+// kTwinTuples on in the longest column it is the shorter way.  Of Sum-6's five stages two have 19 and 28 columns of up to 10 tuples: k = 5,
+// 12 000 samples 55.6 us, 52.7 so, 1 024 13.4 and 12.7; Sum-5, k = 3, 1 024 samples 8.1 and 7.4, 4 096 13.1 and 12.3.
+constexpr int kTwinTuples = 5;
+
+// x of the lane in the lower (upper) half of the wavefront that has this lane's place there
+__device__ __forceinline__ double key_of_half(double x, int upper)
+{
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(x), __double2hiint(x), false, false);
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(x), __double2loint(x), false, false);
+    return __hiloint2double(static_cast<int>(hi[upper]), static_cast<int>(lo[upper]));
+}
+
 template <int K, int KA, bool FRESH>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,
-                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain, bool distinct)
+                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain, bool distinct, bool twins)
 {
     const int lane = threadIdx.x & (kWave - 1);
     for (int base = 0; base < S; base += kWave) {
-        const int c = base + lane;
-        const bool there = c < S;                           // (the others help where a column has ties)
+        const int c = base + (twins ? lane % (kWave / 2) : lane);
+        const bool there = c < S && !(twins && lane >= kWave / 2);         // (the others help where a column has ties)
         float tp[K];
         int tid_[K];
         int gone[K];                                        // all bits: no proof
@@ -225,10 +240,12 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                 double top[K + 1];
 #pragma unroll
                 for (int x = 0; x <= K; ++x) top[x] = -1.0;
-                uint32_t rec = l_rec[q0];
+                uint32_t from = q0, to = q1;
+                if (twins) (lane < kWave / 2 ? to : from) = (q0 + q1 + 1) / 2;
+                uint32_t rec = l_rec[from];
                 asm volatile("" : "+v"(rec));       // (or the compiler folds this read and the loop's into one before its use)
-                int id = static_cast<int>(q0) << 3;
-                for (const uint32_t *next = l_rec + q0 + 1, *const end = l_rec + q1; next <= end; ++next, id += 8) {
+                int id = static_cast<int>(from) << 3;
+                for (const uint32_t *next = l_rec + from + 1, *const end = l_rec + to; next <= end; ++next, id += 8) {
                     const float *list = list_of(rec);
                     const float pb = fact_of(rec);
                     float pa[KA];
@@ -255,6 +272,14 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                             if (x < K) o = key_min(t, o);
                         }
                     }
+                }
+                if (twins) {
+                    double best[K + 1];
+#pragma unroll
+                    for (int x = 0; x <= K; ++x) best[x] = key_max(key_of_half(top[x], 0), key_of_half(top[K - x], 1));
+                    sort_valley<K + 1, K + 1>(best, 0);
+#pragma unroll
+                    for (int x = 0; x <= K; ++x) top[x] = best[x];
                 }
                 bool inner = false, again = false;
 #pragma unroll
@@ -397,9 +422,9 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         S = __builtin_amdgcn_readfirstlane(static_cast<int>(w[1 + 4 * t]));
         const uint32_t *l_ptr = w + w[2 + 4 * t], *l_rec = w + w[3 + 4 * t];
         const int kind = __builtin_amdgcn_readfirstlane(static_cast<int>(w[4 + 4 * t]));
-        const bool last = t == A.n - 1, distinct = kind == 2;
-        if (__builtin_expect(kind != 0, 1)) dtkp_fold_stage<K, KA, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
-        else dtkp_fold_stage<K, KA, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct);
+        const bool last = t == A.n - 1, distinct = kind & 2;
+        if (__builtin_expect(kind != 0, 1)) dtkp_fold_stage<K, KA, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct, kind & 4);
+        else dtkp_fold_stage<K, KA, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct, kind & 4);
         wave_lds_fence();
     };
     stage(1, std::integral_constant<int, 1>{});         // the first operand is naturally initialised: one proof per symbol
@@ -470,7 +495,7 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
     words[0] = n;
     int32_t s_prev = 0;
     int32_t fact_hi = -1;                   // highest fact of the inputs so far
-    bool distinct = true;                   // see fresh_t = 2
+    bool distinct = true;                   // see fresh_t, bit 1
     uint64_t facts_seen = 0;
     for (int t = 0; t < n; ++t) {
         const dol_dist *d = fold->inputs[t];
@@ -489,7 +514,7 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
                 for (int h = 0; h < prov->n_facts && ((mine >> f) & 1); ++h)
                     if (((facts_seen >> h) & 1) && prov->fact_group[h] == prov->fact_group[f]) fresh = false;
             distinct = distinct && fresh && __builtin_popcountll(mine) == d->n_sym;
-            words[4 + 4 * t] = distinct ? 2 : fresh ? 1 : 0;
+            words[4 + 4 * t] = distinct ? 3 : fresh ? 1 : 0;
             for (int32_t i = 0; i < d->n_sym; ++i) fact_hi = std::max(fact_hi, fos[i]);
             facts_seen |= mine;
         }
@@ -517,6 +542,9 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
             words.push_back(static_cast<int32_t>((4u * K * (ij & 0xffffu)) | (static_cast<uint32_t>(fos[ij >> 16]) << 18)));
         }
         words.insert(words.end(), 2, 0);
+        int32_t longest = 0;
+        for (int32_t c = 0; c < f->n_out; ++c) longest = std::max(longest, static_cast<int32_t>(f->h_col_ptr[c + 1] - f->h_col_ptr[c]));
+        if (words[4 + 4 * t] != 0 && f->n_out <= kWave / 2 && longest >= kTwinTuples) words[4 + 4 * t] |= 4;
         s_prev = p->s_last = f->n_out;
         p->max_s = std::max(p->max_s, f->n_out);
     }

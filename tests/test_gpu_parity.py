@@ -920,6 +920,40 @@ def test_fused_dtkp_fold_where_two_proofs_are_equally_probable(dol, k, shared):
     assert_close(host(out.prob), pr, "fold tag prob")
 
 
+@pytest.mark.parametrize("k", [1, 3, 8])
+@pytest.mark.parametrize("columns,longest", [(32, 4), (32, 5), (31, 6), (33, 6), (2, 90), (1, 5)])
+def test_fused_dtkp_fold_of_few_columns(dol, k, columns, longest):
+    """Stages at the edge of a wavefront's half, of columns of one tuple and of up to `longest` (odd and even, more candidates than
+    lanes), so that a column is one lane's or two lanes' work, some with ties.  Against the oracle's composition, bit for bit."""
+    nv, batch = (16, 12, 10), 9
+    n_facts = sum(nv)
+    first = np.cumsum((0,) + nv[:2])
+    fp = W.uniform01(33 + 7 * columns + longest, batch * n_facts).astype(np.float32).reshape(batch, n_facts)
+    fp[::4, 20], fp[::4, 3] = fp[::4, 24], fp[::4, 9]
+    facts = [(f + np.arange(m)).astype(np.int32) for f, m in zip(first, nv)]
+    grp = np.repeat(np.arange(3), nv).astype(np.int32)
+    lengths = np.minimum(longest, 1 + np.arange(columns) % longest) if columns > 2 else np.array([longest, 3][:columns])
+    lengths[columns // 2] = longest
+    m, _, _ = oracle.dtkp_init(facts[0], fp, k)
+    tables, n_cur = [], nv[0]
+    for t in (1, 2):
+        room = n_cur * nv[t]
+        n_out, per = (columns, lengths) if lengths.sum() <= room else (room // 3, np.full(room // 3, 3))
+        tab = np.full(room, -1, np.int32)
+        tab[np.argsort(W.uniform01(5 + t, room), kind="stable")[:per.sum()]] = np.repeat(np.arange(n_out), per)
+        tab = tab.reshape(n_cur, nv[t])
+        dm, _, _ = oracle.dtkp_init(facts[t], fp, k)
+        syms, m, pp, pr = oracle.dtkp_apply2(oracle.dense_to_triples(tab), n_cur, nv[t], k, grp, fp, m, dm)
+        tables.append(dol.FnTable.create_dense(tab))
+        n_cur = syms.size
+    out = dol.Dist.empty(syms, batch, k=k)
+    ins = [dol.Dist(np.arange(n, dtype=np.int32), torch.empty((batch, n), device="cuda")) for n in nv]
+    dol.dtkp_fold_apply2(dol.DtkpFold(ins, facts, tables, out), dol.Prov(dol.DTKP, k, dev(fp), grp))
+    np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), m)
+    np.testing.assert_array_equal(host(out.proof_prob), pp)
+    assert_close(host(out.prob), pr, "fold tag prob")
+
+
 # ---------------------------------------------------------------- config 5
 
 @pytest.mark.parametrize("batch,side,rounds", [(256, 32, 64), (33, 7, 20), (2, 3, 5)])
