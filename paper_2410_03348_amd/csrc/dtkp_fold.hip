@@ -33,7 +33,9 @@ constexpr int kDfWaves = 4;             // most wavefronts (samples) of one work
 //           the product over ascending facts is the proof's stored probability times the new fact's: the stage needs
 //           no mask at all until its k winners are known.  Bit 1: and each input so far gives every symbol a fact of its own, none of them
 //           known before: a proof says which symbols it is of, and no two symbols of a Distribution have one in common.
-//           Bit 2: twins work on the stage (dtkp_fold_stage).
+//           Bits 2 and 3: lanes help (dtkp_fold_stage), from bit 4 on: the stage's shares are the so many-th 64 words behind the others.
+enum Kind : int32_t { kFresh = 1, kDistinct = 2, kTwins = 4, kHelped = 8 };
+constexpr int kShareShift = 4;
 struct DtkpFoldArgs {
     int32_t n, batch, n_facts, max_s, n_words, wave_bytes;
     const int32_t *words;
@@ -46,6 +48,7 @@ struct DtkpFoldArgs {
     const float *gout;
     int64_t ldg;
     float *gfact;
+    int32_t n_shares;
 };
 
 // The K best distinct proofs of one column, by the whole wavefront: lane y < K ends with the y-th (id -1: none).  Lanes K .. 63 take
@@ -136,11 +139,31 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
 // k = 5, 12 000 samples 56.5 us, 55.6 so; k = 7, 1 024 samples 16.8 and 16.5.  A lone wavefront also waits for code that it has not
 // run yet, so it lies in the order it is run in: Sum-5, k = 3, 1 024 samples 8.4 us with the first stage's behind the others' and what
 // is seldom run between them, 8.1 so.)
-// TWINS (twins, FRESH stages of at most 32 columns): the wavefront's halves have the same columns, each works on half of a column's tuples, and
-// the two lists become one as a tuple's and the running one do.  A list with another costs one to two tuples' worth: from
-// kTwinTuples on in the longest column it is the shorter way.  Of Sum-6's five stages two have 19 and 28 columns of up to 10 tuples: k = 5,
-// 12 000 samples 55.6 us, 52.7 so, 1 024 13.4 and 12.7; Sum-5, k = 3, 1 024 samples 8.1 and 7.4, 4 096 13.1 and 12.3.
-constexpr int kTwinTuples = 5;
+// Where a stage has fewer columns than the wavefront has lanes the others help (FRESH stages): a helper works on the second half of a
+// column's tuples, and the two lists become one as a tuple's and the running one do, which costs up to two tuples' worth.
+//   few samples: stages of at most 32 columns are worked on by twins, the wavefront's halves have the same columns.  Of Sum-6's five stages
+//   two have 19 and 28 columns of up to 10 tuples: k = 5, 12 000 samples 55.6 us, 52.7 so, 1 024 13.4 and 12.7; Sum-5, k = 3, 1 024 samples
+//   8.1 and 7.4, 4 096 13.1 and 12.3.
+//   MANY: a lane looks its share up (Share), and of more columns the longest are helped with (of 37 all 27 of more than five tuples).  That
+//   takes a trip to LDS for the share and one for the lists, which several wavefronts on a SIMD hide: Sum-6, k = 5, 12 000 samples 52.5
+//   and 50.0, k = 7 73.0 and 68.6, Sum-5, k = 3, 12 000 28.0 and 26.6, 4 096 12.3 and 12.0, but 2 048 8.6 and 8.7, 1 024 7.4 and 7.7; Sum-3,
+//   k = 5, 2 048 7.7 and 8.0.  (Both ways in one kernel take 76 registers, one wavefront less to a SIMD: 52.6.)
+constexpr int kListCost = 2;            // tuples saved that two lists are worth
+constexpr int kManySamples = 3072;      // three to a SIMD
+
+struct Share {                          // a lane's, in one word
+    enum Role : uint32_t { kWhole, kFirstHalf, kHelper, kIdle };
+    uint32_t word;
+    static __host__ __device__ uint32_t pack(uint32_t col, uint32_t partner, Role role) { return col | partner << 8 | role << 16; }
+    __device__ __forceinline__ int col() const { return word & 0xff; }
+    __device__ __forceinline__ int partner() const { return word >> 8 & 0xff; }
+    __device__ __forceinline__ uint32_t role() const { return word >> 16; }
+};
+
+__device__ __forceinline__ double key_of_lane(double x, int lane)
+{
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(4 * lane, __double2hiint(x)), __builtin_amdgcn_ds_bpermute(4 * lane, __double2loint(x)));
+}
 
 // x of the lane in the lower (upper) half of the wavefront that has this lane's place there
 __device__ __forceinline__ double key_of_half(double x, int upper)
@@ -150,15 +173,17 @@ __device__ __forceinline__ double key_of_half(double x, int upper)
     return __hiloint2double(static_cast<int>(hi[upper]), static_cast<int>(lo[upper]));
 }
 
-template <int K, int KA, bool FRESH>
+template <int K, int KA, bool FRESH, bool MANY>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,
-                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain, bool distinct, bool twins)
+                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain, int kind, const uint32_t *shares)
 {
+    const bool distinct = kind & kDistinct, helped = FRESH && (kind & (MANY ? kHelped : kTwins));
     const int lane = threadIdx.x & (kWave - 1);
     for (int base = 0; base < S; base += kWave) {
-        const int c = base + (twins ? lane % (kWave / 2) : lane);
-        const bool there = c < S && !(twins && lane >= kWave / 2);         // (the others help where a column has ties)
+        const Share mine{MANY && helped ? shares[lane] : Share::pack(lane, 0, Share::kWhole)};
+        const int c = base + (MANY ? mine.col() : helped ? lane % (kWave / 2) : lane);
+        const bool there = c < S && (MANY ? mine.role() < Share::kHelper : !(helped && lane >= kWave / 2));     // (all help where a column has ties)
         float tp[K];
         int tid_[K];
         int gone[K];                                        // all bits: no proof
@@ -241,7 +266,15 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
 #pragma unroll
                 for (int x = 0; x <= K; ++x) top[x] = -1.0;
                 uint32_t from = q0, to = q1;
-                if (twins) (lane < kWave / 2 ? to : from) = (q0 + q1 + 1) / 2;
+                if (helped) {
+                    const uint32_t mid = (q0 + q1 + 1) / 2;
+                    if constexpr (MANY) {
+                        to = mine.role() == Share::kFirstHalf ? mid : mine.role() == Share::kIdle ? q0 : q1;
+                        from = mine.role() == Share::kHelper ? mid : q0;
+                    } else {
+                        (lane < kWave / 2 ? to : from) = mid;
+                    }
+                }
                 uint32_t rec = l_rec[from];
                 asm volatile("" : "+v"(rec));       // (or the compiler folds this read and the loop's into one before its use)
                 int id = static_cast<int>(from) << 3;
@@ -273,13 +306,23 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                         }
                     }
                 }
-                if (twins) {
-                    double best[K + 1];
+                if (helped) {
+                    auto join = [&](auto of_first, auto of_helper) {
+                        double best[K + 1];
 #pragma unroll
-                    for (int x = 0; x <= K; ++x) best[x] = key_max(key_of_half(top[x], 0), key_of_half(top[K - x], 1));
-                    sort_valley<K + 1, K + 1>(best, 0);
+                        for (int x = 0; x <= K; ++x) best[x] = key_max(of_first(x), of_helper(K - x));
+                        sort_valley<K + 1, K + 1>(best, 0);
 #pragma unroll
-                    for (int x = 0; x <= K; ++x) top[x] = best[x];
+                        for (int x = 0; x <= K; ++x) top[x] = best[x];
+                    };
+                    if constexpr (MANY) {
+                        double other[K + 1];
+#pragma unroll
+                        for (int x = 0; x <= K; ++x) other[x] = key_of_lane(top[x], mine.partner());
+                        if (mine.role() == Share::kFirstHalf) join([&](int x) { return top[x]; }, [&](int x) { return other[x]; });
+                    } else {
+                        join([&](int x) { return key_of_half(top[x], 0); }, [&](int x) { return key_of_half(top[x], 1); });
+                    }
                 }
                 bool inner = false, again = false;
 #pragma unroll
@@ -363,7 +406,7 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
     }
 }
 
-template <int K>
+template <int K, bool MANY>
 __global__ void __launch_bounds__(kDfWaves * kWave)
 dtkp_fold_kernel(const DtkpFoldArgs A)
 {
@@ -375,7 +418,8 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
     const uint32_t *w = wl;
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int bufs = A.max_s > kWave ? 2 : 1, flip = (bufs - 1) * A.max_s * K;
-    unsigned char *mine_lds = lds_raw + 64 * sizeof(uint64_t) + sizeof(uint32_t) * A.n_words + static_cast<size_t>(wave) * A.wave_bytes;
+    const int n_words = A.n_words + (MANY ? A.n_shares : 0);
+    unsigned char *mine_lds = lds_raw + 64 * sizeof(uint64_t) + sizeof(uint32_t) * n_words + static_cast<size_t>(wave) * A.wave_bytes;
     uint64_t *bufm = reinterpret_cast<uint64_t *>(mine_lds);
     float *bufp = reinterpret_cast<float *>(bufm + bufs * A.max_s * K);
     float *fp = bufp + bufs * A.max_s * K;
@@ -387,7 +431,7 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         // this costs is round trips
         uint4 *dst = reinterpret_cast<uint4 *>(wl);
         const uint4 *src = reinterpret_cast<const uint4 *>(A.words);
-        const int n4 = A.n_words / 4, step = blockDim.x;      // the host pads the array to whole 16-byte pieces
+        const int n4 = n_words / 4, step = blockDim.x;      // the host pads the array to whole 16-byte pieces
         for (int base = threadIdx.x; base < n4; base += 2 * step) {
             const uint4 v0 = src[base], v1 = src[min(base + step, n4 - 1)];
             dst[base] = v0;
@@ -422,9 +466,10 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         S = __builtin_amdgcn_readfirstlane(static_cast<int>(w[1 + 4 * t]));
         const uint32_t *l_ptr = w + w[2 + 4 * t], *l_rec = w + w[3 + 4 * t];
         const int kind = __builtin_amdgcn_readfirstlane(static_cast<int>(w[4 + 4 * t]));
-        const bool last = t == A.n - 1, distinct = kind & 2;
-        if (__builtin_expect(kind != 0, 1)) dtkp_fold_stage<K, KA, true>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct, kind & 4);
-        else dtkp_fold_stage<K, KA, false>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, distinct, kind & 4);
+        const bool last = t == A.n - 1;
+        const uint32_t *shares = w + A.n_words + kWave * (kind >> kShareShift);
+        if (__builtin_expect(kind & kFresh, kFresh)) dtkp_fold_stage<K, KA, true, MANY>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, kind, shares);
+        else dtkp_fold_stage<K, KA, false, MANY>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, kind, shares);
         wave_lds_fence();
     };
     stage(1, std::integral_constant<int, 1>{});         // the first operand is naturally initialised: one proof per symbol
@@ -483,16 +528,44 @@ namespace {
 struct DtkpFoldPlan {
     DevArray<int32_t> words;
     DevArray<uint64_t> rival;
-    int32_t n_words = 0, max_s = 0, s_last = 0;
+    int32_t n_words = 0, n_shares = 0, max_s = 0, s_last = 0;
 };
 
 Cache<DtkpFoldPlan> &g_fold_plans = *new Cache<DtkpFoldPlan>;      // never destroyed, as the other plan caches
+
+// How a stage's lanes help (Kind), and their shares where they do: the columns in their order, and the other lanes help with those of
+// more than `most` tuples, which is the smallest number so that all of these get one.
+int32_t add_shares(const dol_fn_table *f, std::vector<int32_t> &shares)
+{
+    const int S = f->n_out;
+    if (S > kWave) return 0;
+    auto length = [&](int c) { return static_cast<int>(f->h_col_ptr[c + 1] - f->h_col_ptr[c]); };
+    auto above = [&](int most) {
+        int count = 0;
+        for (int c = 0; c < S; ++c) count += length(c) > most;
+        return count;
+    };
+    int longest = 0;
+    for (int c = 0; c < S; ++c) longest = std::max(longest, length(c));
+    int most = (longest + 1) / 2;
+    while (S + above(most) > kWave) ++most;
+    if (longest - most < kListCost) return 0;
+    const size_t at = shares.size();
+    shares.resize(at + kWave, static_cast<int32_t>(Share::pack(S - 1, 0, Share::kIdle)));
+    for (int c = 0, helper = S; c < S; ++c) {
+        const bool two = length(c) > most;
+        shares[at + c] = static_cast<int32_t>(Share::pack(c, two ? helper : c, two ? Share::kFirstHalf : Share::kWhole));
+        if (two) shares[at + helper++] = static_cast<int32_t>(Share::pack(c, c, Share::kHelper));
+    }
+    return S <= kWave / 2 ? kHelped | kTwins : kHelped;
+}
 
 dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldPlan *p)
 {
     const int n = fold->n_inputs, K = prov->k;
     std::vector<int32_t> words(1 + 4 * static_cast<size_t>(n), 0);
     words[0] = n;
+    std::vector<int32_t> shares;
     int32_t s_prev = 0;
     int32_t fact_hi = -1;                   // highest fact of the inputs so far
     bool distinct = true;                   // see fresh_t, bit 1
@@ -514,7 +587,7 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
                 for (int h = 0; h < prov->n_facts && ((mine >> f) & 1); ++h)
                     if (((facts_seen >> h) & 1) && prov->fact_group[h] == prov->fact_group[f]) fresh = false;
             distinct = distinct && fresh && __builtin_popcountll(mine) == d->n_sym;
-            words[4 + 4 * t] = distinct ? 3 : fresh ? 1 : 0;
+            words[4 + 4 * t] = (fresh ? kFresh : 0) | (distinct ? kDistinct : 0);
             for (int32_t i = 0; i < d->n_sym; ++i) fact_hi = std::max(fact_hi, fos[i]);
             facts_seen |= mine;
         }
@@ -542,14 +615,17 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
             words.push_back(static_cast<int32_t>((4u * K * (ij & 0xffffu)) | (static_cast<uint32_t>(fos[ij >> 16]) << 18)));
         }
         words.insert(words.end(), 2, 0);
-        int32_t longest = 0;
-        for (int32_t c = 0; c < f->n_out; ++c) longest = std::max(longest, static_cast<int32_t>(f->h_col_ptr[c + 1] - f->h_col_ptr[c]));
-        if (words[4 + 4 * t] != 0 && f->n_out <= kWave / 2 && longest >= kTwinTuples) words[4 + 4 * t] |= 4;
+        if (words[4 + 4 * t] & kFresh) {
+            words[4 + 4 * t] |= static_cast<int32_t>(shares.size() / kWave) << kShareShift;
+            words[4 + 4 * t] |= add_shares(f, shares);
+        }
         s_prev = p->s_last = f->n_out;
         p->max_s = std::max(p->max_s, f->n_out);
     }
     while (words.size() % 4) words.push_back(0);
     p->n_words = static_cast<int32_t>(words.size());
+    p->n_shares = static_cast<int32_t>(shares.size());
+    words.insert(words.end(), shares.begin(), shares.end());
     std::vector<uint64_t> rival(static_cast<size_t>(prov->n_facts), 0);      // the other facts of each fact's exclusion group
     for (int f = 0; f < prov->n_facts && prov->fact_group; ++f)
         for (int h = 0; h < prov->n_facts; ++h)
@@ -612,6 +688,7 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
     const int32_t s_last = plan->s_last;
     A.max_s = plan->max_s;
     A.n_words = plan->n_words;
+    A.n_shares = plan->n_shares;
     A.words = plan->words.ptr;
     A.rival = plan->rival.ptr;
     const dol_dist *o = fold->out;
@@ -624,7 +701,10 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
     // k = 5, so four of them together fit a compute unit 28 times over instead of 11)
     int waves = kDfWaves;
     while (waves > 1 && shared_bytes + waves * wave_bytes > 64 * 1024) waves /= 2;
-    const size_t lds = shared_bytes + waves * wave_bytes;
+    // (kManySamples: where the shares' two trips are hidden, see there)
+    const size_t share_bytes = sizeof(uint32_t) * static_cast<size_t>(plan->n_shares);
+    const bool many = A.batch > kManySamples && share_bytes > 0 && shared_bytes + share_bytes + waves * wave_bytes <= 64 * 1024;
+    const size_t lds = shared_bytes + (many ? share_bytes : 0) + waves * wave_bytes;
     if (lds > 64 * 1024) return fail(DOL_EUNSUPPORTED, "the fold needs %zu bytes of LDS per sample, more than 65536", lds);
     A.wave_bytes = static_cast<int32_t>(wave_bytes);
     if (A.batch == 0) return DOL_OK;
@@ -645,17 +725,24 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(A.batch) + waves - 1) / waves)), block(static_cast<unsigned>(waves * kWave));
-#define DOL_DF(KK) hipLaunchKernelGGL(dtkp_fold_kernel<KK>, grid, block, lds, st, A)
-    switch (K) {
-    case 1: DOL_DF(1); break;
-    case 2: DOL_DF(2); break;
-    case 3: DOL_DF(3); break;
-    case 4: DOL_DF(4); break;
-    case 5: DOL_DF(5); break;
-    case 6: DOL_DF(6); break;
-    case 7: DOL_DF(7); break;
-    default: DOL_DF(8); break;
+#define DOL_DF(KK, MANY) hipLaunchKernelGGL((dtkp_fold_kernel<KK, MANY>), grid, block, lds, st, A)
+#define DOL_DF_ALL(MANY)                \
+    switch (K) {                        \
+    case 1: DOL_DF(1, MANY); break;     \
+    case 2: DOL_DF(2, MANY); break;     \
+    case 3: DOL_DF(3, MANY); break;     \
+    case 4: DOL_DF(4, MANY); break;     \
+    case 5: DOL_DF(5, MANY); break;     \
+    case 6: DOL_DF(6, MANY); break;     \
+    case 7: DOL_DF(7, MANY); break;     \
+    default: DOL_DF(8, MANY); break;    \
     }
+    if (many) {
+        DOL_DF_ALL(true)
+    } else {
+        DOL_DF_ALL(false)
+    }
+#undef DOL_DF_ALL
 #undef DOL_DF
     DOL_HIP(hipGetLastError());
     return DOL_OK;

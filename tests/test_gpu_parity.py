@@ -921,10 +921,11 @@ def test_fused_dtkp_fold_where_two_proofs_are_equally_probable(dol, k, shared):
 
 
 @pytest.mark.parametrize("k", [1, 3, 8])
-@pytest.mark.parametrize("columns,longest", [(32, 4), (32, 5), (31, 6), (33, 6), (2, 90), (1, 5)])
-def test_fused_dtkp_fold_of_few_columns(dol, k, columns, longest):
-    """Stages at the edge of a wavefront's half, of columns of one tuple and of up to `longest` (odd and even, more candidates than
-    lanes), so that a column is one lane's or two lanes' work, some with ties.  Against the oracle's composition, bit for bit."""
+@pytest.mark.parametrize("columns,longest", [(32, 4), (32, 5), (31, 6), (33, 6), (37, 7), (62, 6), (63, 9), (2, 90), (1, 5)])
+def test_fused_dtkp_fold_whose_lanes_help(dol, k, columns, longest):
+    """Stages of fewer columns than lanes, at the edge of a wavefront's half and of all of it, columns of one tuple and of up to `longest`
+    (odd and even, more candidates than lanes), so that a column is one lane's or two lanes' work, some with ties; for few samples
+    and, the same ones over and over, for many.  Against the oracle's composition, bit for bit."""
     nv, batch = (16, 12, 10), 9
     n_facts = sum(nv)
     first = np.cumsum((0,) + nv[:2])
@@ -946,12 +947,13 @@ def test_fused_dtkp_fold_of_few_columns(dol, k, columns, longest):
         syms, m, pp, pr = oracle.dtkp_apply2(oracle.dense_to_triples(tab), n_cur, nv[t], k, grp, fp, m, dm)
         tables.append(dol.FnTable.create_dense(tab))
         n_cur = syms.size
-    out = dol.Dist.empty(syms, batch, k=k)
-    ins = [dol.Dist(np.arange(n, dtype=np.int32), torch.empty((batch, n), device="cuda")) for n in nv]
-    dol.dtkp_fold_apply2(dol.DtkpFold(ins, facts, tables, out), dol.Prov(dol.DTKP, k, dev(fp), grp))
-    np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), m)
-    np.testing.assert_array_equal(host(out.proof_prob), pp)
-    assert_close(host(out.prob), pr, "fold tag prob")
+    for tiles in (1, 345):
+        out = dol.Dist.empty(syms, batch * tiles, k=k)
+        ins = [dol.Dist(np.arange(n, dtype=np.int32), torch.empty((batch * tiles, n), device="cuda")) for n in nv]
+        dol.dtkp_fold_apply2(dol.DtkpFold(ins, facts, tables, out), dol.Prov(dol.DTKP, k, dev(np.tile(fp, (tiles, 1))), grp))
+        np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), np.tile(m, (tiles, 1, 1)))
+        np.testing.assert_array_equal(host(out.proof_prob), np.tile(pp, (tiles, 1, 1)))
+        assert_close(host(out.prob), np.tile(pr, (tiles, 1)), "fold tag prob")
 
 
 # ---------------------------------------------------------------- config 5
