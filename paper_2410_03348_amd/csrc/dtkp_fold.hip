@@ -58,6 +58,13 @@ struct DtkpFoldArgs {
 // a time, through code that no wavefront had fetched yet, a column took 4 us (k = 3) to 60 (k = 7) and the others of the stage with it:
 // Sum-6, k = 5, 2 048 samples 50 us with one such sample and 17.7 without any, k = 7 83 and 22.6, Sum-5, k = 3, 1 024 12.9 and 9.1;
 // so 28 and 17.8, 51 and 22.6, 9.5 and 9.1.)
+// One column after the other, though, where a lane each does all of a stage's at once: where more than kManyTies of them are to be ranked
+// they are exact_column's.  Logits twelve and thirty times as far apart, whose products underflow, us, columns by the wavefront up to 2, 4, 8,
+// 16, all: Sum-5, k = 3, 1 024 samples 20.2 20.4 23.8 27.4 27.3 and 63 63 69 144 217; Sum-6, k = 5, 12 000 153 145 169 225 224 and 504 507 516
+// 1 027 2 069; k = 7, 6 000 248 248 239 337 337 and 657 658 666 1 308 3 465; one sample with two equal facts, k = 5, 2 048 28 28 25 25 25.
+template <int K>
+constexpr int kManyTies = K <= 5 ? 4 : 8;
+
 struct Ranked {
     float p;
     int id;
@@ -127,8 +134,8 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
 // list times one factor, i.e. in descending order already: the k + 1 best of both lists are the elementwise maxima of one
 // and the other reversed, sorted again by a short network.  Masks matter only where probabilities are equal: two of the kept
 // ones, or the last one and the best that dropped out, which is what the list's entry behind the k-th holds (of all that
-// dropped out on the way none is larger).  Such a column is ranked again by the whole wavefront (rank_column); candidate by candidate
-// (exact_column) is every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where an
+// dropped out on the way none is larger).  Such a column is ranked again by the whole wavefront (rank_column), or where there are many
+// candidate by candidate (exact_column), as is every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where an
 // eighth of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3,
 // B=1 024, facts of one probability: 65 us, 58.4 so; facts in steps of 1/16 64 and 58.2; Sum-6, k = 5, B=12 000 560 and 516).
 // (Bound by the vector ALUs.  k = 5 costs 33 instructions a tuple by the compiled code, none of them a choice; 65 with
@@ -335,7 +342,16 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                 // Equal probabilities among the kept ones: the masks' order, which only the result shows, unless a proof may be there
                 // twice.  The last of them as probable as the best that dropped out: the kept ones may be others.
                 again |= inner && (last || !distinct);
-                for (uint64_t todo = __ballot(again && there); __builtin_expect(todo != 0, 0); todo &= todo - 1) {
+                uint64_t todo = __ballot(again && there);
+                if (__builtin_expect(__builtin_popcountll(todo) > kManyTies<K>, 0)) {
+                    todo = 0;
+                    if (again && there) {
+                        exact_column();
+#pragma unroll
+                        for (int x = 0; x < K; ++x) tp[x] = tid_[x] < 0 ? -1.0f : tp[x], tid_[x] = max(tid_[x], 0);
+                    }
+                }
+                for (; __builtin_expect(todo != 0, 0); todo &= todo - 1) {
                     const int from = __builtin_ctzll(todo);
                     const Ranked r = rank_column<K, KA>(__builtin_amdgcn_readlane(static_cast<int>(q0), from), __builtin_amdgcn_readlane(static_cast<int>(q1), from), l_rec, cm, cp, fp);
 #pragma unroll

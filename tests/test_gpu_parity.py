@@ -920,6 +920,36 @@ def test_fused_dtkp_fold_where_two_proofs_are_equally_probable(dol, k, shared):
     assert_close(host(out.prob), pr, "fold tag prob")
 
 
+@pytest.mark.parametrize("k", [1, 3, 5, 7])
+def test_fused_dtkp_fold_where_many_columns_have_ties(dol, k):
+    """Samples with no, one, several and all columns of a stage to be ranked by their masks, facts of different probabilities all the
+    same: products of powers of two, products that underflow.  Against the oracle's composition, bit for bit."""
+    batch, nv, n = 48, 10, 4
+    n_facts = n * nv
+    fp = W.uniform01(57 + k, batch * n_facts).astype(np.float32).reshape(batch, n_facts)
+    for r in range(batch - 12):
+        for f in range(r % 12):
+            fp[r, nv + 3 * f % 30] = fp[r, nv + (3 * f + 17) % 30]
+    fp[-12:-6] = np.float32(2.0) ** -(1 + np.arange(n_facts) % nv)
+    fp[-6:] = fp[-6:] ** 60
+    facts = [(nv * t + np.arange(nv)).astype(np.int32) for t in range(n)]
+    grp = (np.arange(n_facts) // nv).astype(np.int32)
+    sym = np.arange(nv, dtype=np.int32)
+    m, _, _ = oracle.dtkp_init(facts[0], fp, k)
+    syms, tables = sym, []
+    for t in range(1, n):
+        dm, _, _ = oracle.dtkp_init(facts[t], fp, k)
+        tab = W.sum_table(syms, sym)
+        syms, m, pp, pr = oracle.dtkp_apply2(oracle.dense_to_triples(tab), syms.size, nv, k, grp, fp, m, dm)
+        tables.append(dol.FnTable.create_dense(tab))
+    out = dol.Dist.empty(syms, batch, k=k)
+    digits = [dol.Dist(sym, torch.empty((batch, nv), device="cuda")) for _ in range(n)]
+    dol.dtkp_fold_apply2(dol.DtkpFold(digits, facts, tables, out), dol.Prov(dol.DTKP, k, dev(fp), grp))
+    np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), m)
+    np.testing.assert_array_equal(host(out.proof_prob), pp)
+    assert_close(host(out.prob), pr, "fold tag prob")
+
+
 @pytest.mark.parametrize("k", [1, 3, 8])
 @pytest.mark.parametrize("columns,longest", [(32, 4), (32, 5), (31, 6), (33, 6), (37, 7), (62, 6), (63, 9), (2, 90), (1, 5)])
 def test_fused_dtkp_fold_whose_lanes_help(dol, k, columns, longest):
