@@ -1,8 +1,8 @@
 // Fused left fold of Apply under DTKP-AM (the loop of Fig. 2 with the top-k proofs provenance of Sec. 3.2 /
 // App. A) over naturally initialised inputs: symbol i of input t carries the single proof {fact_of_sym[t][i]}.
 // One wavefront owns a sample: the fact probabilities and the running Distribution's proofs (S x k masks and
-// probabilities) live in LDS, a lane owns an output symbol, streams the candidates of its tuples through a k-entry
-// sorted list in registers and writes the list back to LDS for the next stage.  Up to four wavefronts form a
+// probabilities) live in LDS, a lane (two where the wavefront has them to spare) owns an output symbol, streams the candidates of its
+// tuples through a k-entry sorted list in registers and writes the list back to LDS for the next stage.  Up to four wavefronts form a
 // workgroup and share one copy of the symbol side.  HBM sees the fact probabilities once and the final Distribution
 // once.  Optionally the gradient of the final tag probabilities w.r.t. the fact probabilities follows in the same
 // launch (lane f owns fact f).
@@ -135,17 +135,17 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
 // and the other reversed, sorted again by a short network.  Masks matter only where probabilities are equal: two of the kept
 // ones, or the last one and the best that dropped out, which is what the list's entry behind the k-th holds (of all that
 // dropped out on the way none is larger).  Such a column is ranked again by the whole wavefront (rank_column), or where there are many
-// candidate by candidate (exact_column), as is every column of a sample (plain = false) with a fact whose probability is negative, -0 or no finite number, or where an
-// eighth of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3,
+// candidate by candidate (exact_column), as is every column of a sample (plain = false) with a fact whose probability is negative, -0
+// or no finite number, or where an eighth of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3,
 // B=1 024, facts of one probability: 65 us, 58.4 so; facts in steps of 1/16 64 and 58.2; Sum-6, k = 5, B=12 000 560 and 516).
 // (Bound by the vector ALUs.  k = 5 costs 33 instructions a tuple by the compiled code, none of them a choice; 65 with
 // probabilities and origins exchanged by compare and select, which the units take 1.9 ns a piece for, and repeated choices by one
 // condition longer.  Of the 33, 19 are the list's maxima and minima in twice the time of the others, and 14 the products, the
 // origins, the addresses and the loop.  What a stage does besides is half as much again: a rank without a proof keeps an origin that can be
 // read and a word of ones for its mask and probability to be put together with, and only the last stage adds probabilities up: Sum-6,
-// k = 5, 12 000 samples 56.5 us, 55.6 so; k = 7, 1 024 samples 16.8 and 16.5.  A lone wavefront also waits for code that it has not
-// run yet, so it lies in the order it is run in: Sum-5, k = 3, 1 024 samples 8.4 us with the first stage's behind the others' and what
-// is seldom run between them, 8.1 so.)
+// k = 5, 12 000 samples 56.5 us, 55.6 so; k = 7, 1 024 samples 16.8 and 16.5.  The code lies in the order it is run in, with what is seldom
+// run behind: Sum-5, k = 3, 1 024 samples 8.1 us so, 8.4 with the first stage's behind the others' and the seldom run between them.  Where
+// the compiled code lies moves small batches by some 2 % either way.)
 // Where a stage has fewer columns than the wavefront has lanes the others help (FRESH stages): a helper works on the second half of a
 // column's tuples, and the two lists become one as a tuple's and the running one do, which costs up to two tuples' worth.
 //   few samples: stages of at most 32 columns are worked on by twins, the wavefront's halves have the same columns.  Of Sum-6's five stages
