@@ -950,6 +950,31 @@ def test_fused_dtkp_fold_where_many_columns_have_ties(dol, k):
     assert_close(host(out.prob), pr, "fold tag prob")
 
 
+@pytest.mark.parametrize("batch,n_sym,n_facts,k", [(1, 1, 1, 1), (1, 1100, 63, 3), (3, 64, 8, 2), (40, 65, 9, 3), (300, 130, 41, 5), (2, 63, 7, 8)])
+def test_dtkp_gradient_of_any_number_of_facts(dol, batch, n_sym, n_facts, k):
+    """The facts in whole and broken eights, one workgroup to a sample and several, one wavefront and all, facts of probability 0 among
+    them.  Against the oracle (1e-5: a sum of at most n_sym * k products and one division)."""
+    pick = W.splitmix64(91 + n_facts, np.arange(3 * batch * n_sym * k)).reshape(batch, n_sym, k, 3) % np.uint64(n_facts)
+    masks = np.bitwise_or.reduce(np.uint64(1) << pick, axis=-1)
+    masks[:, ::5, k - 1] = oracle.ABSENT
+    for x in range(1, k):                       # (no proof twice in a list)
+        for y in range(x):
+            masks[..., x] = np.where(masks[..., x] == masks[..., y], oracle.ABSENT, masks[..., x])
+    fp = (0.02 + 0.3 * W.uniform01(92, batch * n_facts)).astype(np.float32).reshape(batch, n_facts)
+    fp[::2, n_facts // 2] = 0.0
+    prob = np.ones(masks.shape, np.float32)
+    for f in range(n_facts):
+        prob = np.where((masks >> np.uint64(f)) & np.uint64(1) == 1, prob * fp[:, f, None, None], prob)
+    prob[masks == oracle.ABSENT] = 0.0
+    g = W.normal(93, batch * n_sym).astype(np.float32).reshape(batch, n_sym)
+    dist = dol.Dist.empty(np.arange(n_sym, dtype=np.int32), batch, k=k)
+    dist.proof_mask.copy_(dev(masks.view(np.int64)))
+    dist.proof_prob.copy_(dev(prob))
+    gf = torch.full((batch, n_facts), 7.0, device="cuda")
+    dol.dtkp_backward(dist, dol.Prov(dol.DTKP, k, dev(fp), None), dev(g), gf)
+    assert_close(host(gf), oracle.dtkp_prob_bwd(masks, fp, g), "dtkp gradient")
+
+
 @pytest.mark.parametrize("k", [1, 3, 8])
 @pytest.mark.parametrize("columns,longest", [(32, 4), (32, 5), (31, 6), (33, 6), (37, 7), (62, 6), (63, 9), (2, 90), (1, 5)])
 def test_fused_dtkp_fold_whose_lanes_help(dol, k, columns, longest):
