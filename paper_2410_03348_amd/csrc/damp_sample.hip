@@ -118,8 +118,7 @@ __device__ __forceinline__ int wave_number() { return __builtin_amdgcn_readfirst
 
 __device__ __forceinline__ float wave_sum(float x)
 {
-    x = reduce32<AddOp>(x);
-    return x + __shfl_xor(x, 32, kWave);
+    return with_lane32<AddOp>(reduce32<AddOp>(x));
 }
 
 // Whether the sum `acc` of n terms, added up by `lanes` lanes, is so close to 1 that only the defining order can tell on which

@@ -48,6 +48,21 @@ __device__ __forceinline__ int dpp_i(int x)
 // other row of 16.  Every lane of the wavefront must be active.
 struct AddOp { __device__ static float f(float a, float b) { return a + b; } };
 struct MaxOp { __device__ static float f(float a, float b) { return fmaxf(a, b); } };
+// Op of this lane's x and that of the lane 16 (32) away, two instructions; through LDS (ds_bpermute) it is a trip of some 100 clocks.
+template <typename Op>
+__device__ __forceinline__ float with_lane16(float x)
+{
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return Op::f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+template <typename Op>
+__device__ __forceinline__ float with_lane32(float x)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return Op::f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
 template <typename Op>
 __device__ __forceinline__ float reduce32(float x)
 {
@@ -55,8 +70,7 @@ __device__ __forceinline__ float reduce32(float x)
     x = Op::f(x, dpp<0x4E>(x));          // quad_perm [2,3,0,1]
     x = Op::f(x, dpp<0x141>(x));         // row_half_mirror
     x = Op::f(x, dpp<0x140>(x));         // row_mirror
-    x = Op::f(x, __shfl_xor(x, 16, kWave));
-    return x;
+    return with_lane16<Op>(x);
 }
 
 // The same over the 16 lanes of one DPP row.
