@@ -326,6 +326,9 @@ typedef struct {
     float *grad_fact_prob;
 } dol_dtkp_fold;
 dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_prov *prov, void *hip_stream);
+/* Name of the HIP kernel that dol_dtkp_fold_apply2 launches for this fold and its batch ("" where the call would reject its
+ * shapes), as dol_fold_kernel gives that of dol_fold_apply2.  Prepares the fold's tables as the call itself does; no launch. */
+const char *dol_dtkp_fold_kernel(const dol_dtkp_fold *fold, const dol_prov *prov);
 
 /* Repeated Apply with feedback under DAMP (the recursion of App. B, Fig. 9, run for a fixed number of rounds):
  *     r_0 = r0,   r_{t+1} = apply2(r_t, e, f)   for t = 0 .. rounds-1,

@@ -510,6 +510,8 @@ class _DtkpFold(C.Structure):
 
 
 _lib.dol_dtkp_fold_apply2.argtypes = [C.POINTER(_DtkpFold), C.POINTER(_Prov), C.c_void_p]
+_lib.dol_dtkp_fold_kernel.argtypes = [C.POINTER(_DtkpFold), C.POINTER(_Prov)]
+_lib.dol_dtkp_fold_kernel.restype = C.c_char_p
 
 
 class DtkpFold:
@@ -539,6 +541,11 @@ class DtkpFold:
 
 def dtkp_fold_apply2(fold: DtkpFold, prov: Prov, stream=None):
     _native.dtkp_fold_apply2(fold._p, prov._p, None if stream is None else _handle(stream))
+
+
+def dtkp_fold_kernel(fold: DtkpFold, prov: Prov) -> str:
+    """Name of the kernel that dtkp_fold_apply2 launches for this fold."""
+    return _lib.dol_dtkp_fold_kernel(C.byref(fold.c), C.byref(prov.c)).decode()
 
 
 _lib.dol_iterate_apply2.argtypes = [C.POINTER(_Dist), C.POINTER(_Dist), C.c_void_p, C.c_int32, C.c_void_p, C.c_void_p]

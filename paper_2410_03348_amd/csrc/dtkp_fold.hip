@@ -14,6 +14,7 @@
 #include "wave_util.h"
 
 #include <cfloat>
+#include <cstdio>
 #include <vector>
 
 namespace dol {
@@ -156,7 +157,7 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
 //   and 50.0, k = 7 73.0 and 68.6, Sum-5, k = 3, 12 000 28.0 and 26.6, 4 096 12.3 and 12.0, but 2 048 8.6 and 8.7, 1 024 7.4 and 7.7; Sum-3,
 //   k = 5, 2 048 7.7 and 8.0.  (Both ways in one kernel take 76 registers, one wavefront less to a SIMD: 52.6.)
 constexpr int kListCost = 2;            // tuples saved that two lists are worth
-constexpr int kManySamples = 3072;      // three to a SIMD
+constexpr int kManySamples = 3072;      // three to a SIMD (and see share_lookup_pays)
 
 struct Share {                          // a lane's, in one word
     enum Role : uint32_t { kWhole, kFirstHalf, kHelper, kIdle };
@@ -545,6 +546,13 @@ struct DtkpFoldPlan {
     DevArray<int32_t> words;
     DevArray<uint64_t> rival;
     int32_t n_words = 0, n_shares = 0, max_s = 0, s_last = 0;
+    int waves = 0;                      // wavefronts (samples) of a workgroup
+    size_t wave_bytes = 0, lds = 0;     // LDS of one, and of the workgroup
+    bool wide = false;                  // lanes help in a stage of more than 32 columns
+    bool looked_up = false;             // many samples take the build whose lanes look their shares up (share_lookup_pays)
+
+    size_t share_bytes() const { return sizeof(uint32_t) * static_cast<size_t>(n_shares); }
+    bool many(int32_t batch) const { return looked_up && batch > kManySamples; }
 };
 
 Cache<DtkpFoldPlan> &g_fold_plans = *new Cache<DtkpFoldPlan>;      // never destroyed, as the other plan caches
@@ -574,6 +582,55 @@ int32_t add_shares(const dol_fn_table *f, std::vector<int32_t> &shares)
         if (two) shares[at + helper++] = static_cast<int32_t>(Share::pack(c, c, Share::kHelper));
     }
     return S <= kWave / 2 ? kHelped | kTwins : kHelped;
+}
+
+using FoldKernel = void (*)(const DtkpFoldArgs);
+
+template <bool MANY>
+FoldKernel fold_kernel(int k)
+{
+    static const FoldKernel of_k[DOL_MAX_K] = {
+        dtkp_fold_kernel<1, MANY>, dtkp_fold_kernel<2, MANY>, dtkp_fold_kernel<3, MANY>, dtkp_fold_kernel<4, MANY>,
+        dtkp_fold_kernel<5, MANY>, dtkp_fold_kernel<6, MANY>, dtkp_fold_kernel<7, MANY>, dtkp_fold_kernel<8, MANY>};
+    return of_k[k - 1];
+}
+
+constexpr size_t kDfLds = 64 * 1024;    // most LDS of a workgroup
+
+// The workgroup's wavefronts: as many as fit (the symbol side is a third of a lone wavefront's LDS for Sum-6 at k = 5, so four of
+// them together fit a compute unit 28 times over instead of 11).
+void set_workgroup(DtkpFoldPlan *p, int K)
+{
+    const size_t bufs = p->max_s > kWave ? 2 : 1;
+    const size_t shared = 64 * sizeof(uint64_t) + sizeof(uint32_t) * static_cast<size_t>(p->n_words);
+    p->wave_bytes = (bufs * p->max_s * K * (sizeof(uint64_t) + sizeof(float)) + sizeof(float) * (64 + p->max_s) + 15) & ~size_t(15);
+    p->waves = kDfWaves;
+    while (p->waves > 1 && shared + p->waves * p->wave_bytes > kDfLds) p->waves /= 2;
+    p->lds = shared + p->waves * p->wave_bytes;
+}
+
+// Whether many samples (kManySamples) take the build whose lanes look their shares up: where a stage of more than 32 columns
+// gets help, which twins cannot give, and a unit holds as many workgroups as without.  12 000 samples, us, twins / looked up:
+//   Sum-6, k = 5, 20 000 samples 82.0 / 76.8; sums of six digits modulo 40, k = 5 47.9 / 45.2; products of three digits, k = 3
+//   43.4 / 40.9
+//   no such stage: sums of six digits modulo 30, 120 columns at last, k = 3 40.5 / 42.0; modulo 20, 300 at last, k = 5 140 / 145;
+//   modulo 12, k = 5 61.3 / 64.3; without a last one modulo 32, k = 5 42.2 / 41.3; Sum-3, k = 5, 20 000 samples 30.6 / 29.9
+//   a workgroup less for want of registers, k = 8 (four wavefronts to a SIMD instead of five): Sum-6, 20 000 samples 166 / 174,
+//   modulo 40 93 / 97; modulo 36 with 100 columns at last, whose LDS leaves three workgroups either way, 149 / 145
+//   a workgroup less for want of LDS: five digits modulo 50, 300 columns at last, k = 1, 40.6 KB or 41.4: 4 096 samples 12.4 / 16.3
+// (How few wavefronts a SIMD holds does not decide: with one of them modulo 40, 200 columns at last, k = 5 159 / 157 and modulo 50,
+// 300 at last, k = 4 131 / 134.)
+bool share_lookup_pays(const DtkpFoldPlan &p, int K)
+{
+    if (!p.wide || p.lds + p.share_bytes() > kDfLds) return false;
+    auto workgroups = [&](FoldKernel kernel, size_t lds) {
+        int n = 0;
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(kernel), p.waves * kWave, lds);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e == hipSuccess ? n : 0;
+    };
+    const int own = workgroups(fold_kernel<false>(K), p.lds);
+    return own > 0 && workgroups(fold_kernel<true>(K), p.lds + p.share_bytes()) >= own;
 }
 
 dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldPlan *p)
@@ -633,7 +690,9 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
         words.insert(words.end(), 2, 0);
         if (words[4 + 4 * t] & kFresh) {
             words[4 + 4 * t] |= static_cast<int32_t>(shares.size() / kWave) << kShareShift;
-            words[4 + 4 * t] |= add_shares(f, shares);
+            const int32_t help = add_shares(f, shares);
+            words[4 + 4 * t] |= help;
+            p->wide |= help == kHelped;
         }
         s_prev = p->s_last = f->n_out;
         p->max_s = std::max(p->max_s, f->n_out);
@@ -649,6 +708,8 @@ dol_status build_plan(const dol_dtkp_fold *fold, const dol_prov *prov, DtkpFoldP
     hipError_t e;
     if ((e = p->words.upload(words)) != hipSuccess || (e = p->rival.upload(rival)) != hipSuccess)
         return hip_fail(e, "uploading the fold's tables");
+    set_workgroup(p, K);
+    p->looked_up = share_lookup_pays(*p, K);
     return DOL_OK;
 }
 
@@ -678,7 +739,8 @@ dol_status get_plan(const dol_dtkp_fold *fold, const dol_prov *prov, const DtkpF
 
 }  // namespace
 
-extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_prov *prov, void *hip_stream)
+// Checks the call's description as far as its shapes; the fold's plan.
+static dol_status fold_checked(const dol_dtkp_fold *fold, const dol_prov *prov, const DtkpFoldPlan **plan)
 {
     if (!fold || !prov) return fail(DOL_EINVAL, "NULL argument");
     if (prov->kind != DOL_DTKP) return fail(DOL_EINVAL, "dol_dtkp_fold_apply2 needs a DTKP provenance");
@@ -687,42 +749,52 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
     if (K < 1 || K > DOL_MAX_K) return fail(DOL_EINVAL, "k = %d outside 1..%d", K, DOL_MAX_K);
     if (prov->n_facts < 1 || prov->n_facts > 63) return fail(DOL_EINVAL, "n_facts = %d outside 1..63", prov->n_facts);
     if (!fold->inputs || !fold->tables || !fold->fact_of_sym || !fold->out) return fail(DOL_EINVAL, "inputs, tables, fact_of_sym or out is NULL");
-    DtkpFoldArgs A{};
-    A.n = n;
-    A.n_facts = prov->n_facts;
     for (int t = 0; t < n; ++t) {
-        const dol_dist *d = fold->inputs[t];
+        const dol_dist *d = fold->inputs[t], *d0 = fold->inputs[0];
         if (!d) return fail(DOL_EINVAL, "inputs[%d] is NULL", t);
         if (d->batch < 0 || d->n_sym < 1) return fail(DOL_ESHAPE, "inputs[%d] has a bad shape", t);
-        if (t == 0) A.batch = d->batch;
-        if (d->batch != A.batch) return fail(DOL_ESHAPE, "inputs[%d].batch = %d, inputs[0].batch = %d", t, d->batch, A.batch);
+        if (d->batch != d0->batch) return fail(DOL_ESHAPE, "inputs[%d].batch = %d, inputs[0].batch = %d", t, d->batch, d0->batch);
         if (!fold->fact_of_sym[t]) return fail(DOL_EINVAL, "fact_of_sym[%d] is NULL", t);
         if (t && !fold->tables[t - 1]) return fail(DOL_EINVAL, "tables[%d] is NULL", t - 1);
     }
+    if (dol_status st = get_plan(fold, prov, plan)) return st;
+    const dol_dist *o = fold->out;
+    const int32_t batch = fold->inputs[0]->batch, s_last = (*plan)->s_last;
+    if (o->batch != batch || o->n_sym != s_last || o->ld < o->n_sym)
+        return fail(DOL_ESHAPE, "out has %d x %d, the fold produces %d x %d", o->batch, o->n_sym, batch, s_last);
+    if ((*plan)->lds > kDfLds) return fail(DOL_EUNSUPPORTED, "the fold needs %zu bytes of LDS per sample, more than %zu", (*plan)->lds, kDfLds);
+    return DOL_OK;
+}
+
+extern "C" const char *dol_dtkp_fold_kernel(const dol_dtkp_fold *fold, const dol_prov *prov)
+{
+    static thread_local char name[64];
     const DtkpFoldPlan *plan = nullptr;
-    if (dol_status st = get_plan(fold, prov, &plan)) return st;
+    if (fold_checked(fold, prov, &plan) != DOL_OK) return "";
+    snprintf(name, sizeof name, "dtkp_fold_kernel<%d, %s>", prov->k, plan->many(fold->inputs[0]->batch) ? "true" : "false");
+    return name;
+}
+
+extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_prov *prov, void *hip_stream)
+{
+    const DtkpFoldPlan *plan = nullptr;
+    if (dol_status st = fold_checked(fold, prov, &plan)) return st;
+    const int K = prov->k;
     const int32_t s_last = plan->s_last;
+    const dol_dist *o = fold->out;
+    DtkpFoldArgs A{};
+    A.n = fold->n_inputs;
+    A.batch = fold->inputs[0]->batch;
+    A.n_facts = prov->n_facts;
     A.max_s = plan->max_s;
     A.n_words = plan->n_words;
     A.n_shares = plan->n_shares;
     A.words = plan->words.ptr;
     A.rival = plan->rival.ptr;
-    const dol_dist *o = fold->out;
-    if (o->batch != A.batch || o->n_sym != s_last || o->ld < o->n_sym)
-        return fail(DOL_ESHAPE, "out has %d x %d, the fold produces %d x %d", o->batch, o->n_sym, A.batch, s_last);
-    const size_t bufs = A.max_s > kWave ? 2 : 1;
-    const size_t wave_bytes = (bufs * A.max_s * K * (sizeof(uint64_t) + sizeof(float)) + sizeof(float) * (64 + A.max_s) + 15) & ~size_t(15);
-    const size_t shared_bytes = 64 * sizeof(uint64_t) + sizeof(uint32_t) * static_cast<size_t>(A.n_words);
-    // wavefronts to a workgroup: as many as fit 64 KB (the symbol side is a third of a lone wavefront's LDS for Sum-6 at
-    // k = 5, so four of them together fit a compute unit 28 times over instead of 11)
-    int waves = kDfWaves;
-    while (waves > 1 && shared_bytes + waves * wave_bytes > 64 * 1024) waves /= 2;
-    // (kManySamples: where the shares' two trips are hidden, see there)
-    const size_t share_bytes = sizeof(uint32_t) * static_cast<size_t>(plan->n_shares);
-    const bool many = A.batch > kManySamples && share_bytes > 0 && shared_bytes + share_bytes + waves * wave_bytes <= 64 * 1024;
-    const size_t lds = shared_bytes + (many ? share_bytes : 0) + waves * wave_bytes;
-    if (lds > 64 * 1024) return fail(DOL_EUNSUPPORTED, "the fold needs %zu bytes of LDS per sample, more than 65536", lds);
-    A.wave_bytes = static_cast<int32_t>(wave_bytes);
+    const bool many = plan->many(A.batch);
+    const int waves = plan->waves;
+    const size_t lds = plan->lds + (many ? plan->share_bytes() : 0);
+    A.wave_bytes = static_cast<int32_t>(plan->wave_bytes);
     if (A.batch == 0) return DOL_OK;
     if (!o->proof_mask || !o->proof_prob || !o->prob) return fail(DOL_EINVAL, "out.proof_mask, out.proof_prob or out.prob is NULL");
     if (!prov->fact_prob) return fail(DOL_EINVAL, "prov.fact_prob is NULL");
@@ -741,25 +813,7 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(A.batch) + waves - 1) / waves)), block(static_cast<unsigned>(waves * kWave));
-#define DOL_DF(KK, MANY) hipLaunchKernelGGL((dtkp_fold_kernel<KK, MANY>), grid, block, lds, st, A)
-#define DOL_DF_ALL(MANY)                \
-    switch (K) {                        \
-    case 1: DOL_DF(1, MANY); break;     \
-    case 2: DOL_DF(2, MANY); break;     \
-    case 3: DOL_DF(3, MANY); break;     \
-    case 4: DOL_DF(4, MANY); break;     \
-    case 5: DOL_DF(5, MANY); break;     \
-    case 6: DOL_DF(6, MANY); break;     \
-    case 7: DOL_DF(7, MANY); break;     \
-    default: DOL_DF(8, MANY); break;    \
-    }
-    if (many) {
-        DOL_DF_ALL(true)
-    } else {
-        DOL_DF_ALL(false)
-    }
-#undef DOL_DF_ALL
-#undef DOL_DF
+    hipLaunchKernelGGL(many ? fold_kernel<true>(K) : fold_kernel<false>(K), grid, block, lds, st, A);
     DOL_HIP(hipGetLastError());
     return DOL_OK;
 }

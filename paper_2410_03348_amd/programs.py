@@ -356,7 +356,7 @@ class DtkpSumChainFused(Program):
         self.fold = dol.DtkpFold(self.digits, self.facts, self.tables, self.out, target_col=self.target,
                                  grad_fact_prob=self.grad_fact)
         n_facts = self.fact_prob.shape[1]
-        self.launches = [Launch("dtkp_fold_kernel<%d>" % k, lambda: dol.dtkp_fold_apply2(self.fold, self.prov),
+        self.launches = [Launch(dol.dtkp_fold_kernel(self.fold, self.prov), lambda: dol.dtkp_fold_apply2(self.fold, self.prov),
                                 B * (4 * n_facts + syms.size * (12 * k + 4)), 0, "fwd")]
         self.sample_ops = (self.n - 1) * B
         self.min_bytes = self.launches[0].bytes

@@ -1011,6 +1011,36 @@ def test_fused_dtkp_fold_whose_lanes_help(dol, k, columns, longest):
         assert_close(host(out.prob), np.tile(pr, (tiles, 1)), "fold tag prob")
 
 
+def digit_fold(dol, n, k, batch, modulo=0, last=0, seed=1):
+    """A fold over n digits: sums, or sums modulo `modulo`, the last stage spread over `last` columns; the call and its provenance."""
+    sym = np.arange(10, dtype=np.int32)
+    syms, tables = sym, []
+    for t in range(1, n):
+        ids = W.sum_table(syms, sym)
+        ids = ids % modulo if modulo else ids
+        if last and t == n - 1:
+            ids = (np.arange(ids.size) * 7 % last).reshape(ids.shape)
+        tables.append(dol.FnTable.create_dense(ids.astype(np.int32)))
+        syms = tables[-1].out_syms
+    fp = dev(W.uniform01(seed, batch * 10 * n).astype(np.float32).reshape(batch, 10 * n))
+    digits = [dol.Dist(sym, torch.empty((batch, 10), device="cuda")) for _ in range(n)]
+    fold = dol.DtkpFold(digits, [10 * t + sym for t in range(n)], tables, dol.Dist.empty(syms, batch, k=k))
+    return fold, dol.Prov(dol.DTKP, k, fp, np.arange(10 * n) // 10)
+
+
+@pytest.mark.parametrize("n,k,batch,modulo,last,many", [
+    (6, 5, 3073, 0, 0, True), (6, 5, 3072, 0, 0, False),        # three samples to a SIMD
+    (3, 5, 4096, 0, 0, False), (6, 3, 4096, 32, 0, False), (6, 3, 4096, 33, 0, True), (4, 1, 4096, 0, 0, True),   # help for more than 32 columns
+    (5, 1, 4096, 50, 300, False), (5, 2, 4096, 50, 300, True),  # a workgroup less for the shares' LDS, and as many
+    (6, 7, 4096, 0, 0, True), (6, 8, 4096, 0, 0, False), (6, 8, 4096, 36, 100, True)])    # for the registers, and where LDS allows three either way
+def test_fused_dtkp_fold_looks_shares_up_where_that_pays(dol, n, k, batch, modulo, last, many):
+    """The build with looked-up shares is taken where a stage of more than 32 columns is helped and no workgroup of a unit is lost."""
+    fold, prov = digit_fold(dol, n, k, batch, modulo, last)
+    assert dol.dtkp_fold_kernel(fold, prov) == "dtkp_fold_kernel<%d, %s>" % (k, "true" if many else "false")
+    fold.c.out.contents.n_sym += 1
+    assert dol.dtkp_fold_kernel(fold, prov) == ""
+
+
 # ---------------------------------------------------------------- config 5
 
 @pytest.mark.parametrize("batch,side,rounds", [(256, 32, 64), (33, 7, 20), (2, 3, 5)])
