@@ -65,9 +65,18 @@ struct PairArgs {
 
 constexpr int kSharedFacts = 64;        // most of them
 
+// What a kernel takes as the second operand.  (Up to kKeyProofs proofs each has a kernel of its own: in one for both the lists'
+// general union and the facts' keys share 70 registers at k = 3 and 75 at k = 4, apart 56 and 64, 60 and 72.  Tables as below, us,
+// one kernel and two: lists 3 000 x 20 -> 6 000, k = 2 228 and 198, 3 000 x 10 -> 8 000, k = 3 40.6 and 39.2; facts, k = 4 23.5 and
+// 21.4.  Longer lists have no keys, and their facts neither wait in LDS nor are their words read ahead: at k = 5 that took 83
+// registers instead of 77, lists 54.0 us instead of 51.9, facts 28.3 instead of 27.2; facts in a kernel apart 29.0 with k = 5 and
+// 385 instead of 361 with k = 6.)
+enum class Second { kLists, kFacts, kEither };
+
 // Offers every consistent union of a proof of a's symbol with a proof of b's symbol, tuple by tuple.
-template <int K>
+template <int K, Second SECOND>
 struct PairOffer {
+    static constexpr bool kShared = SECOND == Second::kFacts;
     const PairArgs &A;
     const GroupMasks &gm;
     const float *fp;
@@ -84,16 +93,26 @@ struct PairOffer {
     __device__ __forceinline__ uint64_t *lane_masks() const { return reinterpret_cast<uint64_t *>(facts() + A.shared_facts); }
     __device__ __forceinline__ void ask()
     {
-        if (static_cast<int>(threadIdx.x) < A.shared_facts) mine = reinterpret_cast<const uint4 *>(A.fact_b)[threadIdx.x];
+        if (kShared && static_cast<int>(threadIdx.x) < A.shared_facts) mine = reinterpret_cast<const uint4 *>(A.fact_b)[threadIdx.x];
     }
     __device__ __forceinline__ void share() const
     {
-        if (A.shared_facts == 0) return;
+        if (!kShared || A.shared_facts == 0) return;
         if (static_cast<int>(threadIdx.x) < A.shared_facts) facts()[threadIdx.x] = mine;
         lds_barrier();
     }
     // (a tuple's fact is known before its probability can be asked for: from LDS that costs no round trip to memory)
-    __device__ __forceinline__ uint4 fact_of(uint32_t j) const { return A.shared_facts ? facts()[j] : reinterpret_cast<const uint4 *>(A.fact_b)[j]; }
+    __device__ __forceinline__ uint4 fact_of(uint32_t j) const
+    {
+        uint4 f;
+        if (kShared && A.shared_facts) {
+            f = facts()[j];
+            asm volatile("" : "+v"(f.x));       // (or both loads become one of either memory, which waits for the lists too)
+        } else {
+            f = reinterpret_cast<const uint4 *>(A.fact_b)[j];
+        }
+        return f;
+    }
     __device__ __forceinline__ void ahead(uint32_t r) { first = A.ord_tuples[r]; }
     __device__ __forceinline__ void begin(int64_t s)
     {
@@ -141,10 +160,8 @@ struct PairOffer {
     template <class Word>
     __device__ __forceinline__ void run(TopK<K> &top, uint32_t q, uint32_t q1, uint32_t step, Word word) const
     {
-        uint32_t ahead = q < q1 ? word(q) : 0;
         for (; q < q1; q += step) {
-            const uint32_t ij = ahead, j = ij >> 16;
-            ahead = word(min(q + step, q1 - 1));
+            const uint32_t ij = word(q), j = ij >> 16;
             const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K;
             uint64_t ma[K];
             float pa[K];
@@ -152,49 +169,45 @@ struct PairOffer {
 #pragma unroll
             for (int x = 0; x < K; ++x) pa[x] = -1.0f;
             if (A.ap) load_probs<K>(A.ap + ia, pa);
-            if (A.fact_b) {
-                with_fact(top, fact_of(j), ma, pa);
-            } else with_list(top, j, ma, pa);
+            if (SECOND == Second::kFacts || (SECOND == Second::kEither && A.fact_b)) with_fact(top, fact_of(j), ma, pa);
+            else if constexpr (SECOND != Second::kFacts) with_list(top, j, ma, pa);
         }
     }
     __device__ __forceinline__ void listed(TopK<K> &top, uint32_t q, uint32_t q1, uint32_t step) const
     {
         run(top, q, q1, step, [&](uint32_t x) { return A.col_ij[x]; });
     }
-    __device__ __forceinline__ bool has_short() const { return A.fact_b && A.ap; }
-    // A tuple's candidates: which of the operand's proofs there are, joined to the fact, and their probabilities; the answer is
-    // whether they are in descending order.
-    __device__ __forceinline__ bool candidates(uint32_t ij, uint64_t (&m)[K], float (&pr)[K], bool (&ok)[K]) const
+    __device__ __forceinline__ bool has_short() const { return kShared && A.ap; }
+    // One tuple's list and fact.
+    struct Tuple {
+        uint64_t ma[K], bit, rival;
+        float pa[K], pbit;
+        // the fact is above every fact of all proofs, and no rival of one: mostly so, and one look says it for all of them
+        __device__ __forceinline__ bool fresh() const
+        {
+            uint64_t any = 0;
+#pragma unroll
+            for (int x = 0; x < K; ++x) any |= ma[x] != kAbsent ? ma[x] : 0;
+            return !(any & rival) && any < bit;
+        }
+        // whether there is a proof of x and the fact, and its probability (see with_fact)
+        __device__ __forceinline__ bool joins(int x) const { return ma[x] != kAbsent && !(ma[x] & rival); }
+        __device__ __forceinline__ float joint(int x, const float *__restrict__ fp) const
+        {
+            const bool held = (ma[x] & bit) != 0;
+            return held || ma[x] < bit ? (held ? pa[x] : pa[x] * pbit) : proof_prob(ma[x] | bit, fp);
+        }
+    };
+    __device__ __forceinline__ Tuple tuple(uint32_t ij) const
     {
+        Tuple t;
         const int64_t ia = a0 + static_cast<int64_t>(ij & 0xffffu) * K;
         const uint4 f = fact_of(ij >> 16);
-        uint64_t ma[K];
-        float pa[K];
-        load_masks<K>(A.am + ia, ma);
-        load_probs<K>(A.ap + ia, pa);
-        const float pbit = 1.0f * fp[f.x];
-        const uint64_t bit = uint64_t(1) << f.x, rival = (static_cast<uint64_t>(f.z) << 32) | f.y;
-        uint64_t any = 0;
-#pragma unroll
-        for (int x = 0; x < K; ++x) {
-            ok[x] = ma[x] != kAbsent;
-            any |= ok[x] ? ma[x] : 0;
-            pr[x] = pa[x] * pbit;
-            m[x] = ma[x] | bit;
-        }
-        // (mostly the fact is new to all proofs, above every one of theirs and no rival: one look for all of them)
-        if (__builtin_expect((any & rival) || any >= bit, 0)) {
-#pragma unroll
-            for (int x = 0; x < K; ++x) {                       // (see with_fact)
-                ok[x] = ok[x] && !(ma[x] & rival);
-                if (ma[x] & bit) pr[x] = pa[x];
-                else if (ok[x] && !(ma[x] < bit)) pr[x] = proof_prob(m[x], fp);
-            }
-        }
-        bool falls = true;
-#pragma unroll
-        for (int x = 1; x < K; ++x) falls &= !ok[x] || (ok[x - 1] && pr[x - 1] >= pr[x]);
-        return falls;
+        load_masks<K>(A.am + ia, t.ma);
+        load_probs<K>(A.ap + ia, t.pa);
+        t.pbit = 1.0f * fp[f.x];
+        t.bit = uint64_t(1) << f.x, t.rival = (static_cast<uint64_t>(f.z) << 32) | f.y;
+        return t;
     }
     // (the masks of a lane's few tuples wait in LDS for the winners; a key's id is the candidate's number in its lane, and the
     // lane's thread << 8.  Read again from memory once the winners are known: 192.6 us for the formula's pass, 184.2 so.)
@@ -206,31 +219,54 @@ struct PairOffer {
         uint64_t *put = lane_masks() + threadIdx.x;
         int id = threadIdx.x << 8;
         for (; q < q1; q += step, id += K, put += K * blockDim.x) {
-            const uint32_t ij = ahead;
+            const Tuple t = tuple(ahead);
             ahead = word(min(q + step, q1 - 1));
-            uint64_t m[K];
-            float pr[K];
-            bool ok[K];
-            const bool falls = candidates(ij, m, pr, ok);
+            // (uniform.  Where lanes took one way each, after both, facts that are held already, below others or rivals cost up to
+            // a quarter of the launch; us, so and now: table 3 000 x 10 -> 3 000, 64 samples, k = 4 30.7 and 25.1, 3 000 x 20 -> 6 000,
+            // 300 samples, k = 2 114 and 94, 300 x 40 -> 700 with 16 lanes to a column, 100 samples, k = 3 14.0 and 12.5.  One
+            // candidate after the other there too: 11.5, and where facts are new 16.7 instead of 15.7)
+            if (__ballot(!t.fresh()) == 0) {
+                float pr[K];
+                bool ok[K], falls = true;
 #pragma unroll
-            for (int x = 0; x < K; ++x) put[x * blockDim.x] = m[x];
-            if (__builtin_expect(falls, 1)) {
-                keys.offer_falling(ok, pr, id);
+                for (int x = 0; x < K; ++x) {
+                    ok[x] = t.ma[x] != kAbsent;
+                    pr[x] = t.pa[x] * t.pbit;
+                    put[x * blockDim.x] = t.ma[x] | t.bit;
+                    falls &= x == 0 || !ok[x] || (ok[x > 0 ? x - 1 : 0] && pr[x > 0 ? x - 1 : 0] >= pr[x]);
+                }
+                if (__ballot(!falls) == 0) {
+                    keys.offer_falling(ok, pr, id);
+                } else {
+#pragma unroll
+                    for (int x = 0; x < K; ++x) keys.offer(ok[x], pr[x], id + x);
+                }
             } else {
 #pragma unroll
-                for (int x = 0; x < K; ++x) keys.offer(ok[x], pr[x], id + x);
+                for (int x = 0; x < K; ++x) {
+                    if (!t.joins(x)) continue;
+                    put[x * blockDim.x] = t.ma[x] | t.bit;
+                    keys.offer(true, t.joint(x, fp), id + x);
+                }
             }
         }
     }
-    // A column of one tuple: its candidates are the result unless two probabilities are equal or some candidate is no proof; where that may be
-    // it says so.
+    // A column of one tuple: its candidates are the result unless one before another is no proof, they do not fall, or one's
+    // probability is no number to rank by; where that may be it says so.
     __device__ __forceinline__ bool single(TopK<K> &top) const
     {
-        bool ok[K], clear = candidates(first, top.m, top.p, ok);
+        const Tuple t = tuple(first);
+        bool clear = true;
+        float before = __uint_as_float(0x7f800000u);
 #pragma unroll
         for (int x = 0; x < K; ++x) {
-            clear &= !ok[x] || (__float_as_uint(top.p[x]) < 0x7f800000u && (x == 0 || top.p[x > 0 ? x - 1 : 0] != top.p[x]));
-            if (!ok[x]) top.m[x] = kAbsent, top.p[x] = -1.0f;
+            if (!t.joins(x)) {
+                before = -1.0f;
+                continue;
+            }
+            top.m[x] = t.ma[x] | t.bit, top.p[x] = t.joint(x, fp);
+            clear &= __float_as_uint(top.p[x]) < 0x7f800000u && top.p[x] < before;
+            before = top.p[x];
         }
         return clear;
     }
@@ -260,20 +296,25 @@ struct PairOffer {
     }
 };
 
-template <int K>
+template <int K, Second SECOND>
 __global__ void __launch_bounds__(kHugeThreads)
 dtkp_apply2_kernel(ColumnArgs C, PairArgs A, GroupMasks gm)
 {
-    dtkp_columns<K>(C, PairOffer<K>{A, gm, nullptr, 0, 0, {}, 0});
+    dtkp_columns<K>(C, PairOffer<K, SECOND>{A, gm, nullptr, 0, 0, {}, 0});
 }
 
 template <int K>
 static void launch_apply2_k(ColumnArgs C, const PairArgs &A, const GroupMasks &gm, hipStream_t st)
 {
-    const unsigned grid = column_launch<K>(C);
-    const size_t lds = sizeof(uint4) * A.shared_facts +
-                       (K <= kKeyProofs && A.fact_b ? sizeof(uint64_t) * column_threads(C) * kLongDtkpCol * K : 0);     // a lane's masks: 96 bytes at three proofs
-    hipLaunchKernelGGL(dtkp_apply2_kernel<K>, dim3(grid), dim3(column_threads(C)), lds, st, C, A, gm);
+    const dim3 grid(column_launch<K>(C)), block(column_threads(C));
+    if constexpr (K > kKeyProofs) {
+        hipLaunchKernelGGL((dtkp_apply2_kernel<K, Second::kEither>), grid, block, 0, st, C, A, gm);
+    } else if (A.fact_b) {              // a lane's masks: 96 bytes at three proofs
+        const size_t lds = sizeof(uint4) * A.shared_facts + sizeof(uint64_t) * block.x * kLongDtkpCol * K;
+        hipLaunchKernelGGL((dtkp_apply2_kernel<K, Second::kFacts>), grid, block, lds, st, C, A, gm);
+    } else {
+        hipLaunchKernelGGL((dtkp_apply2_kernel<K, Second::kLists>), grid, block, 0, st, C, A, gm);
+    }
 }
 
 #define DOL_DISPATCH_K(k, CALL)                                      \
@@ -480,10 +521,10 @@ dtkp_prob_bwd_kernel(int32_t parts, int32_t n_sym, int32_t n_facts, const uint64
             if (lane == j) mine_tiny = mine_tiny + t;
         }
     }
-    // The wavefront's totals, eight facts at a time: at each distance a lane gives away the half of its sums that the other one keeps, and
-    // every sum meets the others in the order of an exchange of all of them, 20 instructions for eight facts instead of 96, half of
-    // those through LDS (8 334 symbols, 49 facts, us: 64 samples k = 3 13.7, 12.5 so, k = 1 10.6 and 7.9; 300 samples 65 and 56; 899
-    // symbols, 38 facts, k = 5, 64 samples 8.2 and 5.7).
+    // The wavefront's totals, eight facts at a time: at each distance a lane gives away the half of its sums that the other one
+    // keeps, and every sum meets the others in the order of an exchange of all of them, 20 instructions for eight facts instead of
+    // 96, half of those through LDS (8 334 symbols, 49 facts, us: 64 samples k = 3 13.7, 12.5 so, k = 1 10.6 and 7.9; 300 samples
+    // 65 and 56; 899 symbols, 38 facts, k = 5, 64 samples 8.2 and 5.7).
     const int kept = 4 * (lane >> 3 & 1) + 2 * (lane >> 4 & 1) + (lane >> 5);      // which of the eight this lane ends with
 #pragma unroll
     for (int j0 = 0; j0 < 64; j0 += 8) {

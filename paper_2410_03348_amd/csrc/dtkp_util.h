@@ -204,6 +204,12 @@ struct TopKeys {
     __device__ __forceinline__ float prob(int x) const { return __int_as_float(__double2hiint(top[x])); }
 };
 
+// Up to how many proofs a list takes in a candidate equal to a kept one by the code of all others.  (Two ways that each change the
+// list cost moves of all of it from one set of registers to another; in longer lists what a second way skips is more.  Facts of one
+// probability, columns of a table 300 x 40 -> 700, 100 samples, us, two ways / one: k = 3 21.6 / 20.0, 4 34.0 / 32.9, 5 38.9 / 40.4, 7
+// 72.8 / 82.2; softmax k = 3 15.7 / 15.9, 5 27.3 / 32.3, 7 45.3 / 60.3.)
+constexpr int kOneWay = 4;
+
 template <int K>
 struct TopK {
     uint64_t m[K];
@@ -228,10 +234,18 @@ struct TopK {
         bool tie = false;
 #pragma unroll
         for (int x = 0; x < K; ++x) tie |= (prob == p[x]);
-        if (!tie) {
+        if (K <= kOneWay || !tie) {
             bool gt[K];
 #pragma unroll
             for (int x = 0; x < K; ++x) gt[x] = prob > p[x];
+            if (K <= kOneWay && tie) {
+                bool dup = false;
+#pragma unroll
+                for (int x = 0; x < K; ++x) dup |= m[x] == mask, gt[x] |= prob == p[x] && mask < m[x];
+#pragma unroll
+                for (int x = 0; x < K; ++x) gt[x] &= !dup;
+                prob = dup ? -2.0f : prob;              // (below every slot, absent ones included)
+            }
 #pragma unroll
             for (int x = K - 1; x >= 0; --x) {
                 const bool above = x > 0 ? gt[x - 1] : false;

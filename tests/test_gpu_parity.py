@@ -3198,6 +3198,53 @@ def test_dtkp_input_columns_at_the_edges_of_workgroups(dol, k, na, nb, S, B, fac
     np.testing.assert_array_equal(host(got.prob), host(want.prob))
 
 
+@pytest.mark.parametrize("values", [None, (0.5, 0.25, 1.0, 0.0)], ids=["random", "equal"])
+@pytest.mark.parametrize("facts", ["new", "mixed"])
+@pytest.mark.parametrize("nb", [64, 65])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 6])
+def test_dtkp_input_over_lists_in_any_order(dol, k, nb, facts, values):
+    """An operand whose proofs lie in no order, with absent ones before and between them (of any probability), joined to facts that
+    are new to all proofs of a wavefront, and to facts held already, below others and rivals; columns of one tuple and of every
+    kind of length, on both sides of the longest lists ranked by keys, facts in LDS and not.  Against the oracle, bit for bit."""
+    lengths = (1, 2, 3, 4, 5, 15, 16, 17, 64, 65, 70) + (1,) * 70
+    batch, low, n_facts, n = 5, 24, 60, sum(lengths)
+    na = -(-n // nb)
+    fp = W.uniform01(151 + nb, batch * n_facts).astype(np.float32).reshape(batch, n_facts)
+    if values is not None:
+        fp[1:] = np.asarray(values, np.float32)[(fp[1:] * len(values)).astype(int)]
+    grp = np.concatenate([np.repeat(np.arange(4), 6), np.full(n_facts - low, 9)]).astype(np.int32)
+    # a proof: one fact of some of the four groups
+    pick = W.splitmix64(152, np.arange(batch * na * k * 4)).reshape(batch, na, k, 4) % np.uint64(9)
+    am = np.bitwise_or.reduce(np.where(pick < 6, np.uint64(1) << (pick % np.uint64(6) + np.uint64(6) * np.arange(4, dtype=np.uint64)), np.uint64(0)), axis=-1)
+    am[W.uniform01(153, am.size).reshape(am.shape) < 0.2] = oracle.ABSENT
+    am[am == 0] = oracle.ABSENT
+    for x in range(1, k):                       # (no proof twice in a list)
+        for y in range(x):
+            am[..., x] = np.where(am[..., x] == am[..., y], oracle.ABSENT, am[..., x])
+    ap = np.ones(am.shape, np.float32)
+    for f in range(low):
+        ap = np.where((am >> np.uint64(f)) & np.uint64(1) == 1, ap * fp[:, f, None, None], ap)
+    ap[am == oracle.ABSENT] = 0.7
+    fact_b = (low + np.arange(nb) * 5 % (n_facts - low) if facts == "new" else np.arange(nb) * 11 % n_facts).astype(np.int32)
+    col = np.repeat(np.arange(len(lengths)), lengths)[np.argsort(W.splitmix64(154, np.arange(n)))].astype(np.int32)
+    table = np.full(na * nb, -1, np.int32)
+    table[:n] = col
+    table = table.reshape(na, nb)
+    bm = oracle.dtkp_init(fact_b, fp, k)[0]
+    _, om, op, opr = oracle.dtkp_apply2(oracle.dense_to_triples(table), na, nb, k, grp, fp, am, bm)
+    f = dol.FnTable.create_dense(table)
+    prov = dol.Prov(dol.DTKP, k, dev(fp), grp)
+    a = dol.Dist(np.arange(na), torch.zeros((batch, na), device="cuda"), dev(am.view(np.int64)), dev(ap))
+    b = dol.Dist.empty(np.arange(nb), batch, k=k)
+    dol.dtkp_init(b, fact_b, prov)
+    for call in (lambda out: dol.dtkp_apply2_input(a, fact_b, f, prov, out), lambda out: dol.apply2(a, b, f, prov, out)):
+        out = dol.Dist.empty(f.out_syms, batch, k=k)
+        call(out)
+        np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64), om)
+        np.testing.assert_array_equal(host(out.proof_prob), op)
+        assert_close(host(out.prob), opr, "lists in any order")
+
+
 @pytest.mark.parametrize("k,nv", [(1, 6), (3, 6), (3, 20), (8, 12)])
 def test_dtkp_gradient_with_impossible_facts(dol, k, nv):
     """Fact probabilities of exactly 0 and far below 1e-30 in some samples: there the product of a proof's other facts
