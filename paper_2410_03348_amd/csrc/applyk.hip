@@ -360,6 +360,7 @@ struct TupleOffer {
     const GroupMasks &gm;
     const float *fp;
     int64_t s;
+    static constexpr bool kOneWay = false;
     int at[kLongDtkpCol];               // unary_short(): lists of the lane with a slot of probability 0, -1 without
 
     __device__ __forceinline__ void ask() {}

@@ -77,6 +77,9 @@ enum class Second { kLists, kFacts, kEither };
 template <int K, Second SECOND>
 struct PairOffer {
     static constexpr bool kShared = SECOND == Second::kFacts;
+    // (facts of one probability, table 300 x 40 -> 700, 100 samples, us, two ways / one: k = 3 21.6 / 20.0, 4 34.0 / 32.9, 5 38.9 /
+    // 40.4, 7 72.8 / 82.2; softmax k = 3 15.7 / 15.9, 5 27.3 / 32.3, 7 45.3 / 60.3)
+    static constexpr bool kOneWay = SECOND != Second::kEither;
     const PairArgs &A;
     const GroupMasks &gm;
     const float *fp;
@@ -132,7 +135,7 @@ struct PairOffer {
             if (ma[x] == kAbsent || (ma[x] & rival)) continue;
             const bool held = (ma[x] & bit) != 0;
             const float pr = A.ap && (held || ma[x] < bit) ? (held ? pa[x] : pa[x] * pbit) : proof_prob(ma[x] | bit, fp);
-            top.insert(ma[x] | bit, pr);
+            top.template insert<kOneWay>(ma[x] | bit, pr);
         }
     }
     __device__ __forceinline__ void with_list(TopK<K> &top, uint32_t j, const uint64_t (&ma)[K], const float (&pa)[K]) const
@@ -152,7 +155,7 @@ struct PairOffer {
                 if (mb[y] == kAbsent) continue;
                 const uint64_t m = ma[x] | mb[y];
                 if (proof_conflict(m, gm)) continue;
-                top.insert(m, union_prob(ma[x], pa[x], mb[y], pb[y], fp));
+                top.template insert<kOneWay>(m, union_prob(ma[x], pa[x], mb[y], pb[y], fp));
             }
         }
     }

@@ -93,7 +93,7 @@ inline unsigned column_launch(ColumnArgs &A)
 // short column, asked for before anything is known about it; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
 // laned(top, len, r, c) - those of column c, the r-th in order; where it has_short(), short_listed and short_laned offer the same,
 // of at most kLongDtkpCol tuples a lane, to a list of keys, and short_take() finds the proofs of the list, the same of
-// `lanes` lanes, or says that it cannot (to each of them).
+// `lanes` lanes, or says that it cannot (to each of them); kOneWay - how lists take in candidates (TopK::insert).
 // (A candidate's way into a list of probabilities and masks takes some thirty instructions, most of them choices, and so does each
 // entry of another lane's list; into a list of keys seven, and a whole list of three twelve and the lane shifts.)
 constexpr int kKeyProofs = 4;           // longest lists ranked by keys
@@ -175,9 +175,9 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
             }
         }
         offer.listed(top, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes);
-        if (lanes == 4) merge_lists<K, 4>(top);
-        else if (lanes == 16) merge_lists<K, 16>(top);
-        else merge_lists<K>(top);
+        if (lanes == 4) merge_lists<K, 4, Offer::kOneWay>(top);
+        else if (lanes == 16) merge_lists<K, 16, Offer::kOneWay>(top);
+        else merge_lists<K, kWave, Offer::kOneWay>(top);
         if (huge) {                                 // uniform: the wavefronts' lists meet in the first wavefront
             __shared__ uint64_t lm[kHugeThreads / kWave * K];
             __shared__ float lp[kHugeThreads / kWave * K];
@@ -193,7 +193,7 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
 #pragma unroll
                 for (int x = 0; x < K; ++x) { top.m[x] = lm[lane * K + x]; top.p[x] = lp[lane * K + x]; }
             }
-            merge_lists<K, kHugeThreads / kWave>(top);
+            merge_lists<K, kHugeThreads / kWave, Offer::kOneWay>(top);
         }
         if (t % lanes == 0) {
             const int64_t o = static_cast<int64_t>(s) * A.S + c;

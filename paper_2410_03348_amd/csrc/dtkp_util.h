@@ -204,12 +204,6 @@ struct TopKeys {
     __device__ __forceinline__ float prob(int x) const { return __int_as_float(__double2hiint(top[x])); }
 };
 
-// Up to how many proofs a list takes in a candidate equal to a kept one by the code of all others.  (Two ways that each change the
-// list cost moves of all of it from one set of registers to another; in longer lists what a second way skips is more.  Facts of one
-// probability, columns of a table 300 x 40 -> 700, 100 samples, us, two ways / one: k = 3 21.6 / 20.0, 4 34.0 / 32.9, 5 38.9 / 40.4, 7
-// 72.8 / 82.2; softmax k = 3 15.7 / 15.9, 5 27.3 / 32.3, 7 45.3 / 60.3.)
-constexpr int kOneWay = 4;
-
 template <int K>
 struct TopK {
     uint64_t m[K];
@@ -229,16 +223,21 @@ struct TopK {
     // (a proof's probability is a function of its mask, so a candidate whose probability equals none of the kept ones is
     // none of the kept proofs and ranks among them by probability alone: the kept list, sorted, takes it in through one
     // max and K - 1 medians, and no mask is compared)
+    // ONE_WAY: a candidate equal to a kept one is taken in by the same code, which knows from the masks where it ranks or that it
+    // is kept already; else by code of its own.  Two ways that each change the list can cost moves of all of it between
+    // registers (kOneWay of dtkp.hip); what a second way skips is more in long lists and unions (of a Distribution with itself,
+    // k = 4 4.7 us with two, 5.2 with one).
+    template <bool ONE_WAY = false>
     __device__ __forceinline__ void insert(uint64_t mask, float prob)
     {
         bool tie = false;
 #pragma unroll
         for (int x = 0; x < K; ++x) tie |= (prob == p[x]);
-        if (K <= kOneWay || !tie) {
+        if (ONE_WAY || !tie) {
             bool gt[K];
 #pragma unroll
             for (int x = 0; x < K; ++x) gt[x] = prob > p[x];
-            if (K <= kOneWay && tie) {
+            if (ONE_WAY && tie) {
                 bool dup = false;
 #pragma unroll
                 for (int x = 0; x < K; ++x) dup |= m[x] == mask, gt[x] |= prob == p[x] && mask < m[x];
@@ -326,7 +325,7 @@ __device__ __forceinline__ float union_prob(uint64_t ma, float pa, uint64_t mb, 
 }
 
 // All lanes of every aligned group of LANES lanes end with the merge of the group's lists.
-template <int K, int LANES = 64>
+template <int K, int LANES = 64, bool ONE_WAY = false>
 __device__ __forceinline__ void merge_lists(TopK<K> &top)
 {
 #pragma unroll
@@ -342,7 +341,7 @@ __device__ __forceinline__ void merge_lists(TopK<K> &top)
         }
 #pragma unroll
         for (int x = 0; x < K; ++x)
-            if (pm[x] != kAbsent) top.insert(pm[x], pp[x]);
+            if (pm[x] != kAbsent) top.template insert<ONE_WAY>(pm[x], pp[x]);
     }
 }
 
