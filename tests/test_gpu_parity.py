@@ -1041,6 +1041,119 @@ def test_fused_dtkp_fold_looks_shares_up_where_that_pays(dol, n, k, batch, modul
     assert dol.dtkp_fold_kernel(fold, prov) == ""
 
 
+def fold_of_few_and_many(dol, fp, grp, facts, ids, k, tiles, many):
+    """A fold over the ids of its stages (-1: no column), of few samples and of the same ones `tiles` times over: masks and probabilities
+    against the oracle's composition, the gradients of both losses of the many against those of the few, all bit for bit.  many:
+    whether the call then takes the build whose lanes look their shares up."""
+    batch, n_facts = fp.shape
+    sizes = [f.size for f in facts]
+    m = oracle.dtkp_init(facts[0], fp, k)[0]
+    syms, tables = np.arange(sizes[0]), []
+    for t, tab in enumerate(ids, 1):
+        tab = np.ascontiguousarray(tab, np.int32)
+        assert tab.shape == (syms.size, sizes[t])
+        dm = oracle.dtkp_init(facts[t], fp, k)[0]
+        syms, m, pp, pr = oracle.dtkp_apply2(oracle.dense_to_triples(tab), syms.size, sizes[t], k, grp, fp, m, dm)
+        tables.append(dol.FnTable.create_dense(tab))
+    S = syms.size
+    target = (np.arange(batch) * 7 % S).astype(np.int32)
+    g = W.normal(k + S, batch * S).astype(np.float32).reshape(batch, S)
+    few = []
+    for r in (1, tiles):
+        ins = [dol.Dist(np.arange(x, dtype=np.int32), torch.empty((batch * r, x), device="cuda")) for x in sizes]
+        prov = dol.Prov(dol.DTKP, k, dev(np.tile(fp, (r, 1))), grp)
+        out = dol.Dist.empty(syms, batch * r, k=k)
+        for loss in ({}, dict(target_col=dev(np.tile(target, r))), dict(grad_out=dev(np.tile(g, (r, 1))))):
+            gf = torch.full((batch * r, n_facts), 7.0, device="cuda") if loss else None
+            fold = dol.DtkpFold(ins, facts, tables, out, grad_fact_prob=gf, **loss)
+            assert dol.dtkp_fold_kernel(fold, prov) == "dtkp_fold_kernel<%d, %s>" % (k, "true" if many and r > 1 else "false")
+            out.proof_mask.fill_(5), out.proof_prob.fill_(5.0), out.prob.fill_(5.0)
+            dol.dtkp_fold_apply2(fold, prov)
+            np.testing.assert_array_equal(host(out.proof_mask).view(np.uint64).reshape(r, batch, S, k), np.broadcast_to(m, (r,) + m.shape))
+            np.testing.assert_array_equal(host(out.proof_prob).reshape(r, batch, S, k), np.broadcast_to(pp, (r,) + pp.shape))
+            assert_close(host(out.prob), np.tile(pr, (r, 1)), "fold tag prob")
+            if loss and r == 1:
+                few.append(host(gf).view(np.int32))
+            elif loss:
+                want = few.pop(0)
+                np.testing.assert_array_equal(host(gf).view(np.int32).reshape(r, batch, n_facts), np.broadcast_to(want, (r,) + want.shape))
+
+
+def facts_of_all_kinds(n, nv, seed):
+    """Samples' fact probabilities: without equal ones, with one and two equal pairs (some columns to be ranked by their masks), powers of two
+    and products that underflow (most columns), all the same, of four values and certain ones, a fact of probability -0 (every column
+    candidate by candidate)."""
+    n_facts = n * nv
+    fp = W.uniform01(seed, 20 * n_facts).astype(np.float32).reshape(20, n_facts)
+    fp[4:10, nv + 2], fp[7:10, 4] = fp[4:10, 2 * nv + 7], fp[7:10, nv + 5]
+    fp[10:12] = np.float32(2.0) ** -(1 + np.arange(n_facts) % nv)
+    fp[12:14] = fp[12:14] ** 60
+    fp[14] = np.float32(0.1)
+    fp[15:17] = np.asarray((0.5, 0.25, 1.0, 0.0), np.float32)[(fp[15:17] * 4).astype(int)]
+    fp[17] = np.arange(n_facts) % nv == 3
+    fp[18, 12] = -0.0
+    return fp
+
+
+@pytest.mark.parametrize("n,k", [(5, 1), (5, 2), (5, 3), (5, 4), (6, 5), (6, 6), (6, 7), (5, 8)])
+def test_fused_dtkp_fold_of_few_and_many_samples(dol, n, k):
+    """Sum programs both ways in both builds of the fold: few samples, and the same ones over and over so that lanes look their shares up."""
+    fp = facts_of_all_kinds(n, 10, 300 + k)
+    sym, syms, ids = np.arange(10, dtype=np.int32), np.arange(10, dtype=np.int32), []
+    for t in range(1, n):
+        ids.append(W.sum_table(syms, sym))
+        syms = np.unique(ids[-1])
+    facts = [10 * t + sym for t in range(n)]
+    fold_of_few_and_many(dol, fp, np.arange(10 * n) // 10, facts, ids, k, 160, k < 8)
+
+
+@pytest.mark.parametrize("k", [2, 3, 5, 7])
+def test_fused_dtkp_fold_of_many_samples_with_stages_of_every_kind(dol, k):
+    """Stages that lanes help with beside one whose facts are not new (the first input's once more) and a last one of more columns than
+    lanes, which leaves every wavefront two buffers; two symbols of an input by one fact, so that a proof comes twice."""
+    fp = facts_of_all_kinds(5, 10, 320 + k)
+    sym, syms, ids = np.arange(10, dtype=np.int32), np.arange(10, dtype=np.int32), []
+    for t in range(1, 6):
+        tab = W.sum_table(syms, sym)
+        ids.append((np.arange(tab.size) * 7 % 120).reshape(tab.shape) if t == 5 else tab)
+        syms = np.unique(ids[-1])
+    facts = [10 * t + sym for t in (0, 1, 2, 3, 0, 4)]
+    facts[2] = facts[2].copy()
+    facts[2][6] = facts[2][2]
+    fold_of_few_and_many(dol, fp, np.arange(50) // 10, facts, ids, k, 160, True)
+
+
+@pytest.mark.parametrize("k", [1, 3, 5, 7, 8])
+@pytest.mark.parametrize("long,columns,helpers", [((9,), 63, 1), ((9, 9), 62, 2), ((8,) * 27, 37, 27), ((8,) * 31, 33, 31), ((12,) * 20, 20, 20), ((7,), 32, 1),
+                                                   ((90, 40), 2, 1), ((9,) * 2, 63, 0), ((6,), 64, 0)])
+def test_fused_dtkp_fold_with_few_long_columns(dol, k, long, columns, helpers):
+    """The longest columns of a stage are as many as the wavefront has lanes to spare, one fewer, one more (nobody helps then), and more
+    than half of the columns; in the first stage (one proof to a symbol) and, by columns of the same lengths or one that takes nearly
+    all tuples, in the second."""
+    nv = (16, 16, 10)
+    rest = [1 + c % 3 for c in range(columns - len(long))]
+    lengths = np.array((list(long) + rest))[np.argsort(W.uniform01(columns, columns), kind="stable")]
+    assert lengths.sum() <= nv[0] * nv[1]
+    # what the plan works out: columns of more than `most` tuples get a helper
+    most = (lengths.max() + 1) // 2
+    while columns + (lengths > most).sum() > 64:
+        most += 1
+    assert (helpers and (lengths > most).sum() == helpers and lengths.max() - most >= 2) or (not helpers and lengths.max() - most < 2)
+    ids, n_cur = [], nv[0]
+    for t in (1, 2):
+        room = n_cur * nv[t]
+        per = lengths if lengths.sum() <= room else np.array([room - 3, 3])
+        tab = np.full(room, -1, np.int32)
+        tab[np.argsort(W.uniform01(15 + t, room), kind="stable")[:per.sum()]] = np.repeat(np.arange(per.size), per)
+        ids.append(tab.reshape(n_cur, nv[t]))
+        n_cur = per.size
+    first = np.cumsum((0,) + nv[:2])
+    facts = [(f + np.arange(m)).astype(np.int32) for f, m in zip(first, nv)]
+    fp = W.uniform01(43 + columns, 9 * sum(nv)).astype(np.float32).reshape(9, sum(nv))
+    fp[::4, 20], fp[::4, 3] = fp[::4, 24], fp[::4, 9]
+    fold_of_few_and_many(dol, fp, np.repeat(np.arange(3), nv).astype(np.int32), facts, ids, k, 345, helpers and columns > 32 and k < 8)
+
+
 # ---------------------------------------------------------------- config 5
 
 @pytest.mark.parametrize("batch,side,rounds", [(256, 32, 64), (33, 7, 20), (2, 3, 5)])
@@ -2584,6 +2697,105 @@ def test_dense_maps_with_one_and_several_long_columns(dol, na, nb, n_long, B):
     dol.apply2(dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b)), f, None, out)
     assert_close(host(out.prob)[look], want, "forward")
     np.testing.assert_array_equal(host(out.prob)[look] == 1.0, pre32 >= 1.0)
+
+
+def lane_tree(x, pairs_first):
+    """The sum over the last axis as lanes exchange them: neighbours first, or the lane half of them away first.  float32."""
+    while x.shape[-1] > 1:
+        x = x[..., 0::2] + x[..., 1::2] if pairs_first else x[..., :x.shape[-1] // 2] + x[..., x.shape[-1] // 2:]
+    return x[..., 0]
+
+
+def fma32(a, b, c):
+    """float32 fused multiply-add; exact before the one rounding for factors of 16 bits and sums of less than 2^20 times their unit."""
+    return (a.astype(np.float64) * b.astype(np.float64) + c.astype(np.float64)).astype(np.float32)
+
+
+@pytest.mark.parametrize("na,nb,B", [(250, 10, 3), (257, 3, 2), (1000, 10, 2), (1011, 4, 5), (1009, 9, 2)])
+def test_dense_map_sums_keep_their_order(dol, na, nb, B):
+    """The short operand's gradient bit for bit: a lane's rows 64 apart, four at a time, neighbouring lanes' sums first, then rows
+    of 16, halves and wavefronts in order, each wavefront 256 rows."""
+    ids = (W.splitmix64(61 + na, np.arange(na * nb)) % np.uint64(2 * na)).astype(np.int32).reshape(na, nb)
+    f = dol.FnTable.create_dense(ids)
+    assert f.kernel_at(True, B).startswith("damp_byj_bwd"), f.kernel_at(True, B)
+    bits = lambda seed, n: (W.splitmix64(seed, np.arange(n)) % np.uint64(1 << 16)).astype(np.float32)
+    a = bits(1, B * na).reshape(B, na) * np.float32(2.0 ** -26)
+    b = bits(2, B * nb).reshape(B, nb) * np.float32(2.0 ** -16)
+    g = (bits(3, B * f.n_out).reshape(B, f.n_out) - np.float32(32768.0)) * np.float32(2.0 ** -12)
+    da, db, out = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b)), dol.Dist.empty(f.out_syms, B)
+    dol.apply2(da, db, f, None, out)
+    assert float(out.prob.max()) < 1.0
+    ga, gb = torch.empty((B, na), device="cuda"), torch.empty((B, nb), device="cuda")
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), dev(g), ga, gb)
+    rows = -(-na // 256) * 256
+    v, av = np.zeros((B, nb, rows), np.float32), np.zeros((B, 1, rows), np.float32)
+    v[:, :, :na] = np.moveaxis(g[:, np.searchsorted(f.out_syms, ids)], 2, 1)
+    av[:, 0, :na] = a
+    v, av = v.reshape(B, nb, -1, 4, 64), av.reshape(B, 1, -1, 4, 64)
+    acc = np.zeros((B, nb, rows // 256, 64), np.float32)
+    for x in range(4):
+        acc = fma32(v[:, :, :, x], np.broadcast_to(av[:, :, :, x], acc.shape), acc)
+    shares = lane_tree(acc, True)
+    want = np.zeros((B, nb), np.float32)
+    for w in range(shares.shape[-1]):
+        want = want + shares[..., w]
+    np.testing.assert_array_equal(host(gb), want)
+
+
+@pytest.mark.parametrize("na,B", [(19, 64), (28, 16), (100, 80)])
+def test_sum_table_sums_keep_their_order(dol, na, B):
+    """The same for a table of sums, whose samples have 32 lanes each (in whole tiles: what is left of a batch is summed in stretches)."""
+    nb = 10
+    f = dol.FnTable.create_dense(np.add.outer(np.arange(na), np.arange(nb)).astype(np.int32))
+    assert f.kernel_at(True, B).startswith("damp_conv_bwd_tile_kernel"), f.kernel_at(True, B)
+    bits = lambda seed, n: (W.splitmix64(seed, np.arange(n)) % np.uint64(1 << 16)).astype(np.float32)
+    a = bits(4, B * na).reshape(B, na) * np.float32(2.0 ** -24)
+    b = bits(5, B * nb).reshape(B, nb) * np.float32(2.0 ** -20)
+    g = (bits(6, B * f.n_out).reshape(B, f.n_out) - np.float32(32768.0)) * np.float32(2.0 ** -12)
+    da, db, out = dol.Dist(np.arange(na), dev(a)), dol.Dist(np.arange(nb), dev(b)), dol.Dist.empty(f.out_syms, B)
+    dol.apply2(da, db, f, None, out)
+    ga, gb = torch.empty((B, na), device="cuda"), torch.empty((B, nb), device="cuda")
+    dol.backward(dol.OpRecord(dol.OP_APPLY2, da, db, out, f=f), dev(g), ga, gb)
+    rows = -(-na // 32) * 32
+    acc = np.zeros((B, nb, 32), np.float32)
+    for i0 in range(0, rows, 32):
+        live = np.arange(i0, min(i0 + 32, na))
+        for j in range(nb):
+            acc[:, j, :live.size] = fma32(g[:, live + j], a[:, live], acc[:, j, :live.size])
+    np.testing.assert_array_equal(host(gb), lane_tree(acc, True))
+
+
+@pytest.mark.parametrize("batch,n_sym,n_facts,k", [(2, 60, 63, 1), (3, 1100, 9, 2), (300, 130, 41, 3), (1, 2500, 17, 5)])
+def test_dtkp_gradient_sums_keep_their_order(dol, batch, n_sym, n_facts, k):
+    """The top-k gradient bit for bit: a lane's symbols ascending, the lane 32 away first, the nearest last, wavefronts in order, every share
+    divided by the fact's probability (1/2, so that the quotient is exact)."""
+    masks = (np.uint64(1) << (W.splitmix64(71 + n_facts, np.arange(2 * batch * n_sym * k)).reshape(2, batch, n_sym, k) % np.uint64(n_facts)))
+    masks = masks[0] | masks[1]
+    masks[:, ::7, k - 1] = oracle.ABSENT
+    prob = (W.uniform01(72, masks.size).astype(np.float32).reshape(masks.shape) * np.float32(0.9 / k))
+    prob[masks == oracle.ABSENT] = 0.0
+    g = W.normal(73, batch * n_sym).astype(np.float32).reshape(batch, n_sym)
+    dist = dol.Dist.empty(np.arange(n_sym, dtype=np.int32), batch, k=k)
+    dist.proof_mask.copy_(dev(masks.view(np.int64)))
+    dist.proof_prob.copy_(dev(prob))
+    gf = torch.empty((batch, n_facts), device="cuda")
+    dol.dtkp_backward(dist, dol.Prov(dol.DTKP, k, torch.full((batch, n_facts), 0.5, device="cuda"), None), dev(g), gf)
+    waves = max(1, min(16, -(-n_sym // 64)))
+    steps = -(-n_sym // (64 * waves))
+    coef, held = np.zeros((batch, steps * waves * 64, k), np.float32), np.zeros((batch, steps * waves * 64, k), np.uint64)
+    coef[:, :n_sym] = g[:, :, None] * prob
+    held[:, :n_sym] = np.where(masks == oracle.ABSENT, np.uint64(0), masks)
+    coef, held = coef.reshape(batch, steps, waves, 64, k), held.reshape(batch, steps, waves, 64, k)
+    want = np.zeros((batch, n_facts), np.float32)
+    for j in range(n_facts):
+        acc = np.zeros((batch, waves, 64), np.float32)
+        for t in range(steps):
+            for x in range(k):
+                acc = acc + np.where((held[:, t, :, :, x] >> np.uint64(j)) & np.uint64(1) == 1, coef[:, t, :, :, x], np.float32(0.0))
+        shares = lane_tree(acc, False)
+        for w in range(waves):
+            want[:, j] = want[:, j] + shares[:, w] * np.float32(2.0)
+    np.testing.assert_array_equal(host(gf), want)
 
 
 @pytest.mark.parametrize("nb", [4, 16, 40])
