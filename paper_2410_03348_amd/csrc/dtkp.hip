@@ -96,7 +96,8 @@ struct PairOffer {
     __device__ __forceinline__ uint64_t *lane_masks() const { return reinterpret_cast<uint64_t *>(facts() + A.shared_facts); }
     __device__ __forceinline__ void ask()
     {
-        if (kShared && static_cast<int>(threadIdx.x) < A.shared_facts) mine = reinterpret_cast<const uint4 *>(A.fact_b)[threadIdx.x];
+        if (kShared && static_cast<int>(threadIdx.x) < A.shared_facts)
+            mine = reinterpret_cast<const uint4 *>(A.fact_b)[threadIdx.x];
     }
     __device__ __forceinline__ void share() const
     {
@@ -216,7 +217,8 @@ struct PairOffer {
     // lane's thread << 8.  Read again from memory once the winners are known: 192.6 us for the formula's pass, 184.2 so.)
     // ahead: word(q)
     template <class Word>
-    __device__ __forceinline__ void run_short(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, uint32_t ahead, Word word) const
+    __device__ __forceinline__ void run_short(TopKeys<K> &keys, uint32_t q, uint32_t q1, uint32_t step, uint32_t ahead,
+                                              Word word) const
     {
         static_assert(K * kLongDtkpCol <= 256 || K > kKeyProofs, "a candidate's number");
         uint64_t *put = lane_masks() + threadIdx.x;
@@ -225,9 +227,9 @@ struct PairOffer {
             const Tuple t = tuple(ahead);
             ahead = word(min(q + step, q1 - 1));
             // (uniform.  Where lanes took one way each, after both, facts that are held already, below others or rivals cost up to
-            // a quarter of the launch; us, so and now: table 3 000 x 10 -> 3 000, 64 samples, k = 4 30.7 and 25.1, 3 000 x 20 -> 6 000,
-            // 300 samples, k = 2 114 and 94, 300 x 40 -> 700 with 16 lanes to a column, 100 samples, k = 3 14.0 and 12.5.  One
-            // candidate after the other there too: 11.5, and where facts are new 16.7 instead of 15.7)
+            // a quarter of the launch; us, so and now: table 3 000 x 10 -> 3 000, 64 samples, k = 4 30.7 and 25.1, 3 000 x 20 ->
+            // 6 000, 300 samples, k = 2 114 and 94, 300 x 40 -> 700 with 16 lanes to a column, 100 samples, k = 3 14.0 and 12.5.
+            // One candidate after the other there too: 11.5, and where facts are new 16.7 instead of 15.7)
             if (__ballot(!t.fresh()) == 0) {
                 float pr[K];
                 bool ok[K], falls = true;
@@ -535,7 +537,8 @@ dtkp_prob_bwd_kernel(int32_t parts, int32_t n_sym, int32_t n_facts, const uint64
         float u[4], t[2];
 #pragma unroll
         for (int x = 0; x < 4; ++x) {
-            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[j0 + 2 * x]), __float_as_uint(acc[j0 + 2 * x + 1]), false, false);
+            const uint32_t a = __float_as_uint(acc[j0 + 2 * x]), b = __float_as_uint(acc[j0 + 2 * x + 1]);
+            const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
             u[x] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
         }
 #pragma unroll

@@ -7,15 +7,16 @@
 // one of 758 columns 16, with up to 8 (then 16 lanes) 79 and 11, with up to 4 and four lanes up to 16, as here, 75 and 8.
 // Results gathered in LDS and stored as whole lines were slower (106 us): a workgroup of neighbours waits for its longest
 // column.
-// With lists ranked by keys that table took 61 us (73 before), k = 3, and 57 now: a tuple waits for its lists only (its word is read
+// With lists ranked by keys that table took 61 us (73 before), k = 3, then 57: a tuple waits for its lists only (its word is read
 // one tuple ahead, the first with the column's length, its fact lies in LDS), where the fact is new to all proofs one look at them
-// says so and the lists meet as two lanes' do, columns of one tuple go from the operand's list to the result.  Not bound by
-// issue (347 -> 308 vector instructions a wavefront between the first of these and all, no time) but by what a wavefront waits for:
-// 14 us are its way to the first tuple, 21 the short columns, 13 those of 5 to 16 tuples, 10 the longer ones.  Those by a quarter of
-// the lanes: a third fewer instructions, 68 us.  147 MB leave for 98 MB of results, whose order is
-// that of the columns' lengths.  Lengths sorted inside fewer than 4 096 columns leave fewer bytes (129 MB) but unequal lanes:
-// the pass of that expression took 206 us and more instead of 204 (passes in this file repeat the same inputs; where these change
-// from pass to pass they take some ten us more).  Lists read four tuples ahead: 80 us, for want of wavefronts.
+// says so and the lists meet as two lanes' do, columns of one tuple go from the operand's list to the result; and 52 now that facts
+// and lists have a kernel each and LDS is read as LDS (dtkp.hip).  Not bound by issue (347 -> 308 vector instructions a wavefront
+// between the first of these and the second, no time) but by what a wavefront waits for: of the 57, 14 us were its way to the first
+// tuple, 21 the short columns, 13 those of 5 to 16 tuples, 10 the longer ones.  Those by a quarter of the lanes: a third fewer
+// instructions, 68 us.  147 MB leave for 98 MB of results, whose order is that of the columns' lengths.  Lengths sorted inside
+// fewer than 4 096 columns leave fewer bytes (129 MB) but unequal lanes: the pass of that expression took 206 us and more instead
+// of 204 (passes in this file repeat the same inputs; where these change from pass to pass they take some ten us more).  Lists read
+// four tuples ahead: 80 us, for want of wavefronts.
 #pragma once
 
 #include "dtkp_util.h"
@@ -60,11 +61,12 @@ inline int column_threads(const ColumnArgs &A) { return A.n_huge > 0 ? kHugeThre
 //
 // Where the lists of all samples exceed the L2s, the samples go in sets, one sample's columns of all lengths (the very long
 // ones apart: they start first) close together: a line of results holds columns of several lengths and leaves the L2 whole, and
-// its lists are read once.  A set is eight samples, one for each XCD, or more where they are small, so that a set has work for the whole chip.
-// (Seven-symbol expression, k = 3: with 64 samples the last table writes 116 instead of 149 MB and the unary Apply behind it takes
-// 26.6 instead of 29.1 us, the pass 177 instead of 180; with 128 samples 288 instead of 311 us, with 1 024 2 186 instead of
-// 2 668.  Sets of 16 or 32: 178 and 179, 2 237 and 2 252.  With 16 samples, 27 MB, two sets cost 2 %.  The very long columns in
-// their sets: 185, the last set's workgroup columns ending late.)
+// its lists are read once.  A set is eight samples, one for each XCD, or more where they are small, so that a set has work for the
+// whole chip.
+// (Seven-symbol expression, k = 3: with 64 samples the last table writes 116 instead of 149 MB and the unary Apply
+// behind it takes 26.6 instead of 29.1 us, the pass 177 instead of 180; with 128 samples 288 instead of 311 us, with 1 024 2 186
+// instead of 2 668.  Sets of 16 or 32: 178 and 179, 2 237 and 2 252.  With 16 samples, 27 MB, two sets cost 2 %.  The very long
+// columns in their sets: 185, the last set's workgroup columns ending late.)
 constexpr int64_t kL2Bytes = int64_t(32) << 20, kSetBytes = int64_t(8) << 20;
 template <int K>
 inline unsigned column_launch(ColumnArgs &A)
@@ -78,9 +80,13 @@ inline unsigned column_launch(ColumnArgs &A)
     }
     A.per_S = A.S > 1 ? ~uint64_t(0) / static_cast<uint32_t>(A.S) + 1 : 0;
     auto eight = [](int64_t n) { return static_cast<uint32_t>((n + 7) / 8 * 8); };
-    auto groups = [&](int32_t samples, int32_t n, int lanes) { return eight(static_cast<int64_t>(samples) * ((n + threads / lanes - 1) / (threads / lanes))); };
+    auto groups = [&](int32_t samples, int32_t n, int lanes) {
+        const int per = threads / lanes;
+        return eight(static_cast<int64_t>(samples) * ((n + per - 1) / per));
+    };
     auto blocks = [&](int32_t samples) {
-        return SetBlocks{groups(samples, A.n_mid, 16), groups(samples, A.n_quad, 4), eight((static_cast<int64_t>(samples) * A.S + threads - 1) / threads)};
+        return SetBlocks{groups(samples, A.n_mid, 16), groups(samples, A.n_quad, 4),
+                         eight((static_cast<int64_t>(samples) * A.S + threads - 1) / threads)};
     };
     auto all = [](const SetBlocks &b) { return b.mid + b.quad + b.lane; };
     A.b_huge = eight(static_cast<int64_t>(A.batch) * A.n_huge);
@@ -89,13 +95,15 @@ inline unsigned column_launch(ColumnArgs &A)
     return A.b_huge + A.b_wave + (A.sets - 1) * all(A.full) + all(A.last);
 }
 
-// Offer: ask() and share() - what all threads of a workgroup need is on its way, is there; begin(s) - the sample; ahead(r) - the first tuple of the r-th
-// short column, asked for before anything is known about it; listed(top, q, q1, step) - offers the tuples q, q + step, .. below q1 of col_ptr's lists;
-// laned(top, len, r, c) - those of column c, the r-th in order; where it has_short(), short_listed and short_laned offer the same,
-// of at most kLongDtkpCol tuples a lane, to a list of keys, and short_take() finds the proofs of the list, the same of
-// `lanes` lanes, or says that it cannot (to each of them); kOneWay - how lists take in candidates (TopK::insert).
-// (A candidate's way into a list of probabilities and masks takes some thirty instructions, most of them choices, and so does each
-// entry of another lane's list; into a list of keys seven, and a whole list of three twelve and the lane shifts.)
+// Offer: ask() and share() - what all threads of a workgroup need is on its way, is there; begin(s) - the sample; ahead(r) - the
+// first tuple of the r-th short column, asked for before anything is known about it; listed(top, q, q1, step) - offers the
+// tuples q, q + step, .. below q1 of col_ptr's lists; laned(top, len, r, c) - those of column c, the r-th in order; where it
+// has_short(), short_listed and short_laned offer the same, of at most kLongDtkpCol tuples a lane, to a list of keys, and
+// short_take() finds the proofs of the list, the same of `lanes` lanes, or says that it cannot (to each of them); kOneWay - how
+// lists take in candidates (TopK::insert).
+// (A candidate's way into a list of probabilities and masks takes some thirty
+// instructions, most of them choices, and so does each entry of another lane's list; into a list of keys seven, and a whole list of
+// three twelve and the lane shifts.)
 constexpr int kKeyProofs = 4;           // longest lists ranked by keys
 
 // Are two neighbours among the first facts of this wavefront's (first) sample equally probable?  Then proofs are too, most columns
@@ -161,7 +169,8 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
         if (ci >= n) return;                        // (all lanes of a group; never a huge column's)
         offer.begin(s);
         if constexpr (K <= kKeyProofs) {
-            if (lanes <= 16 && offer.has_short() && !equal_facts(offer.A.fact_prob, offer.A.n_facts, s)) {      // (at most kLongDtkpCol tuples a lane)
+            // (at most kLongDtkpCol tuples a lane)
+            if (lanes <= 16 && offer.has_short() && !equal_facts(offer.A.fact_prob, offer.A.n_facts, s)) {
                 TopKeys<K> keys;
                 offer.short_listed(keys, A.col_ptr[c] + t % lanes, A.col_ptr[c + 1], lanes);
                 keys.merge(lanes);
@@ -223,7 +232,7 @@ __device__ __forceinline__ void dtkp_columns(const ColumnArgs &A, Offer offer)
     if (!live) return;
     offer.begin(s);
     bool keys_ok = false;
-    if constexpr (K <= kKeyProofs) keys_ok = offer.has_short() && !equal_facts(offer.A.fact_prob, offer.A.n_facts, s);      // (the same for all)
+    if constexpr (K <= kKeyProofs) keys_ok = offer.has_short() && !equal_facts(offer.A.fact_prob, offer.A.n_facts, s);     // (for all)
     if (len == 0) return;
     bool todo = true;
     if constexpr (K <= kKeyProofs) {

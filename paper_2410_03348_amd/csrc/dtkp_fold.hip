@@ -1,11 +1,11 @@
 // Fused left fold of Apply under DTKP-AM (the loop of Fig. 2 with the top-k proofs provenance of Sec. 3.2 /
 // App. A) over naturally initialised inputs: symbol i of input t carries the single proof {fact_of_sym[t][i]}.
 // One wavefront owns a sample: the fact probabilities and the running Distribution's proofs (S x k masks and
-// probabilities) live in LDS, a lane (two where the wavefront has them to spare) owns an output symbol, streams the candidates of its
-// tuples through a k-entry sorted list in registers and writes the list back to LDS for the next stage.  Up to four wavefronts form a
-// workgroup and share one copy of the symbol side.  HBM sees the fact probabilities once and the final Distribution
-// once.  Optionally the gradient of the final tag probabilities w.r.t. the fact probabilities follows in the same
-// launch (lane f owns fact f).
+// probabilities) live in LDS, a lane (two where the wavefront has them to spare) owns an output symbol, streams the candidates of
+// its tuples through a k-entry sorted list in registers and writes the list back to LDS for the next stage.  Up to four wavefronts
+// form a workgroup and share one copy of the symbol side.  HBM sees the fact probabilities once and the final Distribution once.
+// Optionally the gradient of the final tag probabilities w.r.t. the fact probabilities follows in the same launch (lane f owns fact
+// f).
 // Candidate order, proof probabilities, exclusion test and list order are those of dol_apply2, so the result is the
 // same bit for bit.  The sorted list of a column carries probabilities and the origin of each proof; masks are built
 // for the k winners only, and a stage whose input brings only new, higher facts (fresh_t below) never reads one.
@@ -32,9 +32,10 @@ constexpr int kDfWaves = 4;             // most wavefronts (samples) of one work
 //   fresh_t, bit 0: every fact of input t lies above every fact of the inputs before it and shares no exclusion group
 //           with any of them.  A proof of the running Distribution then never holds the new fact or a rival of it, and
 //           the product over ascending facts is the proof's stored probability times the new fact's: the stage needs
-//           no mask at all until its k winners are known.  Bit 1: and each input so far gives every symbol a fact of its own, none of them
-//           known before: a proof says which symbols it is of, and no two symbols of a Distribution have one in common.
-//           Bits 2 and 3: lanes help (dtkp_fold_stage), from bit 4 on: the stage's shares are the so many-th 64 words behind the others.
+//           no mask at all until its k winners are known.  Bit 1: and each input so far gives every symbol a fact of its own, none
+//           of them known before: a proof says which symbols it is of, and no two symbols of a Distribution have one in common.
+//           Bits 2 and 3: lanes help (dtkp_fold_stage), from bit 4 on: the stage's shares are the so many-th 64 words behind the
+//           others.
 enum Kind : int32_t { kFresh = 1, kDistinct = 2, kTwins = 4, kHelped = 8 };
 constexpr int kShareShift = 4;
 struct DtkpFoldArgs {
@@ -52,17 +53,18 @@ struct DtkpFoldArgs {
     int32_t n_shares;
 };
 
-// The K best distinct proofs of one column, by the whole wavefront: lane y < K ends with the y-th (id -1: none).  Lanes K .. 63 take
-// the candidates as they come, the first K lanes keep the best so far; K times the best of all is taken, the smallest mask among equal
-// probabilities, and with it whatever has its mask.  For probabilities that are finite and not below 0.
-// (Two facts of one probability, in one of a thousand samples of softmax outputs, make tens of such columns.  By its lane, a candidate at
-// a time, through code that no wavefront had fetched yet, a column took 4 us (k = 3) to 60 (k = 7) and the others of the stage with it:
-// Sum-6, k = 5, 2 048 samples 50 us with one such sample and 17.7 without any, k = 7 83 and 22.6, Sum-5, k = 3, 1 024 12.9 and 9.1;
-// so 28 and 17.8, 51 and 22.6, 9.5 and 9.1.)
-// One column after the other, though, where a lane each does all of a stage's at once: where more than kManyTies of them are to be ranked
-// they are exact_column's.  Logits twelve and thirty times as far apart, whose products underflow, us, columns by the wavefront up to 2, 4, 8,
-// 16, all: Sum-5, k = 3, 1 024 samples 20.2 20.4 23.8 27.4 27.3 and 63 63 69 144 217; Sum-6, k = 5, 12 000 153 145 169 225 224 and 504 507 516
-// 1 027 2 069; k = 7, 6 000 248 248 239 337 337 and 657 658 666 1 308 3 465; one sample with two equal facts, k = 5, 2 048 28 28 25 25 25.
+// The K best distinct proofs of one column, by the whole wavefront: lane y < K ends with the y-th (id -1: none).  Lanes K .. 63
+// take the candidates as they come, the first K lanes keep the best so far; K times the best of all is taken, the smallest mask
+// among equal probabilities, and with it whatever has its mask.  For probabilities that are finite and not below 0.
+// (Two facts of one probability, in one of a thousand samples of softmax outputs, make tens of such columns.  By its lane, a
+// candidate at a time, through code that no wavefront had fetched yet, a column took 4 us (k = 3) to 60 (k = 7) and the others of
+// the stage with it: Sum-6, k = 5, 2 048 samples 50 us with one such sample and 17.7 without any, k = 7 83 and 22.6, Sum-5, k = 3,
+// 1 024 12.9 and 9.1; so 28 and 17.8, 51 and 22.6, 9.5 and 9.1.)
+// One column after the other, though, where a lane each does all of a stage's at once: where more than kManyTies of them are to be
+// ranked they are exact_column's.  Logits twelve and thirty times as far apart, whose products underflow, us, columns by the
+// wavefront up to 2, 4, 8, 16, all: Sum-5, k = 3, 1 024 samples 20.2 20.4 23.8 27.4 27.3 and 63 63 69 144 217; Sum-6, k = 5,
+// 12 000 153 145 169 225 224 and 504 507 516 1 027 2 069; k = 7, 6 000 248 248 239 337 337 and 657 658 666 1 308 3 465; one sample
+// with two equal facts, k = 5, 2 048 28 28 25 25 25.
 template <int K>
 constexpr int kManyTies = K <= 5 ? 4 : 8;
 
@@ -83,7 +85,8 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x)
 }
 
 template <int K, int KA>
-__device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const uint32_t *l_rec, const uint64_t *cm, const float *cp, const float *fp)
+__device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const uint32_t *l_rec, const uint64_t *cm,
+                                              const float *cp, const float *fp)
 {
     const int lane = threadIdx.x & (kWave - 1);
     Ranked best{-1.0f, -1};
@@ -114,8 +117,9 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
             uint64_t least = kAbsent;
             for (uint64_t equal = __ballot(key == top); equal; equal &= equal - 1) {
                 const int at = __builtin_ctzll(equal);
-                const uint64_t m = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hi), at))) << 32 |
-                                   static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(lo), at));
+                const uint32_t m_hi = __builtin_amdgcn_readlane(static_cast<int>(hi), at);
+                const uint32_t m_lo = __builtin_amdgcn_readlane(static_cast<int>(lo), at);
+                const uint64_t m = static_cast<uint64_t>(m_hi) << 32 | m_lo;
                 if (from < 0 || m < least) from = at, least = m;
             }
             if (lane == y) best.p = __uint_as_float(top - 1), best_mask = least;
@@ -135,27 +139,29 @@ __device__ __forceinline__ Ranked rank_column(uint32_t q0, uint32_t q1, const ui
 // list times one factor, i.e. in descending order already: the k + 1 best of both lists are the elementwise maxima of one
 // and the other reversed, sorted again by a short network.  Masks matter only where probabilities are equal: two of the kept
 // ones, or the last one and the best that dropped out, which is what the list's entry behind the k-th holds (of all that
-// dropped out on the way none is larger).  Such a column is ranked again by the whole wavefront (rank_column), or where there are many
-// candidate by candidate (exact_column), as is every column of a sample (plain = false) with a fact whose probability is negative, -0
-// or no finite number, or where an eighth of the facts have the probability of their neighbours: most columns would have ties and be done twice (Sum-5, k = 3,
-// B=1 024, facts of one probability: 65 us, 58.4 so; facts in steps of 1/16 64 and 58.2; Sum-6, k = 5, B=12 000 560 and 516).
+// dropped out on the way none is larger).  Such a column is ranked again by the whole wavefront (rank_column), or where there are
+// many candidate by candidate (exact_column), as is every column of a sample (plain = false) with a fact whose probability is
+// negative, -0 or no finite number, or where an eighth of the facts have the probability of their neighbours: most columns would
+// have ties and be done twice (Sum-5, k = 3, B=1 024, facts of one probability: 65 us, 58.4 so; facts in steps of 1/16 64 and 58.2;
+// Sum-6, k = 5, B=12 000 560 and 516).
 // (Bound by the vector ALUs.  k = 5 costs 33 instructions a tuple by the compiled code, none of them a choice; 65 with
 // probabilities and origins exchanged by compare and select, which the units take 1.9 ns a piece for, and repeated choices by one
 // condition longer.  Of the 33, 19 are the list's maxima and minima in twice the time of the others, and 14 the products, the
-// origins, the addresses and the loop.  What a stage does besides is half as much again: a rank without a proof keeps an origin that can be
-// read and a word of ones for its mask and probability to be put together with, and only the last stage adds probabilities up: Sum-6,
-// k = 5, 12 000 samples 56.5 us, 55.6 so; k = 7, 1 024 samples 16.8 and 16.5.  The code lies in the order it is run in, with what is seldom
-// run behind: Sum-5, k = 3, 1 024 samples 8.1 us so, 8.4 with the first stage's behind the others' and the seldom run between them.  Where
-// the compiled code lies moves small batches by some 2 % either way.)
-// Where a stage has fewer columns than the wavefront has lanes the others help (FRESH stages): a helper works on the second half of a
-// column's tuples, and the two lists become one as a tuple's and the running one do, which costs up to two tuples' worth.
-//   few samples: stages of at most 32 columns are worked on by twins, the wavefront's halves have the same columns.  Of Sum-6's five stages
-//   two have 19 and 28 columns of up to 10 tuples: k = 5, 12 000 samples 55.6 us, 52.7 so, 1 024 13.4 and 12.7; Sum-5, k = 3, 1 024 samples
-//   8.1 and 7.4, 4 096 13.1 and 12.3.
-//   MANY: a lane looks its share up (Share), and of more columns the longest are helped with (of 37 all 27 of more than five tuples).  That
-//   takes a trip to LDS for the share and one for the lists, which several wavefronts on a SIMD hide: Sum-6, k = 5, 12 000 samples 52.5
-//   and 50.0, k = 7 73.0 and 68.6, Sum-5, k = 3, 12 000 28.0 and 26.6, 4 096 12.3 and 12.0, but 2 048 8.6 and 8.7, 1 024 7.4 and 7.7; Sum-3,
-//   k = 5, 2 048 7.7 and 8.0.  (Both ways in one kernel take 76 registers, one wavefront less to a SIMD: 52.6.)
+// origins, the addresses and the loop.  What a stage does besides is half as much again: a rank without a proof keeps an origin
+// that can be read and a word of ones for its mask and probability to be put together with, and only the last stage adds
+// probabilities up: Sum-6, k = 5, 12 000 samples 56.5 us, 55.6 so; k = 7, 1 024 samples 16.8 and 16.5.  The code lies in the order
+// it is run in, with what is seldom run behind: Sum-5, k = 3, 1 024 samples 8.1 us so, 8.4 with the first stage's behind the
+// others' and the seldom run between them.  Where the compiled code lies moves small batches by some 2 % either way.)
+// Where a stage has fewer columns than the wavefront has lanes the others help (FRESH stages): a helper works on the second half of
+// a column's tuples, and the two lists become one as a tuple's and the running one do, which costs up to two tuples' worth.
+//   few samples: stages of at most 32 columns are worked on by twins, the wavefront's halves have the same columns.  Of Sum-6's
+//   five stages two have 19 and 28 columns of up to 10 tuples: k = 5, 12 000 samples 55.6 us, 52.7 so, 1 024 13.4 and 12.7; Sum-5,
+//   k = 3, 1 024 samples 8.1 and 7.4, 4 096 13.1 and 12.3.
+//   MANY: a lane looks its share up (Share), and of more columns the longest are helped with (of 37 all 27 of more than five
+//   tuples).  That takes a trip to LDS for the share and one for the lists, which several wavefronts on a SIMD hide: Sum-6, k = 5,
+//   12 000 samples 52.5 and 50.0, k = 7 73.0 and 68.6, Sum-5, k = 3, 12 000 28.0 and 26.6, 4 096 12.3 and 12.0, but 2 048 8.6 and
+//   8.7, 1 024 7.4 and 7.7; Sum-3, k = 5, 2 048 7.7 and 8.0.  (Both ways in one kernel take 76 registers, one wavefront less to a
+//   SIMD: 52.6.)
 constexpr int kListCost = 2;            // tuples saved that two lists are worth
 constexpr int kManySamples = 3072;      // three to a SIMD (and see share_lookup_pays)
 
@@ -170,7 +176,8 @@ struct Share {                          // a lane's, in one word
 
 __device__ __forceinline__ double key_of_lane(double x, int lane)
 {
-    return __hiloint2double(__builtin_amdgcn_ds_bpermute(4 * lane, __double2hiint(x)), __builtin_amdgcn_ds_bpermute(4 * lane, __double2loint(x)));
+    const int hi = __builtin_amdgcn_ds_bpermute(4 * lane, __double2hiint(x)), lo = __builtin_amdgcn_ds_bpermute(4 * lane, __double2loint(x));
+    return __hiloint2double(hi, lo);
 }
 
 // x of the lane in the lower (upper) half of the wavefront that has this lane's place there
@@ -184,14 +191,16 @@ __device__ __forceinline__ double key_of_half(double x, int upper)
 template <int K, int KA, bool FRESH, bool MANY>
 __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s, int S, bool last, const uint32_t *l_ptr,
                                                 const uint32_t *l_rec, const uint64_t *cm, const float *cp, uint64_t *nm,
-                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain, int kind, const uint32_t *shares)
+                                                float *np, const uint64_t *rival, const float *fp, float *gh, bool plain, int kind,
+                                                const uint32_t *shares)
 {
     const bool distinct = kind & kDistinct, helped = FRESH && (kind & (MANY ? kHelped : kTwins));
     const int lane = threadIdx.x & (kWave - 1);
     for (int base = 0; base < S; base += kWave) {
         const Share mine{MANY && helped ? shares[lane] : Share::pack(lane, 0, Share::kWhole)};
         const int c = base + (MANY ? mine.col() : helped ? lane % (kWave / 2) : lane);
-        const bool there = c < S && (MANY ? mine.role() < Share::kHelper : !(helped && lane >= kWave / 2));     // (all help where a column has ties)
+        // (all help where a column has ties)
+        const bool there = c < S && (MANY ? mine.role() < Share::kHelper : !(helped && lane >= kWave / 2));
         float tp[K];
         int tid_[K];
         int gone[K];                                        // all bits: no proof
@@ -340,8 +349,8 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                     tid_[x] = __double2loint(top[x]);       // (0, or that of an absent proof, where there is none)
                     (x + 1 < K ? inner : again) |= hi == next && hi >= 0;
                 }
-                // Equal probabilities among the kept ones: the masks' order, which only the result shows, unless a proof may be there
-                // twice.  The last of them as probable as the best that dropped out: the kept ones may be others.
+                // Equal probabilities among the kept ones: the masks' order, which only the result shows, unless a proof may be
+                // there twice.  The last of them as probable as the best that dropped out: the kept ones may be others.
                 again |= inner && (last || !distinct);
                 uint64_t todo = __ballot(again && there);
                 if (__builtin_expect(__builtin_popcountll(todo) > kManyTies<K>, 0)) {
@@ -354,7 +363,9 @@ __device__ __forceinline__ void dtkp_fold_stage(const DtkpFoldArgs &A, int64_t s
                 }
                 for (; __builtin_expect(todo != 0, 0); todo &= todo - 1) {
                     const int from = __builtin_ctzll(todo);
-                    const Ranked r = rank_column<K, KA>(__builtin_amdgcn_readlane(static_cast<int>(q0), from), __builtin_amdgcn_readlane(static_cast<int>(q1), from), l_rec, cm, cp, fp);
+                    const uint32_t its_q0 = __builtin_amdgcn_readlane(static_cast<int>(q0), from);
+                    const uint32_t its_q1 = __builtin_amdgcn_readlane(static_cast<int>(q1), from);
+                    const Ranked r = rank_column<K, KA>(its_q0, its_q1, l_rec, cm, cp, fp);
 #pragma unroll
                     for (int x = 0; x < K; ++x) {
                         const float p = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r.p), x));
@@ -436,7 +447,8 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
     const int bufs = A.max_s > kWave ? 2 : 1, flip = (bufs - 1) * A.max_s * K;
     const int n_words = A.n_words + (MANY ? A.n_shares : 0);
-    unsigned char *mine_lds = lds_raw + 64 * sizeof(uint64_t) + sizeof(uint32_t) * n_words + static_cast<size_t>(wave) * A.wave_bytes;
+    unsigned char *mine_lds = lds_raw + 64 * sizeof(uint64_t) + sizeof(uint32_t) * n_words +
+                              static_cast<size_t>(wave) * A.wave_bytes;
     uint64_t *bufm = reinterpret_cast<uint64_t *>(mine_lds);
     float *bufp = reinterpret_cast<float *>(bufm + bufs * A.max_s * K);
     float *fp = bufp + bufs * A.max_s * K;
@@ -485,8 +497,10 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
         const int kind = __builtin_amdgcn_readfirstlane(static_cast<int>(w[4 + 4 * t]));
         const bool last = t == A.n - 1;
         const uint32_t *shares = w + A.n_words + kWave * (kind >> kShareShift);
-        if (__builtin_expect(kind & kFresh, kFresh)) dtkp_fold_stage<K, KA, true, MANY>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, kind, shares);
-        else dtkp_fold_stage<K, KA, false, MANY>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, kind, shares);
+        if (__builtin_expect(kind & kFresh, kFresh))
+            dtkp_fold_stage<K, KA, true, MANY>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, kind, shares);
+        else
+            dtkp_fold_stage<K, KA, false, MANY>(A, s, S, last, l_ptr, l_rec, cm, cp, nm, np, rival, fp, gh, plain, kind, shares);
         wave_lds_fence();
     };
     stage(1, std::integral_constant<int, 1>{});         // the first operand is naturally initialised: one proof per symbol
@@ -517,8 +531,9 @@ dtkp_fold_kernel(const DtkpFoldArgs A)
 #pragma unroll
             for (int x = 0; x < K; ++x) {
                 const uint64_t raw = fm[(base + cl) * K + x];
-                const uint64_t mm = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(raw))) |
-                                    (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(raw >> 32)))) << 32);
+                const uint32_t mm_lo = __builtin_amdgcn_readfirstlane(static_cast<int>(raw));
+                const uint32_t mm_hi = __builtin_amdgcn_readfirstlane(static_cast<int>(raw >> 32));
+                const uint64_t mm = static_cast<uint64_t>(mm_hi) << 32 | mm_lo;
                 if (mm == kAbsent) continue;
                 float others = 1.0f;
                 for (uint64_t r = mm; r; r &= r - 1) {
@@ -557,8 +572,8 @@ struct DtkpFoldPlan {
 
 Cache<DtkpFoldPlan> &g_fold_plans = *new Cache<DtkpFoldPlan>;      // never destroyed, as the other plan caches
 
-// How a stage's lanes help (Kind), and their shares where they do: the columns in their order, and the other lanes help with those of
-// more than `most` tuples, which is the smallest number so that all of these get one.
+// How a stage's lanes help (Kind), and their shares where they do: the columns in their order, and the other lanes help with those
+// of more than `most` tuples, which is the smallest number so that all of these get one.
 int32_t add_shares(const dol_fn_table *f, std::vector<int32_t> &shares)
 {
     const int S = f->n_out;
@@ -625,7 +640,8 @@ bool share_lookup_pays(const DtkpFoldPlan &p, int K)
     if (!p.wide || p.lds + p.share_bytes() > kDfLds) return false;
     auto workgroups = [&](FoldKernel kernel, size_t lds) {
         int n = 0;
-        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(kernel), p.waves * kWave, lds);
+        const void *const entry = reinterpret_cast<const void *>(kernel);
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, entry, p.waves * kWave, lds);
         if (e != hipSuccess) (void)hipGetLastError();
         return e == hipSuccess ? n : 0;
     };
@@ -762,7 +778,8 @@ static dol_status fold_checked(const dol_dtkp_fold *fold, const dol_prov *prov, 
     const int32_t batch = fold->inputs[0]->batch, s_last = (*plan)->s_last;
     if (o->batch != batch || o->n_sym != s_last || o->ld < o->n_sym)
         return fail(DOL_ESHAPE, "out has %d x %d, the fold produces %d x %d", o->batch, o->n_sym, batch, s_last);
-    if ((*plan)->lds > kDfLds) return fail(DOL_EUNSUPPORTED, "the fold needs %zu bytes of LDS per sample, more than %zu", (*plan)->lds, kDfLds);
+    if ((*plan)->lds > kDfLds)
+        return fail(DOL_EUNSUPPORTED, "the fold needs %zu bytes of LDS per sample, more than %zu", (*plan)->lds, kDfLds);
     return DOL_OK;
 }
 
@@ -812,7 +829,8 @@ extern "C" dol_status dol_dtkp_fold_apply2(const dol_dtkp_fold *fold, const dol_
         if (A.ldg < s_last) return fail(DOL_ESHAPE, "grad_out_ld = %lld is smaller than %d", static_cast<long long>(A.ldg), s_last);
     }
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(A.batch) + waves - 1) / waves)), block(static_cast<unsigned>(waves * kWave));
+    const dim3 grid(static_cast<unsigned>((static_cast<int64_t>(A.batch) + waves - 1) / waves));
+    const dim3 block(static_cast<unsigned>(waves * kWave));
     hipLaunchKernelGGL(many ? fold_kernel<true>(K) : fold_kernel<false>(K), grid, block, lds, st, A);
     DOL_HIP(hipGetLastError());
     return DOL_OK;
