@@ -1,9 +1,23 @@
 // C ABI entry points of the operators: argument checks, plan lookup, dispatch to the kernels.
 #include "internal.h"
 
+#include <cstring>
+
 namespace dol {
 
 bool is_dtkp(const dol_prov *prov) { return prov && prov->kind == DOL_DTKP; }
+
+// Whether `out` names the symbols that the table produces.  (Mostly it does, and memcmp says so: symbol by symbol a call for 38 400 of
+// them took the host 10.7 us, or 13.4, by where the linker had put the loop; 4.1 so.)
+static dol_status check_out_syms(const dol_dist *out, const dol_fn_table *f)
+{
+    const size_t bytes = sizeof(int32_t) * f->out_syms.size();
+    if (!out->sym_ids || bytes == 0 || std::memcmp(out->sym_ids, f->out_syms.data(), bytes) == 0) return DOL_OK;
+    for (int32_t c = 0; c < f->n_out; ++c)
+        if (out->sym_ids[c] != f->out_syms[c])
+            return fail(DOL_EINVAL, "out.sym_ids[%d] = %d, the table produces %d there", c, out->sym_ids[c], f->out_syms[c]);
+    return DOL_OK;
+}
 
 dol_status check_prov(const dol_prov *prov, int32_t batch)
 {
@@ -61,9 +75,7 @@ dol_status dol_apply2(const dol_dist *a, const dol_dist *b, const dol_fn_table *
     if (a->batch != b->batch || a->batch != out->batch) return fail(DOL_ESHAPE, "batch sizes differ: %d, %d, %d", a->batch, b->batch, out->batch);
     if (a->n_sym != f->na || b->n_sym != f->nb || out->n_sym != f->n_out)
         return fail(DOL_ESHAPE, "operands have %d x %d -> %d symbols, the table is %d x %d -> %d", a->n_sym, b->n_sym, out->n_sym, f->na, f->nb, f->n_out);
-    if (out->sym_ids)
-        for (int32_t c = 0; c < f->n_out; ++c)
-            if (out->sym_ids[c] != f->out_syms[c]) return fail(DOL_EINVAL, "out.sym_ids[%d] = %d, the table produces %d there", c, out->sym_ids[c], f->out_syms[c]);
+    if (dol_status st = check_out_syms(out, f)) return st;
     if (dol_status st = check_work(a->batch, f->n_out)) return st;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     if (!dtkp)
@@ -91,9 +103,7 @@ dol_status dol_dtkp_apply2_input(const dol_dist *a, const int32_t *fact_of_sym_b
     for (int32_t j = 0; j < f->nb; ++j)
         if (fact_of_sym_b[j] < 0 || fact_of_sym_b[j] >= prov->n_facts)
             return fail(DOL_EINVAL, "fact_of_sym_b[%d] = %d outside 0..%d", j, fact_of_sym_b[j], prov->n_facts - 1);
-    if (out->sym_ids)
-        for (int32_t c = 0; c < f->n_out; ++c)
-            if (out->sym_ids[c] != f->out_syms[c]) return fail(DOL_EINVAL, "out.sym_ids[%d] = %d, the table produces %d there", c, out->sym_ids[c], f->out_syms[c]);
+    if (dol_status st = check_out_syms(out, f)) return st;
     if (dol_status st = check_work(a->batch, f->n_out)) return st;
     if (a->batch == 0 || f->n_out == 0) return DOL_OK;
     if (!out->proof_prob) return fail(DOL_EINVAL, "out.proof_prob is NULL");

@@ -1857,6 +1857,31 @@ def test_empty_batch_and_errors(dol):
     assert ei.value.status == 5
 
 
+@pytest.mark.parametrize("n", [1, 5, 1000])
+def test_results_under_other_symbols_are_refused(dol, n):
+    """out.sym_ids are compared with what the table produces, to the last one, whichever call makes the result; without any they pass."""
+    f = dol.FnTable.create_dense(3 * np.arange(n, dtype=np.int32)[:, None])
+    a, one = dol.Dist(np.arange(n), torch.full((2, n), 0.5, device="cuda")), dol.Dist(np.arange(1), torch.ones((2, 1), device="cuda"))
+    prov = dol.Prov(dol.DTKP, 2, torch.full((2, 3), 0.5, device="cuda"), None)
+    pa = dol.Dist.empty(np.arange(n), 2, k=2)
+    dol.dtkp_init(pa, np.zeros(n, np.int32), prov)
+    calls = (lambda out: dol.apply2(a, one, f, None, out), lambda out: dol.dtkp_apply2_input(pa, np.array([1], np.int32), f, prov, out))
+    for call in calls:
+        call(dol.Dist.empty(f.out_syms, 2, k=2))
+        for at in {0, n // 2, n - 1}:
+            ids = f.out_syms.copy()
+            ids[at] += 1
+            out = dol.Dist.empty(ids, 2, k=2)
+            out.prob.fill_(-3.0)
+            with pytest.raises(dol.DolError) as ei:
+                call(out)
+            assert ei.value.status == 1 and "out.sym_ids[%d] = %d, the table produces %d" % (at, ids[at], f.out_syms[at]) in str(ei.value)
+            assert np.all(host(out.prob) == -3.0)
+        out = dol.Dist.empty(f.out_syms, 2, k=2)
+        out.c.sym_ids = None
+        call(out)
+
+
 def test_dtkp_general_conjunction_union_filter(dol):
     """k x k conjunction with overlapping fact sets, exclusion groups, then union and filter under DTKP."""
     B, k, n_facts = 40, 3, 12
